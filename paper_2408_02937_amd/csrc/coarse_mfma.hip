@@ -337,12 +337,19 @@ __global__ __launch_bounds__(kMfmaThreads, kVB == 2 ? 3 : 2) void k_coarse_mfma(
   }
 }
 
-// ---- refinement of the assignment: one wavefront per vector.  The smallest
-// approximate score of the row is the smallest of its tiles' minima; the
-// centroids within the error band of it (from the tiles' kept columns; from all
-// 128 columns of a tile that had more in the band than it could keep) are
-// scored in the fixed double arithmetic and the best is taken, ties to the
-// lowest index; then the next position of the list ("did = atomicAdd(nl_k, 1)").
+// ---- refinement of the assignment.  The smallest approximate score of a row is the
+// smallest of its tiles' minima; the centroids within the error band of it (from
+// the tiles' kept columns; from all 128 columns of a tile that had more in the band
+// than it could keep) are the candidates.  One candidate alone IS the nearest
+// centroid, and that is what most rows have.  Where there are more, they are scored
+// in the fixed double arithmetic and the best is taken, ties to the lowest index;
+// then the next position of the list ("did = atomicAdd(nl_k, 1)").
+// A score is a chain of d dependent double operations, and a wavefront issues every
+// one of them for all its lanes however few have a candidate: with a wavefront to a
+// row and a lane or two at work this was bound by the issue of those instructions
+// (21,845 rows of 768 dimensions: 280 us).  So a workgroup takes the digests of
+// kRefineWaves * per_wave rows first, puts the candidates of the rows that have
+// several into a list, and then scores the list, a thread to a candidate.
 __device__ inline double exact_score(const Dev &D, const float *__restrict__ y, int c) {
   // the fixed arithmetic of coarse.hip: one double FMA per dimension, dimensions in order; the
   // 16-byte loads run eight chunks ahead of the chain (a load per turn of the chain, waited for each
@@ -381,59 +388,150 @@ __device__ inline float error_band(const Dev &D, float ynorm) {
   return coarse_band(D.d, ynorm + __uint_as_float(D.ctrl->cnorm_max_bits)) * 1.01f;
 }
 
-__global__ __launch_bounds__(256) void k_assign_refine(Dev D, int64_t n, const float *__restrict__ Y,
-                                                       TileCands tc, int reserve,
-                                                       int32_t *__restrict__ assign,
-                                                       uint32_t *__restrict__ did) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int64_t i = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-  if (i >= n) return;  // uniform over the wavefront
-  const float *y = Y + i * D.d;
-  const float *tmin = tc.tmin + (size_t)i * tc.tiles;
-  float yn = 0.f, m = __builtin_inff();
-  for (int j = lane; j < D.d; j += kWave) yn = fmaf(y[j], y[j], yn);
-  for (int t = lane; t < tc.tiles; t += kWave) m = fminf(m, tmin[t]);
-  for (int o = kWave / 2; o > 0; o >>= 1) {
-    yn += __shfl_xor(yn, o);
-    m = fminf(m, __shfl_xor(m, o));
-  }
-  const float limit = m + error_band(D, yn);
+constexpr int kRefineWaves = 4, kRefineThreads = kRefineWaves * kWave;
+constexpr int kRefinePerWave = 16;    // rows a wavefront takes at most
+constexpr int kRefineRowCands = 16;   // candidates of a row up to which they go to the workgroup's list
+constexpr int kRefineRows = kRefineWaves * kRefinePerWave, kRefineList = kRefineRows * kRefineRowCands;
+
+// a score as a key: smaller is better, -0 equal to +0
+__device__ inline unsigned long long refine_key(bool l2, double s) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong((l2 ? s : -s) + 0.0);
+  return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
+}
+
+__global__ __launch_bounds__(kRefineThreads) void k_assign_refine(Dev D, int64_t n, const float *__restrict__ Y,
+                                                                  const float *__restrict__ ynorm, TileCands tc,
+                                                                  int per_wave, int reserve,
+                                                                  int32_t *__restrict__ assign,
+                                                                  uint32_t *__restrict__ did) {
+  __shared__ unsigned long long s_key[kRefineRows];  // of the rows whose candidates are listed: their best key ...
+  __shared__ int s_col[kRefineRows];                 // ... and the answer of every row
+  __shared__ int s_lcol[kRefineList];
+  __shared__ uint8_t s_lrow[kRefineList];
+  __shared__ uint32_t s_n;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int rows = kRefineWaves * per_wave;
+  const int64_t i0 = (int64_t)blockIdx.x * rows;
   const bool l2 = D.metric == 0;
-  double best_s = l2 ? __builtin_inf() : -__builtin_inf();
-  int best_c = 0x7fffffff;
-  auto offer = [&](int c) {
-    const double s = exact_score(D, y, c);
-    const bool take = s != best_s ? (l2 ? s < best_s : s > best_s) : c < best_c;
-    best_s = take ? s : best_s;
-    best_c = take ? c : best_c;
-  };
-  for (int t0 = 0; t0 < tc.tiles; t0 += kWave) {
-    const int t = t0 + lane;
-    const size_t at = (size_t)i * tc.tiles + t;
-    const bool near = t < tc.tiles && tmin[t] <= limit;
-    const uint32_t cnt = near ? tc.cnt[at] : 0u;
-    if (near && cnt <= (uint32_t)kTileCands)  // the tile kept all its columns within the band: one lane takes them
-      for (uint32_t j = 0; j < cnt; ++j)
-        if (tc.val[at * kTileCands + j] <= limit) offer(tc.col[at * kTileCands + j]);
-    // a tile with more columns in the band than it could keep: all its columns, shared out over the lanes
-    unsigned long long crowded = __ballot(near && cnt > (uint32_t)kTileCands);
-    while (crowded) {  // uniform
-      const int tt = t0 + __ffsll((long long)crowded) - 1;
-      crowded &= crowded - 1;
-      for (int c = tt * kTileN + lane; c < (tt + 1) * kTileN && c < D.nlist; c += kWave) offer(c);
+  constexpr int kNone = 0x7fffffff;
+  if (tid == 0) s_n = 0;
+  if (tid < rows) { s_key[tid] = ~0ull; s_col[tid] = kNone; }
+  __syncthreads();
+  for (int r = wave * per_wave; r < (wave + 1) * per_wave && i0 + r < n; ++r) {  // uniform over the wavefront
+    const int64_t i = i0 + r;
+    const float *tmin = tc.tmin + (size_t)i * tc.tiles;
+    float m = __builtin_inff();
+    for (int t = lane; t < tc.tiles; t += kWave) m = fminf(m, tmin[t]);
+    const float yn = ynorm[i];
+    for (int o = kWave / 2; o > 0; o >>= 1) m = fminf(m, __shfl_xor(m, o));
+    const float limit = m + error_band(D, yn);
+    // how many candidates, and whether every tile near the minimum kept all of its own
+    uint32_t total = 0;
+    bool crowded = false;
+    int first = 0;  // of a lane's candidates
+    for (int t0 = 0; t0 < tc.tiles; t0 += kWave) {
+      const int t = t0 + lane;
+      const size_t at = (size_t)i * tc.tiles + t;
+      const bool near = t < tc.tiles && tmin[t] <= limit;
+      if (__ballot(near) == 0ull) continue;  // uniform
+      const uint32_t cnt = near ? tc.cnt[at] : 0u;
+      crowded = crowded || __ballot(cnt > (uint32_t)kTileCands) != 0ull;
+      if (cnt <= (uint32_t)kTileCands)
+        for (uint32_t j = 0; j < cnt; ++j)
+          if (tc.val[at * kTileCands + j] <= limit) { ++total; first = tc.col[at * kTileCands + j]; }
+    }
+    const uint32_t mine = total;
+    for (int o = kWave / 2; o > 0; o >>= 1) total += __shfl_xor(total, o);
+    if (!crowded && total == 1) {  // uniform: nobody to compare it with
+      if (mine) s_col[r] = first;
+      continue;
+    }
+    if (!crowded && total <= (uint32_t)kRefineRowCands) {  // uniform: to the list
+      uint32_t base = 0;
+      if (lane == 0 && total) base = atomicAdd(&s_n, total);
+      base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+      uint32_t before = mine;  // candidates of the lanes in front
+      for (int o = 1; o < kWave; o <<= 1) {
+        const uint32_t x = __shfl_up(before, o);
+        if (lane >= o) before += x;
+      }
+      uint32_t to = base + before - mine;
+      for (int t = lane; mine && t < tc.tiles; t += kWave) {
+        const size_t at = (size_t)i * tc.tiles + t;
+        const uint32_t cnt = tmin[t] <= limit ? tc.cnt[at] : 0u;
+        for (uint32_t j = 0; j < cnt; ++j)
+          if (tc.val[at * kTileCands + j] <= limit) {
+            s_lcol[to] = tc.col[at * kTileCands + j];
+            s_lrow[to++] = (uint8_t)r;
+          }
+      }
+      continue;
+    }
+    // many candidates, or tiles that could not keep all of theirs: the wavefront scores them here
+    const float *y = Y + i * D.d;
+    double best_s = l2 ? __builtin_inf() : -__builtin_inf();
+    int best_c = kNone;
+    auto offer = [&](int c) {
+      const double s = exact_score(D, y, c);
+      const bool take = s != best_s ? (l2 ? s < best_s : s > best_s) : c < best_c;
+      best_s = take ? s : best_s;
+      best_c = take ? c : best_c;
+    };
+    for (int t0 = 0; t0 < tc.tiles; t0 += kWave) {
+      const int t = t0 + lane;
+      const size_t at = (size_t)i * tc.tiles + t;
+      const bool near = t < tc.tiles && tmin[t] <= limit;
+      const uint32_t cnt = near ? tc.cnt[at] : 0u;
+      if (near && cnt <= (uint32_t)kTileCands)  // the tile kept all its columns within the band: one lane takes them
+        for (uint32_t j = 0; j < cnt; ++j)
+          if (tc.val[at * kTileCands + j] <= limit) offer(tc.col[at * kTileCands + j]);
+      // a tile with more columns in the band than it could keep: all its columns, shared out over the lanes
+      unsigned long long full = __ballot(near && cnt > (uint32_t)kTileCands);
+      while (full) {  // uniform
+        const int tt = t0 + __ffsll((long long)full) - 1;
+        full &= full - 1;
+        for (int c = tt * kTileN + lane; c < (tt + 1) * kTileN && c < D.nlist; c += kWave) offer(c);
+      }
+    }
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+      const double s = __shfl_xor(best_s, o);
+      const int c = __shfl_xor(best_c, o);
+      const bool take = s != best_s ? (l2 ? s < best_s : s > best_s) : c < best_c;
+      best_s = take ? s : best_s;
+      best_c = take ? c : best_c;
+    }
+    if (lane == 0) s_col[r] = best_c;
+  }
+  __syncthreads();
+  // the listed candidates, a thread to each (a list longer than the workgroup goes round: the scores of the
+  // turns are compared through LDS, keys first, then the lowest index among the equal ones)
+  const int listed = (int)s_n;
+  constexpr int kTurns = kRefineList / kRefineThreads;
+  unsigned long long key[kTurns];
+#pragma unroll
+  for (int u = 0; u < kTurns; ++u) {
+    const int e = tid + u * kRefineThreads;
+    key[u] = ~0ull;
+    if (e < listed) {
+      const double s = exact_score(D, Y + (i0 + s_lrow[e]) * D.d, s_lcol[e]);
+      if (s == s) {  // a score that does not compare is nobody's best
+        key[u] = refine_key(l2, s);
+        atomicMin(&s_key[s_lrow[e]], key[u]);
+      }
     }
   }
-  for (int o = kWave / 2; o > 0; o >>= 1) {
-    const double s = __shfl_xor(best_s, o);
-    const int c = __shfl_xor(best_c, o);
-    const bool take = s != best_s ? (l2 ? s < best_s : s > best_s) : c < best_c;
-    best_s = take ? s : best_s;
-    best_c = take ? c : best_c;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kTurns; ++u) {
+    const int e = tid + u * kRefineThreads;
+    if (e < listed && key[u] != ~0ull && key[u] == s_key[s_lrow[e]]) atomicMin(&s_col[s_lrow[e]], s_lcol[e]);
   }
-  if (best_c == 0x7fffffff) best_c = 0;  // no score compared (a vector with a NaN): nothing was better than the first centroid
-  if (lane == 0) {
-    assign[i] = best_c;
-    if (reserve) did[i] = atomicAdd(&D.reserved_len[best_c], 1u);
+  __syncthreads();
+  if (tid < rows && i0 + tid < n) {
+    int c = s_col[tid];
+    if (c == kNone) c = 0;  // no score compared (a vector with a NaN): nothing was better than the first centroid
+    assign[i0 + tid] = c;
+    if (reserve) did[i0 + tid] = atomicAdd(&D.reserved_len[c], 1u);
   }
 }
 
@@ -478,11 +576,16 @@ void launch_coarse_tiles(const Dev &D, int64_t n, const float *Y, u32x4 *split, 
     hipLaunchKernelGGL((k_coarse_mfma<1, false>), grid, dim3(kMfmaThreads), 0, s, D, n, split, norms, nullptr, tc, nullptr, nullptr, 0);
 }
 
-void launch_assign_refine(const Dev &D, int64_t n, const float *Y, const TileCands &tc, bool reserve,
+void launch_assign_refine(const Dev &D, int64_t n, const float *Y, const float *norms, const TileCands &tc, bool reserve,
                           int32_t *assign, uint32_t *did, hipStream_t s) {
   if (n <= 0) return;
-  unsigned grid = (unsigned)((n + 3) / 4);
-  hipLaunchKernelGGL(k_assign_refine, dim3(grid), dim3(256), 0, s, D, n, Y, tc, reserve ? 1 : 0, assign, did);
+  // as many rows to a wavefront as leave four workgroups to a compute unit (a row's digest is a chain of
+  // trips to memory, so a small batch is spread as wide as it goes)
+  int64_t per = n / (1024 * kRefineWaves);
+  per = per < 1 ? 1 : per > kRefinePerWave ? kRefinePerWave : per;
+  const int64_t rows = per * kRefineWaves;
+  hipLaunchKernelGGL(k_assign_refine, dim3((unsigned)((n + rows - 1) / rows)), dim3(kRefineThreads), 0, s, D, n, Y,
+                     norms, tc, (int)per, reserve ? 1 : 0, assign, did);
 }
 
 }  // namespace rtams

@@ -388,7 +388,7 @@ void assign_round(rtams_index *ix, int64_t m, const float *Y, bool reserve, int3
     for (int64_t o = 0; o < m; o += ix->ins.tile_rows) {
       const int64_t mm = m - o < ix->ins.tile_rows ? m - o : ix->ins.tile_rows;
       launch_coarse_tiles(D, mm, Y + (size_t)o * D.d, ix->ins.ysplit, ix->ins.ynorm, ix->ins.tiles, s);
-      launch_assign_refine(D, mm, Y + (size_t)o * D.d, ix->ins.tiles, reserve, assign_out + o, ix->ins.did + o, s);
+      launch_assign_refine(D, mm, Y + (size_t)o * D.d, ix->ins.ynorm, ix->ins.tiles, reserve, assign_out + o, ix->ins.did + o, s);
     }
   } else {
     int splits = coarse_splits(D, m, ix->ins.part_cap);

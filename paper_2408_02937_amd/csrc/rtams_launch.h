@@ -145,7 +145,7 @@ void launch_coarse_mfma(const Dev &D, int64_t n, const float *Y, u32x4 *split, f
 int coarse_tiles(const Dev &D);
 void launch_coarse_tiles(const Dev &D, int64_t n, const float *Y, u32x4 *split, float *norms, const TileCands &tc,
                          hipStream_t s);
-void launch_assign_refine(const Dev &D, int64_t n, const float *Y, const TileCands &tc, bool reserve,
+void launch_assign_refine(const Dev &D, int64_t n, const float *Y, const float *norms, const TileCands &tc, bool reserve,
                           int32_t *assign, uint32_t *did, hipStream_t s);
 
 // insert.hip -----------------------------------------------------------------
