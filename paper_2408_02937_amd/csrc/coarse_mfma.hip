@@ -3,146 +3,268 @@
 // query batches against many centroids): approximate scores of every (vector,
 // centroid) pair.
 //
-// The contraction runs on the bf16 matrix instruction, which is sixteen times
-// as fast as the fp32 one, on operands split in two: x = hi + lo + r with
-// hi = bf16(x), lo = bf16(x - hi), |r| <= 2^-16 |x|.  Three products,
-// hi hi + hi lo + lo hi (each exact in fp32, accumulated in fp32), leave out
-// lo lo and the two r terms: at most 3.02 * 2^-16 |x c| per coordinate.  The
-// centroids are split once, when they are set; the vectors of a batch by a
-// small kernel in front of the contraction, which then only copies 16-byte
-// operands from memory to LDS to the matrix cores.
-//
 // The approximate scores only FILTER.  Which list a vector joins and which
 // lists a query probes are decided by the fixed double-precision arithmetic of
 // coarse.hip on the few centroids the filter cannot tell apart (refinement
-// kernels below and in probe.hip), so the decisions stay bit-exact:
-//   approx(i, c) = |c|^2 - 2 <y_i, c>   (L2; |y_i|^2 is the same for every c)
-//   approx(i, c) = - <y_i, c>           (IP)            smaller is better
-// and |approx - exact| <= E_i = (4 (d + 4) 2^-24 + 4 * 2^-16) (|y_i|^2 + max_c |c|^2):
-// with sum_j |y_j c_j| <= (|y|^2 + |c|^2) / 2, the split costs 3.02 * 2^-16 of
-// that sum twice over (the factor 2 of the L2 form), the 3 d exact products
-// added in fp32 in any order (3.05 d) 2^-24 of it twice over, and the rounding
-// of |c|^2 and of the final combination 3 * 2^-24 (|y|^2 + |c|^2).  If m is the
-// smallest approximate score of row i, the exact winner lies among the centroids
-// with approx <= m + 2 E_i (coarse_band() in rtams_launch.h is that 2 E_i).
+// kernels below and in probe.hip), so the decisions stay bit-exact.
+//
+// One product of halves is enough for that.  Let mu be the mean of the centroids,
+// c' = c - mu, y' = y - mu (each a rounded fp32 subtraction), and h(x) the value of
+// x as a half under a power-of-two scale (one for all centroids, one per vector;
+// what would be a subnormal half becomes zero).  Up to a term that is the same for
+// every centroid the score of (y, c) is, smaller is better,
+//   b_c - g <y', c'>,   g = 2, b_c = |c'|^2 (L2)      g = 1, b_c = -<mu, c'> (IP)
+// and what the kernel computes is b_c - g <h(y'), h(c')>: products of two halves are
+// exact in fp32 and are accumulated in fp32.  With r(x) = |x - h(x)|, which is
+// COMPUTED (per vector, and the largest over the centroids) and not assumed, n(x) = |x|:
+//   |approx - exact| <= E = g (r(y') n_c + (n(y') + r(y')) r_c + d 2^-23 n_h(y) n_h(c))
+//                          + 2^-22 (max |b_c| + g n(y') n_c + m)
+// the first two terms by Cauchy and Schwarz, the third for d additions in any order
+// (2^-23: an addition may round either way), the last for the roundings of b_c, of the
+// final combination and of the two subtractions (m = (n(y') + n_c)^2 for L2,
+// n_c (|mu| + 2 n(y')) for IP).  If t is the smallest approximate score of a row, the
+// exact winner lies among the centroids with approx <= t + 2 E.  Byte-valued data is
+// exact in a half; for real-valued data r is about 2^-12.3 of the norm, and one or two
+// centroids of thousands lie within the band.  Without the centring the band would
+// grow with the distance of the data from the origin, which decides nothing.
+// (What this replaces: three products of bf16 pairs, a band of 2^-14 of the squared
+// norms, three times the matrix instructions and twice the operand bytes: 324 us for
+// 13,107 x 16,384 x 256, 728 us for 21,845 x 8,192 x 768.)
+// Vectors or centroids whose band is not finite (infinities, overflow) are scored
+// exactly against every centroid; a vector with a NaN compares with nothing and goes
+// to the first list, as it does in the exact arithmetic.
 //
 // For a search the whole score matrix is written (probe selection needs the
 // nprobe-th smallest of a row).  For an assignment it is not: each workgroup
-// reduces its 128 x 128 tile on the spot to, per row, the tile's smallest score
-// and the (up to kTileCands) columns within the band of it; the refinement reads
-// those few bytes per (row, tile) instead of the matrix, twice.
+// reduces its tile on the spot to, per row, the tile's smallest score and the (up to
+// kTileCands) columns within the band of it; the refinement reads those few bytes
+// per (row, tile) instead of the matrix, twice.
 #include "rtams_launch.h"
 
 namespace rtams {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
+typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
 
-constexpr int kMfmaThreads = 256;  // 4 wavefronts: 2 (rows) x 2 (columns), 64 x 64 results each
-#ifndef RTAMS_COARSE_VB
-#define RTAMS_COARSE_VB 2
-#endif
-// 32-vector blocks per wavefront: 2 (64 x 64 scores, 3 wavefronts per SIMD) or 4 (64 x 128 scores, a quarter
-// less LDS traffic per matrix instruction, 2 wavefronts per SIMD; measured: no faster, 28.0 against 28.8 M
-// vectors/s in a bulk load of 20 M x 256 over 16,384 centroids)
-constexpr int kVB = RTAMS_COARSE_VB;
-constexpr int kTileM = 2 * kVB * 32, kTileN = 128, kTileK = 32;  // vectors, centroids, coordinates per step
-constexpr int kVH = kTileM / 64;    // 64-row portions of the vectors a thread stages
-// an operand row in LDS: the tile's 4 groups of 8 bf16 (16 bytes each), group g of row r at place
-// g ^ ((r >> 1) & 3) of the row's 4: the 8 rows that neighbouring lanes read or write then cover all
-// 32 banks once, with no padding
-constexpr int kRowBytes = (kTileK / 8) * 16;
-__device__ inline int lds_place(int row, int g) { return row * kRowBytes + ((g ^ ((row >> 1) & 3)) * 16); }
+constexpr int kMfmaThreads = 256;  // 4 wavefronts: 2 (vectors) x 2 (centroids)
+constexpr int kTileM = 128;        // vectors of a tile: 64 to a wavefront
+constexpr int kTileK = 32;         // coordinates per step
 constexpr int kXcds = 8;  // workgroups go to the chip's 8 dies (each with its own L2) in turn
 
-// the two bf16 halves of a pair of floats, packed as the matrix instruction wants them
-__device__ inline uint32_t pack_bf16(float a, float b) {
-  bf16x2 p;
-  p[0] = (__bf16)a;
-  p[1] = (__bf16)b;  // round to nearest even
+// Operands in memory lie as the tiles are read: blocks of 16 rows x 32 coordinates, 1 KiB each, the steps of a
+// block of rows one after the other.  Inside a block row r has four 16-byte places, and group g of 8 coordinates
+// is at place g ^ ((r >> 1) & 3): the 8 rows that neighbouring lanes read from LDS then cover all 32 banks once,
+// with no padding, and a copy of a block to LDS is 1 KiB in order.
+__device__ inline size_t operand_at(int64_t row, int g, int steps) {
+  return ((size_t)(row >> 4) * steps + (g >> 2)) * 64 + (size_t)(row & 15) * 4 + ((g & 3) ^ (((int)row >> 1) & 3));
+}
+
+__device__ inline uint32_t pack_halves_flushed(float a, float b) {  // nearest even; subnormal halves become zero
+  halfx2 p;
+  p[0] = (_Float16)(fabsf(a) < 6.103515625e-05f ? 0.f : a);
+  p[1] = (_Float16)(fabsf(b) < 6.103515625e-05f ? 0.f : b);
   return __builtin_bit_cast(uint32_t, p);
 }
-__device__ inline void split_pair(float a, float b, uint32_t &hi, uint32_t &lo) {
-  hi = pack_bf16(a, b);
-  lo = pack_bf16(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));  // the differences are exact
+// power of two that brings `top` (the largest magnitude of a row) into 2^13 .. 2^14, as far as a float can
+__device__ inline float half_scale(float top) {
+  if (!(top > 0.f) || !(top < __builtin_inff())) return 1.f;
+  const int e = (int)((__float_as_uint(top) >> 23) & 255u) - 127;  // (a subnormal float counts as 2^-127)
+  int s = 13 - e;
+  s = s > 100 ? 100 : s < -114 ? -114 : s;
+  return __uint_as_float((uint32_t)(s + 127) << 23);
 }
-__device__ inline void split_eight(const float4 &u, const float4 &v, u32x4 &hi, u32x4 &lo) {
-  uint32_t h[4], l[4];
-  split_pair(u.x, u.y, h[0], l[0]);
-  split_pair(u.z, u.w, h[1], l[1]);
-  split_pair(v.x, v.y, h[2], l[2]);
-  split_pair(v.z, v.w, h[3], l[3]);
-  hi = u32x4{h[0], h[1], h[2], h[3]};
-  lo = u32x4{l[0], l[1], l[2], l[3]};
+// 8 scaled coordinates -> 8 halves; adds their squares and the squares of what the halves leave out
+__device__ inline u32x4 halves_of(const float *x, float &nsq, float &rsq) {
+  u32x4 out;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const float a = x[2 * j], b = x[2 * j + 1];
+    const uint32_t packed = pack_halves_flushed(a, b);
+    const halfx2 h = __builtin_bit_cast(halfx2, packed);
+    out[j] = packed;
+    const float ra = a - (float)h[0], rb = b - (float)h[1];  // exact
+    nsq = fmaf(a, a, nsq); nsq = fmaf(b, b, nsq);
+    rsq = fmaf(ra, ra, rsq); rsq = fmaf(rb, rb, rsq);
+  }
+  return out;
 }
-
-// ---- once per set_centroids: squared norms (fp32) with their maximum, and the
-// centroids' split form, per centroid and group of 8 coordinates 16 bytes of hi
-// halves then 16 bytes of lo halves (coordinates past d are zero)
-__global__ __launch_bounds__(256) void k_centroid_norms(Dev D) {
-  int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= D.nlist) return;
-  double acc = 0.0;
-  const float *row = D.centroids + (size_t)c * D.d;
-  for (int j = 0; j < D.d; ++j) acc = __builtin_fma((double)row[j], (double)row[j], acc);
-  float n = (float)acc;
-  D.cnorm[c] = n;
-  atomicMax(&D.ctrl->cnorm_max_bits, __float_as_uint(n));  // non-negative floats order like their bits
+// coordinates 8 g .. 8 g + 7 of a row less the mean; zero past d
+__device__ inline void centred_group(const Dev &D, const float *row, int g, float *x) {
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int j = g * 8 + q * 4;
+    const float4 u = j < D.d ? *reinterpret_cast<const float4 *>(row + j) : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float4 m = j < D.d ? *reinterpret_cast<const float4 *>(D.cmean + j) : make_float4(0.f, 0.f, 0.f, 0.f);
+    x[4 * q] = u.x - m.x; x[4 * q + 1] = u.y - m.y; x[4 * q + 2] = u.z - m.z; x[4 * q + 3] = u.w - m.w;
+  }
 }
-
-// bf16 halves of rows of d floats: per row and group of 8 coordinates 16 bytes of hi halves then 16 bytes
-// of lo halves; coordinates past d are zero, up to whole steps of 32 (D.dgroups groups)
-__device__ inline void split_group(const Dev &D, const float *row, int g, u32x4 *out) {
-  float4 u = make_float4(0.f, 0.f, 0.f, 0.f), v = u;
-  if (g * 8 < D.d) u = *reinterpret_cast<const float4 *>(row + g * 8);
-  if (g * 8 + 4 < D.d) v = *reinterpret_cast<const float4 *>(row + g * 8 + 4);
-  u32x4 hi, lo;
-  split_eight(u, v, hi, lo);
-  out[2 * g] = hi;
-  out[2 * g + 1] = lo;
-}
-
-__global__ __launch_bounds__(256) void k_centroid_split(Dev D) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (int64_t)D.nlist * D.dgroups) return;
-  const int c = (int)(t / D.dgroups), g = (int)(t % D.dgroups);
-  split_group(D, D.centroids + (size_t)c * D.d, g, D.csplit + (size_t)c * D.dgroups * 2);
+__device__ inline float group_top(const float *x) {
+  float t = 0.f;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) t = fmaxf(t, fabsf(x[j]));
+  return t;
 }
 
-// one wavefront per vector of a batch: its split form and, if asked for, its squared norm
-__global__ __launch_bounds__(256) void k_split_rows(Dev D, int64_t n, const float *__restrict__ Y,
-                                                    u32x4 *__restrict__ split, float *__restrict__ norms) {
+// ---- once per set_centroids, behind the transposed copy: the mean of the centroids (a workgroup per chunk of 4
+// coordinates), their largest centred magnitude, then bias, halves and the largest norms
+__global__ __launch_bounds__(256) void k_centroid_mean(Dev D) {
+  __shared__ double s_sum[4][4];
+  const int j = blockIdx.x, lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  if (j == 0 && threadIdx.x == 0) D.ctrl->cen = CentroidStats{};
+  const float4 *col = reinterpret_cast<const float4 *>(D.centroids_t) + (size_t)j * D.nlist;
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int c = threadIdx.x; c < D.nlist; c += 256) {
+    const float4 v = col[c];
+    a[0] += (double)v.x; a[1] += (double)v.y; a[2] += (double)v.z; a[3] += (double)v.w;
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    for (int o = kWave / 2; o > 0; o >>= 1) a[u] += __shfl_xor(a[u], o);
+    if (lane == 0) s_sum[u][wave] = a[u];
+  }
+  __syncthreads();
+  if (threadIdx.x < 4) {
+    const double *p = s_sum[threadIdx.x];
+    D.cmean[4 * j + threadIdx.x] = (float)((p[0] + p[1] + p[2] + p[3]) / (double)D.nlist);
+  }
+}
+
+// largest of a value per wavefront over the workgroup of 4, into a word of float bits (non-negative floats order
+// like their bits).  A few hundred workgroups walk the centroids: an atomic per centroid on one word took 0.2 ms for
+// 16,384 of them.
+__device__ inline void wg_atomic_max(float v, float *lds4, uint32_t *word) {
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  for (int o = kWave / 2; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+  __syncthreads();
+  if (lane == 0) lds4[wave] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) atomicMax(word, __float_as_uint(fmaxf(fmaxf(lds4[0], lds4[1]), fmaxf(lds4[2], lds4[3]))));
+}
+
+// a wavefront per centroid, in turns
+__global__ __launch_bounds__(256) void k_centroid_top(Dev D) {
+  __shared__ float s_max[4];
   const int lane = threadIdx.x & (kWave - 1);
-  const int64_t i = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-  if (i >= n) return;  // uniform over the wavefront
-  const float *row = Y + i * D.d;
-  for (int g = lane; g < D.dgroups; g += kWave) split_group(D, row, g, split + (size_t)i * D.dgroups * 2);
-  if (!norms) return;
-  float nsq = 0.f;
-  for (int j = lane; j < D.d; j += kWave) nsq = fmaf(row[j], row[j], nsq);
-  for (int o = kWave / 2; o > 0; o >>= 1) nsq += __shfl_xor(nsq, o);
-  if (lane == 0) norms[i] = nsq;
+  float top = 0.f, bad = 0.f;
+  for (int c = blockIdx.x * 4 + threadIdx.x / kWave; c < D.nlist; c += gridDim.x * 4) {
+    const float *row = D.centroids + (size_t)c * D.d;
+    for (int j = lane; j < D.d; j += kWave) {
+      const float m = D.cmean[j], v = fabsf(row[j] - m);
+      if (!(v < 1e17f) || !(fabsf(m) < 1e17f)) bad = 1.f;  // (squares and products of these, summed, stay finite)
+      top = fmaxf(top, v);
+    }
+  }
+  wg_atomic_max(top, s_max, &D.ctrl->cen.top_bits);
+  wg_atomic_max(bad, s_max, &D.ctrl->cen.bad);
 }
 
-// ---- approx[i][c] for i < n, c < nlist
-template <int METRIC, bool MATRIX>
-__global__ __launch_bounds__(kMfmaThreads, kVB == 2 ? 3 : 2) void k_coarse_mfma(Dev D, int64_t n, const u32x4 *__restrict__ ysplit,
-                                                              const float *__restrict__ ynorm,
-                                                              float *__restrict__ approx, TileCands tc,
+__global__ __launch_bounds__(256) void k_centroid_halves(Dev D) {
+  __shared__ float s_max[4];
+  const int lane = threadIdx.x & (kWave - 1);
+  CentroidStats &st = D.ctrl->cen;
+  const float scale = half_scale(__uint_as_float(st.top_bits));
+  const bool bad = st.bad != 0u;  // no centroid is told apart by the filter then
+  float top_n = 0.f, top_r = 0.f, top_b = 0.f;
+  for (int c = blockIdx.x * 4 + threadIdx.x / kWave; c < D.nlist; c += gridDim.x * 4) {  // uniform over the wavefront
+    const float *row = D.centroids + (size_t)c * D.d;
+    float nsq = 0.f, rsq = 0.f;
+    double bias = 0.0;
+    for (int g = lane; g < D.dgroups; g += kWave) {
+      float x[8];
+      centred_group(D, row, g, x);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const double m = g * 8 + j < D.d ? (double)D.cmean[g * 8 + j] : 0.0;
+        bias = D.metric == 0 ? __builtin_fma((double)x[j], (double)x[j], bias) : __builtin_fma(-m, (double)x[j], bias);
+        x[j] = bad ? 0.f : x[j] * scale;
+      }
+      D.chalf[operand_at(c, g, D.dgroups / 4)] = halves_of(x, nsq, rsq);
+    }
+    for (int o = kWave / 2; o > 0; o >>= 1) { nsq += __shfl_xor(nsq, o); rsq += __shfl_xor(rsq, o); bias += __shfl_xor(bias, o); }
+    const float b = bad ? 0.f : (float)bias;
+    if (lane == 0) D.cbias[c] = b;
+    top_n = fmaxf(top_n, sqrtf(nsq)); top_r = fmaxf(top_r, sqrtf(rsq)); top_b = fmaxf(top_b, fabsf(b));
+  }
+  wg_atomic_max(top_n, s_max, &st.norm_bits);
+  wg_atomic_max(top_r, s_max, &st.res_bits);
+  wg_atomic_max(top_b, s_max, &st.bias_bits);
+  if (blockIdx.x == 0 && threadIdx.x < kWave) {
+    double m = 0.0;
+    for (int j = lane; j < D.d; j += kWave) m = __builtin_fma((double)D.cmean[j], (double)D.cmean[j], m);
+    for (int o = kWave / 2; o > 0; o >>= 1) m += __shfl_xor(m, o);
+    if (lane == 0) st.mean_norm = (float)__builtin_sqrt(m);
+  }
+}
+
+// ---- the vectors of a batch: halves, and per row what turns an accumulated product into a score (g over the two
+// scales) and the band 2 E.  `lpr` lanes of a wavefront take a row (4 .. 64, a power of two), G groups of 8
+// coordinates each, which stay in registers between the look for the largest one and the conversion.
+template <int G>
+__global__ __launch_bounds__(256) void k_half_rows(Dev D, int64_t n, const float *__restrict__ Y, int lpr,
+                                                   u32x4 *__restrict__ half, RowMeta *__restrict__ meta) {
+  const int lane = threadIdx.x & (kWave - 1), sub = lane & (lpr - 1);
+  const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / lpr;
+  const bool on = i < n;
+  const float *row = Y + (on ? i : n - 1) * D.d;
+  float x[G][8], top = 0.f;
+#pragma unroll
+  for (int t = 0; t < G; ++t) centred_group(D, row, sub + t * lpr, x[t]);  // groups past the row are past d: zero
+#pragma unroll
+  for (int t = 0; t < G; ++t) top = fmaxf(top, group_top(x[t]));
+  for (int o = lpr / 2; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
+  const float scale = half_scale(top);
+  const bool bad = !(top < __builtin_inff());
+  float nsq = 0.f, rsq = 0.f;
+#pragma unroll
+  for (int t = 0; t < G; ++t) {
+    const int g = sub + t * lpr;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[t][j] = bad && x[t][j] == x[t][j] ? 0.f : x[t][j] * scale;  // (a NaN stays one)
+    const u32x4 h = halves_of(x[t], nsq, rsq);
+    if (on && g < D.dgroups) half[operand_at(i, g, D.dgroups / 4)] = h;
+  }
+  for (int o = lpr / 2; o > 0; o >>= 1) { nsq += __shfl_xor(nsq, o); rsq += __shfl_xor(rsq, o); }
+  if (!on || sub != 0) return;
+  const CentroidStats &st = D.ctrl->cen;
+  const float iy = 1.f / scale, ic = 1.f / half_scale(__uint_as_float(st.top_bits));  // powers of two: exact
+  const float g = D.metric == 0 ? 2.f : 1.f;
+  const float ny = sqrtf(nsq), ry = sqrtf(rsq), nc = __uint_as_float(st.norm_bits), rc = __uint_as_float(st.res_bits);
+  const float s = g * iy * ic;
+  const float e = s * (ry * nc + (ny + ry) * rc + (float)D.d * 1.1920929e-7f * (ny + ry) * (nc + rc));
+  const float uy = ny * iy, uc = nc * ic;  // the norms themselves
+  const float m = D.metric == 0 ? (uy + uc) * (uy + uc) : uc * (st.mean_norm + 2.f * uy);
+  float band = 2.f * (1.01f * e + 2.3841858e-7f * 1.01f * (__uint_as_float(st.bias_bits) + s * ny * nc + m)) * 1.01f;
+  // nothing is told apart by the filter where the band says nothing: infinities, or numbers at the ends of the
+  // float range (a NaN in the vector stays out: no comparison holds for it anywhere)
+  if (bad || st.bad != 0u || !(band > 1e-28f) || !(band < 1e37f) || !(s > 1e-30f)) band = __builtin_inff();
+  meta[i] = RowMeta{s, band};
+}
+
+// ---- approximate scores of a tile of 128 vectors x 64 CA centroids; a wavefront has 64 vectors x 32 CA centroids.
+// With CA = 4 a step of 32 coordinates is 16 matrix instructions of 32 clocks to a wavefront between two barriers,
+// and the 12 operands they take are 96 of the 128 bytes a clock that LDS returns: with CA = 2, as with the 64 x 64
+// scores to a wavefront this kernel used to have, LDS would take longer than the matrix cores.  CA = 2 is for
+// batches whose wide tiles would leave compute units without a workgroup.
+// Two buffers in LDS: while one is multiplied the next step's operands are on their way to registers, and go to the
+// other buffer behind the multiplications; one barrier to a step.
+template <int CA, bool MATRIX>
+__global__ __launch_bounds__(kMfmaThreads, 2) void k_coarse_mfma(Dev D, int64_t n, const u32x4 *__restrict__ yhalf,
+                                                              const RowMeta *__restrict__ meta,
+                                                              float *__restrict__ approx, TileCands tc, int die_map,
                                                               unsigned long long *cursor_to_clear,
                                                               uint32_t *__restrict__ zero, int zero_n) {
-  __shared__ __align__(16) unsigned char s_y[2][kTileM * kRowBytes];  // vectors: hi, lo
-  __shared__ __align__(16) unsigned char s_c[2][kTileN * kRowBytes];  // centroids: hi, lo
+  constexpr int kTileN = 64 * CA;
+  constexpr int kUnitsY = kTileM * 4 / kMfmaThreads, kUnitsC = kTileN * 4 / kMfmaThreads;  // 16-byte units a thread brings per step
+  constexpr int kBuf = (kTileM + kTileN) * 4;  // units of a buffer: the vectors', then the centroids'
+  __shared__ u32x4 s_op[2][kBuf];
   __shared__ float s_min[kTileM][2];
-  __shared__ float s_cn[kTileN];  // |c|^2 of the tile's centroids (0 past the last one), read after the last barrier of the k loop
-  __shared__ float s_norm[kTileM];
+  __shared__ float s_cn[kTileN];  // bias of the tile's centroids, read after the last barrier of the k loop
   __shared__ uint32_t s_cnt[kTileM];
   __shared__ int32_t s_col[kTileM][kTileCands];
   __shared__ float s_val[kTileM][kTileCands];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int wv = wave & 1, wc = wave >> 1;  // wavefront's place in the 2 (vectors) x 2 (centroids) arrangement
-  const int d = D.d;
 
   // per-request counters of the search plan start from zero (no memset node on the stream)
   if (cursor_to_clear && blockIdx.x == 0 && tid == 0) *cursor_to_clear = 0ull;
@@ -152,131 +274,124 @@ __global__ __launch_bounds__(kMfmaThreads, kVB == 2 ? 3 : 2) void k_coarse_mfma(
   }
 
   // Which tile: consecutive workgroups land on consecutive dies, so die x takes the column tiles
-  // x, x + 8, ... and walks the row tiles with them: the split centroids of its column tiles stay in
-  // its L2 (2 MiB of 4 for 16,384 centroids of 256 dimensions) while the vectors stream through once.
-  const int col_tiles = (D.nlist + kTileN - 1) / kTileN, per_die = (col_tiles + kXcds - 1) / kXcds;
-  const int die = blockIdx.x % kXcds, turn = blockIdx.x / kXcds;
-  const int col_tile = (turn % per_die) * kXcds + die;
-  if (col_tile >= col_tiles) return;  // uniform
-  const int64_t row0 = (int64_t)(turn / per_die) * kTileM;
+  // x, x + 8, ... and walks the row tiles with them: the centroids of its column tiles stay in
+  // its L2 (1 MiB of 4 for 16,384 centroids of 256 dimensions) while the vectors stream through once.
+  // (Few column tiles: they are dealt out in turn, so that every die has its share.)
+  const int col_tiles = (D.nlist + kTileN - 1) / kTileN;
+  int col_tile;
+  int64_t row_tile;
+  if (die_map) {
+    const int per_die = (col_tiles + kXcds - 1) / kXcds;
+    const int die = blockIdx.x % kXcds, turn = blockIdx.x / kXcds;
+    col_tile = (turn % per_die) * kXcds + die;
+    if (col_tile >= col_tiles) return;  // uniform
+    row_tile = turn / per_die;
+  } else {
+    col_tile = blockIdx.x % col_tiles;
+    row_tile = blockIdx.x / col_tiles;
+  }
+  const int64_t row0 = row_tile * kTileM;
   const int col0 = col_tile * kTileN;
 
-  if (tid < kTileN) s_cn[tid] = (METRIC == 0 && col0 + tid < D.nlist) ? D.cnorm[col0 + tid] : 0.f;
+  if (tid < kTileN) s_cn[tid] = col0 + tid < D.nlist ? D.cbias[col0 + tid] : __builtin_inff();
 
-  floatx16 acc[2][kVB];
+  floatx16 acc[CA][2];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < CA; ++a)
 #pragma unroll
-    for (int b = 0; b < kVB; ++b)
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
 
-  // staging: thread t brings group t % 4 (8 consecutive k, 32 bytes of halves) of rows t / 4 and t / 4 + 64
-  // of the vectors and of the centroids into registers, one k-tile ahead: the loads of tile t + 1 are in
-  // flight while the matrix cores work on tile t out of LDS.  Rows past the last vector or centroid read
-  // the last one (their scores are dropped below); the k past d are zero in both split forms.
-  const int ld_row = tid / 4, ld_g = tid % 4;
-  const u32x4 *srcy[kVH], *srcc[2];
+  // Staging: a wavefront brings blocks of 16 rows, 1 KiB each.  Blocks past the last vector or centroid read the
+  // last one, and rows of the last block past the end hold whatever the memory holds: the scores of both are dropped.
+  const int steps = D.dgroups / 4;
+  const u32x4 *srcy[kUnitsY], *srcc[kUnitsC];
+  {
+    const int64_t last_y = (n - 1) >> 4;
+    const int last_c = (D.nlist - 1) >> 4;
 #pragma unroll
-  for (int h = 0; h < kVH; ++h) {
-    const int64_t r = row0 + ld_row + 64 * h;
-    srcy[h] = ysplit + ((size_t)(r < n ? r : n - 1) * D.dgroups + ld_g) * 2;
-  }
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int c = col0 + ld_row + 64 * h;
-    srcc[h] = D.csplit + ((size_t)(c < D.nlist ? c : D.nlist - 1) * D.dgroups + ld_g) * 2;
-  }
-  u32x4 stagey[kVH][2], stagec[2][2];  // [64-row portion][hi, lo]
-  auto fetch = [&](int k0) {
-#pragma unroll
-    for (int h = 0; h < kVH; ++h) {
-      stagey[h][0] = srcy[h][k0 / 4];
-      stagey[h][1] = srcy[h][k0 / 4 + 1];
+    for (int h = 0; h < kUnitsY; ++h) {
+      const int64_t blk = (row0 >> 4) + wave + 4 * h;
+      srcy[h] = yhalf + (size_t)(blk < last_y ? blk : last_y) * steps * 64 + lane;
     }
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      stagec[h][0] = srcc[h][k0 / 4];
-      stagec[h][1] = srcc[h][k0 / 4 + 1];
+    for (int h = 0; h < kUnitsC; ++h) {
+      const int blk = (col0 >> 4) + wave + 4 * h;
+      srcc[h] = D.chalf + (size_t)(blk < last_c ? blk : last_c) * steps * 64 + lane;
+    }
+  }
+  u32x4 stage[kUnitsY + kUnitsC];
+  auto fetch = [&](int st) {
+#pragma unroll
+    for (int h = 0; h < kUnitsY; ++h) stage[h] = srcy[h][(size_t)st * 64];
+#pragma unroll
+    for (int h = 0; h < kUnitsC; ++h) stage[kUnitsY + h] = srcc[h][(size_t)st * 64];
+  };
+  auto put = [&](u32x4 *buf) {
+#pragma unroll
+    for (int h = 0; h < kUnitsY + kUnitsC; ++h) buf[h * kMfmaThreads + tid] = stage[h];
+  };
+  // operands of v_mfma_f32_32x32x16_f16: lane l supplies 8 consecutive k, the group l / 32 of the
+  // 16, of row (or column) l % 32; vectors and centroids use the same split of k over the lanes.
+  // The centroids are the rows of the product and the vectors its columns, so that a lane ends up
+  // with 16 CA scores of ONE vector per block column and the smallest of them is found in registers.
+  auto multiply = [&](const u32x4 *buf) {
+#pragma unroll
+    for (int kk = 0; kk < kTileK / 16; ++kk) {
+      const int row = lane & 31;  // (block rows start at multiples of 32: same place)
+      const int at = row * 4 + ((kk * 2 + (lane >> 5)) ^ ((row >> 1) & 3));
+      halfx8 c[CA], y[2];
+#pragma unroll
+      for (int a = 0; a < CA; ++a)
+        c[a] = __builtin_bit_cast(halfx8, buf[(kTileM + wc * 32 * CA + a * 32) * 4 + at]);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) y[b] = __builtin_bit_cast(halfx8, buf[(wv * 64 + b * 32) * 4 + at]);
+#pragma unroll
+      for (int a = 0; a < CA; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(c[a], y[b], acc[a][b], 0, 0, 0);
     }
   };
   fetch(0);
-  for (int k0 = 0; k0 < d; k0 += kTileK) {
-#pragma unroll
-    for (int h = 0; h < kVH; ++h) {
-      const int at = lds_place(ld_row + 64 * h, ld_g);
-      *reinterpret_cast<u32x4 *>(&s_y[0][at]) = stagey[h][0];
-      *reinterpret_cast<u32x4 *>(&s_y[1][at]) = stagey[h][1];
+  put(s_op[0]);
+  if (steps > 1) fetch(1);
+  for (int st = 0; st < steps; ++st) {
+    __syncthreads();  // this step's operands are in LDS, and everybody is through with the other buffer
+    multiply(s_op[st & 1]);
+    if (st + 1 < steps) {
+      put(s_op[(st + 1) & 1]);
+      if (st + 2 < steps) fetch(st + 2);
     }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int at = lds_place(ld_row + 64 * h, ld_g);
-      *reinterpret_cast<u32x4 *>(&s_c[0][at]) = stagec[h][0];
-      *reinterpret_cast<u32x4 *>(&s_c[1][at]) = stagec[h][1];
-    }
-    __syncthreads();
-    if (k0 + kTileK < d) fetch(k0 + kTileK);  // uniform
-    // operands of v_mfma_f32_32x32x16_bf16: lane l supplies 8 consecutive k, the group l / 32 of the
-    // 16, of row (or column) l % 32; vectors and centroids use the same split of k over the lanes.
-    // The centroids are the rows of the product and the vectors its columns, so that a lane ends up
-    // with 32 scores of ONE vector per block column and the smallest of them is found in registers.
-#pragma unroll
-    for (int kk = 0; kk < kTileK / 16; ++kk) {
-      const int off = lds_place(lane & 31, kk * 2 + (lane >> 5));  // (block rows start at multiples of 32: same place)
-      bf16x8 ch[2], cl[2], yh[kVB], yl[kVB];
-#pragma unroll
-      for (int a = 0; a < 2; ++a) {
-        const int at = (wc * 64 + a * 32) * kRowBytes + off;
-        ch[a] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(&s_c[0][at]));
-        cl[a] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(&s_c[1][at]));
-      }
-#pragma unroll
-      for (int b = 0; b < kVB; ++b) {
-        const int at = (wv * kVB * 32 + b * 32) * kRowBytes + off;
-        yh[b] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(&s_y[0][at]));
-        yl[b] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(&s_y[1][at]));
-      }
-      // the small products first; every accumulator is touched once in 2 kVB instructions
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < kVB; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cl[a], yh[b], acc[a][b], 0, 0, 0);
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < kVB; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ch[a], yl[b], acc[a][b], 0, 0, 0);
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < kVB; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ch[a], yh[b], acc[a][b], 0, 0, 0);
-    }
-    __syncthreads();
   }
 
   // result layout of a 32 x 32 block: register r of lane l holds row (r / 4) * 8 + (l / 32) * 4 + r % 4 (a
   // centroid), column l % 32 (a vector); acc[a][b] is the block of centroid block a and vector block b
-  auto centroid_of = [&](int a, int r) { return col0 + wc * 64 + a * 32 + (r / 4) * 8 + (lane >> 5) * 4 + (r % 4); };
-  // scores in place: |c|^2 - 2 <y, c> or - <y, c>; centroids past the last one score +inf
+  auto centroid_of = [&](int a, int r) { return col0 + wc * 32 * CA + a * 32 + (r / 4) * 8 + (lane >> 5) * 4 + (r % 4); };
+  RowMeta mt[2];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int b = 0; b < 2; ++b) {
+    const int64_t i = row0 + wv * 64 + b * 32 + (lane & 31);
+    mt[b] = meta[i < n ? i : n - 1];
+  }
+  // scores in place; centroids past the last one score +inf (their bias; their halves are finite), all others less
+#pragma unroll
+  for (int a = 0; a < CA; ++a)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int c = centroid_of(a, r);
-      const bool real = c < D.nlist;
-      const float cn = s_cn[c - col0];
+      const float cn = s_cn[wc * 32 * CA + a * 32 + (r / 4) * 8 + (lane >> 5) * 4 + (r % 4)];
 #pragma unroll
-      for (int b = 0; b < kVB; ++b)
-        acc[a][b][r] = real ? (METRIC == 0 ? cn - 2.f * acc[a][b][r] : -acc[a][b][r]) : __builtin_inff();
+      for (int b = 0; b < 2; ++b) acc[a][b][r] = fmaf(-mt[b].scale, acc[a][b][r], cn);
     }
   if (MATRIX) {
     const bool quads = D.nlist % 4 == 0;  // a lane's 4 consecutive centroids of one vector go out as one 16-byte store
 #pragma unroll
-    for (int b = 0; b < kVB; ++b) {
-      const int64_t i = row0 + wv * kVB * 32 + b * 32 + (lane & 31);
+    for (int b = 0; b < 2; ++b) {
+      const int64_t i = row0 + wv * 64 + b * 32 + (lane & 31);
       if (i >= n) continue;
       float *out = approx + (size_t)i * D.nlist;
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+      for (int a = 0; a < CA; ++a)
 #pragma unroll
         for (int r = 0; r < 16; r += 4) {
           const int c = centroid_of(a, r);
@@ -292,31 +407,29 @@ __global__ __launch_bounds__(kMfmaThreads, kVB == 2 ? 3 : 2) void k_coarse_mfma(
     return;
   }
   // The tile is reduced here: per vector its smallest score and the centroids within the band of it.
-  if (tid < kTileM) s_norm[tid] = ynorm[row0 + tid < n ? row0 + tid : n - 1];
   if (tid < kTileM) s_cnt[tid] = 0u;
 #pragma unroll
-  for (int b = 0; b < kVB; ++b) {  // smallest score of this lane's vector over the wavefront's 64 centroids
+  for (int b = 0; b < 2; ++b) {  // smallest score of this lane's vector over the wavefront's centroids
     float v = __builtin_inff();
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < CA; ++a)
 #pragma unroll
       for (int r = 0; r < 16; ++r) v = fminf(v, acc[a][b][r]);
     v = fminf(v, __shfl_xor(v, 32));  // the other half of the lanes holds the other centroids of the same vector
-    if (lane < 32) s_min[wv * kVB * 32 + b * 32 + lane][wc] = v;
+    if (lane < 32) s_min[wv * 64 + b * 32 + lane][wc] = v;
   }
   __syncthreads();
-  const float cmax = __uint_as_float(D.ctrl->cnorm_max_bits);
 #pragma unroll
-  for (int b = 0; b < kVB; ++b) {
-    const int row = wv * kVB * 32 + b * 32 + (lane & 31);
-    // the smallest of the tile plus 2 E of the vector, a little wider than the refinement's (1.02 against
-    // 1.01), so that what the refinement asks for is certainly among what is kept here
-    const float limit = fminf(s_min[row][0], s_min[row][1]) + coarse_band(D.d, s_norm[row] + cmax) * 1.02f;
+  for (int b = 0; b < 2; ++b) {
+    const int row = wv * 64 + b * 32 + (lane & 31);
+    // the smallest of the tile plus the band of the vector, a little wider than the refinement's, so that
+    // what the refinement asks for is certainly among what is kept here
+    const float limit = fminf(s_min[row][0], s_min[row][1]) + mt[b].band * 1.01f;
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < CA; ++a)
 #pragma unroll
       for (int r = 0; r < 16; ++r)
-        if (acc[a][b][r] <= limit && centroid_of(a, r) < D.nlist) {
+        if (acc[a][b][r] <= limit && acc[a][b][r] < __builtin_inff()) {
           const uint32_t slot = atomicAdd(&s_cnt[row], 1u);
           if (slot < (uint32_t)kTileCands) {
             s_col[row][slot] = centroid_of(a, r);
@@ -339,7 +452,7 @@ __global__ __launch_bounds__(kMfmaThreads, kVB == 2 ? 3 : 2) void k_coarse_mfma(
 
 // ---- refinement of the assignment.  The smallest approximate score of a row is the
 // smallest of its tiles' minima; the centroids within the error band of it (from
-// the tiles' kept columns; from all 128 columns of a tile that had more in the band
+// the tiles' kept columns; from all columns of a tile that had more in the band
 // than it could keep) are the candidates.  One candidate alone IS the nearest
 // centroid, and that is what most rows have.  Where there are more, they are scored
 // in the fixed double arithmetic and the best is taken, ties to the lowest index;
@@ -347,8 +460,8 @@ __global__ __launch_bounds__(kMfmaThreads, kVB == 2 ? 3 : 2) void k_coarse_mfma(
 // A score is a chain of d dependent double operations, and a wavefront issues every
 // one of them for all its lanes however few have a candidate: with a wavefront to a
 // row and a lane or two at work this was bound by the issue of those instructions
-// (21,845 rows of 768 dimensions: 280 us).  So a workgroup takes the digests of
-// kRefineWaves * per_wave rows first, puts the candidates of the rows that have
+// (21,845 rows of 768 dimensions: 280 us).  So a workgroup reads the digests of up to
+// 64 rows first, a few lanes to a row, puts the candidates of the rows that have
 // several into a list, and then scores the list, a thread to a candidate.
 __device__ inline double exact_score(const Dev &D, const float *__restrict__ y, int c) {
   // the fixed arithmetic of coarse.hip: one double FMA per dimension, dimensions in order; the
@@ -383,15 +496,10 @@ __device__ inline double exact_score(const Dev &D, const float *__restrict__ y, 
   return acc;
 }
 
-__device__ inline float error_band(const Dev &D, float ynorm) {
-  // 2 E_i; the norm itself carries a relative error of at most d 2^-24, covered by the factor 1.01
-  return coarse_band(D.d, ynorm + __uint_as_float(D.ctrl->cnorm_max_bits)) * 1.01f;
-}
-
-constexpr int kRefineWaves = 4, kRefineThreads = kRefineWaves * kWave;
-constexpr int kRefinePerWave = 16;    // rows a wavefront takes at most
+constexpr int kRefineThreads = 256;
+constexpr int kRefineRows = 64;       // rows of a workgroup at most
 constexpr int kRefineRowCands = 16;   // candidates of a row up to which they go to the workgroup's list
-constexpr int kRefineRows = kRefineWaves * kRefinePerWave, kRefineList = kRefineRows * kRefineRowCands;
+constexpr int kRefineList = kRefineRows * kRefineRowCands;
 
 // a score as a key: smaller is better, -0 equal to +0
 __device__ inline unsigned long long refine_key(bool l2, double s) {
@@ -400,75 +508,83 @@ __device__ inline unsigned long long refine_key(bool l2, double s) {
 }
 
 __global__ __launch_bounds__(kRefineThreads) void k_assign_refine(Dev D, int64_t n, const float *__restrict__ Y,
-                                                                  const float *__restrict__ ynorm, TileCands tc,
-                                                                  int per_wave, int reserve,
+                                                                  const RowMeta *__restrict__ meta, TileCands tc,
+                                                                  int rows, int lpr, int reserve,
                                                                   int32_t *__restrict__ assign,
                                                                   uint32_t *__restrict__ did) {
   __shared__ unsigned long long s_key[kRefineRows];  // of the rows whose candidates are listed: their best key ...
   __shared__ int s_col[kRefineRows];                 // ... and the answer of every row
+  __shared__ float s_limit[kRefineRows];
+  __shared__ int s_hard[kRefineRows];                // rows with more candidates than are listed
   __shared__ int s_lcol[kRefineList];
   __shared__ uint8_t s_lrow[kRefineList];
-  __shared__ uint32_t s_n;
+  __shared__ uint32_t s_n, s_hards;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  const int rows = kRefineWaves * per_wave;
   const int64_t i0 = (int64_t)blockIdx.x * rows;
   const bool l2 = D.metric == 0;
   constexpr int kNone = 0x7fffffff;
-  if (tid == 0) s_n = 0;
+  if (tid == 0) { s_n = 0; s_hards = 0; }
   if (tid < rows) { s_key[tid] = ~0ull; s_col[tid] = kNone; }
   __syncthreads();
-  for (int r = wave * per_wave; r < (wave + 1) * per_wave && i0 + r < n; ++r) {  // uniform over the wavefront
+  const int sub = tid & (lpr - 1);
+  for (int r0 = 0; r0 < rows; r0 += kRefineThreads / lpr) {  // uniform; the lanes of a row stay together
+    const int r = r0 + tid / lpr;
     const int64_t i = i0 + r;
-    const float *tmin = tc.tmin + (size_t)i * tc.tiles;
+    const bool on = r < rows && i < n;
+    const size_t base = (size_t)(on ? i : n - 1) * tc.tiles;
+    const float *tmin = tc.tmin + base;
     float m = __builtin_inff();
-    for (int t = lane; t < tc.tiles; t += kWave) m = fminf(m, tmin[t]);
-    const float yn = ynorm[i];
-    for (int o = kWave / 2; o > 0; o >>= 1) m = fminf(m, __shfl_xor(m, o));
-    const float limit = m + error_band(D, yn);
+    for (int t = sub; t < tc.tiles; t += lpr) m = fminf(m, tmin[t]);
+    const float band = meta[on ? i : n - 1].band;
+    for (int o = lpr / 2; o > 0; o >>= 1) m = fminf(m, __shfl_xor(m, o));
+    const float limit = m + band;
     // how many candidates, and whether every tile near the minimum kept all of its own
-    uint32_t total = 0;
-    bool crowded = false;
-    int first = 0;  // of a lane's candidates
-    for (int t0 = 0; t0 < tc.tiles; t0 += kWave) {
-      const int t = t0 + lane;
-      const size_t at = (size_t)i * tc.tiles + t;
-      const bool near = t < tc.tiles && tmin[t] <= limit;
-      if (__ballot(near) == 0ull) continue;  // uniform
-      const uint32_t cnt = near ? tc.cnt[at] : 0u;
-      crowded = crowded || __ballot(cnt > (uint32_t)kTileCands) != 0ull;
-      if (cnt <= (uint32_t)kTileCands)
-        for (uint32_t j = 0; j < cnt; ++j)
-          if (tc.val[at * kTileCands + j] <= limit) { ++total; first = tc.col[at * kTileCands + j]; }
+    uint32_t mine = 0, crowded = 0;
+    int first = 0;  // one of the lane's candidates
+    for (int t = sub; t < tc.tiles; t += lpr) {
+      if (!(tmin[t] <= limit)) continue;
+      const uint32_t cnt = tc.cnt[base + t];
+      if (cnt > (uint32_t)kTileCands) crowded = 1u << 16;
+      for (uint32_t j = 0; j < min(cnt, (uint32_t)kTileCands); ++j)
+        if (tc.val[(base + t) * kTileCands + j] <= limit) { ++mine; first = tc.col[(base + t) * kTileCands + j]; }
     }
-    const uint32_t mine = total;
-    for (int o = kWave / 2; o > 0; o >>= 1) total += __shfl_xor(total, o);
-    if (!crowded && total == 1) {  // uniform: nobody to compare it with
+    uint32_t upto = min(mine, 255u) | crowded;  // running sum over the row's lanes: candidates below, crowded tiles above
+    for (int o = 1; o < lpr; o <<= 1) {
+      const uint32_t x = __shfl_up(upto, o);
+      if (sub >= o) upto += x;
+    }
+    const uint32_t total = __shfl(upto, (lane & ~(lpr - 1)) + lpr - 1);
+    uint32_t to = 0;
+    if (on && total > 1u && total <= (uint32_t)kRefineRowCands && sub == 0) to = atomicAdd(&s_n, total);
+    to = __shfl(to, lane & ~(lpr - 1));
+    if (!on) continue;
+    if (total == 1u) {  // nobody to compare it with
       if (mine) s_col[r] = first;
-      continue;
-    }
-    if (!crowded && total <= (uint32_t)kRefineRowCands) {  // uniform: to the list
-      uint32_t base = 0;
-      if (lane == 0 && total) base = atomicAdd(&s_n, total);
-      base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
-      uint32_t before = mine;  // candidates of the lanes in front
-      for (int o = 1; o < kWave; o <<= 1) {
-        const uint32_t x = __shfl_up(before, o);
-        if (lane >= o) before += x;
+    } else if (total > (uint32_t)kRefineRowCands) {
+      if (sub == 0) {
+        s_limit[r] = limit;
+        s_hard[atomicAdd(&s_hards, 1u)] = r;
       }
-      uint32_t to = base + before - mine;
-      for (int t = lane; mine && t < tc.tiles; t += kWave) {
-        const size_t at = (size_t)i * tc.tiles + t;
-        const uint32_t cnt = tmin[t] <= limit ? tc.cnt[at] : 0u;
+    } else if (mine) {  // to the list
+      to += (upto & 0xffffu) - mine;
+      for (int t = sub; t < tc.tiles; t += lpr) {
+        if (!(tmin[t] <= limit)) continue;
+        const uint32_t cnt = tc.cnt[base + t];
         for (uint32_t j = 0; j < cnt; ++j)
-          if (tc.val[at * kTileCands + j] <= limit) {
-            s_lcol[to] = tc.col[at * kTileCands + j];
+          if (tc.val[(base + t) * kTileCands + j] <= limit) {
+            s_lcol[to] = tc.col[(base + t) * kTileCands + j];
             s_lrow[to++] = (uint8_t)r;
           }
       }
-      continue;
     }
-    // many candidates, or tiles that could not keep all of theirs: the wavefront scores them here
-    const float *y = Y + i * D.d;
+  }
+  __syncthreads();
+  // many candidates, or tiles that could not keep all of theirs: a wavefront to a row
+  for (uint32_t h = (uint32_t)wave; h < s_hards; h += kRefineThreads / kWave) {  // uniform over the wavefront
+    const int r = s_hard[h];
+    const size_t base = (size_t)(i0 + r) * tc.tiles;
+    const float limit = s_limit[r];
+    const float *y = Y + (i0 + r) * D.d;
     double best_s = l2 ? __builtin_inf() : -__builtin_inf();
     int best_c = kNone;
     auto offer = [&](int c) {
@@ -479,18 +595,17 @@ __global__ __launch_bounds__(kRefineThreads) void k_assign_refine(Dev D, int64_t
     };
     for (int t0 = 0; t0 < tc.tiles; t0 += kWave) {
       const int t = t0 + lane;
-      const size_t at = (size_t)i * tc.tiles + t;
-      const bool near = t < tc.tiles && tmin[t] <= limit;
-      const uint32_t cnt = near ? tc.cnt[at] : 0u;
+      const bool near = t < tc.tiles && tc.tmin[base + t] <= limit;
+      const uint32_t cnt = near ? tc.cnt[base + t] : 0u;
       if (near && cnt <= (uint32_t)kTileCands)  // the tile kept all its columns within the band: one lane takes them
         for (uint32_t j = 0; j < cnt; ++j)
-          if (tc.val[at * kTileCands + j] <= limit) offer(tc.col[at * kTileCands + j]);
+          if (tc.val[(base + t) * kTileCands + j] <= limit) offer(tc.col[(base + t) * kTileCands + j]);
       // a tile with more columns in the band than it could keep: all its columns, shared out over the lanes
       unsigned long long full = __ballot(near && cnt > (uint32_t)kTileCands);
       while (full) {  // uniform
         const int tt = t0 + __ffsll((long long)full) - 1;
         full &= full - 1;
-        for (int c = tt * kTileN + lane; c < (tt + 1) * kTileN && c < D.nlist; c += kWave) offer(c);
+        for (int c = tt * tc.width + lane; c < (tt + 1) * tc.width && c < D.nlist; c += kWave) offer(c);
       }
     }
     for (int o = kWave / 2; o > 0; o >>= 1) {
@@ -502,7 +617,6 @@ __global__ __launch_bounds__(kRefineThreads) void k_assign_refine(Dev D, int64_t
     }
     if (lane == 0) s_col[r] = best_c;
   }
-  __syncthreads();
   // the listed candidates, a thread to each (a list longer than the workgroup goes round: the scores of the
   // turns are compared through LDS, keys first, then the lowest index among the equal ones)
   const int listed = (int)s_n;
@@ -535,57 +649,75 @@ __global__ __launch_bounds__(kRefineThreads) void k_assign_refine(Dev D, int64_t
   }
 }
 
-void launch_centroid_norms(const Dev &D, hipStream_t s) {
-  hipLaunchKernelGGL(k_centroid_norms, dim3((unsigned)((D.nlist + 255) / 256)), dim3(256), 0, s, D);
-  const int64_t items = (int64_t)D.nlist * D.dgroups;
-  hipLaunchKernelGGL(k_centroid_split, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, D);
+void launch_centroid_halves(const Dev &D, hipStream_t s) {
+  hipLaunchKernelGGL(k_centroid_mean, dim3((unsigned)D.d4), dim3(256), 0, s, D);
+  const dim3 grid((unsigned)(D.nlist < 2048 ? (D.nlist + 3) / 4 : 512));
+  hipLaunchKernelGGL(k_centroid_top, grid, dim3(256), 0, s, D);
+  hipLaunchKernelGGL(k_centroid_halves, grid, dim3(256), 0, s, D);
 }
 
-int coarse_tiles(const Dev &D) { return (D.nlist + kTileN - 1) / kTileN; }
-
-// one workgroup per (row tile, column tile), the column tiles rounded up to a whole turn of the dies
-static unsigned tile_grid(const Dev &D, int64_t n) {
-  const int64_t per_die = (coarse_tiles(D) + kXcds - 1) / kXcds;
-  return (unsigned)(((n + kTileM - 1) / kTileM) * per_die * kXcds);
+static void launch_half_rows(const Dev &D, int64_t n, const float *Y, u32x4 *half, RowMeta *meta, hipStream_t s) {
+  int lpr = 4;
+  while (lpr < kWave && lpr < D.dgroups) lpr *= 2;
+  const dim3 grid((unsigned)((n * lpr + 255) / 256)), block(256);
+  if (D.dgroups <= lpr) hipLaunchKernelGGL(k_half_rows<1>, grid, block, 0, s, D, n, Y, lpr, half, meta);
+  else if (D.dgroups <= 2 * lpr) hipLaunchKernelGGL(k_half_rows<2>, grid, block, 0, s, D, n, Y, lpr, half, meta);
+  else hipLaunchKernelGGL(k_half_rows<4>, grid, block, 0, s, D, n, Y, lpr, half, meta);  // d is at most 2048
 }
 
-static void launch_split_rows(const Dev &D, int64_t n, const float *Y, u32x4 *split, float *norms, hipStream_t s) {
-  hipLaunchKernelGGL(k_split_rows, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, D, n, Y, split, norms);
+// Wide tiles where they give every compute unit a workgroup, else narrow ones.
+static int tile_width(const Dev &D, int64_t n) {
+  return (n + kTileM - 1) / kTileM * ((D.nlist + 255) / 256) >= 256 ? 256 : 128;
+}
+struct TileGrid { unsigned blocks; int die_map; };
+static TileGrid tile_grid(const Dev &D, int64_t n, int width) {
+  const int64_t cols = (D.nlist + width - 1) / width, rows = (n + kTileM - 1) / kTileM;
+  const int64_t padded = (cols + kXcds - 1) / kXcds * kXcds;  // to whole turns of the dies
+  if (cols * 8 >= padded * 7) return {(unsigned)(rows * padded), 1};
+  return {(unsigned)(rows * cols), 0};
 }
 
-void launch_coarse_mfma(const Dev &D, int64_t n, const float *Y, u32x4 *split, float *approx,
+void launch_coarse_mfma(const Dev &D, int64_t n, const float *Y, u32x4 *half, float *approx,
                         unsigned long long *cursor_to_clear, uint32_t *zero, int zero_n, hipStream_t s) {
   if (n <= 0) return;
-  launch_split_rows(D, n, Y, split, nullptr, s);
-  const dim3 grid(tile_grid(D, n));
+  RowMeta *meta = search_row_meta(D, n, half);
+  launch_half_rows(D, n, Y, half, meta, s);
+  const int width = tile_width(D, n);
+  const TileGrid tg = tile_grid(D, n, width);
   const TileCands none{};
-  if (D.metric == 0)
-    hipLaunchKernelGGL((k_coarse_mfma<0, true>), grid, dim3(kMfmaThreads), 0, s, D, n, split, nullptr, approx, none, cursor_to_clear, zero, zero_n);
+  if (width == 256)
+    hipLaunchKernelGGL((k_coarse_mfma<4, true>), dim3(tg.blocks), dim3(kMfmaThreads), 0, s, D, n, half, meta, approx, none, tg.die_map, cursor_to_clear, zero, zero_n);
   else
-    hipLaunchKernelGGL((k_coarse_mfma<1, true>), grid, dim3(kMfmaThreads), 0, s, D, n, split, nullptr, approx, none, cursor_to_clear, zero, zero_n);
+    hipLaunchKernelGGL((k_coarse_mfma<2, true>), dim3(tg.blocks), dim3(kMfmaThreads), 0, s, D, n, half, meta, approx, none, tg.die_map, cursor_to_clear, zero, zero_n);
 }
 
-void launch_coarse_tiles(const Dev &D, int64_t n, const float *Y, u32x4 *split, float *norms, const TileCands &tc,
+void launch_coarse_tiles(const Dev &D, int64_t n, const float *Y, u32x4 *half, RowMeta *meta, TileCands &tc,
                          hipStream_t s) {
   if (n <= 0) return;
-  launch_split_rows(D, n, Y, split, norms, s);
-  const dim3 grid(tile_grid(D, n));
-  if (D.metric == 0)
-    hipLaunchKernelGGL((k_coarse_mfma<0, false>), grid, dim3(kMfmaThreads), 0, s, D, n, split, norms, nullptr, tc, nullptr, nullptr, 0);
+  launch_half_rows(D, n, Y, half, meta, s);
+  // the digests of narrow tiles take twice the room: only as many rows as it holds
+  tc.width = n * 2 <= tc.rows ? tile_width(D, n) : 256;
+  tc.tiles = (D.nlist + tc.width - 1) / tc.width;
+  const TileGrid tg = tile_grid(D, n, tc.width);
+  if (tc.width == 256)
+    hipLaunchKernelGGL((k_coarse_mfma<4, false>), dim3(tg.blocks), dim3(kMfmaThreads), 0, s, D, n, half, meta, nullptr, tc, tg.die_map, nullptr, nullptr, 0);
   else
-    hipLaunchKernelGGL((k_coarse_mfma<1, false>), grid, dim3(kMfmaThreads), 0, s, D, n, split, norms, nullptr, tc, nullptr, nullptr, 0);
+    hipLaunchKernelGGL((k_coarse_mfma<2, false>), dim3(tg.blocks), dim3(kMfmaThreads), 0, s, D, n, half, meta, nullptr, tc, tg.die_map, nullptr, nullptr, 0);
 }
 
-void launch_assign_refine(const Dev &D, int64_t n, const float *Y, const float *norms, const TileCands &tc, bool reserve,
+void launch_assign_refine(const Dev &D, int64_t n, const float *Y, const RowMeta *meta, const TileCands &tc, bool reserve,
                           int32_t *assign, uint32_t *did, hipStream_t s) {
   if (n <= 0) return;
-  // as many rows to a wavefront as leave four workgroups to a compute unit (a row's digest is a chain of
-  // trips to memory, so a small batch is spread as wide as it goes)
-  int64_t per = n / (1024 * kRefineWaves);
-  per = per < 1 ? 1 : per > kRefinePerWave ? kRefinePerWave : per;
-  const int64_t rows = per * kRefineWaves;
+  // four tiles to a lane, so that a workgroup's rows are a turn or a few of trips to memory; as many rows to a
+  // workgroup as leave four workgroups to a compute unit
+  int lpr = 4;
+  while (lpr < kWave && lpr * 4 < tc.tiles) lpr *= 2;
+  int64_t rows = n / 1024;
+  const int64_t turn = kRefineThreads / lpr < kRefineRows ? kRefineThreads / lpr : kRefineRows;  // rows read at a time
+  rows = rows < 4 ? 4 : rows > kRefineRows ? kRefineRows : rows;
+  if (rows > turn) rows = rows / turn * turn;
   hipLaunchKernelGGL(k_assign_refine, dim3((unsigned)((n + rows - 1) / rows)), dim3(kRefineThreads), 0, s, D, n, Y,
-                     norms, tc, (int)per, reserve ? 1 : 0, assign, did);
+                     meta, tc, (int)rows, lpr, reserve ? 1 : 0, assign, did);
 }
 
 }  // namespace rtams

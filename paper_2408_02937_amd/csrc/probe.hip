@@ -20,7 +20,7 @@ constexpr int kSelThreads = 256, kSelThreadsMany = 1024, kSelManyFrom = 4096;
 // exactly.  If the band holds more candidates than LDS, the whole row is scored
 // exactly instead (what small requests, which skip the matrix cores, always do).
 template <bool FROM_APPROX>
-__global__ __launch_bounds__(kSelThreadsMany) void k_probe_plan(Dev D, int nprobe, int max_nprobe,
+__global__ __launch_bounds__(kSelThreadsMany) void k_probe_plan(Dev D, int64_t nq, int nprobe, int max_nprobe,
                                                             SearchScratch S, const float *__restrict__ Q,
                                                             int32_t *probe_out) {
   __shared__ __attribute__((aligned(8))) uint32_t hist[kSelectLdsWords];
@@ -29,7 +29,6 @@ __global__ __launch_bounds__(kSelThreadsMany) void k_probe_plan(Dev D, int nprob
   __shared__ uint64_t k1[kMaxNprobe];
   __shared__ uint64_t k2[kMaxNprobe];
   __shared__ uint32_t pay[kMaxNprobe];
-  __shared__ float s_red[kSelThreadsMany / kWave];
   const int T = (int)blockDim.x;
   const int q = blockIdx.x;
   const int n = D.nlist;
@@ -74,16 +73,7 @@ __global__ __launch_bounds__(kSelThreadsMany) void k_probe_plan(Dev D, int nprob
   bool done = false;  // k1 / k2 / pay hold the nprobe winners, not yet sorted
   if (FROM_APPROX && nprobe < n) {
     const float *ap = S.approx + (size_t)q * n;
-    // |y|^2 for the error band
-    float yn = 0.f;
-    for (int j = threadIdx.x; j < D.d; j += T) { const float v = Q[(size_t)q * D.d + j]; yn = fmaf(v, v, yn); }
-    for (int o = kWave / 2; o > 0; o >>= 1) yn += __shfl_xor(yn, o);
-    if ((threadIdx.x & (kWave - 1)) == 0) s_red[threadIdx.x / kWave] = yn;
-    __syncthreads();
-    yn = 0.f;
-    for (int w = 0; w < T / kWave; ++w) yn += s_red[w];
-    const float cmax = __uint_as_float(D.ctrl->cnorm_max_bits);
-    const float band = coarse_band(D.d, yn + cmax) * 1.01f;  // 2 E, see coarse_mfma.hip
+    const float band = search_row_meta(D, nq, S.qhalf)[q].band;  // 2 E, see coarse_mfma.hip
     const SelectResult ra = wg_radix_select<32>(
         n, (uint32_t)nprobe, [&](int i, uint64_t &k) { k = key_of_float(ap[i] + 0.0f); return true; }, hist, bc);
     const uint32_t tk = (uint32_t)ra.T;  // key of (an upper bound of) the nprobe-th smallest approximation
@@ -192,10 +182,10 @@ void launch_probe_plan(const Dev &D, int64_t nq, int nprobe, int max_nprobe, con
   if (nq <= 0) return;
   const unsigned threads = D.nlist >= kSelManyFrom ? kSelThreadsMany : kSelThreads;
   if (from_approx)
-    hipLaunchKernelGGL(k_probe_plan<true>, dim3((unsigned)nq), dim3(threads), 0, s, D, nprobe, max_nprobe,
+    hipLaunchKernelGGL(k_probe_plan<true>, dim3((unsigned)nq), dim3(threads), 0, s, D, nq, nprobe, max_nprobe,
                        S, Q, probe_out);
   else
-    hipLaunchKernelGGL(k_probe_plan<false>, dim3((unsigned)nq), dim3(threads), 0, s, D, nprobe, max_nprobe,
+    hipLaunchKernelGGL(k_probe_plan<false>, dim3((unsigned)nq), dim3(threads), 0, s, D, nq, nprobe, max_nprobe,
                        S, Q, probe_out);
 }
 

@@ -39,7 +39,7 @@ inline size_t up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Byte offsets of everything in front of the blocks.
 struct Layout {
-  size_t ctrl, hook, centroids, centroids_t, cnorm, csplit, codebooks, codebooks_t, tc_min, tc_cnt, tc_col, tc_val, ins_ysplit, ins_ynorm, tile_rows, reserved_len, visible_len, online, nblk, exceed, seg_dir;
+  size_t ctrl, hook, centroids, centroids_t, cmean, cbias, chalf, codebooks, codebooks_t, tc_min, tc_cnt, tc_col, tc_val, ins_yhalf, ins_ymeta, tile_rows, reserved_len, visible_len, online, nblk, exceed, seg_dir;
   size_t ins_assign, ins_did, ins_pscore, ins_pidx, part_cap;
   size_t rearr_head, rearr_arrays;
   size_t fixed_end;          // end of the part that does not depend on the block count
@@ -94,8 +94,10 @@ void lay_out(const rtams_config *c, int64_t blocks, size_t pool_bytes, Layout *L
   L->hook = take(kHookBytes);
   L->centroids = take(nl * c->d * sizeof(float));
   L->centroids_t = take(nl * c->d * sizeof(float));
-  L->cnorm = take(nl * sizeof(float));
-  L->csplit = take(nl * (size_t)((c->d + 31) / 32) * 4 * 32);
+  const int dgroups = (c->d + 31) / 32 * 4;
+  L->cmean = take((size_t)c->d * sizeof(float));
+  L->cbias = take(nl * sizeof(float));
+  L->chalf = take(half_units((int64_t)nl, dgroups) * sizeof(u32x4));
   L->codebooks = take(c->pq_m > 0 ? (size_t)256 * c->d * sizeof(float) : 0);
   L->codebooks_t = take(c->pq_m > 0 ? (size_t)256 * c->d * sizeof(float) : 0);
   L->reserved_len = take(nl * 4);
@@ -109,16 +111,15 @@ void lay_out(const rtams_config *c, int64_t blocks, size_t pool_bytes, Layout *L
   L->ins_did = take((size_t)c->max_add_batch * 4);
   L->ins_pscore = take(L->part_cap * 8);
   L->ins_pidx = take(L->part_cap * 4);
-  {  // tile digests of one insertion sub-round (40 bytes per row and tile): at most 64 MiB, at least 64 rows
-    const size_t tiles = (nl + 127) / 128;
-    size_t rows = ((size_t)64 << 20) / (tiles * 40);
-    const size_t split_row = (size_t)((c->d + 31) / 32) * 4 * 32;  // a vector as bf16 halves: at most 64 MiB of those, too
-    if (rows > ((size_t)64 << 20) / split_row) rows = ((size_t)64 << 20) / split_row;
+  {  // one insertion sub-round: tile digests (40 bytes per row and tile) and halves, 64 MiB of them, at least 64 rows
+    const size_t tiles = (nl + 255) / 256;
+    size_t rows = ((size_t)64 << 20) / (tiles * 40 + (size_t)dgroups * 16 + sizeof(RowMeta));
+    rows = rows / 128 * 128;  // whole tiles of the contraction
     if (rows > (size_t)c->max_add_batch) rows = (size_t)c->max_add_batch;
     if (rows < 64) rows = 64;
     L->tile_rows = rows;
-    L->ins_ysplit = take(rows * split_row);
-    L->ins_ynorm = take(rows * 4);
+    L->ins_yhalf = take(half_units((int64_t)rows, dgroups) * sizeof(u32x4));
+    L->ins_ymeta = take(rows * sizeof(RowMeta));
     L->tc_min = take(rows * tiles * 4);
     L->tc_cnt = take(rows * tiles * 4);
     L->tc_col = take(rows * tiles * kTileCands * 4);
@@ -148,7 +149,7 @@ void lay_out(const rtams_config *c, int64_t blocks, size_t pool_bytes, Layout *L
 }
 
 struct ScratchLayout {
-  size_t scores, approx, probe_list, probe_len, qbase, qtotal, bound, qnorm, qsplit, rec_cnt, cursor, req_words, lut, records, fixed;
+  size_t scores, approx, probe_list, probe_len, qbase, qtotal, bound, qnorm, qhalf, rec_cnt, cursor, req_words, lut, records, fixed;
   size_t list_cnt, pair_start, pair_slot, grouped, plist, pistart, tile_desc, queues, item_cap;
 };
 
@@ -165,7 +166,7 @@ void lay_out_scratch(const rtams_config *c, ScratchLayout *S) {
   S->qtotal = take(mb * 4);
   S->bound = take(mb * 4);
   S->qnorm = take(mb * 4);
-  S->qsplit = take(mb * (size_t)((c->d + 31) / 32) * 4 * 32);
+  S->qhalf = take(mb * (size_t)((c->d + 31) / 32) * 4 * 32);  // twice what the halves take: whole blocks of rows, and the rows' scales and bands
   S->rec_cnt = take(mb * 4);
   S->cursor = take(8);
   S->req_words = take(16);  // the request's chunk of the shared reserve: chunk, finished workgroups, cursor
@@ -303,7 +304,7 @@ void coarse_and_plan(rtams_index *ix, int64_t nq, const float *Q, int nprobe, co
   const Dev &D = ix->dev;
   const int64_t mode = ix->use_mfma.load(std::memory_order_relaxed);  // 0 never, 1 when it pays, 2 from 32 rows
   const bool mfma = mode == 2 ? nq >= 32 : mode == 1 && mfma_pays_for_search(nq, D.nlist);
-  if (mfma) launch_coarse_mfma(D, nq, Q, S.qsplit, S.approx, S.cursor, S.list_cnt, plan_words(ix), s);
+  if (mfma) launch_coarse_mfma(D, nq, Q, S.qhalf, S.approx, S.cursor, S.list_cnt, plan_words(ix), s);
   else launch_coarse_scores(D, nq, Q, S.scores, S.cursor, S.list_cnt, plan_words(ix), s);
   launch_probe_plan(D, nq, nprobe, ix->cfg.max_nprobe, S, Q, mfma, probe_out, s);
 }
@@ -387,8 +388,8 @@ void assign_round(rtams_index *ix, int64_t m, const float *Y, bool reserve, int3
   if (mode == 2 ? m >= 32 : mode == 1 && mfma_pays_for_assign(m, D.nlist)) {
     for (int64_t o = 0; o < m; o += ix->ins.tile_rows) {
       const int64_t mm = m - o < ix->ins.tile_rows ? m - o : ix->ins.tile_rows;
-      launch_coarse_tiles(D, mm, Y + (size_t)o * D.d, ix->ins.ysplit, ix->ins.ynorm, ix->ins.tiles, s);
-      launch_assign_refine(D, mm, Y + (size_t)o * D.d, ix->ins.ynorm, ix->ins.tiles, reserve, assign_out + o, ix->ins.did + o, s);
+      launch_coarse_tiles(D, mm, Y + (size_t)o * D.d, ix->ins.yhalf, ix->ins.ymeta, ix->ins.tiles, s);
+      launch_assign_refine(D, mm, Y + (size_t)o * D.d, ix->ins.ymeta, ix->ins.tiles, reserve, assign_out + o, ix->ins.did + o, s);
     }
   } else {
     int splits = coarse_splits(D, m, ix->ins.part_cap);
@@ -475,8 +476,9 @@ int rtams_create(const rtams_config *cfg, rtams_index **out) {
   D.ctrl = reinterpret_cast<Ctrl *>(base + L.ctrl);
   D.centroids = reinterpret_cast<float *>(base + L.centroids);
   D.centroids_t = reinterpret_cast<float *>(base + L.centroids_t);
-  D.cnorm = reinterpret_cast<float *>(base + L.cnorm);
-  D.csplit = reinterpret_cast<u32x4 *>(base + L.csplit);
+  D.cmean = reinterpret_cast<float *>(base + L.cmean);
+  D.cbias = reinterpret_cast<float *>(base + L.cbias);
+  D.chalf = reinterpret_cast<u32x4 *>(base + L.chalf);
   D.dgroups = (cfg->d + 31) / 32 * 4;
   D.codebooks = reinterpret_cast<float *>(base + L.codebooks);
   D.codebooks_t = reinterpret_cast<float *>(base + L.codebooks_t);
@@ -496,14 +498,14 @@ int rtams_create(const rtams_config *cfg, rtams_index **out) {
   ix->ins.pscore = reinterpret_cast<double *>(base + L.ins_pscore);
   ix->ins.pidx = reinterpret_cast<int32_t *>(base + L.ins_pidx);
   ix->ins.part_cap = L.part_cap;
-  ix->ins.tiles.tiles = (cfg->nlist + 127) / 128;
+  ix->ins.tiles.rows = (int64_t)L.tile_rows;
   ix->ins.tiles.tmin = reinterpret_cast<float *>(base + L.tc_min);
   ix->ins.tiles.cnt = reinterpret_cast<uint32_t *>(base + L.tc_cnt);
   ix->ins.tiles.col = reinterpret_cast<int32_t *>(base + L.tc_col);
   ix->ins.tiles.val = reinterpret_cast<float *>(base + L.tc_val);
   ix->ins.tile_rows = (int64_t)L.tile_rows;
-  ix->ins.ysplit = reinterpret_cast<u32x4 *>(base + L.ins_ysplit);
-  ix->ins.ynorm = reinterpret_cast<float *>(base + L.ins_ynorm);
+  ix->ins.yhalf = reinterpret_cast<u32x4 *>(base + L.ins_yhalf);
+  ix->ins.ymeta = reinterpret_cast<RowMeta *>(base + L.ins_ymeta);
   {
     uint32_t *a = reinterpret_cast<uint32_t *>(base + L.rearr_arrays);
     RearrangeScratch &R = ix->rearr;
@@ -563,7 +565,7 @@ int rtams_create(const rtams_config *cfg, rtams_index **out) {
     S.qtotal = reinterpret_cast<uint32_t *>(p + SL.qtotal);
     S.bound = reinterpret_cast<uint32_t *>(p + SL.bound);
     S.qnorm = reinterpret_cast<float *>(p + SL.qnorm);
-    S.qsplit = reinterpret_cast<u32x4 *>(p + SL.qsplit);
+    S.qhalf = reinterpret_cast<u32x4 *>(p + SL.qhalf);
     S.rec_cnt = reinterpret_cast<uint32_t *>(p + SL.rec_cnt);
     S.cursor = reinterpret_cast<unsigned long long *>(p + SL.cursor);
     S.list_cnt = reinterpret_cast<uint32_t *>(p + SL.list_cnt);
@@ -650,8 +652,8 @@ int rtams_set_centroids(rtams_index *ix, const float *d_centroids, void *hip_str
   DataStreamScope scope{ix, s};
   HIP_TRY(hipMemcpyAsync(ix->dev.centroids, d_centroids, (size_t)ix->cfg.nlist * ix->cfg.d * 4,
                          hipMemcpyDeviceToDevice, s));
-  launch_centroid_norms(ix->dev, s);
   launch_centroid_transpose(ix->dev, s);
+  launch_centroid_halves(ix->dev, s);
   HIP_TRY(hipGetLastError());
   ix->has_centroids = true;
   return RTAMS_OK;

@@ -26,6 +26,17 @@ struct BlockHeader {
 };
 static_assert(sizeof(BlockHeader) == kHeaderBytes, "header size");
 
+// What the matrix-core filter knows of the centroids (coarse_mfma.hip): magnitudes as float bits, all of them of the
+// centroids less their mean; norms of the scaled halves.
+struct CentroidStats {
+  uint32_t top_bits;   // largest coordinate
+  uint32_t norm_bits;  // largest norm, scaled
+  uint32_t res_bits;   // largest norm of what the halves leave out, scaled
+  uint32_t bias_bits;  // largest |bias|
+  float mean_norm;     // norm of the mean
+  uint32_t bad;        // some coordinate is not finite, or too large for its square
+};
+
 // Control words shared by all kernels (one cache line each for the hot ones).
 struct Ctrl {
   uint32_t cur_P;            // bump pointer of the central pool
@@ -38,9 +49,9 @@ struct Ctrl {
   uint32_t exceed_lists;     // lists for which Exceed() holds
   unsigned long long ntotal; // vectors visible
   uint32_t max_len;          // longest visible list
-  uint32_t cnorm_max_bits;   // largest squared centroid norm, as float bits
   int32_t search_error;      // rtams_status raised by a kernel of a search (scratch too small): inserts do not look at it
-  uint32_t pad3[25];
+  CentroidStats cen;
+  uint32_t pad3[20];
 };
 
 // Words the device writes straight into pinned host memory, so the host can
@@ -80,9 +91,10 @@ struct Dev {
   HostMirror *mirror;       // pinned host memory, device-visible
   float *centroids;         // [nlist][d]
   float *centroids_t;       // the same numbers as [d / 4][nlist] chunks of 4 coordinates: chunk j of consecutive centroids side by side
-  float *cnorm;             // [nlist] squared norms of the centroids (fp32)
-  u32x4 *csplit;            // [nlist][dgroups][2] the centroids as bf16 halves: per group of 8 coordinates the 8 hi, then the 8 lo
-  int32_t dgroups;          // groups of 8 coordinates of a split row, padded with zeros to whole steps of 32 coordinates: 4 ceil(d / 32)
+  float *cmean;             // [d] mean of the centroids
+  float *cbias;             // [nlist] the part of an approximate coarse score that only the centroid decides
+  u32x4 *chalf;             // [nlist] the centroids less their mean as halves (layout: coarse_mfma.hip)
+  int32_t dgroups;          // groups of 8 coordinates of a row of halves, padded with zeros to whole steps of 32 coordinates: 4 ceil(d / 32)
   float *codebooks;         // [pq_m][256][d / pq_m] (product-quantised lists only)
   float *codebooks_t;       // the same with the entries innermost: [pq_m][d / pq_m][256] (for coding inserted vectors)
   uint32_t *reserved_len;   // [nlist] next free position (atomicAdd target)

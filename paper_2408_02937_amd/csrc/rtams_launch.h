@@ -32,7 +32,7 @@ struct SearchScratch {
   uint32_t *qtotal;     // [max_batch] candidates of the query
   uint32_t *bound;      // [max_batch] key of the score the scan compares with
   float *qnorm;         // [max_batch] squared norms of the queries (norm form of the squared distance)
-  u32x4 *qsplit;        // [max_batch][dgroups][2] the queries as bf16 halves, for the matrix-core coarse scores
+  u32x4 *qhalf;         // the queries as halves for the matrix-core coarse scores, then their RowMeta (coarse_mfma.hip)
   uint32_t *rec_cnt;    // [max_batch] survivors recorded so far
   unsigned long long *cursor; // bump pointer into the survivor records
   uint32_t *list_cnt;   // [nlist] queries probing each list
@@ -66,13 +66,21 @@ constexpr int kMaxOverflowChunks = 32;
 
 constexpr int kScanTileQueries = 8;  // queries that share one pass over a list
 
-// What a 64 x 128 tile of approximate coarse scores is reduced to, per row: the
+// What the matrix-core filter knows of a vector: the factor that turns an accumulated product into a score, and
+// the band, twice the error bound of an approximate score (both in coarse_mfma.hip).
+struct RowMeta {
+  float scale, band;
+};
+
+// What a tile of approximate coarse scores is reduced to, per row: the
 // tile's smallest score and the columns within the error band of it.
 constexpr int kTileCands = 4;
 struct TileCands {
-  int32_t tiles;   // tiles per row = ceil(nlist / 128)
+  int32_t tiles;   // tiles per row = ceil(nlist / width)
+  int32_t width;   // centroids of a tile, 256 or 128 (chosen per launch)
+  int64_t rows;    // rows the arrays hold with tiles of 256
   float *tmin;     // [rows][tiles]
-  uint32_t *cnt;   // [rows][tiles] columns within the band (may exceed kTileCands: then all 128 are rescored)
+  uint32_t *cnt;   // [rows][tiles] columns within the band (may exceed kTileCands: then all of the tile are rescored)
   int32_t *col;    // [rows][tiles][kTileCands]
   float *val;      // [rows][tiles][kTileCands]
 };
@@ -85,8 +93,8 @@ struct InsertScratch {
   int32_t *pidx;     // [part_cap]
   size_t part_cap;
   TileCands tiles;   // per (row, tile of 128 centroids) digest of the approximate scores of one sub-round
-  u32x4 *ysplit;     // [tile_rows][dgroups][2] the vectors of one sub-round as bf16 halves
-  float *ynorm;      // [tile_rows] their squared norms
+  u32x4 *yhalf;      // [tile_rows] the vectors of one sub-round as halves
+  RowMeta *ymeta;    // [tile_rows] their scales and bands
   int64_t tile_rows; // rows one sub-round may hold
 };
 
@@ -132,20 +140,20 @@ inline bool mfma_pays_for_search(int64_t nq, int64_t nlist) { return nq >= 32 &&
 // exact kernel takes two centroids to a thread it does not: 64 vectors against 8,192 x 768 centroids
 // are assigned at 0.91 M vectors/s by the exact kernel alone and at 0.78 M through the filter)
 inline bool mfma_pays_for_assign(int64_t m, int64_t nlist) { return m >= 32 && m * nlist >= (int64_t)1 << 20; }
-// Twice the error bound of an approximate score, for a vector of squared norm |y|^2 (norms = |y|^2 + max |c|^2):
-// the exact best lies among the centroids whose approximation is within this of the smallest one.
-__host__ __device__ inline float coarse_band(int d, float norms) {
-  return (8.f * (float)(d + 4) * 5.9604645e-8f + 8.f * 1.52587890625e-5f) * norms;
+// 16-byte units the halves of `rows` rows take: whole blocks of 16 rows
+__host__ __device__ inline size_t half_units(int64_t rows, int dgroups) { return (size_t)((rows + 15) / 16 * 16) * dgroups; }
+// a request's RowMeta behind the halves of its n queries (32 of them at least: the room is 32 dgroups bytes a query)
+__host__ __device__ inline RowMeta *search_row_meta(const Dev &D, int64_t n, u32x4 *half) {
+  return reinterpret_cast<RowMeta *>(half + half_units(n, D.dgroups));
 }
-void launch_centroid_norms(const Dev &D, hipStream_t s);  // and the centroids' split form
+void launch_centroid_halves(const Dev &D, hipStream_t s);  // behind the transposed copy
 void launch_centroid_transpose(const Dev &D, hipStream_t s);  // the copy the exact coarse kernel streams
-// (`split` takes the n rows as bf16 halves, [n][dgroups][2] 16-byte words; `norms` their n squared norms)
-void launch_coarse_mfma(const Dev &D, int64_t n, const float *Y, u32x4 *split, float *approx,
+// (`half` takes the n rows as halves, half_units(n, dgroups) units)
+void launch_coarse_mfma(const Dev &D, int64_t n, const float *Y, u32x4 *half, float *approx,
                         unsigned long long *cursor_to_clear, uint32_t *zero, int zero_n, hipStream_t s);
-int coarse_tiles(const Dev &D);
-void launch_coarse_tiles(const Dev &D, int64_t n, const float *Y, u32x4 *split, float *norms, const TileCands &tc,
-                         hipStream_t s);
-void launch_assign_refine(const Dev &D, int64_t n, const float *Y, const float *norms, const TileCands &tc, bool reserve,
+void launch_coarse_tiles(const Dev &D, int64_t n, const float *Y, u32x4 *half, RowMeta *meta, TileCands &tc,
+                         hipStream_t s);  // chooses tc.width and tc.tiles
+void launch_assign_refine(const Dev &D, int64_t n, const float *Y, const RowMeta *meta, const TileCands &tc, bool reserve,
                           int32_t *assign, uint32_t *did, hipStream_t s);
 
 // insert.hip -----------------------------------------------------------------
