@@ -5,8 +5,10 @@
 //
 // The paper runs all of this in one thread block and separates "reserve",
 // "open" and "fill" with two barriers, which only works while a batch cannot
-// need two new blocks for one list.  Here the three phases are stream-ordered
-// kernels, so any batch size and any block size work across the whole chip; the
+// need two new blocks for one list.  Here the phases of a large batch are
+// stream-ordered kernels, so any batch size and any block size work across the
+// whole chip, and a batch of up to kTailVecs vectors goes through one workgroup
+// with barriers, as the paper has it, however many blocks it needs; the
 // rule that the block of position did lives at chain index did / T_m, offset
 // did % T_m, and that exactly one party opens each new block, is the paper's.
 #include "rtams_launch.h"
@@ -18,15 +20,15 @@ __device__ inline void raise_error(const Dev &D, int code) {
   D.mirror->error = code;
 }
 
+// (read past the caches of the compute unit: another thread of the same workgroup may just have raised it)
+__device__ inline bool pool_failed(const Dev &D) {
+  return __hip_atomic_load(&D.ctrl->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+}
+
 // ---- reserve: finish the arg-min over the centroid splits, then take the next
 // position of that list ("did = atomicAdd(nl_k, 1)").
-__global__ __launch_bounds__(256) void k_reserve(Dev D, int64_t n, int splits,
-                                                 const double *__restrict__ pscore,
-                                                 const int32_t *__restrict__ pidx, int reserve,
-                                                 int32_t *__restrict__ assign,
-                                                 uint32_t *__restrict__ did) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+__device__ inline int best_of_splits(const Dev &D, int64_t i, int splits, const double *__restrict__ pscore,
+                                     const int32_t *__restrict__ pidx) {
   double bs = 0.0;
   int bi = -1;
   for (int s = 0; s < splits; ++s) {
@@ -36,7 +38,17 @@ __global__ __launch_bounds__(256) void k_reserve(Dev D, int64_t n, int splits,
     bool better = bi < 0 || (cs != bs ? (D.metric == 0 ? cs < bs : cs > bs) : ci < bi);
     if (better) { bs = cs; bi = ci; }
   }
-  if (bi < 0) bi = 0;  // no score compared (a vector with a NaN): nothing was better than the first centroid
+  return bi < 0 ? 0 : bi;  // no score compared (a vector with a NaN): nothing was better than the first centroid
+}
+
+__global__ __launch_bounds__(256) void k_reserve(Dev D, int64_t n, int splits,
+                                                 const double *__restrict__ pscore,
+                                                 const int32_t *__restrict__ pidx, int reserve,
+                                                 int32_t *__restrict__ assign,
+                                                 uint32_t *__restrict__ did) {
+  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const int bi = best_of_splits(D, i, splits, pscore, pidx);
   assign[i] = bi;
   if (reserve) did[i] = atomicAdd(&D.reserved_len[bi], 1u);
 }
@@ -58,92 +70,131 @@ __global__ __launch_bounds__(256) void k_reserve_ordered(Dev D, int64_t n, const
   if (at != before) D.reserved_len[list] = at;
 }
 
-// ---- open: one wavefront per list.  Positions visible_len .. reserved_len-1
-// were reserved by this batch; every block index in [nblk, ceil(reserved/T_m))
-// is opened here: table segments first, then blocks from the free stack or the
-// bump pointer ("P[atomicAdd(cur_P, 1)]"), headers linked behind the chain.
-__global__ __launch_bounds__(256) void k_open(Dev D) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int list = blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
-  if (list >= D.nlist) return;
-  const uint32_t T = (uint32_t)D.T_m;
-  const uint32_t newlen = D.reserved_len[list];
-  const uint32_t nb_old = D.nblk[list];
-  const uint32_t nb_new = (newlen + T - 1) / T;
-  if (nb_new <= nb_old) return;  // uniform over the wavefront
-  if (D.ctrl->error != 0) return;
-  const uint32_t count = nb_new - nb_old;
+// ---- open.  Positions visible_len .. reserved_len-1 of a list were reserved by this batch; every block index in
+// [nblk, ceil(reserved/T_m)) is opened here: table segments first, then blocks from the free stack or the
+// bump pointer ("P[atomicAdd(cur_P, 1)]"), headers linked behind the chain.  A workgroup of T threads opens the
+// blocks of up to T different lists, one to a thread (list -1: none): it takes the blocks and table entries of all
+// of them with one atomic each (an atomic per list on the same two words took 0.2 ms where a first batch touched
+// 16,384 lists), and its threads share out the new blocks, whoever's list they are for.
+constexpr int kBatchThreads = 128;
+template <int T>
+struct OpenShared {
+  uint32_t first[T];   // new blocks of the threads before
+  int32_t list[T], old_last[T];
+  uint32_t nb_old[T];
+  uint32_t wave_blocks[T / kWave], wave_slab[T / kWave];
+  int32_t f_old;       // free_top before the pop
+  uint32_t from_stack, base, slab_base, failed;
+};
 
-  // table segments: lane s looks after segment s
-  int32_t seg_off = -1;
-  bool failed = false;
-  if (lane < kTableSegs) {
-    seg_off = D.seg_dir[(size_t)list * kTableSegs + lane];
-    if (seg_off < 0 && lane >= table_seg(nb_old) && lane <= table_seg(nb_new - 1)) {
-      uint32_t sz = (uint32_t)kTableBase << lane;
-      uint32_t off = atomicAdd(&D.ctrl->slab_cur, sz);
-      if ((uint64_t)off + sz > D.slab_cap) failed = true;
-      else { seg_off = (int32_t)off; D.seg_dir[(size_t)list * kTableSegs + lane] = seg_off; }
+// nb_old: the list's blocks so far, newlen: its length with this batch.  Returns whether there were blocks to open.
+template <int T>
+__device__ bool wg_open(const Dev &D, int list, uint32_t nb_old, uint32_t newlen, OpenShared<T> &sh) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const uint32_t Tm = (uint32_t)D.T_m;
+  uint32_t nb_new = 0, count = 0, slab = 0;
+  if (list >= 0) {
+    nb_new = (newlen + Tm - 1) / Tm;
+    if (nb_new > nb_old) {
+      count = nb_new - nb_old;
+      for (int g = table_seg(nb_old); g <= table_seg(nb_new - 1); ++g)
+        if (D.seg_dir[(size_t)list * kTableSegs + g] < 0) slab += (uint32_t)kTableBase << g;
     }
   }
-
-  // blocks: lane 0 takes `count` of them at once
-  int f_old = 0;        // free_top before our pop
-  uint32_t avail = 0;   // how many came off the free stack
-  uint32_t base = 0;    // first block taken from the bump pointer
-  if (lane == 0) {
-    f_old = atomicSub(&D.ctrl->free_top, (int)count);
-    int got = f_old < 0 ? 0 : (f_old < (int)count ? f_old : (int)count);
-    if (got < (int)count) atomicAdd(&D.ctrl->free_top, (int)count - got);  // give back what was not there
-    avail = (uint32_t)got;
-    uint32_t rem = count - avail;
-    if (rem) {
-      base = atomicAdd(&D.ctrl->cur_P, rem);
-      if ((uint64_t)base + rem > D.nblocks) failed = true;
+  uint32_t blocks_to = count, slab_to = slab;  // running sums
+  for (int o = 1; o < kWave; o <<= 1) {
+    const uint32_t a = __shfl_up(blocks_to, o), b = __shfl_up(slab_to, o);
+    if (lane >= o) { blocks_to += a; slab_to += b; }
+  }
+  if (lane == kWave - 1) { sh.wave_blocks[wave] = blocks_to; sh.wave_slab[wave] = slab_to; }
+  __syncthreads();
+  uint32_t total = 0, slab_total = 0;
+  for (int w = 0; w < T / kWave; ++w) {
+    if (w < wave) { blocks_to += sh.wave_blocks[w]; slab_to += sh.wave_slab[w]; }
+    total += sh.wave_blocks[w];
+    slab_total += sh.wave_slab[w];
+  }
+  if (total == 0) return false;  // uniform over the workgroup
+  if (tid == 0) {
+    sh.failed = pool_failed(D) ? 1u : 0u;
+    if (!sh.failed) {
+      const int f = atomicSub(&D.ctrl->free_top, (int)total);
+      const int got = f < 0 ? 0 : (f < (int)total ? f : (int)total);
+      if (got < (int)total) atomicAdd(&D.ctrl->free_top, (int)total - got);  // give back what was not there
+      sh.f_old = f;
+      sh.from_stack = (uint32_t)got;
+      const uint32_t rem = total - (uint32_t)got;
+      sh.base = rem ? atomicAdd(&D.ctrl->cur_P, rem) : 0u;
+      sh.slab_base = slab_total ? atomicAdd(&D.ctrl->slab_cur, slab_total) : 0u;
+      // backstop only: the host refuses batches that might not fit
+      if ((rem && (uint64_t)sh.base + rem > D.nblocks) || (slab_total && (uint64_t)sh.slab_base + slab_total > D.slab_cap)) {
+        sh.failed = 1u;
+        raise_error(D, -3);
+      }
     }
   }
-  if (__any(failed)) {  // backstop only: the host refuses batches that might not fit
-    if (lane == 0) raise_error(D, -3);
-    return;
+  __syncthreads();
+  if (sh.failed) return true;  // uniform
+  sh.first[tid] = blocks_to - count;
+  sh.list[tid] = list;
+  sh.nb_old[tid] = nb_old;
+  sh.old_last[tid] = -1;
+  if (count) {
+    uint32_t off = sh.slab_base + slab_to - slab;
+    for (int g = table_seg(nb_old); g <= table_seg(nb_new - 1); ++g) {
+      int32_t *dir = &D.seg_dir[(size_t)list * kTableSegs + g];
+      if (*dir < 0) { *dir = (int32_t)off; off += (uint32_t)kTableBase << g; }
+    }
+    if (nb_old > 0) sh.old_last[tid] = *table_entry(D, list, nb_old - 1);
   }
-  f_old = __shfl(f_old, 0);
-  avail = __shfl(avail, 0);
-  base = __shfl(base, 0);
-
-  auto block_of = [&](uint32_t jl) -> int32_t {  // jl-th new block of this list
-    return jl < avail ? D.free_stack[f_old - 1 - (int)jl] : (int32_t)(base + (jl - avail));
+  __syncthreads();
+  auto block_of = [&](uint32_t b) -> int32_t {  // b-th new block of this workgroup
+    return b < sh.from_stack ? D.free_stack[sh.f_old - 1 - (int)b] : (int32_t)(sh.base + (b - sh.from_stack));
   };
-  int32_t old_last = -1;
-  if (nb_old > 0) {
-    int s = table_seg(nb_old - 1);
-    int32_t off = __shfl(seg_off, s);
-    old_last = D.slab[off + (nb_old - 1 - table_seg_first(s))];
-  }
-
-  for (uint32_t j0 = 0; j0 < count; j0 += kWave) {
-    uint32_t jl = j0 + lane;
-    bool valid = jl < count;
-    uint32_t bi = nb_old + (valid ? jl : 0);  // chain index
-    int s = table_seg(bi);
-    int32_t off = __shfl(seg_off, s);
-    if (valid) {
-      int32_t b = block_of(jl);
-      BlockHeader *h = block_header(D, (uint32_t)b);
-      h->prev = jl > 0 ? block_of(jl - 1) : old_last;
-      h->next = jl + 1 < count ? block_of(jl + 1) : -1;
-      h->owner = list;
-      h->seq = (int32_t)bi;
-      h->capacity = (int32_t)T;
-      h->size = 0;
-      D.slab[off + (bi - table_seg_first(s))] = b;
-      if (jl == 0 && old_last >= 0) block_header(D, (uint32_t)old_last)->next = b;
+  for (uint32_t b = (uint32_t)tid; b < total; b += T) {
+    int lo = 0, hi = T - 1;  // whose block it is: the last thread whose blocks start at or before b
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (sh.first[mid] <= b) lo = mid; else hi = mid - 1;
     }
+    const uint32_t jl = b - sh.first[lo], bi = sh.nb_old[lo] + jl;
+    const bool more = b + 1 < total && (lo == T - 1 || sh.first[lo + 1] > b + 1);
+    const int32_t me = block_of(b), before = jl > 0 ? block_of(b - 1) : sh.old_last[lo];
+    BlockHeader *h = block_header(D, (uint32_t)me);
+    h->prev = before;
+    h->next = more ? block_of(b + 1) : -1;
+    h->owner = sh.list[lo];
+    h->seq = (int32_t)bi;
+    h->capacity = (int32_t)Tm;
+    h->size = 0;
+    *table_entry(D, sh.list[lo], bi) = me;
+    if (jl == 0 && before >= 0) block_header(D, (uint32_t)before)->next = me;
   }
-  if (lane == 0) D.nblk[list] = nb_new;
+  if (count) D.nblk[list] = nb_new;
+  return true;
 }
 
-// ---- fill: thread (vector i, chunk c) writes chunk c (16 bytes: 4 floats, 8 halves or 16 bytes)
-// of vector i to its slot; the thread of chunk 0 also writes the id.
+__global__ __launch_bounds__(256) void k_open(Dev D) {
+  __shared__ OpenShared<256> sh;
+  const int list = blockIdx.x * blockDim.x + threadIdx.x;
+  const bool on = list < D.nlist;
+  wg_open<256>(D, on ? list : -1, on ? D.nblk[list] : 0u, on ? D.reserved_len[list] : 0u, sh);
+}
+
+// ---- fill: chunk c (16 bytes: 4 floats, 8 halves or 16 bytes) of a vector, as the lists keep it
+__device__ inline float4 stored_chunk(const Dev &D, const float4 *__restrict__ y, int c) {
+  if (D.storage == 1) {
+    const float4 a = y[2 * c], e = y[2 * c + 1];
+    return make_float4(__uint_as_float(pack_halves(a.x, a.y)), __uint_as_float(pack_halves(a.z, a.w)),
+                       __uint_as_float(pack_halves(e.x, e.y)), __uint_as_float(pack_halves(e.z, e.w)));
+  }
+  if (D.storage == 2)
+    return make_float4(__uint_as_float(pack_bytes(y[4 * c])), __uint_as_float(pack_bytes(y[4 * c + 1])),
+                       __uint_as_float(pack_bytes(y[4 * c + 2])), __uint_as_float(pack_bytes(y[4 * c + 3])));
+  return y[c];
+}
+
+// thread (vector i, chunk c) writes the chunk to its slot; the thread of chunk 0 also writes the id
 __global__ __launch_bounds__(256) void k_fill(Dev D, int64_t n, const float *__restrict__ Y,
                                               const int64_t *__restrict__ ids, int64_t id_base,
                                               const int32_t *__restrict__ assign,
@@ -157,60 +208,167 @@ __global__ __launch_bounds__(256) void k_fill(Dev D, int64_t n, const float *__r
   uint32_t mid = pos / (uint32_t)D.T_m, moff = pos % (uint32_t)D.T_m;
   if (mid >= D.nblk[list]) return;  // the block could not be opened (pool exhausted)
   uint32_t b = (uint32_t)*table_entry(D, list, mid);
-  const float4 *y = reinterpret_cast<const float4 *>(Y) + i * D.d4;
-  float4 v;
-  if (D.storage == 1) {
-    const float4 a = y[2 * c], e = y[2 * c + 1];
-    v = make_float4(__uint_as_float(pack_halves(a.x, a.y)), __uint_as_float(pack_halves(a.z, a.w)),
-                    __uint_as_float(pack_halves(e.x, e.y)), __uint_as_float(pack_halves(e.z, e.w)));
-  } else if (D.storage == 2) {
-    v = make_float4(__uint_as_float(pack_bytes(y[4 * c])), __uint_as_float(pack_bytes(y[4 * c + 1])),
-                    __uint_as_float(pack_bytes(y[4 * c + 2])), __uint_as_float(pack_bytes(y[4 * c + 3])));
-  } else {
-    v = y[c];
-  }
-  block_vecs(D, b)[vec_chunk_index(D, moff, c)] = v;
+  block_vecs(D, b)[vec_chunk_index(D, moff, c)] = stored_chunk(D, reinterpret_cast<const float4 *>(Y) + i * D.d4, c);
   if (c == 0) block_ids(D, b)[moff] = ids ? ids[i] : id_base + i;
 }
 
-// ---- publish: one thread per list makes the batch visible and evaluates
-// Exceed() (the equation defining it: vectors appended since the last
-// rearrangement, strictly greater than T_m').
+// ---- publish: makes the batch visible and evaluates Exceed() (the equation defining it: vectors appended since the
+// last rearrangement, strictly greater than T_m'), a list to a thread of the workgroup (list -1: none).  Everything
+// a list needs is asked for at once; the sums over the lists go out with one atomic per wavefront (one per list on
+// the same words, a chain of round trips per list and words written to host memory in front of the fences made
+// this the longest of the insertion kernels); and what the host is told is written last.
+__device__ inline void wg_publish(const Dev &D, int list) {
+  const uint32_t T = (uint32_t)D.T_m;
+  uint32_t newlen = 0, added = 0, told_exceed = 0;
+  if (list >= 0) {
+    newlen = D.reserved_len[list];
+    const uint32_t old = D.visible_len[list], on0 = D.online[list];
+    const bool exceeds = D.exceed[list] != 0, failed = pool_failed(D);
+    if (newlen == old) {
+      newlen = 0;
+    } else if (failed) {  // the batch is dropped as a whole
+      D.reserved_len[list] = old;
+      newlen = 0;
+    } else {
+      for (uint32_t bi = old / T; bi <= (newlen - 1) / T; ++bi) {
+        uint32_t b = (uint32_t)*table_entry(D, list, bi);
+        uint32_t sz = newlen - bi * T;
+        block_header(D, b)->size = (int32_t)(sz < T ? sz : T);
+      }
+      added = newlen - old;
+      D.online[list] = on0 + added;
+      if (D.T_mp > 0 && (int64_t)(on0 + added) > D.T_mp && !exceeds) {
+        D.exceed[list] = 1;
+        told_exceed = atomicAdd(&D.ctrl->exceed_lists, 1u) + 1u;
+      }
+      __hip_atomic_store(&D.visible_len[list], newlen, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+  uint32_t longest = newlen, sum = added;  // (a batch of one insertion round holds fewer than 2^32 vectors)
+  for (int o = kWave / 2; o > 0; o >>= 1) {
+    longest = max(longest, (uint32_t)__shfl_xor((int)longest, o));
+    sum += __shfl_xor(sum, o);
+  }
+  if (told_exceed) D.mirror->exceed_lists = told_exceed;
+  if ((threadIdx.x & (kWave - 1)) == 0 && sum) {
+    atomicAdd(&D.ctrl->ntotal, (unsigned long long)sum);
+    const uint32_t m = atomicMax(&D.ctrl->max_len, longest);
+    if (longest > m) D.mirror->max_len = longest;
+  }
+}
+
+// The allocator's counters are final for this batch (every block is open, and every rearrangement
+// round enqueued before it has returned its spare blocks): the host learns the blocks in use.
+__device__ inline void report_pool(const Dev &D, uint32_t call_seq) {
+  const int32_t f = __hip_atomic_load(&D.ctrl->free_top, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint32_t in_use =
+      __hip_atomic_load(&D.ctrl->cur_P, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - (uint32_t)(f > 0 ? f : 0);
+  D.mirror->pool_word = ((unsigned long long)call_seq << 32) | in_use;
+}
+
 __global__ __launch_bounds__(256) void k_publish(Dev D, uint32_t call_seq) {
   int list = blockIdx.x * blockDim.x + threadIdx.x;
-  // The allocator's counters are final for this batch (k_open has finished, and every rearrangement
-  // round enqueued before it has returned its spare blocks): the host learns the blocks in use.
-  if (list == 0) {
-    const int32_t f = D.ctrl->free_top;
-    const uint32_t in_use = D.ctrl->cur_P - (uint32_t)(f > 0 ? f : 0);
-    D.mirror->pool_word = ((unsigned long long)call_seq << 32) | in_use;
-  }
-  if (list >= D.nlist) return;
-  uint32_t newlen = D.reserved_len[list];
-  uint32_t old = D.visible_len[list];
-  if (newlen == old) return;
-  if (D.ctrl->error != 0) {  // the batch is dropped as a whole
-    D.reserved_len[list] = old;
-    return;
-  }
+  wg_publish(D, list < D.nlist ? list : -1);
+  if (list == 0) report_pool(D, call_seq);
+}
+
+// ---- a batch of up to kTailVecs vectors behind its coarse scores: one workgroup, a vector to a thread.  The vector
+// that took the first new position of its list looks after the list.  What bounds an online batch is the number of
+// launches (each costs the host 4 us, and the chip a start and an end) and then the chain of round trips to memory:
+// reservation, opening, filling and publication as kernels of their own took 25 us per batch of 64 x 128, all of it
+// the host's.  So what does not depend on the step before is asked for ahead of it: the vectors themselves, and the
+// block a position falls into where that block is there already.
+// splits > 0: the lists and positions are still to be had from the partial minima; 0: they are in assign and did.
+// FILL: the vectors are few enough for one workgroup to move (tail_fills), and the batch is published here.
+template <bool FILL>
+__global__ __launch_bounds__(kTailVecs) void k_insert_tail(Dev D, int n, int splits, const double *__restrict__ pscore,
+                                                           const int32_t *__restrict__ pidx,
+                                                           const float *__restrict__ Y,
+                                                           const int64_t *__restrict__ ids, int64_t id_base,
+                                                           int32_t *__restrict__ assign, uint32_t *__restrict__ did,
+                                                           uint32_t call_seq) {
+  __shared__ OpenShared<kTailVecs> sh;
+  __shared__ uint32_t s_blk[kTailVecs], s_off[kTailVecs];  // where every vector goes (block ~0: nowhere)
+  constexpr int kAhead = 4;  // chunks of the batch a thread has in registers from the start
+  const int tid = threadIdx.x;
   const uint32_t T = (uint32_t)D.T_m;
-  for (uint32_t bi = old / T; bi <= (newlen - 1) / T; ++bi) {
-    uint32_t b = (uint32_t)*table_entry(D, list, bi);
-    uint32_t sz = newlen - bi * T;
-    block_header(D, b)->size = (int32_t)(sz < T ? sz : T);
+  const float4 *__restrict__ y4 = reinterpret_cast<const float4 *>(Y);
+  const int chunks = n * D.vchunks;
+  float4 ahead[kAhead];
+  if (FILL && D.storage == 0) {
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+      ahead[u] = tid + u * kTailVecs < chunks ? y4[tid + u * kTailVecs] : make_float4(0.f, 0.f, 0.f, 0.f);
   }
-  uint32_t on = D.online[list] + (newlen - old);
-  D.online[list] = on;
-  if (D.T_mp > 0 && (int64_t)on > D.T_mp && !D.exceed[list]) {
-    D.exceed[list] = 1;
-    uint32_t e = atomicAdd(&D.ctrl->exceed_lists, 1u);
-    D.mirror->exceed_lists = e + 1;
+  int64_t id = 0;
+  if (FILL && tid < n) id = ids ? ids[tid] : id_base + tid;
+  int list = -1;
+  uint32_t pos = 0, vis = 0, nb = 0;
+  if (tid < n) {
+    if (splits > 0) list = best_of_splits(D, tid, splits, pscore, pidx);
+    else list = assign[tid];
+    vis = D.visible_len[list];
+    nb = D.nblk[list];
+    if (splits > 0) pos = atomicAdd(&D.reserved_len[list], 1u);
+    else pos = did[tid];
+    if (!FILL && splits > 0) { assign[tid] = list; did[tid] = pos; }
   }
-  uint32_t m = atomicMax(&D.ctrl->max_len, newlen);
-  if (newlen > m) D.mirror->max_len = newlen;
-  atomicAdd(&D.ctrl->ntotal, (unsigned long long)(newlen - old));
-  __threadfence();
-  __hip_atomic_store(&D.visible_len[list], newlen, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+  const bool leads = tid < n && pos == vis;
+  const uint32_t mid = pos / T;
+  uint32_t blk = ~0u;
+  __syncthreads();  // every position is taken
+  if (FILL && tid < n && mid < nb) blk = (uint32_t)*table_entry(D, list, mid);
+  const uint32_t newlen = leads ? D.reserved_len[list] : 0u;
+  const bool opened = wg_open<kTailVecs>(D, leads ? list : -1, nb, newlen, sh);
+  if (!FILL) return;  // uniform
+  if (opened) {  // uniform
+    __syncthreads();
+    if (tid < n && mid >= nb && mid < D.nblk[list]) blk = (uint32_t)*table_entry(D, list, mid);
+  }
+  if (tid < n) {
+    s_blk[tid] = blk;
+    s_off[tid] = pos % T;
+    if (blk != ~0u) block_ids(D, blk)[pos % T] = id;
+  }
+  __syncthreads();
+  auto put = [&](int t, int i, int c, const float4 &v) {
+    if (s_blk[i] != ~0u) block_vecs(D, s_blk[i])[vec_chunk_index(D, s_off[i], c)] = v;
+  };
+  int t = tid;
+  if (D.storage == 0) {
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u, t += kTailVecs)
+      if (t < chunks) { const int i = t / D.vchunks; put(t, i, t - i * D.vchunks, ahead[u]); }
+  }
+  for (; t < chunks; t += kTailVecs) {
+    const int i = t / D.vchunks, c = t - i * D.vchunks;
+    put(t, i, c, stored_chunk(D, y4 + (size_t)i * D.d4, c));
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's part of the vectors is out ...
+  __syncthreads();                                  // ... and so is everybody's before any list is published
+  wg_publish(D, leads ? list : -1);
+  if (tid == 0) report_pool(D, call_seq);
+}
+
+// ... and the opening and the publication of a larger batch, a vector to a thread, in several workgroups (a thousand
+// leaders' scattered reads and writes keep one compute unit busy for longer than a launch costs).  Whoever leads a
+// list is settled by its position alone: a length that is published meanwhile lies beyond every position of the batch.
+__device__ inline int led_list(const Dev &D, int n, const int32_t *__restrict__ assign, const uint32_t *__restrict__ did) {
+  const int i = blockIdx.x * kBatchThreads + threadIdx.x;
+  if (i >= n) return -1;
+  const int list = assign[i];
+  return did[i] == D.visible_len[list] ? list : -1;
+}
+__global__ __launch_bounds__(kBatchThreads) void k_open_batch(Dev D, int n, const int32_t *__restrict__ assign,
+                                                              const uint32_t *__restrict__ did) {
+  __shared__ OpenShared<kBatchThreads> sh;
+  const int list = led_list(D, n, assign, did);
+  wg_open<kBatchThreads>(D, list, list >= 0 ? D.nblk[list] : 0u, list >= 0 ? D.reserved_len[list] : 0u, sh);
+}
+__global__ __launch_bounds__(kBatchThreads) void k_publish_batch(Dev D, int n, const int32_t *__restrict__ assign,
+                                                                 const uint32_t *__restrict__ did, uint32_t call_seq) {
+  wg_publish(D, led_list(D, n, assign, did));
+  if (blockIdx.x == 0 && threadIdx.x == 0) report_pool(D, call_seq);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -230,7 +388,7 @@ void launch_reserve_ordered(const Dev &D, int64_t n, const InsertScratch &S, hip
 }
 
 void launch_open(const Dev &D, hipStream_t s) {
-  unsigned grid = (unsigned)((D.nlist + 3) / 4);
+  unsigned grid = (unsigned)((D.nlist + 255) / 256);
   hipLaunchKernelGGL(k_open, dim3(grid), dim3(256), 0, s, D);
 }
 
@@ -240,6 +398,29 @@ void launch_fill(const Dev &D, int64_t n, const float *Y, const int64_t *ids, in
   int64_t threads = n * D.vchunks;
   unsigned grid = (unsigned)((threads + 255) / 256);
   hipLaunchKernelGGL(k_fill, dim3(grid), dim3(256), 0, s, D, n, Y, ids, id_base, S.assign, S.did);
+}
+
+// How much one workgroup moves before a launch of its own is faster, in 16-byte chunks: what its threads hold in
+// registers from the start (64 x 768 floats, three times that: 25 us inside against 9 for the two launches).
+constexpr int64_t kTailChunks = 4 * kTailVecs;
+bool tail_fills(const Dev &D, int64_t n) { return n <= kTailVecs && D.pq_m == 0 && n * D.vchunks <= kTailChunks; }
+
+void launch_insert_tail(const Dev &D, int64_t n, int splits, const float *Y, const int64_t *ids, int64_t id_base,
+                        const InsertScratch &S, uint32_t call_seq, hipStream_t s) {
+  const dim3 batch((unsigned)((n + kBatchThreads - 1) / kBatchThreads));
+  if (tail_fills(D, n))
+    hipLaunchKernelGGL(k_insert_tail<true>, dim3(1), dim3(kTailVecs), 0, s, D, (int)n, splits, S.pscore, S.pidx, Y, ids,
+                       id_base, S.assign, S.did, call_seq);
+  else if (splits > 0)
+    hipLaunchKernelGGL(k_insert_tail<false>, dim3(1), dim3(kTailVecs), 0, s, D, (int)n, splits, S.pscore, S.pidx, Y,
+                       ids, id_base, S.assign, S.did, call_seq);
+  else
+    hipLaunchKernelGGL(k_open_batch, batch, dim3(kBatchThreads), 0, s, D, (int)n, S.assign, S.did);
+}
+
+void launch_publish_batch(const Dev &D, int64_t n, const InsertScratch &S, uint32_t call_seq, hipStream_t s) {
+  const dim3 batch((unsigned)((n + kBatchThreads - 1) / kBatchThreads));
+  hipLaunchKernelGGL(k_publish_batch, batch, dim3(kBatchThreads), 0, s, D, (int)n, S.assign, S.did, call_seq);
 }
 
 void launch_publish(const Dev &D, uint32_t call_seq, hipStream_t s) {

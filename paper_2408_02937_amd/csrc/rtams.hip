@@ -381,11 +381,12 @@ int acquire(rtams_index *ix) {
 // Nearest centroid of m vectors (m <= max_add_batch) and, if asked, the slot
 // reservation.  A batch that is a large dense contraction gets approximate
 // scores on the matrix cores, then exact refinement of what they cannot tell
-// apart; smaller batches go through the exact kernel alone.
-void assign_round(rtams_index *ix, int64_t m, const float *Y, bool reserve, int32_t *assign_out, hipStream_t s) {
+// apart; smaller batches go through the exact kernel alone.  With `defer` the reservation behind the exact kernel is
+// left to the caller: the number of partial minima per vector is returned, otherwise 0.
+int assign_round(rtams_index *ix, int64_t m, const float *Y, bool reserve, bool defer, int32_t *assign_out, hipStream_t s) {
   const Dev &D = ix->dev;
   const int64_t mode = ix->use_mfma.load(std::memory_order_relaxed);  // 0 never, 1 when it pays, 2 from 32 rows
-  if (mode == 2 ? m >= 32 : mode == 1 && mfma_pays_for_assign(m, D.nlist)) {
+  if (mode == 2 ? m >= 32 : mode == 1 && mfma_pays_for_assign(m, D.nlist, D.d)) {
     for (int64_t o = 0; o < m; o += ix->ins.tile_rows) {
       const int64_t mm = m - o < ix->ins.tile_rows ? m - o : ix->ins.tile_rows;
       launch_coarse_tiles(D, mm, Y + (size_t)o * D.d, ix->ins.yhalf, ix->ins.ymeta, ix->ins.tiles, s);
@@ -394,8 +395,10 @@ void assign_round(rtams_index *ix, int64_t m, const float *Y, bool reserve, int3
   } else {
     int splits = coarse_splits(D, m, ix->ins.part_cap);
     launch_coarse_argmin(D, m, Y, splits, ix->ins.pscore, ix->ins.pidx, s);
+    if (defer) return splits;
     launch_reserve(D, m, splits, ix->ins, reserve, assign_out, s);
   }
+  return 0;
 }
 
 int read_ctrl(rtams_index *ix, Ctrl *out) {
@@ -711,17 +714,25 @@ int rtams_add(rtams_index *ix, int64_t n, const float *d_vecs, const int64_t *d_
   for (int64_t o = 0; o < n; o += round) {
     int64_t m = n - o < round ? n - o : round;
     const float *Y = d_vecs + (size_t)o * D.d;
+    const int64_t *ids = d_ids ? d_ids + o : nullptr;
+    const int64_t id_base = ix->ntotal_host + o;
+    // only its last round completes the call: the rounds before it report under the call before
+    const uint32_t report = o + round >= n ? seq : seq - 1u;
+    const bool small = m <= kTailVecs;
+    int splits = 0;
     if (ordered) {
-      assign_round(ix, m, Y, false, ix->ins.assign, s);
+      assign_round(ix, m, Y, false, false, ix->ins.assign, s);
       launch_reserve_ordered(D, m, ix->ins, s);
     } else {
-      assign_round(ix, m, Y, true, ix->ins.assign, s);
+      splits = assign_round(ix, m, Y, true, small, ix->ins.assign, s);
     }
-    launch_open(D, s);
-    if (D.pq_m > 0) launch_pq_fill(D, m, Y, d_ids ? d_ids + o : nullptr, ix->ntotal_host + o, ix->ins, s);
-    else launch_fill(D, m, Y, d_ids ? d_ids + o : nullptr, ix->ntotal_host + o, ix->ins, s);
-    // only its last round completes the call: the rounds before it report under the call before
-    launch_publish(D, o + round >= n ? seq : seq - 1u, s);
+    if (small) launch_insert_tail(D, m, splits, Y, ids, id_base, ix->ins, report, s);
+    else launch_open(D, s);
+    if (small && tail_fills(D, m)) continue;  // filled and published
+    if (D.pq_m > 0) launch_pq_fill(D, m, Y, ids, id_base, ix->ins, s);
+    else launch_fill(D, m, Y, ids, id_base, ix->ins, s);
+    if (small) launch_publish_batch(D, m, ix->ins, report, s);
+    else launch_publish(D, report, s);
   }
   HIP_TRY(hipGetLastError());
   ix->avail_lb -= need;
@@ -946,7 +957,7 @@ int rtams_assign(rtams_index *ix, int64_t n, const float *d_vecs, int32_t *d_out
   const int64_t round = ix->cfg.max_add_batch;
   for (int64_t o = 0; o < n; o += round) {
     int64_t m = n - o < round ? n - o : round;
-    assign_round(ix, m, d_vecs + (size_t)o * ix->dev.d, false, d_out + o, s);
+    assign_round(ix, m, d_vecs + (size_t)o * ix->dev.d, false, false, d_out + o, s);
   }
   HIP_TRY(hipGetLastError());
   return RTAMS_OK;

@@ -133,13 +133,15 @@ void launch_coarse_argmin(const Dev &D, int64_t n, const float *Y, int splits, d
 // coarse_mfma.hip ------------------------------------------------------------
 // When the matrix-core filter runs in front of the exact coarse arithmetic: the
 // batch has to be a dense contraction large enough to repay the extra kernel and
-// the refinement (measured crossovers on MI355X, d = 128 and 768: about 1 M (query,
-// centroid) pairs for a search and for an assignment alike).
+// the refinement (measured crossover on MI355X, d = 128 and 768: about 1 M (query,
+// centroid) pairs for a search).
 inline bool mfma_pays_for_search(int64_t nq, int64_t nlist) { return nq >= 32 && nq * nlist >= (int64_t)1 << 20; }
-// (an assignment used to pay from half as many pairs where there are 8192 centroids or more; since the
-// exact kernel takes two centroids to a thread it does not: 64 vectors against 8,192 x 768 centroids
-// are assigned at 0.91 M vectors/s by the exact kernel alone and at 0.78 M through the filter)
-inline bool mfma_pays_for_assign(int64_t m, int64_t nlist) { return m >= 32 && m * nlist >= (int64_t)1 << 20; }
+// An assignment pays from 2^20 pairs, or from 2^26 coordinates of them (measured per insertion batch, exact against
+// filter: 64 x 8,192 x 768 69 and 40 us, 32 x 16,384 x 256 48 and 31, 64 x 8,192 x 128, 64 x 2,048 x 768 and 512 x
+// 1,024 x 128 the same within 2 us, 64 x 2,048 x 128 20 and 30).
+inline bool mfma_pays_for_assign(int64_t m, int64_t nlist, int64_t d) {
+  return m >= 32 && (m * nlist >= (int64_t)1 << 20 || m * nlist * d >= (int64_t)1 << 26);
+}
 // 16-byte units the halves of `rows` rows take: whole blocks of 16 rows
 __host__ __device__ inline size_t half_units(int64_t rows, int dgroups) { return (size_t)((rows + 15) / 16 * 16) * dgroups; }
 // a request's RowMeta behind the halves of its n queries (32 of them at least: the room is 32 dgroups bytes a query)
@@ -165,6 +167,13 @@ void launch_open(const Dev &D, hipStream_t s);
 void launch_fill(const Dev &D, int64_t n, const float *Y, const int64_t *ids, int64_t id_base,
                  const InsertScratch &S, hipStream_t s);
 void launch_publish(const Dev &D, uint32_t call_seq, hipStream_t s);
+// A batch of at most kTailVecs vectors: reservation (splits > 0: from the partial minima; 0: done), opening and,
+// where tail_fills() says so, filling and publication; otherwise a fill and launch_publish_batch follow.
+constexpr int kTailVecs = 1024;
+bool tail_fills(const Dev &D, int64_t n);
+void launch_insert_tail(const Dev &D, int64_t n, int splits, const float *Y, const int64_t *ids, int64_t id_base,
+                        const InsertScratch &S, uint32_t call_seq, hipStream_t s);
+void launch_publish_batch(const Dev &D, int64_t n, const InsertScratch &S, uint32_t call_seq, hipStream_t s);
 
 // probe.hip, group.hip, scan.hip, pq_scan.hip, select.hip ---------------------
 void launch_probe_plan(const Dev &D, int64_t nq, int nprobe, int max_nprobe, const SearchScratch &S,
