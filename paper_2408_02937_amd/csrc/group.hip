@@ -56,8 +56,8 @@ __device__ void sample_scores(const Dev &D, int nprobe, int max_nprobe, int q, u
       const float4 *__restrict__ x = block_vecs(D, b) + (size_t)(g % gpb) * group_stride + lane;
       float acc = 0.f;
       int c = 0;
-      if (METRIC == 1 && ST == 0 && D.scan_mfma) {
-        // inner products of float lists on the matrix cores, exactly as the scan computes them (same
+      if (METRIC == 1 && D.scan_mfma) {
+        // inner products on the matrix cores, exactly as the scan computes them (same
         // instruction, same order of the coordinates), so that a candidate's score here and there is
         // the same bits: every lane offers the one query, component l % 4 of the result is the score
         // of the lane's own vector
@@ -67,9 +67,15 @@ __device__ void sample_scores(const Dev &D, int nprobe, int max_nprobe, int q, u
 #pragma unroll
           for (int u = 0; u < 8; ++u) v[u] = x[(size_t)(c + u) * kWave];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) mfma_chunk(m, v[u], qv[c + u]);
+          for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int s = 0; s < kPieces; ++s) mfma_chunk(m, chunk_piece<ST>(v[u], s), qv[(c + u) * kPieces + s]);
         }
-        for (; c < d4; ++c) mfma_chunk(m, x[(size_t)c * kWave], qv[c]);
+        for (; c < d4; ++c) {
+          const float4 v = x[(size_t)c * kWave];
+#pragma unroll
+          for (int s = 0; s < kPieces; ++s) mfma_chunk(m, chunk_piece<ST>(v, s), qv[c * kPieces + s]);
+        }
         const int r = lane & 3;
         acc = r == 0 ? m[0] : r == 1 ? m[1] : r == 2 ? m[2] : m[3];
       }
@@ -182,7 +188,7 @@ __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, in
   if (qtotal <= no_bound_below) {  // uniform over the workgroup
     if (tid == 0) {
       S.bound[q] = 0xFFFFFFFFu;
-      S.rec_cnt[q] = 0u;
+      *rec_count(S, (uint32_t)q) = 0u;
     }
     return;
   }
@@ -228,7 +234,7 @@ __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, in
     // the sample's scores are direct-form ones; the scan may compare norm-form scores with the bound
     if (norm_form) bound = loosened_key(bound, norm_form_slack(D.d), s_qn);
     S.bound[q] = bound;
-    S.rec_cnt[q] = 0u;
+    *rec_count(S, (uint32_t)q) = 0u;
   }
 }
 

@@ -23,7 +23,7 @@ constexpr int kPqStage = 128;  // survivors a wavefront collects in LDS before i
 __device__ inline void pq_flush(const SearchScratch &S, int q, unsigned long long base, const uint32_t *my_key,
                                 const uint32_t *my_pos, uint32_t n, int lane) {
   uint32_t at = 0;
-  if (lane == 0) at = atomicAdd(&S.rec_cnt[q], n);
+  if (lane == 0) at = atomicAdd(rec_count(S, (uint32_t)q), n);
   at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
   uint32_t *rk = rec_keys_of(S, base) + at, *rp = rec_poss_of(S, base) + at;
   for (uint32_t i = (uint32_t)lane; i < n; i += kWave) {
@@ -172,7 +172,7 @@ __global__ __launch_bounds__(kPqScanThreads) void k_pq_scan(Dev D, int nprobe, i
       }
       if (n_keep > (uint32_t)kPqStage) {  // more than the slice holds: straight out
         uint32_t at = 0;
-        if (lane == 0) at = atomicAdd(&S.rec_cnt[q], n_keep);
+        if (lane == 0) at = atomicAdd(rec_count(S, (uint32_t)q), n_keep);
         at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
         const unsigned long long below = (1ull << lane) - 1ull;
         uint32_t *rk = rec_keys_of(S, base) + at, *rp = rec_poss_of(S, base) + at;

@@ -569,7 +569,9 @@ int rtams_create(const rtams_config *cfg, rtams_index **out) {
     S.bound = reinterpret_cast<uint32_t *>(p + SL.bound);
     S.qnorm = reinterpret_cast<float *>(p + SL.qnorm);
     S.qhalf = reinterpret_cast<u32x4 *>(p + SL.qhalf);
-    S.rec_cnt = reinterpret_cast<uint32_t *>(p + SL.rec_cnt);
+    const bool lines = cfg->nlist >= 16;  // a query's row of scores holds a cache line
+    S.rec_cnt = reinterpret_cast<uint32_t *>(p + (lines ? SL.scores : SL.rec_cnt));
+    S.rec_shift = lines ? 5 : 0;
     S.cursor = reinterpret_cast<unsigned long long *>(p + SL.cursor);
     S.list_cnt = reinterpret_cast<uint32_t *>(p + SL.list_cnt);
     S.pair_start = reinterpret_cast<uint32_t *>(p + SL.pair_start);
@@ -766,18 +768,11 @@ static int search_on(rtams_index *ix, int r, int64_t nq, const float *d_queries,
                      float *d_out_dist, int64_t *d_out_ids, void *hip_stream) {
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   Dev D = ix->dev;
-  {  // flat float lists: requests whose tiles hold several queries scan on the matrix cores (0 never, 1 by the rule below, 2 always)
+  {  // flat lists: which unit scans (0 the vector unit, 1 by the rule, 2 the matrix cores)
     const int64_t mode = ix->scan_mfma.load(std::memory_order_relaxed);
-    // A tile is the queries of the request that probe one list.  With at least as many (query, list)
-    // pairs as lists, or with a list far longer than the average (a hot list is probed by a good
-    // share of any batch and holds most of the bytes), tiles of several queries do most of the work:
-    // that is what the matrix-core kernel is for.  A request whose pairs spread thinly over many lists
-    // of similar length has tiles of one query each and is better off on the vector unit (measured:
-    // 64 queries x 32 probes over 8,192 lists of 768 dimensions, 643 against 667 us).
     const int64_t avg_len = ix->ntotal_host / ix->cfg.nlist + 1;
-    const bool shared = nq * nprobe >= ix->cfg.nlist || (int64_t)ix->mirror->max_len >= 16 * avg_len;
-    D.scan_mfma = D.pq_m == 0 && D.storage == RTAMS_F32 &&
-                  (mode == 2 || (mode == 1 && nq >= kMmMinBatch && shared));
+    D.scan_mfma = D.pq_m == 0 && (mode == 2 || (mode == 1 && nq >= kMmMinBatch &&
+                                                mm_scan_pays(D, nq, nprobe, avg_len, (int64_t)ix->mirror->max_len)));
   }
   D.scan_byte_weight = (int32_t)ix->scan_byte_weight.load(std::memory_order_relaxed);
   D.scan_min_choice = (int32_t)ix->scan_min_choice.load(std::memory_order_relaxed);
@@ -799,6 +794,22 @@ static int search_on(rtams_index *ix, int r, int64_t nq, const float *d_queries,
   const int64_t cap = ix->scan_max_items.load(std::memory_order_relaxed);
   if (budget > cap) budget = cap;
   if (budget < nq * nprobe) budget = nq * nprobe;  // a (query, list) pair is at least one item
+  // ... but never more than the plan can want at its shortest segments, lists being as long as the host knows: the scan
+  // is launched for the whole budget, and workgroups that find their range of items used up each take a place on the
+  // chip and a trip to memory (256 queries x 32 probes over 1 M x 128: 49,152 workgroups for 2,048 items).  Lists that
+  // grow meanwhile get longer segments.
+  if (D.pq_m == 0) {
+    const ScanShape sh = scan_shape(D, (int)budget);
+    const int64_t seg_vecs = (int64_t)kWave * (2 << sh.min_choice);
+    const int64_t probed = nq * nprobe < ix->cfg.nlist ? nq * nprobe : ix->cfg.nlist;
+    const int64_t longest = (int64_t)ix->mirror->max_len;
+    int64_t segs = ix->ntotal_host / seg_vecs + probed;  // of the probed lists together, every one rounded up
+    const int64_t by_longest = probed * (longest / seg_vecs + 1);
+    if (by_longest < segs) segs = by_longest;
+    // one tile to every segment, and another wherever a list is probed by that many more queries
+    const int64_t most = segs + nq * nprobe / sh.tile_q * (longest / seg_vecs + 1);
+    if (budget > most) budget = most;
+  }
   if (budget < 1024) budget = 1024;
   launch_group(D, nq, nprobe, ix->cfg.max_nprobe, k, d_queries, (int)budget, S, s);
   const bool timed = ix->profile_scan.load(std::memory_order_relaxed) != 0;

@@ -33,7 +33,8 @@ struct SearchScratch {
   uint32_t *bound;      // [max_batch] key of the score the scan compares with
   float *qnorm;         // [max_batch] squared norms of the queries (norm form of the squared distance)
   u32x4 *qhalf;         // the queries as halves for the matrix-core coarse scores, then their RowMeta (coarse_mfma.hip)
-  uint32_t *rec_cnt;    // [max_batch] survivors recorded so far
+  uint32_t *rec_cnt;    // survivors recorded so far, of query q at rec_cnt[q << rec_shift] (rec_count())
+  int rec_shift;
   unsigned long long *cursor; // bump pointer into the survivor records
   uint32_t *list_cnt;   // [nlist] queries probing each list
   uint32_t *pair_start; // [nlist] where the pairs of a probed list start in `grouped`

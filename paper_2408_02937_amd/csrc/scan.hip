@@ -196,7 +196,7 @@ __device__ __forceinline__ void scan_item(const Dev &D, const SearchScratch &S,
       }
       if (any) {  // uniform.  One atomic per query with survivors, all of them in one instruction
         uint32_t base_mine = 0;
-        if (lane < NQ && n_mine) base_mine = atomicAdd(&S.rec_cnt[my_q], n_mine);
+        if (lane < NQ && n_mine) base_mine = atomicAdd(rec_count(S, my_q), n_mine);
         const unsigned long long below = (1ull << lane) - 1ull;
 #pragma unroll
         for (int i = 0; i < NQ; ++i) {

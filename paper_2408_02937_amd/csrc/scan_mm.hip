@@ -1,4 +1,4 @@
-// The list scan of flat float lists on the matrix cores.
+// The list scan of flat lists on the matrix cores.
 #include "search_common.h"
 
 namespace rtams {
@@ -45,18 +45,23 @@ static_assert(sizeof(WaveStage) == kMmStageBytes, "staging bytes per wavefront")
 
 // The groups g_lo + wave, g_lo + wave + 4, ... below g_hi of the list against QG groups of four queries.
 // first_b: the block that holds the wavefront's first group (looked up by the caller).
-template <int METRIC, int QG>
+// ST: what the lists keep.  A 16-byte chunk of halves or bytes is widened in registers, one float4 of coordinates at a
+// time, each against the matching float4 of the queries: the conversions run beside the matrix instructions, where
+// the vector-unit kernel has them in front of its own arithmetic (256 queries x 32 probes over 1 M x 128 bytes: 114 us
+// there, bound by instruction issue, for 129 MB of lists).
+template <int METRIC, int QG, int ST>
 __device__ __forceinline__ void scan_groups_mm(const Dev &D, const SearchScratch &S, int list, uint32_t g_lo,
                                                uint32_t g_hi, uint32_t first_b, const float4 *qs,
                                                const TileQuery *tq, WaveStage &st) {
   constexpr int kPrefetch = 4;  // chunks per register set: 8 KiB of loads in flight per wavefront
-  const int d4 = D.d4;
-  const int qstride = d4 + 1;  // float4s between two queries in LDS: an odd stride keeps the four rows a read touches on different banks
+  constexpr int kPieces = pieces_of(ST);
+  const int vc = D.vchunks;
+  const int qstride = D.d4 + 1;  // float4s between two queries in LDS: an odd stride keeps the four rows a read touches on different banks
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int sub = lane & 3;
   const float4 *__restrict__ qrow = qs + sub * qstride;  // query `sub` of group 0; group g is 4 g rows on
   const uint32_t gpb = (uint32_t)D.groups_per_block;
-  const size_t group_stride = (size_t)d4 * kWave;
+  const size_t group_stride = (size_t)vc * kWave;
   uint32_t staged = 0;  // survivors in the staging area (uniform over the wavefront)
   auto wave_sync = [] {  // LDS operations of one wavefront execute in order; keep the compiler from moving them
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -76,7 +81,7 @@ __device__ __forceinline__ void scan_groups_mm(const Dev &D, const SearchScratch
     wave_sync();
     if (lane < kMmTileMax) {
       const uint32_t c = st.qcnt[lane];
-      st.qbase[lane] = c ? atomicAdd(&S.rec_cnt[tq[lane].q], c) : 0u;  // rows past the tile's last query have none
+      st.qbase[lane] = c ? atomicAdd(rec_count(S, tq[lane].q), c) : 0u;  // rows past the tile's last query have none
     }
     wave_sync();
 #pragma unroll
@@ -98,7 +103,7 @@ __device__ __forceinline__ void scan_groups_mm(const Dev &D, const SearchScratch
   // streamed the block number of the next is looked up, and the first loads of the next go out before
   // the survivors of this one are dealt with, so that neither the two dependent table reads nor the
   // first trip to memory of a group stand between two groups (a quarter of a group's time at d = 128).
-  const int d4_main = d4 & ~(2 * kPrefetch - 1);  // chunks that go through the two register sets
+  const int d4_main = vc & ~(2 * kPrefetch - 1);  // chunks that go through the two register sets
   float4 sa[kPrefetch], sb[kPrefetch];
   auto load_set = [&](float4 *s, const float4 *__restrict__ p, int cb) {
 #pragma unroll
@@ -142,9 +147,16 @@ __device__ __forceinline__ void scan_groups_mm(const Dev &D, const SearchScratch
         for (int g = 0; g < kHalf; ++g) mfma_step(acc[h + g], v.w, y[g].w);
       }
     };
+    auto use_chunk = [&](const float4 &raw, int c) {
+#pragma unroll
+      for (int p = 0; p < kPieces; ++p) {
+        use(chunk_piece<ST>(raw, p), c * kPieces + p);
+        if (kPieces > 1) __builtin_amdgcn_sched_barrier(0);  // one piece's widened values at a time
+      }
+    };
     auto use_set = [&](const float4 *s, int cb) {
 #pragma unroll
-      for (int u = 0; u < kPrefetch; ++u) use(s[u], cb + u);
+      for (int u = 0; u < kPrefetch; ++u) use_chunk(s[u], cb + u);
       __builtin_amdgcn_sched_barrier(0);
     };
     if (d4_main) {  // set a holds chunks 0 .. kPrefetch - 1 of this group already
@@ -160,7 +172,7 @@ __device__ __forceinline__ void scan_groups_mm(const Dev &D, const SearchScratch
       use_set(sa, c);
       use_set(sb, c + kPrefetch);
     }
-    for (int c = d4_main; c < d4; ++c) use(x[(size_t)c * kWave], c);
+    for (int c = d4_main; c < vc; ++c) use_chunk(x[(size_t)c * kWave], c);
     const float4 *x_next = x;
     if (more) {  // the next group's first loads go out before this group's survivors are dealt with
       x_next = place(g_next, next_b);
@@ -178,7 +190,8 @@ __device__ __forceinline__ void scan_groups_mm(const Dev &D, const SearchScratch
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         float sc = acc[g][r];
-        sc = METRIC == 0 ? fmaf(-2.f, sc, nr[r] + me.qn) : -sc;
+        // (an infinite coordinate makes the norm form inf - inf: such a vector is infinitely far, as the direct form has it)
+        sc = METRIC == 0 ? fminf(fmaf(-2.f, sc, nr[r] + me.qn), __builtin_inff()) : -sc;
         key[r] = key_of_float(sc + 0.0f);
         if (vbase + r < me.len && key[r] <= me.bound) pass |= 1u << r;
       }
@@ -224,7 +237,7 @@ __device__ __forceinline__ void scan_groups_mm(const Dev &D, const SearchScratch
 // workgroup that finds nothing leaves.  Short scans keep the plain mapping: the swap is a round trip
 // in front of every item, and the launch has tens of thousands of workgroups that find their range
 // used up and should leave at once (measured at 1 M x 128, 2,048 items: 226 instead of 103 us).
-template <int METRIC, bool STEAL>
+template <int METRIC, bool STEAL, int ST>
 __global__ __launch_bounds__(kMmWaves *kWave) void k_scan_mm(Dev D, int max_nprobe, const float *__restrict__ Q,
                                                              SearchScratch S, int tile_rows) {
   extern __shared__ float4 lds_mm[];  // [tile_rows][d / 4 + 1] coordinates of the tile's queries, [tile_rows] TileQuery, [wavefronts] WaveStage
@@ -350,34 +363,33 @@ __global__ __launch_bounds__(kMmWaves *kWave) void k_scan_mm(Dev D, int max_npro
   if (g_end > g_have) g_end = g_have;
   // no barrier from here on: the wavefronts only read the tile
   switch (qg) {
-    case 1: scan_groups_mm<METRIC, 1>(D, S, list, g_begin, g_end, first_b, qs, tq, st); break;
-    case 2: scan_groups_mm<METRIC, 2>(D, S, list, g_begin, g_end, first_b, qs, tq, st); break;
-    case 3: scan_groups_mm<METRIC, 3>(D, S, list, g_begin, g_end, first_b, qs, tq, st); break;
-    case 4: scan_groups_mm<METRIC, 4>(D, S, list, g_begin, g_end, first_b, qs, tq, st); break;
-    case 6: scan_groups_mm<METRIC, 6>(D, S, list, g_begin, g_end, first_b, qs, tq, st); break;
-    default: scan_groups_mm<METRIC, 8>(D, S, list, g_begin, g_end, first_b, qs, tq, st); break;
+    case 1: scan_groups_mm<METRIC, 1, ST>(D, S, list, g_begin, g_end, first_b, qs, tq, st); break;
+    case 2: scan_groups_mm<METRIC, 2, ST>(D, S, list, g_begin, g_end, first_b, qs, tq, st); break;
+    case 3: scan_groups_mm<METRIC, 3, ST>(D, S, list, g_begin, g_end, first_b, qs, tq, st); break;
+    case 4: scan_groups_mm<METRIC, 4, ST>(D, S, list, g_begin, g_end, first_b, qs, tq, st); break;
+    case 6: scan_groups_mm<METRIC, 6, ST>(D, S, list, g_begin, g_end, first_b, qs, tq, st); break;
+    default: scan_groups_mm<METRIC, 8, ST>(D, S, list, g_begin, g_end, first_b, qs, tq, st); break;
   }
 }
 
 void launch_scan_mm(const Dev &D, const ScanShape &sh, int max_nprobe, const float *Q, const SearchScratch &S,
                     hipStream_t s) {
+  typedef void (*Kernel)(Dev, int, const float *, SearchScratch, int);
+  static const Kernel kernels[2][2][3] = {
+      {{k_scan_mm<0, false, 0>, k_scan_mm<0, false, 1>, k_scan_mm<0, false, 2>},
+       {k_scan_mm<0, true, 0>, k_scan_mm<0, true, 1>, k_scan_mm<0, true, 2>}},
+      {{k_scan_mm<1, false, 0>, k_scan_mm<1, false, 1>, k_scan_mm<1, false, 2>},
+       {k_scan_mm<1, true, 0>, k_scan_mm<1, true, 1>, k_scan_mm<1, true, 2>}}};
   // above 64 KiB of dynamic LDS a kernel has to be told (wide vectors only); once per kernel and process
   static const bool once = [] {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k_scan_mm<0, false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMmLdsMax);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k_scan_mm<1, false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMmLdsMax);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k_scan_mm<0, true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMmLdsMax);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k_scan_mm<1, true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMmLdsMax);
+    for (int i = 0; i < 12; ++i)
+      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernels[i / 6][i / 3 % 2][i % 3]),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMmLdsMax);
     return true;
   }();
   (void)once;
-  const dim3 grid((unsigned)sh.grid), block((unsigned)sh.threads);
-  if (D.scan_steal) {
-    if (D.metric == 0) hipLaunchKernelGGL((k_scan_mm<0, true>), grid, block, sh.lds, s, D, max_nprobe, Q, S, sh.tile_q);
-    else hipLaunchKernelGGL((k_scan_mm<1, true>), grid, block, sh.lds, s, D, max_nprobe, Q, S, sh.tile_q);
-  } else {
-    if (D.metric == 0) hipLaunchKernelGGL((k_scan_mm<0, false>), grid, block, sh.lds, s, D, max_nprobe, Q, S, sh.tile_q);
-    else hipLaunchKernelGGL((k_scan_mm<1, false>), grid, block, sh.lds, s, D, max_nprobe, Q, S, sh.tile_q);
-  }
+  hipLaunchKernelGGL(kernels[D.metric][D.scan_steal ? 1 : 0][D.storage], dim3((unsigned)sh.grid), dim3((unsigned)sh.threads),
+                     sh.lds, s, D, max_nprobe, Q, S, sh.tile_q);
 }
 
 }  // namespace rtams

@@ -19,6 +19,10 @@ __device__ inline uint32_t key_of_float(float x) {
 }
 
 // ------------------------------------------------------- survivor records
+// How many a query has.  Every wavefront of the scan reserves places from these counters, and reservations on one
+// cache line are served one after the other, whichever queries they are for: each counter has a line to itself.
+// (They lie in the room of the exact coarse scores, which nobody reads any more once the probes are chosen.)
+__device__ inline uint32_t *rec_count(const SearchScratch &S, uint32_t q) { return S.rec_cnt + ((size_t)q << S.rec_shift); }
 // Where a query's records lie: in its request's slice or, flagged, in the reserve all resources share.
 __device__ inline uint32_t *rec_keys_of(const SearchScratch &S, unsigned long long qbase) {
   return (qbase & kInOverflow) ? S.ovf_key + (qbase & ~kInOverflow) : S.rec_key + qbase;
@@ -356,9 +360,9 @@ __device__ inline uint32_t loosened_key(uint32_t key, float slack, float qn) {
   if (key == 0xFFFFFFFFu) return key;  // "keep everything"
   return key_of_float(loosened(l2_score_of_key(key), slack, qn) + 0.0f);
 }
-// which lists a request scores through the norm form: flat float lists under the L2 metric
+// which lists a request scores through the norm form: flat lists under the L2 metric
 __device__ __host__ inline bool uses_norm_form(const Dev &D) {
-  return D.scan_mfma != 0 && D.metric == 0 && D.pq_m == 0 && D.storage == 0;
+  return D.scan_mfma != 0 && D.metric == 0 && D.pq_m == 0;
 }
 
 
@@ -370,16 +374,14 @@ constexpr int kScanWaves = 4;
 
 // Launch shape of a list scan.  Two kernels share the plan of work items (list, segment, tile of the
 // queries probing the list):
-//  - vector unit (narrow storage, small requests, or the matrix cores switched off): a workgroup is up
-//    to four wavefronts that take four consecutive items, one each, every one with its own tile of up
-//    to 8 queries in LDS;
-//  - matrix cores (flat float lists, requests of 64 queries or more): a workgroup takes ONE item, its
-//    tile of up to 32 queries sits in LDS once, and its four wavefronts share out the item's groups of
-//    vectors.  Large tiles are what keeps a hot list from being read once per 8 of the dozens of
-//    queries that probe it; the price is registers (3 wavefronts per SIMD instead of 4) and a tile to
+//  - vector unit: a workgroup is up to four wavefronts that take four consecutive items, one each, every one with its
+//    own tile of up to 8 queries in LDS;
+//  - matrix cores: a workgroup takes ONE item, its tile of up to 32 queries sits in LDS once, and its four wavefronts
+//    share out the item's groups of vectors.  Large tiles are what keeps a hot list from being read once per 8 of the
+//    dozens of queries that probe it; the price is registers (3 wavefronts per SIMD instead of 4) and a tile to
 //    set up per item, which small requests, whose tiles hold a query or two, do not get back
 //    (measured at 1 and 32 queries: 15 to 20 % slower than the vector unit with its partial-distance
-//    pruning).
+//    pruning; mm_scan_pays() has the larger ones).
 struct ScanShape {
   bool mm;           // the matrix-core kernel
   int tile_q;        // queries of a tile at most
@@ -397,9 +399,27 @@ constexpr size_t kMmStageBytes = (size_t)kMmStageCap * 9 + 8 * kMmTileMax;  // k
 constexpr size_t kMmLdsMax = 160 * 1024 - 1024;  // what a workgroup may take of the CU's 160 KiB
 constexpr int kMmMinBatch = 64;        // queries of a request from which the matrix-core scan pays
 
+// Whether a request of 64 queries or more scans on the matrix cores.  A tile is the queries of the request that probe one
+// list, and what speaks for the matrix cores is many queries to a list; what speaks against them is the set-up of a
+// workgroup per item, which short lists do not repay, and (inner products) that the vector unit needs one instruction
+// per coordinate where it needs two for squared distances.  Requests measured on both, vector unit / matrix cores:
+//  squared distances, floats, 1,024 lists of 977 x 128: 4 pairs to a list 158 / 171 us, 8 205 / 195, 16 281 / 215;
+//    lists of 390 x 200: 16 pairs 127 / 134;  halves: 2 pairs 110 / 110, 4 133 / 126;  bytes: 1 pair 89 / 92, 2 110 / 103
+//  inner products, lists of 1,950 x 96: 1 pair 164 / 171, 2 204 / 200, 8 250 / 232;  lists of 390 x 96: 16 pairs 91 / 98;
+//    d 256 and 768 with 2 to 16 pairs: the vector unit by 1 to 17 %;  halves: 8 pairs 193 / 191, 16 236 / 220
+//  a hot list (16 times the average and more; a good share of any batch probes it): 16,384 lists of 1,220 x 256, 64 queries
+//    2.00 / 2.19 ms, 128 2.62 / 2.51, 256 3.49 / 2.90; of 366: 256 queries 1.07 / 1.13; of 122: 0.50 / 0.59;
+//    4,096 lists of 488 x 64: 64 queries 134 / 137 us, 256 228 / 203;  1,024 lists of 3,906 x 128: 64 371 / 333, 256 602 / 469
+inline bool mm_scan_pays(const Dev &D, int64_t nq, int64_t nprobe, int64_t avg_len, int64_t max_len) {
+  const int64_t pairs = nq * nprobe, nlist = D.nlist;
+  if (max_len >= 16 * avg_len && avg_len >= 448 && (nq >= 128 || pairs >= nlist)) return true;
+  if (D.metric == 0) return avg_len >= 512 && pairs >= (D.storage == 0 ? 8 : D.storage == 1 ? 4 : 2) * nlist;
+  return D.d <= 128 && avg_len >= 1024 && pairs >= (D.storage == 0 ? 2 : 16) * nlist;
+}
+
 inline ScanShape scan_shape(const Dev &D, int item_budget) {
   ScanShape sh{};
-  sh.mm = D.scan_mfma != 0 && D.storage == 0 && D.pq_m == 0;
+  sh.mm = D.scan_mfma != 0 && D.pq_m == 0;
   // room for an uneven split of the items over the XCDs
   const int items = item_budget + item_budget / 2;
   if (!sh.mm) {

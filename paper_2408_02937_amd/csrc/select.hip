@@ -103,6 +103,8 @@ __device__ inline float score_of_key(uint32_t key, int metric) {
   return metric == 0 ? x : -x;
 }
 
+// ST: what flat lists keep (only the finalists' second scores depend on it: quantised lists take 0)
+template <int ST>
 __global__ __launch_bounds__(kTopkThreads) void k_select(Dev D, int k, int nprobe, int max_nprobe,
                                                         const float *__restrict__ Q, SearchScratch S,
                                                         float *__restrict__ out_dist,
@@ -112,7 +114,7 @@ __global__ __launch_bounds__(kTopkThreads) void k_select(Dev D, int k, int nprob
   __shared__ uint32_t sidx[kSurvivorCap];
   __shared__ uint32_t scount;
   const int q = blockIdx.x;
-  const int n = (int)S.rec_cnt[q];
+  const int n = (int)*rec_count(S, (uint32_t)q);
   const unsigned long long base = S.qbase[q];
   const uint32_t *rk = rec_keys_of(S, base), *rp = rec_poss_of(S, base);
   const int metric = D.metric;
@@ -127,7 +129,7 @@ __global__ __launch_bounds__(kTopkThreads) void k_select(Dev D, int k, int nprob
   // of it passed; should it not fit after all, what it added is dropped, the limit is renewed
   // and the portion is read again, cut to what fits for certain.  Ties that no limit can
   // separate (LDS stays more than half full) are left to the selection in place below.
-  // With norm-form scores among the records (flat float lists under L2 scored on the matrix cores) a
+  // With norm-form scores among the records (flat lists under L2 scored on the matrix cores) a
   // limit taken from the k-th best record is loosened twice: once to bound the k-th best direct-form
   // score from above, once more to admit every record whose direct-form score may reach that.
   const bool approx = uses_norm_form(D);
@@ -280,6 +282,28 @@ __global__ __launch_bounds__(kTopkThreads) void k_select(Dev D, int k, int nprob
     locate(i, b, moff);
     return block_ids(D, b)[moff];
   };
+  // The same for lists of halves and bytes: lane s of the four takes the 16-byte chunks s, s + 4, ...
+  auto narrow_key = [&](uint32_t b, uint32_t moff) -> uint32_t {
+    const int sub = (int)(threadIdx.x & 3u), vc = D.vchunks;
+    const float4 *__restrict__ x = block_vecs(D, b) + (size_t)(moff / kWave) * vc * kWave + (moff & (kWave - 1));
+    const float4 *__restrict__ y = reinterpret_cast<const float4 *>(Q + (size_t)q * D.d);
+    float acc = 0.f;
+    for (int c0 = sub; c0 < vc; c0 += 16) {
+      float4 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = x[(size_t)(c0 + 4 * u < vc ? c0 + 4 * u : c0) * kWave];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int c = c0 + 4 * u;
+        if (c >= vc) break;
+#pragma unroll
+        for (int p = 0; p < pieces_of(ST); ++p) accumulate<0>(acc, chunk_piece<ST>(v[u], p), y[pieces_of(ST) * c + p]);
+      }
+    }
+    acc += __shfl_xor(acc, 1);
+    acc += __shfl_xor(acc, 2);
+    return key_of_float(acc + 0.0f);
+  };
   // place in the pool -> key of the candidate's direct-form squared distance.  Four neighbouring lanes share
   // a candidate (a vector's chunks of 4 dimensions lie 1 KiB apart: every chunk is a memory
   // transaction of its own, and this way all of them are in flight at once): lane s of the four
@@ -290,6 +314,7 @@ __global__ __launch_bounds__(kTopkThreads) void k_select(Dev D, int k, int nprob
     locate(i, b, moff);
     const int sub = (int)(threadIdx.x & 3u);
     if (id && sub == 0) *id = block_ids(D, b)[moff];
+    if (ST != 0) return narrow_key(b, moff);
     const float4 *__restrict__ x =
         block_vecs(D, b) + (size_t)(moff / kWave) * D.d4 * kWave + (moff & (kWave - 1));
     const float4 *__restrict__ y = reinterpret_cast<const float4 *>(Q + (size_t)q * D.d);
@@ -317,6 +342,11 @@ __global__ __launch_bounds__(kTopkThreads) void k_select(Dev D, int k, int nprob
     if (sub == 0) {
       *ida = block_ids(D, ba)[ma];
       *idb = block_ids(D, bb)[mb];
+    }
+    if (ST != 0) {
+      ka = narrow_key(ba, ma);
+      kb = narrow_key(bb, mb);
+      return;
     }
     const float4 *__restrict__ xa = block_vecs(D, ba) + (size_t)(ma / kWave) * D.d4 * kWave + (ma & (kWave - 1));
     const float4 *__restrict__ xb = block_vecs(D, bb) + (size_t)(mb / kWave) * D.d4 * kWave + (mb & (kWave - 1));
@@ -450,8 +480,10 @@ __global__ __launch_bounds__(kTopkThreads) void k_select(Dev D, int k, int nprob
 void launch_select(const Dev &D, int64_t nq, int k, int nprobe, int max_nprobe, const float *Q,
                    const SearchScratch &S, float *out_dist, int64_t *out_ids, hipStream_t s) {
   if (nq <= 0) return;
-  hipLaunchKernelGGL(k_select, dim3((unsigned)nq), dim3(kTopkThreads), 0, s, D, k, nprobe, max_nprobe,
-                     Q, S, out_dist, out_ids);
+  const dim3 grid((unsigned)nq), block(kTopkThreads);
+  if (D.storage == 1) hipLaunchKernelGGL(k_select<1>, grid, block, 0, s, D, k, nprobe, max_nprobe, Q, S, out_dist, out_ids);
+  else if (D.storage == 2) hipLaunchKernelGGL(k_select<2>, grid, block, 0, s, D, k, nprobe, max_nprobe, Q, S, out_dist, out_ids);
+  else hipLaunchKernelGGL(k_select<0>, grid, block, 0, s, D, k, nprobe, max_nprobe, Q, S, out_dist, out_ids);
 }
 
 }  // namespace rtams
