@@ -62,6 +62,14 @@ __device__ void sample_scores(const Dev &D, int nprobe, int max_nprobe, int q, u
         // the same bits: every lane offers the one query, component l % 4 of the result is the score
         // of the lane's own vector
         MfmaAcc m = {0.f, 0.f, 0.f, 0.f};
+        if (ST == 0)
+          for (; c + 16 <= d4; c += 16) {
+            float4 v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) v[u] = x[(size_t)(c + u) * kWave];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) mfma_chunk(m, v[u], qv[c + u]);
+          }
         for (; c + 8 <= d4; c += 8) {
           float4 v[8];
 #pragma unroll
@@ -255,35 +263,6 @@ constexpr int kSegChoices = 8;  // segment lengths 2, 4, ..., 256 groups
 constexpr int kLdsEntries = 1024;  // probed lists of a request up to which their entries stay in LDS
 constexpr int kListChunk = 16;  // lists a thread of the grouping workgroup handles side by side
 
-__device__ inline void wg_scan3(uint32_t &a, uint32_t &b, unsigned long long &c, uint32_t *sa,
-                                uint32_t *sb, unsigned long long *sc) {
-  // inclusive scan over the threads of three values at once: shuffles inside a
-  // wavefront, then the wavefront totals through LDS; sa/sb/sc[kGroupThreads-1]
-  // receive the grand totals
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  constexpr int kWaves = kGroupThreads / kWave;
-  for (int o = 1; o < kWave; o <<= 1) {
-    const uint32_t xa = __shfl_up(a, o), xb = __shfl_up(b, o);
-    const unsigned long long xc = __shfl_up(c, o);
-    if (lane >= o) { a += xa; b += xb; c += xc; }
-  }
-  __syncthreads();  // earlier readers of the LDS arrays are done
-  if (lane == kWave - 1) { sa[wave] = a; sb[wave] = b; sc[wave] = c; }
-  __syncthreads();
-  uint32_t oa = 0, ob = 0, ta = 0, tb = 0;
-  unsigned long long oc = 0, tc = 0;
-  for (int w = 0; w < kWaves; ++w) {
-    const uint32_t va = sa[w], vb = sb[w];
-    const unsigned long long vc = sc[w];
-    if (w < wave) { oa += va; ob += vb; oc += vc; }
-    ta += va; tb += vb; tc += vc;
-  }
-  a += oa; b += ob; c += oc;
-  __syncthreads();
-  if (tid == kGroupThreads - 1) { sa[tid] = ta; sb[tid] = tb; sc[tid] = tc; }
-  __syncthreads();
-}
-
 // The pairs of the request grouped by list: `grouped` holds, list after list in list order, the
 // (query, probe) pairs that probe the list, each at the rank the plan gave it.  One workgroup, beside
 // the one that cuts the work items (both derive the same pair starts from the same counters: a
@@ -369,20 +348,6 @@ __device__ void scatter_pairs(const Dev &D, int nq, int nprobe, int max_nprobe, 
   }
 }
 
-// A thread's entries e0 .. e1 - 1, CH at a time: the loads of a chunk go out together, then body(e,
-// entry) for every entry of the chunk that is probed.
-template <int CH, typename Body>
-__device__ __forceinline__ void walk_entries(const uint4 *plist, uint32_t e0, uint32_t e1, Body body) {
-  for (uint32_t eb = e0; eb < e1; eb += CH) {
-    uint4 pl[CH];
-#pragma unroll
-    for (int t = 0; t < CH; ++t) pl[t] = eb + t < e1 ? plist[eb + t] : make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll
-    for (int t = 0; t < CH; ++t)
-      if (pl[t].z) body(eb + (uint32_t)t, pl[t]);
-  }
-}
-
 __global__ __launch_bounds__(kGroupThreads, 4) void k_group(Dev D, int nq, int nprobe, int max_nprobe, int k,
                                                          const float *__restrict__ Q,
                                                          uint32_t item_budget, uint32_t max_per_xcd,
@@ -395,15 +360,13 @@ __global__ __launch_bounds__(kGroupThreads, 4) void k_group(Dev D, int nq, int n
   }
   // the bound's query and sample keys, or the entries of the probed lists of a small request
   __shared__ __attribute__((aligned(16))) unsigned char s_raw[kBoundLdsBytes];
-  static_assert(kBoundLdsBytes >= kLdsEntries * (sizeof(uint4) + sizeof(uint32_t)), "the entries share the bound's LDS");
+  static_assert(kBoundLdsBytes >= kLdsEntries * sizeof(uint4), "the entries share the bound's LDS");
   if (blockIdx.x > 0) {  // this one sets the bound of a query
     sample_bound<false>(D, (int)blockIdx.x - 1 - scatterers, nprobe, max_nprobe, k, Q, S, s_raw);
     return;
   }
-  __shared__ uint32_t s_a[kGroupThreads];
-  __shared__ uint32_t s_b[kGroupThreads];
-  __shared__ unsigned long long s_c[kGroupThreads];
-  __shared__ uint32_t s_items[kSegChoices];
+  __shared__ uint32_t s_a[kGroupThreads / kWave], s_b[kGroupThreads / kWave];  // pairs, items and work of every wavefront's lists
+  __shared__ unsigned long long s_c[kGroupThreads / kWave];
   __shared__ uint32_t s_begin[9];
   constexpr uint32_t kHugeItems = 512, kHugeCap = 64;  // lists with this many items: at most so many are spread over the workgroup
   __shared__ uint4 s_huge_pl[kHugeCap];
@@ -411,7 +374,6 @@ __global__ __launch_bounds__(kGroupThreads, 4) void k_group(Dev D, int nq, int n
   __shared__ uint32_t s_nhuge;
   __shared__ uint32_t s_rows[kListChunk * (kGroupThreads / kWave) + 1];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  if (tid == 0) s_nhuge = 0;
   const uint32_t *__restrict__ list_cnt = S.list_cnt;
   uint4 *__restrict__ tile_desc = S.tile_desc;
   // The entries of the probed lists are written by one thread and read by another several times
@@ -420,7 +382,6 @@ __global__ __launch_bounds__(kGroupThreads, 4) void k_group(Dev D, int nq, int n
   // different lists keeps them in LDS.
   const bool lean = (long long)min((long long)D.nlist, (long long)nq * nprobe) <= kLdsEntries;
   uint4 *plist = lean ? reinterpret_cast<uint4 *>(s_raw) : S.plist;
-  uint32_t *pistart = lean ? reinterpret_cast<uint32_t *>(s_raw + kLdsEntries * sizeof(uint4)) : S.pistart;
   ScanQueues *Qs = S.queues;
   // Cost of a list for the split over the XCDs, per group of 64 vectors: reading it once from HBM
   // (each XCD has its own link to memory) plus the arithmetic of every query that probes it.  On
@@ -435,25 +396,29 @@ __global__ __launch_bounds__(kGroupThreads, 4) void k_group(Dev D, int nq, int n
   // The visible length of every probed list is read ONCE: an insertion may publish while this kernel
   // runs, and the passes below must agree on the segment counts.  (Each pair's own snapshot was
   // taken earlier, so it is not longer than this one.)
+  // Counters and lengths of 16 rows are asked for together, the lengths of all lists: waited for one probed list after
+  // the other they were most of this pass (16,384 lists: 27 us).
   uint32_t n_c = 0;
-  uint32_t cnt[kSegChoices];  // work items of this thread's lists for every segment length
-#pragma unroll
-  for (int e = 0; e < kSegChoices; ++e) cnt[e] = 0;
-  if (tid < kSegChoices) s_items[tid] = 0;
   constexpr int kWavesG = kGroupThreads / kWave;
   for (int lb = 0; lb < D.nlist; lb += kListChunk * kGroupThreads) {  // uniform over the workgroup
     const int rows = min(kListChunk, (D.nlist - lb + kGroupThreads - 1) / kGroupThreads);
-    uint32_t c[kListChunk];
+    uint32_t c[kListChunk], len[kListChunk];
     unsigned long long flags[kListChunk];
 #pragma unroll
     for (int t = 0; t < kListChunk; ++t) {
-      const int l = lb + t * kGroupThreads + tid;
-      c[t] = t < rows && l < D.nlist ? list_cnt[l] : 0u;
+      c[t] = 0u;
+      len[t] = 0u;
+      if (t < rows) {  // uniform
+        const int l = min(lb + t * kGroupThreads + tid, D.nlist - 1);
+        c[t] = list_cnt[l];
+        len[t] = __hip_atomic_load(&D.visible_len[l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
     }
 #pragma unroll
     for (int t = 0; t < kListChunk; ++t) {
       flags[t] = 0ull;
       if (t < rows) {  // uniform
+        if (lb + t * kGroupThreads + tid >= D.nlist) c[t] = 0u;
         flags[t] = __ballot(c[t] != 0u);
         if (lane == 0) s_rows[t * kWavesG + wave] = (uint32_t)__popcll(flags[t]);
       }
@@ -475,183 +440,169 @@ __global__ __launch_bounds__(kGroupThreads, 4) void k_group(Dev D, int nq, int n
       if (lane == 0) s_rows[kListChunk * kWavesG] = carry;
     }
     __syncthreads();
-    uint32_t len[kListChunk];
 #pragma unroll
     for (int t = 0; t < kListChunk; ++t)
-      len[t] = c[t] ? __hip_atomic_load(&D.visible_len[lb + t * kGroupThreads + tid], __ATOMIC_RELAXED,
-                                        __HIP_MEMORY_SCOPE_AGENT)
-                    : 0u;
-#pragma unroll
-    for (int t = 0; t < kListChunk; ++t) {
-      if (!c[t]) continue;
-      const uint32_t at =
-          n_c + s_rows[t * kWavesG + wave] + (uint32_t)__popcll(flags[t] & ((1ull << lane) - 1ull));
-      plist[at] = make_uint4((uint32_t)(lb + t * kGroupThreads + tid), 0u, c[t], len[t]);
-      const uint32_t groups = (len[t] + kWave - 1) / kWave;
-      const uint32_t tiles = (c[t] + tile_q - 1) >> tile_shift;
-#pragma unroll
-      for (int e = 0; e < kSegChoices; ++e) {
-        const uint32_t sg = 2u << e;
-        cnt[e] += (groups ? (groups + sg - 1) / sg : 1u) * tiles;
-      }
-    }
+      if (c[t])
+        plist[n_c + s_rows[t * kWavesG + wave] + (uint32_t)__popcll(flags[t] & ((1ull << lane) - 1ull))] =
+            make_uint4((uint32_t)(lb + t * kGroupThreads + tid), 0u, c[t], len[t]);
     n_c += s_rows[kListChunk * kWavesG];
     __syncthreads();  // the counts are reused by the next rows; the entries are read below by other threads
   }
-  // totals per segment length: shuffles inside the wavefront, one LDS atomic per wavefront
-  // (every lane adding to the same LDS word would serialise)
-#pragma unroll
-  for (int e = 0; e < kSegChoices; ++e) {
-    uint32_t v = cnt[e];
-    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    if (lane == 0 && v) atomicAdd(&s_items[e], v);
-  }
-  // From here on a thread owns `per` consecutive entries and walks them kListChunk at a time, so
-  // that the loads of a chunk go out together: a pass over the entries is a chain of memory
-  // latencies otherwise.  (With one or two entries to a thread the chunk is two wide: sixteen
-  // guarded loads, each waited for by itself, cost a small request three microseconds a pass.)
-  const uint32_t per = (n_c + kGroupThreads - 1) / kGroupThreads;
-  const uint32_t e0 = min(n_c, (uint32_t)tid * per), e1 = min(n_c, e0 + per);
-  auto for_my_entries = [&](auto body) {
-    if (per <= 2) walk_entries<2>(plist, e0, e1, body);  // uniform over the workgroup
-    else walk_entries<kListChunk>(plist, e0, e1, body);
-  };
-  __syncthreads();
-  int choice = kSegChoices - 1;
-  for (int e = min_choice; e < kSegChoices; ++e)
-    if (s_items[e] <= item_budget && s_items[e] <= S.item_cap) { choice = e; break; }
-
-  for (;; ++choice) {  // uniform: every thread sees the same totals
+  // From here on a wavefront owns a range of consecutive entries and walks it 64 at a time, lane = entry, so that the
+  // loads of a turn are one run of memory (a thread with a few entries of its own side by side touches as many cache
+  // lines as it has lanes with every load and store, and this one compute unit is all the chip has at work here:
+  // 3,500 probed lists of 4,096, 18,600 items: 37 us in five passes of that kind).  Two passes: the totals of every
+  // wavefront's range, then the places of its pairs and items, the cuts and the item descriptors in one go.
+  constexpr uint32_t kWaves = kGroupThreads / kWave;
+  const uint32_t w0 = (uint32_t)((unsigned long long)n_c * wave / kWaves);
+  const uint32_t w1 = (uint32_t)((unsigned long long)n_c * (wave + 1) / kWaves);
+  auto entry = [&](uint32_t e) { return e < w1 ? plist[e] : make_uint4(0u, 0u, 0u, 0u); };
+  // The shortest segments are tried first and nearly always fit the budget.  Twice the length never makes fewer than half
+  // the items, so where they do not, no length in front of the one tried next would have done either.
+  int choice = min_choice;
+  for (;;) {  // uniform: every thread sees the same totals
     const uint32_t seg = 2u << choice;
+    auto items_of = [&](const uint4 &pl, uint32_t &groups, uint32_t &tiles) {
+      groups = (pl.w + kWave - 1) / kWave;
+      tiles = (pl.z + tile_q - 1) >> tile_shift;
+      return pl.z ? (groups ? (groups + seg - 1) / seg : 1u) * tiles : 0u;
+    };
+    auto work_of = [&](const uint4 &pl, uint32_t groups) {
+      return pl.z ? (unsigned long long)(pl.z + byte_weight) * (groups ? groups : 1u) : 0ull;
+    };
     uint32_t np = 0, ni = 0;
     unsigned long long wk = 0;
-    for_my_entries([&](uint32_t, const uint4 &pl) {
-      const uint32_t c = pl.z;
-      const uint32_t groups = (pl.w + kWave - 1) / kWave;
-      np += c;
-      ni += (groups ? (groups + seg - 1) / seg : 1u) * ((c + tile_q - 1) >> tile_shift);
-      wk += (unsigned long long)(c + byte_weight) * (groups ? groups : 1u);
-    });
-    uint32_t inp = np, ini = ni;
-    unsigned long long iwk = wk;
-    wg_scan3(inp, ini, iwk, s_a, s_b, s_c);
-    const uint32_t total_items = s_b[kGroupThreads - 1];
-    const unsigned long long total_work = s_c[kGroupThreads - 1];
-    const uint32_t pstart0 = inp - np, istart0 = ini - ni;
-    const unsigned long long wstart0 = iwk - wk;
-    // XCD x starts at the item at which the work prefix passes x/8 of the total
-    if (tid < 9) s_begin[tid] = tid == 8 ? total_items : 0u;
+    for (uint32_t eb = w0; eb < w1; eb += 4 * kWave) {  // four turns' loads at a time
+      uint4 pl[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) pl[u] = entry(eb + u * kWave + (uint32_t)lane);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        uint32_t groups, tiles;
+        np += pl[u].z;
+        ni += items_of(pl[u], groups, tiles);
+        wk += work_of(pl[u], groups);
+      }
+    }
+    for (int o = kWave / 2; o > 0; o >>= 1) { np += __shfl_xor(np, o); ni += __shfl_xor(ni, o); wk += __shfl_xor(wk, o); }
+    if (lane == 0) { s_a[wave] = np; s_b[wave] = ni; s_c[wave] = wk; }
+    if (tid < 9) s_begin[tid] = 0u;
+    if (tid == 0) s_nhuge = 0;
     __syncthreads();
-    {
-      uint32_t is = istart0;
-      unsigned long long ws = wstart0;
-      for_my_entries([&](uint32_t, const uint4 &pl) {
-        const uint32_t c = pl.z;
-        const uint32_t groups = (pl.w + kWave - 1) / kWave;
-        const unsigned long long w = (unsigned long long)(c + byte_weight) * (groups ? groups : 1u);
-        const uint32_t n = (groups ? (groups + seg - 1) / seg : 1u) * ((c + tile_q - 1) >> tile_shift);
-        for (uint32_t x = 1; x < 8; ++x) {  // the cut falls inside this list: at the item the same share of it ends at
-          const unsigned long long cut = total_work * x / 8;
-          if (ws <= cut && cut < ws + w) s_begin[x] = is + (uint32_t)((cut - ws) * n / w);
+    uint32_t ps = 0, is = 0, total_items = 0;  // where this wavefront's pairs, items and work start
+    unsigned long long ws = 0, total_work = 0;
+    for (uint32_t w = 0; w < kWaves; ++w) {
+      if ((int)w < wave) { ps += s_a[w]; is += s_b[w]; ws += s_c[w]; }
+      total_items += s_b[w];
+      total_work += s_c[w];
+    }
+    if (total_items > item_budget && choice < kSegChoices - 1) {
+      int k = 1;
+      while (((unsigned long long)item_budget << k) < total_items) ++k;
+      choice = min(choice + k, kSegChoices - 1);
+      __syncthreads();  // the totals have been read
+      continue;
+    }
+    const bool room = total_items <= S.item_cap;  // (otherwise nothing is written: coarser segments, or no scan at all)
+    // Item descriptors.  Most lists have a handful of items: their lane writes them itself.  A list with more is taken
+    // by the whole wavefront, the lanes writing its items side by side, and one with very many (a
+    // hot list probed by dozens of queries has thousands) by the whole workgroup afterwards.  Inside a list the tiles
+    // of one segment follow each other, and the tiles are of (almost) equal size.
+    constexpr uint32_t kOwnItems = 16;
+    uint4 pl_next = entry(w0 + (uint32_t)lane);
+    for (uint32_t eb = w0; eb < w1; eb += kWave) {
+      const uint4 got = pl_next;
+      pl_next = entry(eb + kWave + (uint32_t)lane);  // the next 64 are on their way while these are written
+      uint32_t groups, tiles;
+      const uint32_t n = items_of(got, groups, tiles);
+      const unsigned long long w = work_of(got, groups);
+      uint32_t psum = got.z, isum = n;
+      unsigned long long wsum = w;
+      for (int o = 1; o < kWave; o <<= 1) {
+        const uint32_t xa = __shfl_up(psum, o), xb = __shfl_up(isum, o);
+        const unsigned long long xc = __shfl_up(wsum, o);
+        if (lane >= o) { psum += xa; isum += xb; wsum += xc; }
+      }
+      const uint4 pl = make_uint4(got.x, ps + psum - got.z, got.z, got.w);
+      const uint32_t ist = is + isum - n;
+      const unsigned long long wst = ws + wsum - w;
+      ps += __shfl(psum, kWave - 1);
+      is += __shfl(isum, kWave - 1);
+      const unsigned long long wend = ws + __shfl(wsum, kWave - 1);
+      // XCD x starts at the item at which the work prefix passes x/8 of the total; a cut inside a list: at the item
+      // the same share of it ends at
+      for (uint32_t x = 1; x < 8; ++x) {
+        const unsigned long long cut = total_work * x / 8;
+        if (cut < ws || cut >= wend) continue;  // uniform: few turns hold a cut
+        if (w && wst <= cut && cut < wst + w) s_begin[x] = ist + (uint32_t)((cut - wst) * n / w);
+      }
+      ws = wend;
+      if (!room) continue;  // uniform
+      tiles = tiles ? tiles : 1u;
+      const uint32_t small = pl.z / tiles;
+      const uint32_t extra = pl.z - small * tiles;  // the first `extra` tiles hold one more
+      if (n <= kOwnItems) {
+        uint32_t sg = 0, tt = 0;
+        for (uint32_t i = 0; i < n; ++i) {
+          const uint32_t p_lo = tt * small + min(tt, extra);
+          tile_desc[ist + i] = make_uint4(pl.x, pl.y + p_lo, small + (tt < extra ? 1u : 0u), sg);
+          if (++tt == tiles) { tt = 0; ++sg; }
         }
-        is += n;
-        ws += w;
-      });
+      }
+      // the few lists with very many items are left to the whole workgroup (below)
+      bool huge = n >= kHugeItems;
+      if (huge) {
+        const uint32_t slot = atomicAdd(&s_nhuge, 1u);
+        if (slot < kHugeCap) {
+          s_huge_pl[slot] = pl;
+          s_huge_ist[slot] = ist;
+        } else {
+          huge = false;  // no room: the wavefront takes it after all
+        }
+      }
+      unsigned long long big = __ballot(n > kOwnItems && !huge);
+      while (big) {  // uniform over the wavefront
+        const int t = __builtin_ctzll(big);
+        big &= big - 1;
+        const uint32_t l = (uint32_t)__shfl((int)pl.x, t), pst = (uint32_t)__shfl((int)pl.y, t);
+        const uint32_t first = (uint32_t)__shfl((int)ist, t), n_t = (uint32_t)__shfl((int)n, t);
+        const uint32_t tiles_t = (uint32_t)__shfl((int)tiles, t);
+        const uint32_t small_t = (uint32_t)__shfl((int)small, t), extra_t = (uint32_t)__shfl((int)extra, t);
+        for (uint32_t i = (uint32_t)lane; i < n_t; i += kWave) {
+          const uint32_t sg = i / tiles_t, tt = i - sg * tiles_t;
+          const uint32_t p_lo = tt * small_t + min(tt, extra_t);
+          tile_desc[first + i] = make_uint4(l, pst + p_lo, small_t + (tt < extra_t ? 1u : 0u), sg);
+        }
+      }
     }
     __syncthreads();
-    if (tid == 0)  // several cuts may fall into one list: keep the sequence monotone
-      for (uint32_t x = 1; x < 8; ++x)
-        if (s_begin[x] < s_begin[x - 1]) s_begin[x] = s_begin[x - 1];
-    __syncthreads();
-    uint32_t longest = 0;
-    for (uint32_t x = 0; x < 8; ++x) longest = max(longest, s_begin[x + 1] - s_begin[x]);
+    uint32_t begin[9], longest = 0;
+    begin[0] = 0u;
+#pragma unroll
+    for (int x = 1; x < 8; ++x) begin[x] = max(begin[x - 1], s_begin[x]);  // several cuts may fall into one list: keep the sequence monotone
+    begin[8] = total_items;
+#pragma unroll
+    for (int x = 0; x < 8; ++x) longest = max(longest, begin[x + 1] - begin[x]);
     if (longest > max_per_xcd) {  // uniform.  Items of very unequal cost: give every XCD the same number instead
-      __syncthreads();
-      if (tid < 9) s_begin[tid] = (uint32_t)((unsigned long long)total_items * tid / 8);
-      __syncthreads();
+#pragma unroll
+      for (int x = 1; x < 8; ++x) begin[x] = (uint32_t)((unsigned long long)total_items * x / 8);
       longest = (total_items + 7) / 8;
     }
-    const bool fits = total_items <= S.item_cap && longest <= max_per_xcd;
-    if (!fits && choice + 1 < kSegChoices + 8) continue;  // coarser segments (bounded: lengths are 32 bit)
-    if (tid < 9) Qs->begin[tid] = s_begin[tid];
+    const bool fits = room && longest <= max_per_xcd;
+    if (!fits && choice + 1 < kSegChoices + 8) {  // coarser segments (bounded: lengths are 32 bit)
+      ++choice;
+      __syncthreads();  // the cuts and the totals have been read
+      continue;
+    }
     if (tid == 0) {
+#pragma unroll
+      for (int x = 0; x < 9; ++x) Qs->begin[x] = begin[x];
       Qs->seg_groups = fits ? seg : 0u;
       if (!fits) {  // more tiles than the request's item descriptors hold: nothing is scanned, and the caller is told
         atomicCAS(&D.ctrl->search_error, 0, -6);
         D.mirror->search_error = -6;
       }
     }
-    // where the pairs and the items of every probed list start
-    {
-      uint32_t ps = pstart0, is = istart0;
-      for_my_entries([&](uint32_t e, const uint4 &pl) {
-        const uint32_t c = pl.z;
-        const uint32_t groups = (pl.w + kWave - 1) / kWave;
-        plist[e] = make_uint4(pl.x, ps, c, pl.w);
-        pistart[e] = is;
-        ps += c;
-        is += (groups ? (groups + seg - 1) / seg : 1u) * ((c + tile_q - 1) >> tile_shift);
-      });
-    }
-    __syncthreads();  // entries written above are read below by other threads
-    // Item descriptors.  A wavefront takes a sixteenth of the entries, 64 at a time, lane = entry.
-    // Most lists have a handful of items: their lane writes them itself.  A list with more is taken
-    // by the whole wavefront, the lanes writing its items side by side, and one with very many (a
-    // hot list probed by dozens of queries has thousands) by the whole workgroup afterwards.  Inside a list the tiles of one segment follow each other,
-    // and the tiles are of (almost) equal size.
-    if (fits) {
-      constexpr uint32_t kWaves = kGroupThreads / kWave;
-      constexpr uint32_t kOwnItems = 16;
-      const uint32_t w0 = (uint32_t)((unsigned long long)n_c * wave / kWaves);
-      const uint32_t w1 = (uint32_t)((unsigned long long)n_c * (wave + 1) / kWaves);
-      for (uint32_t eb = w0; eb < w1; eb += kWave) {
-        const uint32_t mine = eb + (uint32_t)lane;
-        const uint4 pl = mine < w1 ? plist[mine] : make_uint4(0u, 0u, 0u, 0u);
-        const uint32_t ist = mine < w1 ? pistart[mine] : 0u;
-        uint32_t n = 0, tiles = 1, small = 0, extra = 0;
-        if (pl.z) {
-          const uint32_t groups = (pl.w + kWave - 1) / kWave;
-          tiles = (pl.z + tile_q - 1) >> tile_shift;
-          n = (groups ? (groups + seg - 1) / seg : 1u) * tiles;
-          small = pl.z / tiles;
-          extra = pl.z - small * tiles;  // the first `extra` tiles hold one more
-        }
-        if (n <= kOwnItems) {
-          uint32_t sg = 0, tt = 0;
-          for (uint32_t i = 0; i < n; ++i) {
-            const uint32_t p_lo = tt * small + min(tt, extra);
-            tile_desc[ist + i] = make_uint4(pl.x, pl.y + p_lo, small + (tt < extra ? 1u : 0u), sg);
-            if (++tt == tiles) { tt = 0; ++sg; }
-          }
-        }
-        // the few lists with very many items are left to the whole workgroup (below)
-        bool huge = n >= kHugeItems;
-        if (huge) {
-          const uint32_t slot = atomicAdd(&s_nhuge, 1u);
-          if (slot < kHugeCap) {
-            s_huge_pl[slot] = pl;
-            s_huge_ist[slot] = ist;
-          } else {
-            huge = false;  // no room: the wavefront takes it after all
-          }
-        }
-        unsigned long long big = __ballot(n > kOwnItems && !huge);
-        while (big) {  // uniform over the wavefront
-          const int t = __builtin_ctzll(big);
-          big &= big - 1;
-          const uint32_t l = (uint32_t)__shfl((int)pl.x, t), ps = (uint32_t)__shfl((int)pl.y, t);
-          const uint32_t first = (uint32_t)__shfl((int)ist, t), n_t = (uint32_t)__shfl((int)n, t);
-          const uint32_t tiles_t = (uint32_t)__shfl((int)tiles, t);
-          const uint32_t small_t = (uint32_t)__shfl((int)small, t), extra_t = (uint32_t)__shfl((int)extra, t);
-          for (uint32_t i = (uint32_t)lane; i < n_t; i += kWave) {
-            const uint32_t sg = i / tiles_t, tt = i - sg * tiles_t;
-            const uint32_t p_lo = tt * small_t + min(tt, extra_t);
-            tile_desc[first + i] = make_uint4(l, ps + p_lo, small_t + (tt < extra_t ? 1u : 0u), sg);
-          }
-        }
-      }
-    }
-    __syncthreads();
     if (fits) {
       const uint32_t nh = min(s_nhuge, kHugeCap);
       for (uint32_t h = 0; h < nh; ++h) {  // uniform over the workgroup

@@ -19,7 +19,10 @@ constexpr int kSelThreads = 256, kSelThreadsMany = 1024, kSelManyFrom = 4096;
 // candidates are scored in the fixed double arithmetic here and ordered
 // exactly.  If the band holds more candidates than LDS, the whole row is scored
 // exactly instead (what small requests, which skip the matrix cores, always do).
-template <bool FROM_APPROX>
+// MINE: scores of the row a thread holds in registers, 0 for rows too long for that.  A row that is held is read once,
+// all its loads in flight together; every pass of a selection that reads the row again is a chain of trips to memory
+// (16,384 lists: 25 us for the selection alone, most of it such passes).
+template <bool FROM_APPROX, int MINE>
 __global__ __launch_bounds__(kSelThreadsMany) void k_probe_plan(Dev D, int64_t nq, int nprobe, int max_nprobe,
                                                             SearchScratch S, const float *__restrict__ Q,
                                                             int32_t *probe_out) {
@@ -29,16 +32,17 @@ __global__ __launch_bounds__(kSelThreadsMany) void k_probe_plan(Dev D, int64_t n
   __shared__ uint64_t k1[kMaxNprobe];
   __shared__ uint64_t k2[kMaxNprobe];
   __shared__ uint32_t pay[kMaxNprobe];
+  __shared__ float4 yv[FROM_APPROX ? 512 : 1];  // the query (d <= 2048)
   const int T = (int)blockDim.x;
   const int q = blockIdx.x;
   const int n = D.nlist;
   double *sc = S.scores + (size_t)q * n;
   const int metric = D.metric;
   // the fixed arithmetic of coarse.hip for one centroid: a chain of multiply-adds in the order of the
-  // coordinates, fed by 16-byte loads that run eight chunks ahead of it (one coordinate per load, each
-  // waited for, made a candidate of 768 dimensions cost a hundred nanoseconds per coordinate)
-  auto exact = [&](int c) -> double {
-    const float4 *y4 = reinterpret_cast<const float4 *>(Q + (size_t)q * D.d);
+  // coordinates, fed by 16-byte loads of which one set of eight is in flight while the other is used up (one
+  // coordinate per load, each waited for, made a candidate of 768 dimensions cost a hundred nanoseconds per
+  // coordinate; one set at a time, a trip to memory per eight chunks).  The query comes out of LDS.
+  auto exact = [&](int c) __attribute__((always_inline)) -> double {
     const float4 *r4 = reinterpret_cast<const float4 *>(D.centroids + (size_t)c * D.d);
     const int d4 = D.d4;
     double acc = 0.0;
@@ -55,37 +59,71 @@ __global__ __launch_bounds__(kSelThreadsMany) void k_probe_plan(Dev D, int64_t n
         acc = __builtin_fma((double)y.w, (double)r.w, acc);
       }
     };
+    float4 sa[8], sb[8];
+    auto load = [&](float4 *set, int j) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) set[u] = r4[j + u];
+      __builtin_amdgcn_sched_barrier(0);  // the loads go out here
+    };
+    auto use = [&](const float4 *set, int j) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) chain(yv[j + u], set[u]);
+      __builtin_amdgcn_sched_barrier(0);
+    };
     int j = 0;
-    for (; j + 8 <= d4; j += 8) {
-      float4 a[8], b[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) { a[u] = y4[j + u]; b[u] = r4[j + u]; }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) chain(a[u], b[u]);
+    if (d4 >= 8) load(sa, 0);
+    for (; j + 24 <= d4; j += 16) {
+      load(sb, j + 8);
+      use(sa, j);
+      load(sa, j + 16);
+      use(sb, j + 8);
     }
-    for (; j < d4; ++j) chain(y4[j], r4[j]);
+    if (j + 16 <= d4) { load(sb, j + 8); use(sa, j); use(sb, j + 8); j += 16; }
+    else if (j + 8 <= d4) { use(sa, j); j += 8; }
+    for (; j < d4; ++j) chain(yv[j], r4[j]);
     return acc;
   };
   auto key_of_score = [&](double x) -> uint64_t {
     x = (metric == 0 ? x : -x) + 0.0;  // +0.0 folds -0 into +0
     return key_of_double(x);
   };
+  if (FROM_APPROX) {
+    for (int c = threadIdx.x; c < D.d4; c += T) yv[c] = reinterpret_cast<const float4 *>(Q + (size_t)q * D.d)[c];
+    __syncthreads();
+  }
+  constexpr int kHeld = MINE > 0 ? MINE : 1;
   bool done = false;  // k1 / k2 / pay hold the nprobe winners, not yet sorted
   if (FROM_APPROX && nprobe < n) {
     const float *ap = S.approx + (size_t)q * n;
+    float mine[kHeld];
+    if (MINE > 0) {
+#pragma unroll
+      for (int u = 0; u < kHeld; ++u) mine[u] = ap[min((int)threadIdx.x + u * T, n - 1)];
+    }
+    auto each_approx = [&](auto body) {  // body(index, score)
+      if (MINE > 0) {
+#pragma unroll
+        for (int u = 0; u < kHeld; ++u)
+          if ((int)threadIdx.x + u * T < n) body((int)threadIdx.x + u * T, mine[u]);
+      } else {
+        for (int i = threadIdx.x; i < n; i += T) body(i, ap[i]);
+      }
+    };
     const float band = search_row_meta(D, nq, S.qhalf)[q].band;  // 2 E, see coarse_mfma.hip
-    const SelectResult ra = wg_radix_select<32>(
-        n, (uint32_t)nprobe, [&](int i, uint64_t &k) { k = key_of_float(ap[i] + 0.0f); return true; }, hist, bc);
+    const SelectResult ra = wg_radix_select_each<32>(
+        (uint32_t)nprobe, [&](auto body) { each_approx([&](int, float v) { body((uint64_t)key_of_float(v + 0.0f)); }); },
+        hist, bc);
     const uint32_t tk = (uint32_t)ra.T;  // key of (an upper bound of) the nprobe-th smallest approximation
     const float t = __uint_as_float((tk & 0x80000000u) ? (tk & 0x7fffffffu) : ~tk);
     const float limit = t + band;
     if (threadIdx.x == 0) cnt[0] = 0;
     __syncthreads();
-    for (int i = threadIdx.x; i < n; i += T)
-      if (ap[i] <= limit) {
+    each_approx([&](int i, float v) {
+      if (v <= limit) {
         uint32_t p = atomicAdd(&cnt[0], 1u);
         if (p < (uint32_t)kMaxNprobe) pay[p] = (uint32_t)i;
       }
+    });
     __syncthreads();
     const int nc = (int)cnt[0];
     if (nc >= nprobe && nc <= kMaxNprobe) {  // (fewer than nprobe: scores that do not compare, e.g. NaN)
@@ -101,8 +139,6 @@ __global__ __launch_bounds__(kSelThreadsMany) void k_probe_plan(Dev D, int64_t n
       __syncthreads();
     }
   }
-  auto key1 = [&](int i) -> uint64_t { return key_of_score(sc[i]); };
-
   SelectResult r1{~0ull, 0, 0}, r2{~0ull, 0, 0};
   const bool all = nprobe >= n;
   if (!done && FROM_APPROX && all) {  // every list is probed: exact order of the whole row
@@ -110,24 +146,39 @@ __global__ __launch_bounds__(kSelThreadsMany) void k_probe_plan(Dev D, int64_t n
     __syncthreads();
   }
   if (!done) {
+  // (a request whose filter did not narrow the row down reads it from memory: that is rare, and the registers are taken)
+  constexpr bool kHold = MINE > 0 && !FROM_APPROX;
+  double held[kHeld];
+  if (kHold) {
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u) held[u] = sc[min((int)threadIdx.x + u * T, n - 1)];
+  }
+  auto each_key = [&](auto body) {  // body(index, key)
+    if (kHold) {
+#pragma unroll
+      for (int u = 0; u < kHeld; ++u)
+        if ((int)threadIdx.x + u * T < n) body((int)threadIdx.x + u * T, key_of_score(held[u]));
+    } else {
+      for (int i = threadIdx.x; i < n; i += T) body(i, key_of_score(sc[i]));
+    }
+  };
   if (!all) {
-    r1 = wg_radix_select<64>(n, (uint32_t)nprobe, [&](int i, uint64_t &k) { k = key1(i); return true; },
-                             hist, bc);
+    r1 = wg_radix_select_each<64>((uint32_t)nprobe,
+                                  [&](auto body) { each_key([&](int, uint64_t k) { body(k); }); }, hist, bc);
     if (r1.c_eq > r1.need)  // ties at the boundary go to the lower index
-      r2 = wg_radix_select<32>(n, r1.need,
-                               [&](int i, uint64_t &k) { k = (uint32_t)i; return key1(i) == r1.T; },
-                               hist, bc);
+      r2 = wg_radix_select_each<32>(
+          r1.need, [&](auto body) { each_key([&](int i, uint64_t k) { if (k == r1.T) body((uint64_t)(uint32_t)i); }); },
+          hist, bc);
   }
   if (threadIdx.x == 0) cnt[0] = 0;
   __syncthreads();
-  for (int i = threadIdx.x; i < n; i += T) {
-    uint64_t k = key1(i);
+  each_key([&](int i, uint64_t k) {
     bool take = all || k < r1.T || (k == r1.T && (r1.c_eq <= r1.need || (uint64_t)i <= r2.T));
     if (take) {
       uint32_t p = atomicAdd(&cnt[0], 1u);
       k1[p] = k; k2[p] = (uint64_t)i; pay[p] = (uint32_t)i;
     }
-  }
+  });
   __syncthreads();
   wg_sort(nprobe, k1, k2, pay);
   }  // !done
@@ -151,11 +202,12 @@ __global__ __launch_bounds__(kSelThreadsMany) void k_probe_plan(Dev D, int64_t n
     S.pair_slot[(size_t)q * max_nprobe + p] = atomicAdd(&S.list_cnt[list], 1u);
   }
   __syncthreads();
+  unsigned long long tot = 0;
+  if (threadIdx.x < kWave) {
+    for (int p = threadIdx.x; p < nprobe; p += kWave) tot += pay[p];
+    for (int o = kWave / 2; o > 0; o >>= 1) tot += __shfl_xor(tot, o);
+  }
   if (threadIdx.x == 0) {
-    unsigned long long tot = 0;
-    for (int p = 0; p < nprobe; ++p) {
-      tot += pay[p];
-    }
     unsigned long long base = 0;
     if (probe_out) tot = 0;  // the probe hook: nothing is scanned afterwards, no room for records is taken
     if (tot > 0xFFFFFFFFull) tot = ~0ull;  // cannot be indexed: treated as overflow below
@@ -181,12 +233,13 @@ void launch_probe_plan(const Dev &D, int64_t nq, int nprobe, int max_nprobe, con
                        const float *Q, bool from_approx, int32_t *probe_out, hipStream_t s) {
   if (nq <= 0) return;
   const unsigned threads = D.nlist >= kSelManyFrom ? kSelThreadsMany : kSelThreads;
-  if (from_approx)
-    hipLaunchKernelGGL(k_probe_plan<true>, dim3((unsigned)nq), dim3(threads), 0, s, D, nq, nprobe, max_nprobe,
-                       S, Q, probe_out);
-  else
-    hipLaunchKernelGGL(k_probe_plan<false>, dim3((unsigned)nq), dim3(threads), 0, s, D, nq, nprobe, max_nprobe,
-                       S, Q, probe_out);
+  typedef void (*Kernel)(Dev, int64_t, int, int, SearchScratch, const float *, int32_t *);
+  static const Kernel kernels[2][4] = {
+      {k_probe_plan<false, 4>, k_probe_plan<false, 8>, k_probe_plan<false, 16>, k_probe_plan<false, 0>},
+      {k_probe_plan<true, 4>, k_probe_plan<true, 8>, k_probe_plan<true, 16>, k_probe_plan<true, 0>}};
+  const int per = (int)((D.nlist + threads - 1) / threads);  // scores of a row to a thread
+  hipLaunchKernelGGL(kernels[from_approx ? 1 : 0][per <= 4 ? 0 : per <= 8 ? 1 : per <= 16 ? 2 : 3], dim3((unsigned)nq),
+                     dim3(threads), 0, s, D, nq, nprobe, max_nprobe, S, Q, probe_out);
 }
 
 }  // namespace rtams

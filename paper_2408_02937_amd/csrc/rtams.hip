@@ -150,7 +150,7 @@ void lay_out(const rtams_config *c, int64_t blocks, size_t pool_bytes, Layout *L
 
 struct ScratchLayout {
   size_t scores, approx, probe_list, probe_len, qbase, qtotal, bound, qnorm, qhalf, rec_cnt, cursor, req_words, lut, records, fixed;
-  size_t list_cnt, pair_start, pair_slot, grouped, plist, pistart, tile_desc, queues, item_cap;
+  size_t list_cnt, pair_start, pair_slot, grouped, plist, tile_desc, queues, item_cap;
 };
 
 void lay_out_scratch(const rtams_config *c, ScratchLayout *S) {
@@ -178,7 +178,6 @@ void lay_out_scratch(const rtams_config *c, ScratchLayout *S) {
   S->pair_slot = take(mb * mp * 4);
   S->grouped = take(mb * mp * 4);
   S->plist = take(probed * 16);
-  S->pistart = take(probed * 4);
   S->item_cap = mb * mp * 4 > 65536 ? mb * mp * 4 : 65536;
   S->tile_desc = take(S->item_cap * 16);
   S->records = o;
@@ -578,7 +577,6 @@ int rtams_create(const rtams_config *cfg, rtams_index **out) {
     S.pair_slot = reinterpret_cast<uint32_t *>(p + SL.pair_slot);
     S.grouped = reinterpret_cast<uint32_t *>(p + SL.grouped);
     S.plist = reinterpret_cast<uint4 *>(p + SL.plist);
-    S.pistart = reinterpret_cast<uint32_t *>(p + SL.pistart);
     S.tile_desc = reinterpret_cast<uint4 *>(p + SL.tile_desc);
     S.item_cap = (uint32_t)SL.item_cap;
     S.queues = reinterpret_cast<ScanQueues *>(p + SL.queues);

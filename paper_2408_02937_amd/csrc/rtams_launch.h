@@ -40,9 +40,8 @@ struct SearchScratch {
   uint32_t *pair_start; // [nlist] where the pairs of a probed list start in `grouped`
   uint32_t *pair_slot;  // [max_batch][max_nprobe] rank of the pair among the pairs of its list
   uint32_t *grouped;    // [max_batch * max_nprobe] pairs (query << 10 | probe) grouped by list
-  uint4 *plist;         // [min(nlist, max_batch * max_nprobe)] per probed list, in list order: {list, first pair,
-                        // pairs, length as seen by the grouping step}
-  uint32_t *pistart;    // [as plist] first work item of the list
+  uint4 *plist;         // [min(nlist, max_batch * max_nprobe)] per probed list, in list order: {list, unused, pairs,
+                        // length as seen by the grouping step}
   uint4 *tile_desc;     // [item_cap] {list, first pair of the tile, pairs of the tile, segment} per item
   uint32_t item_cap;
   ScanQueues *queues;   // work items of this request, split into one queue per XCD
