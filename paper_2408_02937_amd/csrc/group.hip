@@ -259,7 +259,7 @@ __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, in
 // spread over many wavefronts.  The segment length is the shortest power of two
 // for which the request has at most `item_budget` items and no XCD more than
 // `max_per_xcd` (the launch of the scan is sized from those two).
-constexpr int kSegChoices = 8;  // segment lengths 2, 4, ..., 256 groups
+constexpr int kSegChoices = 8;  // segment lengths 2, 4, ..., 256 groups (1, 2, ..., 128 where the scan walks groups singly)
 constexpr int kLdsEntries = 1024;  // probed lists of a request up to which their entries stay in LDS
 constexpr int kListChunk = 16;  // lists a thread of the grouping workgroup handles side by side
 
@@ -351,7 +351,7 @@ __device__ void scatter_pairs(const Dev &D, int nq, int nprobe, int max_nprobe, 
 __global__ __launch_bounds__(kGroupThreads, 4) void k_group(Dev D, int nq, int nprobe, int max_nprobe, int k,
                                                          const float *__restrict__ Q,
                                                          uint32_t item_budget, uint32_t max_per_xcd,
-                                                         uint32_t tile_q, int min_choice, int scatterers,
+                                                         uint32_t tile_q, uint32_t seg_base, int min_choice, int scatterers,
                                                          SearchScratch S) {
   const int tile_shift = 31 - __clz((int)tile_q);  // tiles hold a power of two of queries
   if (blockIdx.x >= 1 && (int)blockIdx.x <= scatterers) {  // uniform over the workgroup: these group the pairs by list
@@ -461,7 +461,7 @@ __global__ __launch_bounds__(kGroupThreads, 4) void k_group(Dev D, int nq, int n
   // the items, so where they do not, no length in front of the one tried next would have done either.
   int choice = min_choice;
   for (;;) {  // uniform: every thread sees the same totals
-    const uint32_t seg = 2u << choice;
+    const uint32_t seg = seg_base << choice;
     auto items_of = [&](const uint4 &pl, uint32_t &groups, uint32_t &tiles) {
       groups = (pl.w + kWave - 1) / kWave;
       tiles = (pl.z + tile_q - 1) >> tile_shift;
@@ -700,7 +700,7 @@ void launch_group(const Dev &D, int64_t nq, int nprobe, int max_nprobe, int k, c
   const int scatterers = (int)(pairs <= 2048 ? 1 : pairs >= 8 * 2048 ? 8 : (pairs + 2047) / 2048);
   hipLaunchKernelGGL(k_group, dim3(1 + (unsigned)scatterers + (unsigned)nq), dim3(kGroupThreads), 0, s, D, (int)nq,
                      nprobe, max_nprobe, k, Q, (uint32_t)item_budget,
-                     (uint32_t)(sh.grid / (int)kXcds * sh.items_per_wg), (uint32_t)sh.tile_q, sh.min_choice,
+                     (uint32_t)(sh.grid / (int)kXcds * sh.items_per_wg), (uint32_t)sh.tile_q, (uint32_t)sh.seg_base, sh.min_choice,
                      scatterers, S);
 }
 

@@ -772,6 +772,8 @@ static int search_on(rtams_index *ix, int r, int64_t nq, const float *d_queries,
     D.scan_mfma = D.pq_m == 0 && (mode == 2 || (mode == 1 && nq >= kMmMinBatch &&
                                                 mm_scan_pays(D, nq, nprobe, avg_len, (int64_t)ix->mirror->max_len)));
   }
+  const int64_t avg_groups = ix->ntotal_host / ix->cfg.nlist / kWave + 1;
+  D.scan_single = !D.scan_mfma && D.pq_m == 0 && avg_groups <= kSingleList && nq * nprobe * avg_groups < kSingleGroups;
   D.scan_byte_weight = (int32_t)ix->scan_byte_weight.load(std::memory_order_relaxed);
   D.scan_min_choice = (int32_t)ix->scan_min_choice.load(std::memory_order_relaxed);
   // a long scan: its (query, list) pairs are expected to meet this many list bytes (lists of average length)
@@ -798,7 +800,7 @@ static int search_on(rtams_index *ix, int r, int64_t nq, const float *d_queries,
   // grow meanwhile get longer segments.
   if (D.pq_m == 0) {
     const ScanShape sh = scan_shape(D, (int)budget);
-    const int64_t seg_vecs = (int64_t)kWave * (2 << sh.min_choice);
+    const int64_t seg_vecs = (int64_t)kWave * (sh.seg_base << sh.min_choice);
     const int64_t probed = nq * nprobe < ix->cfg.nlist ? nq * nprobe : ix->cfg.nlist;
     const int64_t longest = (int64_t)ix->mirror->max_len;
     int64_t segs = ix->ntotal_host / seg_vecs + probed;  // of the probed lists together, every one rounded up

@@ -8,22 +8,24 @@ namespace rtams {
 // kScanTileQueries of the queries that probe the list.  Every WAVEFRONT works on its own: it
 // takes an item from a queue, copies the item's queries into its slice of LDS,
 // and walks the segment in pairs of groups of 64 vectors, lane = vector (two
-// vectors per lane).  Per chunk of 4 dimensions it loads 1 KiB of consecutive
+// vectors per lane; in small requests over short lists one group and one vector).  Per chunk of 4 dimensions it loads 1 KiB of consecutive
 // memory per group (one float4 per lane) ONCE and every lane accumulates the
 // score of its two vectors against each query of the item; a query chunk is one
 // broadcast LDS read shared by both vectors.  Scores go to each query's
 // candidate slice.  No workgroup barrier is involved anywhere.
 
-// Chunks of 4 dimensions per register set of the software pipeline.  Deeper sets for
-// items with few queries were measured: they cost a wavefront of occupancy and gain nothing.
-constexpr int prefetch_chunks(int) { return 2; }
-
-template <int METRIC, int NQ, int ST>
+// P: 16-byte chunks per register set of the software pipeline, 2 with two groups at a time.  Deeper sets for
+// items with few queries were measured there: they cost a wavefront of occupancy and gain nothing.  With one group at
+// a time 4, the same registers and bytes in flight, or 8 for floats where they divide the vectors evenly (one query
+// over 0.5 M x 768 with 8 / 4: 64.3 / 68.0 us a request, 4 queries 75.9 / 78.6).
+// G: groups of 64 vectors walked side by side, 2, or 1 in small requests over short lists, where a wavefront to every
+// pair of groups would leave most of the chip idle and each of them with a chain of trips to memory.
+template <int METRIC, int NQ, int ST, int G, int P>
 __device__ __forceinline__ void scan_item(const Dev &D, const SearchScratch &S,
                                           const float *__restrict__ Q, int max_nprobe, int list,
                                           uint32_t first, uint32_t g_begin, uint32_t g_count,
                                           float4 *qs) {
-  constexpr int kPrefetch = prefetch_chunks(NQ);
+  constexpr int kPrefetch = P;
   // Partial-distance pruning (L2 only: squared distances only grow) pays for tiles of few queries,
   // where whole pairs of groups drop out; with more queries somebody is nearly always still in
   // and the branches cost more than the skipped arithmetic saves (measured: 8 queries 3 % slower).
@@ -70,11 +72,11 @@ __device__ __forceinline__ void scan_item(const Dev &D, const SearchScratch &S,
     if (ngroups > have) ngroups = have;
   }
   const size_t group_stride = (size_t)vc * kWave;
-  for (uint32_t g0 = g_begin; g0 < ngroups; g0 += 2) {
-    const bool two = g0 + 1 < ngroups;  // uniform over the wavefront
+  for (uint32_t g0 = g_begin; g0 < ngroups; g0 += G) {
+    const bool two = G == 2 && g0 + 1 < ngroups;  // uniform over the wavefront
     const uint32_t g1 = two ? g0 + 1 : g0;
     const uint32_t b0 = (uint32_t)*table_entry(D, list, g0 / gpb);
-    const uint32_t b1 = (uint32_t)*table_entry(D, list, g1 / gpb);
+    const uint32_t b1 = G == 2 ? (uint32_t)*table_entry(D, list, g1 / gpb) : b0;
     const float4 *__restrict__ xa = block_vecs(D, b0) + (size_t)(g0 % gpb) * group_stride + lane;
     const float4 *__restrict__ xb = block_vecs(D, b1) + (size_t)(g1 % gpb) * group_stride + lane;
     float acc0[NQ], acc1[NQ];
@@ -92,7 +94,7 @@ __device__ __forceinline__ void scan_item(const Dev &D, const SearchScratch &S,
 #pragma unroll
         for (int u = 0; u < kPrefetch; ++u) {
           s0[u] = xa[(size_t)(cb + u) * kWave];
-          s1[u] = xb[(size_t)(cb + u) * kWave];
+          if (G == 2) s1[u] = xb[(size_t)(cb + u) * kWave];
         }
         __builtin_amdgcn_sched_barrier(0);  // loads are issued here, not sunk towards their use
       };
@@ -105,7 +107,7 @@ __device__ __forceinline__ void scan_item(const Dev &D, const SearchScratch &S,
             for (int u = 0; u < kPrefetch; ++u) {
               const float4 y = qs[i * d4 + cb + u];
               accumulate<METRIC>(acc0[i], s0[u], y);
-              accumulate<METRIC>(acc1[i], s1[u], y);
+              if (G == 2) accumulate<METRIC>(acc1[i], s1[u], y);
             }
             __builtin_amdgcn_sched_barrier(0);  // keep one query's temporaries from piling up on the next
           }
@@ -114,13 +116,13 @@ __device__ __forceinline__ void scan_item(const Dev &D, const SearchScratch &S,
           for (int u = 0; u < kPrefetch; ++u) {
 #pragma unroll
             for (int s = 0; s < kPieces; ++s) {
-              const float4 x0 = chunk_piece<ST>(s0[u], s), x1 = chunk_piece<ST>(s1[u], s);
+              const float4 x0 = chunk_piece<ST>(s0[u], s), x1 = G == 2 ? chunk_piece<ST>(s1[u], s) : x0;
 #pragma unroll
               for (int i = 0; i < NQ; ++i) {
                 if (kPrune && !((alive >> i) & 1u)) continue;  // uniform
                 const float4 y = qs[i * d4 + (cb + u) * kPieces + s];
                 accumulate<METRIC>(acc0[i], x0, y);
-                accumulate<METRIC>(acc1[i], x1, y);
+                if (G == 2) accumulate<METRIC>(acc1[i], x1, y);
               }
               __builtin_amdgcn_sched_barrier(0);  // one piece's widened values at a time
             }
@@ -157,7 +159,7 @@ __device__ __forceinline__ void scan_item(const Dev &D, const SearchScratch &S,
       }
     }
     for (int c = d4_main; c < vc && alive != 0u; ++c) {  // chunks beyond the last full double set
-      const float4 r0 = xa[(size_t)c * kWave], r1 = xb[(size_t)c * kWave];
+      const float4 r0 = xa[(size_t)c * kWave], r1 = G == 2 ? xb[(size_t)c * kWave] : r0;
 #pragma unroll
       for (int s = 0; s < kPieces; ++s) {
         const float4 x0 = chunk_piece<ST>(r0, s), x1 = chunk_piece<ST>(r1, s);
@@ -165,7 +167,7 @@ __device__ __forceinline__ void scan_item(const Dev &D, const SearchScratch &S,
         for (int i = 0; i < NQ; ++i) {
           const float4 y = qs[i * d4 + c * kPieces + s];
           accumulate<METRIC>(acc0[i], x0, y);
-          accumulate<METRIC>(acc1[i], x1, y);
+          if (G == 2) accumulate<METRIC>(acc1[i], x1, y);
         }
       }
     }
@@ -230,7 +232,7 @@ __device__ __forceinline__ void scan_item(const Dev &D, const SearchScratch &S,
 // 4 (i / 8) + 3 of that XCD's range of items (a contiguous range of lists).
 // Wavefronts past the end of their range leave at once.
 
-template <int METRIC, int ST>
+template <int METRIC, int ST, int G, int P>
 __global__ __launch_bounds__(kScanWaves * kWave) void k_scan(Dev D, int max_nprobe,
                                                              const float *__restrict__ Q, SearchScratch S) {
   extern __shared__ float4 qs_all[];  // [wavefronts][kScanTileQueries][d / 4]
@@ -249,14 +251,14 @@ __global__ __launch_bounds__(kScanWaves * kWave) void k_scan(Dev D, int max_npro
   const uint32_t g_begin = (uint32_t)__builtin_amdgcn_readfirstlane((int)desc.w) * seg;
   switch (pairs) {
     case 0: break;
-    case 1: scan_item<METRIC, 1, ST>(D, S, Q, max_nprobe, list, first, g_begin, seg, qs); break;
-    case 2: scan_item<METRIC, 2, ST>(D, S, Q, max_nprobe, list, first, g_begin, seg, qs); break;
-    case 3: scan_item<METRIC, 3, ST>(D, S, Q, max_nprobe, list, first, g_begin, seg, qs); break;
-    case 4: scan_item<METRIC, 4, ST>(D, S, Q, max_nprobe, list, first, g_begin, seg, qs); break;
-    case 5: scan_item<METRIC, 5, ST>(D, S, Q, max_nprobe, list, first, g_begin, seg, qs); break;
-    case 6: scan_item<METRIC, 6, ST>(D, S, Q, max_nprobe, list, first, g_begin, seg, qs); break;
-    case 7: scan_item<METRIC, 7, ST>(D, S, Q, max_nprobe, list, first, g_begin, seg, qs); break;
-    default: scan_item<METRIC, 8, ST>(D, S, Q, max_nprobe, list, first, g_begin, seg, qs); break;
+    case 1: scan_item<METRIC, 1, ST, G, P>(D, S, Q, max_nprobe, list, first, g_begin, seg, qs); break;
+    case 2: scan_item<METRIC, 2, ST, G, P>(D, S, Q, max_nprobe, list, first, g_begin, seg, qs); break;
+    case 3: scan_item<METRIC, 3, ST, G, P>(D, S, Q, max_nprobe, list, first, g_begin, seg, qs); break;
+    case 4: scan_item<METRIC, 4, ST, G, P>(D, S, Q, max_nprobe, list, first, g_begin, seg, qs); break;
+    case 5: scan_item<METRIC, 5, ST, G, P>(D, S, Q, max_nprobe, list, first, g_begin, seg, qs); break;
+    case 6: scan_item<METRIC, 6, ST, G, P>(D, S, Q, max_nprobe, list, first, g_begin, seg, qs); break;
+    case 7: scan_item<METRIC, 7, ST, G, P>(D, S, Q, max_nprobe, list, first, g_begin, seg, qs); break;
+    default: scan_item<METRIC, 8, ST, G, P>(D, S, Q, max_nprobe, list, first, g_begin, seg, qs); break;
   }
 }
 
@@ -273,15 +275,15 @@ void launch_scan(const Dev &D, int64_t nq, int nprobe, int max_nprobe, const flo
     launch_scan_mm(D, sh, max_nprobe, Q, S, s);
     return;
   }
-  const dim3 grid((unsigned)sh.grid), block((unsigned)sh.threads);
-  switch (D.metric * 3 + D.storage) {
-    case 0: hipLaunchKernelGGL((k_scan<0, 0>), grid, block, sh.lds, s, D, max_nprobe, Q, S); break;
-    case 1: hipLaunchKernelGGL((k_scan<0, 1>), grid, block, sh.lds, s, D, max_nprobe, Q, S); break;
-    case 2: hipLaunchKernelGGL((k_scan<0, 2>), grid, block, sh.lds, s, D, max_nprobe, Q, S); break;
-    case 3: hipLaunchKernelGGL((k_scan<1, 0>), grid, block, sh.lds, s, D, max_nprobe, Q, S); break;
-    case 4: hipLaunchKernelGGL((k_scan<1, 1>), grid, block, sh.lds, s, D, max_nprobe, Q, S); break;
-    default: hipLaunchKernelGGL((k_scan<1, 2>), grid, block, sh.lds, s, D, max_nprobe, Q, S); break;
-  }
+  typedef void (*Kernel)(Dev, int, const float *, SearchScratch);
+  static const Kernel pairs[2][3] = {{k_scan<0, 0, 2, 2>, k_scan<0, 1, 2, 2>, k_scan<0, 2, 2, 2>},
+                                     {k_scan<1, 0, 2, 2>, k_scan<1, 1, 2, 2>, k_scan<1, 2, 2, 2>}};
+  static const Kernel singles[2][3] = {{k_scan<0, 0, 1, 4>, k_scan<0, 1, 1, 4>, k_scan<0, 2, 1, 4>},
+                                       {k_scan<1, 0, 1, 4>, k_scan<1, 1, 1, 4>, k_scan<1, 2, 1, 4>}};
+  static const Kernel deep_singles[2] = {k_scan<0, 0, 1, 8>, k_scan<1, 0, 1, 8>};
+  const Kernel kernel = sh.seg_base == 2 ? pairs[D.metric][D.storage]
+                        : D.storage == 0 && D.vchunks % 16 == 0 ? deep_singles[D.metric] : singles[D.metric][D.storage];
+  hipLaunchKernelGGL(kernel, dim3((unsigned)sh.grid), dim3((unsigned)sh.threads), sh.lds, s, D, max_nprobe, Q, S);
 }
 
 }  // namespace rtams

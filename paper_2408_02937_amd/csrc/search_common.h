@@ -385,7 +385,8 @@ constexpr int kScanWaves = 4;
 struct ScanShape {
   bool mm;           // the matrix-core kernel
   int tile_q;        // queries of a tile at most
-  int min_choice;    // shortest segment the plan may choose: 2 << min_choice groups of 64 vectors
+  int seg_base;      // segments are seg_base << choice groups of 64 vectors: 2, or 1 for small requests over short lists
+  int min_choice;    // the shortest the plan may choose
   int items_per_wg;  // items a workgroup takes
   int threads;       // of a workgroup
   int grid;          // workgroups
@@ -397,6 +398,13 @@ constexpr int kMmQueryWords = 12;      // 32-bit words of LDS per query of a til
 constexpr int kMmStageCap = 256;       // survivors a wavefront stages in LDS before it reserves their places
 constexpr size_t kMmStageBytes = (size_t)kMmStageCap * 9 + 8 * kMmTileMax;  // keys, positions, rows, and two words per query of the tile
 constexpr size_t kMmLdsMax = 160 * 1024 - 1024;  // what a workgroup may take of the CU's 160 KiB
+// The vector unit's scan walks groups singly where lists have so few that pairs leave much of the last one empty, and the
+// request has fewer than two groups for every SIMD.  Pairs / one at a time, us a request: 10 k x 32 in lists of 3 groups,
+// 10 and 64 queries x 8 probes, 47.2 / 45.6 and 49.5 / 47.0; 0.5 M x 768 in lists of 1, 1 and 8 queries x 32 probes,
+// 75.3 / 64.1 and 102.6 / 92.4; but 1 M x 128 in lists of 16, 1 and 2 queries, 60.2 / 61.0 and 63.2 / 64.5, and 12 queries
+// (6,100 groups) 80.9 / 86.7.
+constexpr int64_t kSingleList = 4;
+constexpr int64_t kSingleGroups = 2048;
 constexpr int kMmMinBatch = 64;        // queries of a request from which the matrix-core scan pays
 
 // Whether a request of 64 queries or more scans on the matrix cores.  A tile is the queries of the request that probe one
@@ -427,6 +435,7 @@ inline ScanShape scan_shape(const Dev &D, int item_budget) {
     int waves = kScanWaves;  // as many (4, 2, 1) as fit their query tiles into 64 KiB of LDS
     while (waves > 1 && per_wave * waves > 65536) waves /= 2;
     sh.tile_q = kScanTileQueries;
+    sh.seg_base = D.scan_single ? 1 : 2;
     sh.min_choice = 0;
     sh.items_per_wg = waves;
     sh.threads = waves * kWave;
@@ -441,6 +450,7 @@ inline ScanShape scan_shape(const Dev &D, int item_budget) {
   while (rows > 8 && row * rows + stage > 64 * 1024) rows /= 2;
   while (rows > 4 && row * rows + stage > kMmLdsMax) rows /= 2;
   sh.tile_q = rows;
+  sh.seg_base = 2;
   sh.min_choice = 2;  // at least 8 groups to an item, two for every wavefront (measured: 4 and 16 are slower)
   if (D.scan_min_choice >= 0) sh.min_choice = D.scan_min_choice;
   sh.items_per_wg = 1;

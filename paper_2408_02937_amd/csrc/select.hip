@@ -231,7 +231,28 @@ __global__ __launch_bounds__(kTopkThreads) void k_select(Dev D, int k, int nprob
       }
     }
   };
-  for (int next = 0; next < n;) {  // every branch here is uniform over the workgroup
+  // Records that all fit are taken as they come: every one of them passed the query's bound in the scan.  (Through the
+  // filter below, a count and a reservation per 64 of them, they cost the selection two microseconds more.)
+  int next = 0;
+  if (n <= kSurvivorCap) {
+    constexpr int kMine = kSurvivorCap / kTopkThreads;
+    uint32_t kv[kMine], pv[kMine];
+    const int last = n > 0 ? n - 1 : 0;
+#pragma unroll
+    for (int u = 0; u < kMine; ++u) {
+      const int j = (int)threadIdx.x + u * kTopkThreads;
+      if (u * kTopkThreads < n) { kv[u] = rk[j < n ? j : last]; pv[u] = rp[j < n ? j : last]; }  // uniform
+    }
+#pragma unroll
+    for (int u = 0; u < kMine; ++u) {
+      const int j = (int)threadIdx.x + u * kTopkThreads;
+      if (j < n) { skey[j] = kv[u]; sidx[j] = pv[u]; }
+    }
+    if (threadIdx.x == 0) scount = (uint32_t)n;
+    next = n;
+    __syncthreads();
+  }
+  while (next < n) {  // every branch here is uniform over the workgroup
     const int count = (int)scount;
     const int m = min(n - next, stretch * (kSurvivorCap - count));
     if (threadIdx.x == 0) s_over = 0;
