@@ -410,7 +410,10 @@ constexpr int kMmMinBatch = 64;        // queries of a request from which the ma
 // Whether a request of 64 queries or more scans on the matrix cores.  A tile is the queries of the request that probe one
 // list, and what speaks for the matrix cores is many queries to a list; what speaks against them is the set-up of a
 // workgroup per item, which short lists do not repay, and (inner products) that the vector unit needs one instruction
-// per coordinate where it needs two for squared distances.  Requests measured on both, vector unit / matrix cores:
+// per coordinate where it needs two for squared distances.  Squared distances between floats go by the first of these
+// alone, also where that costs a tenth: behind the matrix cores the selection scores its finalists again in four short
+// sums, which come out closer to 64 bits (2 to 3 times, at d 256) than the one long sum of the vector unit's scan.
+// Requests measured on both, vector unit / matrix cores:
 //  squared distances, floats, 1,024 lists of 977 x 128: 4 pairs to a list 158 / 171 us, 8 205 / 195, 16 281 / 215;
 //    lists of 390 x 200: 16 pairs 127 / 134;  halves: 2 pairs 110 / 110, 4 133 / 126;  bytes: 1 pair 89 / 92, 2 110 / 103
 //  inner products, lists of 1,950 x 96: 1 pair 164 / 171, 2 204 / 200, 8 250 / 232;  lists of 390 x 96: 16 pairs 91 / 98;
@@ -420,8 +423,9 @@ constexpr int kMmMinBatch = 64;        // queries of a request from which the ma
 //    4,096 lists of 488 x 64: 64 queries 134 / 137 us, 256 228 / 203;  1,024 lists of 3,906 x 128: 64 371 / 333, 256 602 / 469
 inline bool mm_scan_pays(const Dev &D, int64_t nq, int64_t nprobe, int64_t avg_len, int64_t max_len) {
   const int64_t pairs = nq * nprobe, nlist = D.nlist;
+  if (D.metric == 0 && D.storage == 0) return pairs >= nlist || max_len >= 16 * avg_len;
   if (max_len >= 16 * avg_len && avg_len >= 448 && (nq >= 128 || pairs >= nlist)) return true;
-  if (D.metric == 0) return avg_len >= 512 && pairs >= (D.storage == 0 ? 8 : D.storage == 1 ? 4 : 2) * nlist;
+  if (D.metric == 0) return avg_len >= 512 && pairs >= (D.storage == 1 ? 4 : 2) * nlist;
   return D.d <= 128 && avg_len >= 1024 && pairs >= (D.storage == 0 ? 2 : 16) * nlist;
 }
 
