@@ -30,9 +30,11 @@
 // (What this replaces: three products of bf16 pairs, a band of 2^-14 of the squared
 // norms, three times the matrix instructions and twice the operand bytes: 324 us for
 // 13,107 x 16,384 x 256, 728 us for 21,845 x 8,192 x 768.)
-// Vectors or centroids whose band is not finite (infinities, overflow) are scored
-// exactly against every centroid; a vector with a NaN compares with nothing and goes
-// to the first list, as it does in the exact arithmetic.
+// Vectors whose band is not finite (infinities, overflow, centroids that are not finite or
+// too large) are scored exactly against every centroid: their scale is zero, so that every
+// approximate score is the centroid's bias, a finite number, and none drops out.  A vector
+// with a NaN compares with nothing and goes to the first list, as it does in the exact
+// arithmetic.
 //
 // For a search the whole score matrix is written (probe selection needs the
 // nprobe-th smallest of a row).  For an assignment it is not: each workgroup
@@ -126,7 +128,9 @@ __global__ __launch_bounds__(256) void k_centroid_mean(Dev D) {
   __syncthreads();
   if (threadIdx.x < 4) {
     const double *p = s_sum[threadIdx.x];
-    D.cmean[4 * j + threadIdx.x] = (float)((p[0] + p[1] + p[2] + p[3]) / (double)D.nlist);
+    const float m = (float)((p[0] + p[1] + p[2] + p[3]) / (double)D.nlist);
+    // (a centroid that is not finite has no share in the mean, or it would take every vector with it)
+    D.cmean[4 * j + threadIdx.x] = fabsf(m) < __builtin_inff() ? m : 0.f;
   }
 }
 
@@ -230,14 +234,17 @@ __global__ __launch_bounds__(256) void k_half_rows(Dev D, int64_t n, const float
   const float iy = 1.f / scale, ic = 1.f / half_scale(__uint_as_float(st.top_bits));  // powers of two: exact
   const float g = D.metric == 0 ? 2.f : 1.f;
   const float ny = sqrtf(nsq), ry = sqrtf(rsq), nc = __uint_as_float(st.norm_bits), rc = __uint_as_float(st.res_bits);
-  const float s = g * iy * ic;
+  float s = g * iy * ic;
   const float e = s * (ry * nc + (ny + ry) * rc + (float)D.d * 1.1920929e-7f * (ny + ry) * (nc + rc));
   const float uy = ny * iy, uc = nc * ic;  // the norms themselves
   const float m = D.metric == 0 ? (uy + uc) * (uy + uc) : uc * (st.mean_norm + 2.f * uy);
   float band = 2.f * (1.01f * e + 2.3841858e-7f * 1.01f * (__uint_as_float(st.bias_bits) + s * ny * nc + m)) * 1.01f;
   // nothing is told apart by the filter where the band says nothing: infinities, or numbers at the ends of the
   // float range (a NaN in the vector stays out: no comparison holds for it anywhere)
-  if (bad || st.bad != 0u || !(band > 1e-28f) || !(band < 1e37f) || !(s > 1e-30f)) band = __builtin_inff();
+  if (bad || st.bad != 0u || !(band > 1e-28f) || !(band < 1e37f) || !(s > 1e-30f)) {
+    band = __builtin_inff();
+    s = 0.f;  // (the products may overflow, or the scale itself, which times a product of zero is a NaN)
+  }
   meta[i] = RowMeta{s, band};
 }
 
@@ -374,7 +381,8 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void k_coarse_mfma(Dev D, int64_t 
     const int64_t i = row0 + wv * 64 + b * 32 + (lane & 31);
     mt[b] = meta[i < n ? i : n - 1];
   }
-  // scores in place; centroids past the last one score +inf (their bias; their halves are finite), all others less
+  // scores in place; centroids past the last one score +inf or a NaN (their bias is infinite, their halves are whatever
+  // the memory holds), all others less than infinity unless the vector holds a NaN
 #pragma unroll
   for (int a = 0; a < CA; ++a)
 #pragma unroll
