@@ -174,11 +174,23 @@ __device__ bool wg_open(const Dev &D, int list, uint32_t nb_old, uint32_t newlen
   return true;
 }
 
+// The longest list with this batch, a list's new length to a thread (0: none).  The lengths are final once the positions
+// are reserved, so this is done in front of the publication, whose one reporting thread then tells the host: a word of
+// host memory that every wavefront with a longer list wrote for itself could keep the smaller of two, and did not get
+// its due until some list grew past the larger.  `known`: ctrl->max_len as of any time before (it only grows).
+__device__ inline void note_longest(const Dev &D, uint32_t newlen, uint32_t known) {
+  if (!__any(newlen > known)) return;  // uniform over the wavefront
+  for (int o = kWave / 2; o > 0; o >>= 1) newlen = max(newlen, (uint32_t)__shfl_xor((int)newlen, o));
+  if ((threadIdx.x & (kWave - 1)) == 0) atomicMax(&D.ctrl->max_len, newlen);
+}
+
 __global__ __launch_bounds__(256) void k_open(Dev D) {
   __shared__ OpenShared<256> sh;
   const int list = blockIdx.x * blockDim.x + threadIdx.x;
   const bool on = list < D.nlist;
-  wg_open<256>(D, on ? list : -1, on ? D.nblk[list] : 0u, on ? D.reserved_len[list] : 0u, sh);
+  const uint32_t newlen = on ? D.reserved_len[list] : 0u;
+  note_longest(D, newlen, D.ctrl->max_len);
+  wg_open<256>(D, on ? list : -1, on ? D.nblk[list] : 0u, newlen, sh);
 }
 
 // ---- fill: chunk c (16 bytes: 4 floats, 8 halves or 16 bytes) of a vector, as the lists keep it
@@ -219,17 +231,13 @@ __global__ __launch_bounds__(256) void k_fill(Dev D, int64_t n, const float *__r
 // this the longest of the insertion kernels); and what the host is told is written last.
 __device__ inline void wg_publish(const Dev &D, int list) {
   const uint32_t T = (uint32_t)D.T_m;
-  uint32_t newlen = 0, added = 0, told_exceed = 0;
+  uint32_t added = 0, told_exceed = 0;
   if (list >= 0) {
-    newlen = D.reserved_len[list];
-    const uint32_t old = D.visible_len[list], on0 = D.online[list];
+    const uint32_t newlen = D.reserved_len[list], old = D.visible_len[list], on0 = D.online[list];
     const bool exceeds = D.exceed[list] != 0, failed = pool_failed(D);
-    if (newlen == old) {
-      newlen = 0;
-    } else if (failed) {  // the batch is dropped as a whole
+    if (newlen != old && failed) {  // the batch is dropped as a whole
       D.reserved_len[list] = old;
-      newlen = 0;
-    } else {
+    } else if (newlen != old) {
       for (uint32_t bi = old / T; bi <= (newlen - 1) / T; ++bi) {
         uint32_t b = (uint32_t)*table_entry(D, list, bi);
         uint32_t sz = newlen - bi * T;
@@ -244,32 +252,26 @@ __device__ inline void wg_publish(const Dev &D, int list) {
       __hip_atomic_store(&D.visible_len[list], newlen, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
-  uint32_t longest = newlen, sum = added;  // (a batch of one insertion round holds fewer than 2^32 vectors)
-  for (int o = kWave / 2; o > 0; o >>= 1) {
-    longest = max(longest, (uint32_t)__shfl_xor((int)longest, o));
-    sum += __shfl_xor(sum, o);
-  }
+  uint32_t sum = added;  // (a batch of one insertion round holds fewer than 2^32 vectors)
+  for (int o = kWave / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
   if (told_exceed) D.mirror->exceed_lists = told_exceed;
-  if ((threadIdx.x & (kWave - 1)) == 0 && sum) {
-    atomicAdd(&D.ctrl->ntotal, (unsigned long long)sum);
-    const uint32_t m = atomicMax(&D.ctrl->max_len, longest);
-    if (longest > m) D.mirror->max_len = longest;
-  }
+  if ((threadIdx.x & (kWave - 1)) == 0 && sum) atomicAdd(&D.ctrl->ntotal, (unsigned long long)sum);
 }
 
-// The allocator's counters are final for this batch (every block is open, and every rearrangement
-// round enqueued before it has returned its spare blocks): the host learns the blocks in use.
-__device__ inline void report_pool(const Dev &D, uint32_t call_seq) {
+// The allocator's counters and the longest list are final for this batch (every block is open, and every rearrangement
+// round enqueued before it has returned its spare blocks): one thread tells the host, in one store of 16 bytes.
+__device__ inline void report(const Dev &D, uint32_t call_seq) {
   const int32_t f = __hip_atomic_load(&D.ctrl->free_top, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint32_t in_use =
       __hip_atomic_load(&D.ctrl->cur_P, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - (uint32_t)(f > 0 ? f : 0);
-  D.mirror->pool_word = ((unsigned long long)call_seq << 32) | in_use;
+  const uint32_t longest = __hip_atomic_load(&D.ctrl->max_len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  *reinterpret_cast<u32x4 *>(const_cast<unsigned long long *>(&D.mirror->pool_word)) = u32x4{in_use, call_seq, 0u, longest};
 }
 
 __global__ __launch_bounds__(256) void k_publish(Dev D, uint32_t call_seq) {
   int list = blockIdx.x * blockDim.x + threadIdx.x;
   wg_publish(D, list < D.nlist ? list : -1);
-  if (list == 0) report_pool(D, call_seq);
+  if (list == 0) report(D, call_seq);
 }
 
 // ---- a batch of up to kTailVecs vectors behind its coarse scores: one workgroup, a vector to a thread.  The vector
@@ -300,6 +302,7 @@ __global__ __launch_bounds__(kTailVecs) void k_insert_tail(Dev D, int n, int spl
     for (int u = 0; u < kAhead; ++u)
       ahead[u] = tid + u * kTailVecs < chunks ? y4[tid + u * kTailVecs] : make_float4(0.f, 0.f, 0.f, 0.f);
   }
+  const uint32_t known = D.ctrl->max_len;
   int64_t id = 0;
   if (FILL && tid < n) id = ids ? ids[tid] : id_base + tid;
   int list = -1;
@@ -319,6 +322,7 @@ __global__ __launch_bounds__(kTailVecs) void k_insert_tail(Dev D, int n, int spl
   __syncthreads();  // every position is taken
   if (FILL && tid < n && mid < nb) blk = (uint32_t)*table_entry(D, list, mid);
   const uint32_t newlen = leads ? D.reserved_len[list] : 0u;
+  note_longest(D, newlen, known);
   const bool opened = wg_open<kTailVecs>(D, leads ? list : -1, nb, newlen, sh);
   if (!FILL) return;  // uniform
   if (opened) {  // uniform
@@ -347,7 +351,7 @@ __global__ __launch_bounds__(kTailVecs) void k_insert_tail(Dev D, int n, int spl
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's part of the vectors is out ...
   __syncthreads();                                  // ... and so is everybody's before any list is published
   wg_publish(D, leads ? list : -1);
-  if (tid == 0) report_pool(D, call_seq);
+  if (tid == 0) report(D, call_seq);
 }
 
 // ... and the opening and the publication of a larger batch, a vector to a thread, in several workgroups (a thousand
@@ -363,12 +367,14 @@ __global__ __launch_bounds__(kBatchThreads) void k_open_batch(Dev D, int n, cons
                                                               const uint32_t *__restrict__ did) {
   __shared__ OpenShared<kBatchThreads> sh;
   const int list = led_list(D, n, assign, did);
-  wg_open<kBatchThreads>(D, list, list >= 0 ? D.nblk[list] : 0u, list >= 0 ? D.reserved_len[list] : 0u, sh);
+  const uint32_t newlen = list >= 0 ? D.reserved_len[list] : 0u;
+  note_longest(D, newlen, D.ctrl->max_len);
+  wg_open<kBatchThreads>(D, list, list >= 0 ? D.nblk[list] : 0u, newlen, sh);
 }
 __global__ __launch_bounds__(kBatchThreads) void k_publish_batch(Dev D, int n, const int32_t *__restrict__ assign,
                                                                  const uint32_t *__restrict__ did, uint32_t call_seq) {
   wg_publish(D, led_list(D, n, assign, did));
-  if (blockIdx.x == 0 && threadIdx.x == 0) report_pool(D, call_seq);
+  if (blockIdx.x == 0 && threadIdx.x == 0) report(D, call_seq);
 }
 
 // ---------------------------------------------------------------- launchers

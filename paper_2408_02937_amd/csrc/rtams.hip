@@ -328,6 +328,9 @@ void tighten_pool_bound(rtams_index *ix) {
   if (left > ix->avail_lb) ix->avail_lb = left;
 }
 
+// Length of the longest list as of the last publication the device reported.
+int64_t longest_list(const rtams_index *ix) { return (int64_t)(ix->mirror->len_word >> 32); }
+
 // Orders this call behind the previous work of the data stream.
 int enter_data_stream(rtams_index *ix, hipStream_t s) {
   if (ix->have_data_stream && ix->data_stream != s) HIP_TRY(hipStreamWaitEvent(s, ix->data_done, 0));
@@ -770,7 +773,7 @@ static int search_on(rtams_index *ix, int r, int64_t nq, const float *d_queries,
     const int64_t mode = ix->scan_mfma.load(std::memory_order_relaxed);
     const int64_t avg_len = ix->ntotal_host / ix->cfg.nlist + 1;
     D.scan_mfma = D.pq_m == 0 && (mode == 2 || (mode == 1 && nq >= kMmMinBatch &&
-                                                mm_scan_pays(D, nq, nprobe, avg_len, (int64_t)ix->mirror->max_len)));
+                                                mm_scan_pays(D, nq, nprobe, avg_len, longest_list(ix))));
   }
   const int64_t avg_groups = ix->ntotal_host / ix->cfg.nlist / kWave + 1;
   D.scan_single = !D.scan_mfma && D.pq_m == 0 && avg_groups <= kSingleList && nq * nprobe * avg_groups < kSingleGroups;
@@ -802,7 +805,7 @@ static int search_on(rtams_index *ix, int r, int64_t nq, const float *d_queries,
     const ScanShape sh = scan_shape(D, (int)budget);
     const int64_t seg_vecs = (int64_t)kWave * (sh.seg_base << sh.min_choice);
     const int64_t probed = nq * nprobe < ix->cfg.nlist ? nq * nprobe : ix->cfg.nlist;
-    const int64_t longest = (int64_t)ix->mirror->max_len;
+    const int64_t longest = longest_list(ix);
     int64_t segs = ix->ntotal_host / seg_vecs + probed;  // of the probed lists together, every one rounded up
     const int64_t by_longest = probed * (longest / seg_vecs + 1);
     if (by_longest < segs) segs = by_longest;
