@@ -260,18 +260,18 @@ __device__ inline void wg_publish(const Dev &D, int list) {
 
 // The allocator's counters and the longest list are final for this batch (every block is open, and every rearrangement
 // round enqueued before it has returned its spare blocks): one thread tells the host, in one store of 16 bytes.
-__device__ inline void report(const Dev &D, uint32_t call_seq) {
+__device__ inline void report(const Dev &D, uint32_t call_seq, uint32_t total) {
   const int32_t f = __hip_atomic_load(&D.ctrl->free_top, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint32_t in_use =
       __hip_atomic_load(&D.ctrl->cur_P, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - (uint32_t)(f > 0 ? f : 0);
   const uint32_t longest = __hip_atomic_load(&D.ctrl->max_len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  *reinterpret_cast<u32x4 *>(const_cast<unsigned long long *>(&D.mirror->pool_word)) = u32x4{in_use, call_seq, 0u, longest};
+  *reinterpret_cast<u32x4 *>(const_cast<unsigned long long *>(&D.mirror->pool_word)) = u32x4{in_use, call_seq, total, longest};
 }
 
-__global__ __launch_bounds__(256) void k_publish(Dev D, uint32_t call_seq) {
+__global__ __launch_bounds__(256) void k_publish(Dev D, uint32_t call_seq, uint32_t total) {
   int list = blockIdx.x * blockDim.x + threadIdx.x;
   wg_publish(D, list < D.nlist ? list : -1);
-  if (list == 0) report(D, call_seq);
+  if (list == 0) report(D, call_seq, total);
 }
 
 // ---- a batch of up to kTailVecs vectors behind its coarse scores: one workgroup, a vector to a thread.  The vector
@@ -288,7 +288,7 @@ __global__ __launch_bounds__(kTailVecs) void k_insert_tail(Dev D, int n, int spl
                                                            const float *__restrict__ Y,
                                                            const int64_t *__restrict__ ids, int64_t id_base,
                                                            int32_t *__restrict__ assign, uint32_t *__restrict__ did,
-                                                           uint32_t call_seq) {
+                                                           uint32_t call_seq, uint32_t total) {
   __shared__ OpenShared<kTailVecs> sh;
   __shared__ uint32_t s_blk[kTailVecs], s_off[kTailVecs];  // where every vector goes (block ~0: nowhere)
   constexpr int kAhead = 4;  // chunks of the batch a thread has in registers from the start
@@ -351,7 +351,7 @@ __global__ __launch_bounds__(kTailVecs) void k_insert_tail(Dev D, int n, int spl
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's part of the vectors is out ...
   __syncthreads();                                  // ... and so is everybody's before any list is published
   wg_publish(D, leads ? list : -1);
-  if (tid == 0) report(D, call_seq);
+  if (tid == 0) report(D, call_seq, total);
 }
 
 // ... and the opening and the publication of a larger batch, a vector to a thread, in several workgroups (a thousand
@@ -372,9 +372,10 @@ __global__ __launch_bounds__(kBatchThreads) void k_open_batch(Dev D, int n, cons
   wg_open<kBatchThreads>(D, list, list >= 0 ? D.nblk[list] : 0u, newlen, sh);
 }
 __global__ __launch_bounds__(kBatchThreads) void k_publish_batch(Dev D, int n, const int32_t *__restrict__ assign,
-                                                                 const uint32_t *__restrict__ did, uint32_t call_seq) {
+                                                                 const uint32_t *__restrict__ did, uint32_t call_seq,
+                                                                 uint32_t total) {
   wg_publish(D, led_list(D, n, assign, did));
-  if (blockIdx.x == 0 && threadIdx.x == 0) report(D, call_seq);
+  if (blockIdx.x == 0 && threadIdx.x == 0) report(D, call_seq, total);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -412,26 +413,26 @@ constexpr int64_t kTailChunks = 4 * kTailVecs;
 bool tail_fills(const Dev &D, int64_t n) { return n <= kTailVecs && D.pq_m == 0 && n * D.vchunks <= kTailChunks; }
 
 void launch_insert_tail(const Dev &D, int64_t n, int splits, const float *Y, const int64_t *ids, int64_t id_base,
-                        const InsertScratch &S, uint32_t call_seq, hipStream_t s) {
+                        const InsertScratch &S, uint32_t call_seq, uint32_t total, hipStream_t s) {
   const dim3 batch((unsigned)((n + kBatchThreads - 1) / kBatchThreads));
   if (tail_fills(D, n))
     hipLaunchKernelGGL(k_insert_tail<true>, dim3(1), dim3(kTailVecs), 0, s, D, (int)n, splits, S.pscore, S.pidx, Y, ids,
-                       id_base, S.assign, S.did, call_seq);
+                       id_base, S.assign, S.did, call_seq, total);
   else if (splits > 0)
     hipLaunchKernelGGL(k_insert_tail<false>, dim3(1), dim3(kTailVecs), 0, s, D, (int)n, splits, S.pscore, S.pidx, Y,
-                       ids, id_base, S.assign, S.did, call_seq);
+                       ids, id_base, S.assign, S.did, call_seq, total);
   else
     hipLaunchKernelGGL(k_open_batch, batch, dim3(kBatchThreads), 0, s, D, (int)n, S.assign, S.did);
 }
 
-void launch_publish_batch(const Dev &D, int64_t n, const InsertScratch &S, uint32_t call_seq, hipStream_t s) {
+void launch_publish_batch(const Dev &D, int64_t n, const InsertScratch &S, uint32_t call_seq, uint32_t total, hipStream_t s) {
   const dim3 batch((unsigned)((n + kBatchThreads - 1) / kBatchThreads));
-  hipLaunchKernelGGL(k_publish_batch, batch, dim3(kBatchThreads), 0, s, D, (int)n, S.assign, S.did, call_seq);
+  hipLaunchKernelGGL(k_publish_batch, batch, dim3(kBatchThreads), 0, s, D, (int)n, S.assign, S.did, call_seq, total);
 }
 
-void launch_publish(const Dev &D, uint32_t call_seq, hipStream_t s) {
+void launch_publish(const Dev &D, uint32_t call_seq, uint32_t total, hipStream_t s) {
   unsigned grid = (unsigned)((D.nlist + 255) / 256);
-  hipLaunchKernelGGL(k_publish, dim3(grid), dim3(256), 0, s, D, call_seq);
+  hipLaunchKernelGGL(k_publish, dim3(grid), dim3(256), 0, s, D, call_seq, total);
 }
 
 }  // namespace rtams

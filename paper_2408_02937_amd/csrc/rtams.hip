@@ -330,6 +330,12 @@ void tighten_pool_bound(rtams_index *ix) {
 
 // Length of the longest list as of the last publication the device reported.
 int64_t longest_list(const rtams_index *ix) { return (int64_t)(ix->mirror->len_word >> 32); }
+// No list is longer than this once every batch enqueued so far is in: that length, and all vectors handed over since.
+// (A pool has at most 2^32 places, so the difference modulo 2^32 is the difference.)
+int64_t longest_list_bound(const rtams_index *ix) {
+  const unsigned long long w = ix->mirror->len_word;
+  return (int64_t)(w >> 32) + (int64_t)(uint32_t)((uint32_t)ix->ntotal_host.load() - (uint32_t)w);
+}
 
 // Orders this call behind the previous work of the data stream.
 int enter_data_stream(rtams_index *ix, hipStream_t s) {
@@ -721,6 +727,7 @@ int rtams_add(rtams_index *ix, int64_t n, const float *d_vecs, const int64_t *d_
     const int64_t id_base = ix->ntotal_host + o;
     // only its last round completes the call: the rounds before it report under the call before
     const uint32_t report = o + round >= n ? seq : seq - 1u;
+    const uint32_t total = (uint32_t)(id_base + m);
     const bool small = m <= kTailVecs;
     int splits = 0;
     if (ordered) {
@@ -729,13 +736,13 @@ int rtams_add(rtams_index *ix, int64_t n, const float *d_vecs, const int64_t *d_
     } else {
       splits = assign_round(ix, m, Y, true, small, ix->ins.assign, s);
     }
-    if (small) launch_insert_tail(D, m, splits, Y, ids, id_base, ix->ins, report, s);
+    if (small) launch_insert_tail(D, m, splits, Y, ids, id_base, ix->ins, report, total, s);
     else launch_open(D, s);
     if (small && tail_fills(D, m)) continue;  // filled and published
     if (D.pq_m > 0) launch_pq_fill(D, m, Y, ids, id_base, ix->ins, s);
     else launch_fill(D, m, Y, ids, id_base, ix->ins, s);
-    if (small) launch_publish_batch(D, m, ix->ins, report, s);
-    else launch_publish(D, report, s);
+    if (small) launch_publish_batch(D, m, ix->ins, report, total, s);
+    else launch_publish(D, report, total, s);
   }
   HIP_TRY(hipGetLastError());
   ix->avail_lb -= need;
@@ -769,6 +776,8 @@ static int search_on(rtams_index *ix, int r, int64_t nq, const float *d_queries,
                      float *d_out_dist, int64_t *d_out_ids, void *hip_stream) {
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   Dev D = ix->dev;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  const bool recorded = hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusActive;
   {  // flat lists: which unit scans (0 the vector unit, 1 by the rule, 2 the matrix cores)
     const int64_t mode = ix->scan_mfma.load(std::memory_order_relaxed);
     const int64_t avg_len = ix->ntotal_host / ix->cfg.nlist + 1;
@@ -776,7 +785,7 @@ static int search_on(rtams_index *ix, int r, int64_t nq, const float *d_queries,
                                                 mm_scan_pays(D, nq, nprobe, avg_len, longest_list(ix))));
   }
   const int64_t avg_groups = ix->ntotal_host / ix->cfg.nlist / kWave + 1;
-  D.scan_single = !D.scan_mfma && D.pq_m == 0 && avg_groups <= kSingleList && nq * nprobe * avg_groups < kSingleGroups;
+  D.scan_single = !recorded && !D.scan_mfma && D.pq_m == 0 && avg_groups <= kSingleList && nq * nprobe * avg_groups < kSingleGroups;
   D.scan_byte_weight = (int32_t)ix->scan_byte_weight.load(std::memory_order_relaxed);
   D.scan_min_choice = (int32_t)ix->scan_min_choice.load(std::memory_order_relaxed);
   // a long scan: its (query, list) pairs are expected to meet this many list bytes (lists of average length)
@@ -797,15 +806,16 @@ static int search_on(rtams_index *ix, int r, int64_t nq, const float *d_queries,
   const int64_t cap = ix->scan_max_items.load(std::memory_order_relaxed);
   if (budget > cap) budget = cap;
   if (budget < nq * nprobe) budget = nq * nprobe;  // a (query, list) pair is at least one item
-  // ... but never more than the plan can want at its shortest segments, lists being as long as the host knows: the scan
-  // is launched for the whole budget, and workgroups that find their range of items used up each take a place on the
-  // chip and a trip to memory (256 queries x 32 probes over 1 M x 128: 49,152 workgroups for 2,048 items).  Lists that
-  // grow meanwhile get longer segments.
-  if (D.pq_m == 0) {
+  // ... but never more than the plan can want at its shortest segments, with every vector handed to add so far in its
+  // list, the batches still on their way among them: the scan is launched for the whole budget, and workgroups that
+  // find their range of items used up each take a place on the chip and a trip to memory (256 queries x 32 probes over
+  // 1 M x 128: 49,152 workgroups for 2,048 items).  Vectors that are handed over while the search runs get longer
+  // segments.  A request recorded into a graph runs when the lists may have any length.
+  if (D.pq_m == 0 && !recorded) {
     const ScanShape sh = scan_shape(D, (int)budget);
     const int64_t seg_vecs = (int64_t)kWave * (sh.seg_base << sh.min_choice);
     const int64_t probed = nq * nprobe < ix->cfg.nlist ? nq * nprobe : ix->cfg.nlist;
-    const int64_t longest = longest_list(ix);
+    const int64_t longest = longest_list_bound(ix);
     int64_t segs = ix->ntotal_host / seg_vecs + probed;  // of the probed lists together, every one rounded up
     const int64_t by_longest = probed * (longest / seg_vecs + 1);
     if (by_longest < segs) segs = by_longest;

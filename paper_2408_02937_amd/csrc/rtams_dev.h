@@ -65,7 +65,9 @@ struct HostMirror {
   // of them whole.  pool_word: (number of the last insertion call published << 32) | blocks in use after it.  The host
   // takes from it how many blocks are left without waiting for the data stream.
   alignas(16) volatile unsigned long long pool_word;
-  volatile unsigned long long len_word;  // length of the longest list << 32
+  // (length of the longest list << 32) | vectors handed to add up to this batch, modulo 2^32: with what the host has
+  // handed over since, a bound of any list at any time.
+  volatile unsigned long long len_word;
 };
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));

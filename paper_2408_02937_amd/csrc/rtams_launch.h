@@ -166,14 +166,15 @@ void launch_reserve_ordered(const Dev &D, int64_t n, const InsertScratch &S, hip
 void launch_open(const Dev &D, hipStream_t s);
 void launch_fill(const Dev &D, int64_t n, const float *Y, const int64_t *ids, int64_t id_base,
                  const InsertScratch &S, hipStream_t s);
-void launch_publish(const Dev &D, uint32_t call_seq, hipStream_t s);
+// (publications report to the host under the call's number and with `total`, the vectors handed to add so far)
+void launch_publish(const Dev &D, uint32_t call_seq, uint32_t total, hipStream_t s);
 // A batch of at most kTailVecs vectors: reservation (splits > 0: from the partial minima; 0: done), opening and,
 // where tail_fills() says so, filling and publication; otherwise a fill and launch_publish_batch follow.
 constexpr int kTailVecs = 1024;
 bool tail_fills(const Dev &D, int64_t n);
 void launch_insert_tail(const Dev &D, int64_t n, int splits, const float *Y, const int64_t *ids, int64_t id_base,
-                        const InsertScratch &S, uint32_t call_seq, hipStream_t s);
-void launch_publish_batch(const Dev &D, int64_t n, const InsertScratch &S, uint32_t call_seq, hipStream_t s);
+                        const InsertScratch &S, uint32_t call_seq, uint32_t total, hipStream_t s);
+void launch_publish_batch(const Dev &D, int64_t n, const InsertScratch &S, uint32_t call_seq, uint32_t total, hipStream_t s);
 
 // probe.hip, group.hip, scan.hip, pq_scan.hip, select.hip ---------------------
 void launch_probe_plan(const Dev &D, int64_t nq, int nprobe, int max_nprobe, const SearchScratch &S,
