@@ -134,14 +134,11 @@ __global__ __launch_bounds__(kSelThreadsMany) void k_probe_plan(Dev D, int64_t n
       }
       wg_sort(nc, k1, k2, pay);  // by (exact score, index): the first nprobe are the answer
       done = true;
-    } else {
-      for (int i = threadIdx.x; i < n; i += T) sc[i] = exact(i);  // the filter did not narrow it: whole row
-      __syncthreads();
     }
   }
   SelectResult r1{~0ull, 0, 0}, r2{~0ull, 0, 0};
   const bool all = nprobe >= n;
-  if (!done && FROM_APPROX && all) {  // every list is probed: exact order of the whole row
+  if (!done && FROM_APPROX) {  // the filter did not narrow it, or every list is probed: exact order of the whole row
     for (int i = threadIdx.x; i < n; i += T) sc[i] = exact(i);
     __syncthreads();
   }

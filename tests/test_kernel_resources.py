@@ -1,5 +1,5 @@
-"""What the compiler gave the kernels of the built library, read from the code objects inside it: the kernels whose
-comments count on a number of wavefronts per SIMD have the registers for it."""
+"""What the compiler gave the kernels of the built library, read from the code objects inside it: no kernel keeps
+private memory, and the kernels whose comments count on a number of wavefronts per SIMD have the registers for it."""
 import os
 import struct
 
@@ -53,6 +53,10 @@ def records():
     out = {k[".name"]: k for e in code_objects(blob) for k in kernels(e)}
     assert len(out) > 40, "the code objects of the library could not be read"
     return out
+
+
+def test_no_kernel_keeps_private_memory(records):
+    assert {n: k[".private_segment_fixed_size"] for n, k in records.items() if k[".private_segment_fixed_size"]} == {}
 
 
 def test_the_selection_runs_two_workgroups_to_a_compute_unit(records):
