@@ -240,8 +240,11 @@ __global__ __launch_bounds__(256) void k_half_rows(Dev D, int64_t n, const float
   const float m = D.metric == 0 ? (uy + uc) * (uy + uc) : uc * (st.mean_norm + 2.f * uy);
   float band = 2.f * (1.01f * e + 2.3841858e-7f * 1.01f * (__uint_as_float(st.bias_bits) + s * ny * nc + m)) * 1.01f;
   // nothing is told apart by the filter where the band says nothing: infinities, or numbers at the ends of the
-  // float range (a NaN in the vector stays out: no comparison holds for it anywhere)
-  if (bad || st.bad != 0u || !(band > 1e-28f) || !(band < 1e37f) || !(s > 1e-30f)) {
+  // float range (a NaN in the vector stays out: no comparison holds for it anywhere).  The lower end: the scale has to be
+  // a normal float, and the hundredth by which the band is widened has to cover what the dozen operations of the band, the
+  // bias and the score lose below the smallest normal float, 1.2e-38 each even if subnormals became zero.  Vectors and
+  // centroids of norms down to 1e-14 stay above both; what lies below is scored exactly against every centroid.
+  if (bad || st.bad != 0u || !(band > 1e-34f) || !(band < 1e37f) || !(s >= 1.17549435e-38f)) {
     band = __builtin_inff();
     s = 0.f;  // (the products may overflow, or the scale itself, which times a product of zero is a NaN)
   }

@@ -60,3 +60,31 @@ def test_the_filter_decides_as_the_exact_kernel(kind, metric, nlist, d, rows):
     assert np.array_equal(got[2][some], o.assign(y[some]))
     torch.cuda.synchronize()
     g.close()
+
+
+@pytest.mark.parametrize("metric", ["l2", "ip"])
+def test_tiny_numbers_stay_in_the_filter(metric):
+    """The same vectors and centroids times 2^-46 (norms of 1e-13): the same lists, and not an exact score for every
+    centroid, which takes more than ten times as long."""
+    rng = np.random.default_rng(46)
+    d, nlist, rows = 64, 4096, 65_536
+    C = rng.standard_normal((nlist, d)).astype(np.float32)
+    y = (C[rng.integers(0, nlist, rows)] + 0.1 * rng.standard_normal((rows, d))).astype(np.float32)
+    got, ms = [], []
+    for f in (1.0, 2.0 ** -46):
+        w = synth.Workload("tiny", metric, d, nlist, 64, 8, 10, np.zeros((0, d), np.float32), C * np.float32(f),
+                           np.zeros((0, d), np.float32), np.zeros((0, d), np.float32), 1, 0)
+        g, _ = make_pair(w, pool_blocks=64, candidates_per_query=1024)
+        yd = dev(y * np.float32(f))
+        for _ in range(3):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            out = g.assign(yd)
+            b.record()
+            torch.cuda.synchronize()
+            t = a.elapsed_time(b)
+        got.append(out.cpu().numpy()); ms.append(t)
+        g.close()
+    print(f"[case] tiny {metric}: {ms} ms", flush=True)
+    assert np.array_equal(got[0], got[1])
+    assert ms[1] < 3 * ms[0]
