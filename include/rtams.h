@@ -283,7 +283,7 @@ int rtams_list_export_codes(rtams_index *ix, int32_t list, int64_t cap, int64_t 
  *   "scan_mfma"            flat lists: whether the scan's dot products run on the matrix cores,
  *                          one workgroup per work item with a tile of up to 32 queries in LDS.  0
  *                          never, 2 always, 1 (default) for requests of 64 queries or more with enough
- *                          queries to a list of enough vectors, by a rule on metric, storage, dimension
+ *                          arithmetic in it, by a rule on metric, storage, dimension, pairs (query, list)
  *                          and list lengths that was measured on both sides.
  *   "scan_min_choice"      shortest segment of a list the plan may make a work item of, as the power
  *                          e of 2 << e groups of 64 vectors (0..7); -1 (default) leaves it to the

@@ -408,25 +408,45 @@ constexpr int64_t kSingleGroups = 2048;
 constexpr int kMmMinBatch = 64;        // queries of a request from which the matrix-core scan pays
 
 // Whether a request of 64 queries or more scans on the matrix cores.  A tile is the queries of the request that probe one
-// list, and what speaks for the matrix cores is many queries to a list; what speaks against them is the set-up of a
-// workgroup per item, which short lists do not repay, and (inner products) that the vector unit needs one instruction
-// per coordinate where it needs two for squared distances.  Squared distances between floats go by the first of these
-// alone, also where that costs a tenth: behind the matrix cores the selection scores its finalists again in four short
-// sums, which come out closer to 64 bits (2 to 3 times, at d 256) than the one long sum of the vector unit's scan.
-// Requests measured on both, vector unit / matrix cores:
-//  squared distances, floats, 1,024 lists of 977 x 128: 4 pairs to a list 158 / 171 us, 8 205 / 195, 16 281 / 215;
-//    lists of 390 x 200: 16 pairs 127 / 134;  halves: 2 pairs 110 / 110, 4 133 / 126;  bytes: 1 pair 89 / 92, 2 110 / 103
-//  inner products, lists of 1,950 x 96: 1 pair 164 / 171, 2 204 / 200, 8 250 / 232;  lists of 390 x 96: 16 pairs 91 / 98;
-//    d 256 and 768 with 2 to 16 pairs: the vector unit by 1 to 17 %;  halves: 8 pairs 193 / 191, 16 236 / 220
-//  a hot list (16 times the average and more; a good share of any batch probes it): 16,384 lists of 1,220 x 256, 64 queries
-//    2.00 / 2.19 ms, 128 2.62 / 2.51, 256 3.49 / 2.90; of 366: 256 queries 1.07 / 1.13; of 122: 0.50 / 0.59;
-//    4,096 lists of 488 x 64: 64 queries 134 / 137 us, 256 228 / 203;  1,024 lists of 3,906 x 128: 64 371 / 333, 256 602 / 469
+// list, and what speaks for the matrix cores is arithmetic: many queries to a list, or (inner products) so wide vectors
+// that the vector unit's tiles of queries in LDS leave a compute unit few wavefronts (from d 512).  What speaks against
+// them is the set-up of a workgroup per item, which short lists do not repay.  Requests of 64 to 256 queries were measured
+// on both over d 32 to 1536, 64 to 16,384 lists of 100 to 10,000 vectors and a quarter of a pair to 256 pairs to a list,
+// even lists and hot ones (16 times the average and more; a good share of any batch probes them).  Vector unit / matrix
+// cores, us a request, the products of the request in brackets:
+//  inner products, floats, even lists.  d 96, 1,024 lists of 1,000: 142 / 141 (0.8 G), 179 / 149 (1.6 G); of 300: 92 / 112
+//    (0.5 G).  d 256, 64 lists of 10,000: 192 / 211 (0.7 G), 272 / 259 (5 G), 1,384 / 1,003 (42 G); 1,024 of 300: 159 / 204
+//    (1.3 G).  From d 512 by pairs: d 512, 64 lists of 1,000: 71 / 65 at 1 pair, 433 / 338 at 256; d 768, 8,192 lists of 400:
+//    551 / 551 at 1/4 pair, 880 / 1,060 at 1/2, 64 lists of 10,000: 295 / 295 at 1, 5,956 / 3,086 at 256; d 1536: 504 / 494,
+//    22,353 / 7,037.  Over all 863 the rule is 1.2 % from the better of the two on average, 1.46 times at worst (d 512,
+//    1,024 lists of 300, 16 pairs: 294 / 430)
+//  the same, hot lists.  d 256, 16,384 lists of 400: 775 / 852 (3.6 G with the hot one), 1,006 / 940 (8 G); 1,024 of 300:
+//    198 / 279 (1.6 G); of 4,000: 1,365 / 1,004 (22 G).  d 768, 4,096 lists of 100: 591 / 768 (1.6 G); of 500: 1,900 / 1,267
+//  inner products, halves and bytes.  d 128, 1,024 lists of 300: 98 / 103 (0.6 G), 4,096 of 500 with a hot one 154 / 142
+//    (0.3 G); halves, d 384, 64 of 10,000: 130 / 109 (0.3 G), 2,159 / 1,355 (63 G); from d 512 always: halves, d 768, 64
+//    lists of 300: 82 / 86, 355 / 231; bytes 96 / 109, 302 / 261
+//  squared distances, floats: by their pairs and the hot list alone, also where that costs a tenth: behind the matrix cores
+//    the selection scores its finalists again in four short sums, which come out closer to 64 bits (2 to 3 times, at d 256)
+//    than the one long sum of the vector unit's scan.  1,024 lists of 977 x 128: 4 pairs to a list 158 / 171, 8 205 / 195,
+//    16 281 / 215; lists of 390 x 200: 16 pairs 127 / 134; hot lists, 16,384 of 1,220 x 256: 64 queries 2,000 / 2,190, 128
+//    2,620 / 2,510, 256 3,490 / 2,900
+//  squared distances, halves and bytes.  1,024 lists of 1,000 x 128, halves: 2 pairs 110 / 110, 4 133 / 126; bytes: 1 pair
+//    89 / 92, 2 110 / 103; halves from d 512, where the margin of the norm form admits more finalists: d 768, 4 pairs
+//    535 / 626, 8 825 / 802.  Hot lists, halves, 1,024 of 1,000 x 128: 64 queries x 16 probes 124 / 120, 256 x 64 340 / 229;
+//    x 768: 550 / 691, 933 / 914 at 128 x 32, 1,933 / 1,298 at 256 x 64; 4,096 of 100 x 64: 88 / 99
 inline bool mm_scan_pays(const Dev &D, int64_t nq, int64_t nprobe, int64_t avg_len, int64_t max_len) {
-  const int64_t pairs = nq * nprobe, nlist = D.nlist;
-  if (D.metric == 0 && D.storage == 0) return pairs >= nlist || max_len >= 16 * avg_len;
-  if (max_len >= 16 * avg_len && avg_len >= 448 && (nq >= 128 || pairs >= nlist)) return true;
-  if (D.metric == 0) return avg_len >= 512 && pairs >= (D.storage == 1 ? 4 : 2) * nlist;
-  return D.d <= 128 && avg_len >= 1024 && pairs >= (D.storage == 0 ? 2 : 16) * nlist;
+  const int64_t pairs = nq * nprobe, nlist = D.nlist, d = D.d;
+  const bool hot = max_len >= 16 * avg_len;
+  if (D.metric == 0) {
+    if (D.storage == 0) return pairs >= nlist || hot;
+    if (hot && avg_len >= 448 && (nq >= 128 || pairs >= nlist)) return true;
+    return avg_len >= 512 && pairs >= (D.storage == 2 ? 2 : d >= 512 ? 8 : 4) * nlist;
+  }
+  // multiply-adds the request can expect, a tenth of its queries meeting the longest list
+  const double products = (double)(nq * d) * (double)(nprobe * avg_len + max_len / 10);
+  if (D.storage != 0) return d >= 512 || ((avg_len >= 512 || (hot && max_len >= 16384)) && products >= 0.3e9);
+  if (hot) return products >= (d >= 512 ? 4e9 : 2e9);
+  return d >= 512 ? pairs >= nlist : products >= (d <= 96 ? 1e9 : 8e9);
 }
 
 inline ScanShape scan_shape(const Dev &D, int item_budget) {
