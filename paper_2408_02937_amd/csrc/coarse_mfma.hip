@@ -271,8 +271,7 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void k_coarse_mfma(Dev D, int64_t 
   __shared__ float s_min[kTileM][2];
   __shared__ float s_cn[kTileN];  // bias of the tile's centroids, read after the last barrier of the k loop
   __shared__ uint32_t s_cnt[kTileM];
-  __shared__ int32_t s_col[kTileM][kTileCands];
-  __shared__ float s_val[kTileM][kTileCands];
+  __shared__ __attribute__((aligned(16))) uint16_t s_kept[kTileM][kTileCands];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int wv = wave & 1, wc = wave >> 1;  // wavefront's place in the 2 (vectors) x 2 (centroids) arrangement
 
@@ -435,7 +434,8 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void k_coarse_mfma(Dev D, int64_t 
     const int row = wv * 64 + b * 32 + (lane & 31);
     // the smallest of the tile plus the band of the vector, a little wider than the refinement's, so that
     // what the refinement asks for is certainly among what is kept here
-    const float limit = fminf(s_min[row][0], s_min[row][1]) + mt[b].band * 1.01f;
+    const float low = fminf(s_min[row][0], s_min[row][1]), width = mt[b].band * 1.01f;
+    const float limit = low + width, per = width < __builtin_inff() ? 255.f / width : 0.f;
 #pragma unroll
     for (int a = 0; a < CA; ++a)
 #pragma unroll
@@ -443,21 +443,22 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void k_coarse_mfma(Dev D, int64_t 
         if (acc[a][b][r] <= limit && acc[a][b][r] < __builtin_inff()) {
           const uint32_t slot = atomicAdd(&s_cnt[row], 1u);
           if (slot < (uint32_t)kTileCands) {
-            s_col[row][slot] = centroid_of(a, r);
-            s_val[row][slot] = acc[a][b][r];
+            // how far above the smallest score, in steps of a 255th of the width and rounded down, over the column
+            const uint32_t above = (uint32_t)fminf((acc[a][b][r] - low) * per, 255.f);
+            s_kept[row][slot] = (uint16_t)(above << 8 | (uint32_t)(centroid_of(a, r) - col0));
           }
         }
   }
   __syncthreads();
   if (tid < kTileM && row0 + tid < n) {
     const size_t at = (size_t)(row0 + tid) * tc.tiles + col_tile;
+    const uint32_t cnt = s_cnt[tid];
+    const uint2 *kept = reinterpret_cast<const uint2 *>(s_kept[tid]);
+    uint2 *out = reinterpret_cast<uint2 *>(tc.kept + at * kTileCands);
     tc.tmin[at] = fminf(s_min[tid][0], s_min[tid][1]);
-    tc.cnt[at] = s_cnt[tid];
-#pragma unroll
-    for (int j = 0; j < kTileCands; ++j) {
-      tc.col[at * kTileCands + j] = s_col[tid][j];
-      tc.val[at * kTileCands + j] = s_val[tid][j];
-    }
+    tc.cnt[at] = cnt;
+    out[0] = kept[0];
+    if (cnt > 4u) out[1] = kept[1];  // (few tiles have so many, and nobody reads what is not counted)
   }
 }
 
@@ -503,14 +504,35 @@ __device__ inline double exact_score(const Dev &D, const float *__restrict__ y, 
 #pragma unroll
     for (int u = 0; u < 8; ++u) chain(a[u], b[u]);
   }
-  for (; j < D.d4; ++j) chain(y4[j], row4[j]);
+  if (j < D.d4) {  // uniform.  What is left, all of it asked for at once too
+    float4 a[8], b[8];
+    const int last = D.d4 - 1 - j;
+#pragma unroll
+    for (int u = 0; u < 7; ++u) { a[u] = y4[j + (u < last ? u : last)]; b[u] = row4[j + (u < last ? u : last)]; }
+#pragma unroll
+    for (int u = 0; u < 7; ++u)
+      if (u <= last) chain(a[u], b[u]);  // uniform
+  }
   return acc;
+}
+
+// What a tile kept of a column (16 bits: steps above the tile's smallest score, column), read again: the column's
+// centroid, or -1 if its score is certainly beyond the limit.  The steps were rounded down, and are taken for a hundredth
+// shorter here than they were there.
+__device__ inline float kept_step(float band) { return band < __builtin_inff() ? band / 255.f : 0.f; }
+__device__ inline int kept_column(const TileCands &tc, size_t base, int t, uint32_t j, float low, float step, float limit) {
+  const uint32_t k = tc.kept[(base + t) * kTileCands + j];
+  return low + (float)(k >> 8) * step <= limit ? t * tc.width + (int)(k & 255u) : -1;
 }
 
 constexpr int kRefineThreads = 256;
 constexpr int kRefineRows = 64;       // rows of a workgroup at most
-constexpr int kRefineRowCands = 16;   // candidates of a row up to which they go to the workgroup's list
-constexpr int kRefineList = kRefineRows * kRefineRowCands;
+// Candidates of a row up to which they go to the workgroup's list, and what the list holds: rows that find it full are
+// scored by a wavefront each.  Data in clusters much tighter than the whole, with tens of centroids to a cluster, has
+// tens of candidates to a row.  Where a workgroup has few rows the list has room for all columns of a tile that could not
+// keep its own, too: a wavefront takes such a tile in four turns, one behind the other.
+constexpr int kRefineRowCands = 64, kRefineFewRows = 8, kRefineRowCandsFew = 1024;
+constexpr int kRefineList = 2048;
 
 // a score as a key: smaller is better, -0 equal to +0
 __device__ inline unsigned long long refine_key(bool l2, double s) {
@@ -526,15 +548,16 @@ __global__ __launch_bounds__(kRefineThreads) void k_assign_refine(Dev D, int64_t
   __shared__ unsigned long long s_key[kRefineRows];  // of the rows whose candidates are listed: their best key ...
   __shared__ int s_col[kRefineRows];                 // ... and the answer of every row
   __shared__ float s_limit[kRefineRows];
-  __shared__ int s_hard[kRefineRows];                // rows with more candidates than are listed
+  __shared__ int s_hard[kRefineRows];                // rows with more candidates than are listed, or no room in the list
+  __shared__ unsigned long long s_lkey[kRefineList];
   __shared__ int s_lcol[kRefineList];
   __shared__ uint8_t s_lrow[kRefineList];
-  __shared__ uint32_t s_n, s_hards;
+  __shared__ uint32_t s_n, s_hards, s_full;  // s_full: where the first row began that did not fit the list
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int64_t i0 = (int64_t)blockIdx.x * rows;
   const bool l2 = D.metric == 0;
   constexpr int kNone = 0x7fffffff;
-  if (tid == 0) { s_n = 0; s_hards = 0; }
+  if (tid == 0) { s_n = 0; s_hards = 0; s_full = (uint32_t)kRefineList; }
   if (tid < rows) { s_key[tid] = ~0ull; s_col[tid] = kNone; }
   __syncthreads();
   const int sub = tid & (lpr - 1);
@@ -548,44 +571,52 @@ __global__ __launch_bounds__(kRefineThreads) void k_assign_refine(Dev D, int64_t
     for (int t = sub; t < tc.tiles; t += lpr) m = fminf(m, tmin[t]);
     const float band = meta[on ? i : n - 1].band;
     for (int o = lpr / 2; o > 0; o >>= 1) m = fminf(m, __shfl_xor(m, o));
-    const float limit = m + band;
-    // how many candidates, and whether every tile near the minimum kept all of its own
-    uint32_t mine = 0, crowded = 0;
+    const float limit = m + band, step = kept_step(band);
+    // how many candidates: what a tile near the minimum kept, or all of its columns where it could not keep all its own
+    uint32_t mine = 0;
     int first = 0;  // one of the lane's candidates
     for (int t = sub; t < tc.tiles; t += lpr) {
       if (!(tmin[t] <= limit)) continue;
       const uint32_t cnt = tc.cnt[base + t];
-      if (cnt > (uint32_t)kTileCands) crowded = 1u << 16;
-      for (uint32_t j = 0; j < min(cnt, (uint32_t)kTileCands); ++j)
-        if (tc.val[(base + t) * kTileCands + j] <= limit) { ++mine; first = tc.col[(base + t) * kTileCands + j]; }
+      if (cnt > (uint32_t)kTileCands) mine += (uint32_t)min(tc.width, D.nlist - t * tc.width);
+      else for (uint32_t j = 0; j < cnt; ++j) {
+        const int c = kept_column(tc, base, t, j, tmin[t], step, limit);
+        if (c >= 0) { ++mine; first = c; }
+      }
     }
-    uint32_t upto = min(mine, 255u) | crowded;  // running sum over the row's lanes: candidates below, crowded tiles above
+    uint32_t upto = mine;  // running sum over the row's lanes
     for (int o = 1; o < lpr; o <<= 1) {
       const uint32_t x = __shfl_up(upto, o);
       if (sub >= o) upto += x;
     }
     const uint32_t total = __shfl(upto, (lane & ~(lpr - 1)) + lpr - 1);
     uint32_t to = 0;
-    if (on && total > 1u && total <= (uint32_t)kRefineRowCands && sub == 0) to = atomicAdd(&s_n, total);
+    const bool listed = on && total > 1u && total <= (uint32_t)(rows <= kRefineFewRows ? kRefineRowCandsFew : kRefineRowCands);
+    if (listed && sub == 0) to = atomicAdd(&s_n, total);
     to = __shfl(to, lane & ~(lpr - 1));
     if (!on) continue;
     if (total == 1u) {  // nobody to compare it with
       if (mine) s_col[r] = first;
-    } else if (total > (uint32_t)kRefineRowCands) {
+    } else if (total > 1u && (!listed || to + total > (uint32_t)kRefineList)) {
       if (sub == 0) {
         s_limit[r] = limit;
         s_hard[atomicAdd(&s_hards, 1u)] = r;
+        if (listed) atomicMin(&s_full, to);  // (whoever reserved behind it did not fit either)
       }
     } else if (mine) {  // to the list
-      to += (upto & 0xffffu) - mine;
+      to += upto - mine;
       for (int t = sub; t < tc.tiles; t += lpr) {
         if (!(tmin[t] <= limit)) continue;
         const uint32_t cnt = tc.cnt[base + t];
-        for (uint32_t j = 0; j < cnt; ++j)
-          if (tc.val[(base + t) * kTileCands + j] <= limit) {
-            s_lcol[to] = tc.col[(base + t) * kTileCands + j];
+        const bool all = cnt > (uint32_t)kTileCands;
+        const uint32_t count = all ? (uint32_t)min(tc.width, D.nlist - t * tc.width) : cnt;
+        for (uint32_t j = 0; j < count; ++j) {
+          const int c = all ? t * tc.width + (int)j : kept_column(tc, base, t, j, tmin[t], step, limit);
+          if (c >= 0) {
+            s_lcol[to] = c;
             s_lrow[to++] = (uint8_t)r;
           }
+        }
       }
     }
   }
@@ -594,7 +625,7 @@ __global__ __launch_bounds__(kRefineThreads) void k_assign_refine(Dev D, int64_t
   for (uint32_t h = (uint32_t)wave; h < s_hards; h += kRefineThreads / kWave) {  // uniform over the wavefront
     const int r = s_hard[h];
     const size_t base = (size_t)(i0 + r) * tc.tiles;
-    const float limit = s_limit[r];
+    const float limit = s_limit[r], step = kept_step(meta[i0 + r].band);
     const float *y = Y + (i0 + r) * D.d;
     double best_s = l2 ? __builtin_inf() : -__builtin_inf();
     int best_c = kNone;
@@ -609,8 +640,10 @@ __global__ __launch_bounds__(kRefineThreads) void k_assign_refine(Dev D, int64_t
       const bool near = t < tc.tiles && tc.tmin[base + t] <= limit;
       const uint32_t cnt = near ? tc.cnt[base + t] : 0u;
       if (near && cnt <= (uint32_t)kTileCands)  // the tile kept all its columns within the band: one lane takes them
-        for (uint32_t j = 0; j < cnt; ++j)
-          if (tc.val[(base + t) * kTileCands + j] <= limit) offer(tc.col[(base + t) * kTileCands + j]);
+        for (uint32_t j = 0; j < cnt; ++j) {
+          const int c = kept_column(tc, base, t, j, tc.tmin[base + t], step, limit);
+          if (c >= 0) offer(c);
+        }
       // a tile with more columns in the band than it could keep: all its columns, shared out over the lanes
       unsigned long long full = __ballot(near && cnt > (uint32_t)kTileCands);
       while (full) {  // uniform
@@ -630,27 +663,19 @@ __global__ __launch_bounds__(kRefineThreads) void k_assign_refine(Dev D, int64_t
   }
   // the listed candidates, a thread to each (a list longer than the workgroup goes round: the scores of the
   // turns are compared through LDS, keys first, then the lowest index among the equal ones)
-  const int listed = (int)s_n;
-  constexpr int kTurns = kRefineList / kRefineThreads;
-  unsigned long long key[kTurns];
-#pragma unroll
-  for (int u = 0; u < kTurns; ++u) {
-    const int e = tid + u * kRefineThreads;
-    key[u] = ~0ull;
-    if (e < listed) {
-      const double s = exact_score(D, Y + (i0 + s_lrow[e]) * D.d, s_lcol[e]);
-      if (s == s) {  // a score that does not compare is nobody's best
-        key[u] = refine_key(l2, s);
-        atomicMin(&s_key[s_lrow[e]], key[u]);
-      }
+  const int entries = (int)min(s_n, s_full);
+  for (int e = tid; e < entries; e += kRefineThreads) {
+    const double s = exact_score(D, Y + (i0 + s_lrow[e]) * D.d, s_lcol[e]);
+    unsigned long long key = ~0ull;
+    if (s == s) {  // a score that does not compare is nobody's best
+      key = refine_key(l2, s);
+      atomicMin(&s_key[s_lrow[e]], key);
     }
+    s_lkey[e] = key;
   }
   __syncthreads();
-#pragma unroll
-  for (int u = 0; u < kTurns; ++u) {
-    const int e = tid + u * kRefineThreads;
-    if (e < listed && key[u] != ~0ull && key[u] == s_key[s_lrow[e]]) atomicMin(&s_col[s_lrow[e]], s_lcol[e]);
-  }
+  for (int e = tid; e < entries; e += kRefineThreads)
+    if (s_lkey[e] != ~0ull && s_lkey[e] == s_key[s_lrow[e]]) atomicMin(&s_col[s_lrow[e]], s_lcol[e]);
   __syncthreads();
   if (tid < rows && i0 + tid < n) {
     int c = s_col[tid];

@@ -39,7 +39,7 @@ inline size_t up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Byte offsets of everything in front of the blocks.
 struct Layout {
-  size_t ctrl, hook, centroids, centroids_t, cmean, cbias, chalf, codebooks, codebooks_t, tc_min, tc_cnt, tc_col, tc_val, ins_yhalf, ins_ymeta, tile_rows, reserved_len, visible_len, online, nblk, exceed, seg_dir;
+  size_t ctrl, hook, centroids, centroids_t, cmean, cbias, chalf, codebooks, codebooks_t, tc_min, tc_cnt, tc_kept, ins_yhalf, ins_ymeta, tile_rows, reserved_len, visible_len, online, nblk, exceed, seg_dir;
   size_t ins_assign, ins_did, ins_pscore, ins_pidx, part_cap;
   size_t rearr_head, rearr_arrays;
   size_t fixed_end;          // end of the part that does not depend on the block count
@@ -111,9 +111,9 @@ void lay_out(const rtams_config *c, int64_t blocks, size_t pool_bytes, Layout *L
   L->ins_did = take((size_t)c->max_add_batch * 4);
   L->ins_pscore = take(L->part_cap * 8);
   L->ins_pidx = take(L->part_cap * 4);
-  {  // one insertion sub-round: tile digests (40 bytes per row and tile) and halves, 64 MiB of them, at least 64 rows
+  {  // one insertion sub-round: tile digests (24 bytes per row and tile) and halves, 64 MiB of them, at least 64 rows
     const size_t tiles = (nl + 255) / 256;
-    size_t rows = ((size_t)64 << 20) / (tiles * 40 + (size_t)dgroups * 16 + sizeof(RowMeta));
+    size_t rows = ((size_t)64 << 20) / (tiles * 24 + (size_t)dgroups * 16 + sizeof(RowMeta));
     rows = rows / 128 * 128;  // whole tiles of the contraction
     if (rows > (size_t)c->max_add_batch) rows = (size_t)c->max_add_batch;
     if (rows < 64) rows = 64;
@@ -122,8 +122,7 @@ void lay_out(const rtams_config *c, int64_t blocks, size_t pool_bytes, Layout *L
     L->ins_ymeta = take(rows * sizeof(RowMeta));
     L->tc_min = take(rows * tiles * 4);
     L->tc_cnt = take(rows * tiles * 4);
-    L->tc_col = take(rows * tiles * kTileCands * 4);
-    L->tc_val = take(rows * tiles * kTileCands * 4);
+    L->tc_kept = take(rows * tiles * kTileCands * 2);
   }
   L->rearr_head = take(sizeof(RearrangeHead));
   L->rearr_arrays = take((size_t)kRearrangeCap * 4 * 7);
@@ -512,8 +511,7 @@ int rtams_create(const rtams_config *cfg, rtams_index **out) {
   ix->ins.tiles.rows = (int64_t)L.tile_rows;
   ix->ins.tiles.tmin = reinterpret_cast<float *>(base + L.tc_min);
   ix->ins.tiles.cnt = reinterpret_cast<uint32_t *>(base + L.tc_cnt);
-  ix->ins.tiles.col = reinterpret_cast<int32_t *>(base + L.tc_col);
-  ix->ins.tiles.val = reinterpret_cast<float *>(base + L.tc_val);
+  ix->ins.tiles.kept = reinterpret_cast<uint16_t *>(base + L.tc_kept);
   ix->ins.tile_rows = (int64_t)L.tile_rows;
   ix->ins.yhalf = reinterpret_cast<u32x4 *>(base + L.ins_yhalf);
   ix->ins.ymeta = reinterpret_cast<RowMeta *>(base + L.ins_ymeta);
