@@ -140,11 +140,14 @@ void launch_coarse_argmin(const Dev &D, int64_t n, const float *Y, int splits, d
 // the refinement (measured crossover on MI355X, d = 128 and 768: about 1 M (query,
 // centroid) pairs for a search).
 inline bool mfma_pays_for_search(int64_t nq, int64_t nlist) { return nq >= 32 && nq * nlist >= (int64_t)1 << 20; }
-// An assignment pays from 2^20 pairs, or from 2^26 coordinates of them (measured per insertion batch, exact against
-// filter: 64 x 8,192 x 768 69 and 40 us, 32 x 16,384 x 256 48 and 31, 64 x 8,192 x 128, 64 x 2,048 x 768 and 512 x
-// 1,024 x 128 the same within 2 us, 64 x 2,048 x 128 20 and 30).
+// An assignment pays from 2^19 pairs, from 2^18 with 1,024 vectors or more, and from 2^26 coordinates of them.  Below that
+// the filter is a few workgroups, each a chain of d / 32 steps, in front of a refinement and a tail that no longer fuse.
+// Insertion batches back to back, vectors of which several centroids are candidates, exact / filter in us: d 768, 256 x
+// 1,024 47 / 60, x 2,048 65 / 61, 64 x 4,096 44 / 55, x 8,192 66 / 57, 1,024 x 256 62 / 66, x 420 93 / 67;  d 256, 256 x
+// 1,024 32 / 35, x 2,048 40 / 36, 2,048 x 128 53 / 41;  d 128, 128 x 2,048 24 / 31, x 4,096 30 / 32, x 8,192 39 / 33, 512 x
+// 1,024 34 / 36;  d 32, 128 x 8,192 26 / 30, 256 x 8,192 40 / 32;  d 1536, 256 x 1,024 72 / 90, x 2,048 98 / 92.
 inline bool mfma_pays_for_assign(int64_t m, int64_t nlist, int64_t d) {
-  return m >= 32 && (m * nlist >= (int64_t)1 << 20 || m * nlist * d >= (int64_t)1 << 26);
+  return m >= 32 && m * nlist >= (int64_t)1 << (m >= 1024 ? 18 : 19) && m * nlist * d >= (int64_t)1 << 26;
 }
 // 16-byte units the halves of `rows` rows take: whole blocks of 16 rows
 __host__ __device__ inline size_t half_units(int64_t rows, int dgroups) { return (size_t)((rows + 15) / 16 * 16) * dgroups; }
