@@ -108,3 +108,32 @@ def test_a_recorded_search_fits_lists_that_grow_between_its_replays():
             assert torch.equal(d, rd) and torch.equal(i, ri)
     del graph
     g.close()
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16", "u8"])
+def test_one_group_at_a_time_through_a_list_of_thousands(storage):
+    """Lists short enough on average to be walked a group at a time, and one of 31,000 groups among them: its segments
+    get longer until they fit, and its queries' neighbours are those of 64-bit arithmetic."""
+    d, hot = 16, 2_000_000
+    lengths = [20] * 11_999 + [hot]
+    rng = np.random.default_rng(3)
+    C = rng.uniform(0, 255, (len(lengths), d)).astype(np.float32)
+    C[-1] = 128.0
+    C[:-1][np.abs(C[:-1] - 128.0).max(axis=1) < 60] = 255.0  # nobody else near the long list's centroid
+    cd = torch.from_numpy(C).cuda()
+    at = torch.from_numpy(rng.permutation(np.repeat(np.arange(len(lengths)), lengths))).cuda()
+    y = cd[at] + torch.randn(len(at), d, device="cuda:0", generator=torch.Generator("cuda:0").manual_seed(3))
+    y.round_().clamp_(0.0, 255.0)  # whole numbers: the same in every kind of list, sums exact
+    g = rtams.Index(d, len(lengths), "l2", 64, pool_blocks=len(at) // 64 + 2 * len(lengths) + 8, n_resources=1,
+                    max_batch=8, max_k=100, max_nprobe=8, candidates_per_query=hot + 100_000, storage=storage)
+    g.set_centroids(cd)
+    g.add(y)
+    mine = torch.nonzero(g.assign(y) == len(lengths) - 1).flatten()
+    assert len(mine) > 0.9 * hot
+    q = cd[-1:] + torch.tensor([[0.0], [1.0], [2.0], [-3.0]], device="cuda:0")
+    for nq, nprobe in ((1, 1), (4, 8), (2, 3)):
+        dist, _ = g.search(q[:nq].contiguous(), 100, nprobe)
+        want = torch.stack([torch.sort(((y[mine] - x) ** 2).double().sum(1))[0][:100] for x in q[:nq]])
+        assert g.poll_error() == 0
+        assert torch.equal(dist.double(), want), f"{storage} {nq} x {nprobe}"
+    g.close()
