@@ -286,8 +286,9 @@ int rtams_list_export_codes(rtams_index *ix, int32_t list, int64_t cap, int64_t 
  *                          arithmetic in it, by a rule on metric, storage, dimension, pairs (query, list)
  *                          and list lengths that was measured on both sides.
  *   "scan_min_choice"      shortest segment of a list the plan may make a work item of, as the power
- *                          e of 2 << e groups of 64 vectors (0..7); -1 (default) leaves it to the
- *                          scan kernel (2 groups on the vector unit, 8 on the matrix cores).
+ *                          e of 2 << e groups of 64 vectors (0..7), where the scan runs on the matrix
+ *                          cores; -1 (default) takes 8 groups.  The vector unit's segments start at 2
+ *                          groups, at 1 in small requests over lists of at most four.
  *   "scan_byte_weight"     what reading a group of 64 vectors costs, in queries' worth of arithmetic,
  *                          when the work is split over the chip's 8 dies; 0 (default) takes 12 for
  *                          L2 and 24 for inner products.

@@ -7,7 +7,8 @@
 // "open" and "fill" with two barriers, which only works while a batch cannot
 // need two new blocks for one list.  Here the phases of a large batch are
 // stream-ordered kernels, so any batch size and any block size work across the
-// whole chip, and a batch of up to kTailVecs vectors goes through one workgroup
+// whole chip, and a batch of up to kTailVecs vectors whose positions the exact
+// coarse kernel leaves open, or which are few enough to move, goes through one workgroup
 // with barriers, as the paper has it, however many blocks it needs; the
 // rule that the block of position did lives at chain index did / T_m, offset
 // did % T_m, and that exactly one party opens each new block, is the paper's.

@@ -264,7 +264,7 @@ struct rtams_index {
   unsigned long long ovf_chunk_cap = 0;
   std::atomic<int64_t> ordered_add{0};  // positions inside a list in the order of the batch instead of arrival order
   std::atomic<int64_t> use_mfma{1};  // matrix-core filter in front of the exact coarse arithmetic
-  std::atomic<int64_t> scan_mfma{1}; // flat float lists: the scan's dot products on the matrix cores
+  std::atomic<int64_t> scan_mfma{1}; // flat lists: the scan's dot products on the matrix cores
   std::atomic<int64_t> scan_byte_weight{0};
   std::atomic<int64_t> scan_min_choice{-1};
   // Scans of LONG requests run one after the other, whatever streams they are on: such a scan fills the
