@@ -775,7 +775,8 @@ static int search_on(rtams_index *ix, int r, int64_t nq, const float *d_queries,
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   Dev D = ix->dev;
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  const bool recorded = hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusActive;
+  if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();  // (not the launches' own error)
+  const bool recorded = capture == hipStreamCaptureStatusActive;
   {  // flat lists: which unit scans (0 the vector unit, 1 by the rule, 2 the matrix cores)
     const int64_t mode = ix->scan_mfma.load(std::memory_order_relaxed);
     const int64_t avg_len = ix->ntotal_host / ix->cfg.nlist + 1;

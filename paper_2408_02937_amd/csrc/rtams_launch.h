@@ -135,19 +135,22 @@ void launch_coarse_argmin(const Dev &D, int64_t n, const float *Y, int splits, d
                           int32_t *pidx, hipStream_t s);
 
 // coarse_mfma.hip ------------------------------------------------------------
+constexpr int kTailVecs = 1024;  // vectors of an insertion batch that one workgroup sees to behind the coarse scores (insert.hip)
 // When the matrix-core filter runs in front of the exact coarse arithmetic: the
 // batch has to be a dense contraction large enough to repay the extra kernel and
 // the refinement (measured crossover on MI355X, d = 128 and 768: about 1 M (query,
 // centroid) pairs for a search).
 inline bool mfma_pays_for_search(int64_t nq, int64_t nlist) { return nq >= 32 && nq * nlist >= (int64_t)1 << 20; }
-// An assignment pays from 2^19 pairs, from 2^18 with 1,024 vectors or more, and from 2^26 coordinates of them.  Below that
-// the filter is a few workgroups, each a chain of d / 32 steps, in front of a refinement and a tail that no longer fuse.
+// An assignment pays from 2^19 pairs and 2^26 coordinates of them.  Below that the filter is a few workgroups, each a
+// chain of d / 32 steps, in front of a refinement and a tail that no longer fuse.  From 1,024 vectors it pays from 2^18
+// pairs, and above that number, where the tail does not fuse either way, from 2^25 coordinates.
 // Insertion batches back to back, vectors of which several centroids are candidates, exact / filter in us: d 768, 256 x
 // 1,024 47 / 60, x 2,048 65 / 61, 64 x 4,096 44 / 55, x 8,192 66 / 57, 1,024 x 256 62 / 66, x 420 93 / 67;  d 256, 256 x
 // 1,024 32 / 35, x 2,048 40 / 36, 2,048 x 128 53 / 41;  d 128, 128 x 2,048 24 / 31, x 4,096 30 / 32, x 8,192 39 / 33, 512 x
-// 1,024 34 / 36;  d 32, 128 x 8,192 26 / 30, 256 x 8,192 40 / 32;  d 1536, 256 x 1,024 72 / 90, x 2,048 98 / 92.
+// 1,024 34 / 36;  d 32, 128 x 8,192 26 / 30, 256 x 8,192 40 / 32, 1,024 x 1,024 30 / 37, 3,700 x 160 37 / 40, x 300 47 / 38,
+// 1,100 x 1,024 36 / 36;  d 1536, 256 x 1,024 72 / 90, x 2,048 98 / 92.
 inline bool mfma_pays_for_assign(int64_t m, int64_t nlist, int64_t d) {
-  return m >= 32 && m * nlist >= (int64_t)1 << (m >= 1024 ? 18 : 19) && m * nlist * d >= (int64_t)1 << 26;
+  return m >= 32 && m * nlist >= (int64_t)1 << (m >= 1024 ? 18 : 19) && m * nlist * d >= (int64_t)1 << (m > kTailVecs ? 25 : 26);
 }
 // 16-byte units the halves of `rows` rows take: whole blocks of 16 rows
 __host__ __device__ inline size_t half_units(int64_t rows, int dgroups) { return (size_t)((rows + 15) / 16 * 16) * dgroups; }
@@ -177,7 +180,6 @@ void launch_fill(const Dev &D, int64_t n, const float *Y, const int64_t *ids, in
 void launch_publish(const Dev &D, uint32_t call_seq, uint32_t total, hipStream_t s);
 // A batch of at most kTailVecs vectors: reservation (splits > 0: from the partial minima; 0: done), opening and,
 // where tail_fills() says so, filling and publication; otherwise a fill and launch_publish_batch follow.
-constexpr int kTailVecs = 1024;
 bool tail_fills(const Dev &D, int64_t n);
 void launch_insert_tail(const Dev &D, int64_t n, int splits, const float *Y, const int64_t *ids, int64_t id_base,
                         const InsertScratch &S, uint32_t call_seq, uint32_t total, hipStream_t s);

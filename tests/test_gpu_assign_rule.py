@@ -9,9 +9,9 @@ from paper_2408_02937_amd import rtams
 pytestmark = pytest.mark.gpu
 
 
-# measured, exact / filter: 40 / 55, 47 / 60, 35 / 48, 65 / 61, 144 / 67 us a batch
+# measured, exact / filter: 40 / 55, 47 / 60, 35 / 48, 65 / 61, 144 / 67, 47 / 38, 30 / 37 us a batch
 @pytest.mark.parametrize("m,nlist,d", [(256, 420, 688), (256, 1024, 768), (256, 420, 512), (256, 2048, 768),
-                                       (512, 4096, 768)])
+                                       (512, 4096, 768), (3725, 306, 32), (1024, 1024, 32)])
 def test_a_batch_takes_the_faster_path(m, nlist, d):
     print(f"[case] assign rule {m} x {nlist} x {d}", flush=True)
     gen = torch.Generator("cuda:0").manual_seed(m + d)
