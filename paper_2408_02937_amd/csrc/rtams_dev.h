@@ -48,7 +48,7 @@ struct Ctrl {
   int32_t error;             // sticky rtams_status raised by a kernel
   uint32_t exceed_lists;     // lists for which Exceed() holds
   unsigned long long ntotal; // vectors visible
-  uint32_t max_len;          // longest visible list
+  uint32_t max_len;          // longest list, taken where a batch's blocks are opened (a batch dropped for lack of blocks counts)
   int32_t search_error;      // rtams_status raised by a kernel of a search (scratch too small): inserts do not look at it
   CentroidStats cen;
   uint32_t pad3[20];
