@@ -726,6 +726,9 @@ int rtams_add(rtams_index *ix, int64_t n, const float *d_vecs, const int64_t *d_
     // only its last round completes the call: the rounds before it report under the call before
     const uint32_t report = o + round >= n ? seq : seq - 1u;
     const uint32_t total = (uint32_t)(id_base + m);
+    // Also the line between opening and publishing a vector to a thread and a list to a thread: above it the two differ by
+    // less than a tenth, lists in front except for few vectors in very many lists (us a batch by list / by vector: 1,025 into
+    // 1,024 lists x 32 30.3 / 31.7, into 4,096 32.6 / 33.6, into 16,384 45.4 / 43.5; 65,536 into 16,384 670 / 695).
     const bool small = m <= kTailVecs;
     int splits = 0;
     if (ordered) {
