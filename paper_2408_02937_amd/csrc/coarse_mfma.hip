@@ -48,18 +48,21 @@ namespace rtams {
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) u32x4 LdsUnit;
 
 constexpr int kMfmaThreads = 256;  // 4 wavefronts: 2 (vectors) x 2 (centroids)
 constexpr int kTileM = 128;        // vectors of a tile: 64 to a wavefront
 constexpr int kTileK = 32;         // coordinates per step
+constexpr int kBuffers = 3;        // steps whose operands have room in LDS
 constexpr int kXcds = 8;  // workgroups go to the chip's 8 dies (each with its own L2) in turn
 
 // Operands in memory lie as the tiles are read: blocks of 16 rows x 32 coordinates, 1 KiB each, the steps of a
 // block of rows one after the other.  Inside a block row r has four 16-byte places, and group g of 8 coordinates
-// is at place g ^ ((r >> 1) & 3): the 8 rows that neighbouring lanes read from LDS then cover all 32 banks once,
-// with no padding, and a copy of a block to LDS is 1 KiB in order.
+// is at place g ^ place_swap(r): the 8 rows that neighbouring lanes read from LDS then cover 32 banks once, and the
+// 16 rows of a quarter of a wavefront all 64, with no padding, and a copy of a block to LDS is 1 KiB in order.
+__device__ inline int place_swap(int row) { return ((row >> 1) & 2) | (((row >> 1) ^ (row >> 3)) & 1); }
 __device__ inline size_t operand_at(int64_t row, int g, int steps) {
-  return ((size_t)(row >> 4) * steps + (g >> 2)) * 64 + (size_t)(row & 15) * 4 + ((g & 3) ^ (((int)row >> 1) & 3));
+  return ((size_t)(row >> 4) * steps + (g >> 2)) * 64 + (size_t)(row & 15) * 4 + ((g & 3) ^ place_swap((int)row & 15));
 }
 
 __device__ inline uint32_t pack_halves_flushed(float a, float b) {  // nearest even; subnormal halves become zero
@@ -252,12 +255,16 @@ __global__ __launch_bounds__(256) void k_half_rows(Dev D, int64_t n, const float
 }
 
 // ---- approximate scores of a tile of 128 vectors x 64 CA centroids; a wavefront has 64 vectors x 32 CA centroids.
-// With CA = 4 a step of 32 coordinates is 16 matrix instructions of 32 clocks to a wavefront between two barriers,
-// and the 12 operands they take are 96 of the 128 bytes a clock that LDS returns: with CA = 2, as with the 64 x 64
-// scores to a wavefront this kernel used to have, LDS would take longer than the matrix cores.  CA = 2 is for
-// batches whose wide tiles would leave compute units without a workgroup.
-// Two buffers in LDS: while one is multiplied the next step's operands are on their way to registers, and go to the
-// other buffer behind the multiplications; one barrier to a step.
+// With CA = 4 a step of 32 coordinates is 16 matrix instructions of 32 clocks to a wavefront between two barriers.
+// CA = 2 is for batches whose wide tiles would leave compute units without a workgroup.
+// Three buffers in LDS: a step's operands are copied there straight from memory (no registers in between) two steps
+// ahead of the multiplications, and the one barrier of a step waits for the copies of that step alone, the next
+// step's stay on their way.  Two workgroups share a compute unit, and one's waits are the other's multiplications.
+// What bounds it: inside the steps the matrix cores are busy 85 % of the clocks, and the chip lowers its clock to 1.6 to
+// 1.7 GHz under them; the reduction of a tile (6 us of the 25 that a tile of 768 dimensions is on a compute unit)
+// overlaps with the steps of the other workgroup.  28,928 x 8,192 x 768 take 370 us, 980 TFLOP/s; 424 us with
+// two buffers filled through registers a step ahead and a branch for every score in the reduction, 30 % of the LDS
+// clocks bank conflicts (the places of a row's groups covered 32 banks, not 64).
 template <int CA, bool MATRIX>
 __global__ __launch_bounds__(kMfmaThreads, 2) void k_coarse_mfma(Dev D, int64_t n, const u32x4 *__restrict__ yhalf,
                                                               const RowMeta *__restrict__ meta,
@@ -265,14 +272,14 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void k_coarse_mfma(Dev D, int64_t 
                                                               unsigned long long *cursor_to_clear,
                                                               uint32_t *__restrict__ zero, int zero_n) {
   constexpr int kTileN = 64 * CA;
-  constexpr int kUnitsY = kTileM * 4 / kMfmaThreads, kUnitsC = kTileN * 4 / kMfmaThreads;  // 16-byte units a thread brings per step
-  constexpr int kBuf = (kTileM + kTileN) * 4;  // units of a buffer: the vectors', then the centroids'
-  __shared__ u32x4 s_op[2][kBuf];
+  constexpr int kUnitsY = kTileM * 4 / kMfmaThreads, kUnitsC = kTileN * 4 / kMfmaThreads;  // copies of 1 KiB a wavefront makes per step
+  constexpr int kBuf = (kTileM + kTileN) * 4;  // 16-byte units of a buffer: the vectors', then the centroids'
+  extern __shared__ u32x4 s_op[];              // kBuffers of them
   __shared__ float s_min[kTileM][2];
-  __shared__ float s_cn[kTileN];  // bias of the tile's centroids, read after the last barrier of the k loop
+  __shared__ float s_cn[kTileN];  // bias of the tile's centroids
   __shared__ uint32_t s_cnt[kTileM];
   __shared__ __attribute__((aligned(16))) uint16_t s_kept[kTileM][kTileCands];
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int wv = wave & 1, wc = wave >> 1;  // wavefront's place in the 2 (vectors) x 2 (centroids) arrangement
 
   // per-request counters of the search plan start from zero (no memset node on the stream)
@@ -302,7 +309,8 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void k_coarse_mfma(Dev D, int64_t 
   const int64_t row0 = row_tile * kTileM;
   const int col0 = col_tile * kTileN;
 
-  if (tid < kTileN) s_cn[tid] = col0 + tid < D.nlist ? D.cbias[col0 + tid] : __builtin_inff();
+  // (asked for in front of the copies, put into LDS behind the multiplications)
+  const float bias = tid < kTileN && col0 + tid < D.nlist ? D.cbias[col0 + tid] : __builtin_inff();
 
   floatx16 acc[CA][2];
 #pragma unroll
@@ -312,67 +320,78 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void k_coarse_mfma(Dev D, int64_t 
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
 
-  // Staging: a wavefront brings blocks of 16 rows, 1 KiB each.  Blocks past the last vector or centroid read the
+  // Copies: a wavefront brings blocks of 16 rows, 1 KiB each.  Blocks past the last vector or centroid read the
   // last one, and rows of the last block past the end hold whatever the memory holds: the scores of both are dropped.
   const int steps = D.dgroups / 4;
-  const u32x4 *srcy[kUnitsY], *srcc[kUnitsC];
+  const u32x4 *src[kUnitsY + kUnitsC];  // the same for every lane
   {
     const int64_t last_y = (n - 1) >> 4;
     const int last_c = (D.nlist - 1) >> 4;
 #pragma unroll
     for (int h = 0; h < kUnitsY; ++h) {
       const int64_t blk = (row0 >> 4) + wave + 4 * h;
-      srcy[h] = yhalf + (size_t)(blk < last_y ? blk : last_y) * steps * 64 + lane;
+      src[h] = yhalf + (size_t)(blk < last_y ? blk : last_y) * steps * 64;
     }
 #pragma unroll
     for (int h = 0; h < kUnitsC; ++h) {
       const int blk = (col0 >> 4) + wave + 4 * h;
-      srcc[h] = D.chalf + (size_t)(blk < last_c ? blk : last_c) * steps * 64 + lane;
+      src[kUnitsY + h] = D.chalf + (size_t)(blk < last_c ? blk : last_c) * steps * 64;
     }
   }
-  u32x4 stage[kUnitsY + kUnitsC];
-  auto fetch = [&](int st) {
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(LdsUnit *)s_op + (uint32_t)wave * 1024u;
+  const uint32_t lane_off = (uint32_t)lane * 16u;
+  auto fetch = [&](int st) {  // asks for a step's operands; they lie in the step's buffer when the wavefront's count of loads says so
+    const uint32_t to = lds0 + (uint32_t)(st % kBuffers) * (kBuf * 16u);
 #pragma unroll
-    for (int h = 0; h < kUnitsY; ++h) stage[h] = srcy[h][(size_t)st * 64];
-#pragma unroll
-    for (int h = 0; h < kUnitsC; ++h) stage[kUnitsY + h] = srcc[h][(size_t)st * 64];
-  };
-  auto put = [&](u32x4 *buf) {
-#pragma unroll
-    for (int h = 0; h < kUnitsY + kUnitsC; ++h) buf[h * kMfmaThreads + tid] = stage[h];
+    for (int h = 0; h < kUnitsY + kUnitsC; ++h)
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                   :: "s"(to + (uint32_t)h * 4096u), "v"(lane_off), "s"(src[h] + (size_t)st * 64) : "memory");
   };
   // operands of v_mfma_f32_32x32x16_f16: lane l supplies 8 consecutive k, the group l / 32 of the
   // 16, of row (or column) l % 32; vectors and centroids use the same split of k over the lanes.
   // The centroids are the rows of the product and the vectors its columns, so that a lane ends up
   // with 16 CA scores of ONE vector per block column and the smallest of them is found in registers.
-  auto multiply = [&](const u32x4 *buf) {
+  struct Operands { halfx8 c[CA], y[2]; };
+  auto read = [&](const u32x4 *buf, int kk) {  // 16 of the step's coordinates
+    Operands o;
+    const int row = lane & 31;  // (block rows start at multiples of 32: same place)
+    const int at = row * 4 + ((kk * 2 + (lane >> 5)) ^ place_swap(row & 15));
 #pragma unroll
-    for (int kk = 0; kk < kTileK / 16; ++kk) {
-      const int row = lane & 31;  // (block rows start at multiples of 32: same place)
-      const int at = row * 4 + ((kk * 2 + (lane >> 5)) ^ ((row >> 1) & 3));
-      halfx8 c[CA], y[2];
+    for (int b = 0; b < 2; ++b) o.y[b] = __builtin_bit_cast(halfx8, buf[(wv * 64 + b * 32) * 4 + at]);
 #pragma unroll
-      for (int a = 0; a < CA; ++a)
-        c[a] = __builtin_bit_cast(halfx8, buf[(kTileM + wc * 32 * CA + a * 32) * 4 + at]);
-#pragma unroll
-      for (int b = 0; b < 2; ++b) y[b] = __builtin_bit_cast(halfx8, buf[(wv * 64 + b * 32) * 4 + at]);
-#pragma unroll
-      for (int a = 0; a < CA; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(c[a], y[b], acc[a][b], 0, 0, 0);
-    }
+    for (int a = 0; a < CA; ++a) o.c[a] = __builtin_bit_cast(halfx8, buf[(kTileM + wc * 32 * CA + a * 32) * 4 + at]);
+    __builtin_amdgcn_sched_barrier(0);  // asked for here, in front of the multiplications that follow
+    return o;
   };
+  auto multiply = [&](const Operands &o) {
+#pragma unroll
+    for (int a = 0; a < CA; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(o.c[a], o.y[b], acc[a][b], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // Loads come back in order: with as many outstanding as the next step has, this step's are in LDS, the wavefront's
+  // own here and everybody's behind the barrier.  Behind it everybody is through with the buffer of the step before as
+  // well (its reads have returned: lgkmcnt), which the step after the next takes.
+  asm volatile("" :: "v"(bias));  // (the bias has its register before the copies are counted)
   fetch(0);
-  put(s_op[0]);
   if (steps > 1) fetch(1);
+  // The multiplications run half a step behind the reads: the second half of a step is multiplied behind the next
+  // barrier, while the first half of the next step comes out of LDS.
+  Operands first, second;
   for (int st = 0; st < steps; ++st) {
-    __syncthreads();  // this step's operands are in LDS, and everybody is through with the other buffer
-    multiply(s_op[st & 1]);
-    if (st + 1 < steps) {
-      put(s_op[(st + 1) & 1]);
-      if (st + 2 < steps) fetch(st + 2);
-    }
+    if (st + 1 < steps) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(kUnitsY + kUnitsC) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (st + 2 < steps) fetch(st + 2);
+    const u32x4 *buf = s_op + (st % kBuffers) * kBuf;
+    first = read(buf, 0);
+    if (st > 0) multiply(second);
+    second = read(buf, 1);
+    multiply(first);
   }
+  multiply(second);
+  if (tid < kTileN) s_cn[tid] = bias;
+  __syncthreads();
 
   // result layout of a 32 x 32 block: register r of lane l holds row (r / 4) * 8 + (l / 32) * 4 + r % 4 (a
   // centroid), column l % 32 (a vector); acc[a][b] is the block of centroid block a and vector block b
@@ -418,36 +437,67 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void k_coarse_mfma(Dev D, int64_t 
   }
   // The tile is reduced here: per vector its smallest score and the centroids within the band of it.
   if (tid < kTileM) s_cnt[tid] = 0u;
+  float mine[2];  // smallest score of this lane's vector over the lane's centroids
 #pragma unroll
-  for (int b = 0; b < 2; ++b) {  // smallest score of this lane's vector over the wavefront's centroids
+  for (int b = 0; b < 2; ++b) {
     float v = __builtin_inff();
 #pragma unroll
     for (int a = 0; a < CA; ++a)
 #pragma unroll
       for (int r = 0; r < 16; ++r) v = fminf(v, acc[a][b][r]);
+    mine[b] = v;
     v = fminf(v, __shfl_xor(v, 32));  // the other half of the lanes holds the other centroids of the same vector
     if (lane < 32) s_min[wv * 64 + b * 32 + lane][wc] = v;
   }
   __syncthreads();
+  // A lane counts its hits and notes the last one, without a branch; it takes their places with one addition.  Nearly
+  // always the hit is its smallest score alone, which is at hand; lanes with several go through the blocks of 32
+  // centroids again that hold some.  (A branch and an addition in LDS for every one of the scores, each waited for,
+  // were 8 us of the 30 that a tile of 768 dimensions took.)
+  uint32_t hits[2][CA], all[2], last[2], slot[2];
+  float low[2], limit[2], per[2];
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
     const int row = wv * 64 + b * 32 + (lane & 31);
     // the smallest of the tile plus the band of the vector, a little wider than the refinement's, so that
-    // what the refinement asks for is certainly among what is kept here
-    const float low = fminf(s_min[row][0], s_min[row][1]), width = mt[b].band * 1.01f;
-    const float limit = low + width, per = width < __builtin_inff() ? 255.f / width : 0.f;
+    // what the refinement asks for is certainly among what is kept here; infinite scores stay out
+    low[b] = fminf(s_min[row][0], s_min[row][1]);
+    const float width = mt[b].band * 1.01f;
+    limit[b] = fminf(low[b] + width, 3.402823466e38f);
+    per[b] = width < __builtin_inff() ? 255.f / width : 0.f;
+    all[b] = last[b] = 0u;
 #pragma unroll
-    for (int a = 0; a < CA; ++a)
+    for (int a = 0; a < CA; ++a) {
+      hits[b][a] = 0u;
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (acc[a][b][r] <= limit && acc[a][b][r] < __builtin_inff()) {
-          const uint32_t slot = atomicAdd(&s_cnt[row], 1u);
-          if (slot < (uint32_t)kTileCands) {
-            // how far above the smallest score, in steps of a 255th of the width and rounded down, over the column
-            const uint32_t above = (uint32_t)fminf((acc[a][b][r] - low) * per, 255.f);
-            s_kept[row][slot] = (uint16_t)(above << 8 | (uint32_t)(centroid_of(a, r) - col0));
-          }
-        }
+      for (int r = 0; r < 16; ++r) {
+        const bool hit = acc[a][b][r] <= limit[b];
+        hits[b][a] += hit ? 1u : 0u;
+        last[b] = hit ? (uint32_t)(a * 16 + r) : last[b];
+      }
+      all[b] += hits[b][a];
+    }
+    slot[b] = all[b] ? atomicAdd(&s_cnt[row], all[b]) : (uint32_t)kTileCands;
+  }
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const int row = wv * 64 + b * 32 + (lane & 31);
+    auto keep = [&](float score, uint32_t at, uint32_t to) {
+      // how far above the smallest score, in steps of a 255th of the width and rounded down, over the column
+      const uint32_t above = (uint32_t)fminf((score - low[b]) * per[b], 255.f);
+      const uint32_t col = (uint32_t)(wc * 32 * CA) + (at >> 4) * 32u + ((at & 15u) >> 2) * 8u + (uint32_t)(lane >> 5) * 4u + (at & 3u);
+      s_kept[row][to] = (uint16_t)(above << 8 | col);
+    };
+    if (all[b] == 1u && slot[b] < (uint32_t)kTileCands) keep(mine[b], last[b], slot[b]);
+    if (__any(all[b] > 1u)) {  // uniform
+      uint32_t to = all[b] > 1u ? slot[b] : (uint32_t)kTileCands;
+#pragma unroll
+      for (int a = 0; a < CA; ++a)
+        if (__any(hits[b][a] && to < (uint32_t)kTileCands))  // uniform
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (acc[a][b][r] <= limit[b] && to < (uint32_t)kTileCands) keep(acc[a][b][r], (uint32_t)(a * 16 + r), to++);
+    }
   }
   __syncthreads();
   if (tid < kTileM && row0 + tid < n) {
@@ -713,6 +763,20 @@ static TileGrid tile_grid(const Dev &D, int64_t n, int width) {
   return {(unsigned)(rows * cols), 0};
 }
 
+template <int CA, bool MATRIX>
+static void launch_tiles(const Dev &D, const TileGrid &tg, int64_t n, const u32x4 *half, const RowMeta *meta, float *approx,
+                         const TileCands &tc, unsigned long long *cursor, uint32_t *zero, int zero_n, hipStream_t s) {
+  constexpr size_t kLds = (size_t)kBuffers * (kTileM + 64 * CA) * kTileK * 2;
+  // above 64 KiB of dynamic LDS a kernel has to be told; once per kernel and process
+  static const bool once = [] {
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(k_coarse_mfma<CA, MATRIX>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds) == hipSuccess;
+  }();
+  (void)once;
+  hipLaunchKernelGGL((k_coarse_mfma<CA, MATRIX>), dim3(tg.blocks), dim3(kMfmaThreads), kLds, s, D, n, half, meta, approx, tc,
+                     tg.die_map, cursor, zero, zero_n);
+}
+
 void launch_coarse_mfma(const Dev &D, int64_t n, const float *Y, u32x4 *half, float *approx,
                         unsigned long long *cursor_to_clear, uint32_t *zero, int zero_n, hipStream_t s) {
   if (n <= 0) return;
@@ -721,10 +785,8 @@ void launch_coarse_mfma(const Dev &D, int64_t n, const float *Y, u32x4 *half, fl
   const int width = tile_width(D, n);
   const TileGrid tg = tile_grid(D, n, width);
   const TileCands none{};
-  if (width == 256)
-    hipLaunchKernelGGL((k_coarse_mfma<4, true>), dim3(tg.blocks), dim3(kMfmaThreads), 0, s, D, n, half, meta, approx, none, tg.die_map, cursor_to_clear, zero, zero_n);
-  else
-    hipLaunchKernelGGL((k_coarse_mfma<2, true>), dim3(tg.blocks), dim3(kMfmaThreads), 0, s, D, n, half, meta, approx, none, tg.die_map, cursor_to_clear, zero, zero_n);
+  if (width == 256) launch_tiles<4, true>(D, tg, n, half, meta, approx, none, cursor_to_clear, zero, zero_n, s);
+  else launch_tiles<2, true>(D, tg, n, half, meta, approx, none, cursor_to_clear, zero, zero_n, s);
 }
 
 void launch_coarse_tiles(const Dev &D, int64_t n, const float *Y, u32x4 *half, RowMeta *meta, TileCands &tc,
@@ -735,10 +797,8 @@ void launch_coarse_tiles(const Dev &D, int64_t n, const float *Y, u32x4 *half, R
   tc.width = n * 2 <= tc.rows ? tile_width(D, n) : 256;
   tc.tiles = (D.nlist + tc.width - 1) / tc.width;
   const TileGrid tg = tile_grid(D, n, tc.width);
-  if (tc.width == 256)
-    hipLaunchKernelGGL((k_coarse_mfma<4, false>), dim3(tg.blocks), dim3(kMfmaThreads), 0, s, D, n, half, meta, nullptr, tc, tg.die_map, nullptr, nullptr, 0);
-  else
-    hipLaunchKernelGGL((k_coarse_mfma<2, false>), dim3(tg.blocks), dim3(kMfmaThreads), 0, s, D, n, half, meta, nullptr, tc, tg.die_map, nullptr, nullptr, 0);
+  if (tc.width == 256) launch_tiles<4, false>(D, tg, n, half, meta, nullptr, tc, nullptr, nullptr, 0, s);
+  else launch_tiles<2, false>(D, tg, n, half, meta, nullptr, tc, nullptr, nullptr, 0, s);
 }
 
 void launch_assign_refine(const Dev &D, int64_t n, const float *Y, const RowMeta *meta, const TileCands &tc, bool reserve,
