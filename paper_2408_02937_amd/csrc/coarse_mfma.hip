@@ -41,6 +41,7 @@
 // reduces its tile on the spot to, per row, the tile's smallest score and the (up to
 // kTileCands) columns within the band of it; the refinement reads those few bytes
 // per (row, tile) instead of the matrix, twice.
+#include <type_traits>
 #include "rtams_launch.h"
 
 namespace rtams {
@@ -48,7 +49,6 @@ namespace rtams {
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) u32x4 LdsUnit;
 
 constexpr int kMfmaThreads = 256;  // 4 wavefronts: 2 (vectors) x 2 (centroids)
 constexpr int kTileM = 128;        // vectors of a tile: 64 to a wavefront
@@ -338,14 +338,13 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void k_coarse_mfma(Dev D, int64_t 
       src[kUnitsY + h] = D.chalf + (size_t)(blk < last_c ? blk : last_c) * steps * 64;
     }
   }
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(LdsUnit *)s_op + (uint32_t)wave * 1024u;
+  const uint32_t lds0 = lds_address(s_op) + (uint32_t)wave * 1024u;
   const uint32_t lane_off = (uint32_t)lane * 16u;
   auto fetch = [&](int st) {  // asks for a step's operands; they lie in the step's buffer when the wavefront's count of loads says so
     const uint32_t to = lds0 + (uint32_t)(st % kBuffers) * (kBuf * 16u);
 #pragma unroll
     for (int h = 0; h < kUnitsY + kUnitsC; ++h)
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                   :: "s"(to + (uint32_t)h * 4096u), "v"(lane_off), "s"(src[h] + (size_t)st * 64) : "memory");
+      copy_to_lds(src[h] + (size_t)st * 64, to + (uint32_t)h * 4096u, lane_off);
   };
   // operands of v_mfma_f32_32x32x16_f16: lane l supplies 8 consecutive k, the group l / 32 of the
   // 16, of row (or column) l % 32; vectors and centroids use the same split of k over the lanes.
@@ -525,6 +524,82 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void k_coarse_mfma(Dev D, int64_t 
 // (21,845 rows of 768 dimensions: 280 us).  So a workgroup reads the digests of up to
 // 64 rows first, a few lanes to a row, puts the candidates of the rows that have
 // several into a list, and then scores the list, a thread to a candidate.
+// The same with four neighbouring lanes to a candidate (all four call with the same arguments, and all have the score):
+// lane s of the four brings chunks s, s + 4, ... and works out their differences, and the chain, the same in all four,
+// takes them from one after the other.  A lane alone waits for a trip to memory per eight chunks, 24 of them at 768
+// dimensions and next to nobody else on the compute unit; here two sets of 16 chunks take turns.  (28,928 rows of 768
+// dimensions, 38 candidates to a workgroup: the refinement 57 us with a lane to a candidate and 1,034 workgroups, 45 with
+// four and 998, in a bulk load of three sub-rounds 40 on average.)
+template <int S>
+__device__ __forceinline__ float quad_take(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), S * 0x55, 0xf, 0xf, true));
+}
+template <int S>
+__device__ __forceinline__ double quad_take(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)b, S * 0x55, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), S * 0x55, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ inline double exact_score_quad(const Dev &D, const float *__restrict__ y, int c) {
+  const float4 *row4 = reinterpret_cast<const float4 *>(D.centroids + (size_t)c * D.d);
+  const float4 *y4 = reinterpret_cast<const float4 *>(y);
+  const bool l2 = D.metric == 0;
+  const int sub = threadIdx.x & 3, last = D.d4 - 1;
+  constexpr int kU = 4;  // chunks of a lane in a set
+  double acc = 0.0;
+  float4 a0[kU], b0[kU], a1[kU], b1[kU];
+  auto load = [&](float4 *a, float4 *b, int j) {
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int at = min(j + 4 * u + sub, last);
+      a[u] = y4[at];
+      b[u] = row4[at];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto use = [&](const float4 *a, const float4 *b, int j) {
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      if (l2) {
+        const double t0 = (double)a[u].x - (double)b[u].x, t1 = (double)a[u].y - (double)b[u].y;
+        const double t2 = (double)a[u].z - (double)b[u].z, t3 = (double)a[u].w - (double)b[u].w;
+        auto chain = [&](auto tag) {
+          constexpr int S = decltype(tag)::value;
+          if (j + 4 * u + S > last) return;  // uniform
+          double t = quad_take<S>(t0); acc = __builtin_fma(t, t, acc);
+          t = quad_take<S>(t1); acc = __builtin_fma(t, t, acc);
+          t = quad_take<S>(t2); acc = __builtin_fma(t, t, acc);
+          t = quad_take<S>(t3); acc = __builtin_fma(t, t, acc);
+        };
+        chain(std::integral_constant<int, 0>{}); chain(std::integral_constant<int, 1>{});
+        chain(std::integral_constant<int, 2>{}); chain(std::integral_constant<int, 3>{});
+      } else {
+        auto chain = [&](auto tag) {
+          constexpr int S = decltype(tag)::value;
+          if (j + 4 * u + S > last) return;  // uniform
+          acc = __builtin_fma((double)quad_take<S>(a[u].x), (double)quad_take<S>(b[u].x), acc);
+          acc = __builtin_fma((double)quad_take<S>(a[u].y), (double)quad_take<S>(b[u].y), acc);
+          acc = __builtin_fma((double)quad_take<S>(a[u].z), (double)quad_take<S>(b[u].z), acc);
+          acc = __builtin_fma((double)quad_take<S>(a[u].w), (double)quad_take<S>(b[u].w), acc);
+        };
+        chain(std::integral_constant<int, 0>{}); chain(std::integral_constant<int, 1>{});
+        chain(std::integral_constant<int, 2>{}); chain(std::integral_constant<int, 3>{});
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  load(a0, b0, 0);
+  for (int j = 0; j <= last; j += 8 * kU) {  // uniform
+    load(a1, b1, j + 4 * kU);
+    use(a0, b0, j);
+    if (j + 4 * kU > last) break;
+    load(a0, b0, j + 8 * kU);
+    use(a1, b1, j + 4 * kU);
+  }
+  return acc;
+}
+
 __device__ inline double exact_score(const Dev &D, const float *__restrict__ y, int c) {
   // the fixed arithmetic of coarse.hip: one double FMA per dimension, dimensions in order; the
   // 16-byte loads run eight chunks ahead of the chain (a load per turn of the chain, waited for each
@@ -711,17 +786,28 @@ __global__ __launch_bounds__(kRefineThreads) void k_assign_refine(Dev D, int64_t
     }
     if (lane == 0) s_col[r] = best_c;
   }
-  // the listed candidates, a thread to each (a list longer than the workgroup goes round: the scores of the
-  // turns are compared through LDS, keys first, then the lowest index among the equal ones)
+  // the listed candidates (a list longer than the workgroup goes round: the scores of the turns are compared through
+  // LDS, keys first, then the lowest index among the equal ones).  Four threads to a candidate while the list is no
+  // longer than the workgroup, as it nearly always is; a thread to each where it is, and issue is what bounds it.
   const int entries = (int)min(s_n, s_full);
-  for (int e = tid; e < entries; e += kRefineThreads) {
-    const double s = exact_score(D, Y + (i0 + s_lrow[e]) * D.d, s_lcol[e]);
+  auto scored = [&](int e, double s) {
     unsigned long long key = ~0ull;
     if (s == s) {  // a score that does not compare is nobody's best
       key = refine_key(l2, s);
       atomicMin(&s_key[s_lrow[e]], key);
     }
     s_lkey[e] = key;
+  };
+  if (entries <= kRefineThreads) {  // uniform
+    for (int e0 = 0; e0 < entries; e0 += kRefineThreads / 4) {  // uniform
+      const int e = e0 + tid / 4;
+      if (e0 + wave * (kWave / 4) >= entries) break;  // uniform over the wavefront: the fours stay whole
+      const int ee = min(e, entries - 1);
+      const double s = exact_score_quad(D, Y + (i0 + s_lrow[ee]) * D.d, s_lcol[ee]);
+      if (e < entries && (tid & 3) == 0) scored(e, s);
+    }
+  } else {
+    for (int e = tid; e < entries; e += kRefineThreads) scored(e, exact_score(D, Y + (i0 + s_lrow[e]) * D.d, s_lcol[e]));
   }
   __syncthreads();
   for (int e = tid; e < entries; e += kRefineThreads)
@@ -805,10 +891,11 @@ void launch_assign_refine(const Dev &D, int64_t n, const float *Y, const RowMeta
                           int32_t *assign, uint32_t *did, hipStream_t s) {
   if (n <= 0) return;
   // four tiles to a lane, so that a workgroup's rows are a turn or a few of trips to memory; as many rows to a
-  // workgroup as leave four workgroups to a compute unit
+  // workgroup as leave four workgroups to a compute unit, all there is room for (28 rows of 28,928 to a workgroup were
+  // 1,034 of them, and the last ten took the kernel as long again as all others)
   int lpr = 4;
   while (lpr < kWave && lpr * 4 < tc.tiles) lpr *= 2;
-  int64_t rows = n / 1024;
+  int64_t rows = (n + 1023) / 1024;
   const int64_t turn = kRefineThreads / lpr < kRefineRows ? kRefineThreads / lpr : kRefineRows;  // rows read at a time
   rows = rows < 4 ? 4 : rows > kRefineRows ? kRefineRows : rows;
   if (rows > turn) rows = rows / turn * turn;

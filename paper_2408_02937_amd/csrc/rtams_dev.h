@@ -180,6 +180,17 @@ __device__ inline size_t vec_chunk_index(const Dev &D, uint32_t moff, int c) {
   return ((size_t)group * D.vchunks + c) * kWave + lane;
 }
 
+// ---- copies straight from memory to LDS: lane l of the wavefront brings the 16 bytes at src + 16 l, and the 1 KiB lies in
+// order at the LDS address `to` (both the same for every lane; lane16 = 16 l).  The compiler does not know of them: whoever
+// asks for copies waits for them (the wavefront's count of loads, in front of the barrier that hands them to others),
+// and does not end before they have come.
+__device__ __forceinline__ void copy_to_lds(const void *src, uint32_t to, uint32_t lane16) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(lane16), "s"(src) : "memory");
+}
+__device__ __forceinline__ uint32_t lds_address(const void *p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)p;
+}
+
 // ---- narrow storage: a 16-byte chunk holds 8 halves or 16 bytes.  piece s of a chunk is the
 // float4 of its dimensions 4s..4s+3 (2 pieces of halves, 4 of bytes).
 typedef _Float16 Half2 __attribute__((ext_vector_type(2)));
