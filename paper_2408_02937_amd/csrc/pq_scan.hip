@@ -14,6 +14,11 @@ namespace rtams {
 // per vector, added up in the order of the sub-spaces.  (The codes of a probed list are read by
 // every query that probes it; they are a small fraction of the flat vectors and stay in cache.)
 // Survivors of the query's bound are appended to its records exactly as in the scan of flat lists.
+// What bounds it: random look-ups in LDS (a wavefront's 64 words meet two to a bank and more), 37 of the 55 us that 256
+// queries x 32 probes over 1 M codes of 16 bytes take; and the set-up of a workgroup (probes, blocks, table), 4 us, which
+// other workgroups hide if they are there.  64 registers leave room for four workgroups on a compute unit, all of such a
+// request at once; the table goes to LDS without passing through registers.  (With 90, half of them waited for the other
+// half: 66 us.)
 constexpr int kPqScanWaves = 8;
 
 constexpr int kPqScanThreads = kPqScanWaves * kWave;
@@ -32,7 +37,7 @@ __device__ inline void pq_flush(const SearchScratch &S, int q, unsigned long lon
   }
 }
 
-__global__ __launch_bounds__(kPqScanThreads) void k_pq_scan(Dev D, int nprobe, int max_nprobe, int parts,
+__global__ __launch_bounds__(kPqScanThreads, 8) void k_pq_scan(Dev D, int nprobe, int max_nprobe, int parts,
                                                             SearchScratch S) {
   extern __shared__ float pq_lut[];            // [M][256]
   __shared__ uint32_t gstart[kMaxNprobe + 1];  // groups of the query in front of probe p
@@ -70,17 +75,9 @@ __global__ __launch_bounds__(kPqScanThreads) void k_pq_scan(Dev D, int nprobe, i
   uint32_t per = (total + (uint32_t)parts - 1) / (uint32_t)parts;
   const uint32_t u_lo = (uint32_t)part * per, u_hi = min(total, u_lo + per);
   if (u_lo >= u_hi) return;  // uniform over the workgroup
-  // the query's table: loads issued here, stored to LDS after the first chunk's blocks are resolved
-  constexpr int kLutRegs = 64 * 64 / kPqScanThreads;  // float4 per thread at M = 64
-  float4 lut_reg[kLutRegs];
-  {
-    const float4 *src = reinterpret_cast<const float4 *>(S.lut + (size_t)q * M * 256);
-#pragma unroll
-    for (int r = 0; r < kLutRegs; ++r) {
-      const int i = tid + r * kPqScanThreads;
-      lut_reg[r] = i < M * 64 ? src[i] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  }
+  // the query's table, 1 KiB per sub-space: on its way to LDS while the first chunk's blocks are resolved
+  for (int m = wave; m < M; m += kPqScanWaves)
+    copy_to_lds(S.lut + ((size_t)q * M + m) * 256, lds_address(pq_lut) + (uint32_t)m * 1024u, (uint32_t)lane * 16u);
   const unsigned long long base = S.qbase[q];
   const uint32_t bound = __hip_atomic_load(&S.bound[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const int metric = D.metric;
@@ -101,14 +98,7 @@ __global__ __launch_bounds__(kPqScanThreads) void k_pq_scan(Dev D, int nprobe, i
         s_blk[tid] = (uint32_t)*table_entry(D, list, (u - gstart[lo]) / gpb);
       }
     }
-    if (c0 == u_lo) {
-      float4 *dst = reinterpret_cast<float4 *>(pq_lut);
-#pragma unroll
-      for (int r = 0; r < kLutRegs; ++r) {
-        const int i = tid + r * kPqScanThreads;
-        if (i < M * 64) dst[i] = lut_reg[r];
-      }
-    }
+    if (c0 == u_lo) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's part of the table is there
     __syncthreads();
     const uint32_t n_here = min((uint32_t)kPqScanThreads, u_hi - c0);
     // a wavefront takes kPqUnits consecutive groups at a time: all their loads are in flight together,
