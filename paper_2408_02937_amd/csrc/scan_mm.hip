@@ -57,7 +57,7 @@ __device__ __forceinline__ void scan_groups_mm(const Dev &D, const SearchScratch
   constexpr int kPieces = pieces_of(ST);
   const int vc = D.vchunks;
   const int qstride = D.d4 + 1;  // float4s between two queries in LDS: an odd stride keeps the four rows a read touches on different banks
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int sub = lane & 3;
   const float4 *__restrict__ qrow = qs + sub * qstride;  // query `sub` of group 0; group g is 4 g rows on
   const uint32_t gpb = (uint32_t)D.groups_per_block;
@@ -115,8 +115,9 @@ __device__ __forceinline__ void scan_groups_mm(const Dev &D, const SearchScratch
   };
   uint32_t g0 = g_lo + (uint32_t)wave;
   if (g0 >= g_hi) return;  // nothing staged yet
+  first_b = (uint32_t)__builtin_amdgcn_readfirstlane((int)first_b);
   const float4 *x = place(g0, first_b);
-  uint32_t cur_b = first_b;  // the block of group g0
+  uint32_t cur_b = first_b;  // the block of group g0 (the same for every lane, as is all that follows from it: scalar registers)
   if (d4_main) load_set(sa, x, 0);
   for (;;) {
     const uint32_t g_next = g0 + kMmWaves;
@@ -175,12 +176,15 @@ __device__ __forceinline__ void scan_groups_mm(const Dev &D, const SearchScratch
     for (int c = d4_main; c < vc; ++c) use_chunk(x[(size_t)c * kWave], c);
     const float4 *x_next = x;
     if (more) {  // the next group's first loads go out before this group's survivors are dealt with
+      next_b = (uint32_t)__builtin_amdgcn_readfirstlane((int)next_b);
       x_next = place(g_next, next_b);
       if (d4_main) load_set(sa, x_next, 0);
     }
 
     // scores -> keys; which of the lane's 4 candidates per group of queries survive
-    const float nr[4] = {quad_broadcast<0>(nrm), quad_broadcast<1>(nrm), quad_broadcast<2>(nrm), quad_broadcast<3>(nrm)};
+    auto norm_of = [&](int r) {  // of candidate r (moved again for every group of queries: four registers kept for it were spilled)
+      return r == 0 ? quad_broadcast<0>(nrm) : r == 1 ? quad_broadcast<1>(nrm) : r == 2 ? quad_broadcast<2>(nrm) : quad_broadcast<3>(nrm);
+    };
     const uint32_t vbase = g0 * kWave + 4u * (uint32_t)(lane >> 2);
     const uint32_t slot_base = slot_of(D, cur_b, (g0 % gpb) * kWave + 4u * (uint32_t)(lane >> 2));
 #pragma unroll
@@ -191,7 +195,7 @@ __device__ __forceinline__ void scan_groups_mm(const Dev &D, const SearchScratch
       for (int r = 0; r < 4; ++r) {
         float sc = acc[g][r];
         // (an infinite coordinate makes the norm form inf - inf: such a vector is infinitely far, as the direct form has it)
-        sc = METRIC == 0 ? fminf(fmaf(-2.f, sc, nr[r] + me.qn), __builtin_inff()) : -sc;
+        sc = METRIC == 0 ? fminf(fmaf(-2.f, sc, norm_of(r) + me.qn), __builtin_inff()) : -sc;
         key[r] = key_of_float(sc + 0.0f);
         if (vbase + r < me.len && key[r] <= me.bound) pass |= 1u << r;
       }
@@ -237,8 +241,12 @@ __device__ __forceinline__ void scan_groups_mm(const Dev &D, const SearchScratch
 // workgroup that finds nothing leaves.  Short scans keep the plain mapping: the swap is a round trip
 // in front of every item, and the launch has tens of thousands of workgroups that find their range
 // used up and should leave at once (measured at 1 M x 128, 2,048 items: 226 instead of 103 us).
+// Wavefronts to a SIMD: four where the launch is short and its last workgroups count (256 queries x 32 probes over 1 M x
+// 128, 2,048 items: bytes 89 us with three and 87 with four, floats 105 and 104: what is scanned comes from memory at
+// 7 TB/s meanwhile, and only the launch's end is shorter); three for long scans and inner products of floats, which
+// gain nothing by it.
 template <int METRIC, bool STEAL, int ST>
-__global__ __launch_bounds__(kMmWaves *kWave) void k_scan_mm(Dev D, int max_nprobe, const float *__restrict__ Q,
+__global__ __launch_bounds__(kMmWaves *kWave, STEAL || (METRIC == 1 && ST == 0) ? 3 : 4) void k_scan_mm(Dev D, int max_nprobe, const float *__restrict__ Q,
                                                              SearchScratch S, int tile_rows) {
   extern __shared__ float4 lds_mm[];  // [tile_rows][d / 4 + 1] coordinates of the tile's queries, [tile_rows] TileQuery, [wavefronts] WaveStage
   ScanQueues *Qs = S.queues;
@@ -283,8 +291,8 @@ __global__ __launch_bounds__(kMmWaves *kWave) void k_scan_mm(Dev D, int max_npro
     // number of the item it took from the next XCD: what it loaded above was nothing)
     if (!has_own || s_item != own) desc = S.tile_desc[s_item];
   }
-  const int list = (int)desc.x;
-  const uint32_t first = desc.y;
+  const int list = __builtin_amdgcn_readfirstlane((int)desc.x);  // (one item to the workgroup)
+  const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)desc.y);
   if (pairs == 0) return;
   const int d4 = D.d4, qstride = d4 + 1;
   float4 *qs = lds_mm;
@@ -299,11 +307,11 @@ __global__ __launch_bounds__(kMmWaves *kWave) void k_scan_mm(Dev D, int max_npro
   if (rows > tile_rows || rows > kMmTileMax) return;  // a descriptor the launch was not sized for: nothing is scanned
   // The block number of the wavefront's first group of vectors is asked for now (two dependent reads)
   // and used after the tile is set up.  Never past the list's chain, whatever the descriptors say.
-  const uint32_t g_begin = desc.w * seg;
+  const uint32_t g_begin = (uint32_t)__builtin_amdgcn_readfirstlane((int)desc.w) * seg;
   const uint32_t g_have = D.nblk[list] * (uint32_t)D.groups_per_block;
   uint32_t first_b = 0;
   {
-    const uint32_t g0 = g_begin + threadIdx.x / kWave;
+    const uint32_t g0 = g_begin + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     if (g0 < g_have) first_b = (uint32_t)*table_entry(D, list, g0 / (uint32_t)D.groups_per_block);
   }
   // the tile's queries: words first (one thread per row), then coordinates (the workgroup together)

@@ -378,7 +378,7 @@ constexpr int kScanWaves = 4;
 //    own tile of up to 8 queries in LDS;
 //  - matrix cores: a workgroup takes ONE item, its tile of up to 32 queries sits in LDS once, and its four wavefronts
 //    share out the item's groups of vectors.  Large tiles are what keeps a hot list from being read once per 8 of the
-//    dozens of queries that probe it; the price is registers (3 wavefronts per SIMD instead of 4) and a tile to
+//    dozens of queries that probe it; the price is registers (3 wavefronts per SIMD in long scans) and a tile to
 //    set up per item, which small requests, whose tiles hold a query or two, do not get back
 //    (measured at 1 and 32 queries: 15 to 20 % slower than the vector unit with its partial-distance
 //    pruning; mm_scan_pays() has the larger ones).
