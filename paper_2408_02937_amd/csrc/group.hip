@@ -235,7 +235,8 @@ __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, in
   uint32_t bound = 0xFFFFFFFFu;
   if ((uint32_t)k <= want_groups * kWave) {
     const SelectResult r = wg_radix_select<32>(
-        (int)(want_groups * kWave), (uint32_t)k, [&](int i, uint64_t &kv) { kv = skey[i]; return true; }, hist, bc);
+        (int)(want_groups * kWave), (uint32_t)k, [&](int i, uint64_t &kv) { kv = skey[i]; return true; }, hist, bc,
+        (uint32_t)(k + k / 16));
     bound = (uint32_t)r.T;  // the k-th smallest key, or an upper bound of it that admits the same candidates
   }
   if (tid == 0) {

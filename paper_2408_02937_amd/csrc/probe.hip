@@ -112,7 +112,7 @@ __global__ __launch_bounds__(kSelThreadsMany) void k_probe_plan(Dev D, int64_t n
     const float band = search_row_meta(D, nq, S.qhalf)[q].band;  // 2 E, see coarse_mfma.hip
     const SelectResult ra = wg_radix_select_each<32>(
         (uint32_t)nprobe, [&](auto body) { each_approx([&](int, float v) { body((uint64_t)key_of_float(v + 0.0f)); }); },
-        hist, bc);
+        hist, bc, (uint32_t)(nprobe + nprobe / 8));
     const uint32_t tk = (uint32_t)ra.T;  // key of (an upper bound of) the nprobe-th smallest approximation
     const float t = __uint_as_float((tk & 0x80000000u) ? (tk & 0x7fffffffu) : ~tk);
     const float limit = t + band;
@@ -132,7 +132,7 @@ __global__ __launch_bounds__(kSelThreadsMany) void k_probe_plan(Dev D, int64_t n
         k1[p] = key_of_score(exact(c));
         k2[p] = (uint64_t)c;
       }
-      wg_sort(nc, k1, k2, pay);  // by (exact score, index): the first nprobe are the answer
+      wg_sort<64>(nc, k1, k2, pay);  // by (exact score, index): the first nprobe are the answer
       done = true;
     }
   }
@@ -159,10 +159,14 @@ __global__ __launch_bounds__(kSelThreadsMany) void k_probe_plan(Dev D, int64_t n
       for (int i = threadIdx.x; i < n; i += T) body(i, key_of_score(sc[i]));
     }
   };
+  // The winners are sorted by (score, index): a threshold that admits a few more than nprobe does, the first nprobe are
+  // taken behind the sort.  Only where ties leave more than that are they told apart by index first.
+  // (Behind the filter this is rare, and the scalar registers are taken: exactly nprobe there.)
+  const uint32_t room = (uint32_t)(FROM_APPROX ? nprobe : min(nprobe + 16, kMaxNprobe));
   if (!all) {
     r1 = wg_radix_select_each<64>((uint32_t)nprobe,
-                                  [&](auto body) { each_key([&](int, uint64_t k) { body(k); }); }, hist, bc);
-    if (r1.c_eq > r1.need)  // ties at the boundary go to the lower index
+                                  [&](auto body) { each_key([&](int, uint64_t k) { body(k); }); }, hist, bc, FROM_APPROX ? 0u : room);
+    if ((uint32_t)nprobe - r1.need + r1.c_eq > room)  // ties at the boundary go to the lower index
       r2 = wg_radix_select_each<32>(
           r1.need, [&](auto body) { each_key([&](int i, uint64_t k) { if (k == r1.T) body((uint64_t)(uint32_t)i); }); },
           hist, bc);
@@ -170,14 +174,14 @@ __global__ __launch_bounds__(kSelThreadsMany) void k_probe_plan(Dev D, int64_t n
   if (threadIdx.x == 0) cnt[0] = 0;
   __syncthreads();
   each_key([&](int i, uint64_t k) {
-    bool take = all || k < r1.T || (k == r1.T && (r1.c_eq <= r1.need || (uint64_t)i <= r2.T));
+    bool take = all || k < r1.T || (k == r1.T && ((uint32_t)nprobe - r1.need + r1.c_eq <= room || (uint64_t)i <= r2.T));
     if (take) {
       uint32_t p = atomicAdd(&cnt[0], 1u);
       k1[p] = k; k2[p] = (uint64_t)i; pay[p] = (uint32_t)i;
     }
   });
   __syncthreads();
-  wg_sort(nprobe, k1, k2, pay);
+  wg_sort<64>(FROM_APPROX ? nprobe : (int)cnt[0], k1, k2, pay);
   }  // !done
   if (done) {  // the sort carried no payload: the list index is the second key
     __syncthreads();

@@ -80,6 +80,9 @@ __device__ inline void overflow_request_done(const SearchScratch &S, uint32_t wo
 // the selection stops early and T is the largest key that group can hold; else
 // T is the k-th smallest key itself and the c_eq keys equal it).  Callers take
 // key < T, and key == T under the tie rule.  Requires 1 <= k <= #valid.
+// `stop`: the caller is content with a threshold that admits at most so many keys (k - need + c_eq of them, all
+// <= T): it sorts what it takes anyway, and the passes that would tell the last bin's few keys apart, each with two
+// barriers and a microsecond of its own, are left out.
 struct SelectResult {
   uint64_t T;
   uint32_t need, c_eq;
@@ -122,7 +125,7 @@ constexpr int kSelectLdsWords = 2 * 256 + 4 * 16;
 // `each(body)` calls body(key) for every key of the calling thread that takes part.  `hist` holds
 // kSelectLdsWords words, 8-byte aligned; the workgroup has at most 16 wavefronts.
 template <int BITS, typename Each>
-__device__ SelectResult wg_radix_select_each(uint32_t k, Each each, uint32_t *hist, uint32_t *bc) {
+__device__ __forceinline__ SelectResult wg_radix_select_each(uint32_t k, Each each, uint32_t *hist, uint32_t *bc, uint32_t stop = 0) {
   typedef typename std::conditional<BITS == 32, unsigned int, unsigned long long>::type Key;  // what the range is reduced in
   // The first digit is the 8 bits that end at the highest bit in which any two keys differ: scores
   // of one query's candidates share sign, exponent and often the first mantissa bits; digits on
@@ -146,10 +149,13 @@ __device__ SelectResult wg_radix_select_each(uint32_t k, Each each, uint32_t *hi
   }
   __syncthreads();
   uint64_t kmin = ~0ull, kmax = 0ull;
-  for (int w = 0; w < (int)(blockDim.x / kWave); ++w) {
-    const uint64_t a = range[2 * w], b = range[2 * w + 1];
-    kmin = a < kmin ? a : kmin;
-    kmax = b > kmax ? b : kmax;
+  for (int w0 = 0; w0 < (int)(blockDim.x / kWave); w0 += 4) {  // (workgroups of this library have whole fours of wavefronts)
+#pragma unroll
+    for (int w = w0; w < w0 + 4; ++w) {
+      const uint64_t a = range[2 * w], b = range[2 * w + 1];
+      kmin = a < kmin ? a : kmin;
+      kmax = b > kmax ? b : kmax;
+    }
   }
   int shift = 0;
   uint64_t prefix = 0, mask = 0;
@@ -180,7 +186,7 @@ __device__ SelectResult wg_radix_select_each(uint32_t k, Each each, uint32_t *hi
     // bits the prefix already holds: only keys that match the prefix were counted, so they agree.
     prefix |= (uint64_t)dg << shift;
     mask |= (uint64_t)255u << shift;
-    if (c_eq == need) {  // the whole bin belongs to the k smallest: the lower digits cannot matter
+    if (c_eq == need || k - need + c_eq <= stop) {  // the whole bin is taken: the lower digits cannot matter
       if (shift > 0) prefix |= (1ull << shift) - 1ull;  // threshold = largest key of the bin
       break;
     }
@@ -194,7 +200,7 @@ __device__ SelectResult wg_radix_select_each(uint32_t k, Each each, uint32_t *hi
 // Items 0..n-1 given by fn(i, key) (false: the item does not take part); keys are
 // read from memory, four independent loads in flight per thread.
 template <int BITS, typename Fn>
-__device__ SelectResult wg_radix_select(int n, uint32_t k, Fn fn, uint32_t *hist, uint32_t *bc) {
+__device__ __forceinline__ SelectResult wg_radix_select(int n, uint32_t k, Fn fn, uint32_t *hist, uint32_t *bc, uint32_t stop = 0) {
   auto each = [&](auto body) {
     for (int i0 = threadIdx.x; i0 < n; i0 += 4 * blockDim.x) {
       uint64_t key[4];
@@ -209,32 +215,34 @@ __device__ SelectResult wg_radix_select(int n, uint32_t k, Fn fn, uint32_t *hist
         if (ok[u]) body(key[u]);
     }
   };
-  return wg_radix_select_each<BITS>(k, each, hist, bc);
+  return wg_radix_select_each<BITS>(k, each, hist, bc, stop);
 }
 
-// Bitonic sort of m (power of two) entries in LDS by (k1, k2) ascending; pay is
-// carried along.  The first wavefront does all of it (LDS operations of one
-// wavefront execute in order, so the steps need no workgroup barrier); the
-// others wait at the end.
+// Bitonic sort of m (power of two) entries in LDS by (k1, k2) ascending; pay is carried along.  A wavefront takes 64
+// neighbouring pairs: with strides up to 64 they lie in 128 entries that are its own, and as LDS operations of one
+// wavefront execute in order those steps need no barrier; only the longer strides have one in front and one behind.
+// (One wavefront for all of it took 35 us for the 293 finalists of a hot list's query; this takes 5.)
 __device__ inline void wg_bitonic_sort(int m, uint64_t *k1, uint64_t *k2, uint32_t *pay) {
   __syncthreads();
-  if (threadIdx.x < kWave) {
-    for (int size = 2; size <= m; size <<= 1) {
-      for (int stride = size >> 1; stride > 0; stride >>= 1) {
+  for (int size = 2; size <= m; size <<= 1) {
+    for (int stride = size >> 1; stride > 0; stride >>= 1) {
+      if (stride > kWave) {
+        __syncthreads();
+      } else {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        for (int t = threadIdx.x; t < m / 2; t += kWave) {
-          int i = 2 * t - (t & (stride - 1));
-          int j = i + stride;
-          bool up = (i & size) == 0;
-          uint64_t a1 = k1[i], a2 = k2[i], b1 = k1[j], b2 = k2[j];
-          bool a_gt_b = a1 != b1 ? a1 > b1 : a2 > b2;
-          if (a_gt_b == up) {
-            k1[i] = b1; k2[i] = b2; k1[j] = a1; k2[j] = a2;
-            uint32_t p = pay[i]; pay[i] = pay[j]; pay[j] = p;
-          }
+      }
+      for (int t = threadIdx.x; t < m / 2; t += (int)blockDim.x) {
+        const int i = 2 * t - (t & (stride - 1)), j = i + stride;
+        const bool up = (i & size) == 0;
+        const uint64_t a1 = k1[i], a2 = k2[i], b1 = k1[j], b2 = k2[j];
+        const bool a_gt_b = a1 != b1 ? a1 > b1 : a2 > b2;
+        if (a_gt_b == up) {
+          k1[i] = b1; k2[i] = b2; k1[j] = a1; k2[j] = a2;
+          const uint32_t p = pay[i]; pay[i] = pay[j]; pay[j] = p;
         }
       }
+      if (stride > kWave) __syncthreads();
     }
   }
   __syncthreads();
@@ -252,7 +260,9 @@ __device__ inline int next_pow2(int v) {
 // e (equal pairs in the order they stand in), and the entry is written to that place — two
 // barriers instead of the dozens of dependent LDS round trips of a sorting network, which costs a
 // single wavefront 5 to 7 us for 32 to 128 entries.  More entries go through the network.
+// BITS: what the first key has, 32 or 64.
 constexpr int kRankSortMax = 256;
+template <int BITS>
 __device__ inline void wg_sort(int n, uint64_t *k1, uint64_t *k2, uint32_t *pay) {
   const int T = (int)blockDim.x;
   if (n > kRankSortMax || n > T) {  // uniform over the workgroup
@@ -273,21 +283,24 @@ __device__ inline void wg_sort(int n, uint64_t *k1, uint64_t *k2, uint32_t *pay)
     a1 = k1[e]; a2 = k2[e]; ap = pay[e];
     const int per = (n + S - 1) / S;
     const int lo = s * per, hi = lo + per < n ? lo + per : n;
-    // the second key is only looked at where the first ties; four first keys per round of LDS reads
-    auto count = [&](int j, uint64_t b1) {
-      if (b1 < a1) {
-        ++before;
-      } else if (b1 == a1) {
-        const uint64_t b2 = k2[j];
-        before += (b2 < a2 || (b2 == a2 && j < e)) ? 1u : 0u;
+    // 32 bits decide nearly always (64-bit comparisons take four times as long): the whole key, or the upper half of
+    // it.  Everything else is looked at only where those are equal, other than for the entry itself, which every entry
+    // meets (it made nearly every turn of some lane a trip to LDS for the second key: 100 entries took 2.9 us).
+    const uint32_t *w = reinterpret_cast<const uint32_t *>(k1) + (BITS == 64 ? 1 : 0);
+    const uint32_t aw = w[2 * e];
+    auto count = [&](int j, uint32_t bw) {
+      before += bw < aw ? 1u : 0u;
+      if (bw == aw && j != e) {
+        const uint64_t b1 = k1[j], b2 = k2[j];
+        before += (b1 < a1 || (b1 == a1 && (b2 < a2 || (b2 == a2 && j < e)))) ? 1u : 0u;
       }
     };
     int j = lo;
     for (; j + 4 <= hi; j += 4) {
-      const uint64_t b0 = k1[j], b1 = k1[j + 1], b2 = k1[j + 2], b3 = k1[j + 3];
+      const uint32_t b0 = w[2 * j], b1 = w[2 * j + 2], b2 = w[2 * j + 4], b3 = w[2 * j + 6];
       count(j, b0); count(j + 1, b1); count(j + 2, b2); count(j + 3, b3);
     }
-    for (; j < hi; ++j) count(j, k1[j]);
+    for (; j < hi; ++j) count(j, w[2 * j]);
   }
   for (int o = 1; o < S; o <<= 1) before += __shfl_xor(before, o);  // the S lanes of an entry are neighbours in one wavefront
   __syncthreads();  // everybody has read
