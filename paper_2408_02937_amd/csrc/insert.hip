@@ -185,23 +185,41 @@ __device__ inline void note_longest(const Dev &D, uint32_t newlen, uint32_t know
   if ((threadIdx.x & (kWave - 1)) == 0) atomicMax(&D.ctrl->max_len, newlen);
 }
 
-__global__ __launch_bounds__(256) void k_open(Dev D) {
+// `start`, where the fill goes by lists: the new vectors of list l are start[l] .. of the batch in the order of the fill,
+// list after list (which list comes first is as the workgroups arrive, and does not matter).
+__global__ __launch_bounds__(256) void k_open(Dev D, uint32_t *__restrict__ start) {
   __shared__ OpenShared<256> sh;
   const int list = blockIdx.x * blockDim.x + threadIdx.x;
   const bool on = list < D.nlist;
   const uint32_t newlen = on ? D.reserved_len[list] : 0u;
+  if (start) {  // uniform
+    __shared__ uint32_t s_sum[4], s_base;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const uint32_t added = on ? newlen - D.visible_len[list] : 0u;
+    uint32_t upto = added;
+    for (int o = 1; o < kWave; o <<= 1) {
+      const uint32_t x = __shfl_up(upto, o);
+      if (lane >= o) upto += x;
+    }
+    if (lane == kWave - 1) s_sum[wave] = upto;
+    __syncthreads();
+    if (threadIdx.x == 0) s_base = atomicAdd(&D.ctrl->fill_cur, s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3]);
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) upto += s_sum[w];
+    if (on) start[list] = s_base + upto - added;
+  }
   note_longest(D, newlen, D.ctrl->max_len);
   wg_open<256>(D, on ? list : -1, on ? D.nblk[list] : 0u, newlen, sh);
 }
 
 // ---- fill: chunk c (16 bytes: 4 floats, 8 halves or 16 bytes) of a vector, as the lists keep it
-__device__ inline float4 stored_chunk(const Dev &D, const float4 *__restrict__ y, int c) {
-  if (D.storage == 1) {
+__device__ __forceinline__ float4 stored_chunk(int storage, const float4 *__restrict__ y, int c) {
+  if (storage == 1) {
     const float4 a = y[2 * c], e = y[2 * c + 1];
     return make_float4(__uint_as_float(pack_halves(a.x, a.y)), __uint_as_float(pack_halves(a.z, a.w)),
                        __uint_as_float(pack_halves(e.x, e.y)), __uint_as_float(pack_halves(e.z, e.w)));
   }
-  if (D.storage == 2)
+  if (storage == 2)
     return make_float4(__uint_as_float(pack_bytes(y[4 * c])), __uint_as_float(pack_bytes(y[4 * c + 1])),
                        __uint_as_float(pack_bytes(y[4 * c + 2])), __uint_as_float(pack_bytes(y[4 * c + 3])));
   return y[c];
@@ -221,8 +239,68 @@ __global__ __launch_bounds__(256) void k_fill(Dev D, int64_t n, const float *__r
   uint32_t mid = pos / (uint32_t)D.T_m, moff = pos % (uint32_t)D.T_m;
   if (mid >= D.nblk[list]) return;  // the block could not be opened (pool exhausted)
   uint32_t b = (uint32_t)*table_entry(D, list, mid);
-  block_vecs(D, b)[vec_chunk_index(D, moff, c)] = stored_chunk(D, reinterpret_cast<const float4 *>(Y) + i * D.d4, c);
+  block_vecs(D, b)[vec_chunk_index(D, moff, c)] = stored_chunk(D.storage, reinterpret_cast<const float4 *>(Y) + i * D.d4, c);
   if (c == 0) block_ids(D, b)[moff] = ids ? ids[i] : id_base + i;
+}
+
+// ... or, for large batches, list by list.  A vector's chunks lie 1 KiB apart in its group, so a thread's store above is 16
+// bytes of a cache line that belong to it alone, and the vectors of one list, which share those lines, are anywhere in the
+// batch: 65,536 x 768 took 228 us for 400 MB.  So the batch is put in the order of its lists first (k_fill_order: source
+// and place of every vector; ids go out here), and a workgroup takes 64 consecutive ones, 16 chunks of each: 256 bytes
+// of a vector at a time into LDS, and out of it with consecutive places side by side, as many to a cache line as the
+// batch has for the list: 65,536 x 768 into 8,192 lists 124 us behind 7 for the order.
+__global__ __launch_bounds__(256) void k_fill_order(Dev D, int64_t n, const int64_t *__restrict__ ids, int64_t id_base,
+                                                    const int32_t *__restrict__ assign, const uint32_t *__restrict__ did,
+                                                    const uint32_t *__restrict__ start, uint2 *__restrict__ order) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const int list = assign[i];
+  const uint32_t pos = did[i], mid = pos / (uint32_t)D.T_m, moff = pos % (uint32_t)D.T_m;
+  const uint32_t at = start[list] + (pos - D.visible_len[list]);
+  if (at >= (uint32_t)n) return;  // (cannot be: the lists' new vectors are the batch)
+  uint2 to = make_uint2(~0u, 0u);
+  if (mid < D.nblk[list]) {  // (otherwise the block could not be opened: pool exhausted)
+    const uint32_t b = (uint32_t)*table_entry(D, list, mid);
+    to = make_uint2((uint32_t)i, slot_of(D, b, moff));
+    block_ids(D, b)[moff] = ids ? ids[i] : id_base + i;
+  }
+  order[at] = to;
+}
+
+constexpr int kFillSlots = 64, kFillChunks = 16;
+template <int ST>
+__global__ __launch_bounds__(256) void k_fill_lists(Dev D, int64_t n, const float *__restrict__ Y,
+                                                    const uint2 *__restrict__ order) {
+  __shared__ float4 tile[kFillSlots][kFillChunks + 1];  // (the odd row length spreads a column over the banks)
+  __shared__ uint2 s_at[kFillSlots];
+  const int tid = threadIdx.x;
+  const int64_t s0 = (int64_t)blockIdx.x * kFillSlots;
+  const int c0 = (int)blockIdx.y * kFillChunks, chunks = min(kFillChunks, D.vchunks - c0);
+  if (tid < kFillSlots) s_at[tid] = s0 + tid < n ? order[s0 + tid] : make_uint2(~0u, 0u);
+  __syncthreads();
+  {
+    const int c = tid % kFillChunks;
+    float4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint32_t i = s_at[tid / kFillChunks + 16 * u].x;
+      v[u] = i != ~0u && c < chunks ? stored_chunk(ST, reinterpret_cast<const float4 *>(Y) + (size_t)i * D.d4, c0 + c)
+                                    : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) tile[tid / kFillChunks + 16 * u][c] = v[u];
+  }
+  __syncthreads();
+  const int slot = tid & (kFillSlots - 1);
+  const uint2 at = s_at[slot];
+  if (at.x == ~0u) return;
+  const uint32_t b = at.y / (uint32_t)D.T_m, moff = at.y - b * (uint32_t)D.T_m;
+  float4 *to = block_vecs(D, b) + vec_chunk_index(D, moff, c0);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int c = tid / kFillSlots + 4 * u;
+    if (c < chunks) to[(size_t)c * kWave] = tile[slot][c];
+  }
 }
 
 // ---- publish: makes the batch visible and evaluates Exceed() (the equation defining it: vectors appended since the
@@ -272,7 +350,10 @@ __device__ inline void report(const Dev &D, uint32_t call_seq, uint32_t total) {
 __global__ __launch_bounds__(256) void k_publish(Dev D, uint32_t call_seq, uint32_t total) {
   int list = blockIdx.x * blockDim.x + threadIdx.x;
   wg_publish(D, list < D.nlist ? list : -1);
-  if (list == 0) report(D, call_seq, total);
+  if (list == 0) {
+    report(D, call_seq, total);
+    D.ctrl->fill_cur = 0u;
+  }
 }
 
 // ---- a batch of up to kTailVecs vectors behind its coarse scores: one workgroup, a vector to a thread.  The vector
@@ -347,7 +428,7 @@ __global__ __launch_bounds__(kTailVecs) void k_insert_tail(Dev D, int n, int spl
   }
   for (; t < chunks; t += kTailVecs) {
     const int i = t / D.vchunks, c = t - i * D.vchunks;
-    put(t, i, c, stored_chunk(D, y4 + (size_t)i * D.d4, c));
+    put(t, i, c, stored_chunk(D.storage, y4 + (size_t)i * D.d4, c));
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's part of the vectors is out ...
   __syncthreads();                                  // ... and so is everybody's before any list is published
@@ -395,14 +476,35 @@ void launch_reserve_ordered(const Dev &D, int64_t n, const InsertScratch &S, hip
                      S.did);
 }
 
-void launch_open(const Dev &D, hipStream_t s) {
+// The partial minima of the exact coarse kernel have been read when the blocks are opened: their scratch takes the order.
+static uint32_t *fill_start(const InsertScratch &S) { return reinterpret_cast<uint32_t *>(S.pidx); }
+static uint2 *fill_order(const InsertScratch &S) { return reinterpret_cast<uint2 *>(S.pscore); }
+// By lists pays where the moving takes longer than the launch in front of it: from 8,192 vectors, or from 2^18 chunks.
+// Batches back to back, us a batch by vector / by lists: 4,096 x 32 into 4,096 lists 47.2 / 51.1, into 16,384 74.4 / 69.4, 2,048 x
+// 128 into 1,024 39.4 / 41.7, 4,096 x 128 43.7 / 42.1 (into 8 lists 59.7 / 62.4), 2,048 x 768 into 8,192 75.1 / 75.9, 4,096 x 256 into
+// 16,384 107.5 / 100.6, 4,096 x 768 into 8,192 122 / 115, 16,384 x 32 into 4,096 85 / 74, 65,536 x 768 into 8,192 1,377 / 1,101.
+static bool fills_by_lists(const Dev &D, int64_t n, const InsertScratch &S) {
+  return D.pq_m == 0 && (n >= 8192 || (n > kTailVecs && n * D.vchunks >= (int64_t)1 << 18)) &&
+         (size_t)D.nlist <= S.part_cap && (size_t)n <= S.part_cap;
+}
+
+void launch_open(const Dev &D, int64_t n, const InsertScratch &S, hipStream_t s) {
   unsigned grid = (unsigned)((D.nlist + 255) / 256);
-  hipLaunchKernelGGL(k_open, dim3(grid), dim3(256), 0, s, D);
+  hipLaunchKernelGGL(k_open, dim3(grid), dim3(256), 0, s, D, fills_by_lists(D, n, S) ? fill_start(S) : nullptr);
 }
 
 void launch_fill(const Dev &D, int64_t n, const float *Y, const int64_t *ids, int64_t id_base,
                  const InsertScratch &S, hipStream_t s) {
   if (n <= 0) return;
+  if (fills_by_lists(D, n, S)) {
+    hipLaunchKernelGGL(k_fill_order, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, D, n, ids, id_base, S.assign, S.did,
+                       fill_start(S), fill_order(S));
+    const dim3 grid((unsigned)((n + kFillSlots - 1) / kFillSlots), (unsigned)((D.vchunks + kFillChunks - 1) / kFillChunks));
+    if (D.storage == 1) hipLaunchKernelGGL(k_fill_lists<1>, grid, dim3(256), 0, s, D, n, Y, fill_order(S));
+    else if (D.storage == 2) hipLaunchKernelGGL(k_fill_lists<2>, grid, dim3(256), 0, s, D, n, Y, fill_order(S));
+    else hipLaunchKernelGGL(k_fill_lists<0>, grid, dim3(256), 0, s, D, n, Y, fill_order(S));
+    return;
+  }
   int64_t threads = n * D.vchunks;
   unsigned grid = (unsigned)((threads + 255) / 256);
   hipLaunchKernelGGL(k_fill, dim3(grid), dim3(256), 0, s, D, n, Y, ids, id_base, S.assign, S.did);

@@ -738,7 +738,7 @@ int rtams_add(rtams_index *ix, int64_t n, const float *d_vecs, const int64_t *d_
       splits = assign_round(ix, m, Y, true, small, ix->ins.assign, s);
     }
     if (small) launch_insert_tail(D, m, splits, Y, ids, id_base, ix->ins, report, total, s);
-    else launch_open(D, s);
+    else launch_open(D, m, ix->ins, s);
     if (small && tail_fills(D, m)) continue;  // filled and published
     if (D.pq_m > 0) launch_pq_fill(D, m, Y, ids, id_base, ix->ins, s);
     else launch_fill(D, m, Y, ids, id_base, ix->ins, s);

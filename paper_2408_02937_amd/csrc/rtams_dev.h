@@ -51,7 +51,8 @@ struct Ctrl {
   uint32_t max_len;          // longest list, taken where a batch's blocks are opened (a batch dropped for lack of blocks counts)
   int32_t search_error;      // rtams_status raised by a kernel of a search (scratch too small): inserts do not look at it
   CentroidStats cen;
-  uint32_t pad3[20];
+  uint32_t fill_cur;         // vectors of the batch whose lists have their place in the order of the fill (0 between batches)
+  uint32_t pad3[19];
 };
 
 // Words the device writes straight into pinned host memory, so the host can
