@@ -190,8 +190,9 @@ int rtams_search(rtams_index *ix, int64_t nq, const float *d_queries, int32_t k,
                  float *d_out_dist, int64_t *d_out_ids, void *hip_stream);
 
 /* rtams_search for callers that cannot allocate and have no scratch of their own to hand over: code under
- * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same answers,
- * same kernels; the request's scratch is not a slice of the caller's d_scratch but an array in the device
+ * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same answers, (but for small
+ * requests, which it plans like all others) the same kernels; the request's scratch is not a slice
+ * of the caller's d_scratch but an array in the device
  * image of this library (32 MiB on every GPU the library runs on, held until the process ends; its
  * address on the index's device is looked up once, in rtams_create).  Neither this call nor anything it
  * launches allocates or frees memory.  Limits: nq at most 64 (EINVAL beyond; also EINVAL when the fixed
@@ -301,6 +302,10 @@ int rtams_list_export_codes(rtams_index *ix, int32_t list, int64_t cap, int64_t 
  *   "scan_steal"           1 (default): in such a long scan on the matrix cores, a die that has run out
  *                          of its share of the work items takes items from the back of another die's
  *                          share; 0: every die scans its own share only.  The result is the same.
+ *   "small_requests"       1 (default): a small request over flat lists (few queries, 32 to 4,096 lists,
+ *                          at most 64 probes and some 32 MB of lists in all) runs in three launches that
+ *                          make no plan of the scan; 0: in five like every other.  The result is the
+ *                          same.
  *   "use_mfma"             whether approximate coarse scores from the matrix cores filter the
  *                          centroids before the exact arithmetic decides: 0 never, 1 for batches large
  *                          enough to repay it (default), 2 for every batch of 32 rows or more.

@@ -1,0 +1,249 @@
+// The pruning bound of a query, set by one workgroup.
+#pragma once
+#include "search_common.h"
+
+namespace rtams {
+
+// ------------------------------------------------------------- pruning bound
+constexpr int kSampleMax = 4096;  // candidates the bound of a query is taken from, at most
+#ifndef RTAMS_SAMPLE_DIVISOR
+#define RTAMS_SAMPLE_DIVISOR 4
+#endif
+constexpr int kSampleDivisor = RTAMS_SAMPLE_DIVISOR;
+constexpr int kNoBoundBelow = 4096;  // candidates of a query up to which the scan keeps them all
+
+// The scan writes nothing for a candidate that cannot be among the k best of
+// its query: before it starts, every query gets a BOUND, the k-th best score
+// of a sample of its candidates (the first few groups of its nearest probed
+// lists, where most of its neighbours are).  The k-th best of any k or more
+// candidates cannot be better than the final k-th best, so keeping what is not
+// worse than the bound loses nothing.  One workgroup per query: a wavefront per
+// group of 64 vectors, lane = vector, scores to LDS, radix selection there.
+// These workgroups run beside the one that groups the pairs (same launch): both
+// need only the plan, and the scan needs both.
+// What the sample needs of the nearest list, read ahead by the caller (every one of these is a round
+// trip to memory, and read where they are used they would follow one another): the list, its
+// length, its number of blocks, and where the table segment of this wavefront's first group starts.
+struct NearestList {
+  int list;
+  uint32_t len, nblk;
+  int32_t dir;
+};
+
+template <int METRIC, int ST>
+__device__ void sample_scores(const Dev &D, int nprobe, int max_nprobe, int q, uint32_t want_groups,
+                              const float *__restrict__ Q, const SearchScratch &S, const float4 *qv,
+                              uint32_t *skey, const NearestList &first) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int d4 = D.vchunks;  // 16-byte chunks of a stored vector
+  constexpr int kPieces = pieces_of(ST);  // float4s of the query that go with a chunk
+  const uint32_t gpb = (uint32_t)D.groups_per_block;
+  const size_t group_stride = (size_t)d4 * kWave;
+  // the sample is the first want_groups groups of the probed lists taken in order, nearest first
+  uint32_t g_first = 0;  // groups of the lists before list p
+  for (int p = 0; p < nprobe && g_first < want_groups; ++p) {  // uniform over the workgroup
+    const size_t o = (size_t)q * max_nprobe + p;
+    const int list = p == 0 ? first.list : S.probe_list[o];
+    const uint32_t len = p == 0 ? first.len : S.probe_len[o];
+    uint32_t groups = (len + kWave - 1) / kWave;
+    const uint32_t have = (p == 0 ? first.nblk : D.nblk[list]) * gpb;  // never index the block table past the chain
+    if (groups > have) groups = have;
+    if (groups > want_groups - g_first) groups = want_groups - g_first;
+    for (uint32_t g = (uint32_t)wave; g < groups; g += blockDim.x / kWave) {
+      const uint32_t b = p == 0 && g == (uint32_t)wave ? (uint32_t)*table_entry_at(D, first.dir, g / gpb)
+                                                       : (uint32_t)*table_entry(D, list, g / gpb);
+      const float4 *__restrict__ x = block_vecs(D, b) + (size_t)(g % gpb) * group_stride + lane;
+      float acc = 0.f;
+      int c = 0;
+      if (METRIC == 1 && D.scan_mfma) {
+        // inner products on the matrix cores, exactly as the scan computes them (same
+        // instruction, same order of the coordinates), so that a candidate's score here and there is
+        // the same bits: every lane offers the one query, component l % 4 of the result is the score
+        // of the lane's own vector
+        MfmaAcc m = {0.f, 0.f, 0.f, 0.f};
+        if (ST == 0)
+          for (; c + 16 <= d4; c += 16) {
+            float4 v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) v[u] = x[(size_t)(c + u) * kWave];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) mfma_chunk(m, v[u], qv[c + u]);
+          }
+        for (; c + 8 <= d4; c += 8) {
+          float4 v[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) v[u] = x[(size_t)(c + u) * kWave];
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int s = 0; s < kPieces; ++s) mfma_chunk(m, chunk_piece<ST>(v[u], s), qv[(c + u) * kPieces + s]);
+        }
+        for (; c < d4; ++c) {
+          const float4 v = x[(size_t)c * kWave];
+#pragma unroll
+          for (int s = 0; s < kPieces; ++s) mfma_chunk(m, chunk_piece<ST>(v, s), qv[c * kPieces + s]);
+        }
+        const int r = lane & 3;
+        acc = r == 0 ? m[0] : r == 1 ? m[1] : r == 2 ? m[2] : m[3];
+      }
+      // loads of 1 KiB in flight per wavefront: sixteen, then eight, then one at a time (the workgroup
+      // is alone on its CU and a group is a chain of such round trips)
+      if (ST == 0) {
+        for (; c + 16 <= d4; c += 16) {
+          float4 v[16];
+#pragma unroll
+          for (int u = 0; u < 16; ++u) v[u] = x[(size_t)(c + u) * kWave];
+#pragma unroll
+          for (int u = 0; u < 16; ++u) accumulate<METRIC>(acc, v[u], qv[c + u]);
+        }
+      }
+      for (; c + 8 <= d4; c += 8) {
+        float4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = x[(size_t)(c + u) * kWave];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+          for (int s = 0; s < kPieces; ++s) accumulate<METRIC>(acc, chunk_piece<ST>(v[u], s), qv[(c + u) * kPieces + s]);
+      }
+      for (; c < d4; ++c) {
+        const float4 v = x[(size_t)c * kWave];
+#pragma unroll
+        for (int s = 0; s < kPieces; ++s) accumulate<METRIC>(acc, chunk_piece<ST>(v, s), qv[c * kPieces + s]);
+      }
+      const uint32_t v = g * kWave + lane;
+      skey[(size_t)(g_first + g) * kWave + lane] =
+          v < len ? key_of_float((METRIC == 0 ? acc : -acc) + 0.0f) : 0xFFFFFFFFu;
+    }
+    g_first += groups;
+  }
+  // groups the lists did not have stay at the worst key (set by the caller)
+}
+
+// The same sample over product-quantiser codes: a vector's score is the sum, in the order of the
+// sub-spaces, of the request's table entries that its codes name (the table stays in global
+// memory here: a few thousand look-ups per query).
+__device__ void pq_sample_scores(const Dev &D, int nprobe, int max_nprobe, int q, uint32_t want_groups,
+                                 const SearchScratch &S, uint32_t *skey) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int words = D.pq_m / 4;
+  const float *lut = S.lut + (size_t)q * D.pq_m * 256;
+  const uint32_t gpb = (uint32_t)D.groups_per_block;
+  uint32_t g_first = 0;
+  for (int p = 0; p < nprobe && g_first < want_groups; ++p) {  // uniform over the workgroup
+    const size_t o = (size_t)q * max_nprobe + p;
+    const int list = S.probe_list[o];
+    const uint32_t len = S.probe_len[o];
+    uint32_t groups = (len + kWave - 1) / kWave;
+    const uint32_t have = D.nblk[list] * gpb;  // never index the block table past the chain
+    if (groups > have) groups = have;
+    if (groups > want_groups - g_first) groups = want_groups - g_first;
+    for (uint32_t g = (uint32_t)wave; g < groups; g += blockDim.x / kWave) {
+      const uint32_t b = (uint32_t)*table_entry(D, list, g / gpb);
+      const uint32_t *__restrict__ x = block_codes(D, b) + (size_t)(g % gpb) * words * kWave + lane;
+      float acc = 0.f;
+      for (int c = 0; c < words; ++c) {
+        const uint32_t w = x[(size_t)c * kWave];
+        const float *t = lut + (size_t)c * 4 * 256;
+        acc += t[w & 255u];
+        acc += t[256 + ((w >> 8) & 255u)];
+        acc += t[512 + ((w >> 16) & 255u)];
+        acc += t[768 + (w >> 24)];
+      }
+      const uint32_t v = g * kWave + lane;
+      skey[(size_t)(g_first + g) * kWave + lane] =
+          v < len ? key_of_float((D.metric == 0 ? acc : -acc) + 0.0f) : 0xFFFFFFFFu;
+    }
+    g_first += groups;
+  }
+}
+
+// LDS of a bound: the query (d <= 2048) and the keys of the sample.  The caller owns it, so that a
+// kernel whose workgroups do different jobs can use the same bytes for each.
+constexpr size_t kBoundLdsBytes = 512 * sizeof(float4) + kSampleMax * sizeof(uint32_t);
+
+template <bool PQ>
+__device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, int k, const float *__restrict__ Q,
+                             const SearchScratch &S, unsigned char *lds) {
+  float4 *qv = reinterpret_cast<float4 *>(lds);
+  uint32_t *skey = reinterpret_cast<uint32_t *>(lds + 512 * sizeof(float4));
+  __shared__ __attribute__((aligned(8))) uint32_t hist[kSelectLdsWords];
+  __shared__ uint32_t bc[4];
+  const int tid = threadIdx.x;
+  // what decides how the workgroup goes on, all on its way at once
+  const size_t o0 = (size_t)q * max_nprobe;
+  const uint32_t qtotal = S.qtotal[q];
+  NearestList first{PQ ? 0 : S.probe_list[o0], S.probe_len[o0], 0u, 0};
+  // |q|^2 for the norm form of the squared distance (the first wavefront computes it, in double)
+  const bool norm_form = !PQ && uses_norm_form(D);
+  __shared__ float s_qn;
+  if (norm_form && tid < kWave) {
+    double a = 0.0;
+    for (int c = tid; c < D.d; c += kWave) {
+      const double v = (double)Q[(size_t)q * D.d + c];
+      a = __builtin_fma(v, v, a);
+    }
+    for (int o = kWave / 2; o > 0; o >>= 1) a += __shfl_xor(a, o);
+    if (tid == 0) { s_qn = (float)a; S.qnorm[q] = (float)a; }
+  }
+  // A query with no more candidates than the selection holds in LDS at once needs no bound.  For
+  // inner products neither does one whose records cost less than a sample would: the sample is 512
+  // vectors or more read by one workgroup (80 us at d = 768), a record is 8 bytes (short lists, wide
+  // vectors).  (For L2 the bound also lets the scan stop early, which is worth the sample.)
+  const uint32_t no_bound_below =
+      D.metric == 0 ? (uint32_t)kNoBoundBelow : max((uint32_t)kNoBoundBelow, 32u * (uint32_t)D.d);
+  if (qtotal <= no_bound_below) {  // uniform over the workgroup
+    if (tid == 0) {
+      S.bound[q] = 0xFFFFFFFFu;
+      *rec_count(S, (uint32_t)q) = 0u;
+    }
+    return;
+  }
+  // sample size: 4 k, at least 512 and at least a fraction of the nearest list (the longer that
+  // list, the more candidates a given score admits), at most kSampleMax and at most 1 MiB of
+  // vectors (one workgroup reads the sample: a hot list of wide vectors would hold up the scan),
+  // in whole groups
+  uint32_t cap = PQ ? (uint32_t)kSampleMax : ((1u << 20) / ((uint32_t)D.vchunks * 16u)) & ~(uint32_t)(kWave - 1);
+  cap = cap < 512u ? 512u : (cap > (uint32_t)kSampleMax ? (uint32_t)kSampleMax : cap);
+  uint32_t want = (uint32_t)k * 4u;
+  const uint32_t part = first.len / (uint32_t)kSampleDivisor;
+  if (!PQ) {  // on their way while the query and the keys are set up
+    first.nblk = D.nblk[first.list];
+    first.dir = table_dir(D, first.list, (uint32_t)(tid / kWave) / (uint32_t)D.groups_per_block);
+  }
+  want = want < part ? part : want;
+  want = want < 512u ? 512u : (want > cap ? cap : want);
+  const uint32_t want_groups = (want + kWave - 1) / kWave;
+  if (!PQ)
+    for (int c = tid; c < D.d4; c += (int)blockDim.x) qv[c] = reinterpret_cast<const float4 *>(Q + (size_t)q * D.d)[c];
+  for (int i = tid; i < (int)(want_groups * kWave); i += (int)blockDim.x) skey[i] = 0xFFFFFFFFu;
+  __syncthreads();
+  if (PQ) pq_sample_scores(D, nprobe, max_nprobe, q, want_groups, S, skey);
+  else if (D.metric == 0) {
+    if (D.storage == 1) sample_scores<0, 1>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, first);
+    else if (D.storage == 2) sample_scores<0, 2>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, first);
+    else sample_scores<0, 0>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, first);
+  } else {
+    if (D.storage == 1) sample_scores<1, 1>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, first);
+    else if (D.storage == 2) sample_scores<1, 2>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, first);
+    else sample_scores<1, 0>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, first);
+  }
+  __syncthreads();
+  // k-th smallest key of the sample; with fewer than k candidates in it, it is the worst key
+  // and everything is kept
+  uint32_t bound = 0xFFFFFFFFu;
+  if ((uint32_t)k <= want_groups * kWave) {
+    const SelectResult r = wg_radix_select<32>(
+        (int)(want_groups * kWave), (uint32_t)k, [&](int i, uint64_t &kv) { kv = skey[i]; return true; }, hist, bc,
+        (uint32_t)(k + k / 16));
+    bound = (uint32_t)r.T;  // the k-th smallest key, or an upper bound of it that admits the same candidates
+  }
+  if (tid == 0) {
+    // the sample's scores are direct-form ones; the scan may compare norm-form scores with the bound
+    if (norm_form) bound = loosened_key(bound, norm_form_slack(D.d), s_qn);
+    S.bound[q] = bound;
+    *rec_count(S, (uint32_t)q) = 0u;
+  }
+}
+
+}  // namespace rtams

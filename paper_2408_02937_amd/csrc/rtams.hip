@@ -3,6 +3,7 @@
 #include "../../include/rtams.h"
 #include "../../include/rtams_measure.h"
 
+#include <algorithm>
 #include <atomic>
 #include <cstdarg>
 #include <cstdio>
@@ -265,6 +266,7 @@ struct rtams_index {
   std::atomic<int64_t> ordered_add{0};  // positions inside a list in the order of the batch instead of arrival order
   std::atomic<int64_t> use_mfma{1};  // matrix-core filter in front of the exact coarse arithmetic
   std::atomic<int64_t> scan_mfma{1}; // flat lists: the scan's dot products on the matrix cores
+  std::atomic<int64_t> small_requests{1};  // small requests in three launches, without a plan (0: like all others)
   std::atomic<int64_t> scan_byte_weight{0};
   std::atomic<int64_t> scan_min_choice{-1};
   // Scans of LONG requests run one after the other, whatever streams they are on: such a scan fills the
@@ -296,12 +298,17 @@ int plan_words(const rtams_index *ix) {
                sizeof(ScanQueues) / 4);
 }
 
+// Whether the probes of nq queries are chosen behind the matrix-core filter.
+bool searches_by_filter(const rtams_index *ix, int64_t nq) {
+  const int64_t mode = ix->use_mfma.load(std::memory_order_relaxed);  // 0 never, 1 when it pays, 2 from 32 rows
+  return mode == 2 ? nq >= 32 : mode == 1 && mfma_pays_for_search(nq, ix->dev.nlist);
+}
+
 // Coarse scores of the queries, probe selection and the plan of the scan.
 void coarse_and_plan(rtams_index *ix, int64_t nq, const float *Q, int nprobe, const SearchScratch &S,
                      int32_t *probe_out, hipStream_t s) {
   const Dev &D = ix->dev;
-  const int64_t mode = ix->use_mfma.load(std::memory_order_relaxed);  // 0 never, 1 when it pays, 2 from 32 rows
-  const bool mfma = mode == 2 ? nq >= 32 : mode == 1 && mfma_pays_for_search(nq, D.nlist);
+  const bool mfma = searches_by_filter(ix, nq);
   if (mfma) launch_coarse_mfma(D, nq, Q, S.qhalf, S.approx, S.cursor, S.list_cnt, plan_words(ix), s);
   else launch_coarse_scores(D, nq, Q, S.scores, S.cursor, S.list_cnt, plan_words(ix), s);
   launch_probe_plan(D, nq, nprobe, ix->cfg.max_nprobe, S, Q, mfma, probe_out, s);
@@ -578,6 +585,7 @@ int rtams_create(const rtams_config *cfg, rtams_index **out) {
     const bool lines = cfg->nlist >= 16;  // a query's row of scores holds a cache line
     S.rec_cnt = reinterpret_cast<uint32_t *>(p + (lines ? SL.scores : SL.rec_cnt));
     S.rec_shift = lines ? 5 : 0;
+    S.small_count = reinterpret_cast<uint32_t *>(p + SL.rec_cnt);  // (free where the counters have lines; small requests need 32 lists)
     S.cursor = reinterpret_cast<unsigned long long *>(p + SL.cursor);
     S.list_cnt = reinterpret_cast<uint32_t *>(p + SL.list_cnt);
     S.pair_start = reinterpret_cast<uint32_t *>(p + SL.pair_start);
@@ -599,7 +607,10 @@ int rtams_create(const rtams_config *cfg, rtams_index **out) {
     S.req_chunk = reinterpret_cast<uint32_t *>(p + SL.req_words);
     S.req_done = S.req_chunk + 1;
     S.req_cursor = reinterpret_cast<unsigned long long *>(p + SL.req_words + 8);
-    if (hipMemset(p + SL.req_words, 0, 16) != hipSuccess) return fail(RTAMS_EHIP, "hipMemset of the scratch failed");
+    // the request's words, and in front of them what a small request expects to be zero (the static array, which may be in use
+    // by another index, takes no small requests)
+    const size_t zero = with_reserve ? SL.rec_cnt : SL.req_words;
+    if (hipMemset(p + zero, 0, SL.req_words + 16 - zero) != hipSuccess) return fail(RTAMS_EHIP, "hipMemset of the scratch failed");
     if (hipEventCreateWithFlags(&R.done, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&R.scan_done, hipEventDisableTiming) != hipSuccess ||
         hipEventCreate(&R.t0) != hipSuccess || hipEventCreate(&R.t1) != hipSuccess)
@@ -773,6 +784,18 @@ static int check_search_args(rtams_index *ix, int64_t nq, const float *d_queries
   return RTAMS_OK;
 }
 
+// The selection of a request whose scan is enqueued, and the end of the request.
+static int finish_search(rtams_index *ix, const Dev &D, const SearchScratch &S, int r, int64_t nq, const float *d_queries, int32_t k, int32_t nprobe,
+                         float *d_out_dist, int64_t *d_out_ids, hipStream_t s) {
+  launch_select(D, nq, k, nprobe, ix->cfg.max_nprobe, d_queries, S, d_out_dist, d_out_ids, s);
+  hipError_t e = hipGetLastError();
+  hipError_t e2 = hipEventRecord(ix->res[r].done, s);
+  ix->res[r].state.store(RES_PENDING, std::memory_order_release);
+  if (e != hipSuccess || e2 != hipSuccess)
+    return fail(RTAMS_EHIP, "search launch failed: %s", hipGetErrorString(e != hipSuccess ? e : e2));
+  return RTAMS_OK;
+}
+
 static int search_on(rtams_index *ix, int r, int64_t nq, const float *d_queries, int32_t k, int32_t nprobe,
                      float *d_out_dist, int64_t *d_out_ids, void *hip_stream) {
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
@@ -800,6 +823,26 @@ static int search_on(rtams_index *ix, int r, int64_t nq, const float *d_queries,
   const SearchScratch &S = ix->res[r].s;
   // a rearrangement is switching block tables: start behind its last switch
   if (ix->fence_cur) (void)hipStreamWaitEvent(s, ix->fence_cur, 0);
+  // A small request goes without a plan.  (Not in a recorded request, whose lists may have any length when it runs, and not on
+  // the library's static array, where another index may leave anything between two requests.)
+  const int64_t longest = longest_list_bound(ix);
+  const bool small = !recorded && r < ix->n_res && ix->small_requests.load(std::memory_order_relaxed) != 0 &&
+                     !searches_by_filter(ix, nq) && small_request(D, nq, nprobe, ix->ntotal_host / ix->cfg.nlist + 1, longest);
+  if (small) {
+    const int64_t size = D.scan_single ? kWave : 2 * kWave;
+    const int64_t units = std::min(ix->ntotal_host / size + nprobe, nprobe * (longest / size + 1));
+    const int64_t usual = nprobe * (avg_groups * kWave / size + 1) * 5 / 4 + longest / size;
+    // the survivor counters lie in the room of the approximate scores: that of the exact ones is in use while the bounds are set
+    SearchScratch own = S;
+    own.rec_cnt = reinterpret_cast<uint32_t *>(S.approx);
+    launch_small_front(D, nq, nprobe, ix->cfg.max_nprobe, k, d_queries, own, s);
+    const bool timed = ix->profile_scan.load(std::memory_order_relaxed) != 0;
+    if (timed) ix->timed_scans[0].fetch_add(1, std::memory_order_relaxed);
+    if (timed) (void)hipEventRecord(ix->res[r].t0, s);
+    launch_scan_small(D, nq, nprobe, ix->cfg.max_nprobe, std::min(units, usual), d_queries, own, s);
+    if (timed) { (void)hipEventRecord(ix->res[r].t1, s); ix->res[r].timed = true; }
+    return finish_search(ix, D, own, r, nq, d_queries, k, nprobe, d_out_dist, d_out_ids, s);
+  }
   coarse_and_plan(ix, nq, d_queries, nprobe, S, nullptr, s);
   // The grouped scan is cut into work items of bounded size, one wavefront each;
   // the budget of items grows with the request so that a small batch still
@@ -842,13 +885,7 @@ static int search_on(rtams_index *ix, int r, int64_t nq, const float *d_queries,
     launch_scan(D, nq, nprobe, ix->cfg.max_nprobe, d_queries, (int)budget, S, s);
     if (timed) { (void)hipEventRecord(ix->res[r].t1, s); ix->res[r].timed = true; }
   }
-  launch_select(D, nq, k, nprobe, ix->cfg.max_nprobe, d_queries, S, d_out_dist, d_out_ids, s);
-  hipError_t e = hipGetLastError();
-  hipError_t e2 = hipEventRecord(ix->res[r].done, s);
-  ix->res[r].state.store(RES_PENDING, std::memory_order_release);
-  if (e != hipSuccess || e2 != hipSuccess)
-    return fail(RTAMS_EHIP, "search launch failed: %s", hipGetErrorString(e != hipSuccess ? e : e2));
-  return RTAMS_OK;
+  return finish_search(ix, D, S, r, nq, d_queries, k, nprobe, d_out_dist, d_out_ids, s);
 }
 
 int rtams_search(rtams_index *ix, int64_t nq, const float *d_queries, int32_t k, int32_t nprobe,
@@ -1217,6 +1254,7 @@ int rtams_set_param(rtams_index *ix, const char *key, int64_t value) {
   if (!strcmp(key, "scan_steal")) { ix->scan_steal = value != 0; return RTAMS_OK; }
   if (!strcmp(key, "scan_exclusive_bytes")) { ix->scan_exclusive_bytes = value > 0 ? value : 0; return RTAMS_OK; }
   if (!strcmp(key, "scan_min_choice")) { ix->scan_min_choice = value < 0 ? -1 : value > 7 ? 7 : value; return RTAMS_OK; }
+  if (!strcmp(key, "small_requests")) { ix->small_requests = value != 0; return RTAMS_OK; }
   if (!strcmp(key, "scan_byte_weight")) { ix->scan_byte_weight = value > 0 ? value : 0; return RTAMS_OK; }
   if (!strcmp(key, "scan_max_items")) { ix->scan_max_items = value > 1024 ? value : 1024; return RTAMS_OK; }
   if (!strcmp(key, "scan_items_per_pair")) { ix->scan_items_per_pair = value > 0 ? value : 1; return RTAMS_OK; }

@@ -33,6 +33,7 @@ struct SearchScratch {
   uint32_t *bound;      // [max_batch] key of the score the scan compares with
   float *qnorm;         // [max_batch] squared norms of the queries (norm form of the squared distance)
   u32x4 *qhalf;         // the queries as halves for the matrix-core coarse scores, then their RowMeta (coarse_mfma.hip)
+  uint32_t *small_count; // [max_batch] workgroups of a query's coarse scores that are done (small.hip; 0 between requests)
   uint32_t *rec_cnt;    // survivors recorded so far, of query q at rec_cnt[q << rec_shift] (rec_count())
   int rec_shift;
   unsigned long long *cursor; // bump pointer into the survivor records
@@ -127,6 +128,7 @@ struct RearrangeScratch {
 // coarse.hip ---------------------------------------------------------------
 int coarse_vt(int d);                      // vectors per workgroup for this dimension
 int coarse_splits(const Dev &D, int64_t n, size_t part_cap);
+int coarse_vectors(const Dev &D, int64_t n);  // vectors of a workgroup's tile for this batch
 // full score matrix scores[n][nlist]
 void launch_coarse_scores(const Dev &D, int64_t n, const float *Y, double *scores,
                           unsigned long long *cursor_to_clear, uint32_t *zero, int zero_n, hipStream_t s);
@@ -202,6 +204,14 @@ void launch_scan_mm(const Dev &D, const ScanShape &sh, int max_nprobe, const flo
 // the scan over product-quantiser codes (launch_scan hands quantised lists on to it)
 void launch_pq_scan(const Dev &D, int64_t nq, int nprobe, int max_nprobe, int item_budget,
                     const SearchScratch &S, hipStream_t s);
+// a small request over flat lists (small.hip): coarse scores, probes and bounds; then the scan, `units` (of one or two groups)
+// at most to a query's lists as far as the host knows; launch_select follows
+constexpr double kSmallBytes = 32e6;
+bool small_request(const Dev &D, int64_t nq, int nprobe, int64_t avg_len, int64_t longest);
+void launch_small_front(const Dev &D, int64_t nq, int nprobe, int max_nprobe, int k, const float *Q, const SearchScratch &S,
+                        hipStream_t s);
+void launch_scan_small(const Dev &D, int64_t nq, int nprobe, int max_nprobe, int64_t units, const float *Q,
+                       const SearchScratch &S, hipStream_t s);
 void launch_select(const Dev &D, int64_t nq, int k, int nprobe, int max_nprobe, const float *Q,
                    const SearchScratch &S, float *out_dist, int64_t *out_ids, hipStream_t s);
 

@@ -506,6 +506,7 @@ __global__ __launch_bounds__(kTopkThreads, 4) void k_select(Dev D, int k, int np
       out_ids[o] = -1;
     }
   }
+  if (blockIdx.x == 0 && threadIdx.x == 0) *S.cursor = 0ull;  // the next request on this slice finds its records' room free
   // the records are not looked at any more (the selection ended with a barrier)
   if (threadIdx.x == 0) overflow_request_done(S, gridDim.x);
 }

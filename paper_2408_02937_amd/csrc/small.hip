@@ -1,0 +1,105 @@
+// A small request over flat lists in three launches instead of five: coarse scores, probes and bound in one kernel, a scan
+// that finds its own work, the selection.
+//
+// What bounds such a request is the chain of its launches, each with a start and an end of two microseconds and a few trips
+// to memory before it has what the one before it left behind, and the plan: pairs counted and grouped by list, work items
+// cut and shared out by one workgroup, which a request whose pairs hardly share a list does not get back.  Here the last
+// workgroup of a query's coarse scores goes on with its probes and its bound, and the wavefronts of the scan take the
+// groups of the query's lists in turn from the lengths alone.
+// 10 queries x 8 probes over 100 lists of 100 x 32 floats: 31.6 us back to back where the five launches took 42.7; one
+// query x 32 probes over 1,000 lists of 1,000 x 128: 45.7 and 47.3.  Above kSmallBytes, where the scan's own time hides the
+// plan, and with lists that several queries share, the plan is repaid.
+#include "bound.h"
+#include "coarse_exact.h"
+#include "probe_plan.h"
+#include "scan_item.h"
+
+namespace rtams {
+
+constexpr int kSmallThreads = 512;  // eight wavefronts: the bound's sample of 512 vectors in one turn
+
+template <int METRIC, int MINE>
+__global__ __launch_bounds__(kSmallThreads) void k_small_front(Dev D, int64_t nq, int nprobe, int max_nprobe, int k,
+                                                               const float *__restrict__ Q, int splits, SearchScratch S) {
+  // (the probes' keys, then the bound's query and sample)
+  __shared__ __attribute__((aligned(16))) unsigned char s_raw[kBoundLdsBytes];
+  static_assert(sizeof(ProbeShared<false>) <= kBoundLdsBytes, "the probes share the bound's LDS");
+  __shared__ uint32_t s_last;
+  const int q = blockIdx.x;
+  coarse_tile<METRIC, 1, 1, false, true, kSmallThreads>(D, nq, Q, splits, S.scores, nullptr, nullptr, nullptr, nullptr, 0);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's scores are out ...
+  __syncthreads();                                  // ... and so are everybody's before the workgroup counts itself off
+  if (splits > 1) {  // uniform
+    if (threadIdx.x == 0) {
+      s_last = atomicAdd(&S.small_count[q], 1u) + 1u == (uint32_t)splits;
+      if (s_last) S.small_count[q] = 0u;  // for the next request
+    }
+    __syncthreads();
+    if (!s_last) return;  // uniform: the last one goes on
+  }
+  probe_plan<false, MINE, true>(D, nq, q, nprobe, max_nprobe, S, Q, nullptr, *reinterpret_cast<ProbeShared<false> *>(s_raw));
+  __syncthreads();  // the plan is read below by other threads, and its LDS is used again
+  sample_bound<false>(D, q, nprobe, max_nprobe, k, Q, S, s_raw);
+}
+
+// Workgroup `part` of the `parts` of query q: its wavefronts take every (parts x wavefronts)-th unit of G groups of the
+// query's lists, counted list after list.  At most 64 probes, a lane to each.
+template <int METRIC, int ST, int G, int P>
+__global__ __launch_bounds__(kScanWaves * kWave) void k_scan_small(Dev D, int nprobe, int max_nprobe, int parts,
+                                                                   const float *__restrict__ Q, SearchScratch S) {
+  extern __shared__ float4 qs_small[];  // [wavefronts][d / 4]
+  const int lane = threadIdx.x & (kWave - 1);
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave), waves = blockDim.x / kWave;
+  const uint32_t q = blockIdx.x / (uint32_t)parts, part = blockIdx.x % (uint32_t)parts;
+  float4 *qs = qs_small + (size_t)wave * D.d4;
+  const size_t o = (size_t)q * max_nprobe + min(lane, nprobe - 1);
+  const int my_list = S.probe_list[o];
+  const uint32_t my_len = S.probe_len[o];
+  const uint32_t have = D.nblk[my_list] * (uint32_t)D.groups_per_block;  // never past the list's chain
+  const uint32_t units = lane < nprobe ? (min((my_len + kWave - 1) / kWave, have) + G - 1) / G : 0u;
+  uint32_t upto = units;
+  for (int d = 1; d < kWave; d <<= 1) {
+    const uint32_t x = __shfl_up(upto, d);
+    if (lane >= d) upto += x;
+  }
+  const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)upto, kWave - 1);
+  const uint32_t first = units ? upto - units : ~0u;  // the lane's probe starts at this unit
+  for (uint32_t u = part * waves + wave; u < total; u += (uint32_t)parts * waves) {  // uniform over the wavefront
+    const int p = 63 - __clzll((long long)__ballot(first <= u));  // the last probe that starts at or before u
+    const uint32_t g = (u - (uint32_t)__builtin_amdgcn_readlane((int)first, p)) * G;
+    scan_item<METRIC, 1, ST, G, P>(D, S, Q, max_nprobe, __builtin_amdgcn_readlane(my_list, p), q << 10 | (uint32_t)p, g, G, qs);
+  }
+}
+
+bool small_request(const Dev &D, int64_t nq, int nprobe, int64_t avg_len, int64_t longest) {
+  if (D.pq_m > 0 || D.scan_mfma || D.nlist < 32 || D.nlist > 4096 || nprobe > kWave || coarse_vectors(D, nq) != 1) return false;
+  // every query reads its lists for itself
+  return (double)nq * (double)(nprobe * avg_len + longest) * D.vchunks * 16.0 <= kSmallBytes;
+}
+
+void launch_small_front(const Dev &D, int64_t nq, int nprobe, int max_nprobe, int k, const float *Q, const SearchScratch &S,
+                        hipStream_t s) {
+  const int splits = (D.nlist + kSmallThreads - 1) / kSmallThreads;  // a centroid to a thread
+  typedef void (*Kernel)(Dev, int64_t, int, int, int, const float *, int, SearchScratch);
+  static const Kernel kernels[2][3] = {{k_small_front<0, 2>, k_small_front<0, 4>, k_small_front<0, 8>},
+                                       {k_small_front<1, 2>, k_small_front<1, 4>, k_small_front<1, 8>}};
+  hipLaunchKernelGGL(kernels[D.metric][splits <= 2 ? 0 : splits <= 4 ? 1 : 2], dim3((unsigned)nq, (unsigned)splits),
+                     dim3(kSmallThreads), (size_t)D.d * sizeof(double), s, D, nq, nprobe, max_nprobe, k, Q, splits, S);
+}
+
+void launch_scan_small(const Dev &D, int64_t nq, int nprobe, int max_nprobe, int64_t units, const float *Q,
+                       const SearchScratch &S, hipStream_t s) {
+  // a unit to a wavefront while the chip has room for them, by what a query's lists may come to
+  int64_t parts = (units + kScanWaves - 1) / kScanWaves;
+  const int64_t most = (1024 + nq - 1) / nq;
+  parts = parts < 1 ? 1 : parts > most ? most : parts;
+  typedef void (*Kernel)(Dev, int, int, int, const float *, SearchScratch);
+  static const Kernel pairs[2][3] = {{k_scan_small<0, 0, 2, 2>, k_scan_small<0, 1, 2, 2>, k_scan_small<0, 2, 2, 2>},
+                                     {k_scan_small<1, 0, 2, 2>, k_scan_small<1, 1, 2, 2>, k_scan_small<1, 2, 2, 2>}};
+  static const Kernel singles[2][3] = {{k_scan_small<0, 0, 1, 4>, k_scan_small<0, 1, 1, 4>, k_scan_small<0, 2, 1, 4>},
+                                       {k_scan_small<1, 0, 1, 4>, k_scan_small<1, 1, 1, 4>, k_scan_small<1, 2, 1, 4>}};
+  hipLaunchKernelGGL(D.scan_single ? singles[D.metric][D.storage] : pairs[D.metric][D.storage], dim3((unsigned)(nq * parts)),
+                     dim3(kScanWaves * kWave), (size_t)kScanWaves * D.d * sizeof(float), s, D, nprobe, max_nprobe, (int)parts, Q, S);
+}
+
+}  // namespace rtams
