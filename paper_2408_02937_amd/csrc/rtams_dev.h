@@ -76,7 +76,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 struct Dev {
   int32_t d, nlist, metric, T_m;
   int32_t pq_m;             // 0: flat lists; M > 0: product-quantiser codes, M bytes per vector
-  int32_t scan_mfma;        // flat lists: the scan's dot products run on the matrix cores (set per request)
+  int32_t scan_mfma;        // flat lists: the scan's dot products run on the matrix cores, 2: on the 16-bit instructions (set per request)
   int32_t scan_single;      // a request of few groups of vectors in short lists: the vector-unit scan takes them one at a time (set per request)
   int32_t scan_steal;       // a long scan on the matrix cores: XCDs that are done take items of the others (set per request)
   int32_t scan_min_choice;  // shortest segment the plan may choose, as a power of two of pairs of groups (-1: the kernel's default; set per request)

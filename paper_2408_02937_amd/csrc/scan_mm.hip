@@ -31,7 +31,8 @@ namespace rtams {
 struct TileQuery {  // kMmQueryWords 32-bit words
   uint32_t q, len, bound;
   float qn;
-  uint32_t pad[4];
+  float unscale;  // narrow lists: what turns a product of the pieces into a product of the query
+  uint32_t pad[3];
   uint64_t keys, poss;  // addresses of the query's survivor records (keys, positions)
 };
 static_assert(sizeof(TileQuery) == kMmQueryWords * 4, "words per query of a tile");
@@ -43,31 +44,18 @@ struct WaveStage {  // survivors of one wavefront on their way out
 };
 static_assert(sizeof(WaveStage) == kMmStageBytes, "staging bytes per wavefront");
 
-// The groups g_lo + wave, g_lo + wave + 4, ... below g_hi of the list against QG groups of four queries.
-// first_b: the block that holds the wavefront's first group (looked up by the caller).
-// ST: what the lists keep.  A 16-byte chunk of halves or bytes is widened in registers, one float4 of coordinates at a
-// time, each against the matching float4 of the queries: the conversions run beside the matrix instructions, where
-// the vector-unit kernel has them in front of its own arithmetic (256 queries x 32 probes over 1 M x 128 bytes: 114 us
-// there, bound by instruction issue, for 129 MB of lists).
-template <int METRIC, int QG, int ST>
-__device__ __forceinline__ void scan_groups_mm(const Dev &D, const SearchScratch &S, int list, uint32_t g_lo,
-                                               uint32_t g_hi, uint32_t first_b, const float4 *qs,
-                                               const TileQuery *tq, WaveStage &st) {
-  constexpr int kPrefetch = 4;  // chunks per register set: 8 KiB of loads in flight per wavefront
-  constexpr int kPieces = pieces_of(ST);
-  const int vc = D.vchunks;
-  const int qstride = D.d4 + 1;  // float4s between two queries in LDS: an odd stride keeps the four rows a read touches on different banks
-  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int sub = lane & 3;
-  const float4 *__restrict__ qrow = qs + sub * qstride;  // query `sub` of group 0; group g is 4 g rows on
-  const uint32_t gpb = (uint32_t)D.groups_per_block;
-  const size_t group_stride = (size_t)vc * kWave;
-  uint32_t staged = 0;  // survivors in the staging area (uniform over the wavefront)
-  auto wave_sync = [] {  // LDS operations of one wavefront execute in order; keep the compiler from moving them
+// The staging area at work: what a wavefront keeps, and its way out.
+struct Staging {
+  const SearchScratch &S;
+  const TileQuery *tq;
+  WaveStage &st;
+  uint32_t staged;  // survivors in the area (uniform over the wavefront)
+  __device__ __forceinline__ void wave_sync() {  // LDS operations of one wavefront execute in order; keep the compiler from moving them
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-  };
-  auto flush = [&]() __attribute__((always_inline)) {
+  }
+  __device__ __forceinline__ void flush() {
+    const int lane = threadIdx.x & (kWave - 1);
     if (lane < kMmTileMax) st.qcnt[lane] = 0u;
     wave_sync();
     constexpr int kMine = kMmStageCap / kWave;
@@ -98,7 +86,51 @@ __device__ __forceinline__ void scan_groups_mm(const Dev &D, const SearchScratch
     }
     wave_sync();
     staged = 0;
-  };
+  }
+  // which of the lane's four candidates (bits of `pass`) survive for row `row` of the tile, at places slot, slot + 1, ...
+  __device__ __forceinline__ void keep(uint32_t pass, const uint32_t *key, uint32_t slot, uint32_t row) {
+    if (__ballot(pass != 0u) == 0ull) return;  // uniform
+    // places in the staging area: candidate r of every lane, lane after lane, then candidate r + 1
+    uint32_t at[4], total = 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const unsigned long long m = __ballot((pass >> r) & 1u);
+      at[r] = total + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+      total += (uint32_t)__popcll(m);
+    }
+    if (staged + total > (uint32_t)kMmStageCap) flush();  // uniform; at most 4 x 64 at once: they always fit an empty area
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (pass & (1u << r)) {
+        const uint32_t e = staged + at[r];
+        st.key[e] = key[r];
+        st.pos[e] = slot + r;
+        st.row[e] = (uint8_t)row;
+      }
+    staged += total;
+  }
+};
+
+// The groups g_lo + wave, g_lo + wave + 4, ... below g_hi of the list against QG groups of four queries.
+// first_b: the block that holds the wavefront's first group (looked up by the caller).
+// ST: what the lists keep.  A 16-byte chunk of halves or bytes is widened in registers, one float4 of coordinates at a
+// time, each against the matching float4 of the queries: the conversions run beside the matrix instructions, where
+// the vector-unit kernel has them in front of its own arithmetic (256 queries x 32 probes over 1 M x 128 bytes: 114 us
+// there, bound by instruction issue, for 129 MB of lists).
+template <int METRIC, int QG, int ST>
+__device__ __forceinline__ void scan_groups_mm(const Dev &D, const SearchScratch &S, int list, uint32_t g_lo,
+                                               uint32_t g_hi, uint32_t first_b, const float4 *qs,
+                                               const TileQuery *tq, WaveStage &st) {
+  constexpr int kPrefetch = 4;  // chunks per register set: 8 KiB of loads in flight per wavefront
+  constexpr int kPieces = pieces_of(ST);
+  const int vc = D.vchunks;
+  const int qstride = D.d4 + 1;  // float4s between two queries in LDS: an odd stride keeps the four rows a read touches on different banks
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int sub = lane & 3;
+  const float4 *__restrict__ qrow = qs + sub * qstride;  // query `sub` of group 0; group g is 4 g rows on
+  const uint32_t gpb = (uint32_t)D.groups_per_block;
+  const size_t group_stride = (size_t)vc * kWave;
+  Staging stage{S, tq, st, 0u};
   // The wavefront's groups of vectors as a software pipeline ACROSS the groups: while one is being
   // streamed the block number of the next is looked up, and the first loads of the next go out before
   // the survivors of this one are dealt with, so that neither the two dependent table reads nor the
@@ -199,32 +231,187 @@ __device__ __forceinline__ void scan_groups_mm(const Dev &D, const SearchScratch
         key[r] = key_of_float(sc + 0.0f);
         if (vbase + r < me.len && key[r] <= me.bound) pass |= 1u << r;
       }
-      if (__ballot(pass != 0u) == 0ull) continue;  // uniform
-      // places in the staging area: candidate r of every lane, lane after lane, then candidate r + 1
-      uint32_t at[4], total = 0;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const unsigned long long m = __ballot((pass >> r) & 1u);
-        at[r] = total + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-        total += (uint32_t)__popcll(m);
-      }
-      if (staged + total > (uint32_t)kMmStageCap) flush();  // uniform; at most 4 x 64 at once: they always fit an empty area
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (pass & (1u << r)) {
-          const uint32_t e = staged + at[r];
-          st.key[e] = key[r];
-          st.pos[e] = slot_base + r;
-          st.row[e] = (uint8_t)(4 * g + sub);
-        }
-      staged += total;
+      stage.keep(pass, key, slot_base, (uint32_t)(4 * g + sub));
     }
     if (!more) break;
     g0 = g_next;
     x = x_next;
     cur_b = next_b;
   }
-  if (staged) flush();
+  if (stage.staged) stage.flush();
+}
+
+// ---- squared distances to lists of halves and bytes.  What is stored is an operand of the 16-bit matrix instructions as it
+// is (halves), or a byte's conversion away (bf16 holds them exactly); the query, 24 bits of each coordinate, is split into
+// three pieces of the operand's type once per tile, and the products of the pieces, which are exact, add up in 32 bits to
+// the product of the query.  v_mfma_f32_16x16x32: lane l supplies eight coordinates of vector (or query) l % 16, and the 16
+// bytes that the lists keep of a vector are such eight, or twice such eight: four chunks of 16 vectors are the operand of
+// one or two instructions, whatever coordinate falls to which place, as long as both operands agree.  Queries whose second
+// and third pieces are zero (byte values) leave them out.
+// Against 4x4x1 instructions on widened floats (d x 8 clocks for every 4 queries and 64 vectors, and a conversion per
+// coordinate beside them) this takes d x 6 clocks for 16 queries, or d x 2: 256 queries x 32 probes over 1 M x 128 bytes,
+// 1,024 lists, 87 us with the former and 56 with these.  Where it pays: narrow_scan_pays.
+// The first piece is summed for itself, so that the norm form keeps its margin (norm_form_slack); |x|^2 is a sum of integers for bytes, and for halves the diagonal of the vectors' products with
+// themselves.  The selection scores its finalists again in the direct form, as behind the other scan.
+typedef _Float16 HalfX8 __attribute__((ext_vector_type(8)));
+typedef __bf16 Bf16X8 __attribute__((ext_vector_type(8)));
+template <int ST>
+__device__ __forceinline__ MfmaAcc narrow_product(const u32x4 &a, const u32x4 &b, const MfmaAcc &acc) {
+  if (ST == 1) return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(HalfX8, a), __builtin_bit_cast(HalfX8, b), acc, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(Bf16X8, a), __builtin_bit_cast(Bf16X8, b), acc, 0, 0, 0);
+}
+// eight bytes as eight bf16
+__device__ __forceinline__ u32x4 bytes_to_bf16(uint32_t lo, uint32_t hi) {
+  u32x4 out;
+  auto two = [](float a, float b) {  // the upper halves of two floats
+    return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+  };
+  out[0] = two((float)(lo & 255u), (float)((lo >> 8) & 255u));
+  out[1] = two((float)((lo >> 16) & 255u), (float)(lo >> 24));
+  out[2] = two((float)(hi & 255u), (float)((hi >> 8) & 255u));
+  out[3] = two((float)((hi >> 16) & 255u), (float)(hi >> 24));
+  return out;
+}
+// Row of query pieces in LDS: the coordinates of whole fours of chunks, and 16 bytes that spread the rows over the banks.
+constexpr int kNarrowPieces = 3;
+
+// Groups g_lo + wave, ... below g_hi against 16 CB queries.  qp: [pieces][rows][row_bytes].
+template <int ST, int CB>
+__device__ __forceinline__ void scan_groups_narrow(const Dev &D, const SearchScratch &S, int list, uint32_t g_lo, uint32_t g_hi,
+                                                   uint32_t first_b, const char *qp, int rows, int pieces, const TileQuery *tq,
+                                                   WaveStage &st) {
+  constexpr int kSteps = ST == 2 ? 2 : 1;  // instructions to a chunk
+  const int vc = D.vchunks, quads = (vc + 3) / 4;
+  const uint32_t row_bytes = narrow_row_bytes(D), piece_bytes = row_bytes * (uint32_t)rows;
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int col = lane & 15, kg = lane >> 4;  // the lane's vector of 16 and query of 16, and its chunk of four
+  const uint32_t gpb = (uint32_t)D.groups_per_block;
+  const size_t group_stride = (size_t)vc * kWave;
+  const char *my_q = qp + (uint32_t)col * row_bytes + (uint32_t)kg * (kSteps * 16u);
+  Staging stage{S, tq, st, 0u};
+  uint32_t g0 = g_lo + (uint32_t)wave;
+  if (g0 >= g_hi) return;  // nothing staged yet
+  uint32_t cur_b = (uint32_t)__builtin_amdgcn_readfirstlane((int)first_b);
+  auto place = [&](uint32_t g, uint32_t b) {
+    return reinterpret_cast<const u32x4 *>(block_vecs(D, b)) + (size_t)(g % gpb) * group_stride;
+  };
+  u32x4 cur[4];
+  auto load = [&](u32x4 *to, const u32x4 *x, int quad) {  // the lane's chunk of the quad, of its vector in each block of 16
+    const uint32_t at = (uint32_t)(min(4 * quad + kg, vc - 1) * kWave + col);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) to[b] = x[at + 16u * b];
+    __builtin_amdgcn_sched_barrier(0);  // the loads go out here
+  };
+  const u32x4 *x = place(g0, cur_b);
+  load(cur, x, 0);
+  for (;;) {
+    const uint32_t g_next = g0 + kMmWaves;
+    const bool more = g_next < g_hi;  // uniform over the wavefront
+    uint32_t next_b = 0;
+    if (more) next_b = (uint32_t)*table_entry(D, list, g_next / gpb);  // on its way while this group is streamed
+    MfmaAcc acc[4][CB], low[4][CB], gram[ST == 1 ? 4 : 1];
+    uint32_t sq[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) acc[b][cb] = low[b][cb] = (MfmaAcc){0.f, 0.f, 0.f, 0.f};
+      if (ST == 1) gram[b] = (MfmaAcc){0.f, 0.f, 0.f, 0.f};
+    }
+    const u32x4 *x_next = x;
+#pragma unroll 1
+    for (int quad = 0; quad < quads; ++quad) {
+      u32x4 nxt[4];
+      if (quad + 1 < quads) {
+        load(nxt, x, quad + 1);
+      } else if (more) {  // the next group's first loads go out before this group's survivors are dealt with
+        next_b = (uint32_t)__builtin_amdgcn_readfirstlane((int)next_b);
+        x_next = place(g_next, next_b);
+        load(nxt, x_next, 0);
+      }
+      if (4 * quad + kg >= vc) {  // chunks past the vector
+#pragma unroll
+        for (int b = 0; b < 4; ++b) cur[b] = (u32x4){0u, 0u, 0u, 0u};
+      }
+#pragma unroll
+      for (int j = 0; j < kSteps; ++j) {
+        u32x4 a[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          if (ST == 1) {
+            a[b] = cur[b];
+            gram[b] = narrow_product<ST>(a[b], a[b], gram[b]);
+          } else {
+            const uint32_t w0 = cur[b][2 * j], w1 = cur[b][2 * j + 1];
+            sq[b] = __builtin_amdgcn_udot4(w0, w0, sq[b], false);
+            sq[b] = __builtin_amdgcn_udot4(w1, w1, sq[b], false);
+            a[b] = bytes_to_bf16(w0, w1);
+          }
+        }
+        auto add_piece = [&](int pc, MfmaAcc (&to)[4][CB]) {
+          u32x4 y[CB];
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb)
+            y[cb] = *reinterpret_cast<const u32x4 *>(my_q + (uint32_t)pc * piece_bytes + (uint32_t)(16 * cb) * row_bytes + (uint32_t)quad * (4u * kSteps * 16u) + 16u * j);
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) to[b][cb] = narrow_product<ST>(a[b], y[cb], to[b][cb]);
+        };
+        add_piece(0, acc);
+#pragma unroll 1
+        for (int pc = 1; pc < pieces; ++pc) add_piece(pc, low);  // uniform
+      }
+#pragma unroll
+      for (int b = 0; b < 4; ++b) cur[b] = nxt[b];
+    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[b][cb][r] += low[b][cb][r];
+    __builtin_amdgcn_sched_barrier(0);  // (the second sums' registers are free from here on)
+    // (what the lane's place comes to below is worked out here again, not kept in registers through the loop above)
+    int kge = kg, cole = col;
+    asm volatile("" : "+v"(kge), "+v"(cole));
+    // |x|^2 of the lane's four rows of a block: rows 4 kg .. 4 kg + 3 (the result's layout)
+    float nr[4][4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      if (ST == 2) {
+        uint32_t t = sq[b] + (uint32_t)__shfl_xor((int)sq[b], 16);
+        t += (uint32_t)__shfl_xor((int)t, 32);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) nr[b][r] = (float)(uint32_t)__shfl((int)t, 4 * kge + r);
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) nr[b][r] = __shfl(gram[b][r], 16 * kge + 4 * kge + r);  // the diagonal: column 4 kge + r of those rows
+      }
+    }
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+      const TileQuery me = tq[16 * cb + cole];  // len 0 for rows past the tile: nothing of theirs is kept
+      const float m2 = -2.f * me.unscale;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const uint32_t vbase = g0 * kWave + 16u * b + 4u * (uint32_t)kge;
+        uint32_t key[4], pass = 0u;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          // (an infinite coordinate makes the norm form inf - inf: such a vector is infinitely far, as the direct form has it)
+          const float sc = fminf(fmaf(m2, acc[b][cb][r], nr[b][r] + me.qn), __builtin_inff());
+          key[r] = key_of_float(sc + 0.0f);
+          if (vbase + r < me.len && key[r] <= me.bound) pass |= 1u << r;
+        }
+        stage.keep(pass, key, slot_of(D, cur_b, (g0 % gpb) * kWave + 16u * b + 4u * (uint32_t)kge), (uint32_t)(16 * cb + cole));
+      }
+    }
+    if (!more) break;
+    g0 = g_next;
+    x = x_next;
+    cur_b = next_b;
+  }
+  if (stage.staged) stage.flush();
 }
 
 // Hardware hands consecutive workgroup ids to the 8 XCDs in turn, so workgroup i runs on XCD i % 8 and
@@ -245,10 +432,11 @@ __device__ __forceinline__ void scan_groups_mm(const Dev &D, const SearchScratch
 // 128, 2,048 items: bytes 89 us with three and 87 with four, floats 105 and 104: what is scanned comes from memory at
 // 7 TB/s meanwhile, and only the launch's end is shorter); three for long scans and inner products of floats, which
 // gain nothing by it.
-template <int METRIC, bool STEAL, int ST>
-__global__ __launch_bounds__(kMmWaves *kWave, STEAL || (METRIC == 1 && ST == 0) ? 3 : 4) void k_scan_mm(Dev D, int max_nprobe, const float *__restrict__ Q,
+template <int METRIC, bool STEAL, int ST, bool NARROW>
+__global__ __launch_bounds__(kMmWaves *kWave, STEAL || NARROW || (METRIC == 1 && ST == 0) ? 3 : 4) void k_scan_mm(Dev D, int max_nprobe, const float *__restrict__ Q,
                                                              SearchScratch S, int tile_rows) {
-  extern __shared__ float4 lds_mm[];  // [tile_rows][d / 4 + 1] coordinates of the tile's queries, [tile_rows] TileQuery, [wavefronts] WaveStage
+  // [tile_rows][d / 4 + 1] coordinates of the tile's queries (or the pieces of narrow lists), [tile_rows] TileQuery, [wavefronts] WaveStage
+  extern __shared__ float4 lds_mm[];
   ScanQueues *Qs = S.queues;
   const uint32_t xcd = blockIdx.x % kXcds;
   const uint32_t own = Qs->begin[xcd] + blockIdx.x / kXcds;
@@ -296,14 +484,16 @@ __global__ __launch_bounds__(kMmWaves *kWave, STEAL || (METRIC == 1 && ST == 0) 
   if (pairs == 0) return;
   const int d4 = D.d4, qstride = d4 + 1;
   float4 *qs = lds_mm;
-  TileQuery *tq = reinterpret_cast<TileQuery *>(lds_mm + (size_t)tile_rows * qstride);
+  const uint32_t row_bytes = NARROW ? narrow_row_bytes(D) : 0u;
+  TileQuery *tq = reinterpret_cast<TileQuery *>(NARROW ? reinterpret_cast<float4 *>(reinterpret_cast<char *>(lds_mm) + (size_t)kNarrowPieces * tile_rows * row_bytes)
+                                                       : lds_mm + (size_t)tile_rows * qstride);
   WaveStage &st = reinterpret_cast<WaveStage *>(tq + tile_rows)[threadIdx.x / kWave];
   // groups of four queries of this tile: 1, 2, 3, 4, 6 or 8, whichever holds the item's queries; exactly
   // that many rows of LDS are set up, and the instantiation below reads exactly that many (the plan never
   // puts more queries into a tile than tile_rows)
   int qg = (int)((pairs + 3u) / 4u);
   qg = qg == 5 ? 6 : qg == 7 ? 8 : qg;
-  const int rows = 4 * qg;
+  const int rows = NARROW ? (pairs > 16u ? 32 : 16) : 4 * qg;
   if (rows > tile_rows || rows > kMmTileMax) return;  // a descriptor the launch was not sized for: nothing is scanned
   // The block number of the wavefront's first group of vectors is asked for now (two dependent reads)
   // and used after the tile is set up.  Never past the list's chain, whatever the descriptors say.
@@ -328,10 +518,59 @@ __global__ __launch_bounds__(kMmWaves *kWave, STEAL || (METRIC == 1 && ST == 0) 
       t.poss = (uint64_t)(uintptr_t)rec_poss_of(S, qb);
       t.bound = S.bound[t.q];
       if (METRIC == 0) t.qn = S.qnorm[t.q];
+      if (NARROW) t.unscale = ST == 1 ? 1.f / half_piece_scale(t.qn) : 1.f;
     }
     tq[threadIdx.x] = t;
     my_len = t.len;
   }
+  __shared__ uint32_t s_pieces[kMmWaves];
+  if (NARROW) {
+    // ... as pieces; coordinates past d are zero
+    const int cols = (int)((row_bytes - 16u) / 8u), total = rows * cols;  // four coordinates at a time
+    char *qp = reinterpret_cast<char *>(lds_mm);
+    const uint32_t piece_bytes = row_bytes * (uint32_t)rows;
+    uint32_t have = 0u;
+    constexpr int kInFlight = 4, kThreads = kMmWaves * kWave;
+    for (int base = (int)threadIdx.x; base < total; base += kInFlight * kThreads) {
+      float4 v[kInFlight];
+      float qn[kInFlight];
+#pragma unroll
+      for (int u = 0; u < kInFlight; ++u) {
+        const int idx = base + u * kThreads, row = idx < total ? idx / cols : rows, col = idx - row * cols;
+        const bool on = row < (int)pairs && col < d4;
+        const uint32_t q = on ? S.grouped[first + row] >> 10 : 0u;
+        v[u] = on ? reinterpret_cast<const float4 *>(Q + (size_t)q * D.d)[col] : make_float4(0.f, 0.f, 0.f, 0.f);
+        qn[u] = on && ST == 1 ? S.qnorm[q] : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < kInFlight; ++u) {
+        const int idx = base + u * kThreads, row = idx < total ? idx / cols : rows, col = idx - row * cols;
+        if (row >= rows) continue;
+        const float scale = ST == 1 ? half_piece_scale(qn[u]) : 1.f;
+        float w[4] = {v[u].x * scale, v[u].y * scale, v[u].z * scale, v[u].w * scale};
+#pragma unroll
+        for (int pc = 0; pc < kNarrowPieces; ++pc) {
+          uint32_t bits[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if (ST == 1) {
+              const _Float16 h = (_Float16)w[e];
+              bits[e] = (uint32_t)__builtin_bit_cast(uint16_t, h);
+              w[e] -= (float)h;
+            } else {
+              bits[e] = __float_as_uint(w[e]) >> 16;
+              w[e] -= __uint_as_float(bits[e] << 16);
+            }
+            if (bits[e] & 0x7fffu) have = max(have, (uint32_t)pc + 1u);
+          }
+          *reinterpret_cast<uint2 *>(qp + (size_t)pc * piece_bytes + (size_t)row * row_bytes + (size_t)col * 8) =
+              make_uint2(bits[0] | bits[1] << 16, bits[2] | bits[3] << 16);
+        }
+      }
+    }
+    for (int o = kWave / 2; o > 0; o >>= 1) have = max(have, (uint32_t)__shfl_xor((int)have, o));
+    if ((threadIdx.x & (kWave - 1)) == 0) s_pieces[threadIdx.x / kWave] = have;
+  } else
   // coordinates: the rows x d / 4 float4s of the tile are dealt out over the workgroup, eight independent
   // loads per thread in flight (a row at a time would be a chain of memory latencies per row); which
   // query a row holds is read from the grouped pairs again rather than waited for in LDS
@@ -370,6 +609,13 @@ __global__ __launch_bounds__(kMmWaves *kWave, STEAL || (METRIC == 1 && ST == 0) 
   if (g_end > g_begin + seg) g_end = g_begin + seg;  // ... inside this item's segment
   if (g_end > g_have) g_end = g_have;
   // no barrier from here on: the wavefronts only read the tile
+  if (NARROW) {
+    const char *qp = reinterpret_cast<const char *>(lds_mm);
+    const int pieces = __builtin_amdgcn_readfirstlane((int)max(max(s_pieces[0], s_pieces[1]), max(s_pieces[2], s_pieces[3])));
+    if (rows == 16) scan_groups_narrow<ST, 1>(D, S, list, g_begin, g_end, first_b, qp, rows, pieces, tq, st);
+    else scan_groups_narrow<ST, 2>(D, S, list, g_begin, g_end, first_b, qp, rows, pieces, tq, st);
+    return;
+  }
   switch (qg) {
     case 1: scan_groups_mm<METRIC, 1, ST>(D, S, list, g_begin, g_end, first_b, qs, tq, st); break;
     case 2: scan_groups_mm<METRIC, 2, ST>(D, S, list, g_begin, g_end, first_b, qs, tq, st); break;
@@ -384,19 +630,22 @@ void launch_scan_mm(const Dev &D, const ScanShape &sh, int max_nprobe, const flo
                     hipStream_t s) {
   typedef void (*Kernel)(Dev, int, const float *, SearchScratch, int);
   static const Kernel kernels[2][2][3] = {
-      {{k_scan_mm<0, false, 0>, k_scan_mm<0, false, 1>, k_scan_mm<0, false, 2>},
-       {k_scan_mm<0, true, 0>, k_scan_mm<0, true, 1>, k_scan_mm<0, true, 2>}},
-      {{k_scan_mm<1, false, 0>, k_scan_mm<1, false, 1>, k_scan_mm<1, false, 2>},
-       {k_scan_mm<1, true, 0>, k_scan_mm<1, true, 1>, k_scan_mm<1, true, 2>}}};
+      {{k_scan_mm<0, false, 0, false>, k_scan_mm<0, false, 1, false>, k_scan_mm<0, false, 2, false>},
+       {k_scan_mm<0, true, 0, false>, k_scan_mm<0, true, 1, false>, k_scan_mm<0, true, 2, false>}},
+      {{k_scan_mm<1, false, 0, false>, k_scan_mm<1, false, 1, false>, k_scan_mm<1, false, 2, false>},
+       {k_scan_mm<1, true, 0, false>, k_scan_mm<1, true, 1, false>, k_scan_mm<1, true, 2, false>}}};
+  static const Kernel narrow[2][2] = {{k_scan_mm<0, false, 1, true>, k_scan_mm<0, false, 2, true>},
+                                      {k_scan_mm<0, true, 1, true>, k_scan_mm<0, true, 2, true>}};
   // above 64 KiB of dynamic LDS a kernel has to be told (wide vectors only); once per kernel and process
   static const bool once = [] {
-    for (int i = 0; i < 12; ++i)
-      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernels[i / 6][i / 3 % 2][i % 3]),
+    for (int i = 0; i < 16; ++i)
+      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(i < 12 ? kernels[i / 6][i / 3 % 2][i % 3] : narrow[(i - 12) / 2][i % 2]),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMmLdsMax);
     return true;
   }();
   (void)once;
-  hipLaunchKernelGGL(kernels[D.metric][D.scan_steal ? 1 : 0][D.storage], dim3((unsigned)sh.grid), dim3((unsigned)sh.threads),
+  const Kernel kernel = scans_narrow(D) ? narrow[D.scan_steal ? 1 : 0][D.storage - 1] : kernels[D.metric][D.scan_steal ? 1 : 0][D.storage];
+  hipLaunchKernelGGL(kernel, dim3((unsigned)sh.grid), dim3((unsigned)sh.threads),
                      sh.lds, s, D, max_nprobe, Q, S, sh.tile_q);
 }
 

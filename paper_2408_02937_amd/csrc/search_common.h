@@ -361,6 +361,23 @@ __device__ __forceinline__ float quad_broadcast(float v) {
 // 2 |x - q|^2 + 3 |q|^2).  So whoever compares a norm-form score with a limit taken from direct-form
 // scores, or the other way round, first raises the limit by that much ("loosened"), and the selection
 // scores its finalists again in the direct form: the result is the one the direct form gives.
+// Lists of halves and bytes may go through 16-bit matrix instructions with the query in three pieces (scan_mm.hip), which
+// may add with roundings either way, 2^-23 each: d of them on the products of the first piece, 2 d on those of the others,
+// which are 2^-7 of them at most and are summed for themselves, and d on |x|^2 for halves (none for bytes); with
+// |x| |q| <= 1.5 |q|^2 + v / 2 and |x|^2 <= 2 |q|^2 + 2 v that is (10.2 |q|^2 + 7.1 v) d 2^-24 with the direct form's own
+// d + 2 roundings: the same margin holds both.
+__host__ __device__ inline uint32_t narrow_row_bytes(const Dev &D) {  // of a query's piece in LDS
+  return (uint32_t)((D.vchunks + 3) / 4 * 4) * (D.storage == 1 ? 16u : 32u) + 16u;
+}
+__host__ __device__ inline bool scans_narrow(const Dev &D) { return D.scan_mfma == 2; }
+// power of two that brings a query of squared norm qn to a length of 2^13 to 2^14
+__device__ inline float half_piece_scale(float qn) {
+  if (!(qn > 0.f) || !(qn < __builtin_inff())) return 1.f;
+  const int e = (int)((__float_as_uint(qn) >> 23) & 255u) - 127;  // |q| < 2^((e + 1) / 2)
+  int s = 14 - ((e + 2) >> 1);
+  s = s > 100 ? 100 : s < -100 ? -100 : s;
+  return __uint_as_float((uint32_t)(s + 127) << 23);
+}
 __device__ inline float norm_form_slack(int d) { return 1.01f * (float)(4 * d + 8) * 5.9604645e-8f; }
 __device__ inline float loosened(float v, float slack, float qn) {
   const float r = v + slack * (2.f * fmaxf(v, 0.f) + 3.f * qn) + 1e-30f;
@@ -462,6 +479,19 @@ inline bool mm_scan_pays(const Dev &D, int64_t nq, int64_t nprobe, int64_t avg_l
   return d >= 512 ? pairs >= nlist : products >= (d <= 96 ? 1e9 : 8e9);
 }
 
+// Whether such a request over lists of halves or bytes, squared distances, scans on the 16-bit instructions (scan_mm.hip):
+// wherever the vectors are wide enough to repay the queries' splitting, and three pieces of 16 queries fit beside another
+// workgroup's in LDS.  4x4x1 / 16-bit, us a request (queries of three pieces), 256 lists:
+//  bytes, 128 queries x 32 probes, lists of 600: d 16 44 / 47, d 32 48 / 46, d 64 58 / 48, d 128 71 / 56, d 320
+//    128 / 81, d 640 192 / 144; 256 x 32, lists of 1,500: d 16 58 / 63, d 32 65 / 64, d 128 115 / 79, d 640 372 /
+//    264; 64 x 8, of 1,500: d 64 47 / 46, d 128 56 / 53, d 640 173 / 154
+//  halves, 128 x 32, lists of 600: d 16 46 / 45, d 32 50 / 45, d 128 74 / 58, d 320 128 / 86, d 640 196 / 154;
+//    256 x 32, of 1,500: d 16 60 / 59, d 128 114 / 84, d 640 434 / 370; 64 x 8, of 1,500: d 64 49 / 50, d 128 54 /
+//    55, d 640 124 / 124
+inline bool narrow_scan_pays(const Dev &D) {
+  return D.metric == 0 && D.pq_m == 0 && D.storage != 0 && D.d >= (D.storage == 2 ? 64 : 32) && D.d <= 640;
+}
+
 inline ScanShape scan_shape(const Dev &D, int item_budget) {
   ScanShape sh{};
   sh.mm = D.scan_mfma != 0 && D.pq_m == 0;
@@ -480,11 +510,13 @@ inline ScanShape scan_shape(const Dev &D, int item_budget) {
     sh.grid = ((items + waves - 1) / waves + (int)kXcds - 1) / (int)kXcds * (int)kXcds;
     return sh;
   }
-  const size_t row = (size_t)(D.d + 4) * sizeof(float) + kMmQueryWords * 4;  // a query of the tile: coordinates, one float4 of padding, its words
+  // a query of the tile: coordinates, one float4 of padding, its words (or its three pieces and its words)
+  const bool narrow = scans_narrow(D);
+  const size_t row = (narrow ? (size_t)3 * narrow_row_bytes(D) : (size_t)(D.d + 4) * sizeof(float)) + kMmQueryWords * 4;
   const size_t stage = kMmWaves * kMmStageBytes;
   int rows = kMmTileMax;
   // two workgroups should fit a CU side by side; a tile is never below 8 queries unless LDS cannot hold that
-  while (rows > 8 && row * rows + stage > 64 * 1024) rows /= 2;
+  while (rows > (narrow ? 16 : 8) && row * rows + stage > 64 * 1024) rows /= 2;
   while (rows > 4 && row * rows + stage > kMmLdsMax) rows /= 2;
   sh.tile_q = rows;
   sh.seg_base = 2;

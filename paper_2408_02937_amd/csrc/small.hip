@@ -6,9 +6,9 @@
 // cut and shared out by one workgroup, which a request whose pairs hardly share a list does not get back.  Here the last
 // workgroup of a query's coarse scores goes on with its probes and its bound, and the wavefronts of the scan take the
 // groups of the query's lists in turn from the lengths alone.
-// 10 queries x 8 probes over 100 lists of 100 x 32 floats: 31.6 us back to back where the five launches took 42.7; one
-// query x 32 probes over 1,000 lists of 1,000 x 128: 45.7 and 47.3.  Above kSmallBytes, where the scan's own time hides the
-// plan, and with lists that several queries share, the plan is repaid.
+// 10 queries x 8 probes over 64 lists, 10,000 x 32 floats: 31.6 us back to back where the five launches took 42.7; one
+// query x 32 probes over 1,024 lists, 1 M x 128: 45.7 and 47.3.  Above kSmallBytes the scan's own time hides the
+// plan, and what several queries read of one list is read once.
 #include "bound.h"
 #include "coarse_exact.h"
 #include "probe_plan.h"
