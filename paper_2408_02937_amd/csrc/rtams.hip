@@ -547,7 +547,10 @@ int rtams_create(const rtams_config *cfg, rtams_index **out) {
   void *dm = nullptr;
   if (hipHostGetDevicePointer(&dm, hm, 0) != hipSuccess) return bail(fail(RTAMS_EHIP, "hipHostGetDevicePointer failed"));
   D.mirror = static_cast<HostMirror *>(dm);
-  if (hipEventCreateWithFlags(&ix->data_done, hipEventDisableTiming) != hipSuccess ||
+  // data_done orders streams of this device behind one another and is never asked from the host, so its record needs no
+  // fence to the system, which costs every insertion call a microsecond or two on the GPU and as much on the host (64 vectors
+  // a call back to back: 17.5 us a call, 19.3 with the fence).  The others are asked.
+  if (hipEventCreateWithFlags(&ix->data_done, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess ||
       hipEventCreateWithFlags(&ix->fence_ev[0], hipEventDisableTiming) != hipSuccess ||
       hipEventCreateWithFlags(&ix->fence_ev[1], hipEventDisableTiming) != hipSuccess)
     return bail(fail(RTAMS_EHIP, "hipEventCreate failed"));
