@@ -31,10 +31,11 @@ struct NearestList {
 };
 
 template <int METRIC, int ST>
-__device__ void sample_scores(const Dev &D, int nprobe, int max_nprobe, int q, uint32_t want_groups,
+__device__ uint32_t sample_scores(const Dev &D, int nprobe, int max_nprobe, int q, uint32_t want_groups,
                               const float *__restrict__ Q, const SearchScratch &S, const float4 *qv,
-                              uint32_t *skey, const NearestList &first) {
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+                              uint32_t *skey, uint32_t *gkey, uint32_t part, uint32_t parts, const NearestList &first) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const uint32_t mine = (uint32_t)(tid / kWave) * parts + part, step = blockDim.x / kWave * parts;
   const int d4 = D.vchunks;  // 16-byte chunks of a stored vector
   constexpr int kPieces = pieces_of(ST);  // float4s of the query that go with a chunk
   const uint32_t gpb = (uint32_t)D.groups_per_block;
@@ -49,8 +50,8 @@ __device__ void sample_scores(const Dev &D, int nprobe, int max_nprobe, int q, u
     const uint32_t have = (p == 0 ? first.nblk : D.nblk[list]) * gpb;  // never index the block table past the chain
     if (groups > have) groups = have;
     if (groups > want_groups - g_first) groups = want_groups - g_first;
-    for (uint32_t g = (uint32_t)wave; g < groups; g += blockDim.x / kWave) {
-      const uint32_t b = p == 0 && g == (uint32_t)wave ? (uint32_t)*table_entry_at(D, first.dir, g / gpb)
+    for (uint32_t g = mine; g < groups; g += step) {
+      const uint32_t b = p == 0 && g == mine ? (uint32_t)*table_entry_at(D, first.dir, g / gpb)
                                                        : (uint32_t)*table_entry(D, list, g / gpb);
       const float4 *__restrict__ x = block_vecs(D, b) + (size_t)(g % gpb) * group_stride + lane;
       float acc = 0.f;
@@ -112,12 +113,14 @@ __device__ void sample_scores(const Dev &D, int nprobe, int max_nprobe, int q, u
         for (int s = 0; s < kPieces; ++s) accumulate<METRIC>(acc, chunk_piece<ST>(v, s), qv[c * kPieces + s]);
       }
       const uint32_t v = g * kWave + lane;
-      skey[(size_t)(g_first + g) * kWave + lane] =
-          v < len ? key_of_float((METRIC == 0 ? acc : -acc) + 0.0f) : 0xFFFFFFFFu;
+      const uint32_t key = v < len ? key_of_float((METRIC == 0 ? acc : -acc) + 0.0f) : 0xFFFFFFFFu;
+      const size_t at = (size_t)(g_first + g) * kWave + lane;
+      if (gkey) __hip_atomic_store(&gkey[at], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // uniform
+      else skey[at] = key;
     }
     g_first += groups;
   }
-  // groups the lists did not have stay at the worst key (set by the caller)
+  return g_first;  // groups the lists did not have stay at the worst key (set by the caller)
 }
 
 // The same sample over product-quantiser codes: a vector's score is the sum, in the order of the
@@ -162,9 +165,19 @@ __device__ void pq_sample_scores(const Dev &D, int nprobe, int max_nprobe, int q
 // kernel whose workgroups do different jobs can use the same bytes for each.
 constexpr size_t kBoundLdsBytes = 512 * sizeof(float4) + kSampleMax * sizeof(uint32_t);
 
+// A request of few queries leaves compute units idle while one of them reads a sample of wide vectors or of a long list:
+// up to kSampleParts workgroups read it then (part of parts), leave the keys in the row of the query's approximate scores,
+// which nobody needs any more, and the last one goes on.  One compute unit reads 40 to 60 GB/s however much it asks for at
+// once; this launch, with one workgroup to a query and with several, whole turns in both (us): 64 queries over lists of 610 x
+// 768 floats, samples of 1,536 chunks of 1 KiB, 34.8 / 20.9; 128 queries over lists of 2,441 x 96, up to 1,000 chunks, 51.4 /
+// 42.0; 32 queries over lists of 1,000 x 128, 256 chunks, 15.9 / 16.5, so such a sample is left to one.
+constexpr int kComputeUnits = 256;
+constexpr int kSampleParts = 4;
+constexpr uint32_t kSplitChunks = 512;
+
 template <bool PQ>
 __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, int k, const float *__restrict__ Q,
-                             const SearchScratch &S, unsigned char *lds) {
+                             const SearchScratch &S, unsigned char *lds, uint32_t part, uint32_t parts) {
   float4 *qv = reinterpret_cast<float4 *>(lds);
   uint32_t *skey = reinterpret_cast<uint32_t *>(lds + 512 * sizeof(float4));
   __shared__ __attribute__((aligned(8))) uint32_t hist[kSelectLdsWords];
@@ -193,7 +206,7 @@ __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, in
   const uint32_t no_bound_below =
       D.metric == 0 ? (uint32_t)kNoBoundBelow : max((uint32_t)kNoBoundBelow, 32u * (uint32_t)D.d);
   if (qtotal <= no_bound_below) {  // uniform over the workgroup
-    if (tid == 0) {
+    if (tid == 0 && part == 0) {
       S.bound[q] = 0xFFFFFFFFu;
       *rec_count(S, (uint32_t)q) = 0u;
     }
@@ -206,27 +219,55 @@ __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, in
   uint32_t cap = PQ ? (uint32_t)kSampleMax : ((1u << 20) / ((uint32_t)D.vchunks * 16u)) & ~(uint32_t)(kWave - 1);
   cap = cap < 512u ? 512u : (cap > (uint32_t)kSampleMax ? (uint32_t)kSampleMax : cap);
   uint32_t want = (uint32_t)k * 4u;
-  const uint32_t part = first.len / (uint32_t)kSampleDivisor;
-  if (!PQ) {  // on their way while the query and the keys are set up
-    first.nblk = D.nblk[first.list];
-    first.dir = table_dir(D, first.list, (uint32_t)(tid / kWave) / (uint32_t)D.groups_per_block);
-  }
-  want = want < part ? part : want;
+  const uint32_t share = first.len / (uint32_t)kSampleDivisor;
+  want = want < share ? share : want;
   want = want < 512u ? 512u : (want > cap ? cap : want);
-  const uint32_t want_groups = (want + kWave - 1) / kWave;
+  uint32_t want_groups = (want + kWave - 1) / kWave;
+  if (!PQ) {
+    if (parts > 1 && (want_groups * (uint32_t)D.vchunks < kSplitChunks || want_groups * kWave > (uint32_t)D.nlist)) {
+      if (part) return;  // uniform, and the same for all workgroups of the query
+      parts = 1;
+    }
+    // whole turns of the wavefronts, a group to each (128 queries over lists of 2,441, ten groups: the last two were a turn of their own)
+    const uint32_t turn = blockDim.x / kWave * parts;
+    want_groups = max((want_groups + turn / 2) / turn * turn, min(want_groups, 512u / kWave));
+    want_groups = min(want_groups, (uint32_t)kSampleMax / kWave);
+    if (parts > 1) want_groups = min(want_groups, (uint32_t)D.nlist / kWave);
+    // on their way while the query and the keys are set up
+    first.nblk = D.nblk[first.list];
+    first.dir = table_dir(D, first.list, ((uint32_t)(tid / kWave) * parts + part) / (uint32_t)D.groups_per_block);
+  }
   if (!PQ)
     for (int c = tid; c < D.d4; c += (int)blockDim.x) qv[c] = reinterpret_cast<const float4 *>(Q + (size_t)q * D.d)[c];
   for (int i = tid; i < (int)(want_groups * kWave); i += (int)blockDim.x) skey[i] = 0xFFFFFFFFu;
   __syncthreads();
-  if (PQ) pq_sample_scores(D, nprobe, max_nprobe, q, want_groups, S, skey);
-  else if (D.metric == 0) {
-    if (D.storage == 1) sample_scores<0, 1>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, first);
-    else if (D.storage == 2) sample_scores<0, 2>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, first);
-    else sample_scores<0, 0>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, first);
+  if (PQ) {
+    pq_sample_scores(D, nprobe, max_nprobe, q, want_groups, S, skey);
   } else {
-    if (D.storage == 1) sample_scores<1, 1>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, first);
-    else if (D.storage == 2) sample_scores<1, 2>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, first);
-    else sample_scores<1, 0>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, first);
+    uint32_t *gkey = parts > 1 ? reinterpret_cast<uint32_t *>(S.approx) + (size_t)q * D.nlist : nullptr;
+    uint32_t groups;
+    if (D.metric == 0) {
+      if (D.storage == 1) groups = sample_scores<0, 1>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, gkey, part, parts, first);
+      else if (D.storage == 2) groups = sample_scores<0, 2>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, gkey, part, parts, first);
+      else groups = sample_scores<0, 0>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, gkey, part, parts, first);
+    } else {
+      if (D.storage == 1) groups = sample_scores<1, 1>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, gkey, part, parts, first);
+      else if (D.storage == 2) groups = sample_scores<1, 2>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, gkey, part, parts, first);
+      else groups = sample_scores<1, 0>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, gkey, part, parts, first);
+    }
+    if (parts > 1) {  // uniform
+      __shared__ uint32_t s_last;
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's keys are out ...
+      __syncthreads();                                  // ... and so are everybody's before the workgroup counts itself off
+      if (tid == 0) {
+        s_last = atomicAdd(&S.done_count[q], 1u) + 1u == parts;
+        if (s_last) S.done_count[q] = 0u;  // (a small request expects it at zero)
+      }
+      __syncthreads();
+      if (!s_last) return;  // uniform: the last one goes on
+      for (uint32_t i = (uint32_t)tid; i < groups * kWave; i += blockDim.x)
+        skey[i] = __hip_atomic_load(&gkey[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
   __syncthreads();
   // k-th smallest key of the sample; with fewer than k candidates in it, it is the worst key

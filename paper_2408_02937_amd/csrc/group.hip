@@ -110,7 +110,7 @@ __device__ void scatter_pairs(const Dev &D, int nq, int nprobe, int max_nprobe, 
 __global__ __launch_bounds__(kGroupThreads, 4) void k_group(Dev D, int nq, int nprobe, int max_nprobe, int k,
                                                          const float *__restrict__ Q,
                                                          uint32_t item_budget, uint32_t max_per_xcd,
-                                                         uint32_t tile_q, uint32_t seg_base, int min_choice, int scatterers,
+                                                         uint32_t tile_q, uint32_t seg_base, int min_choice, int scatterers, int sample_parts,
                                                          SearchScratch S) {
   const int tile_shift = 31 - __clz((int)tile_q);  // tiles hold a power of two of queries
   if (blockIdx.x >= 1 && (int)blockIdx.x <= scatterers) {  // uniform over the workgroup: these group the pairs by list
@@ -121,7 +121,8 @@ __global__ __launch_bounds__(kGroupThreads, 4) void k_group(Dev D, int nq, int n
   __shared__ __attribute__((aligned(16))) unsigned char s_raw[kBoundLdsBytes];
   static_assert(kBoundLdsBytes >= kLdsEntries * sizeof(uint4), "the entries share the bound's LDS");
   if (blockIdx.x > 0) {  // this one sets the bound of a query
-    sample_bound<false>(D, (int)blockIdx.x - 1 - scatterers, nprobe, max_nprobe, k, Q, S, s_raw);
+    const uint32_t at = blockIdx.x - 1u - (uint32_t)scatterers, part = at / (uint32_t)nq;
+    sample_bound<false>(D, (int)(at - part * (uint32_t)nq), nprobe, max_nprobe, k, Q, S, s_raw, part, (uint32_t)sample_parts);
     return;
   }
   __shared__ uint32_t s_a[kGroupThreads / kWave], s_b[kGroupThreads / kWave];  // pairs, items and work of every wavefront's lists
@@ -442,7 +443,7 @@ __global__ __launch_bounds__(kPqBoundThreads) void k_pq_bound(Dev D, int nprobe,
   __threadfence_block();
   __syncthreads();  // the sample below reads the table
   __shared__ __attribute__((aligned(16))) unsigned char s_raw[kBoundLdsBytes];
-  sample_bound<true>(D, q, nprobe, max_nprobe, k, nullptr, S, s_raw);
+  sample_bound<true>(D, q, nprobe, max_nprobe, k, nullptr, S, s_raw, 0u, 1u);
 }
 
 
@@ -458,10 +459,13 @@ void launch_group(const Dev &D, int64_t nq, int nprobe, int max_nprobe, int k, c
   const ScanShape sh = scan_shape(D, item_budget);
   const int64_t pairs = nq * nprobe;
   const int scatterers = (int)(pairs <= 2048 ? 1 : pairs >= 8 * 2048 ? 8 : (pairs + 2047) / 2048);
-  hipLaunchKernelGGL(k_group, dim3(1 + (unsigned)scatterers + (unsigned)nq), dim3(kGroupThreads), 0, s, D, (int)nq,
+  // (as many workgroups to a query as are on the chip at once)
+  const int64_t room = (2 * kComputeUnits - 1 - scatterers) / nq;
+  const int parts = room < 1 ? 1 : room > kSampleParts ? kSampleParts : (int)room;
+  hipLaunchKernelGGL(k_group, dim3(1 + (unsigned)scatterers + (unsigned)(nq * parts)), dim3(kGroupThreads), 0, s, D, (int)nq,
                      nprobe, max_nprobe, k, Q, (uint32_t)item_budget,
                      (uint32_t)(sh.grid / (int)kXcds * sh.items_per_wg), (uint32_t)sh.tile_q, (uint32_t)sh.seg_base, sh.min_choice,
-                     scatterers, S);
+                     scatterers, parts, S);
 }
 
 }  // namespace rtams

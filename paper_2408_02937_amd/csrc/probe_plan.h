@@ -231,6 +231,7 @@ __device__ __forceinline__ void probe_plan(const Dev &D, int64_t nq, int q, int 
     }
     S.qbase[q] = base;
     S.qtotal[q] = (uint32_t)tot;
+    if (!DIRECT && D.nlist >= 32) S.done_count[q] = 0u;  // (the static array and a recorded request's slice may hold anything)
   }
 }
 

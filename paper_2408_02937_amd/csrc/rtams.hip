@@ -588,7 +588,7 @@ int rtams_create(const rtams_config *cfg, rtams_index **out) {
     const bool lines = cfg->nlist >= 16;  // a query's row of scores holds a cache line
     S.rec_cnt = reinterpret_cast<uint32_t *>(p + (lines ? SL.scores : SL.rec_cnt));
     S.rec_shift = lines ? 5 : 0;
-    S.small_count = reinterpret_cast<uint32_t *>(p + SL.rec_cnt);  // (free where the counters have lines; small requests need 32 lists)
+    S.done_count = reinterpret_cast<uint32_t *>(p + SL.rec_cnt);  // (free where the counters have lines; who counts here needs 32 lists)
     S.cursor = reinterpret_cast<unsigned long long *>(p + SL.cursor);
     S.list_cnt = reinterpret_cast<uint32_t *>(p + SL.list_cnt);
     S.pair_start = reinterpret_cast<uint32_t *>(p + SL.pair_start);

@@ -33,7 +33,7 @@ struct SearchScratch {
   uint32_t *bound;      // [max_batch] key of the score the scan compares with
   float *qnorm;         // [max_batch] squared norms of the queries (norm form of the squared distance)
   u32x4 *qhalf;         // the queries as halves for the matrix-core coarse scores, then their RowMeta (coarse_mfma.hip)
-  uint32_t *small_count; // [max_batch] workgroups of a query's coarse scores that are done (small.hip; 0 between requests)
+  uint32_t *done_count; // [max_batch] workgroups of a query that are done with their part of it (small.hip, bound.h; 0 between requests)
   uint32_t *rec_cnt;    // survivors recorded so far, of query q at rec_cnt[q << rec_shift] (rec_count())
   int rec_shift;
   unsigned long long *cursor; // bump pointer into the survivor records

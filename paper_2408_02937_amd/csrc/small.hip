@@ -31,15 +31,15 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_front(Dev D, int64_t nq
   __syncthreads();                                  // ... and so are everybody's before the workgroup counts itself off
   if (splits > 1) {  // uniform
     if (threadIdx.x == 0) {
-      s_last = atomicAdd(&S.small_count[q], 1u) + 1u == (uint32_t)splits;
-      if (s_last) S.small_count[q] = 0u;  // for the next request
+      s_last = atomicAdd(&S.done_count[q], 1u) + 1u == (uint32_t)splits;
+      if (s_last) S.done_count[q] = 0u;  // for the next request
     }
     __syncthreads();
     if (!s_last) return;  // uniform: the last one goes on
   }
   probe_plan<false, MINE, true>(D, nq, q, nprobe, max_nprobe, S, Q, nullptr, *reinterpret_cast<ProbeShared<false> *>(s_raw));
   __syncthreads();  // the plan is read below by other threads, and its LDS is used again
-  sample_bound<false>(D, q, nprobe, max_nprobe, k, Q, S, s_raw);
+  sample_bound<false>(D, q, nprobe, max_nprobe, k, Q, S, s_raw, 0u, 1u);
 }
 
 // Workgroup `part` of the `parts` of query q: its wavefronts take every (parts x wavefronts)-th unit of G groups of the
