@@ -124,34 +124,60 @@ __device__ uint32_t sample_scores(const Dev &D, int nprobe, int max_nprobe, int 
 }
 
 // The same sample over product-quantiser codes: a vector's score is the sum, in the order of the
-// sub-spaces, of the request's table entries that its codes name (the table stays in global
-// memory here: a few thousand look-ups per query).
+// sub-spaces, of the entries of the query's table (in LDS) that its codes name.  What a wavefront needs of its group of
+// the nearest list is read ahead by the caller, while the table is made: five trips to memory, one behind the other.
+constexpr int kPqAhead = 4;  // words of codes of a vector
+struct PqNearest {
+  int list;
+  uint32_t len, nblk;
+  uint32_t code[kPqAhead];
+};
+__device__ __forceinline__ const uint32_t *pq_group(const Dev &D, int list, uint32_t g) {
+  const uint32_t gpb = (uint32_t)D.groups_per_block, b = (uint32_t)*table_entry(D, list, g / gpb);
+  return block_codes(D, b) + (size_t)(g % gpb) * (D.pq_m / 4) * kWave + (threadIdx.x & (kWave - 1));
+}
+__device__ __forceinline__ PqNearest pq_nearest(const Dev &D, int max_nprobe, int q, const SearchScratch &S) {
+  const size_t o = (size_t)q * max_nprobe;
+  PqNearest first{S.probe_list[o], S.probe_len[o], 0u, {}};
+  first.nblk = D.nblk[first.list];
+  const uint32_t g = threadIdx.x / kWave;
+  if (g < min((first.len + kWave - 1) / kWave, first.nblk * (uint32_t)D.groups_per_block)) {  // uniform over the wavefront
+    const uint32_t *x = pq_group(D, first.list, g);
+#pragma unroll
+    for (int c = 0; c < kPqAhead; ++c) first.code[c] = x[(size_t)min(c, D.pq_m / 4 - 1) * kWave];
+  }
+  return first;
+}
 __device__ void pq_sample_scores(const Dev &D, int nprobe, int max_nprobe, int q, uint32_t want_groups,
-                                 const SearchScratch &S, uint32_t *skey) {
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+                                 const SearchScratch &S, const float *lut, const PqNearest &first, uint32_t *skey) {
+  const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int words = D.pq_m / 4;
-  const float *lut = S.lut + (size_t)q * D.pq_m * 256;
-  const uint32_t gpb = (uint32_t)D.groups_per_block;
   uint32_t g_first = 0;
   for (int p = 0; p < nprobe && g_first < want_groups; ++p) {  // uniform over the workgroup
     const size_t o = (size_t)q * max_nprobe + p;
-    const int list = S.probe_list[o];
-    const uint32_t len = S.probe_len[o];
+    const int list = p == 0 ? first.list : S.probe_list[o];
+    const uint32_t len = p == 0 ? first.len : S.probe_len[o];
     uint32_t groups = (len + kWave - 1) / kWave;
-    const uint32_t have = D.nblk[list] * gpb;  // never index the block table past the chain
+    const uint32_t have = (p == 0 ? first.nblk : D.nblk[list]) * (uint32_t)D.groups_per_block;  // never index the block table past the chain
     if (groups > have) groups = have;
     if (groups > want_groups - g_first) groups = want_groups - g_first;
-    for (uint32_t g = (uint32_t)wave; g < groups; g += blockDim.x / kWave) {
-      const uint32_t b = (uint32_t)*table_entry(D, list, g / gpb);
-      const uint32_t *__restrict__ x = block_codes(D, b) + (size_t)(g % gpb) * words * kWave + lane;
+    for (uint32_t g = wave; g < groups; g += blockDim.x / kWave) {
+      const bool ahead = p == 0 && g == wave;  // uniform over the wavefront
+      const uint32_t *__restrict__ x = ahead && words <= kPqAhead ? nullptr : pq_group(D, list, g);
       float acc = 0.f;
-      for (int c = 0; c < words; ++c) {
-        const uint32_t w = x[(size_t)c * kWave];
-        const float *t = lut + (size_t)c * 4 * 256;
-        acc += t[w & 255u];
-        acc += t[256 + ((w >> 8) & 255u)];
-        acc += t[512 + ((w >> 16) & 255u)];
-        acc += t[768 + (w >> 24)];
+      for (int c0 = 0; c0 < words; c0 += kPqAhead) {
+        uint32_t w[kPqAhead];
+#pragma unroll
+        for (int c = 0; c < kPqAhead; ++c) w[c] = ahead && c0 == 0 ? first.code[c] : x[(size_t)min(c0 + c, words - 1) * kWave];
+#pragma unroll
+        for (int c = 0; c < kPqAhead; ++c)
+          if (c0 + c < words) {
+            const float *t = lut + (size_t)(c0 + c) * 4 * 256;
+            acc += t[w[c] & 255u];
+            acc += t[256 + ((w[c] >> 8) & 255u)];
+            acc += t[512 + ((w[c] >> 16) & 255u)];
+            acc += t[768 + (w[c] >> 24)];
+          }
       }
       const uint32_t v = g * kWave + lane;
       skey[(size_t)(g_first + g) * kWave + lane] =
@@ -161,9 +187,10 @@ __device__ void pq_sample_scores(const Dev &D, int nprobe, int max_nprobe, int q
   }
 }
 
-// LDS of a bound: the query (d <= 2048) and the keys of the sample.  The caller owns it, so that a
+// LDS of a bound: the query (d <= 2048; none where a table is) and the keys of the sample.  The caller owns it, so that a
 // kernel whose workgroups do different jobs can use the same bytes for each.
 constexpr size_t kBoundLdsBytes = 512 * sizeof(float4) + kSampleMax * sizeof(uint32_t);
+constexpr size_t kPqBoundLdsBytes = kSampleMax * sizeof(uint32_t);
 
 // A request of few queries leaves compute units idle while one of them reads a sample of wide vectors or of a long list:
 // up to kSampleParts workgroups read it then (part of parts), leave the keys in the row of the query's approximate scores,
@@ -177,16 +204,17 @@ constexpr uint32_t kSplitChunks = 512;
 
 template <bool PQ>
 __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, int k, const float *__restrict__ Q,
-                             const SearchScratch &S, unsigned char *lds, uint32_t part, uint32_t parts) {
+                             const SearchScratch &S, unsigned char *lds, uint32_t part, uint32_t parts,
+                             const float *lut = nullptr, const PqNearest &nearest = PqNearest{}) {
   float4 *qv = reinterpret_cast<float4 *>(lds);
-  uint32_t *skey = reinterpret_cast<uint32_t *>(lds + 512 * sizeof(float4));
+  uint32_t *skey = reinterpret_cast<uint32_t *>(lds + (PQ ? 0 : 512 * sizeof(float4)));
   __shared__ __attribute__((aligned(8))) uint32_t hist[kSelectLdsWords];
   __shared__ uint32_t bc[4];
   const int tid = threadIdx.x;
   // what decides how the workgroup goes on, all on its way at once
   const size_t o0 = (size_t)q * max_nprobe;
   const uint32_t qtotal = S.qtotal[q];
-  NearestList first{PQ ? 0 : S.probe_list[o0], S.probe_len[o0], 0u, 0};
+  NearestList first{PQ ? 0 : S.probe_list[o0], PQ ? nearest.len : S.probe_len[o0], 0u, 0};
   // |q|^2 for the norm form of the squared distance (the first wavefront computes it, in double)
   const bool norm_form = !PQ && uses_norm_form(D);
   __shared__ float s_qn;
@@ -242,7 +270,7 @@ __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, in
   for (int i = tid; i < (int)(want_groups * kWave); i += (int)blockDim.x) skey[i] = 0xFFFFFFFFu;
   __syncthreads();
   if (PQ) {
-    pq_sample_scores(D, nprobe, max_nprobe, q, want_groups, S, skey);
+    pq_sample_scores(D, nprobe, max_nprobe, q, want_groups, S, lut, nearest, skey);
   } else {
     uint32_t *gkey = parts > 1 ? reinterpret_cast<uint32_t *>(S.approx) + (size_t)q * D.nlist : nullptr;
     uint32_t groups;
