@@ -196,11 +196,12 @@ constexpr size_t kPqBoundLdsBytes = kSampleMax * sizeof(uint32_t);
 // up to kSampleParts workgroups read it then (part of parts), leave the keys in the row of the query's approximate scores,
 // which nobody needs any more, and the last one goes on.  One compute unit reads 40 to 60 GB/s however much it asks for at
 // once; this launch, with one workgroup to a query and with several, whole turns in both (us): 64 queries over lists of 610 x
-// 768 floats, samples of 1,536 chunks of 1 KiB, 34.8 / 20.9; 128 queries over lists of 2,441 x 96, up to 1,000 chunks, 51.4 /
-// 42.0; 32 queries over lists of 1,000 x 128, 256 chunks, 15.9 / 16.5, so such a sample is left to one.
+// 768 floats, samples of 1,536 chunks of 1 KiB, 34.8 / 20.9; 128 queries over lists of 2,441 x 96, 192 to 1,000 chunks, 51.4 /
+// 27.1 (41.3 where those of 512 and more are shared, 32.1 from 320, 28.2 from 200); 32 queries over lists of 1,000 x 128, 256
+// chunks, a single turn of the wavefronts, 15.9 / 16.5, so such a sample is left to one.
 constexpr int kComputeUnits = 256;
 constexpr int kSampleParts = 4;
-constexpr uint32_t kSplitChunks = 512;
+constexpr uint32_t kSplitChunks = 260;
 
 template <bool PQ>
 __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, int k, const float *__restrict__ Q,
