@@ -219,6 +219,7 @@ struct Resource {
   hipEvent_t t0 = nullptr, t1 = nullptr;  // around the grouped scan when profiling is on
   hipEvent_t scan_done = nullptr;         // behind the scan of the slot's request (large requests queue up their scans)
   bool timed = false;
+  bool small = false;                     // its last request went without a plan
   SearchScratch s{};
 };
 
@@ -787,6 +788,13 @@ static int check_search_args(rtams_index *ix, int64_t nq, const float *d_queries
   return RTAMS_OK;
 }
 
+// The scratch of a small request: its survivor counters lie in the room of the approximate scores, as that of the exact ones,
+// where a planned request has them, is in use while the bounds are set.
+static SearchScratch small_scratch(SearchScratch S) {
+  S.rec_cnt = reinterpret_cast<uint32_t *>(S.approx);
+  return S;
+}
+
 // The selection of a request whose scan is enqueued, and the end of the request.
 static int finish_search(rtams_index *ix, const Dev &D, const SearchScratch &S, int r, int64_t nq, const float *d_queries, int32_t k, int32_t nprobe,
                          float *d_out_dist, int64_t *d_out_ids, hipStream_t s) {
@@ -832,13 +840,12 @@ static int search_on(rtams_index *ix, int r, int64_t nq, const float *d_queries,
   const int64_t longest = longest_list_bound(ix);
   const bool small = !recorded && r < ix->n_res && ix->small_requests.load(std::memory_order_relaxed) != 0 &&
                      !searches_by_filter(ix, nq) && small_request(D, nq, nprobe, ix->ntotal_host / ix->cfg.nlist + 1, longest);
+  ix->res[r].small = small;
   if (small) {
     const int64_t size = D.scan_single ? kWave : 2 * kWave;
     const int64_t units = std::min(ix->ntotal_host / size + nprobe, nprobe * (longest / size + 1));
     const int64_t usual = nprobe * (avg_groups * kWave / size + 1) * 5 / 4 + longest / size;
-    // the survivor counters lie in the room of the approximate scores: that of the exact ones is in use while the bounds are set
-    SearchScratch own = S;
-    own.rec_cnt = reinterpret_cast<uint32_t *>(S.approx);
+    const SearchScratch own = small_scratch(S);
     launch_small_front(D, nq, nprobe, ix->cfg.max_nprobe, k, d_queries, own, s);
     const bool timed = ix->profile_scan.load(std::memory_order_relaxed) != 0;
     if (timed) ix->timed_scans[0].fetch_add(1, std::memory_order_relaxed);
@@ -1231,6 +1238,18 @@ int rtams_scan_kernels(rtams_index *ix, int64_t *launches3, int reset) {
   for (int i = 0; i < 3; ++i)
     launches3[i] = reset ? ix->timed_scans[i].exchange(0, std::memory_order_relaxed)
                          : ix->timed_scans[i].load(std::memory_order_relaxed);
+  return RTAMS_OK;
+}
+
+int rtams_request_trace(rtams_index *ix, int32_t resource, int64_t nq, uint32_t *h_bounds, uint32_t *h_kept, int32_t *small) {
+  if (!ix || resource < 0 || resource > ix->n_res || nq < 0 || nq > ix->cfg.max_batch) return fail(RTAMS_EINVAL, "bad argument to request_trace");
+  if (resource == ix->n_res && (!ix->static_ok || nq > ix->static_max_batch)) return fail(RTAMS_EINVAL, "no such request on the static array");
+  const Resource &R = ix->res[resource];
+  const SearchScratch S = R.small ? small_scratch(R.s) : R.s;
+  if (small) *small = R.small ? 1 : 0;
+  if (h_bounds && nq > 0) HIP_TRY(hipMemcpy(h_bounds, S.bound, (size_t)nq * 4, hipMemcpyDeviceToHost));
+  if (h_kept && nq > 0)
+    HIP_TRY(hipMemcpy2D(h_kept, 4, S.rec_cnt, (size_t)4 << S.rec_shift, 4, (size_t)nq, hipMemcpyDeviceToHost));
   return RTAMS_OK;
 }
 

@@ -31,6 +31,7 @@ SYMBOLS = [
     "rtams_poll_error", "rtams_clear_error", "rtams_last_error", "rtams_set_param", "rtams_scan_time",
     "rtams_copy_plain", "rtams_read_plain", "rtams_set_codebooks", "rtams_list_export_codes",
     "rtams_search_noalloc", "rtams_overflow_bytes_for", "rtams_scan_kernels",
+    "rtams_request_trace",
 ]
 
 
@@ -104,6 +105,7 @@ def lib():
         L.rtams_set_param.argtypes = [vp, C.c_char_p, i64]
         L.rtams_scan_time.argtypes = [vp, C.POINTER(C.c_double), C.POINTER(i64), C.c_int]
         L.rtams_scan_kernels.argtypes = [vp, C.POINTER(i64), C.c_int]
+        L.rtams_request_trace.argtypes = [vp, i32, i64, vp, vp, C.POINTER(i32)]
         L.rtams_copy_plain.argtypes = [vp, vp, C.c_size_t, vp]
         L.rtams_read_plain.argtypes = [vp, C.c_size_t, vp, vp]
         _lib = L
@@ -337,6 +339,14 @@ class Index:
         n = (C.c_int64 * 3)()
         _chk(lib().rtams_scan_kernels(self._h, n, int(reset)), "rtams_scan_kernels")
         return {"k_scan": n[0], "k_scan_mm": n[1], "k_pq_scan": n[2]}
+
+    def request_trace(self, nq: int, resource: int = 0):
+        """What the last request on a stream resource left behind, once it is done: the keys of its queries' bounds, the
+        number of candidates the scan kept of each (uint32 tensors on the host), and whether it went without a plan."""
+        bounds, kept, small = torch.empty(nq, dtype=torch.uint32), torch.empty(nq, dtype=torch.uint32), C.c_int32()
+        _chk(lib().rtams_request_trace(self._h, resource, nq, bounds.data_ptr(), kept.data_ptr(), C.byref(small)),
+             "rtams_request_trace")
+        return bounds, kept, bool(small.value)
 
     def set_param(self, key: str, value: int) -> None:
         _chk(lib().rtams_set_param(self._h, key.encode(), value), "rtams_set_param")
