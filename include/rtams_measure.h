@@ -28,10 +28,11 @@ int rtams_scan_kernels(rtams_index *ix, int64_t *launches3, int reset);
 /* What the last request on a stream resource left in its scratch (0 .. n_resources - 1; n_resources is the static
  * array of rtams_search_noalloc, which the next request of any index overwrites), for tests of how requests are
  * answered.  Per query of its nq: h_bounds the pruning bound as the key the scan compared with (0xFFFFFFFF: every
- * candidate kept), h_kept the number of candidates the scan kept.  *small: 1 where the request went without a plan
- * ("small_requests").  Any pointer may be NULL.  The caller has waited for the request. */
+ * candidate kept), h_kept the number of candidates the scan kept.  *path, how it was scanned: 0 by the vector unit from
+ * a plan, 1 by the vector unit without one ("small_requests"), 2 by the matrix cores in floats, 3 by their 16-bit
+ * instructions, 4 over product-quantiser codes.  Any pointer may be NULL.  The caller has waited for the request. */
 int rtams_request_trace(rtams_index *ix, int32_t resource, int64_t nq, uint32_t *h_bounds, uint32_t *h_kept,
-                        int32_t *small);
+                        int32_t *path);
 /* A plain device-to-device copy kernel
  * (bytes a multiple of 16).  Profiler counters of HBM traffic are scaled by
  * what they read for this kernel, whose traffic is known. */

@@ -219,7 +219,7 @@ struct Resource {
   hipEvent_t t0 = nullptr, t1 = nullptr;  // around the grouped scan when profiling is on
   hipEvent_t scan_done = nullptr;         // behind the scan of the slot's request (large requests queue up their scans)
   bool timed = false;
-  bool small = false;                     // its last request went without a plan
+  int path = 0;                           // how its last request was scanned (rtams_request_trace)
   SearchScratch s{};
 };
 
@@ -840,7 +840,7 @@ static int search_on(rtams_index *ix, int r, int64_t nq, const float *d_queries,
   const int64_t longest = longest_list_bound(ix);
   const bool small = !recorded && r < ix->n_res && ix->small_requests.load(std::memory_order_relaxed) != 0 &&
                      !searches_by_filter(ix, nq) && small_request(D, nq, nprobe, ix->ntotal_host / ix->cfg.nlist + 1, longest);
-  ix->res[r].small = small;
+  ix->res[r].path = D.pq_m > 0 ? 4 : D.scan_mfma ? 1 + D.scan_mfma : small ? 1 : 0;
   if (small) {
     const int64_t size = D.scan_single ? kWave : 2 * kWave;
     const int64_t units = std::min(ix->ntotal_host / size + nprobe, nprobe * (longest / size + 1));
@@ -1241,12 +1241,12 @@ int rtams_scan_kernels(rtams_index *ix, int64_t *launches3, int reset) {
   return RTAMS_OK;
 }
 
-int rtams_request_trace(rtams_index *ix, int32_t resource, int64_t nq, uint32_t *h_bounds, uint32_t *h_kept, int32_t *small) {
+int rtams_request_trace(rtams_index *ix, int32_t resource, int64_t nq, uint32_t *h_bounds, uint32_t *h_kept, int32_t *path) {
   if (!ix || resource < 0 || resource > ix->n_res || nq < 0 || nq > ix->cfg.max_batch) return fail(RTAMS_EINVAL, "bad argument to request_trace");
   if (resource == ix->n_res && (!ix->static_ok || nq > ix->static_max_batch)) return fail(RTAMS_EINVAL, "no such request on the static array");
   const Resource &R = ix->res[resource];
-  const SearchScratch S = R.small ? small_scratch(R.s) : R.s;
-  if (small) *small = R.small ? 1 : 0;
+  const SearchScratch S = R.path == 1 ? small_scratch(R.s) : R.s;
+  if (path) *path = R.path;
   if (h_bounds && nq > 0) HIP_TRY(hipMemcpy(h_bounds, S.bound, (size_t)nq * 4, hipMemcpyDeviceToHost));
   if (h_kept && nq > 0)
     HIP_TRY(hipMemcpy2D(h_kept, 4, S.rec_cnt, (size_t)4 << S.rec_shift, 4, (size_t)nq, hipMemcpyDeviceToHost));

@@ -342,11 +342,11 @@ class Index:
 
     def request_trace(self, nq: int, resource: int = 0):
         """What the last request on a stream resource left behind, once it is done: the keys of its queries' bounds, the
-        number of candidates the scan kept of each (uint32 tensors on the host), and whether it went without a plan."""
-        bounds, kept, small = torch.empty(nq, dtype=torch.uint32), torch.empty(nq, dtype=torch.uint32), C.c_int32()
-        _chk(lib().rtams_request_trace(self._h, resource, nq, bounds.data_ptr(), kept.data_ptr(), C.byref(small)),
+        number of candidates the scan kept of each (uint32 tensors on the host), and how it was scanned."""
+        bounds, kept, path = torch.empty(nq, dtype=torch.uint32), torch.empty(nq, dtype=torch.uint32), C.c_int32()
+        _chk(lib().rtams_request_trace(self._h, resource, nq, bounds.data_ptr(), kept.data_ptr(), C.byref(path)),
              "rtams_request_trace")
-        return bounds, kept, bool(small.value)
+        return bounds, kept, ("k_scan", "k_scan_small", "k_scan_mm", "k_scan_mm narrow", "k_pq_scan")[path.value]
 
     def set_param(self, key: str, value: int) -> None:
         _chk(lib().rtams_set_param(self._h, key.encode(), value), "rtams_set_param")
