@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstring>
 #include <deque>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <shared_mutex>
@@ -1248,8 +1249,12 @@ int rtams_request_trace(rtams_index *ix, int32_t resource, int64_t nq, uint32_t 
   const SearchScratch S = R.path == 1 ? small_scratch(R.s) : R.s;
   if (path) *path = R.path;
   if (h_bounds && nq > 0) HIP_TRY(hipMemcpy(h_bounds, S.bound, (size_t)nq * 4, hipMemcpyDeviceToHost));
-  if (h_kept && nq > 0)
-    HIP_TRY(hipMemcpy2D(h_kept, 4, S.rec_cnt, (size_t)4 << S.rec_shift, 4, (size_t)nq, hipMemcpyDeviceToHost));
+  if (h_kept && nq > 0) {
+    std::unique_ptr<uint32_t[]> rows(new (std::nothrow) uint32_t[(size_t)nq << S.rec_shift]);
+    if (!rows) return fail(RTAMS_EINVAL, "out of host memory");
+    HIP_TRY(hipMemcpy(rows.get(), S.rec_cnt, ((size_t)nq << S.rec_shift) * 4, hipMemcpyDeviceToHost));
+    for (int64_t q = 0; q < nq; ++q) h_kept[q] = rows[(size_t)q << S.rec_shift];
+  }
   return RTAMS_OK;
 }
 
