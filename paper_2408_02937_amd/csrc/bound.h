@@ -17,8 +17,9 @@ constexpr int kNoBoundBelow = 4096;  // candidates of a query up to which the sc
 // of a sample of its candidates (the first few groups of its nearest probed
 // lists, where most of its neighbours are).  The k-th best of any k or more
 // candidates cannot be better than the final k-th best, so keeping what is not
-// worse than the bound loses nothing.  One workgroup per query: a wavefront per
-// group of 64 vectors, lane = vector, scores to LDS, radix selection there.
+// worse than the bound loses nothing.  One workgroup to a query, or several that
+// share its sample (below): a wavefront per group of 64 vectors, lane = vector,
+// scores to LDS, radix selection there.
 // These workgroups run beside the one that groups the pairs (same launch): both
 // need only the plan, and the scan needs both.
 // What the sample needs of the nearest list, read ahead by the caller (every one of these is a round
@@ -193,12 +194,15 @@ constexpr size_t kBoundLdsBytes = 512 * sizeof(float4) + kSampleMax * sizeof(uin
 constexpr size_t kPqBoundLdsBytes = kSampleMax * sizeof(uint32_t);
 
 // A request of few queries leaves compute units idle while one of them reads a sample of wide vectors or of a long list:
-// up to kSampleParts workgroups read it then (part of parts), leave the keys in the row of the query's approximate scores,
+// three or kSampleParts workgroups read it then (part of parts), leave the keys in the row of the query's approximate scores,
 // which nobody needs any more, and the last one goes on.  One compute unit reads 40 to 60 GB/s however much it asks for at
-// once; this launch, with one workgroup to a query and with several, whole turns in both (us): 64 queries over lists of 610 x
-// 768 floats, samples of 1,536 chunks of 1 KiB, 34.8 / 20.9; 128 queries over lists of 2,441 x 96, 192 to 1,000 chunks, 51.4 /
-// 27.1 (41.3 where those of 512 and more are shared, 32.1 from 320, 28.2 from 200); 32 queries over lists of 1,000 x 128, 256
-// chunks, a single turn of the wavefronts, 15.9 / 16.5, so such a sample is left to one.
+// once; this launch, with one workgroup to a query and with several (us): 64 queries over lists of 610 x 768 floats, samples
+// of 1,536 chunks of 1 KiB, 34.8 / 20.9; 128 queries over lists of 2,441 x 96, 192 to 1,000 chunks, 51.4 / 27.1.
+// Whole requests, shared against not, 32 probes: samples of eight groups 0.93 to 0.99 of the time from 512 chunks up to 64
+// queries and 0.99 to 1.01 at 120 to 160, from 288 to 400 chunks 0.98 to 1.01; of a quarter of lists of 3,600 x 96, 336
+// chunks, 0.96 to 0.98 at 120 to 160; eight groups of 256 chunks and fewer 1.00 to 1.04, so such a sample is left to one:
+// the hand-over between the workgroups is a microsecond.  Two workgroups to a query (168 queries and more) are 1 to 1.5 %
+// behind one.
 constexpr int kComputeUnits = 256;
 constexpr int kSampleParts = 4;
 constexpr uint32_t kSplitChunks = 260;
@@ -230,21 +234,25 @@ __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, in
   }
   // A query with no more candidates than the selection holds in LDS at once needs no bound.  For
   // inner products neither does one whose records cost less than a sample would: the sample is 512
-  // vectors or more read by one workgroup (80 us at d = 768), a record is 8 bytes (short lists, wide
-  // vectors).  (For L2 the bound also lets the scan stop early, which is worth the sample.)
+  // vectors or more, a record is 8 bytes (short lists, wide vectors).  Requests of 1 to 256 queries without a bound against
+  // with one, up to 32 d candidates: d 256 0.93 to 1.12 of the time, d 384 0.92 to 1.16, d 768 0.56 to 1.08, d 1024 0.52 to
+  // 1.14, the large ones where long lists meet few of the candidates.  (For L2 the bound also lets the scan stop early,
+  // which is worth the sample.)
   const uint32_t no_bound_below =
       D.metric == 0 ? (uint32_t)kNoBoundBelow : max((uint32_t)kNoBoundBelow, 32u * (uint32_t)D.d);
-  if (qtotal <= no_bound_below) {  // uniform over the workgroup
+  auto keep_everything = [&]() {
     if (tid == 0 && part == 0) {
       S.bound[q] = 0xFFFFFFFFu;
       *rec_count(S, (uint32_t)q) = 0u;
     }
+  };
+  if (qtotal <= no_bound_below) {  // uniform over the workgroup
+    keep_everything();
     return;
   }
   // sample size: 4 k, at least 512 and at least a fraction of the nearest list (the longer that
-  // list, the more candidates a given score admits), at most kSampleMax and at most 1 MiB of
-  // vectors (one workgroup reads the sample: a hot list of wide vectors would hold up the scan),
-  // in whole groups
+  // list, the more candidates a given score admits), at most kSampleMax and, but for the 512, at most
+  // 1 MiB of vectors (with the rounding below a third more; a hot list of wide vectors would hold up the scan), in whole groups
   uint32_t cap = PQ ? (uint32_t)kSampleMax : ((1u << 20) / ((uint32_t)D.vchunks * 16u)) & ~(uint32_t)(kWave - 1);
   cap = cap < 512u ? 512u : (cap > (uint32_t)kSampleMax ? (uint32_t)kSampleMax : cap);
   uint32_t want = (uint32_t)k * 4u;
@@ -257,11 +265,32 @@ __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, in
       if (part) return;  // uniform, and the same for all workgroups of the query
       parts = 1;
     }
-    // whole turns of the wavefronts, a group to each (128 queries over lists of 2,441, ten groups: the last two were a turn of their own)
-    const uint32_t turn = blockDim.x / kWave * parts;
-    want_groups = max((want_groups + turn / 2) / turn * turn, min(want_groups, 512u / kWave));
-    want_groups = min(want_groups, (uint32_t)kSampleMax / kWave);
-    if (parts > 1) want_groups = min(want_groups, (uint32_t)D.nlist / kWave);
+    // One workgroup takes the nearest number of whole turns of its wavefronts, a group to each (256 queries over lists of
+    // 2,441, ten groups: the last two were a turn of their own), but no fewer than 2 k or the cap come to: a sample of fewer
+    // than k vectors is no bound at all (256 queries, k 600, lists of 1,560 x 400: 557 us a request without one, 455 with).
+    // What several share is not rounded: up to whole turns of theirs, eight groups became sixteen for two workgroups (200
+    // queries over lists of 600 x 384: 305 us, 279 with eight left to one).  And 2 k is enough for them (64 queries over
+    // lists of 364 x 300, k 200: 159 us with eight groups, 165 with 4 k's thirteen; k 500: 234 with eight, 206 with thirteen).
+    const uint32_t least = max(512u, (uint32_t)k * 2u);
+    if (parts == 1) {
+      const uint32_t turn = blockDim.x / kWave, whole = (want_groups + turn / 2) / turn * turn;
+      want_groups = min(max(whole, min(want_groups, (least + kWave - 1) / kWave)), (uint32_t)kSampleMax / kWave);
+    } else {
+      want_groups = min(want_groups, (max(least, share) + kWave - 1) / kWave);
+    }
+    // a sample of fewer than k vectors (lists end inside a group) is no bound and need not be read
+    if ((uint32_t)k * 2u > want_groups * kWave) {  // uniform
+      uint32_t groups = 0, vectors = 0;
+      for (int p = 0; p < nprobe && groups < want_groups; ++p) {
+        const uint32_t len = S.probe_len[o0 + p], take = min((len + kWave - 1) / kWave, want_groups - groups);
+        groups += take;
+        vectors += min(len, take * kWave);
+      }
+      if (vectors < (uint32_t)k) {
+        keep_everything();
+        return;
+      }
+    }
     // on their way while the query and the keys are set up
     first.nblk = D.nblk[first.list];
     first.dir = table_dir(D, first.list, ((uint32_t)(tid / kWave) * parts + part) / (uint32_t)D.groups_per_block);

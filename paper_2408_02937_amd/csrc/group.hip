@@ -465,9 +465,9 @@ void launch_group(const Dev &D, int64_t nq, int nprobe, int max_nprobe, int k, c
   const ScanShape sh = scan_shape(D, item_budget);
   const int64_t pairs = nq * nprobe;
   const int scatterers = (int)(pairs <= 2048 ? 1 : pairs >= 8 * 2048 ? 8 : (pairs + 2047) / 2048);
-  // (as many workgroups to a query as are on the chip at once)
+  // (as many workgroups to a query as are on the chip at once; two are not worth their hand-over)
   const int64_t room = (2 * kComputeUnits - 1 - scatterers) / nq;
-  const int parts = room < 1 ? 1 : room > kSampleParts ? kSampleParts : (int)room;
+  const int parts = room < 3 ? 1 : room > kSampleParts ? kSampleParts : (int)room;
   hipLaunchKernelGGL(k_group, dim3(1 + (unsigned)scatterers + (unsigned)(nq * parts)), dim3(kGroupThreads), 0, s, D, (int)nq,
                      nprobe, max_nprobe, k, Q, (uint32_t)item_budget,
                      (uint32_t)(sh.grid / (int)kXcds * sh.items_per_wg), (uint32_t)sh.tile_q, (uint32_t)sh.seg_base, sh.min_choice,
