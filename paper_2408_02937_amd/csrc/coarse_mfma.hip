@@ -849,17 +849,20 @@ static TileGrid tile_grid(const Dev &D, int64_t n, int width) {
   return {(unsigned)(rows * cols), 0};
 }
 
+static constexpr size_t tile_lds(int ca) { return (size_t)kBuffers * (kTileM + 64 * ca) * kTileK * 2; }
+
+hipError_t allow_large_lds_coarse() {
+  hipError_t e = allow_lds(k_coarse_mfma<4, true>, tile_lds(4));
+  if (e == hipSuccess) e = allow_lds(k_coarse_mfma<4, false>, tile_lds(4));
+  if (e == hipSuccess) e = allow_lds(k_coarse_mfma<2, true>, tile_lds(2));
+  if (e == hipSuccess) e = allow_lds(k_coarse_mfma<2, false>, tile_lds(2));
+  return e;
+}
+
 template <int CA, bool MATRIX>
 static void launch_tiles(const Dev &D, const TileGrid &tg, int64_t n, const u32x4 *half, const RowMeta *meta, float *approx,
                          const TileCands &tc, unsigned long long *cursor, uint32_t *zero, int zero_n, hipStream_t s) {
-  constexpr size_t kLds = (size_t)kBuffers * (kTileM + 64 * CA) * kTileK * 2;
-  // above 64 KiB of dynamic LDS a kernel has to be told; once per kernel and process
-  static const bool once = [] {
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(k_coarse_mfma<CA, MATRIX>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds) == hipSuccess;
-  }();
-  (void)once;
-  hipLaunchKernelGGL((k_coarse_mfma<CA, MATRIX>), dim3(tg.blocks), dim3(kMfmaThreads), kLds, s, D, n, half, meta, approx, tc,
+  hipLaunchKernelGGL((k_coarse_mfma<CA, MATRIX>), dim3(tg.blocks), dim3(kMfmaThreads), tile_lds(CA), s, D, n, half, meta, approx, tc,
                      tg.die_map, cursor, zero, zero_n);
 }
 

@@ -449,14 +449,13 @@ __global__ __launch_bounds__(kPqBoundThreads) void k_pq_bound(Dev D, int nprobe,
 }
 
 
+hipError_t allow_large_lds_group() { return allow_lds(k_pq_bound, 64 * 1024); }
+
 void launch_group(const Dev &D, int64_t nq, int nprobe, int max_nprobe, int k, const float *Q,
                   int item_budget, const SearchScratch &S, hipStream_t s) {
   if (nq <= 0) return;
   if (D.pq_m > 0) {
-    // (64 codes to a vector: 64 KiB, and the keys beside them; above 64 KiB in all a kernel has to be told, once)
-    static const bool once = hipFuncSetAttribute(reinterpret_cast<const void *>(k_pq_bound),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024) == hipSuccess;
-    (void)once;
+    // (64 codes to a vector: 64 KiB, and the keys beside them)
     hipLaunchKernelGGL(k_pq_bound, dim3((unsigned)nq), dim3(kPqBoundThreads), (size_t)D.pq_m * 1024, s, D, nprobe, max_nprobe, k, Q, S);
     return;
   }

@@ -194,6 +194,9 @@ __global__ __launch_bounds__(kPqScanThreads, 8) void k_pq_scan(Dev D, int nprobe
 }
 
 
+// (64 codes to a vector: 64 KiB, and the kernel's own 8)
+hipError_t allow_large_lds_pq_scan() { return allow_lds(k_pq_scan, 64 * 1024); }
+
 void launch_pq_scan(const Dev &D, int64_t nq, int nprobe, int max_nprobe, int item_budget,
                     const SearchScratch &S, hipStream_t s) {
   if (nq <= 0) return;
@@ -201,9 +204,6 @@ void launch_pq_scan(const Dev &D, int64_t nq, int nprobe, int max_nprobe, int it
   int parts = (int)(item_budget / (nq * 32));
   parts = parts < 1 ? 1 : (parts > 64 ? 64 : parts);
   const size_t lds = (size_t)D.pq_m * 256 * sizeof(float);
-  if (lds > 48 * 1024)  // with the kernel's own 8 KiB this passes the default limit of a workgroup
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k_pq_scan),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   hipLaunchKernelGGL(k_pq_scan, dim3((unsigned)(nq * parts)), dim3(kPqScanThreads), lds, s, D, nprobe,
                      max_nprobe, parts, S);
 }

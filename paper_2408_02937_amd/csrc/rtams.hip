@@ -212,6 +212,22 @@ int static_scratch_of_current_device(void **out) {
   return RTAMS_OK;
 }
 
+bool g_lds_allowed[kMaxDevices] = {};  // (under g_static_mutex)
+
+int allow_large_lds_on_current_device() {
+  int dev = -1;
+  HIP_TRY(hipGetDevice(&dev));
+  if (dev < 0 || dev >= kMaxDevices) return fail(RTAMS_EINVAL, "device %d outside 0..%d", dev, kMaxDevices - 1);
+  std::lock_guard<std::mutex> g(g_static_mutex);
+  if (g_lds_allowed[dev]) return RTAMS_OK;
+  HIP_TRY(allow_large_lds_coarse());
+  HIP_TRY(allow_large_lds_group());
+  HIP_TRY(allow_large_lds_scan_mm());
+  HIP_TRY(allow_large_lds_pq_scan());
+  g_lds_allowed[dev] = true;
+  return RTAMS_OK;
+}
+
 enum { RES_FREE = 0, RES_BUSY = 1, RES_PENDING = 2 };
 
 struct Resource {
@@ -474,6 +490,8 @@ int rtams_create(const rtams_config *cfg, rtams_index **out) {
   if (slice < SL.fixed + kAlign)
     return fail(RTAMS_EINVAL, "scratch slice of %zu bytes is smaller than its fixed part %zu", slice,
                 SL.fixed + kAlign);
+
+  if (const int rc = allow_large_lds_on_current_device()) return rc;
 
   rtams_index *ix = new (std::nothrow) rtams_index();
   if (!ix) return fail(RTAMS_EINVAL, "out of host memory");

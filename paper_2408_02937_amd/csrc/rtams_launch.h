@@ -125,6 +125,17 @@ struct RearrangeScratch {
   int32_t *vic_seq;    // [cap] its position in the owner's chain
 };
 
+// A kernel whose workgroups may take more than 64 KiB of LDS has to be told so, on every device by itself: rtams_create
+// does it for the index's.
+hipError_t allow_large_lds_coarse();
+hipError_t allow_large_lds_group();
+hipError_t allow_large_lds_scan_mm();
+hipError_t allow_large_lds_pq_scan();
+template <typename Kernel>
+inline hipError_t allow_lds(Kernel kernel, size_t bytes) {
+  return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
 // coarse.hip ---------------------------------------------------------------
 int coarse_vt(int d);                      // vectors per workgroup for this dimension
 int coarse_splits(const Dev &D, int64_t n, size_t part_cap);

@@ -626,25 +626,25 @@ __global__ __launch_bounds__(kMmWaves *kWave, STEAL || NARROW || (METRIC == 1 &&
   }
 }
 
+typedef void (*MmKernel)(Dev, int, const float *, SearchScratch, int);
+static const MmKernel mm_kernels[2][2][3] = {
+    {{k_scan_mm<0, false, 0, false>, k_scan_mm<0, false, 1, false>, k_scan_mm<0, false, 2, false>},
+     {k_scan_mm<0, true, 0, false>, k_scan_mm<0, true, 1, false>, k_scan_mm<0, true, 2, false>}},
+    {{k_scan_mm<1, false, 0, false>, k_scan_mm<1, false, 1, false>, k_scan_mm<1, false, 2, false>},
+     {k_scan_mm<1, true, 0, false>, k_scan_mm<1, true, 1, false>, k_scan_mm<1, true, 2, false>}}};
+static const MmKernel mm_narrow[2][2] = {{k_scan_mm<0, false, 1, true>, k_scan_mm<0, false, 2, true>},
+                                         {k_scan_mm<0, true, 1, true>, k_scan_mm<0, true, 2, true>}};
+
+hipError_t allow_large_lds_scan_mm() {  // (wide vectors only)
+  hipError_t e = hipSuccess;
+  for (int i = 0; i < 16 && e == hipSuccess; ++i)
+    e = allow_lds(i < 12 ? mm_kernels[i / 6][i / 3 % 2][i % 3] : mm_narrow[(i - 12) / 2][i % 2], kMmLdsMax);
+  return e;
+}
+
 void launch_scan_mm(const Dev &D, const ScanShape &sh, int max_nprobe, const float *Q, const SearchScratch &S,
                     hipStream_t s) {
-  typedef void (*Kernel)(Dev, int, const float *, SearchScratch, int);
-  static const Kernel kernels[2][2][3] = {
-      {{k_scan_mm<0, false, 0, false>, k_scan_mm<0, false, 1, false>, k_scan_mm<0, false, 2, false>},
-       {k_scan_mm<0, true, 0, false>, k_scan_mm<0, true, 1, false>, k_scan_mm<0, true, 2, false>}},
-      {{k_scan_mm<1, false, 0, false>, k_scan_mm<1, false, 1, false>, k_scan_mm<1, false, 2, false>},
-       {k_scan_mm<1, true, 0, false>, k_scan_mm<1, true, 1, false>, k_scan_mm<1, true, 2, false>}}};
-  static const Kernel narrow[2][2] = {{k_scan_mm<0, false, 1, true>, k_scan_mm<0, false, 2, true>},
-                                      {k_scan_mm<0, true, 1, true>, k_scan_mm<0, true, 2, true>}};
-  // above 64 KiB of dynamic LDS a kernel has to be told (wide vectors only); once per kernel and process
-  static const bool once = [] {
-    for (int i = 0; i < 16; ++i)
-      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(i < 12 ? kernels[i / 6][i / 3 % 2][i % 3] : narrow[(i - 12) / 2][i % 2]),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMmLdsMax);
-    return true;
-  }();
-  (void)once;
-  const Kernel kernel = scans_narrow(D) ? narrow[D.scan_steal ? 1 : 0][D.storage - 1] : kernels[D.metric][D.scan_steal ? 1 : 0][D.storage];
+  const MmKernel kernel = scans_narrow(D) ? mm_narrow[D.scan_steal ? 1 : 0][D.storage - 1] : mm_kernels[D.metric][D.scan_steal ? 1 : 0][D.storage];
   hipLaunchKernelGGL(kernel, dim3((unsigned)sh.grid), dim3((unsigned)sh.threads),
                      sh.lds, s, D, max_nprobe, Q, S, sh.tile_q);
 }
