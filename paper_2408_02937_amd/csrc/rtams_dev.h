@@ -186,7 +186,7 @@ __device__ inline size_t vec_chunk_index(const Dev &D, uint32_t moff, int c) {
 // asks for copies waits for them (the wavefront's count of loads, in front of the barrier that hands them to others),
 // and does not end before they have come.
 __device__ __forceinline__ void copy_to_lds(const void *src, uint32_t to, uint32_t lane16) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(lane16), "s"(src) : "memory");
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"{m0}"(to), "v"(lane16), "s"(src) : "memory");
 }
 __device__ __forceinline__ uint32_t lds_address(const void *p) {
   return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)p;
