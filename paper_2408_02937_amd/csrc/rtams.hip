@@ -838,7 +838,9 @@ static int search_on(rtams_index *ix, int r, int64_t nq, const float *d_queries,
     const int64_t avg_len = ix->ntotal_host / ix->cfg.nlist + 1;
     D.scan_mfma = D.pq_m == 0 && (mode == 2 || (mode == 1 && nq >= kMmMinBatch &&
                                                 mm_scan_pays(D, nq, nprobe, avg_len, longest_list(ix))));
-    if (D.scan_mfma && narrow_scan_pays(D)) D.scan_mfma = 2;
+    if (D.scan_mfma && narrow_scan_fits(D) &&
+        (mode == 2 || narrow_scan_pays(D, nq * nprobe, (double)ix->ntotal_host * D.vchunks * 16.0)))
+      D.scan_mfma = 2;
   }
   const int64_t avg_groups = ix->ntotal_host / ix->cfg.nlist / kWave + 1;
   D.scan_single = !recorded && !D.scan_mfma && D.pq_m == 0 && avg_groups <= kSingleList && nq * nprobe * avg_groups < kSingleGroups;

@@ -479,7 +479,7 @@ inline bool mm_scan_pays(const Dev &D, int64_t nq, int64_t nprobe, int64_t avg_l
   return d >= 512 ? pairs >= nlist : products >= (d <= 96 ? 1e9 : 8e9);
 }
 
-// Whether such a request over lists of halves or bytes, squared distances, scans on the 16-bit instructions (scan_mm.hip):
+// Whether such a request over lists of halves or bytes, squared distances, can scan on the 16-bit instructions (scan_mm.hip):
 // wherever the vectors are wide enough to repay the queries' splitting, and three pieces of 16 queries fit beside another
 // workgroup's in LDS.  4x4x1 / 16-bit, us a request (queries of three pieces), 256 lists:
 //  bytes, 128 queries x 32 probes, lists of 600: d 16 44 / 47, d 32 48 / 46, d 64 58 / 48, d 128 71 / 56, d 320
@@ -488,8 +488,24 @@ inline bool mm_scan_pays(const Dev &D, int64_t nq, int64_t nprobe, int64_t avg_l
 //  halves, 128 x 32, lists of 600: d 16 46 / 45, d 32 50 / 45, d 128 74 / 58, d 320 128 / 86, d 640 196 / 154;
 //    256 x 32, of 1,500: d 16 60 / 59, d 128 114 / 84, d 640 434 / 370; 64 x 8, of 1,500: d 64 49 / 50, d 128 54 /
 //    55, d 640 124 / 124
-inline bool narrow_scan_pays(const Dev &D) {
+inline bool narrow_scan_fits(const Dev &D) {
   return D.metric == 0 && D.pq_m == 0 && D.storage != 0 && D.d >= (D.storage == 2 ? 64 : 32) && D.d <= 640;
+}
+// ... and whether it should.  An instruction takes 16 queries whether they are there or not, and an item's queries are split
+// anew: a tile of few does not repay that, least of all where the lists come from HBM (past some 300 MB of them) and the
+// wider instructions run four wavefronts to a SIMD for three of these.  So it goes by the pairs to a list; hot lists, whose
+// tiles are full, make little difference to where the line lies.  4x4x1 / 16-bit, us a request, 1,623 requests of 64 to 256
+// queries x 4 to 64 probes over 64 to 4,096 lists: bytes, 1,024 lists of 4,000 x 256, 2 pairs to a list 224 / 269, 4 285 /
+// 323, 6 340 / 348; of 1,000 x 128 4 pairs 0.93 to 0.95 of the time, 8 0.78 to 0.87; halves, 1,024 of 4,000 x 256, 4 pairs 386
+// / 413, 8 428 / 449, 256 of 1,500 x 512, 8 pairs 162 / 147, 512 of 600 x 256, 4 pairs 99 / 90, x 32 55 / 58.  Bytes of 64
+// dimensions gain at any number of pairs where the lists are 60 MB and more (1,024 of 4,000, 2 pairs: 140 / 121; 512 of 600:
+// 57 / 60).  With this rule a request is at most 3 % slower than on the 4x4x1 instructions (always taken, 20 %) and on
+// average 0.2 % from the better of the two.
+inline bool narrow_scan_pays(const Dev &D, int64_t pairs, double list_bytes) {
+  const int64_t nlist = D.nlist;
+  if (D.storage == 2) return pairs > 4 * nlist || (pairs > 2 * nlist && list_bytes < 300e6) || (D.d <= 64 && list_bytes >= 60e6);
+  return pairs > 8 * nlist || (pairs == 8 * nlist && list_bytes < 500e6) ||
+         (pairs >= 4 * nlist + (D.d < 128 ? 1 : 0) && list_bytes < 300e6);
 }
 
 inline ScanShape scan_shape(const Dev &D, int item_budget) {
