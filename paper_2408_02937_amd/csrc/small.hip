@@ -8,7 +8,7 @@
 // groups of the query's lists in turn from the lengths alone.
 // 10 queries x 8 probes over 64 lists, 10,000 x 32 floats: 31.6 us back to back where the five launches took 42.7; one
 // query x 32 probes over 1,024 lists, 1 M x 128: 45.7 and 47.3.  Above kSmallBytes the scan's own time hides the
-// plan, and what several queries read of one list is read once.
+// plan, and what several queries read of one list is read once.  Wide vectors: small_request().
 #include "bound.h"
 #include "coarse_exact.h"
 #include "probe_plan.h"
@@ -74,7 +74,17 @@ __global__ __launch_bounds__(kScanWaves * kWave) void k_scan_small(Dev D, int np
 bool small_request(const Dev &D, int64_t nq, int nprobe, int64_t avg_len, int64_t longest) {
   if (D.pq_m > 0 || D.scan_mfma || D.nlist < 32 || D.nlist > 4096 || nprobe > kWave || coarse_vectors(D, nq) != 1) return false;
   // every query reads its lists for itself
-  return (double)nq * (double)(nprobe * avg_len + longest) * D.vchunks * 16.0 <= kSmallBytes;
+  if ((double)nq * (double)(nprobe * avg_len + longest) * D.vchunks * 16.0 > kSmallBytes) return false;
+  // Half as many workgroups as in a planned request read the centroids here, and one the sample of a query, which a planned
+  // request of few queries shares between four: with wide vectors that takes longer than two launches.  Small / planned, the
+  // middle and the largest of 5 to 60 requests each of 1 to 32 queries x 8 to 64 probes over 64 to 4,096 lists of 100 to
+  // 1,500 vectors, up to 32 MB: d 32 0.81 to 0.90, 1.01; d 128 0.81 to 0.95, 1.02; d 256 0.86 to 0.97, 1.00; d 512 without a
+  // bound 0.80 to 0.94, 1.00, with one and long lists of floats 1.01, 1.06, of halves and bytes 1.00, 1.04; d 768 short lists
+  // 0.81 to 0.99, 1.06, long ones 1.00 to 1.03, 1.12; d 1024 short lists 1.00 to 1.03, 1.09; d 1536 1.07 to 1.11, 1.18.
+  const bool short_lists = avg_len / kWave + 1 <= kSingleList;  // a sample is a few groups of each, shared or not
+  const int64_t no_bound_below = D.metric == 0 ? 4096 : 32 * (int64_t)D.d > 4096 ? 32 * (int64_t)D.d : 4096;
+  if (D.d > (short_lists ? 768 : 512)) return false;
+  return short_lists || D.vchunks < 96 || nprobe * avg_len <= no_bound_below;
 }
 
 void launch_small_front(const Dev &D, int64_t nq, int nprobe, int max_nprobe, int k, const float *Q, const SearchScratch &S,
@@ -98,7 +108,10 @@ void launch_scan_small(const Dev &D, int64_t nq, int nprobe, int max_nprobe, int
                                      {k_scan_small<1, 0, 2, 2>, k_scan_small<1, 1, 2, 2>, k_scan_small<1, 2, 2, 2>}};
   static const Kernel singles[2][3] = {{k_scan_small<0, 0, 1, 4>, k_scan_small<0, 1, 1, 4>, k_scan_small<0, 2, 1, 4>},
                                        {k_scan_small<1, 0, 1, 4>, k_scan_small<1, 1, 1, 4>, k_scan_small<1, 2, 1, 4>}};
-  hipLaunchKernelGGL(D.scan_single ? singles[D.metric][D.storage] : pairs[D.metric][D.storage], dim3((unsigned)(nq * parts)),
+  static const Kernel deep_singles[2] = {k_scan_small<0, 0, 1, 8>, k_scan_small<1, 0, 1, 8>};
+  const Kernel kernel = !D.scan_single ? pairs[D.metric][D.storage]
+                        : D.storage == 0 && D.vchunks % 16 == 0 ? deep_singles[D.metric] : singles[D.metric][D.storage];
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(nq * parts)),
                      dim3(kScanWaves * kWave), (size_t)kScanWaves * D.d * sizeof(float), s, D, nprobe, max_nprobe, (int)parts, Q, S);
 }
 

@@ -1,6 +1,6 @@
 """Small requests go without a plan (three launches); the same requests through the plan give the same answers bit for bit:
 number of lists around what a workgroup takes, few and many probes, empty lists, fewer candidates than k, every kind of
-list, requests of different sizes in turn on the same slices."""
+list, requests of different sizes in turn on the same slices.  Which way a request went is read back every time."""
 import pytest
 import torch
 
@@ -25,25 +25,50 @@ def build(n, d, nlist, metric, storage, T=64, hot=False, n_resources=2):
     return g, q
 
 
+def goes_small(g, n, longest, nq, nprobe):
+    """The rule: vectors of a workgroup's coarse tile, bytes the queries read, and how wide vectors may be."""
+    blocks = (g.nlist + 255) // 256
+    vt = 8 if g.d <= 768 else 4
+    while vt > 1 and (nq + vt - 1) // vt * blocks < 256:
+        vt //= 2
+    if not 32 <= g.nlist <= 4096 or nprobe > 64 or vt > 1:
+        return False
+    avg = n // g.nlist + 1
+    chunks = g.d // {"f32": 4, "f16": 8, "u8": 16}[g.storage]
+    if nq * (nprobe * avg + longest) * chunks * 16 > 32e6:
+        return False
+    short = avg // 64 + 1 <= 4
+    if g.d > (768 if short else 512):
+        return False
+    return short or chunks < 96 or nprobe * avg <= (4096 if g.metric == rtams.L2 else max(4096, 32 * g.d))
+
+
 def both(g, q, k, nprobe):
+    sizes = g.list_sizes()
+    torch.cuda.synchronize()
+    small = goes_small(g, int(sizes.sum()), int(sizes.max()), q.shape[0], nprobe)
     out = []
-    for small in (1, 0, 1):
-        g.set_param("small_requests", small)
+    for on in (1, 0, 1):
+        g.set_param("small_requests", on)
         out.append(g.search(q, k, nprobe))
         torch.cuda.synchronize()
+        assert g.request_trace(q.shape[0])[2] == ("k_scan_small" if on and small else "k_scan"), f"{q.shape[0]} x {nprobe}"
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
     assert torch.equal(out[0][0], out[2][0]) and torch.equal(out[0][1], out[2][1])
     assert g.poll_error() == 0
+    return small
 
 
 @pytest.mark.parametrize("metric", ["l2", "ip"])
 @pytest.mark.parametrize("nlist,d,n", [(32, 4, 500), (33, 32, 9000), (511, 64, 30000), (513, 128, 30000), (1025, 96, 40000),
-                                       (2049, 36, 30000), (4096, 64, 60000), (4097, 64, 60000), (700, 1536, 3000)])
+                                       (2049, 36, 30000), (4096, 64, 60000), (4097, 64, 60000), (700, 1536, 3000),
+                                       (700, 768, 3000), (700, 772, 3000), (64, 512, 30000), (64, 384, 30000), (64, 380, 30000)])
 def test_small_requests_answer_like_planned_ones(nlist, d, n, metric):
     print(f"[case] small path {metric} {n} x {d} into {nlist}", flush=True)
     g, q = build(n, d, nlist, metric, "f32")
-    for nq, k, nprobe in ((1, 100, 32), (10, 10, 8), (3, 1, 1), (7, 128, min(64, nlist)), (1, 50, min(63, nlist)), (33, 5, 2)):
-        both(g, q[:nq].contiguous(), k, nprobe)
+    took = [both(g, q[:nq].contiguous(), k, nprobe)
+            for nq, k, nprobe in ((1, 100, 32), (10, 10, 8), (3, 1, 1), (7, 128, min(64, nlist)), (1, 50, min(63, nlist)), (33, 5, 2))]
+    assert not any(took) if nlist > 4096 or d > 768 else any(took)
     g.close()
 
 
@@ -54,7 +79,8 @@ def test_small_requests_over_narrow_empty_and_hot_lists(storage, d, n, hot, metr
     print(f"[case] small path {metric} {storage} {n} hot={hot}", flush=True)
     g, q = build(n, d, 200, metric, storage, hot=hot)
     for nq, k, nprobe in ((1, 100, 32), (9, 10, 64), (2, 128, 1)):
-        both(g, q[:nq].contiguous(), k, nprobe)
+        took = both(g, q[:nq].contiguous(), k, nprobe)
+        assert took or hot
     g.close()
 
 
@@ -85,6 +111,7 @@ def test_requests_of_all_kinds_in_turn_on_several_streams():
     print("[case] small path, streams", flush=True)
     g, q = build(40000, 64, 300, "l2", "f32", n_resources=6)
     sizes = [(1, 10, 4), (40, 20, 32), (5, 100, 64), (40, 3, 1), (2, 128, 16)]
+    assert [both(g, q[:nq].contiguous(), k, nprobe) for nq, k, nprobe in sizes] == [True, False, True, True, True]
     g.set_param("small_requests", 0)
     want = []
     for nq, k, nprobe in sizes:
@@ -94,7 +121,7 @@ def test_requests_of_all_kinds_in_turn_on_several_streams():
     streams = [torch.cuda.Stream() for _ in range(4)]
     for turn in range(6):
         got = []
-        for j, (nq, k, nprobe) in enumerate(sizes[:4]):
+        for j, (nq, k, nprobe) in enumerate(sizes):
             s = streams[(turn + j) % 4]
             with torch.cuda.stream(s):
                 got.append(g.search(q[:nq], k, nprobe))
