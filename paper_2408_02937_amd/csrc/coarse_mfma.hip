@@ -262,7 +262,8 @@ __global__ __launch_bounds__(256) void k_half_rows(Dev D, int64_t n, const float
 // step's stay on their way.  Two workgroups share a compute unit, and one's waits are the other's multiplications.
 // What bounds it: inside the steps the matrix cores are busy 85 % of the clocks, and the chip lowers its clock to 1.6 to
 // 1.7 GHz under them; the reduction of a tile (6 us of the 25 that a tile of 768 dimensions is on a compute unit)
-// overlaps with the steps of the other workgroup.  28,928 x 8,192 x 768 take 370 us, 980 TFLOP/s; 424 us with
+// overlaps with the steps of the other workgroup (it keeps the masks of many comparisons at a time and spills 175 scalar
+// registers to lanes of vector registers at CA = 4, 47 at CA = 2).  28,928 x 8,192 x 768 take 370 us, 980 TFLOP/s; 424 us with
 // two buffers filled through registers a step ahead and a branch for every score in the reduction, 30 % of the LDS
 // clocks bank conflicts (the places of a row's groups covered 32 banks, not 64).
 template <int CA, bool MATRIX>
@@ -523,9 +524,11 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void k_coarse_mfma(Dev D, int64_t 
 // row and a lane or two at work this was bound by the issue of those instructions
 // (21,845 rows of 768 dimensions: 280 us).  So a workgroup reads the digests of up to
 // 64 rows first, a few lanes to a row, puts the candidates of the rows that have
-// several into a list, and then scores the list, a thread to a candidate.
-// The same with four neighbouring lanes to a candidate (all four call with the same arguments, and all have the score):
-// lane s of the four brings chunks s, s + 4, ... and works out their differences, and the chain, the same in all four,
+// several into a list, and then scores the list: four threads to a candidate while the list is no longer than the
+// workgroup, a thread to each where it is.
+
+// exact_score() below with four neighbouring lanes to a candidate (all four call with the same arguments, and all have the
+// score): lane s of the four brings chunks s, s + 4, ... and works out their differences, and the chain, the same in all four,
 // takes them from one after the other.  A lane alone waits for a trip to memory per eight chunks, 24 of them at 768
 // dimensions and next to nobody else on the compute unit; here two sets of 16 chunks take turns.  (28,928 rows of 768
 // dimensions, 38 candidates to a workgroup: the refinement 57 us with a lane to a candidate and 1,034 workgroups, 45 with

@@ -493,7 +493,7 @@ inline bool narrow_scan_fits(const Dev &D) {
 }
 // ... and whether it should.  An instruction takes 16 queries whether they are there or not, and an item's queries are split
 // anew: a tile of few does not repay that, least of all where the lists come from HBM (past some 300 MB of them) and the
-// wider instructions run four wavefronts to a SIMD for three of these.  So it goes by the pairs to a list; hot lists, whose
+// 4x4x1 instructions run four wavefronts to a SIMD where these run three.  So it goes by the pairs to a list; hot lists, whose
 // tiles are full, make little difference to where the line lies.  4x4x1 / 16-bit, us a request, 1,623 requests of 64 to 256
 // queries x 4 to 64 probes over 64 to 4,096 lists: bytes, 1,024 lists of 4,000 x 256, 2 pairs to a list 224 / 269, 4 285 /
 // 323, 6 340 / 348; of 1,000 x 128 4 pairs 0.93 to 0.95 of the time, 8 0.78 to 0.87; halves, 1,024 of 4,000 x 256, 4 pairs 386

@@ -17,6 +17,8 @@
 namespace rtams {
 
 constexpr int kSmallThreads = 512;  // eight wavefronts: the bound's sample of 512 vectors in one turn
+// (With three kernels' worth of code in one, k_small_front spills 28 to 53 scalar registers to lanes of vector registers, 169
+// of them.  At one query it takes 19 us where coarse scores, probes and bound took 4.6, 6.8 and 8.5: what is saved is launches.)
 
 template <int METRIC, int MINE>
 __global__ __launch_bounds__(kSmallThreads) void k_small_front(Dev D, int64_t nq, int nprobe, int max_nprobe, int k,

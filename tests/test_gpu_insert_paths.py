@@ -46,13 +46,39 @@ def test_batches_of_one_launch_into_narrow_lists(storage, d):
     run([1, 65, 256, 257], d, 30, "l2", False, storage)
 
 
-# list by list from 8,192 vectors; a workgroup moves 64 vectors x 16 chunks: 1, 15, 16, 17, 33 chunks of a vector
-@pytest.mark.parametrize("n", [1025, 8192, 8257])
+# list by list from 8,192 vectors, or from 2^18 chunks above 1,024; a workgroup moves 64 vectors x 16 chunks: 1, 15, 16, 17, 33
+# chunks of a vector.  1,025 narrow vectors go vector by vector
+@pytest.mark.parametrize("n", [1025, 8191, 8192, 8257])
 @pytest.mark.parametrize("storage,d", [("f32", 4), ("f32", 60), ("f32", 64), ("f32", 68), ("f32", 132), ("f16", 136), ("u8", 272)])
 @pytest.mark.parametrize("nlist,hot", [(1, True), (7, False), (2500, False)])
 def test_large_batches_list_by_list(n, storage, d, nlist, hot):
     print(f"[case] list by list {n} {storage} d={d} nlist={nlist}", flush=True)
     run([70, n, 3, n], d, nlist, "l2", hot, storage, pool_blocks=9000)
+
+
+# 192 and 64 chunks of a vector: 2^18 of them are 1,366 and 4,096 vectors
+@pytest.mark.parametrize("d,n", [(768, 1365), (768, 1366), (768, 2049), (256, 4095), (256, 4096), (256, 4200), (1024, 1025)])
+def test_fewer_vectors_list_by_list_where_they_are_wide(d, n):
+    print(f"[case] list by list, wide: {n} x {d}", flush=True)
+    run([70, n, 3, n], d, 300, "l2", False, "f32", pool_blocks=2000)
+
+
+def test_rounds_and_ids_of_the_caller_list_by_list():
+    """One call of three rounds (8,192, 8,192 and 3,616 vectors, the last by vector) with ids of its own, beside one without."""
+    print("[case] list by list, rounds and ids", flush=True)
+    rng = np.random.default_rng(12)
+    d, nlist, n = 36, 90, 20_000
+    C = rng.standard_normal((nlist, d)).astype(np.float32)
+    w = synth.Workload("rounds", "l2", d, nlist, 64, 8, 10, np.zeros((0, d), np.float32), C, np.zeros((0, d), np.float32),
+                       np.zeros((0, d), np.float32), 1, 0)
+    g, o = make_pair(w, pool_blocks=2000, candidates_per_query=16384, max_add_batch=8192)
+    for ids in (None, rng.permutation(10 * n)[:n].astype(np.int64) + (1 << 40)):
+        y = (C[rng.integers(0, nlist, n)] + 0.05 * rng.standard_normal((n, d))).astype(np.float32)
+        g.add(dev(y), None if ids is None else dev(ids)); o.add(y, ids)
+    g.validate()
+    assert_lists_equal(g, o)
+    assert g.ntotal == o.ntotal and g.poll_error() == 0
+    g.close()
 
 
 def test_a_vector_with_a_nan_joins_the_first_list_in_one_launch():

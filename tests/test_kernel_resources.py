@@ -59,10 +59,28 @@ def test_no_kernel_keeps_private_memory(records):
     assert {n: k[".private_segment_fixed_size"] for n, k in records.items() if k[".private_segment_fixed_size"]} == {}
 
 
-def test_the_selection_runs_two_workgroups_to_a_compute_unit(records):
-    mine = {n: k for n, k in records.items() if "k_select" in n}
-    assert len(mine) == 3
+# Kernels whose comments count on so many workgroups to a compute unit: four SIMDs of 512 registers (taken by the lane, in
+# eights) and 160 KiB of LDS.  Name, kernels of that name, wavefronts of a workgroup, workgroups, dynamic LDS of a workgroup.
+# The scan: four wavefronts to a SIMD in short scans but of inner products of floats, three elsewhere (LDS by the tile).
+@pytest.mark.parametrize("name,count,waves,groups,lds", [
+    ("8k_select", 3, 8, 2, 0),
+    ("7k_group", 1, 8, 2, 0),
+    ("9k_pq_scan", 1, 8, 4, 16 * 1024),             # 16 codes to a vector
+    ("10k_pq_bound", 1, 16, 1, 64 * 1024),          # 64
+    ("13k_coarse_mfmaILi4", 2, 4, 2, 3 * 384 * 64),
+    ("13k_coarse_mfmaILi2", 2, 4, 2, 3 * 256 * 64),
+    ("15k_assign_refine", 1, 4, 4, 0),
+    ("9k_scan_mmILi0ELb0ELi0ELb0", 1, 4, 4, 0),
+    ("9k_scan_mmILi0ELb0ELi1ELb0", 1, 4, 4, 0),
+    ("9k_scan_mmILi0ELb0ELi2ELb0", 1, 4, 4, 0),
+    ("9k_scan_mmILi1ELb0ELi1ELb0", 1, 4, 4, 0),
+    ("9k_scan_mmILi1ELb0ELi2ELb0", 1, 4, 4, 0),
+    ("9k_scan_mmILi", 16, 4, 3, 0),
+])
+def test_as_many_workgroups_to_a_compute_unit_as_the_comments_say(records, name, count, waves, groups, lds):
+    mine = {n: k for n, k in records.items() if name in n}
+    assert len(mine) == count
     for n, k in mine.items():
-        # 8 wavefronts of 512 threads, two workgroups on 4 SIMDs: four wavefronts a SIMD, of 512 registers
-        assert k[".vgpr_count"] <= 128, n
-        assert 2 * k[".group_segment_fixed_size"] <= 160 * 1024, n
+        wavefronts_to_a_simd = (waves * groups + 3) // 4
+        assert (k[".vgpr_count"] + 7) // 8 * 8 * wavefronts_to_a_simd <= 512, n
+        assert groups * (k[".group_segment_fixed_size"] + lds) <= 160 * 1024, n
