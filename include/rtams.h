@@ -303,8 +303,8 @@ int rtams_list_export_codes(rtams_index *ix, int32_t list, int64_t cap, int64_t 
  *                          of its share of the work items takes items from the back of another die's
  *                          share; 0: every die scans its own share only.  The result is the same.
  *   "small_requests"       1 (default): a small request over flat lists (few queries, 32 to 4,096 lists,
- *                          at most 64 probes and some 32 MB of lists in all, vectors of up to 512
- *                          dimensions, 768 over short lists) runs in three launches that make no plan
+ *                          at most 64 probes and some 32 MB of lists in all, vectors that are
+ *                          not too wide for it, by a measured rule) runs in three launches that make no plan
  *                          of the scan; 0: in five like every other.  The result is the same.
  *   "use_mfma"             whether approximate coarse scores from the matrix cores filter the
  *                          centroids before the exact arithmetic decides: 0 never, 1 for batches large

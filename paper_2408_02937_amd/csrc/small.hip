@@ -78,15 +78,22 @@ bool small_request(const Dev &D, int64_t nq, int nprobe, int64_t avg_len, int64_
   // every query reads its lists for itself
   if ((double)nq * (double)(nprobe * avg_len + longest) * D.vchunks * 16.0 > kSmallBytes) return false;
   // Half as many workgroups as in a planned request read the centroids here, and one the sample of a query, which a planned
-  // request of few queries shares between four: with wide vectors that takes longer than two launches.  Small / planned, the
-  // middle and the largest of 5 to 60 requests each of 1 to 32 queries x 8 to 64 probes over 64 to 4,096 lists of 100 to
-  // 1,500 vectors, up to 32 MB: d 32 0.81 to 0.90, 1.01; d 128 0.81 to 0.95, 1.02; d 256 0.86 to 0.97, 1.00; d 512 without a
-  // bound 0.80 to 0.94, 1.00, with one and long lists of floats 1.01, 1.06, of halves and bytes 1.00, 1.04; d 768 short lists
-  // 0.81 to 0.99, 1.06, long ones 1.00 to 1.03, 1.12; d 1024 short lists 1.00 to 1.03, 1.09; d 1536 1.07 to 1.11, 1.18.
+  // request of few queries shares between four: with wide vectors that takes longer than two launches, unless many pairs
+  // make the plan long, many queries fill the chip (53 x 3 probes, 438 short lists x 776: 54 us, planned 61), or a planned
+  // request has one workgroup for the centroids as well, up to 256 of them.  Small / planned, the middle and the largest of
+  // 5 to 60 requests each of 1 to 32 queries x 8 to 64 probes over 64 to 4,096 lists of up to 1,500 vectors, up to 32 MB:
+  //  d 32 0.81 to 0.90, 1.01; d 128 0.81 to 0.95, 1.02; d 256 0.86 to 0.97, 1.00; d 512 without a bound 0.80 to 0.94, 1.00,
+  //    with one and long lists of floats 1.01, 1.06, of halves and bytes 1.00, 1.04
+  //  long lists, d 768: floats 1.12, halves and bytes 0.93 to 1.00, 1.00, with a bound 1.02, 1.05
+  //  short lists, floats: d 768 0.88 to 0.98, 1.04, d 1024 0.91 to 1.03, 1.09, d 1536 0.97 to 1.11, 1.22, of these from 400
+  //    pairs 0.82 to 0.99, 1.02; halves and bytes: d 1024 0.80 to 0.95, 1.02, d 1536 0.81 to 1.03, 1.18, from 100 pairs 0.48
+  //    to 0.83, 0.83, d 2048 from 128 pairs 1.04 to 1.07, 1.12, from 256 0.51 to 0.82, 1.05
   const bool short_lists = avg_len / kWave + 1 <= kSingleList;  // a sample is a few groups of each, shared or not
+  const bool narrow = D.storage != 0;
+  const int wide = short_lists ? (narrow ? 1024 : 768) : (narrow ? 768 : 512);
+  if (D.d > wide && D.nlist > 256 && !(short_lists && (nq >= 16 || nq * nprobe >= (narrow ? 100 : 400) * (D.d > 1536 ? 2 : 1)))) return false;
   const int64_t no_bound_below = D.metric == 0 ? 4096 : 32 * (int64_t)D.d > 4096 ? 32 * (int64_t)D.d : 4096;
-  if (D.d > (short_lists ? 768 : 512)) return false;
-  return short_lists || D.vchunks < 96 || nprobe * avg_len <= no_bound_below;
+  return short_lists || nprobe * avg_len <= no_bound_below || (D.vchunks < 96 && D.d <= 512);
 }
 
 void launch_small_front(const Dev &D, int64_t nq, int nprobe, int max_nprobe, int k, const float *Q, const SearchScratch &S,

@@ -37,10 +37,11 @@ def goes_small(g, n, longest, nq, nprobe):
     chunks = g.d // {"f32": 4, "f16": 8, "u8": 16}[g.storage]
     if nq * (nprobe * avg + longest) * chunks * 16 > 32e6:
         return False
-    short = avg // 64 + 1 <= 4
-    if g.d > (768 if short else 512):
+    short, narrow = avg // 64 + 1 <= 4, g.storage != "f32"
+    wide = (1024 if narrow else 768) if short else (768 if narrow else 512)
+    if g.d > wide and g.nlist > 256 and not (short and (nq >= 16 or nq * nprobe >= (100 if narrow else 400) * (2 if g.d > 1536 else 1))):
         return False
-    return short or chunks < 96 or nprobe * avg <= (4096 if g.metric == rtams.L2 else max(4096, 32 * g.d))
+    return short or nprobe * avg <= (4096 if g.metric == rtams.L2 else max(4096, 32 * g.d)) or (chunks < 96 and g.d <= 512)
 
 
 def both(g, q, k, nprobe):
@@ -68,19 +69,19 @@ def test_small_requests_answer_like_planned_ones(nlist, d, n, metric):
     g, q = build(n, d, nlist, metric, "f32")
     took = [both(g, q[:nq].contiguous(), k, nprobe)
             for nq, k, nprobe in ((1, 100, 32), (10, 10, 8), (3, 1, 1), (7, 128, min(64, nlist)), (1, 50, min(63, nlist)), (33, 5, 2))]
-    assert not any(took) if nlist > 4096 or d > 768 else any(took)
+    assert any(took) == (nlist <= 4096)
     g.close()
 
 
 @pytest.mark.parametrize("metric", ["l2", "ip"])
-@pytest.mark.parametrize("storage,d", [("f16", 72), ("u8", 80)])
+@pytest.mark.parametrize("storage,d", [("f16", 72), ("u8", 80), ("u8", 1024), ("f16", 1032), ("u8", 1040)])
 @pytest.mark.parametrize("n,hot", [(20, False), (6000, False), (20000, True)])
 def test_small_requests_over_narrow_empty_and_hot_lists(storage, d, n, hot, metric):
     print(f"[case] small path {metric} {storage} {n} hot={hot}", flush=True)
     g, q = build(n, d, 200, metric, storage, hot=hot)
     for nq, k, nprobe in ((1, 100, 32), (9, 10, 64), (2, 128, 1)):
         took = both(g, q[:nq].contiguous(), k, nprobe)
-        assert took or hot
+        assert took or hot or d > 1000 and nq > 1
     g.close()
 
 
