@@ -254,7 +254,12 @@ __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, in
   // list, the more candidates a given score admits), at most kSampleMax and, but for the 512, at most
   // 1 MiB of vectors (with the rounding below a third more; a hot list of wide vectors would hold up the scan), in whole groups
   uint32_t cap = PQ ? (uint32_t)kSampleMax : ((1u << 20) / ((uint32_t)D.vchunks * 16u)) & ~(uint32_t)(kWave - 1);
-  cap = cap < 512u ? 512u : (cap > (uint32_t)kSampleMax ? (uint32_t)kSampleMax : cap);
+  // ... and for squared distances what k needs: a sample of fewer than k vectors is no bound at all, every candidate is then
+  // kept and scored again (176 queries x 45 probes over lists of up to 144,000 x 1,036 floats, k 703: 19.0 ms a request without
+  // a bound, 14.9 with; 64 queries x 32 over lists of 1,000 x 1,536 bytes, k 1,000: 0.13 of the time; inner products, which
+  // score nothing again, were up to 1.44 times as slow with so large a sample)
+  const uint32_t least = max(512u, (uint32_t)k + (uint32_t)k / 4u);
+  cap = min(max(cap, D.metric == 0 ? (least + kWave - 1) & ~(uint32_t)(kWave - 1) : 512u), (uint32_t)kSampleMax);
   uint32_t want = (uint32_t)k * 4u;
   const uint32_t share = first.len / (uint32_t)kSampleDivisor;
   want = want < share ? share : want;
@@ -266,12 +271,12 @@ __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, in
       parts = 1;
     }
     // One workgroup takes the nearest number of whole turns of its wavefronts, a group to each (256 queries over lists of
-    // 2,441, ten groups: the last two were a turn of their own), but no fewer than 2 k or the cap come to: a sample of fewer
-    // than k vectors is no bound at all (256 queries, k 600, lists of 1,560 x 400: 557 us a request without one, 455 with).
+    // 2,441, ten groups: the last two were a turn of their own), but no fewer than a quarter more than k as far as the cap
+    // goes (256 queries, k 600, lists of 1,560 x 400: 557 us a request with eight groups, which are no bound, 455 with ten).
     // What several share is not rounded: up to whole turns of theirs, eight groups became sixteen for two workgroups (200
-    // queries over lists of 600 x 384: 305 us, 279 with eight left to one).  And 2 k is enough for them (64 queries over
-    // lists of 364 x 300, k 200: 159 us with eight groups, 165 with 4 k's thirteen; k 500: 234 with eight, 206 with thirteen).
-    const uint32_t least = max(512u, (uint32_t)k * 2u);
+    // queries over lists of 600 x 384: 305 us, 279 with eight left to one).  And that quarter more than k is enough for them
+    // (64 queries over lists of 364 x 300, k 200: 159 us with eight groups, 165 with 4 k's thirteen; k 500: 234 with eight, 206
+    // with ten or thirteen).
     if (parts == 1) {
       const uint32_t turn = blockDim.x / kWave, whole = (want_groups + turn / 2) / turn * turn;
       want_groups = min(max(whole, min(want_groups, (least + kWave - 1) / kWave)), (uint32_t)kSampleMax / kWave);

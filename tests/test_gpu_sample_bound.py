@@ -1,8 +1,9 @@
 """The pruning bound of a query is the k-th best score of a sample of its candidates, whatever k: read back after the
 request and compared with the sample taken here, in the order of the exported lists.  Scores are small whole numbers, the
 same in every form and order.  What decides the size of a sample: 4 k vectors, 512 at least, a quarter of the nearest list,
-1 MiB of them at most (but 512 in any case).  One workgroup reads the nearest number of whole turns of its wavefronts, but no
-fewer than 2 k or that 1 MiB comes to; several that share a sample need 2 k instead of 4."""
+1 MiB of them at most (but 512 in any case, and under squared distances a quarter more than k).  One workgroup reads the
+nearest number of whole turns of its wavefronts, but no fewer than a quarter more than k or that 1 MiB comes to; several that
+share a sample do without the 4 k."""
 import pytest
 import torch
 
@@ -21,13 +22,13 @@ def workgroups(nq, nprobe):
     return 1 if room < 3 else min(4, room)
 
 
-def sample_groups(k, nearest, chunks, nlist, parts):
+def sample_groups(k, nearest, chunks, nlist, parts, l2):
     """Groups of 64 vectors of the sample of a query whose nearest list holds `nearest` vectors of `chunks` 16-byte chunks."""
-    cap = min(max((1 << 20) // (16 * chunks) // 64 * 64, 512), 4096)
+    least = max(512, k + k // 4)
+    cap = min(max((1 << 20) // (16 * chunks) // 64 * 64, (least + 63) // 64 * 64 if l2 else 512), 4096)
     want = (min(max(4 * k, nearest // 4, 512), cap) + 63) // 64
     if parts > 1 and (want * chunks < 260 or want * 64 > nlist):
         parts = 1
-    least = max(512, 2 * k)
     if parts > 1:
         return min(want, (max(least, nearest // 4) + 63) // 64)
     whole = (want + 4) // 8 * 8  # eight wavefronts, a group to each in turn
@@ -71,7 +72,7 @@ def check(g, q, k, nprobe, chunks, some):
     bounded = 0
     for i in some:
         lists = [int(x) for x in probes[i]]
-        groups = sample_groups(k, int(sizes[lists[0]]), chunks, nlist, workgroups(nq, nprobe))
+        groups = sample_groups(k, int(sizes[lists[0]]), chunks, nlist, workgroups(nq, nprobe), not metric_ip)
         scores, left = [], groups
         total = sum(int(sizes[l]) for l in lists)
         for l in lists:
