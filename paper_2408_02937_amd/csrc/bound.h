@@ -270,18 +270,20 @@ __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, in
       if (part) return;  // uniform, and the same for all workgroups of the query
       parts = 1;
     }
-    // One workgroup takes the nearest number of whole turns of its wavefronts, a group to each (256 queries over lists of
-    // 2,441, ten groups: the last two were a turn of their own), but no fewer than a quarter more than k as far as the cap
-    // goes (256 queries, k 600, lists of 1,560 x 400: 557 us a request with eight groups, which are no bound, 455 with ten).
-    // What several share is not rounded: up to whole turns of theirs, eight groups became sixteen for two workgroups (200
-    // queries over lists of 600 x 384: 305 us, 279 with eight left to one).  And that quarter more than k is enough for them
-    // (64 queries over lists of 364 x 300, k 200: 159 us with eight groups, 165 with 4 k's thirteen; k 500: 234 with eight, 206
-    // with ten or thirteen).
-    if (parts == 1) {
-      const uint32_t turn = blockDim.x / kWave, whole = (want_groups + turn / 2) / turn * turn;
+    // A sample is the nearest number of whole turns of the wavefronts that read it, a group to each, if it is more than one
+    // turn (256 queries over lists of 2,441 x 96, ten groups to one workgroup: the last two were a turn of their own; 128
+    // queries, three workgroups, up to 35 groups: this launch 27 us with 24 and 33 with 35), but no fewer than a quarter more
+    // than k as far as the cap goes (256 queries, k 600, lists of 1,560 x 400: 557 us a request with eight groups, which are
+    // no bound, 455 with ten).  Up to one turn is not rounded: eight groups, sixteen for two workgroups, made 305 us of 200
+    // queries over lists of 600 x 384 that take 279 with eight and one.  And that quarter more than k is enough for several
+    // (64 queries over lists of 364 x 300, k 200: 159 us with eight groups, 165 with 4 k's thirteen; k 500: 234 with eight,
+    // 206 with ten or thirteen).
+    const uint32_t turn = blockDim.x / kWave * parts;
+    if (parts > 1) want_groups = min(want_groups, (max(least, share) + kWave - 1) / kWave);
+    if (want_groups > turn) {
+      const uint32_t whole = (want_groups + turn / 2) / turn * turn;
       want_groups = min(max(whole, min(want_groups, (least + kWave - 1) / kWave)), (uint32_t)kSampleMax / kWave);
-    } else {
-      want_groups = min(want_groups, (max(least, share) + kWave - 1) / kWave);
+      if (parts > 1) want_groups = min(want_groups, (uint32_t)D.nlist / kWave);
     }
     // a sample of fewer than k vectors (lists end inside a group) is no bound and need not be read
     if ((uint32_t)k * 2u > want_groups * kWave) {  // uniform

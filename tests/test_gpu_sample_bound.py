@@ -1,9 +1,9 @@
 """The pruning bound of a query is the k-th best score of a sample of its candidates, whatever k: read back after the
 request and compared with the sample taken here, in the order of the exported lists.  Scores are small whole numbers, the
 same in every form and order.  What decides the size of a sample: 4 k vectors, 512 at least, a quarter of the nearest list,
-1 MiB of them at most (but 512 in any case, and under squared distances a quarter more than k).  One workgroup reads the
-nearest number of whole turns of its wavefronts, but no fewer than a quarter more than k or that 1 MiB comes to; several that
-share a sample do without the 4 k."""
+1 MiB of them at most (but 512 in any case, and under squared distances a quarter more than k).  Several workgroups that share
+a sample do without the 4 k.  A sample of more than one turn of the wavefronts that read it is the nearest number of whole
+turns, but no fewer than a quarter more than k or that 1 MiB comes to."""
 import pytest
 import torch
 
@@ -30,9 +30,13 @@ def sample_groups(k, nearest, chunks, nlist, parts, l2):
     if parts > 1 and (want * chunks < 260 or want * 64 > nlist):
         parts = 1
     if parts > 1:
-        return min(want, (max(least, nearest // 4) + 63) // 64)
-    whole = (want + 4) // 8 * 8  # eight wavefronts, a group to each in turn
-    return min(max(whole, min(want, (least + 63) // 64)), 64)
+        want = min(want, (max(least, nearest // 4) + 63) // 64)
+    turn = 8 * parts  # eight wavefronts to a workgroup, a group to each in turn
+    if want > turn:
+        want = min(max((want + turn // 2) // turn * turn, min(want, (least + 63) // 64)), 64)
+        if parts > 1:
+            want = min(want, nlist // 64)
+    return want
 
 
 def score_of_key(key):
