@@ -491,18 +491,22 @@ inline bool mm_scan_pays(const Dev &D, int64_t nq, int64_t nprobe, int64_t avg_l
 inline bool narrow_scan_fits(const Dev &D) {
   return D.metric == 0 && D.pq_m == 0 && D.storage != 0 && D.d >= (D.storage == 2 ? 64 : 32) && D.d <= 640;
 }
-// ... and whether it should.  An instruction takes 16 queries whether they are there or not, and an item's queries are split
-// anew: a tile of few does not repay that, least of all where the lists come from HBM (past some 300 MB of them) and the
-// 4x4x1 instructions run four wavefronts to a SIMD where these run three.  So it goes by the pairs to a list; hot lists, whose
-// tiles are full, make little difference to where the line lies.  4x4x1 / 16-bit, us a request, 1,623 requests of 64 to 256
-// queries x 4 to 64 probes over 64 to 4,096 lists: bytes, 1,024 lists of 4,000 x 256, 2 pairs to a list 224 / 269, 4 285 /
-// 323, 6 340 / 348; of 1,000 x 128 4 pairs 0.93 to 0.95 of the time, 8 0.78 to 0.87; halves, 1,024 of 4,000 x 256, 4 pairs 386
-// / 413, 8 428 / 449, 256 of 1,500 x 512, 8 pairs 162 / 147, 512 of 600 x 256, 4 pairs 99 / 90, x 32 55 / 58.  Bytes of 64
-// dimensions gain at any number of pairs where the lists are 60 MB and more (1,024 of 4,000, 2 pairs: 140 / 121; 512 of 600:
-// 57 / 60).  With this rule a request is at most 3 % slower than on the 4x4x1 instructions (always taken, 20 %) and on
-// average 0.2 % from the better of the two.
+// ... and whether it should.  Nearly always; but an instruction takes 16 queries whether they are there or not, and an item's
+// queries are split anew, which a tile of few repays only if its loads keep coming, and where a vector is a power of two of
+// 16-byte chunks, the groups that wavefronts read side by side lie a power of two apart and memory answers more slowly.
+// There it goes by the pairs to a list and by what the lists come to (past some 300 MB they come from HBM); hot lists,
+// whose tiles are full, make little difference to where the line lies.  4x4x1 / 16-bit, us a request, over 1,900 requests of
+// 64 to 256 queries x 4 to 64 probes over 64 to 4,096 lists: bytes, 1,024 lists of 4,000 x 256, 2 pairs to a list 224 / 269, 4
+// 285 / 323, 6 340 / 348; of 1,000 x 128 4 pairs 0.93 to 0.95 of the time, 8 0.78 to 0.87; halves, 1,024 of 4,000 x 256, 4
+// pairs 386 / 413, 8 428 / 449, 256 of 1,500 x 512, 8 pairs 162 / 147, 512 of 600 x 256, 4 pairs 99 / 90, x 32 55 / 58.  Bytes
+// of 64 dimensions gain at any number of pairs where the lists are 60 MB and more (1,024 of 4,000, 2 pairs: 140 / 121; 512
+// of 600: 57 / 60).  Other numbers of chunks: bytes, 1,024 of 2,000 x 192, 2 pairs 141 / 125, x 320 202 / 169, x 352 272 / 192, x
+// 384 210 / 182; halves, 512 of 3,600 x 288, 4 pairs 272 / 247, x 352 328 / 294, x 400 337 / 311.
+// Over 2,049 requests the rule is 0.3 % from the better of the two on average and at most 10 % behind (640 dimensions of
+// bytes, 2 pairs: 192 / 211); always the 16-bit instructions are up to 20 % behind, never are up to 1.8 times as slow.
 inline bool narrow_scan_pays(const Dev &D, int64_t pairs, double list_bytes) {
   const int64_t nlist = D.nlist;
+  if (D.vchunks & (D.vchunks - 1)) return true;
   if (D.storage == 2) return pairs > 4 * nlist || (pairs > 2 * nlist && list_bytes < 300e6) || (D.d <= 64 && list_bytes >= 60e6);
   return pairs > 8 * nlist || (pairs == 8 * nlist && list_bytes < 500e6) ||
          (pairs >= 4 * nlist + (D.d < 128 ? 1 : 0) && list_bytes < 300e6);

@@ -1,5 +1,5 @@
 """Which instructions scan a request for squared distances over lists of halves and bytes, on both sides of the lines of the
-rule (pairs to a list, bytes of the lists, dimension), and that the answers are those of the vector unit."""
+rule (pairs to a list, bytes of the lists, chunks of a vector), and that the answers are those of the vector unit."""
 import pytest
 import torch
 
@@ -23,6 +23,8 @@ WIDE, NARROW = "k_scan_mm", "k_scan_mm narrow"
     ("u8", 64, 16000, 64, 2, NARROW),     # two, 66 MB of 64 dimensions
     ("u8", 512, 10000, 64, 4, WIDE),      # four, 330 MB
     ("u8", 512, 10000, 64, 5, NARROW),
+    ("u8", 192, 600, 64, 2, NARROW),      # two, twelve chunks to a vector
+    ("f16", 360, 8000, 64, 4, NARROW),    # four, 370 MB, 45 chunks
     ("u8", 656, 600, 64, 8, WIDE),        # wider than the 16-bit scan takes
 ])
 def test_the_instructions_that_scan(storage, d, length, nq, nprobe, path):
