@@ -1,5 +1,6 @@
 // One workgroup's part of the exact coarse scores: the fixed arithmetic that decides list membership and probe choice.
 #pragma once
+#include <type_traits>
 #include "rtams_launch.h"
 
 namespace rtams {
@@ -193,14 +194,17 @@ __device__ __forceinline__ void coarse_tile(
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
 #pragma unroll
     for (int v = 0; v < VT; ++v) {
-      for (int o = kWave / 2; o > 0; o >>= 1) {
-        const double sb = __shfl_xor(best_s[v], o);
-        const int ib = __shfl_xor(best_i[v], o);
+      auto step = [&](auto tag) {  // (where a step brings nothing, a lane meets itself)
+        constexpr int kI = decltype(tag)::value;
+        const double sb = wave_step<kI>(best_s[v], best_s[v]);
+        const int ib = (int)wave_step<kI>((uint32_t)best_i[v], (uint32_t)best_i[v]);
         const bool take = better_pair(METRIC, sb, ib, best_s[v], best_i[v]);
         best_s[v] = take ? sb : best_s[v];
         best_i[v] = take ? ib : best_i[v];
-      }
-      if (lane == 0) { red_s[v][wave] = best_s[v]; red_i[v][wave] = best_i[v]; }
+      };
+      step(std::integral_constant<int, 0>{}); step(std::integral_constant<int, 1>{}); step(std::integral_constant<int, 2>{});
+      step(std::integral_constant<int, 3>{}); step(std::integral_constant<int, 4>{}); step(std::integral_constant<int, 5>{});
+      if (lane == kWave - 1) { red_s[v][wave] = best_s[v]; red_i[v][wave] = best_i[v]; }
     }
     __syncthreads();
     const int v = threadIdx.x;  // (a thread of the first wavefront to each vector)

@@ -48,10 +48,7 @@ __device__ void scatter_pairs(const Dev &D, int nq, int nprobe, int max_nprobe, 
     for (int t = 0; t < kListChunk; ++t) {
       incl[t] = c[t];
       if (t < rows) {  // uniform
-        for (int o = 1; o < kWave; o <<= 1) {
-          const uint32_t x = __shfl_up(incl[t], o);
-          if (lane >= o) incl[t] += x;
-        }
+        incl[t] = wave_running_sum(incl[t]);
         if (lane == kWave - 1) s_tot[t * kWavesG + wave] = incl[t];
       }
     }
@@ -61,13 +58,9 @@ __device__ void scatter_pairs(const Dev &D, int nq, int nprobe, int max_nprobe, 
       const int counts = rows * kWavesG;
       for (int i0 = 0; i0 < counts; i0 += kWave) {
         const uint32_t v = i0 + lane < counts ? s_tot[i0 + lane] : 0u;
-        uint32_t in2 = v;
-        for (int o = 1; o < kWave; o <<= 1) {
-          const uint32_t x = __shfl_up(in2, o);
-          if (lane >= o) in2 += x;
-        }
+        const uint32_t in2 = wave_running_sum(v);
         if (i0 + lane < counts) s_tot[i0 + lane] = carry + in2 - v;
-        carry += __shfl(in2, kWave - 1);
+        carry += last_lane(in2);
       }
       if (lane == 0) s_tot[kListChunk * kWavesG] = carry;
     }
@@ -189,13 +182,9 @@ __global__ __launch_bounds__(kGroupThreads, 4) void k_group(Dev D, int nq, int n
       const int counts = rows * kWavesG;
       for (int i0 = 0; i0 < counts; i0 += kWave) {
         const uint32_t v = i0 + lane < counts ? s_rows[i0 + lane] : 0u;
-        uint32_t incl = v;
-        for (int o = 1; o < kWave; o <<= 1) {
-          const uint32_t x = __shfl_up(incl, o);
-          if (lane >= o) incl += x;
-        }
+        const uint32_t incl = wave_running_sum(v);
         if (i0 + lane < counts) s_rows[i0 + lane] = carry + incl - v;
-        carry += __shfl(incl, kWave - 1);
+        carry += last_lane(incl);
       }
       if (lane == 0) s_rows[kListChunk * kWavesG] = carry;
     }
@@ -245,7 +234,9 @@ __global__ __launch_bounds__(kGroupThreads, 4) void k_group(Dev D, int nq, int n
         wk += work_of(pl[u], groups);
       }
     }
-    for (int o = kWave / 2; o > 0; o >>= 1) { np += __shfl_xor(np, o); ni += __shfl_xor(ni, o); wk += __shfl_xor(wk, o); }
+    np = last_lane(wave_running_sum(np));
+    ni = last_lane(wave_running_sum(ni));
+    wk = last_lane(wave_running_sum(wk));
     if (lane == 0) { s_a[wave] = np; s_b[wave] = ni; s_c[wave] = wk; }
     if (tid < 9) s_begin[tid] = 0u;
     if (tid == 0) s_nhuge = 0;
@@ -277,19 +268,14 @@ __global__ __launch_bounds__(kGroupThreads, 4) void k_group(Dev D, int nq, int n
       uint32_t groups, tiles;
       const uint32_t n = items_of(got, groups, tiles);
       const unsigned long long w = work_of(got, groups);
-      uint32_t psum = got.z, isum = n;
-      unsigned long long wsum = w;
-      for (int o = 1; o < kWave; o <<= 1) {
-        const uint32_t xa = __shfl_up(psum, o), xb = __shfl_up(isum, o);
-        const unsigned long long xc = __shfl_up(wsum, o);
-        if (lane >= o) { psum += xa; isum += xb; wsum += xc; }
-      }
+      const uint32_t psum = wave_running_sum(got.z), isum = wave_running_sum(n);
+      const unsigned long long wsum = wave_running_sum(w);
       const uint4 pl = make_uint4(got.x, ps + psum - got.z, got.z, got.w);
       const uint32_t ist = is + isum - n;
       const unsigned long long wst = ws + wsum - w;
-      ps += __shfl(psum, kWave - 1);
-      is += __shfl(isum, kWave - 1);
-      const unsigned long long wend = ws + __shfl(wsum, kWave - 1);
+      ps += last_lane(psum);
+      is += last_lane(isum);
+      const unsigned long long wend = ws + last_lane(wsum);
       // XCD x starts at the item at which the work prefix passes x/8 of the total; a cut inside a list: at the item
       // the same share of it ends at
       for (uint32_t x = 1; x < 8; ++x) {

@@ -102,11 +102,7 @@ __device__ bool wg_open(const Dev &D, int list, uint32_t nb_old, uint32_t newlen
         if (D.seg_dir[(size_t)list * kTableSegs + g] < 0) slab += (uint32_t)kTableBase << g;
     }
   }
-  uint32_t blocks_to = count, slab_to = slab;  // running sums
-  for (int o = 1; o < kWave; o <<= 1) {
-    const uint32_t a = __shfl_up(blocks_to, o), b = __shfl_up(slab_to, o);
-    if (lane >= o) { blocks_to += a; slab_to += b; }
-  }
+  uint32_t blocks_to = wave_running_sum(count), slab_to = wave_running_sum(slab);
   if (lane == kWave - 1) { sh.wave_blocks[wave] = blocks_to; sh.wave_slab[wave] = slab_to; }
   __syncthreads();
   uint32_t total = 0, slab_total = 0;
@@ -181,8 +177,8 @@ __device__ bool wg_open(const Dev &D, int list, uint32_t nb_old, uint32_t newlen
 // its due until some list grew past the larger.  `known`: ctrl->max_len as of any time before (it only grows).
 __device__ inline void note_longest(const Dev &D, uint32_t newlen, uint32_t known) {
   if (!__any(newlen > known)) return;  // uniform over the wavefront
-  for (int o = kWave / 2; o > 0; o >>= 1) newlen = max(newlen, (uint32_t)__shfl_xor((int)newlen, o));
-  if ((threadIdx.x & (kWave - 1)) == 0) atomicMax(&D.ctrl->max_len, newlen);
+  newlen = wave_reduce_last(newlen, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+  if ((threadIdx.x & (kWave - 1)) == kWave - 1) atomicMax(&D.ctrl->max_len, newlen);
 }
 
 // `start`, where the fill goes by lists: the new vectors of list l are start[l] .. of the batch in the order of the fill,
@@ -196,11 +192,7 @@ __global__ __launch_bounds__(256) void k_open(Dev D, uint32_t *__restrict__ star
     __shared__ uint32_t s_sum[4], s_base;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const uint32_t added = on ? newlen - D.visible_len[list] : 0u;
-    uint32_t upto = added;
-    for (int o = 1; o < kWave; o <<= 1) {
-      const uint32_t x = __shfl_up(upto, o);
-      if (lane >= o) upto += x;
-    }
+    uint32_t upto = wave_running_sum(added);
     if (lane == kWave - 1) s_sum[wave] = upto;
     __syncthreads();
     if (threadIdx.x == 0) s_base = atomicAdd(&D.ctrl->fill_cur, s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3]);
@@ -331,8 +323,7 @@ __device__ inline void wg_publish(const Dev &D, int list) {
       __hip_atomic_store(&D.visible_len[list], newlen, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
-  uint32_t sum = added;  // (a batch of one insertion round holds fewer than 2^32 vectors)
-  for (int o = kWave / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+  const uint32_t sum = last_lane(wave_running_sum(added));  // (a batch of one insertion round holds fewer than 2^32 vectors)
   if (told_exceed) D.mirror->exceed_lists = told_exceed;
   if ((threadIdx.x & (kWave - 1)) == 0 && sum) atomicAdd(&D.ctrl->ntotal, (unsigned long long)sum);
 }

@@ -60,13 +60,9 @@ __global__ __launch_bounds__(kPqScanThreads, 8) void k_pq_scan(Dev D, int nprobe
         const uint32_t have = D.nblk[S.probe_list[o]] * gpb;  // never index the block table past the chain
         groups = groups > have ? have : groups;
       }
-      uint32_t incl = groups;
-      for (int d = 1; d < kWave; d <<= 1) {
-        const uint32_t t = __shfl_up(incl, d);
-        if (lane >= d) incl += t;
-      }
+      const uint32_t incl = wave_running_sum(groups);
       if (p < nprobe) gstart[p] = carry + incl - groups;
-      carry += __shfl(incl, kWave - 1);
+      carry += last_lane(incl);
     }
     if (lane == 0) gstart[nprobe] = carry;
   }

@@ -222,9 +222,9 @@ __device__ __forceinline__ void probe_plan(const Dev &D, int64_t nq, int q, int 
   unsigned long long tot = 0;
   if (threadIdx.x < kWave) {
     for (int p = threadIdx.x; p < nprobe; p += kWave) tot += pay[p];
-    for (int o = kWave / 2; o > 0; o >>= 1) tot += __shfl_xor(tot, o);
+    tot = wave_running_sum(tot);  // of all, in the last lane
   }
-  if (threadIdx.x == 0) {
+  if (threadIdx.x == kWave - 1) {
     unsigned long long base = 0;
     if (probe_out) tot = 0;  // the probe hook: nothing is scanned afterwards, no room for records is taken
     if (tot > 0xFFFFFFFFull) tot = ~0ull;  // cannot be indexed: treated as overflow below

@@ -94,11 +94,7 @@ __device__ inline void wg_pick_bin(const uint32_t *hist, uint32_t need, uint32_t
   if (threadIdx.x < kWave) {  // first wavefront: which bin holds the need-th item
       int l = threadIdx.x;
       uint32_t h0 = hist[4 * l], h1 = hist[4 * l + 1], h2 = hist[4 * l + 2], h3 = hist[4 * l + 3];
-      uint32_t sum = h0 + h1 + h2 + h3, incl = sum;
-      for (int o = 1; o < kWave; o <<= 1) {
-        uint32_t t = __shfl_up(incl, o);
-        if (l >= o) incl += t;
-      }
+      uint32_t sum = h0 + h1 + h2 + h3, incl = wave_running_sum(sum);
       uint32_t excl = incl - sum;
       if (excl < need && need <= incl) {  // exactly one lane
         uint32_t cum = excl;
@@ -140,12 +136,11 @@ __device__ __forceinline__ SelectResult wg_radix_select_each(uint32_t k, Each ea
   {
     Key lo = ~(Key)0, hi = 0;
     each([&](uint64_t key) { lo = (Key)key < lo ? (Key)key : lo; hi = (Key)key > hi ? (Key)key : hi; });
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-      const Key a = __shfl_xor(lo, o), b = __shfl_xor(hi, o);
-      lo = a < lo ? a : lo;
-      hi = b > hi ? b : hi;
-    }
-    if (lane == 0) { range[2 * wave] = (uint64_t)lo; range[2 * wave + 1] = (uint64_t)hi; }
+    lo = wave_reduce_last(lo, [](Key a, Key b) { return b < a ? b : a; });
+    hi = wave_reduce_last(hi, [](Key a, Key b) { return b > a ? b : a; });
+    int at = lane;
+    asm volatile("" : "+v"(at));  // (no mask of these lanes is kept in scalar registers, which the callers have none to spare of)
+    if (at == kWave - 1) { range[2 * wave] = (uint64_t)lo; range[2 * wave + 1] = (uint64_t)hi; }
   }
   __syncthreads();
   uint64_t kmin = ~0ull, kmax = 0ull;
@@ -302,7 +297,7 @@ __device__ inline void wg_sort(int n, uint64_t *k1, uint64_t *k2, uint32_t *pay)
     }
     for (; j < hi; ++j) count(j, w[2 * j]);
   }
-  for (int o = 1; o < S; o <<= 1) before += __shfl_xor(before, o);  // the S lanes of an entry are neighbours in one wavefront
+  before = group_sum(before, S);  // the S lanes of an entry are neighbours in one wavefront
   __syncthreads();  // everybody has read
   if (on && s == 0) { k1[before] = a1; k2[before] = a2; pay[before] = ap; }
   __syncthreads();

@@ -335,8 +335,8 @@ __global__ __launch_bounds__(kTopkThreads, 4) void k_select(Dev D, int k, int np
         for (int p = 0; p < pieces_of(ST); ++p) accumulate<0>(acc, chunk_piece<ST>(v[u], p), y[pieces_of(ST) * c + p]);
       }
     }
-    acc += __shfl_xor(acc, 1);
-    acc += __shfl_xor(acc, 2);
+    acc += quad_xor<1>(acc);
+    acc += quad_xor<2>(acc);
     return key_of_float(acc + 0.0f);
   };
   // place in the pool -> key of the candidate's direct-form squared distance.  Four neighbouring lanes share
@@ -363,8 +363,8 @@ __global__ __launch_bounds__(kTopkThreads, 4) void k_select(Dev D, int k, int np
       for (int u = 0; u < 8; ++u) accumulate<0>(acc, v[u], y[c + 4 * u]);
     }
     for (; c < D.d4; c += 4) accumulate<0>(acc, x[(size_t)c * kWave], y[c]);
-    acc += __shfl_xor(acc, 1);
-    acc += __shfl_xor(acc, 2);
+    acc += quad_xor<1>(acc);
+    acc += quad_xor<2>(acc);
     return key_of_float(acc + 0.0f);
   };
   // The same for two candidates at once: both block look-ups go out together, then all the chunks of
@@ -404,10 +404,10 @@ __global__ __launch_bounds__(kTopkThreads, 4) void k_select(Dev D, int k, int np
       accumulate<0>(acca, va, y[c]);
       accumulate<0>(accb, vb, y[c]);
     }
-    acca += __shfl_xor(acca, 1);
-    acca += __shfl_xor(acca, 2);
-    accb += __shfl_xor(accb, 1);
-    accb += __shfl_xor(accb, 2);
+    acca += quad_xor<1>(acca);
+    acca += quad_xor<2>(acca);
+    accb += quad_xor<1>(accb);
+    accb += quad_xor<2>(accb);
     ka = key_of_float(acca + 0.0f);
     kb = key_of_float(accb + 0.0f);
   };

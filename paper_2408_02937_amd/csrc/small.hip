@@ -59,12 +59,7 @@ __global__ __launch_bounds__(kScanWaves * kWave) void k_scan_small(Dev D, int np
   const uint32_t my_len = S.probe_len[o];
   const uint32_t have = D.nblk[my_list] * (uint32_t)D.groups_per_block;  // never past the list's chain
   const uint32_t units = lane < nprobe ? (min((my_len + kWave - 1) / kWave, have) + G - 1) / G : 0u;
-  uint32_t upto = units;
-  for (int d = 1; d < kWave; d <<= 1) {
-    const uint32_t x = __shfl_up(upto, d);
-    if (lane >= d) upto += x;
-  }
-  const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)upto, kWave - 1);
+  const uint32_t upto = wave_running_sum(units), total = last_lane(upto);
   const uint32_t first = units ? upto - units : ~0u;  // the lane's probe starts at this unit
   for (uint32_t u = part * waves + wave; u < total; u += (uint32_t)parts * waves) {  // uniform over the wavefront
     const int p = 63 - __clzll((long long)__ballot(first <= u));  // the last probe that starts at or before u
