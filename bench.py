@@ -171,10 +171,14 @@ class Bench:
         elapsed = time.perf_counter() - t0
         g.set_param("profile_scan", 0)
         scan_ms, scan_n = g.scan_time(reset=True)
-        by_kernel = g.scan_kernels(reset=True)  # which scan kernel the library chose for these requests
-        self.scan_kernel = max(by_kernel, key=by_kernel.get)
+        g.scan_kernels(reset=True)
+        self.scan_kernel = self.scanned_by(self.B)  # which scan kernel the library chose for these requests
         assert g.poll_error() == 0, "a kernel raised an error during the timed steps"
         return elapsed, scan_ms, scan_n
+
+    def scanned_by(self, bs):
+        """How the last request, of `bs` queries, was scanned."""
+        return self.g.request_trace(bs)[2].split()[0]
 
     def scan_scheduling(self, steps, warmup, union_b):
         """The same timed steps with the scans of different requests made to run one after the other,
@@ -193,7 +197,11 @@ class Bench:
         g.set_param("scan_exclusive_bytes", 16 << 30)
         return out
 
-    def scan_bytes(self, batches, bs=None, first=0):
+    def vector_bytes(self, kernel):
+        """What the scan reads of a vector: its floats, or its 16-bit halves where those are kept and scanned."""
+        return self.w.d * (2 if kernel == "k_scan_halves" else 4)
+
+    def scan_bytes(self, batches, bs=None, first=0, kernel=None):
         """Algorithmic bytes of the scan per launch: what the method must read.  The scan reads a list
         once for all the queries of the batch that probe it, so these are the bytes of the UNION of
         the probed lists; bytes counted once per (query, list) pair are reported beside them, never
@@ -202,7 +210,8 @@ class Bench:
         bs = bs or self.B
         nb = max(len(self.queries) // bs, 1)
         sizes = g.list_sizes()
-        per_list = lambda l: l * w.d * 4 + ((l + w.block_vecs - 1) // w.block_vecs) * 4
+        each = self.vector_bytes(kernel or self.scan_kernel)
+        per_list = lambda l: l * each + ((l + w.block_vecs - 1) // w.block_vecs) * 4
         pair_bytes, union_bytes = [], []
         for i in range(batches):
             b = (first + i) % nb
@@ -216,7 +225,7 @@ class Bench:
         multiply-add instructions per lane for L2 (d multiply-adds for IP); the yardstick is the rate at
         which 256 CUs x 4 SIMDs x 16 lanes issue one fp32 instruction per lane and clock at 2.4 GHz."""
         w = self.w
-        pair_vecs = pair_b / (w.d * 4 + 4.0 / w.block_vecs)
+        pair_vecs = pair_b / (self.vector_bytes(self.scan_kernel) + 4.0 / w.block_vecs)
         lane_ops = pair_vecs * w.d * (2 if w.metric == "l2" else 1)
         scan_avg_ms = scan_ms / max(scan_n, 1)
         achieved = union_b / (scan_avg_ms * 1e-3) / 1e9 if scan_n else float("nan")
@@ -284,7 +293,7 @@ class Bench:
             note(f"configuration {self.idx}: latency of one request at batch {bs}, alone and beside the insert stream")
             alone = self.latencies(bs, iters, s)
             _, scan_ms = self.latencies(bs, max(iters // 3, 20), s, timed_scan=True)  # the timing events cost a few microseconds
-            _, ub = self.scan_bytes(min(iters, 32), bs=bs)
+            _, ub = self.scan_bytes(min(iters, 32), bs=bs, kernel=self.scanned_by(bs))
             stop, sent = threading.Event(), [0]
             th = threading.Thread(target=self.inserter, args=(stop, sent))
             t0 = time.perf_counter()
@@ -340,13 +349,14 @@ class Bench:
         self.g.close()
 
 
-def measured_traffic(workload: str, batch: int):
-    """HBM bytes per scan launch from the committed profiler summary of this
-    workload (FETCH_SIZE + WRITE_SIZE, scaled by the copy-kernel yardstick), or None."""
+def measured_traffic(workload: str, batch: int, kernel: str):
+    """HBM bytes per scan launch from the committed profiler summary of this workload
+    (FETCH_SIZE + WRITE_SIZE, scaled by the copy-kernel yardstick), or None where there is
+    none for the kernel that was timed."""
     path = os.path.join(ROOT, "profiles", f"k_scan_{workload}_batch{batch}_pmc.txt")
     try:
         for line in open(path):
-            if line.startswith("traffic_bytes_per_launch:"):
+            if line.startswith(f"traffic_bytes_per_launch of {kernel}:"):
                 return float(line.split(":")[1])
     except OSError:
         pass
@@ -480,7 +490,7 @@ def main() -> int:
         "ms_per_step": elapsed / args.steps * 1e3, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "f32", "data": "synthetic",
         "config": b.config_block(),
-        "roofline": b.roofline(scan_ms, scan_n, pair_b, union_b, measured_traffic(w.name, b.B)),
+        "roofline": b.roofline(scan_ms, scan_n, pair_b, union_b, measured_traffic(w.name, b.B, b.scan_kernel)),
         "inserts_per_s_in_step": args.steps * b.ib / elapsed,
         "bulk_load_vectors_per_s": len(w.base) / b.bulk_s,
         "host_generation_s": b.host_generation_s,

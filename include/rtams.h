@@ -146,6 +146,14 @@ int rtams_destroy(rtams_index *ix);
  * once, before the first add. */
 int rtams_set_centroids(rtams_index *ix, const float *d_centroids, void *hip_stream);
 
+/* Optional: halves beside the lists of an index that keeps floats.  rtams_halves_bytes says what they take (2 bytes a
+ * coordinate of the pool's vectors; 0: this kind of index keeps none), rtams_set_halves hands over that much device
+ * memory (256-byte aligned, the caller's, until the index is destroyed) before the first add.  Insertions then write every
+ * vector there as well, and long scans read the halves, half the bytes, to tell which vectors have to be scored; what
+ * is returned is computed from the floats as without them.  ESTATE once vectors are in. */
+size_t rtams_halves_bytes(const rtams_index *ix);
+int rtams_set_halves(rtams_index *ix, void *d_halves, size_t bytes);
+
 /* Product-quantised lists (pq_m > 0 only; the paper names IVF-PQ beside
  * IVF-Flat as a kind of list its blocks hold, without spelling it out; this is
  * the textbook method).  d_codebooks [pq_m][256][d / pq_m] fp32, copied into

@@ -30,7 +30,7 @@ int rtams_scan_kernels(rtams_index *ix, int64_t *launches3, int reset);
  * answered.  Per query of its nq: h_bounds the pruning bound as the key the scan compared with (0xFFFFFFFF: every
  * candidate kept), h_kept the number of candidates the scan kept.  *path, how it was scanned: 0 by the vector unit from
  * a plan, 1 by the vector unit without one ("small_requests"), 2 by the matrix cores in floats, 3 by their 16-bit
- * instructions, 4 over product-quantiser codes.  Any pointer may be NULL.  The caller has waited for the request. */
+ * instructions, 4 over product-quantiser codes, 5 by the halves beside the lists.  Any pointer may be NULL.  The caller has waited for the request. */
 int rtams_request_trace(rtams_index *ix, int32_t resource, int64_t nq, uint32_t *h_bounds, uint32_t *h_kept,
                         int32_t *path);
 /* A plain device-to-device copy kernel

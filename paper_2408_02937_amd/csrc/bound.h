@@ -124,6 +124,97 @@ __device__ uint32_t sample_scores(const Dev &D, int nprobe, int max_nprobe, int 
   return g_first;  // groups the lists did not have stay at the worst key (set by the caller)
 }
 
+// The same sample from the halves beside the lists: half the bytes, and a compute unit reads no more than so many at once.  A score is
+// of the query against what the halves hold; what they leave out goes into the bound where it is used (halves_bound_key),
+// for inner products but what depends on the vector, which is added here: the score is then no less than the vector's own.
+template <int METRIC>
+__device__ uint32_t sample_scores_halves(const Dev &D, int nprobe, int max_nprobe, int q, uint32_t want_groups, const SearchScratch &S,
+                                         const float4 *qv, float qnorm, uint32_t *skey, uint32_t *gkey, uint32_t part, uint32_t parts,
+                                         const NearestList &first) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), hc = D.hchunks;
+  const uint32_t mine = (uint32_t)(tid / kWave) * parts + part, step = blockDim.x / kWave * parts;
+  const uint32_t gpb = (uint32_t)D.groups_per_block;
+  const float ixs = 1.f / halves_scale(D);
+  const float over = qnorm * ((halves_are_floats(D) ? 0.f : 4.9e-4f) + (float)(2 * D.d + 8) * 6.0e-8f);
+  const int sub = lane & 3, of16 = lane >> 2, quads = (hc + 3) / 4;  // the lane's chunk of four, and its vector of each 16
+  uint32_t g_first = 0;  // groups of the lists before list p
+  for (int p = 0; p < nprobe && g_first < want_groups; ++p) {  // uniform over the workgroup
+    const size_t o = (size_t)q * max_nprobe + p;
+    const int list = p == 0 ? first.list : S.probe_list[o];
+    const uint32_t len = p == 0 ? first.len : S.probe_len[o];
+    uint32_t groups = (len + kWave - 1) / kWave;
+    const uint32_t have = (p == 0 ? first.nblk : D.nblk[list]) * gpb;  // never index the block table past the chain
+    if (groups > have) groups = have;
+    if (groups > want_groups - g_first) groups = want_groups - g_first;
+    for (uint32_t g = mine; g < groups; g += step) {
+      const uint32_t b = p == 0 && g == mine ? (uint32_t)*table_entry_at(D, first.dir, g / gpb) : (uint32_t)*table_entry(D, list, g / gpb);
+      const char *__restrict__ x = block_halves(D, b) + (size_t)(g % gpb) * ((size_t)hc * (kWave * 16));
+      float acc[4] = {0.f, 0.f, 0.f, 0.f}, nrm[4] = {0.f, 0.f, 0.f, 0.f};
+      auto load = [&](u32x4 *v, int quad) {  // the lane's chunk of vector 16 b + of16
+        const int width = min(hc - 4 * quad, 4), s = min(sub, width - 1);
+#pragma unroll
+        for (int b4 = 0; b4 < 4; ++b4) v[b4] = *reinterpret_cast<const u32x4 *>(x + (size_t)quad * (kWave * 64) + ((16 * b4 + of16) * width + s) * 16);
+      };
+      auto use = [&](const u32x4 *v, int quad) {
+        const bool on = 4 * quad + sub < hc;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          float4 y = qv[on ? 8 * quad + 2 * sub + s : 0];
+          if (!on) y = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+          for (int b4 = 0; b4 < 4; ++b4) {
+            const uint32_t w0 = on ? v[b4][2 * s] : 0u, w1 = on ? v[b4][2 * s + 1] : 0u;
+            const Half2 a = __builtin_bit_cast(Half2, w0), e = __builtin_bit_cast(Half2, w1);
+            accumulate<METRIC>(acc[b4], make_float4((float)a.x * ixs, (float)a.y * ixs, (float)e.x * ixs, (float)e.y * ixs), y);
+            if (METRIC == 1) nrm[b4] = __builtin_amdgcn_fdot2(e, e, __builtin_amdgcn_fdot2(a, a, nrm[b4], false), false);
+          }
+        }
+      };
+      int quad = 0;
+      for (; quad + 3 <= quads; quad += 3) {  // 12 loads of 1 KiB in flight
+        u32x4 v[3][4];
+#pragma unroll
+        for (int u = 0; u < 3; ++u) load(v[u], quad + u);
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+          use(v[u], quad + u);
+          __builtin_amdgcn_sched_barrier(0);  // one step's widened values at a time
+        }
+      }
+      for (; quad + 2 <= quads; quad += 2) {
+        u32x4 v[2][4];
+        load(v[0], quad);
+        load(v[1], quad + 1);
+        use(v[0], quad);
+        use(v[1], quad + 1);
+      }
+      if (quad < quads) {
+        u32x4 v[4];
+        load(v, quad);
+        use(v, quad);
+      }
+      // the four lanes of a vector have its sum between them; lane s of the four goes on with vector 16 s + of16
+      float mine = 0.f, mine_n = 0.f;
+#pragma unroll
+      for (int b4 = 0; b4 < 4; ++b4) {
+        float a = acc[b4] + quad_xor<1>(acc[b4]), n = nrm[b4];
+        a += quad_xor<2>(a);
+        if (METRIC == 1) { n += quad_xor<1>(n); n += quad_xor<2>(n); }
+        mine = sub == b4 ? a : mine;
+        mine_n = sub == b4 ? n : mine_n;
+      }
+      const uint32_t in_group = 16u * (uint32_t)sub + (uint32_t)of16, v = g * kWave + in_group;
+      const float sc = METRIC == 0 ? mine : fmaf(over, sqrtf(mine_n) * ixs, -mine);
+      const uint32_t key = v < len && fabsf(sc) < __builtin_inff() ? key_of_float(sc + 0.0f) : 0xFFFFFFFFu;
+      const size_t at = (size_t)(g_first + g) * kWave + in_group;
+      if (gkey) __hip_atomic_store(&gkey[at], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // uniform
+      else skey[at] = key;
+    }
+    g_first += groups;
+  }
+  return g_first;
+}
+
 // The same sample over product-quantiser codes: a vector's score is the sum, in the order of the
 // sub-spaces, of the entries of the query's table (in LDS) that its codes name.  What a wavefront needs of its group of
 // the nearest list is read ahead by the caller, while the table is made: five trips to memory, one behind the other.
@@ -203,11 +294,51 @@ constexpr size_t kPqBoundLdsBytes = kSampleMax * sizeof(uint32_t);
 // chunks, 0.96 to 0.98 at 120 to 160; eight groups of 256 chunks and fewer 1.00 to 1.04, so such a sample is left to one:
 // the hand-over between the workgroups is a microsecond.  Two workgroups to a query (168 queries and more) are 1 to 1.5 %
 // behind one.
-constexpr int kComputeUnits = 256;
 constexpr int kSampleParts = 4;
 constexpr uint32_t kSplitChunks = 260;
 
-template <bool PQ>
+// A query's halves and what goes with them (half_query_row), by one wavefront.
+__device__ inline void make_half_query(const Dev &D, const SearchScratch &S, int q, const float *__restrict__ Q, float *norm_out) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const float4 *__restrict__ y = reinterpret_cast<const float4 *>(Q + (size_t)q * D.d);
+  double nsq = 0.0;
+  for (int c = lane; c < D.d4; c += kWave) {
+    const float4 v = y[c];
+    nsq += (double)v.x * v.x + (double)v.y * v.y + (double)v.z * v.z + (double)v.w * v.w;
+  }
+  for (int o = kWave / 2; o > 0; o >>= 1) nsq += __shfl_xor(nsq, o);
+  const float scale = half_piece_scale((float)nsq), inv = 1.f / scale;
+  u32x4 *row = half_query_row(D, S, (uint32_t)q);
+  double hsq = 0.0, rsq = 0.0;  // |q'|^2 and |q - q'|^2
+  for (int c = lane; c < (int)half_row_units(D); c += kWave) {
+    uint2 h[2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const bool on = 2 * c + p < D.d4;
+      float4 v = y[on ? 2 * c + p : 0];
+      if (!on) v = make_float4(0.f, 0.f, 0.f, 0.f);
+      bool exact = true;
+      h[p] = pack_four_halves(v, scale, exact);
+      const float4 b = chunk_piece<1>(make_float4(__uint_as_float(h[p].x), __uint_as_float(h[p].y), 0.f, 0.f), 0);
+      auto add = [&](float have, float want) {
+        const double t = (double)have * (double)inv, r = (double)want - t;
+        hsq += t * t;
+        rsq += r * r;
+      };
+      add(b.x, v.x); add(b.y, v.y); add(b.z, v.z); add(b.w, v.w);
+    }
+    row[c] = u32x4{h[0].x, h[0].y, h[1].x, h[1].y};
+  }
+  for (int o = kWave / 2; o > 0; o >>= 1) { hsq += __shfl_xor(hsq, o); rsq += __shfl_xor(rsq, o); }
+  if (lane == 0) {
+    const float norm = sqrtf((float)(nsq > hsq ? nsq : hsq)) * 1.00001f;
+    *reinterpret_cast<float4 *>(row + half_row_units(D)) = make_float4(inv, (float)hsq, norm, sqrtf((float)rsq) * 1.00001f);
+    *norm_out = norm;
+  }
+}
+
+// HALVES: the request reads the halves beside the lists
+template <bool PQ, bool HALVES>
 __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, int k, const float *__restrict__ Q,
                              const SearchScratch &S, unsigned char *lds, uint32_t part, uint32_t parts,
                              const float *lut = nullptr, const PqNearest &nearest = PqNearest{}) {
@@ -221,8 +352,11 @@ __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, in
   const uint32_t qtotal = S.qtotal[q];
   NearestList first{PQ ? 0 : S.probe_list[o0], PQ ? nearest.len : S.probe_len[o0], 0u, 0};
   // |q|^2 for the norm form of the squared distance (the first wavefront computes it, in double)
-  const bool norm_form = !PQ && uses_norm_form(D);
+  constexpr bool halves = HALVES;
+  const bool norm_form = !PQ && !halves && uses_norm_form(D);
   __shared__ float s_qn;
+  __shared__ float s_norm;
+  if (halves && tid < kWave) make_half_query(D, S, q, Q, &s_norm);
   if (norm_form && tid < kWave) {
     double a = 0.0;
     for (int c = tid; c < D.d; c += kWave) {
@@ -239,11 +373,12 @@ __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, in
   // 1.14, the large ones where long lists meet few of the candidates.  (For L2 the bound also lets the scan stop early,
   // which is worth the sample.)
   const uint32_t no_bound_below =
-      D.metric == 0 ? (uint32_t)kNoBoundBelow : max((uint32_t)kNoBoundBelow, 32u * (uint32_t)D.d);
+      D.metric == 0 || halves ? (uint32_t)kNoBoundBelow : max((uint32_t)kNoBoundBelow, 32u * (uint32_t)D.d);
   auto keep_everything = [&]() {
     if (tid == 0 && part == 0) {
       S.bound[q] = 0xFFFFFFFFu;
-      *rec_count(S, (uint32_t)q) = 0u;
+      if (halves) rec_words_clear(S, (uint32_t)q);
+      else *rec_count(S, (uint32_t)q) = 0u;
     }
   };
   if (qtotal <= no_bound_below) {  // uniform over the workgroup
@@ -253,7 +388,8 @@ __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, in
   // sample size: 4 k, at least 512 and at least a fraction of the nearest list (the longer that
   // list, the more candidates a given score admits), at most kSampleMax and, but for the 512, at most
   // 1 MiB of vectors (with the rounding below a third more; a hot list of wide vectors would hold up the scan), in whole groups
-  uint32_t cap = PQ ? (uint32_t)kSampleMax : ((1u << 20) / ((uint32_t)D.vchunks * 16u)) & ~(uint32_t)(kWave - 1);
+  const uint32_t chunks = halves ? (uint32_t)D.hchunks : (uint32_t)D.vchunks;  // 16 bytes each, of a vector of the sample
+  uint32_t cap = PQ ? (uint32_t)kSampleMax : ((1u << 20) / (chunks * 16u)) & ~(uint32_t)(kWave - 1);
   // ... and for squared distances what k needs: a sample of fewer than k vectors is no bound at all, every candidate is then
   // kept and scored again (176 queries x 45 probes over lists of up to 144,000 x 1,036 floats, k 703: 19.0 ms a request without
   // a bound, 14.9 with; 64 queries x 32 over lists of 1,000 x 1,536 bytes, k 1,000: 0.13 of the time; inner products, which
@@ -266,7 +402,7 @@ __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, in
   want = want < 512u ? 512u : (want > cap ? cap : want);
   uint32_t want_groups = (want + kWave - 1) / kWave;
   if (!PQ) {
-    if (parts > 1 && (want_groups * (uint32_t)D.vchunks < kSplitChunks || want_groups * kWave > (uint32_t)D.nlist)) {
+    if (parts > 1 && (want_groups * chunks < kSplitChunks || want_groups * kWave > (uint32_t)D.nlist)) {
       if (part) return;  // uniform, and the same for all workgroups of the query
       parts = 1;
     }
@@ -303,7 +439,8 @@ __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, in
     first.dir = table_dir(D, first.list, ((uint32_t)(tid / kWave) * parts + part) / (uint32_t)D.groups_per_block);
   }
   if (!PQ)
-    for (int c = tid; c < D.d4; c += (int)blockDim.x) qv[c] = reinterpret_cast<const float4 *>(Q + (size_t)q * D.d)[c];
+    for (int c = tid; c < (HALVES ? 2 * D.hchunks : D.d4); c += (int)blockDim.x)
+      qv[c] = !HALVES || c < D.d4 ? reinterpret_cast<const float4 *>(Q + (size_t)q * D.d)[c] : make_float4(0.f, 0.f, 0.f, 0.f);
   for (int i = tid; i < (int)(want_groups * kWave); i += (int)blockDim.x) skey[i] = 0xFFFFFFFFu;
   __syncthreads();
   if (PQ) {
@@ -311,7 +448,10 @@ __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, in
   } else {
     uint32_t *gkey = parts > 1 ? reinterpret_cast<uint32_t *>(S.approx) + (size_t)q * D.nlist : nullptr;
     uint32_t groups;
-    if (D.metric == 0) {
+    if (HALVES) {  // (of a request that reads halves)
+      groups = D.metric == 0 ? sample_scores_halves<0>(D, nprobe, max_nprobe, q, want_groups, S, qv, s_norm, skey, gkey, part, parts, first)
+                             : sample_scores_halves<1>(D, nprobe, max_nprobe, q, want_groups, S, qv, s_norm, skey, gkey, part, parts, first);
+    } else if (D.metric == 0) {
       if (D.storage == 1) groups = sample_scores<0, 1>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, gkey, part, parts, first);
       else if (D.storage == 2) groups = sample_scores<0, 2>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, gkey, part, parts, first);
       else groups = sample_scores<0, 0>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, gkey, part, parts, first);
@@ -348,7 +488,8 @@ __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, in
     // the sample's scores are direct-form ones; the scan may compare norm-form scores with the bound
     if (norm_form) bound = loosened_key(bound, norm_form_slack(D.d), s_qn);
     S.bound[q] = bound;
-    *rec_count(S, (uint32_t)q) = 0u;
+    if (halves) rec_words_clear(S, (uint32_t)q);
+    else *rec_count(S, (uint32_t)q) = 0u;
   }
 }
 

@@ -116,7 +116,11 @@ __device__ inline float group_top(const float *x) {
 __global__ __launch_bounds__(256) void k_centroid_mean(Dev D) {
   __shared__ double s_sum[4][4];
   const int j = blockIdx.x, lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  if (j == 0 && threadIdx.x == 0) D.ctrl->cen = CentroidStats{};
+  if (j == 0 && threadIdx.x == 0) {
+    D.ctrl->cen = CentroidStats{};
+    D.ctrl->half_top = 0u;
+    D.ctrl->half_inexact = 0u;
+  }
   const float4 *col = reinterpret_cast<const float4 *>(D.centroids_t) + (size_t)j * D.nlist;
   double a[4] = {0.0, 0.0, 0.0, 0.0};
   for (int c = threadIdx.x; c < D.nlist; c += 256) {
@@ -153,17 +157,19 @@ __device__ inline void wg_atomic_max(float v, float *lds4, uint32_t *word) {
 __global__ __launch_bounds__(256) void k_centroid_top(Dev D) {
   __shared__ float s_max[4];
   const int lane = threadIdx.x & (kWave - 1);
-  float top = 0.f, bad = 0.f;
+  float top = 0.f, bad = 0.f, whole = 0.f;
   for (int c = blockIdx.x * 4 + threadIdx.x / kWave; c < D.nlist; c += gridDim.x * 4) {
     const float *row = D.centroids + (size_t)c * D.d;
     for (int j = lane; j < D.d; j += kWave) {
-      const float m = D.cmean[j], v = fabsf(row[j] - m);
+      const float x = row[j], m = D.cmean[j], v = fabsf(x - m);
       if (!(v < 1e17f) || !(fabsf(m) < 1e17f)) bad = 1.f;  // (squares and products of these, summed, stay finite)
       top = fmaxf(top, v);
+      whole = fmaxf(whole, fabsf(x) < __builtin_inff() ? fabsf(x) : 0.f);
     }
   }
   wg_atomic_max(top, s_max, &D.ctrl->cen.top_bits);
   wg_atomic_max(bad, s_max, &D.ctrl->cen.bad);
+  wg_atomic_max(whole, s_max, &D.ctrl->half_top);
 }
 
 __global__ __launch_bounds__(256) void k_centroid_halves(Dev D) {
@@ -200,7 +206,10 @@ __global__ __launch_bounds__(256) void k_centroid_halves(Dev D) {
     double m = 0.0;
     for (int j = lane; j < D.d; j += kWave) m = __builtin_fma((double)D.cmean[j], (double)D.cmean[j], m);
     for (int o = kWave / 2; o > 0; o >>= 1) m += __shfl_xor(m, o);
-    if (lane == 0) st.mean_norm = (float)__builtin_sqrt(m);
+    if (lane == 0) {
+      st.mean_norm = (float)__builtin_sqrt(m);
+      D.ctrl->half_scale = halves_scale_for(D.ctrl->half_top);
+    }
   }
 }
 

@@ -100,11 +100,10 @@ __device__ void scatter_pairs(const Dev &D, int nq, int nprobe, int max_nprobe, 
   }
 }
 
-__global__ __launch_bounds__(kGroupThreads, 4) void k_group(Dev D, int nq, int nprobe, int max_nprobe, int k,
-                                                         const float *__restrict__ Q,
-                                                         uint32_t item_budget, uint32_t max_per_xcd,
-                                                         uint32_t tile_q, uint32_t seg_base, int min_choice, int scatterers, int sample_parts,
-                                                         SearchScratch S) {
+template <bool HALVES>
+__device__ __forceinline__ void group_request(const Dev &D, int nq, int nprobe, int max_nprobe, int k, const float *__restrict__ Q,
+                                              uint32_t item_budget, uint32_t max_per_xcd, uint32_t tile_q, uint32_t seg_base,
+                                              int min_choice, int scatterers, int sample_parts, const SearchScratch &S) {
   const int tile_shift = 31 - __clz((int)tile_q);  // tiles hold a power of two of queries
   if (blockIdx.x >= 1 && (int)blockIdx.x <= scatterers) {  // uniform over the workgroup: these group the pairs by list
     scatter_pairs(D, nq, nprobe, max_nprobe, S, (int)blockIdx.x - 1, scatterers);
@@ -115,7 +114,7 @@ __global__ __launch_bounds__(kGroupThreads, 4) void k_group(Dev D, int nq, int n
   static_assert(kBoundLdsBytes >= kLdsEntries * sizeof(uint4), "the entries share the bound's LDS");
   if (blockIdx.x > 0) {  // this one sets the bound of a query
     const uint32_t at = blockIdx.x - 1u - (uint32_t)scatterers, part = at / (uint32_t)nq;
-    sample_bound<false>(D, (int)(at - part * (uint32_t)nq), nprobe, max_nprobe, k, Q, S, s_raw, part, (uint32_t)sample_parts);
+    sample_bound<false, HALVES>(D, (int)(at - part * (uint32_t)nq), nprobe, max_nprobe, k, Q, S, s_raw, part, (uint32_t)sample_parts);
     return;
   }
   __shared__ uint32_t s_a[kGroupThreads / kWave], s_b[kGroupThreads / kWave];  // pairs, items and work of every wavefront's lists
@@ -370,6 +369,21 @@ __global__ __launch_bounds__(kGroupThreads, 4) void k_group(Dev D, int nq, int n
   }
 }
 
+__global__ __launch_bounds__(kGroupThreads, 4) void k_group(Dev D, int nq, int nprobe, int max_nprobe, int k,
+                                                         const float *__restrict__ Q,
+                                                         uint32_t item_budget, uint32_t max_per_xcd,
+                                                         uint32_t tile_q, uint32_t seg_base, int min_choice, int scatterers, int sample_parts,
+                                                         SearchScratch S) {
+  group_request<false>(D, nq, nprobe, max_nprobe, k, Q, item_budget, max_per_xcd, tile_q, seg_base, min_choice, scatterers, sample_parts, S);
+}
+// ... of a request that reads the halves beside the lists: its samples do, too
+__global__ __launch_bounds__(kGroupThreads, 4) void k_plan_halves(Dev D, int nq, int nprobe, int max_nprobe, int k,
+                                                         const float *__restrict__ Q,
+                                                         uint32_t item_budget, uint32_t max_per_xcd,
+                                                         uint32_t tile_q, uint32_t seg_base, int min_choice, int scatterers, int sample_parts,
+                                                         SearchScratch S) {
+  group_request<true>(D, nq, nprobe, max_nprobe, k, Q, item_budget, max_per_xcd, tile_q, seg_base, min_choice, scatterers, sample_parts, S);
+}
 
 constexpr int kPqBoundThreads = 1024;
 
@@ -431,7 +445,7 @@ __global__ __launch_bounds__(kPqBoundThreads) void k_pq_bound(Dev D, int nprobe,
   }
   __syncthreads();  // the sample below reads the table
   __shared__ __attribute__((aligned(16))) unsigned char s_raw[kPqBoundLdsBytes];
-  sample_bound<true>(D, q, nprobe, max_nprobe, k, nullptr, S, s_raw, 0u, 1u, s_lut, nearest);
+  sample_bound<true, false>(D, q, nprobe, max_nprobe, k, nullptr, S, s_raw, 0u, 1u, s_lut, nearest);
 }
 
 
@@ -453,7 +467,7 @@ void launch_group(const Dev &D, int64_t nq, int nprobe, int max_nprobe, int k, c
   // (as many workgroups to a query as are on the chip at once; two are not worth their hand-over)
   const int64_t room = (2 * kComputeUnits - 1 - scatterers) / nq;
   const int parts = room < 3 ? 1 : room > kSampleParts ? kSampleParts : (int)room;
-  hipLaunchKernelGGL(k_group, dim3(1 + (unsigned)scatterers + (unsigned)(nq * parts)), dim3(kGroupThreads), 0, s, D, (int)nq,
+  hipLaunchKernelGGL(D.scan_halves ? k_plan_halves : k_group, dim3(1 + (unsigned)scatterers + (unsigned)(nq * parts)), dim3(kGroupThreads), 0, s, D, (int)nq,
                      nprobe, max_nprobe, k, Q, (uint32_t)item_budget,
                      (uint32_t)(sh.grid / (int)kXcds * sh.items_per_wg), (uint32_t)sh.tile_q, (uint32_t)sh.seg_base, sh.min_choice,
                      scatterers, parts, S);

@@ -218,20 +218,29 @@ __device__ __forceinline__ float4 stored_chunk(int storage, const float4 *__rest
 }
 
 // thread (vector i, chunk c) writes the chunk to its slot; the thread of chunk 0 also writes the id
-__global__ __launch_bounds__(256) void k_fill(Dev D, int64_t n, const float *__restrict__ Y,
+// (Number: 32 bits where the chunks can be counted in them; a division of 64-bit numbers is most of such a thread's instructions)
+template <typename Number>
+__global__ __launch_bounds__(256) void k_fill(Dev D, Number chunks, const float *__restrict__ Y,
                                               const int64_t *__restrict__ ids, int64_t id_base,
                                               const int32_t *__restrict__ assign,
                                               const uint32_t *__restrict__ did) {
-  int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n * D.vchunks) return;
-  int64_t i = t / D.vchunks;
-  int c = (int)(t - i * D.vchunks);
+  const Number t = (Number)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= chunks) return;
+  const Number i = t / (Number)D.vchunks;
+  const int c = (int)(t - i * (Number)D.vchunks);
   int list = assign[i];
   uint32_t pos = did[i];
   uint32_t mid = pos / (uint32_t)D.T_m, moff = pos % (uint32_t)D.T_m;
   if (mid >= D.nblk[list]) return;  // the block could not be opened (pool exhausted)
   uint32_t b = (uint32_t)*table_entry(D, list, mid);
-  block_vecs(D, b)[vec_chunk_index(D, moff, c)] = stored_chunk(D.storage, reinterpret_cast<const float4 *>(Y) + i * D.d4, c);
+  const float4 v = stored_chunk(D.storage, reinterpret_cast<const float4 *>(Y) + (size_t)i * D.d4, c);
+  block_vecs(D, b)[vec_chunk_index(D, moff, c)] = v;
+  if (D.halves_stride) {  // uniform
+    const uint32_t known = D.ctrl->half_inexact;
+    bool exact = true;
+    put_halves(D, b, moff, c, v, halves_scale(D), exact);
+    if (!exact && !known) D.ctrl->half_inexact = 1u;
+  }
   if (c == 0) block_ids(D, b)[moff] = ids ? ids[i] : id_base + i;
 }
 
@@ -240,7 +249,10 @@ __global__ __launch_bounds__(256) void k_fill(Dev D, int64_t n, const float *__r
 // batch: 65,536 x 768 took 228 us for 400 MB.  So the batch is put in the order of its lists first (k_fill_order: source
 // and place of every vector; ids go out here), and a workgroup takes 64 consecutive ones, 16 chunks of each: 256 bytes
 // of a vector at a time into LDS, and out of it with consecutive places side by side, as many to a cache line as the
-// batch has for the list: 65,536 x 768 into 8,192 lists 124 us behind 7 for the order.
+// batch has for the list: 65,536 x 768 into 8,192 lists 124 us behind 7 for the order.  A run of a list ends inside a line of memory
+// that the next one goes on with, so neighbouring runs go to one XCD, and the vectors, which nobody reads again, are read past the
+// caches, where the lines wait for their other halves: with the halves beside the lists, half as much again to write, 154 us
+// without the two, 131 with the second and 129 with both.
 __global__ __launch_bounds__(256) void k_fill_order(Dev D, int64_t n, const int64_t *__restrict__ ids, int64_t id_base,
                                                     const int32_t *__restrict__ assign, const uint32_t *__restrict__ did,
                                                     const uint32_t *__restrict__ start, uint2 *__restrict__ order) {
@@ -260,13 +272,15 @@ __global__ __launch_bounds__(256) void k_fill_order(Dev D, int64_t n, const int6
 }
 
 constexpr int kFillSlots = 64, kFillChunks = 16;
+constexpr unsigned kFillXcds = 8;
 template <int ST>
 __global__ __launch_bounds__(256) void k_fill_lists(Dev D, int64_t n, const float *__restrict__ Y,
                                                     const uint2 *__restrict__ order) {
   __shared__ float4 tile[kFillSlots][kFillChunks + 1];  // (the odd row length spreads a column over the banks)
   __shared__ uint2 s_at[kFillSlots];
   const int tid = threadIdx.x;
-  const int64_t s0 = (int64_t)blockIdx.x * kFillSlots;
+  const uint32_t of_xcd = gridDim.x / kFillXcds;
+  const int64_t s0 = (int64_t)(blockIdx.x % kFillXcds * of_xcd + blockIdx.x / kFillXcds) * kFillSlots;
   const int c0 = (int)blockIdx.y * kFillChunks, chunks = min(kFillChunks, D.vchunks - c0);
   if (tid < kFillSlots) s_at[tid] = s0 + tid < n ? order[s0 + tid] : make_uint2(~0u, 0u);
   __syncthreads();
@@ -276,23 +290,52 @@ __global__ __launch_bounds__(256) void k_fill_lists(Dev D, int64_t n, const floa
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const uint32_t i = s_at[tid / kFillChunks + 16 * u].x;
-      v[u] = i != ~0u && c < chunks ? stored_chunk(ST, reinterpret_cast<const float4 *>(Y) + (size_t)i * D.d4, c0 + c)
-                                    : make_float4(0.f, 0.f, 0.f, 0.f);
+      const bool on = i != ~0u && c < chunks;
+      if (ST == 0) {
+        typedef float Floats __attribute__((ext_vector_type(4)));
+        Floats z = {0.f, 0.f, 0.f, 0.f};
+        if (on) z = __builtin_nontemporal_load(reinterpret_cast<const Floats *>(Y) + (size_t)i * D.d4 + c0 + c);
+        v[u] = make_float4(z.x, z.y, z.z, z.w);
+      } else {
+        v[u] = on ? stored_chunk(ST, reinterpret_cast<const float4 *>(Y) + (size_t)i * D.d4, c0 + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) tile[tid / kFillChunks + 16 * u][c] = v[u];
   }
   __syncthreads();
-  const int slot = tid & (kFillSlots - 1);
+  {
+    const int slot = tid & (kFillSlots - 1);
+    const uint2 at = s_at[slot];
+    if (at.x != ~0u) {
+      const uint32_t b = at.y / (uint32_t)D.T_m, moff = at.y - b * (uint32_t)D.T_m;
+      float4 *to = block_vecs(D, b) + vec_chunk_index(D, moff, c0);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int c = tid / kFillSlots + 4 * u;
+        if (c < chunks) to[(size_t)c * kWave] = tile[slot][c];
+      }
+    }
+  }
+  if (ST != 0 || D.halves_stride == 0) return;  // uniform
+  // four lanes to a vector: 64 bytes of halves side by side
+  const int slot = tid / 4;
   const uint2 at = s_at[slot];
   if (at.x == ~0u) return;
+  const uint32_t known = D.ctrl->half_inexact;
+  const float scale = halves_scale(D);
+  bool exact = true;
   const uint32_t b = at.y / (uint32_t)D.T_m, moff = at.y - b * (uint32_t)D.T_m;
-  float4 *to = block_vecs(D, b) + vec_chunk_index(D, moff, c0);
+  char *half = block_halves(D, b);
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int c = tid / kFillSlots + 4 * u;
-    if (c < chunks) to[(size_t)c * kWave] = tile[slot][c];
+  for (int u = 0; u < kFillChunks / 8; ++u) {
+    const int h = (tid & 3) + 4 * u;
+    if (2 * h >= chunks) break;
+    const uint2 lo = pack_four_halves(tile[slot][2 * h], scale, exact);
+    const uint2 hi = 2 * h + 1 < chunks ? pack_four_halves(tile[slot][2 * h + 1], scale, exact) : make_uint2(0u, 0u);
+    *reinterpret_cast<u32x4 *>(half + half_chunk_at(D, moff, (uint32_t)(c0 / 2 + h))) = u32x4{lo.x, lo.y, hi.x, hi.y};
   }
+  if (!exact && !known) D.ctrl->half_inexact = 1u;
 }
 
 // ---- publish: makes the batch visible and evaluates Exceed() (the equation defining it: vectors appended since the
@@ -408,8 +451,13 @@ __global__ __launch_bounds__(kTailVecs) void k_insert_tail(Dev D, int n, int spl
     if (blk != ~0u) block_ids(D, blk)[pos % T] = id;
   }
   __syncthreads();
+  const float scale = D.halves_stride ? halves_scale(D) : 1.f;
+  const uint32_t inexact = D.ctrl->half_inexact;
+  bool exact = true;
   auto put = [&](int t, int i, int c, const float4 &v) {
-    if (s_blk[i] != ~0u) block_vecs(D, s_blk[i])[vec_chunk_index(D, s_off[i], c)] = v;
+    if (s_blk[i] == ~0u) return;
+    block_vecs(D, s_blk[i])[vec_chunk_index(D, s_off[i], c)] = v;
+    if (D.halves_stride) put_halves(D, s_blk[i], s_off[i], c, v, scale, exact);  // uniform
   };
   int t = tid;
   if (D.storage == 0) {
@@ -421,6 +469,7 @@ __global__ __launch_bounds__(kTailVecs) void k_insert_tail(Dev D, int n, int spl
     const int i = t / D.vchunks, c = t - i * D.vchunks;
     put(t, i, c, stored_chunk(D.storage, y4 + (size_t)i * D.d4, c));
   }
+  if (!exact && !inexact) D.ctrl->half_inexact = 1u;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's part of the vectors is out ...
   __syncthreads();                                  // ... and so is everybody's before any list is published
   wg_publish(D, leads ? list : -1);
@@ -490,7 +539,8 @@ void launch_fill(const Dev &D, int64_t n, const float *Y, const int64_t *ids, in
   if (fills_by_lists(D, n, S)) {
     hipLaunchKernelGGL(k_fill_order, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, D, n, ids, id_base, S.assign, S.did,
                        fill_start(S), fill_order(S));
-    const dim3 grid((unsigned)((n + kFillSlots - 1) / kFillSlots), (unsigned)((D.vchunks + kFillChunks - 1) / kFillChunks));
+    constexpr int64_t kTurn = kFillSlots * (int64_t)kFillXcds;
+    const dim3 grid((unsigned)((n + kTurn - 1) / kTurn) * kFillXcds, (unsigned)((D.vchunks + kFillChunks - 1) / kFillChunks));
     if (D.storage == 1) hipLaunchKernelGGL(k_fill_lists<1>, grid, dim3(256), 0, s, D, n, Y, fill_order(S));
     else if (D.storage == 2) hipLaunchKernelGGL(k_fill_lists<2>, grid, dim3(256), 0, s, D, n, Y, fill_order(S));
     else hipLaunchKernelGGL(k_fill_lists<0>, grid, dim3(256), 0, s, D, n, Y, fill_order(S));
@@ -498,7 +548,8 @@ void launch_fill(const Dev &D, int64_t n, const float *Y, const int64_t *ids, in
   }
   int64_t threads = n * D.vchunks;
   unsigned grid = (unsigned)((threads + 255) / 256);
-  hipLaunchKernelGGL(k_fill, dim3(grid), dim3(256), 0, s, D, n, Y, ids, id_base, S.assign, S.did);
+  if (threads < (int64_t)1 << 31) hipLaunchKernelGGL(k_fill<uint32_t>, dim3(grid), dim3(256), 0, s, D, (uint32_t)threads, Y, ids, id_base, S.assign, S.did);
+  else hipLaunchKernelGGL(k_fill<uint64_t>, dim3(grid), dim3(256), 0, s, D, (uint64_t)threads, Y, ids, id_base, S.assign, S.did);
 }
 
 // How much one workgroup moves before a launch of its own is faster, in 16-byte chunks: what its threads hold in

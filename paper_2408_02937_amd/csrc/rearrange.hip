@@ -204,7 +204,7 @@ __global__ __launch_bounds__(kRearrThreads) void k_rearr_plan(Dev D, RearrangeSc
   }
 }
 
-// ---- block copies: whole blocks (header, ids, vectors), 16 bytes per thread
+// ---- block copies: whole blocks (header, ids, vectors, and the halves beside them), 16 bytes per thread
 template <int PHASE>
 __global__ __launch_bounds__(256) void k_rearr_copy(Dev D, RearrangeScratch R) {
   const RearrangeHead *H = R.head;
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(256) void k_rearr_copy(Dev D, RearrangeScratch R) {
   if (M == 0) return;
   const int list = H->list;
   const uint32_t b0 = (uint32_t)*table_entry(D, list, 0);
-  const uint32_t per = (uint32_t)(D.block_stride / 16);
+  const uint32_t own = (uint32_t)(D.block_stride / 16), per = own + (uint32_t)(D.halves_stride / 16);
   const uint64_t work = (uint64_t)M * per;
   for (uint64_t w = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; w < work;
        w += (uint64_t)gridDim.x * blockDim.x) {
@@ -225,9 +225,10 @@ __global__ __launch_bounds__(256) void k_rearr_copy(Dev D, RearrangeScratch R) {
     } else {
       from = (uint32_t)*table_entry(D, list, R.mv_t[j]); to = tgt;
     }
-    const uint4 *src = reinterpret_cast<const uint4 *>(D.blocks + (size_t)from * D.block_stride);
-    uint4 *dst = reinterpret_cast<uint4 *>(D.blocks + (size_t)to * D.block_stride);
-    dst[o] = src[o];
+    const bool half = o >= own;
+    char *base = half ? D.halves : D.blocks;
+    const size_t stride = half ? D.halves_stride : D.block_stride, at = (size_t)(half ? o - own : o) * 16;
+    *reinterpret_cast<uint4 *>(base + (size_t)to * stride + at) = *reinterpret_cast<const uint4 *>(base + (size_t)from * stride + at);
   }
 }
 

@@ -224,6 +224,7 @@ int allow_large_lds_on_current_device() {
   HIP_TRY(allow_large_lds_group());
   HIP_TRY(allow_large_lds_scan_mm());
   HIP_TRY(allow_large_lds_pq_scan());
+  HIP_TRY(allow_large_lds_scan_halves());
   g_lds_allowed[dev] = true;
   return RTAMS_OK;
 }
@@ -284,6 +285,7 @@ struct rtams_index {
   std::atomic<int64_t> ordered_add{0};  // positions inside a list in the order of the batch instead of arrival order
   std::atomic<int64_t> use_mfma{1};  // matrix-core filter in front of the exact coarse arithmetic
   std::atomic<int64_t> scan_mfma{1}; // flat lists: the scan's dot products on the matrix cores
+  std::atomic<int64_t> scan_halves{1};     // the scan reads the halves beside float lists, where there are: 0 never, 1 when it pays, 2 whenever it can
   std::atomic<int64_t> small_requests{1};  // small requests in three launches, without a plan (0: like all others)
   std::atomic<int64_t> scan_byte_weight{0};
   std::atomic<int64_t> scan_min_choice{-1};
@@ -504,6 +506,7 @@ int rtams_create(const rtams_config *cfg, rtams_index **out) {
   D.storage = cfg->storage;
   D.vchunks = cfg->storage == RTAMS_F16 ? cfg->d / 8 : cfg->storage == RTAMS_U8 ? cfg->d / 16 : cfg->d / 4;
   D.groups_per_block = cfg->block_vecs / kWave;
+  D.hchunks = (cfg->d + 7) / 8;
   D.nblocks = (uint32_t)L.nblocks;
   D.slab_cap = (uint32_t)(L.slab_cap > 0xffffffffull ? 0xffffffffull : L.slab_cap);
   D.T_mp = cfg->rearrange_threshold;
@@ -703,6 +706,24 @@ int rtams_set_centroids(rtams_index *ix, const float *d_centroids, void *hip_str
   return RTAMS_OK;
 }
 
+size_t rtams_halves_bytes(const rtams_index *ix) {
+  if (!ix || ix->cfg.pq_m > 0 || ix->cfg.storage != RTAMS_F32 || ix->cfg.nlist < 16) return 0;
+  return (size_t)ix->dev.nblocks * (size_t)ix->cfg.block_vecs * (size_t)ix->dev.hchunks * 16;
+}
+
+int rtams_set_halves(rtams_index *ix, void *d_halves, size_t bytes) {
+  if (!ix || !d_halves || (uintptr_t)d_halves % kAlign) return fail(RTAMS_EINVAL, "bad argument to set_halves");
+  const size_t want = rtams_halves_bytes(ix);
+  if (want == 0) return fail(RTAMS_ESTATE, "this index keeps no halves beside its lists (lists of floats, 16 of them or more, do)");
+  if (bytes < want) return fail(RTAMS_EINVAL, "halves of %zu bytes, %zu needed", bytes, want);
+  std::lock_guard<std::mutex> g(ix->data_mutex);
+  if (ix->ntotal_host > 0) return fail(RTAMS_ESTATE, "halves cannot be added once vectors are in");
+  std::unique_lock<std::shared_mutex> searches(ix->fence_mutex);
+  ix->dev.halves = static_cast<char *>(d_halves);
+  ix->dev.halves_stride = (uint64_t)ix->cfg.block_vecs * (uint64_t)ix->dev.hchunks * 16;
+  return RTAMS_OK;
+}
+
 int rtams_set_codebooks(rtams_index *ix, const float *d_codebooks, void *hip_stream) {
   if (!ix || !d_codebooks) return fail(RTAMS_EINVAL, "NULL argument");
   if (ix->cfg.pq_m == 0) return fail(RTAMS_ESTATE, "the index holds flat lists (pq_m is 0)");
@@ -817,7 +838,7 @@ static SearchScratch small_scratch(SearchScratch S) {
 // The selection of a request whose scan is enqueued, and the end of the request.
 static int finish_search(rtams_index *ix, const Dev &D, const SearchScratch &S, int r, int64_t nq, const float *d_queries, int32_t k, int32_t nprobe,
                          float *d_out_dist, int64_t *d_out_ids, hipStream_t s) {
-  launch_select(D, nq, k, nprobe, ix->cfg.max_nprobe, d_queries, S, d_out_dist, d_out_ids, s);
+  launch_select(D, nq, k, d_queries, S, d_out_dist, d_out_ids, s);
   hipError_t e = hipGetLastError();
   hipError_t e2 = hipEventRecord(ix->res[r].done, s);
   ix->res[r].state.store(RES_PENDING, std::memory_order_release);
@@ -861,7 +882,16 @@ static int search_on(rtams_index *ix, int r, int64_t nq, const float *d_queries,
   const int64_t longest = longest_list_bound(ix);
   const bool small = !recorded && r < ix->n_res && ix->small_requests.load(std::memory_order_relaxed) != 0 &&
                      !searches_by_filter(ix, nq) && small_request(D, nq, nprobe, ix->ntotal_host / ix->cfg.nlist + 1, longest);
-  ix->res[r].path = D.pq_m > 0 ? 4 : D.scan_mfma ? 1 + D.scan_mfma : small ? 1 : 0;
+  if (!small && D.halves_stride != 0) {  // (the index holds lists of floats)
+    const int64_t mode = ix->scan_halves.load(std::memory_order_relaxed);
+    D.scan_halves = mode == 2 || (mode == 1 && ix->scan_mfma.load(std::memory_order_relaxed) == 1 &&
+                                  halves_scan_pays(D, nq, nprobe, k, ix->ntotal_host / ix->cfg.nlist + 1, longest_list(ix)));
+    if (D.scan_halves) {
+      const int64_t avg_len = ix->ntotal_host / ix->cfg.nlist + 1;
+      if (nq * nprobe >= 16 * (int64_t)ix->cfg.nlist || longest_list(ix) >= 16 * avg_len) D.scan_halves = 2;
+    }
+  }
+  ix->res[r].path = D.pq_m > 0 ? 4 : D.scan_halves ? 5 : D.scan_mfma ? 1 + D.scan_mfma : small ? 1 : 0;
   if (small) {
     const int64_t size = D.scan_single ? kWave : 2 * kWave;
     const int64_t units = std::min(ix->ntotal_host / size + nprobe, nprobe * (longest / size + 1));
@@ -903,7 +933,7 @@ static int search_on(rtams_index *ix, int r, int64_t nq, const float *d_queries,
   if (budget < 1024) budget = 1024;
   launch_group(D, nq, nprobe, ix->cfg.max_nprobe, k, d_queries, (int)budget, S, s);
   const bool timed = ix->profile_scan.load(std::memory_order_relaxed) != 0;
-  if (timed) ix->timed_scans[D.pq_m > 0 ? 2 : D.scan_mfma ? 1 : 0].fetch_add(1, std::memory_order_relaxed);
+  if (timed) ix->timed_scans[D.pq_m > 0 ? 2 : D.scan_mfma || D.scan_halves ? 1 : 0].fetch_add(1, std::memory_order_relaxed);
   if (long_scan) {  // behind the long scan enqueued before it
     std::lock_guard<std::mutex> chain(ix->scan_mutex);
     if (ix->scan_tail && ix->scan_tail != ix->res[r].scan_done) (void)hipStreamWaitEvent(s, ix->scan_tail, 0);
@@ -1302,6 +1332,7 @@ int rtams_set_param(rtams_index *ix, const char *key, int64_t value) {
   if (!strcmp(key, "scan_steal")) { ix->scan_steal = value != 0; return RTAMS_OK; }
   if (!strcmp(key, "scan_exclusive_bytes")) { ix->scan_exclusive_bytes = value > 0 ? value : 0; return RTAMS_OK; }
   if (!strcmp(key, "scan_min_choice")) { ix->scan_min_choice = value < 0 ? -1 : value > 7 ? 7 : value; return RTAMS_OK; }
+  if (!strcmp(key, "scan_halves")) { ix->scan_halves = value; return RTAMS_OK; }
   if (!strcmp(key, "small_requests")) { ix->small_requests = value != 0; return RTAMS_OK; }
   if (!strcmp(key, "scan_byte_weight")) { ix->scan_byte_weight = value > 0 ? value : 0; return RTAMS_OK; }
   if (!strcmp(key, "scan_max_items")) { ix->scan_max_items = value > 1024 ? value : 1024; return RTAMS_OK; }

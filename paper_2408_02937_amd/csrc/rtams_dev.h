@@ -52,7 +52,10 @@ struct Ctrl {
   int32_t search_error;      // rtams_status raised by a kernel of a search (scratch too small): inserts do not look at it
   CentroidStats cen;
   uint32_t fill_cur;         // vectors of the batch whose lists have their place in the order of the fill (0 between batches)
-  uint32_t pad3[19];
+  uint32_t half_top;         // largest coordinate of a centroid, float bits ...
+  float half_scale;          // ... and the power of two that the halves beside the lists are scaled by
+  uint32_t half_inexact;     // some vector's halves are not its floats
+  uint32_t pad3[16];
 };
 
 // Words the device writes straight into pinned host memory, so the host can
@@ -111,6 +114,11 @@ struct Dev {
   int32_t *slab;            // block-table entries
   int32_t *free_stack;      // [nblocks]
   int32_t *mark;            // [nblocks] scratch for validation
+  // (behind all that the kernels of small requests read)
+  char *halves;             // flat lists of floats: the halves of block b's vectors, at b * halves_stride
+  uint64_t halves_stride;   // bytes of a block's halves (0: none are kept)
+  int32_t hchunks;          // 16-byte chunks of a vector's halves: d / 8, rounded up
+  int32_t scan_halves;      // the request reads them: 1, 2 with tiles of 32 queries (set per request)
 };
 
 // ---- block table: a growable array per list, made of doubling segments ----
@@ -274,6 +282,44 @@ __device__ __forceinline__ uint32_t pack_halves(float lo, float hi) {
 __device__ __forceinline__ uint32_t byte_of(float f) { return (uint32_t)fminf(fmaxf(__builtin_rintf(f), 0.f), 255.f); }
 __device__ __forceinline__ uint32_t pack_bytes(const float4 &v) {
   return byte_of(v.x) | (byte_of(v.y) << 8) | (byte_of(v.z) << 16) | (byte_of(v.w) << 24);
+}
+
+// ---- halves beside the lists of floats: every coordinate under one power-of-two scale as a half.  A scan that reads them instead
+// of the floats has half the bytes to read; what it keeps is scored again from the floats, so they decide nothing but what
+// is looked at.  The scale brings the largest coordinate of a centroid to 2^8: vectors may be 2^7 times as large before a half
+// overflows.  In groups of 64 vectors as the lists, but within a group 32 coordinates (four 16-byte chunks) of a vector side by
+// side, vector after vector, then the next 32; what is left of d (rounded up to 8, with zeros) likewise.  So what is written of a
+// vector is whole 64-byte pieces, and 16 vectors' worth of a matrix instruction is 1 KiB in one run.
+__device__ inline float halves_scale(const Dev &D) { return D.ctrl->half_scale; }
+__device__ inline float halves_scale_for(uint32_t t) {  // t: that coordinate, float bits
+  if (t < 0x00800000u || t >= 0x7f800000u) return 1.f;
+  int s = 8 - ((int)(t >> 23) - 127);
+  s = s > 100 ? 100 : s < -100 ? -100 : s;
+  return __uint_as_float((uint32_t)(s + 127) << 23);
+}
+// (what lies below the smallest normal half is zero, whatever a unit makes of subnormals)
+__device__ __forceinline__ float no_subnormal_half(float x) { return fabsf(x) < 6.1035156e-5f ? 0.f : x; }
+// (halves times one over the scale are the floats, to the last bit: `exact` stays true)
+__device__ __forceinline__ uint2 pack_four_halves(const float4 &v, float scale, bool &exact) {
+  const float a = v.x * scale, b = v.y * scale, c = v.z * scale, e = v.w * scale;
+  const uint2 h = make_uint2(pack_halves(no_subnormal_half(a), no_subnormal_half(b)), pack_halves(no_subnormal_half(c), no_subnormal_half(e)));
+  const Half2 lo = __builtin_bit_cast(Half2, h.x), hi = __builtin_bit_cast(Half2, h.y);
+  exact = exact && (float)lo.x == a && (float)lo.y == b && (float)hi.x == c && (float)hi.y == e && fabsf(a) < 65536.f && fabsf(b) < 65536.f &&
+          fabsf(c) < 65536.f && fabsf(e) < 65536.f;
+  return h;
+}
+__device__ inline char *block_halves(const Dev &D, uint32_t b) { return D.halves + (size_t)b * D.halves_stride; }
+// byte offset, inside a block's halves, of 16-byte chunk c of the vector at moff
+__device__ inline size_t half_chunk_at(const Dev &D, uint32_t moff, uint32_t c) {
+  const uint32_t quad = c / 4u, width = min((uint32_t)D.hchunks - 4u * quad, 4u);
+  return (size_t)(moff / kWave) * ((size_t)D.hchunks * (kWave * 16u)) + (size_t)quad * (kWave * 64u) + (moff % kWave * width + c % 4u) * 16u;
+}
+// chunk c of four floats of the vector at moff
+__device__ __forceinline__ void put_halves(const Dev &D, uint32_t b, uint32_t moff, int c, const float4 &v, float scale, bool &exact) {
+  const uint2 h = pack_four_halves(v, scale, exact);
+  char *to = block_halves(D, b) + half_chunk_at(D, moff, (uint32_t)c >> 1);
+  if (c == D.d4 - 1 && !(c & 1)) *reinterpret_cast<u32x4 *>(to) = u32x4{h.x, h.y, 0u, 0u};
+  else reinterpret_cast<uint2 *>(to)[c & 1] = h;
 }
 
 }  // namespace rtams

@@ -131,6 +131,7 @@ hipError_t allow_large_lds_coarse();
 hipError_t allow_large_lds_group();
 hipError_t allow_large_lds_scan_mm();
 hipError_t allow_large_lds_pq_scan();
+hipError_t allow_large_lds_scan_halves();
 template <typename Kernel>
 inline hipError_t allow_lds(Kernel kernel, size_t bytes) {
   return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
@@ -212,6 +213,8 @@ void launch_scan(const Dev &D, int64_t nq, int nprobe, int max_nprobe, const flo
 struct ScanShape;
 void launch_scan_mm(const Dev &D, const ScanShape &sh, int max_nprobe, const float *Q, const SearchScratch &S,
                     hipStream_t s);
+// the scan of the halves beside float lists (launch_scan hands such requests on to it)
+void launch_scan_halves(const Dev &D, const ScanShape &sh, int max_nprobe, const SearchScratch &S, hipStream_t s);
 // the scan over product-quantiser codes (launch_scan hands quantised lists on to it)
 void launch_pq_scan(const Dev &D, int64_t nq, int nprobe, int max_nprobe, int item_budget,
                     const SearchScratch &S, hipStream_t s);
@@ -223,8 +226,8 @@ void launch_small_front(const Dev &D, int64_t nq, int nprobe, int max_nprobe, in
                         hipStream_t s);
 void launch_scan_small(const Dev &D, int64_t nq, int nprobe, int max_nprobe, int64_t units, const float *Q,
                        const SearchScratch &S, hipStream_t s);
-void launch_select(const Dev &D, int64_t nq, int k, int nprobe, int max_nprobe, const float *Q,
-                   const SearchScratch &S, float *out_dist, int64_t *out_ids, hipStream_t s);
+void launch_select(const Dev &D, int64_t nq, int k, const float *Q, const SearchScratch &S, float *out_dist, int64_t *out_ids,
+                   hipStream_t s);
 
 // pq.hip -----------------------------------------------------------------------
 void launch_pq_fill(const Dev &D, int64_t n, const float *Y, const int64_t *ids, int64_t id_base,

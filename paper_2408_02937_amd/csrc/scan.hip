@@ -53,6 +53,10 @@ void launch_scan(const Dev &D, int64_t nq, int nprobe, int max_nprobe, const flo
     return;
   }
   const ScanShape sh = scan_shape(D, item_budget);
+  if (D.scan_halves) {
+    launch_scan_halves(D, sh, max_nprobe, S, s);
+    return;
+  }
   if (sh.mm) {
     launch_scan_mm(D, sh, max_nprobe, Q, S, s);
     return;

@@ -390,11 +390,94 @@ __device__ __host__ inline bool uses_norm_form(const Dev &D) {
   return D.scan_mfma != 0 && D.metric == 0 && D.pq_m == 0;
 }
 
+// ---- scores from the halves beside the lists.  With x' the vector and q' the query as their halves have them (u = 2^-11 the
+// unit roundoff of halves, t = 2^-14 sqrt(d) / scale what zeroed subnormals can come to, s = |q - q'| computed),
+//   |x - x'| <= u |x| + t.
+// Squared distances: | |q - x| - |q' - x'| | <= s + t + u |x|, where |x| is at most |q| plus the distance: whichever of the two
+// distances is r, the other one is at most r + 1.001 u (|q| + r) + e with e = s + 1.001 t.  The scan has |q' - x'|^2 in the
+// norm form.  Its sum of products is one of at most 64 after the other, each an addition that may be 2^-23 off, and of d / 64 such
+// sums; |x'|^2 is of lanes' sums of a quarter of the coordinates: with P >= |q'|, |x'|, all in all it is off by at most
+// halves_slack(d) P^2, and the direct form by d + 2 roundings of itself.  (The margin goes with the distance times the norm over
+// 2^11, and with the norm squared over 2^15: that of the norm form in one sum of d, which it need not be here, over 2^12 at d 256.)
+// Inner products: |<q, x> - <q', x'>| <= |x'| (s + 1.001 u |q|) + 1.001 t |q|, and the roundings of the sum of products and the d
+// of the direct one: a |x'| + e.  The scan has |x'| of every vector and keeps the least the inner product's negative can be but
+// for e, which is in the bound.
+struct HalfQuery {
+  float unscale;  // turns a product of halves into a product
+  float a;        // squared distances: |q'|^2; inner products: a as above
+  float norm;     // |q|, from above
+  float e;
+  float u;        // 1.001 2^-11, or 0 where the halves of all vectors are their floats
+};
+// whether the halves of every vector inserted so far are its floats (then nothing is left out: u and t are zero)
+__device__ inline bool halves_are_floats(const Dev &D) {
+  return __hip_atomic_load(&D.ctrl->half_inexact, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
+}
+__host__ __device__ inline uint32_t half_row_units(const Dev &D) { return (uint32_t)(D.hchunks + 3) / 4u * 4u; }
+// of query q: its halves, zeros up to whole steps of 32 coordinates, then what half_query() makes its HalfQuery of: one over its
+// scale, |q'|^2, |q| from above, and s (in the room the coarse filter has for
+// halves of the queries, twice what they take; nobody needs those once the probes are chosen)
+__device__ inline u32x4 *half_query_row(const Dev &D, const SearchScratch &S, uint32_t q) {
+  return S.qhalf + (size_t)q * (half_row_units(D) + 1u);
+}
+__device__ inline HalfQuery half_query(const Dev &D, const SearchScratch &S, uint32_t q) {
+  const float4 w = *reinterpret_cast<const float4 *>(half_query_row(D, S, q) + half_row_units(D));
+  const bool exact = halves_are_floats(D);
+  const float ixs = 1.f / halves_scale(D), t = exact ? 0.f : 6.11e-5f * sqrtf((float)D.d) * ixs;  // (6.11e-5: 1.001 2^-14)
+  HalfQuery m{w.x * ixs, w.y, w.z, w.w + t, exact ? 0.f : 4.888e-4f};
+  if (D.metric != 0) {
+    m.a = 1.002f * (w.w + w.z * (m.u + (float)(D.d + D.d / 64 + 140) * 6.0e-8f));
+    m.e = 1.002f * t * w.z + 1e-30f;
+  }
+  return m;
+}
+
+__device__ inline float halves_slack(const Dev &D) { return (float)(2 * (128 + D.d / 64 + 1) + 16 * ((D.d + 31) / 32) + 8) * 6.0e-8f; }
+__device__ inline uint32_t halves_reach_key(const Dev &D, uint32_t key, const HalfQuery &m) {
+  const float v = l2_score_of_key(key);
+  if (!(v < __builtin_inff())) return 0xFFFFFFFFu;  // "keep everything", as behind a NaN
+  const float r0 = sqrtf(fmaxf(v, 0.f)), p = 1.01f * (m.norm + r0) + m.e, fp = halves_slack(D) * p * p;
+  float r = sqrtf(r0 * r0 * (1.f + (float)(D.d + 8) * 6.0e-8f) + fp) * 1.000001f;
+  r += m.u * (m.norm + r) + m.e;
+  const float w = (r * r + fp) * 1.000001f + 1e-30f;
+  return w < __builtin_inff() ? key_of_float(w) : 0xFFFFFFFFu;
+}
+__device__ inline uint32_t halves_reach_ip_key(uint32_t key, const HalfQuery &m) {
+  const float v = l2_score_of_key(key), w = v + m.e + (fabsf(v) + m.e) * 2.4e-7f;
+  return fabsf(w) < __builtin_inff() ? key_of_float(w + 0.0f) : 0xFFFFFFFFu;
+}
+// The query's bound, the k-th best score of a sample of its candidates from their halves, as one of what the scan of halves has.  Squared
+// distances: a vector is no further from the query than from what its halves hold, and u |x| + t; inner products: the sample
+// holds upper bounds but for e (sample_scores_halves).
+__device__ inline uint32_t halves_bound_key(const Dev &D, uint32_t key, const HalfQuery &m) {
+  if (key == 0xFFFFFFFFu) return key;
+  if (D.metric != 0) return halves_reach_ip_key(halves_reach_ip_key(key, m), m);
+  const float v = l2_score_of_key(key);
+  if (!(v < __builtin_inff())) return 0xFFFFFFFFu;
+  float r = sqrtf(fmaxf(v, 0.f)) * (1.f + (float)(D.d + 8) * 6.0e-8f);
+  r += m.u * (m.norm + r) + m.e;
+  return halves_reach_key(D, key_of_float(r * r * 1.000001f), m);
+}
+// A vector or query whose halves are not finite says nothing: it is kept, and its query's flag, behind its counter of records, has
+// the selection score all of the records again.
+__device__ inline uint32_t *rec_flag(const SearchScratch &S, uint32_t q) { return rec_count(S, q) + 1; }
+// ... and behind that what the workgroups that share a query's selection count: those that are done, finalists scored, and whether one of
+// them found that it cannot be shared (select.hip)
+__device__ inline uint32_t *rec_done(const SearchScratch &S, uint32_t q) { return rec_count(S, q) + 2; }
+__device__ inline uint32_t *rec_scored(const SearchScratch &S, uint32_t q) { return rec_count(S, q) + 3; }
+__device__ inline uint32_t *rec_alone(const SearchScratch &S, uint32_t q) { return rec_count(S, q) + 4; }
+__device__ inline void rec_words_clear(const SearchScratch &S, uint32_t q) {
+  uint32_t *w = rec_count(S, q);
+#pragma unroll
+  for (int i = 0; i < 5; ++i) w[i] = 0u;
+}
+
 
 // ---------------------------------------------------- launch shape of the scan
 // Hardware hands consecutive workgroup ids to the 8 XCDs in turn; a workgroup of the scan is up to
 // four wavefronts, one work item each.
 constexpr uint32_t kXcds = 8;
+constexpr int kComputeUnits = 256;
 constexpr int kScanWaves = 4;
 
 // Launch shape of a list scan.  Two kernels share the plan of work items (list, segment, tile of the
@@ -408,7 +491,7 @@ constexpr int kScanWaves = 4;
 //    (measured at 1 and 32 queries: 15 to 20 % slower than the vector unit with its partial-distance
 //    pruning; mm_scan_pays() has the larger ones).
 struct ScanShape {
-  bool mm;           // the matrix-core kernel
+  bool mm;           // a matrix-core kernel
   int tile_q;        // queries of a tile at most
   int seg_base;      // segments are seg_base << choice groups of 64 vectors: 2, or 1 for small requests over short lists
   int min_choice;    // the shortest the plan may choose
@@ -422,6 +505,13 @@ constexpr int kMmTileMax = 32;         // queries of its tile at most
 constexpr int kMmQueryWords = 12;      // 32-bit words of LDS per query of a tile beside its coordinates
 constexpr int kMmStageCap = 256;       // survivors a wavefront stages in LDS before it reserves their places
 constexpr size_t kMmStageBytes = (size_t)kMmStageCap * 9 + 8 * kMmTileMax;  // keys, positions, rows, and two words per query of the tile
+constexpr uint32_t kHalfStep = 2048;   // the scan of halves: bytes of a step, and steps a wavefront has in LDS
+constexpr uint32_t kHalfRing = 2;
+constexpr int kHalfQueryWords = 6;
+constexpr int kHalfStageCap = 128;
+constexpr size_t kHalfStageBytes = (size_t)kHalfStageCap * 9 + 8 * kMmTileMax;
+constexpr int kHalfConsts = 4;         // the scan of halves: 32-bit words per query of a tile that go into its scores
+constexpr uint32_t kHalfPlaces = 8;    // ... and the places of a wavefront's groups it keeps (copies are at most four groups ahead)
 constexpr size_t kMmLdsMax = 160 * 1024 - 1024;  // what a workgroup may take of the CU's 160 KiB
 // The vector unit's scan walks groups singly where lists have so few that pairs leave much of the last one empty, and the
 // request has fewer than two groups for every SIMD.  Pairs / one at a time, us a request: 10 k x 32 in lists of 3 groups,
@@ -507,9 +597,28 @@ inline bool narrow_scan_pays(const Dev &D, int64_t pairs, double list_bytes) {
          (pairs >= 4 * nlist + (D.d < 128 ? 1 : 0) && list_bytes < 300e6);
 }
 
+// Whether a request over lists of floats with halves beside them reads those.  What speaks for them is bytes: the lists it meets, once
+// each, and a fifth of what its pairs meet (squared distances: 16-bit instructions have the better of the arithmetic as well).
+// What speaks against them is what is scored again, which goes with the dimensions and with k, in a few compute units when there are
+// few queries.  Floats / halves, us a request of 1 to 256 queries: 1 M x 128 bytes in 1,024 lists, 32 probes, k 100, 8 queries 67 / 73, 32 112 /
+// 94, 256 192 / 125; 10 M x 96 in 4,096, inner products, 128 x 64, k 10 618 / 360; 5 M x 768 in 8,192, 64 x 32 740 / 492; 20 M x
+// 256 in 16,384, hot lists, 256 x 64 2,870 / 1,670; but 132,802 x 912 in 88, inner products, 200 x 8, k 128 215 / 451, and
+// 964,127 x 356 in 667, one of them a fifth of it, 8 x 2, k 100 57 / 124.  Over 8,485 requests for squared distances (d 24 to 512, 64 to
+// 16,384 lists, even ones and hot ones) the rule is 1.3 % behind the better of the two on average, and 1.33 times at worst, never would
+// be 13 %; over 5,565 for inner products (d 24 to 1,024) 0.6 % and 1.25 times, and 7 %.  One to seven queries for squared distances stay
+// with the floats, whose scan leaves off early and scores nothing again (up to 1.6 times as slow, 1.15 times as fast on average).
+inline bool halves_scan_pays(const Dev &D, int64_t nq, int64_t nprobe, int64_t k, int64_t avg_len, int64_t max_len) {
+  const int64_t pairs = nq * nprobe;
+  const double per = D.d * 4e-6, hot = (double)max_len * (nq < 10 ? (double)nq / 10.0 : 1.0);  // MB of a vector; a tenth of the queries meet the longest list
+  const double lists = ((double)(pairs < D.nlist ? pairs : D.nlist) * (double)avg_len + hot) * per;
+  const double again = (double)k * D.d * 1e-4;
+  if (D.metric != 0) return lists >= 130.0 + 0.4 * D.d + 140.0 * again;
+  return nq >= 8 && lists + 0.2 * (double)nq * ((double)(nprobe * avg_len) + (double)max_len / 10.0) * per >= 100.0 + 0.2 * D.d + 60.0 * again;
+}
+
 inline ScanShape scan_shape(const Dev &D, int item_budget) {
   ScanShape sh{};
-  sh.mm = D.scan_mfma != 0 && D.pq_m == 0;
+  sh.mm = (D.scan_mfma != 0 || D.scan_halves != 0) && D.pq_m == 0;
   // room for an uneven split of the items over the XCDs
   const int items = item_budget + item_budget / 2;
   if (!sh.mm) {
@@ -523,6 +632,18 @@ inline ScanShape scan_shape(const Dev &D, int item_budget) {
     sh.threads = waves * kWave;
     sh.lds = per_wave * waves;
     sh.grid = ((items + waves - 1) / waves + (int)kXcds - 1) / (int)kXcds * (int)kXcds;
+    return sh;
+  }
+  if (D.scan_halves) {  // a query's halves and 16 bytes that spread the rows over the banks, its words, and what its scores are made of
+    const size_t row = (size_t)half_row_units(D) * 16 + 16 + kHalfQueryWords * 4;
+    const size_t rest = kMmWaves * (kHalfStageBytes + kHalfPlaces * 4) + kHalfConsts * kMmTileMax * 4, ring = kMmWaves * kHalfRing * kHalfStep;
+    sh.tile_q = D.scan_halves == 2 ? 32 : 16;
+    sh.seg_base = 2;
+    sh.min_choice = D.scan_min_choice >= 0 ? D.scan_min_choice : D.d >= 512 ? 1 : 2;
+    sh.items_per_wg = 1;
+    sh.threads = kMmWaves * kWave;
+    sh.lds = row * sh.tile_q + rest + ring;
+    sh.grid = (items + (int)kXcds - 1) / (int)kXcds * (int)kXcds;
     return sh;
   }
   // a query of the tile: coordinates, one float4 of padding, its words (or its three pieces and its words)

@@ -109,6 +109,8 @@ __device__ __forceinline__ int select_topk(int count, int k, KeyFn key, ItemFn i
 }
 
 constexpr int kTopkThreads = 512;
+constexpr int kSelectParts = 8;  // workgroups that share a query's finalists, at most
+constexpr int64_t kSharedWork = 32768;  // ... where its records come to so many chunks of four coordinates
 
 __device__ inline float score_of_key(uint32_t key, int metric) {
   const float x = __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
@@ -118,16 +120,23 @@ __device__ inline float score_of_key(uint32_t key, int metric) {
 // ST: what flat lists keep (only the finalists' second scores depend on it: quantised lists take 0)
 // (four wavefronts to a SIMD, or a compute unit takes one workgroup instead of two; measured with 129 registers and with
 // 125: 256 queries over 1 M x 16 codes on four streams 74.5 / 73.7 us a request, float lists the same within noise)
-template <int ST>
-__global__ __launch_bounds__(kTopkThreads, 4) void k_select(Dev D, int k, int nprobe, int max_nprobe,
-                                                        const float *__restrict__ Q, SearchScratch S,
-                                                        float *__restrict__ out_dist,
-                                                        int64_t *__restrict__ out_ids) {
+// HALVES: the records are what the halves beside float lists can say (scan_halves.hip).  METRIC: of the finalists' second scores;
+// CHAIN: they are one sum in the order of the coordinates, as the vector unit's scan and all inner products have it, and not four short
+// ones, as behind the matrix cores' squared distances: reading halves makes no difference to what is returned.
+template <int ST, bool HALVES, int METRIC, bool CHAIN>
+__device__ __forceinline__ void select_query(const Dev &D, int nq, int k, const float *__restrict__ Q, const SearchScratch &S,
+                                             float *__restrict__ out_dist, int64_t *__restrict__ out_ids) {
   __shared__ SelectShared sh;
   __shared__ uint32_t skey[kSurvivorCap];
   __shared__ uint32_t sidx[kSurvivorCap];
   __shared__ uint32_t scount;
-  const int q = blockIdx.x;
+  // Behind halves several workgroups may share a query's finalists (part of parts): a finalist's second score reads 16 bytes of a
+  // line of memory for every four coordinates, 0.4 G such a second for a compute unit, and most of them idle where the
+  // queries are few (64 queries, 170 to 250 finalists of 768 dimensions each: 113 us with one workgroup to a query).  Every one of
+  // them takes the records and has a limit of its own; a finalist is scored by the one its place in the pool falls to, and the last one
+  // to finish sorts what all have scored.
+  const int part = HALVES ? (int)blockIdx.x / nq : 0, parts = HALVES ? (int)gridDim.x / nq : 1;
+  const int q = HALVES ? (int)blockIdx.x - part * nq : (int)blockIdx.x;
   const int n = (int)*rec_count(S, (uint32_t)q);
   const unsigned long long base = S.qbase[q];
   const uint32_t *rk = rec_keys_of(S, base), *rp = rec_poss_of(S, base);
@@ -135,6 +144,14 @@ __global__ __launch_bounds__(kTopkThreads, 4) void k_select(Dev D, int k, int np
   const int lane = threadIdx.x & (kWave - 1);
   if (threadIdx.x == 0) scount = 0;
   __syncthreads();
+  // (what they have scored goes behind the records, where there is room for it)
+  const bool shared = HALVES && parts > 1 && !halves_are_floats(D) && (int64_t)n * D.d4 >= kSharedWork &&
+                      S.qtotal[q] >= (uint32_t)n + 2u * kMaxK;
+  if (HALVES && part > 0 && !shared) {  // uniform
+    if (threadIdx.x == 0) overflow_request_done(S, gridDim.x);
+    return;
+  }
+  auto mine = [&](uint32_t slot) { return !HALVES || !shared || (slot * 2654435761u >> 16) % (uint32_t)parts == (uint32_t)part; };
 
   // The records are taken into LDS in portions.  Once LDS is more than half full the k-th best
   // of what it holds becomes the limit (it cannot be better than the final k-th best): what is
@@ -146,19 +163,223 @@ __global__ __launch_bounds__(kTopkThreads, 4) void k_select(Dev D, int k, int np
   // With norm-form scores among the records (flat lists under L2 scored on the matrix cores) a
   // limit taken from the k-th best record is loosened twice: once to bound the k-th best direct-form
   // score from above, once more to admit every record whose direct-form score may reach that.
-  const bool approx = uses_norm_form(D);
-  const float slack = norm_form_slack(D.d), qn = approx ? S.qnorm[q] : 0.f;
+  // Squared distances from halves: the same with their margin.  Inner products from halves are lower bounds of the negated
+  // inner products, each with a margin of its own: a limit is the worst inner product of the k best such, from the floats
+  // (limit_of_scored).
+  const bool approx = HALVES || uses_norm_form(D);
+  constexpr bool kScoredLimit = HALVES && METRIC == 1;
+  const float slack = norm_form_slack(D.d), qn = !HALVES && approx ? S.qnorm[q] : 0.f;
+  auto hq = [&]() { return half_query(D, S, (uint32_t)q); };  // (read where it is wanted: registers are short here)
   auto limit_from = [&](uint32_t kth) {
+    if (HALVES) return halves_reach_key(D, halves_reach_key(D, kth, hq()), hq());
     return approx ? loosened_key(loosened_key(kth, slack, qn), slack, qn) : kth;
+  };
+  // a record's place in the pool (slot_of) -> which block, which place in it
+  auto locate = [&](int i, uint32_t &b, uint32_t &moff) {
+    b = (uint32_t)i / (uint32_t)D.T_m;
+    moff = (uint32_t)i - b * (uint32_t)D.T_m;
+  };
+  auto id_of = [&](int i) -> int64_t {
+    uint32_t b, moff;
+    locate(i, b, moff);
+    return block_ids(D, b)[moff];
+  };
+  // Where the halves beside the lists are the floats, the finalists are scored from those: a vector's chunks lie side by side by fours
+  // there, where 16 bytes of the lists are a line of memory each.
+  const bool from_halves = HALVES && halves_are_floats(D);
+  const float ixs = HALVES ? 1.f / halves_scale(D) : 1.f;
+  auto half_floats = [&](const uint2 &h) {
+    const float4 f = chunk_piece<1>(make_float4(__uint_as_float(h.x), __uint_as_float(h.y), 0.f, 0.f), 0);
+    return make_float4(f.x * ixs, f.y * ixs, f.z * ixs, f.w * ixs);
+  };
+  auto half_chunk = [&](uint32_t b, uint32_t moff, int c) -> uint2 {  // chunk c of four floats
+    return *reinterpret_cast<const uint2 *>(block_halves(D, b) + half_chunk_at(D, moff, (uint32_t)c >> 1) + (c & 1) * 8);
+  };
+  auto key_from_halves = [&](uint32_t b, uint32_t moff) __attribute__((always_inline)) -> uint32_t {  // squared distances, as direct_key has them
+    const int sub = (int)(threadIdx.x & 3u);
+    const float4 *__restrict__ y = reinterpret_cast<const float4 *>(Q + (size_t)q * D.d);
+    float acc = 0.f;
+    for (int c0 = sub; c0 < D.d4; c0 += 32) {
+      uint2 h[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) h[u] = half_chunk(b, moff, min(c0 + 4 * u, D.d4 - 1));
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (c0 + 4 * u < D.d4) accumulate<0>(acc, half_floats(h[u]), y[c0 + 4 * u]);
+    }
+    acc += quad_xor<1>(acc);
+    acc += quad_xor<2>(acc);
+    return key_of_float(acc + 0.0f);
+  };
+  // The same for lists of halves and bytes: lane s of the four takes the 16-byte chunks s, s + 4, ...
+  auto narrow_key = [&](uint32_t b, uint32_t moff) __attribute__((always_inline)) -> uint32_t {
+    const int sub = (int)(threadIdx.x & 3u), vc = D.vchunks;
+    const float4 *__restrict__ x = block_vecs(D, b) + (size_t)(moff / kWave) * vc * kWave + (moff & (kWave - 1));
+    const float4 *__restrict__ y = reinterpret_cast<const float4 *>(Q + (size_t)q * D.d);
+    float acc = 0.f;
+    for (int c0 = sub; c0 < vc; c0 += 16) {
+      float4 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = x[(size_t)(c0 + 4 * u < vc ? c0 + 4 * u : c0) * kWave];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int c = c0 + 4 * u;
+        if (c >= vc) break;
+#pragma unroll
+        for (int p = 0; p < pieces_of(ST); ++p) accumulate<METRIC>(acc, chunk_piece<ST>(v[u], p), y[pieces_of(ST) * c + p]);
+      }
+    }
+    acc += quad_xor<1>(acc);
+    acc += quad_xor<2>(acc);
+    return key_of_float((METRIC == 0 ? acc : -acc) + 0.0f);
+  };
+  // place in the pool -> key of the candidate's direct-form squared distance (inner products from halves: of its inner product).  Four neighbouring lanes share
+  // a candidate (a vector's chunks of 4 dimensions lie 1 KiB apart: every chunk is a memory
+  // transaction of its own, and this way all of them are in flight at once): lane s of the four
+  // takes chunks s, s + 4, ..., and the four partial sums are added pairwise.  All four lanes call
+  // this with the same place and get the key.
+  // One sum in the order of the coordinates (CHAIN): every chunk's four products are added by the lane that has the chunk, and the
+  // four take the sum over from it.
+  auto direct_key = [&](int i, int64_t *id) -> uint32_t {
+    uint32_t b, moff;
+    locate(i, b, moff);
+    const int sub = (int)(threadIdx.x & 3u);
+    if (id && sub == 0) *id = block_ids(D, b)[moff];
+    if (CHAIN) {
+      const float4 *__restrict__ x = block_vecs(D, b) + (size_t)(moff / kWave) * D.d4 * kWave + (moff & (kWave - 1));
+      const float4 *__restrict__ y = reinterpret_cast<const float4 *>(Q + (size_t)q * D.d);
+      float acc = 0.f;
+      for (int c0 = 0; c0 < D.d4; c0 += 32) {  // uniform
+        float4 v[8], w[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int c = min(c0 + 4 * u + sub, D.d4 - 1);
+          v[u] = from_halves ? half_floats(half_chunk(b, moff, c)) : x[(size_t)c * kWave];
+          w[u] = y[c];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          auto add = [&](auto lane_of) {
+            constexpr int kLane = decltype(lane_of)::value;
+            if (c0 + 4 * u + kLane >= D.d4) return;  // uniform
+            float t = acc;
+            accumulate<METRIC>(t, v[u], w[u]);
+            acc = quad_broadcast<kLane>(t);
+          };
+          add(std::integral_constant<int, 0>{});
+          add(std::integral_constant<int, 1>{});
+          add(std::integral_constant<int, 2>{});
+          add(std::integral_constant<int, 3>{});
+        }
+      }
+      return key_of_float((METRIC == 0 ? acc : -acc) + 0.0f);
+    }
+    if (ST != 0) return narrow_key(b, moff);
+    if (HALVES && from_halves) return key_from_halves(b, moff);  // uniform
+    const float4 *__restrict__ x =
+        block_vecs(D, b) + (size_t)(moff / kWave) * D.d4 * kWave + (moff & (kWave - 1));
+    const float4 *__restrict__ y = reinterpret_cast<const float4 *>(Q + (size_t)q * D.d);
+    float acc = 0.f;
+    int c = sub;
+    for (; c + 28 < D.d4; c += 32) {
+      float4 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = x[(size_t)(c + 4 * u) * kWave];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) accumulate<METRIC>(acc, v[u], y[c + 4 * u]);
+    }
+    for (; c < D.d4; c += 4) accumulate<METRIC>(acc, x[(size_t)c * kWave], y[c]);
+    acc += quad_xor<1>(acc);
+    acc += quad_xor<2>(acc);
+    return key_of_float((METRIC == 0 ? acc : -acc) + 0.0f);
+  };
+  // The same for two candidates at once: both block look-ups go out together, then all the chunks of
+  // both (a candidate is a chain of two round trips to memory; two of them side by side cost one).
+  auto direct_key_pair = [&](int ia, int ib, int64_t *ida, int64_t *idb, uint32_t &ka, uint32_t &kb) {
+    uint32_t ba, ma, bb, mb;
+    locate(ia, ba, ma);
+    locate(ib, bb, mb);
+    const int sub = (int)(threadIdx.x & 3u);
+    if (sub == 0) {
+      *ida = block_ids(D, ba)[ma];
+      *idb = block_ids(D, bb)[mb];
+    }
+    if (HALVES && from_halves) {  // uniform
+      ka = key_from_halves(ba, ma);
+      kb = key_from_halves(bb, mb);
+      return;
+    }
+    if (ST != 0) {
+      ka = narrow_key(ba, ma);
+      kb = narrow_key(bb, mb);
+      return;
+    }
+    const float4 *__restrict__ xa = block_vecs(D, ba) + (size_t)(ma / kWave) * D.d4 * kWave + (ma & (kWave - 1));
+    const float4 *__restrict__ xb = block_vecs(D, bb) + (size_t)(mb / kWave) * D.d4 * kWave + (mb & (kWave - 1));
+    const float4 *__restrict__ y = reinterpret_cast<const float4 *>(Q + (size_t)q * D.d);
+    float acca = 0.f, accb = 0.f;
+    int c = sub;
+    for (; c + 28 < D.d4; c += 32) {
+      float4 va[8], vb[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) va[u] = xa[(size_t)(c + 4 * u) * kWave];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) vb[u] = xb[(size_t)(c + 4 * u) * kWave];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) accumulate<METRIC>(acca, va[u], y[c + 4 * u]);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) accumulate<METRIC>(accb, vb[u], y[c + 4 * u]);
+    }
+    for (; c < D.d4; c += 4) {
+      const float4 va = xa[(size_t)c * kWave], vb = xb[(size_t)c * kWave];
+      accumulate<METRIC>(acca, va, y[c]);
+      accumulate<METRIC>(accb, vb, y[c]);
+    }
+    acca += quad_xor<1>(acca);
+    acca += quad_xor<2>(acca);
+    accb += quad_xor<1>(accb);
+    accb += quad_xor<2>(accb);
+    ka = key_of_float((METRIC == 0 ? acca : -acca) + 0.0f);
+    kb = key_of_float((METRIC == 0 ? accb : -accb) + 0.0f);
+  };
+  // A limit from any k or more candidates (sh.pay[0 .. m), at most kMaxK): no final k-th best is worse than the worst of them.
+  __shared__ uint32_t s_worst;
+  auto limit_of_scored = [&](int m) -> uint32_t {
+    if (threadIdx.x == 0) s_worst = 0u;
+    __syncthreads();
+    uint32_t worst = 0u;
+    for (int p0 = 0; p0 < m; p0 += kTopkThreads / 4) {  // uniform trip count
+      const int p = p0 + (int)(threadIdx.x >> 2);
+      const uint32_t key = direct_key((int)sh.pay[p < m ? p : m - 1], nullptr);
+      worst = key > worst ? key : worst;
+    }
+    worst = wave_reduce_last(worst, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+    if (lane == kWave - 1) atomicMax(&s_worst, worst);
+    __syncthreads();
+    return halves_reach_ip_key(s_worst, hq());
+  };
+  // ... namely those of `count` records whose keys are not worse than T, which k or more are
+  auto limit_below = [&](int count, uint32_t T, auto key, auto item) -> uint32_t {
+    if (threadIdx.x == 0) sh.cnt[0] = 0;
+    __syncthreads();
+    for (int j = threadIdx.x; j < count; j += kTopkThreads)
+      if (key(j) <= T) {
+        const uint32_t p = atomicAdd(&sh.cnt[0], 1u);
+        if (p < (uint32_t)kMaxK) sh.pay[p] = (uint32_t)item(j);
+      }
+    __syncthreads();
+    return limit_of_scored(min((int)sh.cnt[0], kMaxK));
   };
   // what LDS holds is cut down to the records not worse than the limit: everybody reads its
   // entries, then everybody writes the kept ones back
   auto keep_not_worse = [&](int have, uint32_t lim) {
+    int tid = (int)threadIdx.x;
+    asm volatile("" : "+v"(tid));  // (addresses made from it are not kept from one use of this to the next)
     constexpr int kMine = kSurvivorCap / kTopkThreads;
     uint32_t mk[kMine], mi[kMine];
 #pragma unroll
     for (int u = 0; u < kMine; ++u) {
-      const int j = (int)threadIdx.x + u * kTopkThreads;
+      const int j = tid + u * kTopkThreads;
       mk[u] = j < have ? skey[j] : 0xFFFFFFFFu;
       mi[u] = j < have ? sidx[j] : 0u;
     }
@@ -167,7 +388,7 @@ __global__ __launch_bounds__(kTopkThreads, 4) void k_select(Dev D, int k, int np
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < kMine; ++u) {
-      const int j = (int)threadIdx.x + u * kTopkThreads;
+      const int j = tid + u * kTopkThreads;
       const bool keep = j < have && mk[u] <= lim;
       const unsigned long long mask = __ballot(keep);
       if (mask) {
@@ -184,7 +405,11 @@ __global__ __launch_bounds__(kTopkThreads, 4) void k_select(Dev D, int k, int np
     __syncthreads();
   };
   uint32_t limit = S.bound[q];
+  if (HALVES) limit = halves_bound_key(D, limit, hq());
   bool in_lds = true;
+  // (halves that are not finite among the records: none of the keys is gone by)
+  const bool flagged = HALVES && *rec_flag(S, (uint32_t)q) != 0u;
+  if (flagged) { limit = 0xFFFFFFFFu; in_lds = false; }
   __shared__ uint32_t s_over;
   int stretch = 1;  // portions as a multiple of the room in LDS
   // More records than LDS holds (the query's bound was loose: its sample did not look like its
@@ -193,14 +418,17 @@ __global__ __launch_bounds__(kTopkThreads, 4) void k_select(Dev D, int k, int np
   // with tens of thousands of records (a hot list) takes a pilot as large as LDS: the k-th best of
   // 4096 lets about k / 4096 of the records pass, which fit in one go.
   constexpr int kPilot = 1024;
-  if (n > kSurvivorCap && k <= kPilot) {  // uniform over the workgroup
+  if (!flagged && n > kSurvivorCap && k <= kPilot) {  // uniform over the workgroup
     const int pilot = n >= 8 * kSurvivorCap ? kSurvivorCap : kPilot;
     const int stride = n / pilot;
     for (int j = threadIdx.x; j < pilot; j += kTopkThreads) skey[j] = rk[(size_t)j * stride];
     __syncthreads();
     const SelectResult r = wg_radix_select<32>(
         pilot, (uint32_t)k, [&](int j, uint64_t &kv) { kv = skey[j]; return true; }, sh.hist, sh.bc, (uint32_t)(k + k / 16));
-    const uint32_t lim = limit_from((uint32_t)r.T);
+    uint32_t lim;
+    if constexpr (kScoredLimit)
+      lim = limit_below(pilot, (uint32_t)r.T, [&](int j) { return skey[j]; }, [&](int j) { return (int)rp[(size_t)j * stride]; });
+    else lim = limit_from((uint32_t)r.T);
     limit = lim < limit ? lim : limit;
     stretch = pilot == kSurvivorCap ? 16 : 4;
     __syncthreads();  // the pilot's keys are done with
@@ -247,8 +475,8 @@ __global__ __launch_bounds__(kTopkThreads, 4) void k_select(Dev D, int k, int np
   };
   // Records that all fit are taken as they come: every one of them passed the query's bound in the scan.  (Through the
   // filter below, a count and a reservation per 64 of them, they cost the selection two microseconds more.)
-  int next = 0;
-  if (n <= kSurvivorCap) {
+  int next = flagged ? n : 0;
+  if (!flagged && n <= kSurvivorCap) {
     constexpr int kMine = kSurvivorCap / kTopkThreads;
     uint32_t kv[kMine], pv[kMine];
     const int last = n > 0 ? n - 1 : 0;
@@ -291,7 +519,11 @@ __global__ __launch_bounds__(kTopkThreads, 4) void k_select(Dev D, int k, int np
       // tighten
       const SelectResult r = wg_radix_select<32>(
           have, (uint32_t)k, [&](int j, uint64_t &kv) { kv = skey[j]; return true; }, sh.hist, sh.bc, (uint32_t)(k + k / 16));
-      const uint32_t lim = limit_from((uint32_t)r.T);
+      uint32_t lim;
+      if constexpr (kScoredLimit)
+        lim = limit_below(have, (uint32_t)r.T, [&](int j) { return skey[j]; },
+                          [&](int j) { return deferred ? (int)rp[sidx[j]] : (int)sidx[j]; });
+      else lim = limit_from((uint32_t)r.T);
       limit = lim < limit ? lim : limit;
       keep_not_worse(have, limit);  // drop what is worse
       if ((int)scount > kSurvivorCap / 2) { in_lds = false; break; }
@@ -307,110 +539,6 @@ __global__ __launch_bounds__(kTopkThreads, 4) void k_select(Dev D, int k, int np
     for (int j = threadIdx.x; j < have; j += kTopkThreads) sidx[j] = rp[sidx[j]];
     __syncthreads();
   }
-  // a record's place in the pool (slot_of) -> which block, which place in it
-  auto locate = [&](int i, uint32_t &b, uint32_t &moff) {
-    b = (uint32_t)i / (uint32_t)D.T_m;
-    moff = (uint32_t)i - b * (uint32_t)D.T_m;
-  };
-  auto id_of = [&](int i) -> int64_t {
-    uint32_t b, moff;
-    locate(i, b, moff);
-    return block_ids(D, b)[moff];
-  };
-  // The same for lists of halves and bytes: lane s of the four takes the 16-byte chunks s, s + 4, ...
-  auto narrow_key = [&](uint32_t b, uint32_t moff) __attribute__((always_inline)) -> uint32_t {
-    const int sub = (int)(threadIdx.x & 3u), vc = D.vchunks;
-    const float4 *__restrict__ x = block_vecs(D, b) + (size_t)(moff / kWave) * vc * kWave + (moff & (kWave - 1));
-    const float4 *__restrict__ y = reinterpret_cast<const float4 *>(Q + (size_t)q * D.d);
-    float acc = 0.f;
-    for (int c0 = sub; c0 < vc; c0 += 16) {
-      float4 v[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = x[(size_t)(c0 + 4 * u < vc ? c0 + 4 * u : c0) * kWave];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int c = c0 + 4 * u;
-        if (c >= vc) break;
-#pragma unroll
-        for (int p = 0; p < pieces_of(ST); ++p) accumulate<0>(acc, chunk_piece<ST>(v[u], p), y[pieces_of(ST) * c + p]);
-      }
-    }
-    acc += quad_xor<1>(acc);
-    acc += quad_xor<2>(acc);
-    return key_of_float(acc + 0.0f);
-  };
-  // place in the pool -> key of the candidate's direct-form squared distance.  Four neighbouring lanes share
-  // a candidate (a vector's chunks of 4 dimensions lie 1 KiB apart: every chunk is a memory
-  // transaction of its own, and this way all of them are in flight at once): lane s of the four
-  // takes chunks s, s + 4, ..., and the four partial sums are added pairwise.  All four lanes call
-  // this with the same place and get the key.
-  auto direct_key = [&](int i, int64_t *id) -> uint32_t {
-    uint32_t b, moff;
-    locate(i, b, moff);
-    const int sub = (int)(threadIdx.x & 3u);
-    if (id && sub == 0) *id = block_ids(D, b)[moff];
-    if (ST != 0) return narrow_key(b, moff);
-    const float4 *__restrict__ x =
-        block_vecs(D, b) + (size_t)(moff / kWave) * D.d4 * kWave + (moff & (kWave - 1));
-    const float4 *__restrict__ y = reinterpret_cast<const float4 *>(Q + (size_t)q * D.d);
-    float acc = 0.f;
-    int c = sub;
-    for (; c + 28 < D.d4; c += 32) {
-      float4 v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = x[(size_t)(c + 4 * u) * kWave];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) accumulate<0>(acc, v[u], y[c + 4 * u]);
-    }
-    for (; c < D.d4; c += 4) accumulate<0>(acc, x[(size_t)c * kWave], y[c]);
-    acc += quad_xor<1>(acc);
-    acc += quad_xor<2>(acc);
-    return key_of_float(acc + 0.0f);
-  };
-  // The same for two candidates at once: both block look-ups go out together, then all the chunks of
-  // both (a candidate is a chain of two round trips to memory; two of them side by side cost one).
-  auto direct_key_pair = [&](int ia, int ib, int64_t *ida, int64_t *idb, uint32_t &ka, uint32_t &kb) {
-    uint32_t ba, ma, bb, mb;
-    locate(ia, ba, ma);
-    locate(ib, bb, mb);
-    const int sub = (int)(threadIdx.x & 3u);
-    if (sub == 0) {
-      *ida = block_ids(D, ba)[ma];
-      *idb = block_ids(D, bb)[mb];
-    }
-    if (ST != 0) {
-      ka = narrow_key(ba, ma);
-      kb = narrow_key(bb, mb);
-      return;
-    }
-    const float4 *__restrict__ xa = block_vecs(D, ba) + (size_t)(ma / kWave) * D.d4 * kWave + (ma & (kWave - 1));
-    const float4 *__restrict__ xb = block_vecs(D, bb) + (size_t)(mb / kWave) * D.d4 * kWave + (mb & (kWave - 1));
-    const float4 *__restrict__ y = reinterpret_cast<const float4 *>(Q + (size_t)q * D.d);
-    float acca = 0.f, accb = 0.f;
-    int c = sub;
-    for (; c + 28 < D.d4; c += 32) {
-      float4 va[8], vb[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) va[u] = xa[(size_t)(c + 4 * u) * kWave];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) vb[u] = xb[(size_t)(c + 4 * u) * kWave];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) accumulate<0>(acca, va[u], y[c + 4 * u]);
-#pragma unroll
-      for (int u = 0; u < 8; ++u) accumulate<0>(accb, vb[u], y[c + 4 * u]);
-    }
-    for (; c < D.d4; c += 4) {
-      const float4 va = xa[(size_t)c * kWave], vb = xb[(size_t)c * kWave];
-      accumulate<0>(acca, va, y[c]);
-      accumulate<0>(accb, vb, y[c]);
-    }
-    acca += quad_xor<1>(acca);
-    acca += quad_xor<2>(acca);
-    accb += quad_xor<1>(accb);
-    accb += quad_xor<2>(accb);
-    ka = key_of_float(acca + 0.0f);
-    kb = key_of_float(accb + 0.0f);
-  };
   int kk = -1;
   if (approx && in_lds) {  // uniform over the workgroup
     // The usual case: the finalists (every record that may be among the k best by direct-form
@@ -421,23 +549,25 @@ __global__ __launch_bounds__(kTopkThreads, 4) void k_select(Dev D, int k, int np
     if (have > k) {
       const SelectResult r = wg_radix_select<32>(
           have, (uint32_t)k, [&](int j, uint64_t &kv) { kv = skey[j]; return true; }, sh.hist, sh.bc, (uint32_t)(k + k / 16));
-      lim = limit_from((uint32_t)r.T);
-      limit = lim < limit ? lim : limit;
+      lim = kScoredLimit ? (uint32_t)r.T : limit_from((uint32_t)r.T);
+      if (!kScoredLimit) limit = lim < limit ? lim : limit;
     }
     if (threadIdx.x == 0) sh.cnt[0] = 0;
     __syncthreads();
-    for (int j = threadIdx.x; j < have; j += kTopkThreads)
-      if (skey[j] <= lim) {
-        const uint32_t p = atomicAdd(&sh.cnt[0], 1u);
-        if (p < (uint32_t)kMaxK) sh.pay[p] = sidx[j];
-      }
-    __syncthreads();
-    const int m = (int)sh.cnt[0];
-    if (m <= kMaxK) {
+    auto collect = [&](bool all, uint32_t above, uint32_t upto, bool share) {  // records whose keys are in (above, upto]
+      for (int j = threadIdx.x; j < have; j += kTopkThreads)
+        if (skey[j] <= upto && (all || skey[j] > above) && (!share || mine(sidx[j]))) {
+          const uint32_t p = atomicAdd(&sh.cnt[0], 1u);
+          if (p < (uint32_t)kMaxK) sh.pay[p] = sidx[j];
+        }
+      __syncthreads();
+    };
+    uint32_t worst = 0u;
+    auto score = [&](int from, int m) {  // finalists from .. m - 1
       constexpr int kFours = kTopkThreads / 4;
-      for (int p0 = 0; p0 < m;) {  // uniform trip count: the lanes of a four stay together
+      for (int p0 = from; p0 < m;) {  // uniform trip count: the lanes of a four stay together
         const int p = p0 + (int)(threadIdx.x >> 2);
-        if (m - p0 > kFours) {  // uniform: every four takes two finalists, p and p + kFours
+        if (!CHAIN && m - p0 > kFours) {  // uniform: every four takes two finalists, p and p + kFours
           const int p2 = p + kFours;
           int64_t id = 0, id2 = 0;
           uint32_t key, key2;
@@ -450,6 +580,7 @@ __global__ __launch_bounds__(kTopkThreads, 4) void k_select(Dev D, int k, int np
         } else {
           int64_t id = 0;
           const uint32_t key = direct_key((int)sh.pay[p < m ? p : m - 1], &id);
+          if (kScoredLimit) worst = max(worst, key);
           if (p < m && (threadIdx.x & 3u) == 0) {
             sh.k1[p] = key;
             sh.k2[p] = (uint64_t)id ^ 0x8000000000000000ull;
@@ -457,8 +588,77 @@ __global__ __launch_bounds__(kTopkThreads, 4) void k_select(Dev D, int k, int np
           p0 += kFours;
         }
       }
-      wg_sort<32>(m, sh.k1, sh.k2, sh.pay);
-      kk = k < m ? k : m;
+    };
+    collect(true, 0u, lim, !kScoredLimit || have <= k);
+    int m = (int)sh.cnt[0], from = 0;  // (a shared query's k best are scored by all of its workgroups, and belong to the first)
+    if (m <= kMaxK) {
+      score(0, m);
+      if constexpr (kScoredLimit) {
+        // the k best by what halves say are scored: whatever may still be better than the worst of them is scored as well
+        if (have > k) {  // uniform
+          worst = wave_reduce_last(worst, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+          if (threadIdx.x == 0) s_worst = 0u;
+          __syncthreads();
+          if (lane == kWave - 1) atomicMax(&s_worst, worst);
+          __syncthreads();
+          const uint32_t upto = halves_reach_ip_key(s_worst, hq());
+          limit = upto < limit ? upto : limit;
+          if (upto > lim) collect(false, lim, upto, true);
+          const int more = (int)sh.cnt[0];
+          if (more <= kMaxK) score(m, more);
+          if (part > 0) from = m;
+          m = more;
+        }
+      }
+      if (!shared && m <= kMaxK) {
+        wg_sort<32>(m, sh.k1, sh.k2, sh.pay);
+        kk = k < m ? k : m;
+      }
+    }
+    if (HALVES && shared) {  // uniform
+      __syncthreads();
+      if (m > kMaxK) {
+        if (threadIdx.x == 0) __hip_atomic_store(rec_alone(S, (uint32_t)q), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      } else {
+        if (threadIdx.x == 0) sh.cnt[1] = m > from ? atomicAdd(rec_scored(S, (uint32_t)q), (uint32_t)(m - from)) : 0u;
+        __syncthreads();
+        const uint32_t at = sh.cnt[1];
+        uint32_t *ok = const_cast<uint32_t *>(rk) + n, *op = const_cast<uint32_t *>(rp) + n;
+        for (int p = from + (int)threadIdx.x; p < m; p += kTopkThreads) {
+          const uint32_t o = at + (uint32_t)(p - from);
+          if (o >= (uint32_t)kMaxK) continue;  // (too many all in all: the last workgroup sees that)
+          __hip_atomic_store(&op[o], (uint32_t)sh.k1[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_store(&ok[2 * o], (uint32_t)sh.k2[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_store(&ok[2 * o + 1], (uint32_t)(sh.k2[p] >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      }
+    }
+  }
+  if (HALVES && shared) {  // uniform
+    if (!in_lds && threadIdx.x == 0) __hip_atomic_store(rec_alone(S, (uint32_t)q), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // what this wavefront has scored is out ...
+    __syncthreads();                                  // ... and so is everybody's before the workgroup counts itself off
+    if (threadIdx.x == 0) {
+      sh.bc[0] = atomicAdd(rec_done(S, (uint32_t)q), 1u) + 1u == (uint32_t)parts;
+      sh.bc[1] = __hip_atomic_load(rec_alone(S, (uint32_t)q), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      sh.bc[2] = __hip_atomic_load(rec_scored(S, (uint32_t)q), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (!sh.bc[0]) {  // uniform: the last one goes on
+      if (threadIdx.x == 0) overflow_request_done(S, gridDim.x);
+      return;
+    }
+    const int all = (int)sh.bc[2];
+    if (!sh.bc[1] && all <= kMaxK) {  // (otherwise the last one goes on alone, from its own records)
+      const uint32_t *ok = rk + n, *op = rp + n;
+      for (int p = threadIdx.x; p < all; p += kTopkThreads) {
+        sh.k1[p] = __hip_atomic_load(&op[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sh.k2[p] = (uint64_t)__hip_atomic_load(&ok[2 * p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) |
+                   (uint64_t)__hip_atomic_load(&ok[2 * p + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) << 32;
+        sh.pay[p] = 0u;
+      }
+      wg_sort<32>(all, sh.k1, sh.k2, sh.pay);
+      kk = k < all ? k : all;
     }
   }
   if (approx && kk < 0) {  // uniform over the workgroup
@@ -507,19 +707,34 @@ __global__ __launch_bounds__(kTopkThreads, 4) void k_select(Dev D, int k, int np
       out_ids[o] = -1;
     }
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) *S.cursor = 0ull;  // the next request on this slice finds its records' room free
+  if (q == 0 && threadIdx.x == 0) *S.cursor = 0ull;  // the next request on this slice finds its records' room free
   // the records are not looked at any more (the selection ended with a barrier)
   if (threadIdx.x == 0) overflow_request_done(S, gridDim.x);
 }
 
+template <int ST>
+__global__ __launch_bounds__(kTopkThreads, 4) void k_select(Dev D, int k, const float *__restrict__ Q, SearchScratch S,
+                                                        float *__restrict__ out_dist, int64_t *__restrict__ out_ids) {
+  select_query<ST, false, 0, false>(D, 0, k, Q, S, out_dist, out_ids);
+}
+template <int METRIC, bool CHAIN>
+__global__ __launch_bounds__(kTopkThreads, 4) void k_select_halves(Dev D, int nq, int k, const float *__restrict__ Q, SearchScratch S,
+                                                        float *__restrict__ out_dist, int64_t *__restrict__ out_ids) {
+  select_query<0, true, METRIC, CHAIN>(D, nq, k, Q, S, out_dist, out_ids);
+}
 
-void launch_select(const Dev &D, int64_t nq, int k, int nprobe, int max_nprobe, const float *Q,
-                   const SearchScratch &S, float *out_dist, int64_t *out_ids, hipStream_t s) {
+void launch_select(const Dev &D, int64_t nq, int k, const float *Q, const SearchScratch &S, float *out_dist, int64_t *out_ids,
+                   hipStream_t s) {
   if (nq <= 0) return;
-  const dim3 grid((unsigned)nq), block(kTopkThreads);
-  if (D.storage == 1) hipLaunchKernelGGL(k_select<1>, grid, block, 0, s, D, k, nprobe, max_nprobe, Q, S, out_dist, out_ids);
-  else if (D.storage == 2) hipLaunchKernelGGL(k_select<2>, grid, block, 0, s, D, k, nprobe, max_nprobe, Q, S, out_dist, out_ids);
-  else hipLaunchKernelGGL(k_select<0>, grid, block, 0, s, D, k, nprobe, max_nprobe, Q, S, out_dist, out_ids);
+  if (D.scan_halves) {
+    const int64_t parts = 2 * kComputeUnits / nq < 1 ? 1 : 2 * kComputeUnits / nq > kSelectParts ? kSelectParts : 2 * kComputeUnits / nq;
+    const auto kernel = D.metric != 0 ? k_select_halves<1, true> : D.scan_mfma ? k_select_halves<0, false> : k_select_halves<0, true>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(nq * parts)), dim3(kTopkThreads), 0, s, D, (int)nq, k, Q, S, out_dist, out_ids);
+    return;
+  }
+  typedef void (*Kernel)(Dev, int, const float *, SearchScratch, float *, int64_t *);
+  static const Kernel kernels[3] = {k_select<0>, k_select<1>, k_select<2>};
+  hipLaunchKernelGGL(kernels[D.storage], dim3((unsigned)nq), dim3(kTopkThreads), 0, s, D, k, Q, S, out_dist, out_ids);
 }
 
 }  // namespace rtams

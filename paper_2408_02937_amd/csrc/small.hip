@@ -41,7 +41,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_front(Dev D, int64_t nq
   }
   probe_plan<false, MINE, true>(D, nq, q, nprobe, max_nprobe, S, Q, nullptr, *reinterpret_cast<ProbeShared<false> *>(s_raw));
   __syncthreads();  // the plan is read below by other threads, and its LDS is used again
-  sample_bound<false>(D, q, nprobe, max_nprobe, k, Q, S, s_raw, 0u, 1u);
+  sample_bound<false, false>(D, q, nprobe, max_nprobe, k, Q, S, s_raw, 0u, 1u);
 }
 
 // Workgroup `part` of the `parts` of query q: its wavefronts take every (parts x wavefronts)-th unit of G groups of the

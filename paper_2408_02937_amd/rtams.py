@@ -18,6 +18,7 @@ LIB_PATH = os.path.join(_HERE, "librtams.so")
 
 L2, IP = 0, 1
 OK, EINVAL, ESTATE, EPOOL, EBUSY, EHIP, ESCRATCH, ENOSPARE = 0, -1, -2, -3, -4, -5, -6, -7
+HALVES_LEAST = 32 << 20  # bytes of halves beside the lists from which an Index keeps them
 STORAGE = {"f32": 0, "f16": 1, "u8": 2}  # what flat lists keep of a coordinate
 _NAMES = {EINVAL: "EINVAL", ESTATE: "ESTATE", EPOOL: "EPOOL", EBUSY: "EBUSY", EHIP: "EHIP",
           ESCRATCH: "ESCRATCH", ENOSPARE: "ENOSPARE"}
@@ -31,7 +32,7 @@ SYMBOLS = [
     "rtams_poll_error", "rtams_clear_error", "rtams_last_error", "rtams_set_param", "rtams_scan_time",
     "rtams_copy_plain", "rtams_read_plain", "rtams_set_codebooks", "rtams_list_export_codes",
     "rtams_search_noalloc", "rtams_overflow_bytes_for", "rtams_scan_kernels",
-    "rtams_request_trace",
+    "rtams_request_trace", "rtams_halves_bytes", "rtams_set_halves",
 ]
 
 
@@ -82,6 +83,9 @@ def lib():
         L.rtams_overflow_bytes_for.argtypes = [i32, i64]
         L.rtams_create.argtypes = [cp, C.POINTER(vp)]
         L.rtams_destroy.argtypes = [vp]
+        L.rtams_halves_bytes.restype = C.c_size_t
+        L.rtams_halves_bytes.argtypes = [vp]
+        L.rtams_set_halves.argtypes = [vp, vp, C.c_size_t]
         L.rtams_set_centroids.argtypes = [vp, vp, vp]
         L.rtams_set_codebooks.argtypes = [vp, vp, vp]
         L.rtams_list_export_codes.argtypes = [vp, i32, i64, vp, vp, C.POINTER(i64), vp]
@@ -186,6 +190,13 @@ class Index:
         torch.cuda.synchronize(self.device)
         _chk(L.rtams_create(C.byref(cfg), C.byref(h)), "rtams_create")
         self._h = h
+        # halves beside lists of floats, for long scans to read: half as much again as the lists take, left out where that is
+        # more than a quarter of what is still free, or so little that no scan of it is long
+        self.halves = None
+        nbytes = L.rtams_halves_bytes(h)
+        if nbytes >= HALVES_LEAST and nbytes <= torch.cuda.mem_get_info(self.device)[0] // 4:
+            self.halves = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+            _chk(L.rtams_set_halves(h, self.halves.data_ptr(), nbytes), "rtams_set_halves")
 
     def close(self):
         if getattr(self, "_h", None):
@@ -346,7 +357,7 @@ class Index:
         bounds, kept, path = torch.empty(nq, dtype=torch.uint32), torch.empty(nq, dtype=torch.uint32), C.c_int32()
         _chk(lib().rtams_request_trace(self._h, resource, nq, bounds.data_ptr(), kept.data_ptr(), C.byref(path)),
              "rtams_request_trace")
-        return bounds, kept, ("k_scan", "k_scan_small", "k_scan_mm", "k_scan_mm narrow", "k_pq_scan")[path.value]
+        return bounds, kept, ("k_scan", "k_scan_small", "k_scan_mm", "k_scan_mm narrow", "k_pq_scan", "k_scan_halves")[path.value]
 
     def set_param(self, key: str, value: int) -> None:
         _chk(lib().rtams_set_param(self._h, key.encode(), value), "rtams_set_param")

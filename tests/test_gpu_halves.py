@@ -1,0 +1,219 @@
+"""The scan of the halves beside float lists says which vectors are scored, never what is returned: the same bits as the
+request has without it, whichever unit that takes.  The halves' memory starts as NaNs."""
+import pytest
+import torch
+
+from paper_2408_02937_amd import rtams
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def index(d, nlist, metric, block_vecs, n, nprobe, monkeypatch, threshold=0, resources=1):
+    monkeypatch.setattr(rtams, "HALVES_LEAST", 1)
+    g = rtams.Index(d, nlist, metric, block_vecs, pool_blocks=n // block_vecs + 3 * nlist + 64, n_resources=resources, max_batch=256, max_k=1024,
+                    max_nprobe=nprobe, candidates_per_query=n, rearrange_threshold=threshold)
+    assert g.halves is not None
+    g.halves.fill_(0xFF)
+    return g
+
+
+def both(g, q, k, nprobe):
+    g.set_param("small_requests", 0)
+    g.set_param("scan_halves", 0)
+    want = g.search(q, k, nprobe)
+    torch.cuda.synchronize()
+    g.set_param("scan_halves", 2)
+    got = g.search(q, k, nprobe)
+    torch.cuda.synchronize()
+    assert g.poll_error() == 0
+    path = g.request_trace(q.shape[0])[2]
+    assert path == "k_scan_halves"
+    return want, got
+
+
+def same(want, got, finite_only=False):
+    (d0, i0), (d1, i1) = want, got
+    if finite_only:  # (the order of infinitely far ones and of NaNs is left open)
+        ok = torch.isfinite(d0)
+        assert torch.equal(ok, torch.isfinite(d1))
+        assert torch.equal(d0[ok], d1[ok]) and torch.equal(i0[ok], i1[ok])
+        return
+    assert torch.equal(d0.view(torch.int32), d1.view(torch.int32))
+    assert torch.equal(i0, i1)
+
+
+# dimensions: one chunk of halves, a chunk half filled, whole steps and a rest of one to three chunks, 64 coordinates and their
+# neighbours, the widest; tiles of 16 and 32 queries and one more; k of one, and more than the sample's first size
+@pytest.mark.parametrize("metric", ["l2", "ip"])
+@pytest.mark.parametrize("d,nlist,block_vecs,nq,nprobe,k", [
+    (4, 16, 64, 1, 16, 1), (12, 17, 128, 16, 5, 10), (32, 64, 64, 17, 8, 100), (36, 33, 192, 33, 33, 128), (64, 64, 128, 256, 64, 50),
+    (100, 40, 64, 64, 20, 1000), (128, 64, 256, 256, 32, 100), (260, 20, 64, 7, 20, 600), (768, 100, 128, 64, 8, 10), (2048, 16, 64, 40, 16, 100)])
+@pytest.mark.parametrize("whole", [False, True])
+def test_the_same_bits_as_the_floats_alone(metric, d, nlist, block_vecs, nq, nprobe, k, whole, monkeypatch):
+    print(f"[case] halves {metric} d {d}, {nq} x {nprobe}, k {k}, whole {whole}", flush=True)
+    gen = torch.Generator(DEV).manual_seed(d + nq)
+    n = min(60_000, 20_000_000 // d)
+    centres = torch.randn(nlist, d, device=DEV, generator=gen)
+
+    def rows(m):
+        # a few lists hold one to 70 vectors: ends of units, of groups and of blocks
+        at = torch.cat([torch.arange(min(nlist, 8), device=DEV).repeat_interleave(torch.tensor([1, 31, 32, 33, 63, 64, 65, 70][:min(nlist, 8)], device=DEV))[:m],
+                        torch.randint(8 if nlist > 16 else 0, nlist, (max(0, m - 359),), device=DEV, generator=gen)])[:m]
+        x = centres[at] + 0.2 * torch.randn(len(at), d, device=DEV, generator=gen)
+        return (60 * x).round_() if whole else x  # (whole numbers: their halves are their floats)
+
+    g = index(d, nlist, metric, block_vecs, n, nprobe, monkeypatch)
+    g.set_centroids((60 * centres).round_() if whole else centres)
+    x = rows(n)
+    for piece in (x[:1], x[1:70], x[70:2000], x[2000:]):  # the tail, by vector and by lists
+        g.add(piece.contiguous())
+    q = rows(max(nq, 359))[-nq:].contiguous()
+    same(*both(g, q, k, nprobe))
+    for steal in (1, 0):  # as a long scan, whose workgroups take other dies' items
+        g.set_param("scan_exclusive_pairs", steal)
+        g.set_param("scan_exclusive_bytes", 1 if steal else 16 << 30)
+        same(*both(g, q, k, nprobe))
+    g.close()
+
+
+# finalists by the thousand and queries whose workgroups share them; vectors that no half can tell apart
+@pytest.mark.parametrize("metric", ["l2", "ip"])
+@pytest.mark.parametrize("spread,nq,k", [(0.1, 8, 50), (0.1, 130, 100), (1e-4, 8, 10), (0.0, 24, 300)])
+def test_shared_and_many_finalists(metric, spread, nq, k, monkeypatch):
+    print(f"[case] finalists {metric}, spread {spread}, {nq} queries, k {k}", flush=True)
+    gen = torch.Generator(DEV).manual_seed(nq)
+    d, nlist, n = 512, 16, 40_000
+    centres = torch.randn(nlist, d, device=DEV, generator=gen)
+    x = centres[torch.randint(nlist, (n,), device=DEV, generator=gen)] + spread * torch.randn(n, d, device=DEV, generator=gen)
+    g = index(d, nlist, metric, 128, n, nlist, monkeypatch)
+    g.set_centroids(centres)
+    g.add(x)
+    q = (x[:nq] + spread * torch.randn(nq, d, device=DEV, generator=gen)).contiguous()
+    for nprobe in (2, nlist):
+        same(*both(g, q, k, nprobe))
+    g.close()
+
+
+@pytest.mark.parametrize("metric", ["l2", "ip"])
+def test_what_halves_cannot_hold_is_scored(metric, monkeypatch):
+    print(f"[case] infinities and large values, {metric}", flush=True)
+    gen = torch.Generator(DEV).manual_seed(3)
+    d, nlist, n = 96, 32, 20_000
+    centres = torch.randn(nlist, d, device=DEV, generator=gen)
+    x = centres[torch.randint(nlist, (n,), device=DEV, generator=gen)] + 0.1 * torch.randn(n, d, device=DEV, generator=gen)
+    x[::97] *= 1e4      # past the largest half
+    x[1::101] *= 1e-9   # below the smallest
+    x[5] = float("inf")
+    x[7, 3] = float("nan")
+    q = x[100:140].clone()
+    q[2] *= 1e25
+    q[3] = float("nan")
+    q[4] = 0.0
+    g = index(d, nlist, metric, 64, n, nlist, monkeypatch)
+    g.set_centroids(centres)
+    g.add(x)
+    same(*both(g, q, 20, nlist), finite_only=True)
+    g.close()
+
+
+def test_the_halves_move_with_their_blocks_and_grow_with_the_lists(monkeypatch):
+    print("[case] rearrangement", flush=True)
+    gen = torch.Generator(DEV).manual_seed(4)
+    d, nlist, n = 100, 24, 30_000
+    centres = torch.randn(nlist, d, device=DEV, generator=gen)
+    x = centres[torch.randint(nlist, (n,), device=DEV, generator=gen)] + 0.3 * torch.randn(n, d, device=DEV, generator=gen)
+    g = index(d, nlist, "l2", 64, n, nlist, monkeypatch, threshold=300)
+    g.set_centroids(centres)
+    for lo in range(0, n, 777):
+        g.add(x[lo:lo + 777].contiguous())
+    for _ in range(2):
+        same(*both(g, x[:50].contiguous(), 60, 6))
+        g.rearrange(-1)
+        torch.cuda.synchronize()
+        g.validate()
+    g.close()
+
+
+def test_recorded_requests_read_them_too(monkeypatch):
+    print("[case] recorded", flush=True)
+    gen = torch.Generator(DEV).manual_seed(5)
+    d, nlist, n, nq, k = 128, 64, 50_000, 96, 40
+    centres = torch.randn(nlist, d, device=DEV, generator=gen)
+    x = centres[torch.randint(nlist, (n,), device=DEV, generator=gen)] + 0.2 * torch.randn(n, d, device=DEV, generator=gen)
+    g = index(d, nlist, "ip", 128, n, 16, monkeypatch, resources=4)
+    g.set_centroids(centres)
+    g.add(x)
+    q = x[:nq].clone()
+    _, want = both(g, q, k, 16)
+    od, oi = torch.empty(nq, k, device=DEV), torch.empty(nq, k, dtype=torch.int64, device=DEV)
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        g.search(q, k, 16, od, oi)
+    for turn in range(4):
+        q.copy_(x[turn * 100:turn * 100 + nq])
+        want = g.search(q, k, 16)
+        torch.cuda.synchronize()
+        od.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        same(want, (od, oi))
+    g.close()
+
+
+# metric, d, lists, vectors of a list, queries, probes, k, which scan takes it
+@pytest.mark.parametrize("metric,d,nlist,length,nq,nprobe,k,path", [
+    ("l2", 128, 64, 4000, 8, 32, 10, "k_scan_halves"),    # 133 MB of lists, 525 that the pairs meet, of which a fifth: 238 of 133
+    ("l2", 128, 64, 4000, 7, 64, 10, "k_scan"),           # fewer than eight queries
+    ("l2", 128, 64, 1000, 64, 32, 10, "k_scan_halves"),   # 33 MB, and 1,050 that the pairs meet
+    ("l2", 128, 64, 1000, 8, 32, 10, "k_scan"),           # 33 and 131
+    ("ip", 128, 64, 6000, 64, 32, 10, "k_scan_halves"),   # 199.7 MB of 199.1
+    ("ip", 128, 64, 4000, 64, 32, 10, "k_scan"),          # 133
+])
+def test_which_requests_read_them(metric, d, nlist, length, nq, nprobe, k, path, monkeypatch):
+    monkeypatch.setattr(rtams, "HALVES_LEAST", 1)
+    gen = torch.Generator(DEV).manual_seed(6)
+    centres = torch.randn(nlist, d, device=DEV, generator=gen)
+    centres *= 8.0 * d ** 0.5 / centres.norm(dim=1, keepdim=True)
+    x = centres.repeat_interleave(length, 0) + 0.5 * torch.randn(nlist * length, d, device=DEV, generator=gen)
+    g = rtams.Index(d, nlist, metric, 128, pool_blocks=len(x) // 128 + 2 * nlist + 8, n_resources=1, max_batch=256, max_k=16, max_nprobe=nprobe,
+                    candidates_per_query=len(x))
+    g.set_centroids(centres)
+    g.add(x)
+    q = x[::97][:nq].contiguous()
+    g.set_param("small_requests", 0)
+    torch.cuda.synchronize()
+    g.search(q, k, nprobe)
+    torch.cuda.synchronize()
+    assert g.request_trace(nq)[2] == path
+    g.close()
+
+
+def test_who_keeps_halves_and_when_they_are_taken():
+    L = rtams.lib()
+    kinds = {"f32": (64, {}), "16 lists": (16, {}), "15 lists": (15, {}), "f16": (64, dict(storage="f16")), "u8": (64, dict(storage="u8")), "pq": (64, dict(pq_m=8))}
+    for name, (nlist, more) in kinds.items():
+        g = rtams.Index(32, nlist, "l2", 64, pool_blocks=200, n_resources=1, max_batch=8, max_k=8, max_nprobe=8, candidates_per_query=1000, **more)
+        want = L.rtams_halves_bytes(g._h)
+        assert want == (g.pool_stats().blocks_total * 64 * 64 if name in ("f32", "16 lists") else 0), name
+        if not want:
+            t = torch.empty(1 << 20, dtype=torch.uint8, device=DEV)
+            assert L.rtams_set_halves(g._h, t.data_ptr(), 1 << 20) == rtams.ESTATE, name
+        g.close()
+    g = rtams.Index(32, 64, "l2", 64, pool_blocks=200, n_resources=1, max_batch=8, max_k=8, max_nprobe=8, candidates_per_query=1000)
+    assert g.halves is None  # too few for any scan of them to be long
+    want = L.rtams_halves_bytes(g._h)
+    t = torch.empty(want + 256, dtype=torch.uint8, device=DEV)
+    assert L.rtams_set_halves(g._h, None, want) == rtams.EINVAL
+    assert L.rtams_set_halves(g._h, t.data_ptr() + 16, want) == rtams.EINVAL
+    assert L.rtams_set_halves(g._h, t.data_ptr(), want - 1) == rtams.EINVAL
+    x = torch.randn(500, 32, device=DEV)
+    g.set_centroids(x[:64].contiguous())
+    assert L.rtams_set_halves(g._h, t.data_ptr(), want) == rtams.OK
+    g.add(x)
+    assert L.rtams_set_halves(g._h, t.data_ptr(), want) == rtams.ESTATE
+    torch.cuda.synchronize()
+    g.close()
