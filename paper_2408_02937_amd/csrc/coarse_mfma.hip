@@ -537,15 +537,14 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void k_coarse_mfma(Dev D, int64_t 
 // workgroup, a thread to each where it is.
 
 // exact_score() below with four neighbouring lanes to a candidate (all four call with the same arguments, and all have the
-// score): lane s of the four brings chunks s, s + 4, ... and works out their differences, and the chain, the same in all four,
-// takes them from one after the other.  A lane alone waits for a trip to memory per eight chunks, 24 of them at 768
-// dimensions and next to nobody else on the compute unit; here two sets of 16 chunks take turns.  (28,928 rows of 768
-// dimensions, 38 candidates to a workgroup: the refinement 57 us with a lane to a candidate and 1,034 workgroups, 45 with
-// four and 998, in a bulk load of three sub-rounds 40 on average.)
-template <int S>
-__device__ __forceinline__ float quad_take(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), S * 0x55, 0xf, 0xf, true));
-}
+// score): lane s of the four brings chunks s, s + 4, ... and goes on with the chain at each of them, and the sum goes from
+// lane to lane with the chain.  (The others' operations at that time are of no use, but a wavefront issues them anyway, and
+// the sum moves once per chunk where the terms would move once each: a workgroup's 38 candidates wait for the issue of 2.3
+// instructions to a dimension instead of 3.8, or 5 with the conversions of inner products.)  A lane alone waits for a trip
+// to memory per eight chunks, 24 of them at 768 dimensions and next to nobody else on the compute unit; here two sets of
+// 16 chunks take turns.  (28,928 rows of 768 dimensions, 38 candidates to a workgroup: the refinement 57 us with a lane to
+// a candidate and 1,034 workgroups, 45 with four and 998, 35 since the sum moves; in a bulk load of three sub-rounds 31 on
+// average.)
 template <int S>
 __device__ __forceinline__ double quad_take(double v) {
   const long long b = __double_as_longlong(v);
@@ -573,31 +572,21 @@ __device__ inline double exact_score_quad(const Dev &D, const float *__restrict_
   auto use = [&](const float4 *a, const float4 *b, int j) {
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
+      double p0 = a[u].x, p1 = a[u].y, p2 = a[u].z, p3 = a[u].w, q0 = b[u].x, q1 = b[u].y, q2 = b[u].z, q3 = b[u].w;
       if (l2) {
-        const double t0 = (double)a[u].x - (double)b[u].x, t1 = (double)a[u].y - (double)b[u].y;
-        const double t2 = (double)a[u].z - (double)b[u].z, t3 = (double)a[u].w - (double)b[u].w;
-        auto chain = [&](auto tag) {
-          constexpr int S = decltype(tag)::value;
-          if (j + 4 * u + S > last) return;  // uniform
-          double t = quad_take<S>(t0); acc = __builtin_fma(t, t, acc);
-          t = quad_take<S>(t1); acc = __builtin_fma(t, t, acc);
-          t = quad_take<S>(t2); acc = __builtin_fma(t, t, acc);
-          t = quad_take<S>(t3); acc = __builtin_fma(t, t, acc);
-        };
-        chain(std::integral_constant<int, 0>{}); chain(std::integral_constant<int, 1>{});
-        chain(std::integral_constant<int, 2>{}); chain(std::integral_constant<int, 3>{});
-      } else {
-        auto chain = [&](auto tag) {
-          constexpr int S = decltype(tag)::value;
-          if (j + 4 * u + S > last) return;  // uniform
-          acc = __builtin_fma((double)quad_take<S>(a[u].x), (double)quad_take<S>(b[u].x), acc);
-          acc = __builtin_fma((double)quad_take<S>(a[u].y), (double)quad_take<S>(b[u].y), acc);
-          acc = __builtin_fma((double)quad_take<S>(a[u].z), (double)quad_take<S>(b[u].z), acc);
-          acc = __builtin_fma((double)quad_take<S>(a[u].w), (double)quad_take<S>(b[u].w), acc);
-        };
-        chain(std::integral_constant<int, 0>{}); chain(std::integral_constant<int, 1>{});
-        chain(std::integral_constant<int, 2>{}); chain(std::integral_constant<int, 3>{});
+        p0 = q0 = p0 - q0; p1 = q1 = p1 - q1; p2 = q2 = p2 - q2; p3 = q3 = p3 - q3;
       }
+      auto chain = [&](auto tag) {
+        constexpr int S = decltype(tag)::value;
+        if (j + 4 * u + S > last) return;  // uniform
+        double next = __builtin_fma(p0, q0, acc);
+        next = __builtin_fma(p1, q1, next);
+        next = __builtin_fma(p2, q2, next);
+        next = __builtin_fma(p3, q3, next);
+        acc = quad_take<S>(next);
+      };
+      chain(std::integral_constant<int, 0>{}); chain(std::integral_constant<int, 1>{});
+      chain(std::integral_constant<int, 2>{}); chain(std::integral_constant<int, 3>{});
     }
     __builtin_amdgcn_sched_barrier(0);
   };
