@@ -94,14 +94,15 @@ __device__ inline u32x4 halves_of(const float *x, float &nsq, float &rsq) {
   }
   return out;
 }
-// coordinates 8 g .. 8 g + 7 of a row less the mean; zero past d
+// coordinates 8 g .. 8 g + 7 of a row less the mean; zero past d (the row's last chunk is asked for there: a branch
+// around every load would keep the loads of a row apart)
 __device__ inline void centred_group(const Dev &D, const float *row, int g, float *x) {
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
-    const int j = g * 8 + q * 4;
-    const float4 u = j < D.d ? *reinterpret_cast<const float4 *>(row + j) : make_float4(0.f, 0.f, 0.f, 0.f);
-    const float4 m = j < D.d ? *reinterpret_cast<const float4 *>(D.cmean + j) : make_float4(0.f, 0.f, 0.f, 0.f);
-    x[4 * q] = u.x - m.x; x[4 * q + 1] = u.y - m.y; x[4 * q + 2] = u.z - m.z; x[4 * q + 3] = u.w - m.w;
+    const int j = g * 8 + q * 4, at = min(j, D.d - 4);
+    const float4 u = *reinterpret_cast<const float4 *>(row + at), m = *reinterpret_cast<const float4 *>(D.cmean + at);
+    x[4 * q] = j < D.d ? u.x - m.x : 0.f; x[4 * q + 1] = j < D.d ? u.y - m.y : 0.f;
+    x[4 * q + 2] = j < D.d ? u.z - m.z : 0.f; x[4 * q + 3] = j < D.d ? u.w - m.w : 0.f;
   }
 }
 __device__ inline float group_top(const float *x) {
@@ -141,30 +142,52 @@ __global__ __launch_bounds__(256) void k_centroid_mean(Dev D) {
   }
 }
 
-// largest of a value per wavefront over the workgroup of 4, into a word of float bits (non-negative floats order
-// like their bits).  A few hundred workgroups walk the centroids: an atomic per centroid on one word took 0.2 ms for
-// 16,384 of them.
-__device__ inline void wg_atomic_max(float v, float *lds4, uint32_t *word) {
+// Largest of a value per wavefront over the workgroup, into a word of float bits (non-negative floats order like their
+// bits).  Atomics on one word follow each other at about 12 ns, and that is what bounds both kernels below: one per
+// centroid took 0.2 ms for 16,384 of them, one per workgroup of 4 wavefronts and word 18 us of the 38 that 8,192 x 768
+// took.  So workgroups are the largest there are, and a value that cannot change the word stays out of the line: zero,
+// or no larger than what a look at the word finds there (it only grows; an old value costs an atomic, no more).
+constexpr int kTopThreads = 1024, kTopWaves = kTopThreads / kWave;
+__device__ inline void wg_atomic_max(float v, float *lds, uint32_t *word) {
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   for (int o = kWave / 2; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
   __syncthreads();
-  if (lane == 0) lds4[wave] = v;
+  if (lane == 0) lds[wave] = v;
   __syncthreads();
-  if (threadIdx.x == 0) atomicMax(word, __float_as_uint(fmaxf(fmaxf(lds4[0], lds4[1]), fmaxf(lds4[2], lds4[3]))));
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kTopWaves; ++w) v = fmaxf(v, lds[w]);
+    const uint32_t bits = __float_as_uint(v);
+    if (bits > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(word, bits);
+  }
 }
 
-// a wavefront per centroid, in turns
-__global__ __launch_bounds__(256) void k_centroid_top(Dev D) {
-  __shared__ float s_max[4];
+// a wavefront per centroid, in turns; four chunks of a row to a lane asked for at once (past the row's end its last
+// chunk again, which changes no maximum)
+__global__ __launch_bounds__(kTopThreads) void k_centroid_top(Dev D) {
+  __shared__ float s_max[kTopWaves];
   const int lane = threadIdx.x & (kWave - 1);
+  const float4 *mean = reinterpret_cast<const float4 *>(D.cmean);
   float top = 0.f, bad = 0.f, whole = 0.f;
-  for (int c = blockIdx.x * 4 + threadIdx.x / kWave; c < D.nlist; c += gridDim.x * 4) {
-    const float *row = D.centroids + (size_t)c * D.d;
-    for (int j = lane; j < D.d; j += kWave) {
-      const float x = row[j], m = D.cmean[j], v = fabsf(x - m);
-      if (!(v < 1e17f) || !(fabsf(m) < 1e17f)) bad = 1.f;  // (squares and products of these, summed, stay finite)
-      top = fmaxf(top, v);
-      whole = fmaxf(whole, fabsf(x) < __builtin_inff() ? fabsf(x) : 0.f);
+  auto look = [&](float x, float m) {
+    const float v = fabsf(x - m);
+    if (!(v < 1e17f) || !(fabsf(m) < 1e17f)) bad = 1.f;  // (squares and products of these, summed, stay finite)
+    top = fmaxf(top, v);
+    whole = fmaxf(whole, fabsf(x) < __builtin_inff() ? fabsf(x) : 0.f);
+  };
+  for (int c = blockIdx.x * kTopWaves + threadIdx.x / kWave; c < D.nlist; c += gridDim.x * kTopWaves) {
+    const float4 *row = reinterpret_cast<const float4 *>(D.centroids + (size_t)c * D.d);
+    for (int j0 = 0; j0 < D.d4; j0 += 4 * kWave) {
+      float4 x[4], m[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int j = min(j0 + u * kWave + lane, D.d4 - 1);
+        x[u] = row[j];
+        m[u] = mean[j];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        look(x[u].x, m[u].x); look(x[u].y, m[u].y); look(x[u].z, m[u].z); look(x[u].w, m[u].w);
+      }
     }
   }
   wg_atomic_max(top, s_max, &D.ctrl->cen.top_bits);
@@ -172,14 +195,14 @@ __global__ __launch_bounds__(256) void k_centroid_top(Dev D) {
   wg_atomic_max(whole, s_max, &D.ctrl->half_top);
 }
 
-__global__ __launch_bounds__(256) void k_centroid_halves(Dev D) {
-  __shared__ float s_max[4];
+__global__ __launch_bounds__(kTopThreads) void k_centroid_halves(Dev D) {
+  __shared__ float s_max[kTopWaves];
   const int lane = threadIdx.x & (kWave - 1);
   CentroidStats &st = D.ctrl->cen;
   const float scale = half_scale(__uint_as_float(st.top_bits));
   const bool bad = st.bad != 0u;  // no centroid is told apart by the filter then
   float top_n = 0.f, top_r = 0.f, top_b = 0.f;
-  for (int c = blockIdx.x * 4 + threadIdx.x / kWave; c < D.nlist; c += gridDim.x * 4) {  // uniform over the wavefront
+  for (int c = blockIdx.x * kTopWaves + threadIdx.x / kWave; c < D.nlist; c += gridDim.x * kTopWaves) {  // uniform over the wavefront
     const float *row = D.centroids + (size_t)c * D.d;
     float nsq = 0.f, rsq = 0.f;
     double bias = 0.0;
@@ -231,12 +254,18 @@ __global__ __launch_bounds__(256) void k_half_rows(Dev D, int64_t n, const float
   for (int o = lpr / 2; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
   const float scale = half_scale(top);
   const bool bad = !(top < __builtin_inff());
+  if (bad) {  // what is left of such a row are its NaNs (every comparison and select of this kernel is paid per coordinate)
+#pragma unroll
+    for (int t = 0; t < G; ++t)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) x[t][j] = x[t][j] == x[t][j] ? 0.f : x[t][j];
+  }
   float nsq = 0.f, rsq = 0.f;
 #pragma unroll
   for (int t = 0; t < G; ++t) {
     const int g = sub + t * lpr;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) x[t][j] = bad && x[t][j] == x[t][j] ? 0.f : x[t][j] * scale;  // (a NaN stays one)
+    for (int j = 0; j < 8; ++j) x[t][j] *= scale;
     const u32x4 h = halves_of(x[t], nsq, rsq);
     if (on && g < D.dgroups) half[operand_at(i, g, D.dgroups / 4)] = h;
   }
@@ -824,9 +853,9 @@ __global__ __launch_bounds__(kRefineThreads) void k_assign_refine(Dev D, int64_t
 
 void launch_centroid_halves(const Dev &D, hipStream_t s) {
   hipLaunchKernelGGL(k_centroid_mean, dim3((unsigned)D.d4), dim3(256), 0, s, D);
-  const dim3 grid((unsigned)(D.nlist < 2048 ? (D.nlist + 3) / 4 : 512));
-  hipLaunchKernelGGL(k_centroid_top, grid, dim3(256), 0, s, D);
-  hipLaunchKernelGGL(k_centroid_halves, grid, dim3(256), 0, s, D);
+  const dim3 grid((unsigned)std::min((D.nlist + kTopWaves - 1) / kTopWaves, 512));
+  hipLaunchKernelGGL(k_centroid_top, grid, dim3(kTopThreads), 0, s, D);
+  hipLaunchKernelGGL(k_centroid_halves, grid, dim3(kTopThreads), 0, s, D);
 }
 
 static void launch_half_rows(const Dev &D, int64_t n, const float *Y, u32x4 *half, RowMeta *meta, hipStream_t s) {
