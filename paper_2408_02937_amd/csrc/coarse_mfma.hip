@@ -853,7 +853,7 @@ __global__ __launch_bounds__(kRefineThreads) void k_assign_refine(Dev D, int64_t
 
 void launch_centroid_halves(const Dev &D, hipStream_t s) {
   hipLaunchKernelGGL(k_centroid_mean, dim3((unsigned)D.d4), dim3(256), 0, s, D);
-  const dim3 grid((unsigned)std::min((D.nlist + kTopWaves - 1) / kTopWaves, 512));
+  const dim3 grid((unsigned)std::min((D.nlist + kTopWaves - 1) / kTopWaves, 256));
   hipLaunchKernelGGL(k_centroid_top, grid, dim3(kTopThreads), 0, s, D);
   hipLaunchKernelGGL(k_centroid_halves, grid, dim3(kTopThreads), 0, s, D);
 }
