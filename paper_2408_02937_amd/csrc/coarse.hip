@@ -57,6 +57,90 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse(
   coarse_tile<METRIC, VT, NC, ARGMIN, false, kCoarseThreads>(D, n, Y, splits, scores, pscore, pidx, cursor_to_clear, zero, zero_n);
 }
 
+// ---- inner products on the matrix cores' double instructions.  v_mfma_f64_16x16x4 takes its four products one after the
+// other, in order, each with a fused multiply-add (compared bit for bit with that chain over 51,200 sums of 96 products
+// of widely spread sizes), so it IS the fixed arithmetic: 16 vectors against 16 centroids, one chunk of a row to an
+// instruction.  (Sums of squared differences are no such product.)  The instruction does 16 multiply-adds a clock and
+// SIMD, what the vector unit does too; what the kernel above loses is that every one of its multiply-adds takes a
+// coordinate out of LDS, the same for all lanes, and here a word of LDS serves 16 of them.  What bounds it: the rate of
+// the instruction where there are wavefronts for every SIMD (two tiles of 16 vectors against 8,192 centroids of 768
+// dimensions add 12 us, 10.3 at 64 clocks an instruction), and the chain of one wavefront, d / 4 instructions, where there
+// are not.  Choosing 16 of 8,192 lists, 768 dimensions, whole calls: 64 vectors 61 us through the kernel above, 49 here, 17
+// vectors 62 and 38; 128 against 4,096 57 and 46; 64 against 8,192 lists of 1,536 dimensions 92 and 84, of 256 37 and 31.
+// A wavefront has 16 centroids, which it reads from the transposed copy (a lane a float, 256 bytes of 16 centroids' chunk
+// together), two sets of kDotSet chunks in turn, and 16 vectors, which the workgroup holds in LDS in the order of the
+// lanes.  Two groups of vectors to a wavefront, which read the centroids half as often, or sets of 32 chunks are no faster.
+typedef double DotAcc __attribute__((ext_vector_type(4)));
+constexpr int kDotThreads = 256, kDotWaves = kDotThreads / kWave, kDotSet = 16;
+
+__global__ __launch_bounds__(kDotThreads) void k_coarse_dots(Dev D, int64_t n, const float *__restrict__ Y,
+                                                             double *__restrict__ scores, unsigned long long *cursor_to_clear,
+                                                             uint32_t *__restrict__ zero, int zero_n) {
+  extern __shared__ float s_dots[];  // [d4][64]: lane 16 g + v has coordinate g of the chunk, of vector v
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, d4 = D.d4;
+  const int64_t v0 = (int64_t)blockIdx.x * 16;
+  if (cursor_to_clear && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *cursor_to_clear = 0ull;
+  if (zero) {
+    const int nthreads = gridDim.x * gridDim.y * kDotThreads;
+    for (int i = (blockIdx.y * gridDim.x + blockIdx.x) * kDotThreads + threadIdx.x; i < zero_n; i += nthreads) zero[i] = 0u;
+  }
+  const int c = ((int)blockIdx.y * kDotWaves + wave) * 16 + (lane & 15);
+  const float *col = D.centroids_t + (size_t)min(c, D.nlist - 1) * 4 + lane / 16;  // (past the end: dropped below)
+  const size_t stride = (size_t)D.nlist * 4;
+  float b0[kDotSet], b1[kDotSet];
+  auto load_set = [&](float *b, int j0) {  // past the row's end its last chunk again
+#pragma unroll
+    for (int u = 0; u < kDotSet; ++u) b[u] = col[(size_t)min(j0 + u, d4 - 1) * stride];
+    __builtin_amdgcn_sched_barrier(0);  // the loads go out here, not where they are used
+  };
+  load_set(b0, 0);
+  for (int t = threadIdx.x; t < 16 * d4; t += kDotThreads) {
+    const int v = t & 15, j = t >> 4;
+    const int64_t row = v0 + v < n ? v0 + v : n - 1;
+    const float4 y = reinterpret_cast<const float4 *>(Y)[(size_t)row * d4 + j];
+    float *to = s_dots + (size_t)j * kWave + v;
+    to[0] = y.x; to[16] = y.y; to[32] = y.z; to[48] = y.w;
+  }
+  __syncthreads();
+  DotAcc acc = {0.0, 0.0, 0.0, 0.0};
+  auto use_set = [&](const float *b, int j0) {  // a whole set
+    float y[kDotSet];
+#pragma unroll
+    for (int u = 0; u < kDotSet; ++u) y[u] = s_dots[(size_t)(j0 + u) * kWave + lane];
+#pragma unroll
+    for (int u = 0; u < kDotSet; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)y[u], (double)b[u], acc, 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto use_rest = [&](const float *b, int j0) {
+#pragma unroll
+    for (int u = 0; u < kDotSet; ++u) {
+      if (j0 + u >= d4) break;  // uniform
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)s_dots[(size_t)(j0 + u) * kWave + lane], (double)b[u], acc, 0, 0, 0);
+    }
+  };
+  int j = 0;
+#pragma unroll 1
+  for (; j + 2 * kDotSet <= d4; j += 2 * kDotSet) {
+    load_set(b1, j + kDotSet);
+    use_set(b0, j);
+    load_set(b0, j + 2 * kDotSet);
+    use_set(b1, j + kDotSet);
+  }
+  if (j < d4) {  // uniform
+    if (j + kDotSet < d4) load_set(b1, j + kDotSet);
+    use_rest(b0, j);
+    if (j + kDotSet < d4) use_rest(b1, j + kDotSet);
+  }
+  if (c >= D.nlist) return;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int64_t row = v0 + 4 * i + lane / 16;
+    if (row < n) scores[(size_t)row * D.nlist + c] = acc[i];
+  }
+}
+
+hipError_t allow_large_lds_dots() { return allow_lds(k_coarse_dots, 16 * 2048 * sizeof(float)); }  // (the widest vectors)
+
 // once per set_centroids: the transposed copy the kernel above streams
 __global__ __launch_bounds__(256) void k_centroid_transpose(Dev D) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -92,8 +176,28 @@ static void launch_coarse(const Dev &D, int64_t n, const float *Y, int splits, d
 #undef RTAMS_GO
 }
 
+// Whether the scores of n vectors go to the matrix cores' double instructions.  Narrow vectors gain or lose nothing at any
+// number of lists.  A wide vector's chain is longer there (64 clocks to four coordinates), which a batch that leaves the
+// chip idle pays: from 2^17 pairs it is repaid, and from three eighths of that against 4,096 lists or more, where the kernel
+// for vectors on their own, one to a workgroup, would read all the centroids for each.  Choosing 16 lists, us, the
+// vector unit / here: 768 dimensions, 64 x 200 23 / 26, x 1,024 24 / 27, 128 x 1,024 30 / 30, 256 x 1,024 37 / 32, 8 x 4,096 33 /
+// 30, 32 x 4,096 36 / 31; 1,536, 48 x 1,024 34 / 40, 128 x 1,024 47 / 46, 256 x 1,024 58 / 48, 17 x 4,096 61 / 48; 256, 64 x
+// 1,024 18 / 19, 256 x 1,024 25 / 22, 8 x 4,096 21 / 22, 17 x 4,096 24 / 22; 128, 17 x
+// 2,048 17 / 18; 96, 128 x 200 18 / 17, x 4,096 25 / 24.
+static bool dots_pay(const Dev &D, int64_t n) {
+  const int64_t pairs = n * D.nlist;
+  return D.metric != 0 && n >= 8 && D.nlist <= 1 << 20 &&
+         (D.d <= 96 || pairs >= (int64_t)1 << 17 || (D.nlist >= 4096 && pairs >= 3 << 14));
+}
+
 void launch_coarse_scores(const Dev &D, int64_t n, const float *Y, double *scores,
                           unsigned long long *cursor_to_clear, uint32_t *zero, int zero_n, hipStream_t s) {
+  if (dots_pay(D, n)) {
+    const dim3 grid((unsigned)((n + 15) / 16), (unsigned)((D.nlist + 16 * kDotWaves - 1) / (16 * kDotWaves)));
+    hipLaunchKernelGGL(k_coarse_dots, grid, dim3(kDotThreads), (size_t)16 * D.d * sizeof(float), s, D, n, Y, scores,
+                       cursor_to_clear, zero, zero_n);
+    return;
+  }
   int splits = coarse_splits(D, n, 0);
   launch_coarse<false>(D, n, Y, splits, scores, nullptr, nullptr, cursor_to_clear, zero, zero_n, s);
 }

@@ -221,6 +221,7 @@ int allow_large_lds_on_current_device() {
   std::lock_guard<std::mutex> g(g_static_mutex);
   if (g_lds_allowed[dev]) return RTAMS_OK;
   HIP_TRY(allow_large_lds_coarse());
+  HIP_TRY(allow_large_lds_dots());
   HIP_TRY(allow_large_lds_group());
   HIP_TRY(allow_large_lds_scan_mm());
   HIP_TRY(allow_large_lds_pq_scan());

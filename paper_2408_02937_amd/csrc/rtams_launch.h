@@ -128,6 +128,7 @@ struct RearrangeScratch {
 // A kernel whose workgroups may take more than 64 KiB of LDS has to be told so, on every device by itself: rtams_create
 // does it for the index's.
 hipError_t allow_large_lds_coarse();
+hipError_t allow_large_lds_dots();
 hipError_t allow_large_lds_group();
 hipError_t allow_large_lds_scan_mm();
 hipError_t allow_large_lds_pq_scan();
