@@ -345,6 +345,12 @@ __device__ __forceinline__ float quad_broadcast(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), R * 0x55, 0xf, 0xf, true));
 }
 
+// value of lane 16 (l / 16) + r for every lane l (a move inside each row of sixteen lanes)
+template <int R>
+__device__ __forceinline__ float row_broadcast(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x150 + R, 0xf, 0xf, true));
+}
+
 // ---- norm form of the squared distance.  On the matrix cores a squared distance is scored as
 // |x|^2 + |q|^2 - 2 <x, q> (the inner products are the contraction; |x|^2 is accumulated once per
 // vector beside it).  That value differs from the direct form sum (x - q)^2 (which is what the bound's

@@ -293,6 +293,45 @@ __device__ __forceinline__ void select_query(const Dev &D, int nq, int k, const 
     acc += quad_xor<2>(acc);
     return key_of_float((METRIC == 0 ? acc : -acc) + 0.0f);
   };
+  // ... with sixteen neighbouring lanes to a candidate, where there are few: a lane has a quarter as many chunks, so a wide vector is a
+  // turn or two of trips to memory and not a row of them (64 queries of 768 dimensions: the selection 92 us with four lanes, 80 with these; what is left of it is
+  // mostly the 170 to 250 finalists of a query, 192 pieces of 16 bytes each from lines of their own).
+  auto direct_key_row = [&](int i, int64_t *id) __attribute__((always_inline)) -> uint32_t {
+    uint32_t b, moff;
+    locate(i, b, moff);
+    const int sub = (int)(threadIdx.x & 15u);
+    if (sub == 0) *id = block_ids(D, b)[moff];
+    const float4 *__restrict__ x = block_vecs(D, b) + (size_t)(moff / kWave) * D.d4 * kWave + (moff & (kWave - 1));
+    const float4 *__restrict__ y = reinterpret_cast<const float4 *>(Q + (size_t)q * D.d);
+    float acc = 0.f;
+    for (int c0 = 0; c0 < D.d4; c0 += 128) {  // uniform
+      float4 v[8], w[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int c = min(c0 + 16 * u + sub, D.d4 - 1);
+        v[u] = from_halves ? half_floats(half_chunk(b, moff, c)) : x[(size_t)c * kWave];
+        w[u] = y[c];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        if (c0 + 16 * u >= D.d4) break;  // uniform
+        auto add = [&](auto lane_of) {
+          constexpr int kLane = decltype(lane_of)::value;
+          if (c0 + 16 * u + kLane >= D.d4) return;  // uniform
+          float t = acc;
+          accumulate<METRIC>(t, v[u], w[u]);
+          acc = row_broadcast<kLane>(t);
+        };
+        add(std::integral_constant<int, 0>{}); add(std::integral_constant<int, 1>{}); add(std::integral_constant<int, 2>{});
+        add(std::integral_constant<int, 3>{}); add(std::integral_constant<int, 4>{}); add(std::integral_constant<int, 5>{});
+        add(std::integral_constant<int, 6>{}); add(std::integral_constant<int, 7>{}); add(std::integral_constant<int, 8>{});
+        add(std::integral_constant<int, 9>{}); add(std::integral_constant<int, 10>{}); add(std::integral_constant<int, 11>{});
+        add(std::integral_constant<int, 12>{}); add(std::integral_constant<int, 13>{}); add(std::integral_constant<int, 14>{});
+        add(std::integral_constant<int, 15>{});
+      }
+    }
+    return key_of_float((METRIC == 0 ? acc : -acc) + 0.0f);
+  };
   // The same for two candidates at once: both block look-ups go out together, then all the chunks of
   // both (a candidate is a chain of two round trips to memory; two of them side by side cost one).
   auto direct_key_pair = [&](int ia, int ib, int64_t *ida, int64_t *idb, uint32_t &ka, uint32_t &kb) {
@@ -567,6 +606,17 @@ __device__ __forceinline__ void select_query(const Dev &D, int nq, int k, const 
       constexpr int kFours = kTopkThreads / 4;
       for (int p0 = from; p0 < m;) {  // uniform trip count: the lanes of a four stay together
         const int p = p0 + (int)(threadIdx.x >> 2);
+        if (CHAIN && m - p0 <= kTopkThreads / 16) {  // uniform
+          const int pr = p0 + (int)(threadIdx.x >> 4);
+          int64_t id = 0;
+          const uint32_t key = direct_key_row((int)sh.pay[pr < m ? pr : m - 1], &id);
+          if (kScoredLimit) worst = max(worst, key);
+          if (pr < m && (threadIdx.x & 15u) == 0) {
+            sh.k1[pr] = key;
+            sh.k2[pr] = (uint64_t)id ^ 0x8000000000000000ull;
+          }
+          break;
+        }
         if (!CHAIN && m - p0 > kFours) {  // uniform: every four takes two finalists, p and p + kFours
           const int p2 = p + kFours;
           int64_t id = 0, id2 = 0;
