@@ -530,7 +530,7 @@ def main() -> int:
         p2, u2 = b2.scan_bytes(32, first=20)
         block = {"config": b2.config_block(), "value": 200 * b2.B / e2, "unit": "queries/s",
                  "ms_per_step": e2 / 200 * 1e3,
-                 "roofline": b2.roofline(ms2, n2, p2, u2, measured_traffic(b2.w.name, b2.B)),
+                 "roofline": b2.roofline(ms2, n2, p2, u2, measured_traffic(b2.w.name, b2.B, b2.scan_kernel)),
                  "scan_scheduling": b2.scan_scheduling(200, 20, u2),
                  "latency_by_query_batch": b2.latency_table(args.latency_iters or 1000, PROTOCOL[2]["latency_batches"]),
                  "at_configured_insert_rate": b2.at_configured_rate(2000),
