@@ -144,8 +144,8 @@ __global__ __launch_bounds__(256) void k_centroid_mean(Dev D) {
 
 // Largest of a value per wavefront over the workgroup, into a word of float bits (non-negative floats order like their
 // bits).  Atomics on one word follow each other at about 12 ns, and that is what bounds both kernels below: one per
-// centroid took 0.2 ms for 16,384 of them, one per workgroup of 4 wavefronts and word 18 us of the 38 that 8,192 x 768
-// took.  So workgroups are the largest there are, and a value that cannot change the word stays out of the line: zero,
+// centroid took 0.2 ms for 16,384 of them, one per workgroup of 4 wavefronts and word 18 us of the 33 and 38 that 8,192 x
+// 768 took; 13 and 27 now.  So workgroups are the largest there are, and a value that cannot change the word stays out of the line: zero,
 // or no larger than what a look at the word finds there (it only grows; an old value costs an atomic, no more).
 constexpr int kTopThreads = 1024, kTopWaves = kTopThreads / kWave;
 __device__ inline void wg_atomic_max(float v, float *lds, uint32_t *word) {

@@ -230,15 +230,16 @@ __global__ __launch_bounds__(256) void k_fill(Dev D, Number chunks, const float 
   const int c = (int)(t - i * (Number)D.vchunks);
   int list = assign[i];
   uint32_t pos = did[i];
+  const float scale = D.halves_stride ? halves_scale(D) : 1.f;
+  const uint32_t known = D.halves_stride ? D.ctrl->half_inexact : 1u;
   uint32_t mid = pos / (uint32_t)D.T_m, moff = pos % (uint32_t)D.T_m;
   if (mid >= D.nblk[list]) return;  // the block could not be opened (pool exhausted)
   uint32_t b = (uint32_t)*table_entry(D, list, mid);
   const float4 v = stored_chunk(D.storage, reinterpret_cast<const float4 *>(Y) + (size_t)i * D.d4, c);
   block_vecs(D, b)[vec_chunk_index(D, moff, c)] = v;
   if (D.halves_stride) {  // uniform
-    const uint32_t known = D.ctrl->half_inexact;
     bool exact = true;
-    put_halves(D, b, moff, c, v, halves_scale(D), exact);
+    put_halves(D, b, moff, c, v, scale, exact);
     if (!exact && !known) D.ctrl->half_inexact = 1u;
   }
   if (c == 0) block_ids(D, b)[moff] = ids ? ids[i] : id_base + i;
@@ -419,6 +420,8 @@ __global__ __launch_bounds__(kTailVecs) void k_insert_tail(Dev D, int n, int spl
       ahead[u] = tid + u * kTailVecs < chunks ? y4[tid + u * kTailVecs] : make_float4(0.f, 0.f, 0.f, 0.f);
   }
   const uint32_t known = D.ctrl->max_len;
+  const float scale = FILL && D.halves_stride ? halves_scale(D) : 1.f;
+  const uint32_t inexact = FILL && D.halves_stride ? D.ctrl->half_inexact : 1u;
   int64_t id = 0;
   if (FILL && tid < n) id = ids ? ids[tid] : id_base + tid;
   int list = -1;
@@ -451,8 +454,6 @@ __global__ __launch_bounds__(kTailVecs) void k_insert_tail(Dev D, int n, int spl
     if (blk != ~0u) block_ids(D, blk)[pos % T] = id;
   }
   __syncthreads();
-  const float scale = D.halves_stride ? halves_scale(D) : 1.f;
-  const uint32_t inexact = D.ctrl->half_inexact;
   bool exact = true;
   auto put = [&](int t, int i, int c, const float4 &v) {
     if (s_blk[i] == ~0u) return;
