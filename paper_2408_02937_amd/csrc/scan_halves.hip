@@ -15,6 +15,10 @@ namespace rtams {
 // the sets would have to go round in unrolled code, or be moved, which waits for them.)  So nothing else may be loaded into
 // vector registers in the loop, or its wait would be for everything in flight: the blocks of the next units are looked up by
 // scalar loads.
+// What bounds it: HBM.  The scans of floats / of halves, one request at a time: 128 queries against 10 M x 96 544 / 279 us (6.0
+// TB/s, what a plain read reaches), 64 against 5 M x 768 627 / 296, 256 against skewed lists of 20 M x 256 2,595 / 1,370 (5.0
+// TB/s; 1.034 times its bytes cross HBM), and where the lists fit the last-level cache 256 against 1 M x 128 104 / 55.  Two steps of
+// 2 KiB ahead: three, four or steps of 4 KiB leave fewer workgroups on a compute unit, 1.5 to 2 times as long with four.
 constexpr uint32_t kHalfUnit = 32;
 typedef _Float16 HalfX8 __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ MfmaAcc half_product(const u32x4 &a, const u32x4 &b, const MfmaAcc &acc) {
