@@ -294,7 +294,8 @@ __device__ __forceinline__ void select_query(const Dev &D, int nq, int k, const 
     return key_of_float((METRIC == 0 ? acc : -acc) + 0.0f);
   };
   // ... with sixteen neighbouring lanes to a candidate, where there are few: a lane has a quarter as many chunks, so a wide vector is a
-  // turn or two of trips to memory and not a row of them (64 queries of 768 dimensions: the selection 92 us with four lanes, 80 with these; what is left of it is
+  // turn or two of trips to memory and not a row of them (64 queries of 768 dimensions: the selection 92 us with four lanes, 80 with these, 73 by half as many
+  // workgroups to a query; what is left of it is
   // mostly the 170 to 250 finalists of a query, 192 pieces of 16 bytes each from lines of their own).
   auto direct_key_row = [&](int i, int64_t *id) __attribute__((always_inline)) -> uint32_t {
     uint32_t b, moff;
@@ -777,7 +778,9 @@ void launch_select(const Dev &D, int64_t nq, int k, const float *Q, const Search
                    hipStream_t s) {
   if (nq <= 0) return;
   if (D.scan_halves) {
-    const int64_t parts = 2 * kComputeUnits / nq < 1 ? 1 : 2 * kComputeUnits / nq > kSelectParts ? kSelectParts : 2 * kComputeUnits / nq;
+    // as many to a query as give every compute unit a workgroup: each reads all of the query's records, so twice as many
+    // cost more than they bring (256 queries over 20 M x 256, skewed 174 / 206 us, 64 over 5 M x 768 73 / 77)
+    const int64_t parts = std::min<int64_t>((kComputeUnits + nq - 1) / nq, kSelectParts);
     const auto kernel = D.metric != 0 ? k_select_halves<1, true> : D.scan_mfma ? k_select_halves<0, false> : k_select_halves<0, true>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(nq * parts)), dim3(kTopkThreads), 0, s, D, (int)nq, k, Q, S, out_dist, out_ids);
     return;
