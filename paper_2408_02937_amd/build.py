@@ -10,7 +10,7 @@ LIB = os.path.join(HERE, "librtams.so")
 SOURCES = ["rtams.hip", "coarse.hip", "coarse_mfma.hip", "insert.hip", "pq.hip", "probe.hip", "group.hip", "scan.hip", "scan_mm.hip", "scan_halves.hip",
            "pq_scan.hip", "small.hip", "select.hip", "rearrange.hip", "maint.hip"]
 HEADERS = ["rtams_dev.h", "rtams_launch.h", "search_common.h", "coarse_exact.h", "bound.h",
-           "probe_plan.h", "scan_item.h", "scan_tile.h", os.path.join("..", "..", "include", "rtams.h"),
+           "probe_plan.h", "scan_item.h", "scan_tile.h", "halves.h", os.path.join("..", "..", "include", "rtams.h"),
            os.path.join("..", "..", "include", "rtams_measure.h")]
 
 # packed-fp32 instructions are switched off for every device compilation

@@ -135,6 +135,10 @@ __device__ __forceinline__ void group_request(const Dev &D, int nq, int nprobe, 
   const bool lean = (long long)min((long long)D.nlist, (long long)nq * nprobe) <= kLdsEntries;
   uint4 *plist = lean ? reinterpret_cast<uint4 *>(s_raw) : S.plist;
   ScanQueues *Qs = S.queues;
+  // the word of an item that says how many pairs it has
+  auto pairs_word = [&](uint32_t pairs, uint32_t len, uint32_t sg, uint32_t seg) {
+    return HALVES ? half_item_word(pairs, len, sg, seg) : pairs;
+  };
   // Cost of a list for the split over the XCDs, per group of 64 vectors: reading it once from HBM
   // (each XCD has its own link to memory) plus the arithmetic of every query that probes it.  On
   // this chip one group's bytes cost about as much as the arithmetic of 12 queries (L2) or 24 (IP).
@@ -291,7 +295,7 @@ __device__ __forceinline__ void group_request(const Dev &D, int nq, int nprobe, 
         uint32_t sg = 0, tt = 0;
         for (uint32_t i = 0; i < n; ++i) {
           const uint32_t p_lo = tt * small + min(tt, extra);
-          tile_desc[ist + i] = make_uint4(pl.x, pl.y + p_lo, small + (tt < extra ? 1u : 0u), sg);
+          tile_desc[ist + i] = make_uint4(pl.x, pl.y + p_lo, pairs_word(small + (tt < extra ? 1u : 0u), pl.w, sg, seg), sg);
           if (++tt == tiles) { tt = 0; ++sg; }
         }
       }
@@ -314,10 +318,11 @@ __device__ __forceinline__ void group_request(const Dev &D, int nq, int nprobe, 
         const uint32_t first = (uint32_t)__shfl((int)ist, t), n_t = (uint32_t)__shfl((int)n, t);
         const uint32_t tiles_t = (uint32_t)__shfl((int)tiles, t);
         const uint32_t small_t = (uint32_t)__shfl((int)small, t), extra_t = (uint32_t)__shfl((int)extra, t);
+        const uint32_t len_t = HALVES ? (uint32_t)__shfl((int)pl.w, t) : 0u;
         for (uint32_t i = (uint32_t)lane; i < n_t; i += kWave) {
           const uint32_t sg = i / tiles_t, tt = i - sg * tiles_t;
           const uint32_t p_lo = tt * small_t + min(tt, extra_t);
-          tile_desc[first + i] = make_uint4(l, pst + p_lo, small_t + (tt < extra_t ? 1u : 0u), sg);
+          tile_desc[first + i] = make_uint4(l, pst + p_lo, pairs_word(small_t + (tt < extra_t ? 1u : 0u), len_t, sg, seg), sg);
         }
       }
     }
@@ -361,7 +366,7 @@ __device__ __forceinline__ void group_request(const Dev &D, int nq, int nprobe, 
         for (uint32_t i = (uint32_t)tid; i < n; i += kGroupThreads) {
           const uint32_t sg = i / tiles, tt = i - sg * tiles;
           const uint32_t p_lo = tt * small + min(tt, extra);
-          tile_desc[first + i] = make_uint4(pl.x, pl.y + p_lo, small + (tt < extra ? 1u : 0u), sg);
+          tile_desc[first + i] = make_uint4(pl.x, pl.y + p_lo, pairs_word(small + (tt < extra ? 1u : 0u), pl.w, sg, seg), sg);
         }
       }
     }

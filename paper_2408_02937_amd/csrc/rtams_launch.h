@@ -43,7 +43,7 @@ struct SearchScratch {
   uint32_t *grouped;    // [max_batch * max_nprobe] pairs (query << 10 | probe) grouped by list
   uint4 *plist;         // [min(nlist, max_batch * max_nprobe)] per probed list, in list order: {list, unused, pairs,
                         // length as seen by the grouping step}
-  uint4 *tile_desc;     // [item_cap] {list, first pair of the tile, pairs of the tile, segment} per item
+  uint4 *tile_desc;     // [item_cap] {list, first pair of the tile, pairs of the tile, segment} per item (scans of halves: half_item_word() for the pairs)
   uint32_t item_cap;
   ScanQueues *queues;   // work items of this request, split into one queue per XCD
   float *lut;           // [max_batch][pq_m][256] sub-scores of the queries against the codebooks (PQ lists)

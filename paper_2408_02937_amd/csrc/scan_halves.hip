@@ -19,14 +19,14 @@ namespace rtams {
 // TB/s, what a plain read reaches), 64 against 5 M x 768 627 / 296, 256 against skewed lists of 20 M x 256 2,595 / 1,370 (5.0
 // TB/s; 1.034 times its bytes cross HBM), and where the lists fit the last-level cache 256 against 1 M x 128 104 / 55.  Two steps of
 // 2 KiB ahead: three, four or steps of 4 KiB leave fewer workgroups on a compute unit, 1.5 to 2 times as long with four.
-constexpr uint32_t kHalfUnit = 32;
 typedef _Float16 HalfX8 __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ MfmaAcc half_product(const u32x4 &a, const u32x4 &b, const MfmaAcc &acc) {
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(HalfX8, a), __builtin_bit_cast(HalfX8, b), acc, 0, 0, 0);
 }
 
-// Entry i of a list's block table by scalar loads (i the same for the whole wavefront; an entry below the list's length when the
-// request was planned was written by kernels that ended before this one began).
+// Entry i of a list's block table by scalar loads (i the same for the whole wavefront).  Only for entries below the length that the plan
+// saw: those were out before the plan ended, so no cache of this kernel has them as they were before.  An entry that an insertion
+// makes while the scan runs may read as whatever was in its place.
 typedef const __attribute__((address_space(4))) int32_t *ScalarInts;
 __device__ __forceinline__ int32_t table_dir_scalar(const Dev &D, int list, uint32_t i) {
   return ((ScalarInts)(uintptr_t)D.seg_dir)[(size_t)list * kTableSegs + table_seg(i)];
@@ -43,7 +43,7 @@ struct HalfCopies {
 };
 struct HalfItem {
   int list;
-  uint32_t u_end;     // units of the list up to which the wavefront goes
+  uint32_t u_end;     // units of the list up to which the wavefront goes: the plan's
   uint32_t quads, upb, ring_at;  // steps of a unit; units of a block; LDS address of the wavefront's ring
   uint32_t off, off_last;  // where a lane's chunk lies among those of its 16 vectors, in a step and in the last one of a vector
   uint32_t *places;   // LDS: where the wavefront's n-th unit lies in the pool, at n % kHalfPlaces
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(kMmWaves *kWave, 4) void k_scan_halves(Dev D, int m
   extern __shared__ float4 lds_halves[];
   uint4 desc;
   uint32_t seg;
-  const uint32_t pairs = take_item<STEAL>(S, desc, seg);
+  const uint32_t word = take_item<STEAL>(S, desc, seg), pairs = half_item_pairs(word);
   if (pairs == 0) return;  // uniform over the workgroup
   const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)desc.y);
   const int rows = pairs > 16u ? 32 : 16;
@@ -202,8 +202,8 @@ __global__ __launch_bounds__(kMmWaves *kWave, 4) void k_scan_halves(Dev D, int m
   float *consts = reinterpret_cast<float *>(tq + tile_rows);  // bounds, c0, c1 and lengths, kMmTileMax of each
   uint32_t *places = reinterpret_cast<uint32_t *>(consts + kHalfConsts * kMmTileMax);
   HalfStage &st = reinterpret_cast<HalfStage *>(places + kMmWaves * kHalfPlaces)[wave];
-  // the wavefront's first steps are on their way before the tile is set up; up to what the list holds by now, which is no less
-  // than any query of the tile wants, and never past its chain, whatever the descriptors say
+  // the wavefront's first steps are on their way before the tile is set up; up to the length that the plan saw, which is no less
+  // than any query of the tile wants, and never past the list's chain, whatever the descriptors say
   HalfItem it;
   it.list = __builtin_amdgcn_readfirstlane((int)desc.x);
   it.quads = (uint32_t)(D.hchunks + 3) / 4u;
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(kMmWaves *kWave, 4) void k_scan_halves(Dev D, int m
   it.ring_at = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_address(ring_mine));
   const uint32_t per_seg = seg * (kWave / kHalfUnit), u_begin = (uint32_t)__builtin_amdgcn_readfirstlane((int)desc.w) * per_seg;
   HalfCopies c{nullptr, u_begin + (uint32_t)wave, 0u, 0u, 0u, 0u};
-  // what only the descriptor decides is asked for together: the tile's pairs, the length, and where the table has the blocks of the
+  // what only the descriptor decides is asked for together: the tile's pairs, the blocks of the list, and where the table has the blocks of the
   // first two units (trips to memory behind one another were 6 us of an item's 18: 1 M x 128, 8 groups to an item)
   constexpr uint32_t kInFlight = 4, kThreads = kMmWaves * kWave;
   const uint32_t total = (uint32_t)rows * units;
@@ -226,10 +226,10 @@ __global__ __launch_bounds__(kMmWaves *kWave, 4) void k_scan_halves(Dev D, int m
     row[u] = min((threadIdx.x + u * kThreads) / units, (uint32_t)rows);
     pk_row[u] = row[u] < pairs ? S.grouped[first + row[u]] : 0u;
   }
-  const uint32_t len = __hip_atomic_load(&D.visible_len[it.list], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), blocks = D.nblk[it.list];
-  const uint32_t i0 = c.u / it.upb, i1 = (c.u + kMmWaves) / it.upb;
+  const uint32_t blocks = D.nblk[it.list], planned = u_begin + (uint32_t)__builtin_amdgcn_readfirstlane((int)half_item_units(word));
+  const uint32_t i0 = min(c.u, planned) / it.upb, i1 = min(c.u + kMmWaves, planned) / it.upb;
   const int32_t dir0 = table_dir_scalar(D, it.list, i0), dir1 = table_dir_scalar(D, it.list, i1);
-  it.u_end = (uint32_t)__builtin_amdgcn_readfirstlane((int)min(min((len + kHalfUnit - 1) / kHalfUnit, blocks * it.upb), u_begin + per_seg));
+  it.u_end = (uint32_t)__builtin_amdgcn_readfirstlane((int)min(blocks * it.upb, planned));
   if (c.u < it.u_end) {  // uniform over the wavefront
     const uint32_t b0 = table_entry_scalar(D, dir0, i0);
     if (c.u + kMmWaves < it.u_end) c.next = table_entry_scalar(D, dir1, i1);

@@ -3,6 +3,7 @@
 // and the launch shape of the list scan (the planning kernel needs it as well).
 #pragma once
 #include <type_traits>
+#include "halves.h"
 #include "rtams_launch.h"
 
 namespace rtams {
