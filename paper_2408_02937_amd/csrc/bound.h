@@ -126,16 +126,16 @@ __device__ uint32_t sample_scores(const Dev &D, int nprobe, int max_nprobe, int 
 
 // The same sample from the halves beside the lists: half the bytes, and a compute unit reads no more than so many at once.  A score is
 // of the query against what the halves hold; what they leave out goes into the bound where it is used (halves_bound_key),
-// for inner products but what depends on the vector, which is added here: the score is then no less than the vector's own.
+// for inner products but what depends on the vector, `over` times its length, which is added here: the score is then no less than
+// the vector's own.
 template <int METRIC>
 __device__ uint32_t sample_scores_halves(const Dev &D, int nprobe, int max_nprobe, int q, uint32_t want_groups, const SearchScratch &S,
-                                         const float4 *qv, float qnorm, uint32_t *skey, uint32_t *gkey, uint32_t part, uint32_t parts,
+                                         const float4 *qv, float over, uint32_t *skey, uint32_t *gkey, uint32_t part, uint32_t parts,
                                          const NearestList &first) {
   const int tid = threadIdx.x, lane = tid & (kWave - 1), hc = D.hchunks;
   const uint32_t mine = (uint32_t)(tid / kWave) * parts + part, step = blockDim.x / kWave * parts;
   const uint32_t gpb = (uint32_t)D.groups_per_block;
   const float ixs = 1.f / halves_scale(D);
-  const float over = qnorm * ((halves_are_floats(D) ? 0.f : 4.9e-4f) + (float)(2 * D.d + 8) * 6.0e-8f);
   const int sub = lane & 3, of16 = lane >> 2, quads = (hc + 3) / 4;  // the lane's chunk of four, and its vector of each 16
   uint32_t g_first = 0;  // groups of the lists before list p
   for (int p = 0; p < nprobe && g_first < want_groups; ++p) {  // uniform over the workgroup
@@ -297,8 +297,9 @@ constexpr size_t kPqBoundLdsBytes = kSampleMax * sizeof(uint32_t);
 constexpr int kSampleParts = 4;
 constexpr uint32_t kSplitChunks = 260;
 
-// A query's halves and what goes with them (half_query_row), by one wavefront.
-__device__ inline void make_half_query(const Dev &D, const SearchScratch &S, int q, const float *__restrict__ Q, float *norm_out) {
+// A query's halves and what goes with them (half_query_row), by one wavefront, and `over` of its sample.  (Workgroups that share the
+// sample all write the row; should they find halves_are_floats different, either is right.)
+__device__ inline void make_half_query(const Dev &D, const SearchScratch &S, int q, const float *__restrict__ Q, float *over_out) {
   const int lane = threadIdx.x & (kWave - 1);
   const float4 *__restrict__ y = reinterpret_cast<const float4 *>(Q + (size_t)q * D.d);
   double nsq = 0.0;
@@ -332,8 +333,9 @@ __device__ inline void make_half_query(const Dev &D, const SearchScratch &S, int
   for (int o = kWave / 2; o > 0; o >>= 1) { hsq += __shfl_xor(hsq, o); rsq += __shfl_xor(rsq, o); }
   if (lane == 0) {
     const float norm = sqrtf((float)(nsq > hsq ? nsq : hsq)) * 1.00001f;
-    *reinterpret_cast<float4 *>(row + half_row_units(D)) = make_float4(inv, (float)hsq, norm, sqrtf((float)rsq) * 1.00001f);
-    *norm_out = norm;
+    const bool exact = halves_are_floats(D);
+    *reinterpret_cast<float4 *>(row + half_row_units(D)) = make_float4(exact ? -inv : inv, (float)hsq, norm, sqrtf((float)rsq) * 1.00001f);
+    *over_out = norm * ((exact ? 0.f : 4.9e-4f) + (float)(2 * D.d + 8) * 6.0e-8f);
   }
 }
 
@@ -355,8 +357,8 @@ __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, in
   constexpr bool halves = HALVES;
   const bool norm_form = !PQ && !halves && uses_norm_form(D);
   __shared__ float s_qn;
-  __shared__ float s_norm;
-  if (halves && tid < kWave) make_half_query(D, S, q, Q, &s_norm);
+  __shared__ float s_over;
+  if (halves && tid < kWave) make_half_query(D, S, q, Q, &s_over);
   if (norm_form && tid < kWave) {
     double a = 0.0;
     for (int c = tid; c < D.d; c += kWave) {
@@ -449,8 +451,8 @@ __device__ void sample_bound(const Dev &D, int q, int nprobe, int max_nprobe, in
     uint32_t *gkey = parts > 1 ? reinterpret_cast<uint32_t *>(S.approx) + (size_t)q * D.nlist : nullptr;
     uint32_t groups;
     if (HALVES) {  // (of a request that reads halves)
-      groups = D.metric == 0 ? sample_scores_halves<0>(D, nprobe, max_nprobe, q, want_groups, S, qv, s_norm, skey, gkey, part, parts, first)
-                             : sample_scores_halves<1>(D, nprobe, max_nprobe, q, want_groups, S, qv, s_norm, skey, gkey, part, parts, first);
+      groups = D.metric == 0 ? sample_scores_halves<0>(D, nprobe, max_nprobe, q, want_groups, S, qv, s_over, skey, gkey, part, parts, first)
+                             : sample_scores_halves<1>(D, nprobe, max_nprobe, q, want_groups, S, qv, s_over, skey, gkey, part, parts, first);
     } else if (D.metric == 0) {
       if (D.storage == 1) groups = sample_scores<0, 1>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, gkey, part, parts, first);
       else if (D.storage == 2) groups = sample_scores<0, 2>(D, nprobe, max_nprobe, q, want_groups, Q, S, qv, skey, gkey, part, parts, first);

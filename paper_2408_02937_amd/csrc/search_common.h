@@ -416,22 +416,28 @@ struct HalfQuery {
   float e;
   float u;        // 1.001 2^-11, or 0 where the halves of all vectors are their floats
 };
-// whether the halves of every vector inserted so far are its floats (then nothing is left out: u and t are zero)
+// Whether the halves of every vector inserted so far are its floats (then nothing is left out: u and t are zero).  Insertions
+// write the word while searches run, so a request asks once, for each query where its bound is set, behind the lengths of its
+// lists (an insertion writes the word before it publishes: "yes" holds for all that the request may see), and goes by what it wrote
+// down then (halves_exact_for): workgroups that share a query, and the threads of one, have to agree.
 __device__ inline bool halves_are_floats(const Dev &D) {
   return __hip_atomic_load(&D.ctrl->half_inexact, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
 }
 __host__ __device__ inline uint32_t half_row_units(const Dev &D) { return (uint32_t)(D.hchunks + 3) / 4u * 4u; }
 // of query q: its halves, zeros up to whole steps of 32 coordinates, then what half_query() makes its HalfQuery of: one over its
-// scale, |q'|^2, |q| from above, and s (in the room the coarse filter has for
+// scale (with the sign set where halves_are_floats), |q'|^2, |q| from above, and s (in the room the coarse filter has for
 // halves of the queries, twice what they take; nobody needs those once the probes are chosen)
 __device__ inline u32x4 *half_query_row(const Dev &D, const SearchScratch &S, uint32_t q) {
   return S.qhalf + (size_t)q * (half_row_units(D) + 1u);
 }
+__device__ inline bool halves_exact_for(const Dev &D, const SearchScratch &S, uint32_t q) {
+  return *reinterpret_cast<const float *>(half_query_row(D, S, q) + half_row_units(D)) < 0.f;
+}
 __device__ inline HalfQuery half_query(const Dev &D, const SearchScratch &S, uint32_t q) {
   const float4 w = *reinterpret_cast<const float4 *>(half_query_row(D, S, q) + half_row_units(D));
-  const bool exact = halves_are_floats(D);
+  const bool exact = w.x < 0.f;
   const float ixs = 1.f / halves_scale(D), t = exact ? 0.f : 6.11e-5f * sqrtf((float)D.d) * ixs;  // (6.11e-5: 1.001 2^-14)
-  HalfQuery m{w.x * ixs, w.y, w.z, w.w + t, exact ? 0.f : 4.888e-4f};
+  HalfQuery m{fabsf(w.x) * ixs, w.y, w.z, w.w + t, exact ? 0.f : 4.888e-4f};
   if (D.metric != 0) {
     m.a = 1.002f * (w.w + w.z * (m.u + (float)(D.d + D.d / 64 + 140) * 6.0e-8f));
     m.e = 1.002f * t * w.z + 1e-30f;

@@ -145,7 +145,8 @@ __device__ __forceinline__ void select_query(const Dev &D, int nq, int k, const 
   if (threadIdx.x == 0) scount = 0;
   __syncthreads();
   // (what they have scored goes behind the records, where there is room for it)
-  const bool shared = HALVES && parts > 1 && !halves_are_floats(D) && (int64_t)n * D.d4 >= kSharedWork &&
+  const bool from_halves = HALVES && halves_exact_for(D, S, (uint32_t)q);
+  const bool shared = HALVES && parts > 1 && !from_halves && (int64_t)n * D.d4 >= kSharedWork &&
                       S.qtotal[q] >= (uint32_t)n + 2u * kMaxK;
   if (HALVES && part > 0 && !shared) {  // uniform
     if (threadIdx.x == 0) overflow_request_done(S, gridDim.x);
@@ -186,7 +187,6 @@ __device__ __forceinline__ void select_query(const Dev &D, int nq, int k, const 
   };
   // Where the halves beside the lists are the floats, the finalists are scored from those: a vector's chunks lie side by side by fours
   // there, where 16 bytes of the lists are a line of memory each.
-  const bool from_halves = HALVES && halves_are_floats(D);
   const float ixs = HALVES ? 1.f / halves_scale(D) : 1.f;
   auto half_floats = [&](const uint2 &h) {
     const float4 f = chunk_piece<1>(make_float4(__uint_as_float(h.x), __uint_as_float(h.y), 0.f, 0.f), 0);
