@@ -641,7 +641,7 @@ __device__ __forceinline__ void select_query(const Dev &D, int nq, int k, const 
       }
     };
     collect(true, 0u, lim, !kScoredLimit || have <= k);
-    int m = (int)sh.cnt[0], from = 0;  // (a shared query's k best are scored by all of its workgroups, and belong to the first)
+    int m = (int)sh.cnt[0];  // (a shared query's k best are scored by all of its workgroups)
     if (m <= kMaxK) {
       score(0, m);
       if constexpr (kScoredLimit) {
@@ -657,7 +657,6 @@ __device__ __forceinline__ void select_query(const Dev &D, int nq, int k, const 
           if (upto > lim) collect(false, lim, upto, true);
           const int more = (int)sh.cnt[0];
           if (more <= kMaxK) score(m, more);
-          if (part > 0) from = m;
           m = more;
         }
       }
@@ -671,12 +670,25 @@ __device__ __forceinline__ void select_query(const Dev &D, int nq, int k, const 
       if (m > kMaxK) {
         if (threadIdx.x == 0) __hip_atomic_store(rec_alone(S, (uint32_t)q), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       } else {
-        if (threadIdx.x == 0) sh.cnt[1] = m > from ? atomicAdd(rec_scored(S, (uint32_t)q), (uint32_t)(m - from)) : 0u;
+        // What is handed over are the workgroup's own of all it has scored.  (Whose a finalist is cannot go by a threshold: where
+        // more than kMaxK records offered themselves for a limit, the workgroups have limits, and so thresholds, of their own.)
+        constexpr int kMine = kMaxK / kTopkThreads;
+        uint32_t slot[kMine];
+        if (threadIdx.x == 0) sh.cnt[1] = 0u;
         __syncthreads();
-        const uint32_t at = sh.cnt[1];
+#pragma unroll
+        for (int u = 0; u < kMine; ++u) {
+          const int p = (int)threadIdx.x + u * kTopkThreads;
+          slot[u] = p < m && mine(sh.pay[p]) ? atomicAdd(&sh.cnt[1], 1u) : ~0u;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) sh.bc[0] = sh.cnt[1] ? atomicAdd(rec_scored(S, (uint32_t)q), sh.cnt[1]) : 0u;
+        __syncthreads();
         uint32_t *ok = const_cast<uint32_t *>(rk) + n, *op = const_cast<uint32_t *>(rp) + n;
-        for (int p = from + (int)threadIdx.x; p < m; p += kTopkThreads) {
-          const uint32_t o = at + (uint32_t)(p - from);
+#pragma unroll
+        for (int u = 0; u < kMine; ++u) {
+          const int p = (int)threadIdx.x + u * kTopkThreads;
+          const uint32_t o = slot[u] == ~0u ? ~0u : sh.bc[0] + slot[u];
           if (o >= (uint32_t)kMaxK) continue;  // (too many all in all: the last workgroup sees that)
           __hip_atomic_store(&op[o], (uint32_t)sh.k1[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           __hip_atomic_store(&ok[2 * o], (uint32_t)sh.k2[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

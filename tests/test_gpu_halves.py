@@ -217,3 +217,54 @@ def test_who_keeps_halves_and_when_they_are_taken():
     assert L.rtams_set_halves(g._h, t.data_ptr(), want) == rtams.ESTATE
     torch.cuda.synchronize()
     g.close()
+
+
+# A query's workgroups take a limit from whichever of its records they come by first, and need not take the same.  Here some 1,060 of the
+# first 4,096 records share the first digit of their scores (inner products from 128 to 512), more than the 1,024 that are scored for
+# a limit.  The last of them, below 256, decides whether the digits of the next selection are of one or of two: a threshold of 259 or of
+# 258, with inner products closer to 259 than halves tell apart, some of them among the 1,000 best, on either side of it.
+# (Two of these 64 fail where a workgroup leaves out what lies below its own threshold.)
+@pytest.mark.parametrize("sixteen", range(4))
+def test_workgroups_of_a_query_with_limits_of_their_own(sixteen, monkeypatch):
+    for seed in range(16 * sixteen, 16 * sixteen + 16):
+        print(f"[case] limits of their own, seed {seed}", flush=True)
+        limits_of_their_own(seed, monkeypatch)
+
+
+def limits_of_their_own(seed, monkeypatch):
+    d, nlist, nq, k, top = 64, 16, 32, 1000, 1200
+    gen = torch.Generator(DEV).manual_seed(seed)
+
+    def between(m, lo, hi):
+        return lo + (hi - lo) * torch.rand(m, device=DEV, generator=gen)
+
+    x = 0.02 * torch.randn(4700 + 3096, d, device=DEV, generator=gen)
+    x[:, :3] = 0.0
+    axis = torch.zeros(d, device=DEV)
+    axis[3:6] = 3 ** -0.5
+    norm = 115.5 * 3 ** 0.5  # of the query, whose halves are its floats
+    x -= (x @ axis)[:, None] * axis
+    x[:, 0] = 0.3
+    margin = 1.002 * norm * (4.888e-4 + (d + d // 64 + 140) * 6.0e-8)  # of a vector of length 1: what a score of halves is below the inner product's negative
+    edge = 259 - margin * ((259 / norm) ** 2 + 0.09 + 0.02 ** 2 * 60) ** 0.5
+    best = torch.cat([between(950, 300, 400), between(40, 259.2, 262), between(20, edge - 0.02, edge + 0.06), between(8, 258.1, 258.6),
+                      between(top - 1019, 256.2, 257.4), between(1, 255.4, 255.5)])[torch.randperm(top, device=DEV, generator=gen)]
+    rest, out = between(4700 - top, -20, 100), between(3096, -80, -30)
+    near = torch.cat([best[:300], rest[:700], out])  # the nearest list, which the sample is of
+    far = torch.cat([best[300:], rest[700:]])
+    ips = torch.cat([near[torch.randperm(len(near), device=DEV, generator=gen)], far[torch.randperm(len(far), device=DEV, generator=gen)]])
+    x[:len(near), 1], x[:len(near), 0] = 0.3, 0.0
+    x += ips[:, None] / norm * axis
+    centres = 0.01 * torch.randn(nlist, d, device=DEV, generator=gen)
+    centres[0] += axis
+    centres[0, 1], centres[1, 0] = 100.0, 100.0
+    g = index(d, nlist, "ip", 64, len(x), nlist, monkeypatch)
+    g.set_centroids(centres)
+    g.add(x)
+    q = torch.zeros(nq, d, device=DEV)
+    q[:, 3:6] = 115.5
+    want, got = both(g, q, k, nlist)
+    kept = g.request_trace(nq)[1].to(torch.int64)
+    assert kept.min() > 4096 and want[0][:, -1].min() > 258.7, (kept, want[0][:, -1])
+    same(want, got)
+    g.close()
