@@ -268,3 +268,21 @@ def limits_of_their_own(seed, monkeypatch):
     assert kept.min() > 4096 and want[0][:, -1].min() > 258.7, (kept, want[0][:, -1])
     same(want, got)
     g.close()
+
+
+# Coordinates that vanish under the scale of the halves: one centroid is so large that all others' vectors are zero there
+def test_vectors_that_vanish_under_the_scale(monkeypatch):
+    print("[case] vectors that vanish under the scale", flush=True)
+    gen = torch.Generator(DEV).manual_seed(8)
+    d, nlist, n = 64, 16, 4000
+    centres = 1e-20 * torch.randn(nlist, d, device=DEV, generator=gen)
+    centres[0] = 2.0 ** 100
+    x = centres[1 + torch.randint(nlist - 1, (n,), device=DEV, generator=gen)] + 1e-21 * torch.randn(n, d, device=DEV, generator=gen)
+    g = index(d, nlist, "ip", 64, n, nlist, monkeypatch)
+    g.set_centroids(centres)
+    g.add(x)
+    q = 1e18 * torch.randn(8, d, device=DEV, generator=gen)
+    want, got = both(g, q, 10, nlist)
+    assert want[0].abs().min() > 0
+    same(want, got)
+    g.close()
