@@ -286,3 +286,21 @@ def test_vectors_that_vanish_under_the_scale(monkeypatch):
     assert want[0].abs().min() > 0
     same(want, got)
     g.close()
+
+
+# Queries so short that their squares, or those of what their halves leave out, are zero in 32 bits
+@pytest.mark.parametrize("metric", ["l2", "ip"])
+@pytest.mark.parametrize("size", [1e-17, 1e-20, 1e-22, 1e-24, 1e-30])
+@pytest.mark.parametrize("whole", [False, True])
+def test_short_queries(metric, size, whole, monkeypatch):
+    print(f"[case] queries of {size}, {metric}, whole {whole}", flush=True)
+    gen = torch.Generator(DEV).manual_seed(9)
+    d, nlist, n = 128, 16, 20_000
+    centres = 60 * torch.randn(nlist, d, device=DEV, generator=gen)
+    x = centres[torch.randint(nlist, (n,), device=DEV, generator=gen)] + 20 * torch.randn(n, d, device=DEV, generator=gen)
+    x = x.round_() if whole else x
+    g = index(d, nlist, metric, 64, n, nlist, monkeypatch)
+    g.set_centroids(centres)
+    g.add(x)
+    same(*both(g, size * torch.randn(40, d, device=DEV, generator=gen), 100, 8))
+    g.close()
