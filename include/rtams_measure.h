@@ -25,6 +25,8 @@ int rtams_scan_time(rtams_index *ix, double *ms_sum, int64_t *launches, int rese
  * over product-quantiser codes (k_pq_scan), each since the last reset, counted
  * at launch while "profile_scan" is 1.  The library chooses per request. */
 int rtams_scan_kernels(rtams_index *ix, int64_t *launches3, int reset);
+/* ... and how many were scans of the halves beside float lists (k_scan_halves), which are none of those three. */
+int rtams_scans_of_halves(rtams_index *ix, int64_t *launches, int reset);
 /* What the last request on a stream resource left in its scratch (0 .. n_resources - 1; n_resources is the static
  * array of rtams_search_noalloc, which the next request of any index overwrites), for tests of how requests are
  * answered.  Per query of its nq: h_bounds the pruning bound as the key the scan compared with (0xFFFFFFFF: every

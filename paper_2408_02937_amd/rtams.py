@@ -32,7 +32,7 @@ SYMBOLS = [
     "rtams_poll_error", "rtams_clear_error", "rtams_last_error", "rtams_set_param", "rtams_scan_time",
     "rtams_copy_plain", "rtams_read_plain", "rtams_set_codebooks", "rtams_list_export_codes",
     "rtams_search_noalloc", "rtams_overflow_bytes_for", "rtams_scan_kernels",
-    "rtams_request_trace", "rtams_halves_bytes", "rtams_set_halves",
+    "rtams_request_trace", "rtams_halves_bytes", "rtams_set_halves", "rtams_scans_of_halves",
 ]
 
 
@@ -109,6 +109,7 @@ def lib():
         L.rtams_set_param.argtypes = [vp, C.c_char_p, i64]
         L.rtams_scan_time.argtypes = [vp, C.POINTER(C.c_double), C.POINTER(i64), C.c_int]
         L.rtams_scan_kernels.argtypes = [vp, C.POINTER(i64), C.c_int]
+        L.rtams_scans_of_halves.argtypes = [vp, C.POINTER(i64), C.c_int]
         L.rtams_request_trace.argtypes = [vp, i32, i64, vp, vp, C.POINTER(i32)]
         L.rtams_copy_plain.argtypes = [vp, vp, C.c_size_t, vp]
         L.rtams_read_plain.argtypes = [vp, C.c_size_t, vp, vp]
@@ -349,7 +350,9 @@ class Index:
     def scan_kernels(self, reset: bool = False) -> dict:
         n = (C.c_int64 * 3)()
         _chk(lib().rtams_scan_kernels(self._h, n, int(reset)), "rtams_scan_kernels")
-        return {"k_scan": n[0], "k_scan_mm": n[1], "k_pq_scan": n[2]}
+        h = C.c_int64()
+        _chk(lib().rtams_scans_of_halves(self._h, C.byref(h), int(reset)), "rtams_scans_of_halves")
+        return {"k_scan": n[0], "k_scan_mm": n[1], "k_pq_scan": n[2], "k_scan_halves": h.value}
 
     def request_trace(self, nq: int, resource: int = 0):
         """What the last request on a stream resource left behind, once it is done: the keys of its queries' bounds, the

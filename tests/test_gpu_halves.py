@@ -192,6 +192,27 @@ def test_which_requests_read_them(metric, d, nlist, length, nq, nprobe, k, path,
     g.close()
 
 
+def test_timed_scans_of_halves_are_counted_as_such(monkeypatch):
+    gen = torch.Generator(DEV).manual_seed(10)
+    d, nlist, n = 64, 16, 5000
+    x = torch.randn(n, d, device=DEV, generator=gen)
+    g = index(d, nlist, "l2", 64, n, 8, monkeypatch)
+    g.set_centroids(x[:nlist].contiguous())
+    g.add(x)
+    g.set_param("small_requests", 0)
+    g.set_param("profile_scan", 1)
+    for halves, mfma, name in ((2, 1, "k_scan_halves"), (2, 2, "k_scan_halves"), (0, 2, "k_scan_mm"), (0, 0, "k_scan")):
+        g.set_param("scan_halves", halves)
+        g.set_param("scan_mfma", mfma)
+        for _ in range(2):
+            g.search(x[:64].contiguous(), 5, 8)
+            torch.cuda.synchronize()
+        assert g.scan_kernels()[name] == 2
+        got = g.scan_kernels(reset=True)
+        assert got.pop(name) == 2 and not any(got.values()), (name, got)
+    g.close()
+
+
 def test_who_keeps_halves_and_when_they_are_taken():
     L = rtams.lib()
     kinds = {"f32": (64, {}), "16 lists": (16, {}), "15 lists": (15, {}), "f16": (64, dict(storage="f16")), "u8": (64, dict(storage="u8")), "pq": (64, dict(pq_m=8))}
