@@ -287,6 +287,7 @@ struct rtams_index {
   std::atomic<int64_t> use_mfma{1};  // matrix-core filter in front of the exact coarse arithmetic
   std::atomic<int64_t> scan_mfma{1}; // flat lists: the scan's dot products on the matrix cores
   std::atomic<int64_t> scan_halves{1};     // the scan reads the halves beside float lists, where there are: 0 never, 1 when it pays, 2 whenever it can
+  std::atomic<int64_t> halves_rest{0};     // requests that the rule leaves to the floats all the same (halves_may_tell)
   std::atomic<int64_t> small_requests{1};  // small requests in three launches, without a plan (0: like all others)
   std::atomic<int64_t> scan_byte_weight{0};
   std::atomic<int64_t> scan_min_choice{-1};
@@ -362,6 +363,24 @@ int64_t longest_list(const rtams_index *ix) { return (int64_t)(ix->mirror->len_w
 int64_t longest_list_bound(const rtams_index *ix) {
   const unsigned long long w = ix->mirror->len_word;
   return (int64_t)(w >> 32) + (int64_t)(uint32_t)((uint32_t)ix->ntotal_host.load() - (uint32_t)w);
+}
+
+// Whether halves are worth another try.  They tell nothing where most of what a request meets lies within their margin of its bound:
+// squared distances of queries or vectors many times as long as the vectors are apart, and vectors of which no half is finite.
+// Then what the scan kept is scored by one workgroup to a query, and that is slower than the floats would have been: 256 queries x
+// 32 over 1 M x 128 1,000 us instead of 171 where the centroids are 1,000 times too small for the vectors, and 878 instead of 199
+// where one query in a hundred is 1,000 times as long as the others.  Such a selection says so in a word of the host's, and
+// the next kHalvesRest requests that the rule would send to the halves take the floats: a try that fails costs a few times
+// what such a request takes, so one in 1,024 is less than 1 %.  Either way returns the same.
+constexpr int64_t kHalvesRest = 1024;
+bool halves_may_tell(rtams_index *ix) {
+  if (ix->mirror->halves_failed) {
+    ix->mirror->halves_failed = 0;
+    ix->halves_rest.store(kHalvesRest, std::memory_order_relaxed);
+  }
+  int64_t left = ix->halves_rest.load(std::memory_order_relaxed);
+  while (left > 0 && !ix->halves_rest.compare_exchange_weak(left, left - 1, std::memory_order_relaxed)) {}
+  return left <= 0;
 }
 
 // Orders this call behind the previous work of the data stream.
@@ -886,7 +905,7 @@ static int search_on(rtams_index *ix, int r, int64_t nq, const float *d_queries,
   if (!small && D.halves_stride != 0) {  // (the index holds lists of floats)
     const int64_t mode = ix->scan_halves.load(std::memory_order_relaxed);
     D.scan_halves = mode == 2 || (mode == 1 && ix->scan_mfma.load(std::memory_order_relaxed) == 1 &&
-                                  halves_scan_pays(D, nq, nprobe, k, ix->ntotal_host / ix->cfg.nlist + 1, longest_list(ix)));
+                                  halves_scan_pays(D, nq, nprobe, k, ix->ntotal_host / ix->cfg.nlist + 1, longest_list(ix)) && halves_may_tell(ix));
     if (D.scan_halves) {
       const int64_t avg_len = ix->ntotal_host / ix->cfg.nlist + 1;
       if (nq * nprobe >= 16 * (int64_t)ix->cfg.nlist || longest_list(ix) >= 16 * avg_len) D.scan_halves = 2;

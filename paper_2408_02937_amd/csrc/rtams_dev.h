@@ -64,6 +64,7 @@ struct HostMirror {
   volatile int32_t error;
   volatile uint32_t exceed_lists;
   volatile int32_t search_error;
+  volatile uint32_t halves_failed;  // a query's scan of halves left more than halves are for (select.hip); the host clears it
   volatile uint32_t rearr_state;  // of the last rearrangement round: 0 done, 1 another round owed, 2 stalled for lack of a spare block
   // The two words below are written by every publication, by one thread in one store of 16 bytes; the host reads either
   // of them whole.  pool_word: (number of the last insertion call published << 32) | blocks in use after it.  The host

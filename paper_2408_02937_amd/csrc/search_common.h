@@ -620,6 +620,10 @@ inline bool narrow_scan_pays(const Dev &D, int64_t pairs, double list_bytes) {
 // 16,384 lists, even ones and hot ones) the rule is 1.3 % behind the better of the two on average, and 1.33 times at worst, never would
 // be 13 %; over 5,565 for inner products (d 24 to 1,024) 0.6 % and 1.25 times, and 7 %.  One to seven queries for squared distances stay
 // with the floats, whose scan leaves off early and scores nothing again (up to 1.6 times as slow, 1.15 times as fast on average).
+// What the rule cannot see is how much of a request lies within the halves' margin, which grows with the vectors' length beside
+// their distances (1 M x 128 as above, k 100, vectors 0.3 apart about centres of length 11; 32 / 256 queries: 76 / 81 and 161 / 120;
+// all of them 30 away from zero in every coordinate 72 / 115 and 202 / 149; queries 100 times as long 102 / 121 and 187 / 158).
+// Where it is most of the request, 800 us and more, the floats take over: halves_may_tell(), rtams.hip.
 inline bool halves_scan_pays(const Dev &D, int64_t nq, int64_t nprobe, int64_t k, int64_t avg_len, int64_t max_len) {
   const int64_t pairs = nq * nprobe;
   const double per = D.d * 4e-6, hot = (double)max_len * (nq < 10 ? (double)nq / 10.0 : 1.0);  // MB of a vector; a tenth of the queries meet the longest list

@@ -736,6 +736,7 @@ __device__ __forceinline__ void select_query(const Dev &D, int nq, int k, const 
         if (j < have && (threadIdx.x & 3u) == 0) skey[j] = key;
       }
     } else {
+      if (HALVES && n > kSurvivorCap / 2 && threadIdx.x == 0) D.mirror->halves_failed = 1u;  // (halves_may_tell, rtams.hip)
       // the records are this query's own
       uint32_t *wk = const_cast<uint32_t *>(rk);
       for (int j0 = 0; j0 < n; j0 += kTopkThreads / 4) {

@@ -192,6 +192,38 @@ def test_which_requests_read_them(metric, d, nlist, length, nq, nprobe, k, path,
     g.close()
 
 
+# Queries so far away that halves cannot tell their candidates apart: the rule leaves the next 1,024 requests to the floats, whatever they ask
+def test_halves_that_tell_nothing_get_a_rest(monkeypatch):
+    print("[case] a rest", flush=True)
+    monkeypatch.setattr(rtams, "HALVES_LEAST", 1)
+    gen = torch.Generator(DEV).manual_seed(11)
+    d, nlist, length, nq, nprobe = 128, 64, 4000, 8, 32
+    centres = torch.randn(nlist, d, device=DEV, generator=gen)
+    x = centres.repeat_interleave(length, 0) + 0.3 * torch.randn(nlist * length, d, device=DEV, generator=gen)
+    g = rtams.Index(d, nlist, "l2", 128, pool_blocks=len(x) // 128 + 2 * nlist + 8, n_resources=1, max_batch=nq, max_k=16, max_nprobe=nprobe,
+                    candidates_per_query=len(x))
+    g.set_centroids(centres)
+    g.add(x)
+    g.set_param("small_requests", 0)
+    torch.cuda.synchronize()
+    near, far = x[::31999][:nq].contiguous(), 1e3 * x[::31999][:nq].contiguous()
+
+    def search(q):
+        out = g.search(q, 10, nprobe)
+        torch.cuda.synchronize()
+        return g.request_trace(nq)[2], out
+
+    assert [search(near)[0] for _ in range(3)] == ["k_scan_halves"] * 3  # these are told apart
+    path, first = search(far)
+    assert path == "k_scan_halves" and g.request_trace(nq)[1].to(torch.int64).max() > 2048
+    path, again = search(far)
+    assert path == "k_scan"
+    same(first, again)
+    assert {search(near)[0] for _ in range(1023)} == {"k_scan"}
+    assert search(near)[0] == "k_scan_halves"
+    g.close()
+
+
 def test_timed_scans_of_halves_are_counted_as_such(monkeypatch):
     gen = torch.Generator(DEV).manual_seed(10)
     d, nlist, n = 64, 16, 5000
