@@ -153,6 +153,9 @@ int rtams_set_centroids(rtams_index *ix, const float *d_centroids, void *hip_str
  * is returned is computed from the floats as without them.  ESTATE once vectors are in. */
 size_t rtams_halves_bytes(const rtams_index *ix);
 int rtams_set_halves(rtams_index *ix, void *d_halves, size_t bytes);
+/* Gives them up: calls from here on go without, and the memory is the caller's again once the work enqueued before has run.
+ * ESTATE where there are none, or where a request that reads them was recorded into a graph, which may be launched again. */
+int rtams_drop_halves(rtams_index *ix);
 
 /* Product-quantised lists (pq_m > 0 only; the paper names IVF-PQ beside
  * IVF-Flat as a kind of list its blocks hold, without spelling it out; this is

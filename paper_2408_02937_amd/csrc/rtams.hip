@@ -287,6 +287,7 @@ struct rtams_index {
   std::atomic<int64_t> use_mfma{1};  // matrix-core filter in front of the exact coarse arithmetic
   std::atomic<int64_t> scan_mfma{1}; // flat lists: the scan's dot products on the matrix cores
   std::atomic<int64_t> scan_halves{1};     // the scan reads the halves beside float lists, where there are: 0 never, 1 when it pays, 2 whenever it can
+  std::atomic<bool> halves_recorded{false};  // a request that reads them was recorded into a graph
   std::atomic<int64_t> halves_rest{0};     // requests that the rule leaves to the floats all the same (halves_may_tell)
   std::atomic<int64_t> small_requests{1};  // small requests in three launches, without a plan (0: like all others)
   std::atomic<int64_t> scan_byte_weight{0};
@@ -744,6 +745,17 @@ int rtams_set_halves(rtams_index *ix, void *d_halves, size_t bytes) {
   return RTAMS_OK;
 }
 
+int rtams_drop_halves(rtams_index *ix) {
+  if (!ix) return fail(RTAMS_EINVAL, "NULL argument");
+  std::lock_guard<std::mutex> g(ix->data_mutex);
+  std::unique_lock<std::shared_mutex> searches(ix->fence_mutex);
+  if (!ix->dev.halves) return fail(RTAMS_ESTATE, "the index has no halves beside its lists");
+  if (ix->halves_recorded.load(std::memory_order_relaxed)) return fail(RTAMS_ESTATE, "a recorded request reads the halves");
+  ix->dev.halves = nullptr;
+  ix->dev.halves_stride = 0;
+  return RTAMS_OK;
+}
+
 int rtams_set_codebooks(rtams_index *ix, const float *d_codebooks, void *hip_stream) {
   if (!ix || !d_codebooks) return fail(RTAMS_EINVAL, "NULL argument");
   if (ix->cfg.pq_m == 0) return fail(RTAMS_ESTATE, "the index holds flat lists (pq_m is 0)");
@@ -907,6 +919,7 @@ static int search_on(rtams_index *ix, int r, int64_t nq, const float *d_queries,
     D.scan_halves = mode == 2 || (mode == 1 && ix->scan_mfma.load(std::memory_order_relaxed) == 1 &&
                                   halves_scan_pays(D, nq, nprobe, k, ix->ntotal_host / ix->cfg.nlist + 1, longest_list(ix)) && halves_may_tell(ix));
     if (D.scan_halves) {
+      if (recorded) ix->halves_recorded.store(true, std::memory_order_relaxed);
       const int64_t avg_len = ix->ntotal_host / ix->cfg.nlist + 1;
       if (nq * nprobe >= 16 * (int64_t)ix->cfg.nlist || longest_list(ix) >= 16 * avg_len) D.scan_halves = 2;
     }

@@ -32,7 +32,7 @@ SYMBOLS = [
     "rtams_poll_error", "rtams_clear_error", "rtams_last_error", "rtams_set_param", "rtams_scan_time",
     "rtams_copy_plain", "rtams_read_plain", "rtams_set_codebooks", "rtams_list_export_codes",
     "rtams_search_noalloc", "rtams_overflow_bytes_for", "rtams_scan_kernels",
-    "rtams_request_trace", "rtams_halves_bytes", "rtams_set_halves", "rtams_scans_of_halves",
+    "rtams_request_trace", "rtams_halves_bytes", "rtams_set_halves", "rtams_scans_of_halves", "rtams_drop_halves",
 ]
 
 
@@ -86,6 +86,7 @@ def lib():
         L.rtams_halves_bytes.restype = C.c_size_t
         L.rtams_halves_bytes.argtypes = [vp]
         L.rtams_set_halves.argtypes = [vp, vp, C.c_size_t]
+        L.rtams_drop_halves.argtypes = [vp]
         L.rtams_set_centroids.argtypes = [vp, vp, vp]
         L.rtams_set_codebooks.argtypes = [vp, vp, vp]
         L.rtams_list_export_codes.argtypes = [vp, i32, i64, vp, vp, C.POINTER(i64), vp]
@@ -153,7 +154,11 @@ class Index:
                  rearrange_threshold: int = 0, n_resources: int = 8, max_batch: int = 256,
                  max_k: int = 128, max_nprobe: int = 64, max_add_batch: int = 65536,
                  candidates_per_query: int = 65536, device: str = "cuda:0", pq_m: int = 0,
-                 overflow_candidates: int = 0, overflow_chunks: int = 4, storage: str = "f32"):
+                 overflow_candidates: int = 0, overflow_chunks: int = 4, storage: str = "f32",
+                 halves: Optional[bool] = None):
+        """halves: whether lists of floats get halves beside them (`halves_bytes` of device memory, half as much again as the
+        lists take), which make long searches faster and change no answer: True, False, or None for what fits easily (see
+        below).  `drop_halves()` gives the memory back."""
         L = lib()
         self.d, self.nlist, self.block_vecs, self.pq_m = d, nlist, block_vecs, pq_m
         self.metric = {"l2": L2, "ip": IP}[metric]
@@ -191,13 +196,33 @@ class Index:
         torch.cuda.synchronize(self.device)
         _chk(L.rtams_create(C.byref(cfg), C.byref(h)), "rtams_create")
         self._h = h
-        # halves beside lists of floats, for long scans to read: half as much again as the lists take, left out where that is
-        # more than a quarter of what is still free, or so little that no scan of it is long
+        # unless told otherwise: not where they are more than a quarter of what is still free, or so little that no scan of
+        # them is long
         self.halves = None
         nbytes = L.rtams_halves_bytes(h)
-        if nbytes >= HALVES_LEAST and nbytes <= torch.cuda.mem_get_info(self.device)[0] // 4:
+        if halves and not nbytes:
+            raise ValueError("this kind of index keeps no halves beside its lists (lists of floats, 16 of them or more, do)")
+        if halves is None and nbytes >= HALVES_LEAST and nbytes <= torch.cuda.mem_get_info(self.device)[0] // 4:
+            try:
+                self.halves = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+            except torch.OutOfMemoryError:  # (taken by somebody else meanwhile)
+                pass
+        elif halves:
             self.halves = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+        if self.halves is not None:
             _chk(L.rtams_set_halves(h, self.halves.data_ptr(), nbytes), "rtams_set_halves")
+
+    @property
+    def halves_bytes(self) -> int:
+        """Device memory that the halves beside the lists take; 0: there are none."""
+        return 0 if self.halves is None else self.halves.numel()
+
+    def drop_halves(self) -> None:
+        """Gives the memory of the halves back (to torch's allocator; torch.cuda.empty_cache() returns it to the device), once
+        all work enqueued on the device is done.  Answers stay what they are; long searches read the floats from here on."""
+        _chk(lib().rtams_drop_halves(self._h), "rtams_drop_halves")
+        torch.cuda.synchronize(self.device)
+        self.halves = None
 
     def close(self):
         if getattr(self, "_h", None):

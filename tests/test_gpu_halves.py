@@ -161,6 +161,9 @@ def test_recorded_requests_read_them_too(monkeypatch):
         graph.replay()
         torch.cuda.synchronize()
         same(want, (od, oi))
+    with pytest.raises(rtams.RtamsError) as e:  # the graph may be launched again
+        g.drop_halves()
+    assert e.value.code == rtams.ESTATE
     g.close()
 
 
@@ -243,6 +246,62 @@ def test_timed_scans_of_halves_are_counted_as_such(monkeypatch):
         got = g.scan_kernels(reset=True)
         assert got.pop(name) == 2 and not any(got.values()), (name, got)
     g.close()
+
+
+def test_whether_an_index_keeps_halves_is_its_callers_choice(monkeypatch):
+    print("[case] kept, declined and given back", flush=True)
+    kw = dict(block_vecs=64, pool_blocks=500, n_resources=2, max_batch=64, max_k=10, max_nprobe=8, candidates_per_query=10_000)
+    gen = torch.Generator(DEV).manual_seed(12)
+    x, q = torch.randn(10_000, 32, device=DEV, generator=gen), torch.randn(64, 32, device=DEV, generator=gen)
+
+    def filled(**more):
+        g = rtams.Index(32, 64, "l2", **kw, **more)
+        g.set_centroids(x[:64].contiguous())
+        g.add(x)
+        g.set_param("scan_halves", 2)
+        g.set_param("small_requests", 0)
+        return g
+
+    def search(g):
+        out = g.search(q, 10, 8)
+        torch.cuda.synchronize()
+        return g.request_trace(64)[2], out
+
+    with pytest.raises(ValueError):
+        rtams.Index(32, 64, "l2", **kw, storage="f16", halves=True)
+    plain = filled()
+    assert plain.halves_bytes == 0  # too few for any scan of them to be long ...
+    with pytest.raises(rtams.RtamsError) as e:
+        plain.drop_halves()
+    assert e.value.code == rtams.ESTATE
+    kept = filled(halves=True)      # ... but for whoever wants them
+    assert kept.halves_bytes == rtams.lib().rtams_halves_bytes(kept._h) > 0
+    monkeypatch.setattr(rtams, "HALVES_LEAST", 1)
+    with_rule, declined = filled(), filled(halves=False)
+    assert with_rule.halves_bytes == kept.halves_bytes and declined.halves_bytes == 0
+    path, want = search(declined)
+    assert path == "k_scan_mm"
+    same(want, search(plain)[1])
+    for g in (kept, with_rule):
+        path, got = search(g)
+        assert path == "k_scan_halves"
+        same(want, got)
+    before = torch.cuda.memory_allocated()
+    nbytes = kept.halves_bytes
+    kept.drop_halves()
+    assert kept.halves_bytes == 0 and torch.cuda.memory_allocated() <= before - nbytes
+    path, got = search(kept)
+    assert path == "k_scan_mm"
+    same(want, got)
+    more = torch.randn(3000, 32, device=DEV, generator=gen)
+    for g in (kept, with_rule):
+        g.add(more)
+        g.rearrange(-1)
+    torch.cuda.synchronize()
+    same(search(with_rule)[1], search(kept)[1])
+    kept.validate()
+    for g in (plain, kept, with_rule, declined):
+        g.close()
 
 
 def test_who_keeps_halves_and_when_they_are_taken():
