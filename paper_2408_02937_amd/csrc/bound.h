@@ -308,8 +308,7 @@ __device__ inline void make_half_query(const Dev &D, const SearchScratch &S, int
     nsq += (double)v.x * v.x + (double)v.y * v.y + (double)v.z * v.z + (double)v.w * v.w;
   }
   for (int o = kWave / 2; o > 0; o >>= 1) nsq += __shfl_xor(nsq, o);
-  // (a short query's squares are not for 32 bits: 1e-23 and shorter is nothing there, and what its halves leave out long before)
-  const float scale = nsq < 0x1p-60 ? half_piece_scale((float)(nsq * 0x1p100)) * 0x1p50f : half_piece_scale((float)nsq), inv = 1.f / scale;
+  const float scale = half_query_scale(nsq), inv = 1.f / scale;
   u32x4 *row = half_query_row(D, S, (uint32_t)q);
   double hsq = 0.0, rsq = 0.0;  // |q'|^2 and |q - q'|^2
   for (int c = lane; c < (int)half_row_units(D); c += kWave) {
@@ -336,7 +335,7 @@ __device__ inline void make_half_query(const Dev &D, const SearchScratch &S, int
     const float norm = (float)__builtin_sqrt(nsq > hsq ? nsq : hsq) * 1.00001f, left = (float)__builtin_sqrt(rsq) * 1.00001f;
     const bool exact = halves_are_floats(D);
     *reinterpret_cast<float4 *>(row + half_row_units(D)) = make_float4(exact ? -inv : inv, (float)hsq, norm, left);
-    *over_out = norm * ((exact ? 0.f : 4.9e-4f) + (float)(2 * D.d + 8) * 6.0e-8f);
+    *over_out = halves_over(norm, exact, D.d);
   }
 }
 

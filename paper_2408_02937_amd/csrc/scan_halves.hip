@@ -5,7 +5,7 @@ namespace rtams {
 
 // A long scan is bound by the bytes of the lists, and most of what it reads only says that a vector is not among the k
 // best.  Halves say that as well: the scan reads those, keeps what could come under its query's bound for all that halves
-// leave out (HalfQuery, search_common.h), and the selection scores what may be among the k best again from the floats.
+// leave out (HalfQuery, halves.h), and the selection scores what may be among the k best again from the floats.
 // v_mfma_f32_16x16x32_f16: the queries of the tile are the rows of the product and the vectors its columns; lane l supplies
 // eight coordinates of query and of vector l % 16, a 16-byte chunk of each, and holds, for vector l % 16 of a block of 16, its
 // scores against queries 4 (l / 16) .. + 3; |x'|^2 adds up on the vector unit beside it, a chunk's share to a lane.
@@ -88,7 +88,7 @@ __device__ __forceinline__ void scan_units_halves(const Dev &D, const SearchScra
   StagingOf<HalfTileQuery, kHalfStageCap> stage{S, tq, st, 0u};
   if (u0 >= it.u_end) return;  // nothing staged yet
   uint32_t quad = 0, slot = 0;
-  MfmaAcc acc[2][CB], sum[2][CB];  // products of at most 64 coordinates, and the sums of those (halves_slack, search_common.h)
+  MfmaAcc acc[2][CB], sum[2][CB];  // products of at most 64 coordinates, and the sums of those (halves_slack, halves.h)
   float sq[2];
   auto clear = [&]() {
 #pragma unroll

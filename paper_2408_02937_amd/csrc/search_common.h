@@ -372,14 +372,6 @@ __host__ __device__ inline uint32_t narrow_row_bytes(const Dev &D) {  // of a qu
   return (uint32_t)((D.vchunks + 3) / 4 * 4) * (D.storage == 1 ? 16u : 32u) + 16u;
 }
 __host__ __device__ inline bool scans_narrow(const Dev &D) { return D.scan_mfma == 2; }
-// power of two that brings a query of squared norm qn to a length of 2^13 to 2^14
-__device__ inline float half_piece_scale(float qn) {
-  if (!(qn > 0.f) || !(qn < __builtin_inff())) return 1.f;
-  const int e = (int)((__float_as_uint(qn) >> 23) & 255u) - 127;  // |q| < 2^((e + 1) / 2)
-  int s = 14 - ((e + 2) >> 1);
-  s = s > 100 ? 100 : s < -100 ? -100 : s;
-  return __uint_as_float((uint32_t)(s + 127) << 23);
-}
 __device__ inline float norm_form_slack(int d) { return 1.01f * (float)(4 * d + 8) * 5.9604645e-8f; }
 __device__ inline float loosened(float v, float slack, float qn) {
   const float r = v + slack * (2.f * fmaxf(v, 0.f) + 3.f * qn) + 1e-30f;
@@ -397,25 +389,6 @@ __device__ __host__ inline bool uses_norm_form(const Dev &D) {
   return D.scan_mfma != 0 && D.metric == 0 && D.pq_m == 0;
 }
 
-// ---- scores from the halves beside the lists.  With x' the vector and q' the query as their halves have them (u = 2^-11 the
-// unit roundoff of halves, t = 2^-14 sqrt(d) / scale what zeroed subnormals can come to, s = |q - q'| computed),
-//   |x - x'| <= u |x| + t.
-// Squared distances: | |q - x| - |q' - x'| | <= s + t + u |x|, where |x| is at most |q| plus the distance: whichever of the two
-// distances is r, the other one is at most r + 1.001 u (|q| + r) + e with e = s + 1.001 t.  The scan has |q' - x'|^2 in the
-// norm form.  Its sum of products is one of at most 64 after the other, each an addition that may be 2^-23 off, and of d / 64 such
-// sums; |x'|^2 is of lanes' sums of a quarter of the coordinates: with P >= |q'|, |x'|, all in all it is off by at most
-// halves_slack(d) P^2, and the direct form by d + 2 roundings of itself.  (The margin goes with the distance times the norm over
-// 2^11, and with the norm squared over 2^15: that of the norm form in one sum of d, which it need not be here, over 2^12 at d 256.)
-// Inner products: |<q, x> - <q', x'>| <= |x'| (s + 1.001 u |q|) + 1.001 t |q|, and the roundings of the sum of products and the d
-// of the direct one: a |x'| + e.  The scan has |x'| of every vector and keeps the least the inner product's negative can be but
-// for e, which is in the bound.
-struct HalfQuery {
-  float unscale;  // turns a product of halves into a product
-  float a;        // squared distances: |q'|^2; inner products: a as above
-  float norm;     // |q|, from above
-  float e;
-  float u;        // 1.001 2^-11, or 0 where the halves of all vectors are their floats
-};
 // Whether the halves of every vector inserted so far are its floats (then nothing is left out: u and t are zero).  Insertions
 // write the word while searches run, so a request asks once, for each query where its bound is set, behind the lengths of its
 // lists (an insertion writes the word before it publishes: "yes" holds for all that the request may see), and goes by what it wrote
@@ -435,41 +408,25 @@ __device__ inline bool halves_exact_for(const Dev &D, const SearchScratch &S, ui
 }
 __device__ inline HalfQuery half_query(const Dev &D, const SearchScratch &S, uint32_t q) {
   const float4 w = *reinterpret_cast<const float4 *>(half_query_row(D, S, q) + half_row_units(D));
-  const bool exact = w.x < 0.f;
-  const float ixs = 1.f / halves_scale(D), t = exact ? 0.f : 6.11e-5f * sqrtf((float)D.d) * ixs;  // (6.11e-5: 1.001 2^-14)
-  HalfQuery m{fabsf(w.x) * ixs, w.y, w.z, w.w + t, exact ? 0.f : 4.888e-4f};
-  if (D.metric != 0) {
-    m.a = 1.002f * (w.w + w.z * (m.u + (float)(D.d + D.d / 64 + 140) * 6.0e-8f));
-    m.e = 1.002f * t * w.z + 1e-30f;
-  }
-  return m;
+  return half_query_of(w.x, w.y, w.z, w.w, D.d, D.metric, 1.f / halves_scale(D));
 }
-
-__device__ inline float halves_slack(const Dev &D) { return (float)(2 * (128 + D.d / 64 + 1) + 16 * ((D.d + 31) / 32) + 8) * 6.0e-8f; }
 __device__ inline uint32_t halves_reach_key(const Dev &D, uint32_t key, const HalfQuery &m) {
   const float v = l2_score_of_key(key);
   if (!(v < __builtin_inff())) return 0xFFFFFFFFu;  // "keep everything", as behind a NaN
-  const float r0 = sqrtf(fmaxf(v, 0.f)), p = 1.01f * (m.norm + r0) + m.e, fp = halves_slack(D) * p * p;
-  float r = sqrtf(r0 * r0 * (1.f + (float)(D.d + 8) * 6.0e-8f) + fp) * 1.000001f;
-  r += m.u * (m.norm + r) + m.e;
-  const float w = (r * r + fp) * 1.000001f + 1e-30f;
+  const float w = halves_reach(v, D.d, m);
   return w < __builtin_inff() ? key_of_float(w) : 0xFFFFFFFFu;
 }
 __device__ inline uint32_t halves_reach_ip_key(uint32_t key, const HalfQuery &m) {
-  const float v = l2_score_of_key(key), w = v + m.e + (fabsf(v) + m.e) * 2.4e-7f;
+  const float w = halves_reach_ip(l2_score_of_key(key), m);
   return fabsf(w) < __builtin_inff() ? key_of_float(w + 0.0f) : 0xFFFFFFFFu;
 }
-// The query's bound, the k-th best score of a sample of its candidates from their halves, as one of what the scan of halves has.  Squared
-// distances: a vector is no further from the query than from what its halves hold, and u |x| + t; inner products: the sample
-// holds upper bounds but for e (sample_scores_halves).
+// The query's bound, the k-th best score of a sample of its candidates from their halves, as one of what the scan of halves has.
 __device__ inline uint32_t halves_bound_key(const Dev &D, uint32_t key, const HalfQuery &m) {
   if (key == 0xFFFFFFFFu) return key;
   if (D.metric != 0) return halves_reach_ip_key(halves_reach_ip_key(key, m), m);
   const float v = l2_score_of_key(key);
   if (!(v < __builtin_inff())) return 0xFFFFFFFFu;
-  float r = sqrtf(fmaxf(v, 0.f)) * (1.f + (float)(D.d + 8) * 6.0e-8f);
-  r += m.u * (m.norm + r) + m.e;
-  return halves_reach_key(D, key_of_float(r * r * 1.000001f), m);
+  return halves_reach_key(D, key_of_float(halves_sampled(v, D.d, m)), m);
 }
 // A vector or query whose halves are not finite says nothing: it is kept, and its query's flag, behind its counter of records, has
 // the selection score all of the records again.
