@@ -64,7 +64,11 @@ def test_no_kernel_keeps_private_memory(records):
 # The scan: four wavefronts to a SIMD in short scans but of inner products of floats, three elsewhere (LDS by the tile).
 @pytest.mark.parametrize("name,count,waves,groups,lds", [
     ("8k_select", 3, 8, 2, 0),
+    ("15k_select_halves", 3, 8, 2, 0),
     ("7k_group", 1, 8, 2, 0),
+    ("13k_plan_halves", 1, 8, 2, 0),
+    ("13k_scan_halves", 4, 4, 6, 26368),            # steps, staging, and 16 queries of 96 dimensions
+    ("13k_scan_halves", 4, 4, 4, 40320),            # 32 of 256
     ("9k_pq_scan", 1, 8, 4, 16 * 1024),             # 16 codes to a vector
     ("10k_pq_bound", 1, 16, 1, 64 * 1024),          # 64
     ("13k_coarse_mfmaILi4", 2, 4, 2, 3 * 384 * 64),
