@@ -791,9 +791,12 @@ void launch_select(const Dev &D, int64_t nq, int k, const float *Q, const Search
                    hipStream_t s) {
   if (nq <= 0) return;
   if (D.scan_halves) {
-    // as many to a query as give every compute unit a workgroup: each reads all of the query's records, so twice as many
-    // cost more than they bring (256 queries over 20 M x 256, skewed 174 / 206 us, 64 over 5 M x 768 73 / 77)
-    const int64_t parts = std::min<int64_t>((kComputeUnits + nq - 1) / nq, kSelectParts);
+    // as many to a query as give no compute unit two workgroups: each reads all of the query's records, so twice as many
+    // cost more than they bring (256 queries over 20 M x 256, skewed 174 / 206 us, 64 over 5 M x 768 73 / 77).  Whole requests
+    // whose finalists are shared, k 100 to 128 of 64 probes, over 1 M x 256, 500 k x 768 and 200 k x 1,536, both metrics: at 32 to
+    // 128 queries half as many 1.02 times as long on average (up to 1.09), twice as many 1.06 (1.19), four times 1.26; one more
+    // than fits, for a number that does not divide (40 to 240 queries), 1.06 (1.14).  Of 32 queries and fewer eight workgroups are as good as 16.
+    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(kComputeUnits / nq, kSelectParts));
     const auto kernel = D.metric != 0 ? k_select_halves<1, true> : D.scan_mfma ? k_select_halves<0, false> : k_select_halves<0, true>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(nq * parts)), dim3(kTopkThreads), 0, s, D, (int)nq, k, Q, S, out_dist, out_ids);
     return;

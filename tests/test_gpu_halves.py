@@ -80,7 +80,7 @@ def test_the_same_bits_as_the_floats_alone(metric, d, nlist, block_vecs, nq, npr
 
 # finalists by the thousand and queries whose workgroups share them; vectors that no half can tell apart
 @pytest.mark.parametrize("metric", ["l2", "ip"])
-@pytest.mark.parametrize("spread,nq,k", [(0.1, 8, 50), (0.1, 130, 100), (1e-4, 8, 10), (0.0, 24, 300)])
+@pytest.mark.parametrize("spread,nq,k", [(0.1, 8, 50), (0.1, 128, 100), (0.1, 130, 100), (1e-4, 8, 10), (0.0, 24, 300)])
 def test_shared_and_many_finalists(metric, spread, nq, k, monkeypatch):
     print(f"[case] finalists {metric}, spread {spread}, {nq} queries, k {k}", flush=True)
     gen = torch.Generator(DEV).manual_seed(nq)
