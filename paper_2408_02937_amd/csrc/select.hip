@@ -110,7 +110,11 @@ __device__ __forceinline__ int select_topk(int count, int k, KeyFn key, ItemFn i
 
 constexpr int kTopkThreads = 512;
 constexpr int kSelectParts = 8;  // workgroups that share a query's finalists, at most
-constexpr int64_t kSharedWork = 32768;  // ... where its records come to so many chunks of four coordinates
+// ... where its records come to so many chunks of four coordinates.  Whole requests of 1 to 128 queries, d 32 to 1,536, one
+// workgroup / several: below 5,000 several are 1.03 times as long on average (up to 1.07), at 7,000 to 11,000 1.01, at 13,000 to
+// 16,000 0.95 by squared distances and 1.01 by inner products, at 25,000 to 28,000 0.92 and 0.98, above 50,000 0.88 and 0.96
+// (one query by inner products 1.02: two turns of a chain each)
+constexpr int64_t kSharedWork = 16384;
 
 __device__ inline float score_of_key(uint32_t key, int metric) {
   const float x = __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
