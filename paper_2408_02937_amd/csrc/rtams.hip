@@ -920,8 +920,7 @@ static int search_on(rtams_index *ix, int r, int64_t nq, const float *d_queries,
                                   halves_scan_pays(D, nq, nprobe, k, ix->ntotal_host / ix->cfg.nlist + 1, longest_list(ix)) && halves_may_tell(ix));
     if (D.scan_halves) {
       if (recorded) ix->halves_recorded.store(true, std::memory_order_relaxed);
-      const int64_t avg_len = ix->ntotal_host / ix->cfg.nlist + 1;
-      if (nq * nprobe >= 16 * (int64_t)ix->cfg.nlist || longest_list(ix) >= 16 * avg_len) D.scan_halves = 2;
+      if (wide_half_tiles_pay(D, nq, nprobe, ix->ntotal_host, longest_list(ix))) D.scan_halves = 2;
     }
   }
   ix->res[r].path = D.pq_m > 0 ? 4 : D.scan_halves ? 5 : D.scan_mfma ? 1 + D.scan_mfma : small ? 1 : 0;

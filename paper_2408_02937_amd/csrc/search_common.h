@@ -590,6 +590,19 @@ inline bool halves_scan_pays(const Dev &D, int64_t nq, int64_t nprobe, int64_t k
   return nq >= 8 && lists + 0.2 * (double)nq * ((double)(nprobe * avg_len) + (double)max_len / 10.0) * per >= 100.0 + 0.2 * D.d + 60.0 * again;
 }
 
+// Whether a scan of halves has tiles of 32 queries instead of 16: half the passes over a list that so many meet, and a workgroup
+// less on a compute unit.  Whole requests, tiles of 16 / 32, us: even lists, 16 pairs to each 110 / 109 (1 M x 128), 97 / 92 (2 M x
+// 32), 332 / 274 (400 k x 768; inner products 282 / 286), 32 pairs 130 / 119, 118 / 103, 374 / 326, 64 pairs 367 / 263; but 8 pairs
+// 115 / 116, 89 / 85, 244 / 254.  One hot list: the pairs that make a second tile of 16 are its own, and what it costs is paid by
+// all others; by squared distances, 256 queries, 20 M x 256 in 16,384 lists of a Zipf law 1,809 / 1,658, 20 M x 96 in 4,096 1,029 / 942,
+// 6 M x 256 in 1,024 980 / 851, where the list meets 24 queries or fewer 1.01 times as long (up to 1.10); but where the others are short,
+// 12 M and 6 M x 256 in 16,384 lists, 1,093 / 1,179 and 663 / 704; wide, 6 M x 768 in 8,192, 2,514 / 2,591; or by inner
+// products 12 M x 256 in 16,384 1,626 / 2,166, 6 M x 768 2,847 / 2,924.
+inline bool wide_half_tiles_pay(const Dev &D, int64_t nq, int64_t nprobe, int64_t ntotal, int64_t longest) {
+  if (nq * nprobe >= 16 * (int64_t)D.nlist) return true;
+  return D.metric == 0 && D.d <= 256 && ntotal >= 1024 * (int64_t)D.nlist && nq * longest >= 24 * ntotal;
+}
+
 inline ScanShape scan_shape(const Dev &D, int item_budget) {
   ScanShape sh{};
   sh.mm = (D.scan_mfma != 0 || D.scan_halves != 0) && D.pq_m == 0;
