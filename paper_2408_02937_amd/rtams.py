@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import weakref
 from typing import Optional, Tuple
 
 import torch
@@ -146,6 +147,26 @@ def read_plain(src: torch.Tensor, sink: torch.Tensor, stream=None) -> None:
     _chk(lib().rtams_read_plain(src.data_ptr(), nbytes, sink.data_ptr(), _stream_ptr(stream)), "rtams_read_plain")
 
 
+_halves_by_rule = weakref.WeakSet()  # indexes with halves that nobody asked for
+
+
+def _device_bytes(nbytes: int, device: torch.device) -> torch.Tensor:
+    """Device memory; where there is none left, halves that nobody asked for make room."""
+    try:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        kept = [ix for ix in list(_halves_by_rule) if ix.device == device]
+        if not kept:
+            raise
+    for ix in kept:
+        try:
+            ix.drop_halves()
+        except RtamsError:  # (a recorded request reads them)
+            pass
+    torch.cuda.empty_cache()
+    return torch.empty(nbytes, dtype=torch.uint8, device=device)
+
+
 class Index:
     """rtams_index over a pool and a scratch tensor that this object keeps alive."""
 
@@ -158,7 +179,7 @@ class Index:
                  halves: Optional[bool] = None):
         """halves: whether lists of floats get halves beside them (`halves_bytes` of device memory, half as much again as the
         lists take), which make long searches faster and change no answer: True, False, or None for what fits easily (see
-        below).  `drop_halves()` gives the memory back."""
+        below), and goes when a later Index finds no memory left.  `drop_halves()` gives the memory back."""
         L = lib()
         self.d, self.nlist, self.block_vecs, self.pq_m = d, nlist, block_vecs, pq_m
         self.metric = {"l2": L2, "ip": IP}[metric]
@@ -178,7 +199,7 @@ class Index:
         if per_res == 0:
             raise RtamsError(EINVAL, "scratch_bytes_for", L.rtams_last_error().decode())
         # caller-owned device memory: one pool, one scratch area
-        self.pool = torch.empty(pool_bytes, dtype=torch.uint8, device=self.device)
+        self.pool = _device_bytes(pool_bytes, self.device)
         # the reserve shared by all resources: overflow_chunks chunks of overflow_candidates entries
         overflow_bytes = 0
         if overflow_candidates > 0:
@@ -186,7 +207,7 @@ class Index:
             if overflow_bytes == 0:
                 raise RtamsError(EINVAL, "overflow_bytes_for", "overflow_chunks must be in 1..32")
         scratch_bytes = per_res * n_resources + overflow_bytes
-        self.scratch = torch.empty(scratch_bytes, dtype=torch.uint8, device=self.device)
+        self.scratch = _device_bytes(scratch_bytes, self.device)
         cfg.d_pool, cfg.pool_bytes = self.pool.data_ptr(), pool_bytes
         cfg.d_scratch, cfg.scratch_bytes = self.scratch.data_ptr(), scratch_bytes
         cfg.overflow_bytes = overflow_bytes
@@ -205,10 +226,11 @@ class Index:
         if halves is None and nbytes >= HALVES_LEAST and nbytes <= torch.cuda.mem_get_info(self.device)[0] // 4:
             try:
                 self.halves = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+                _halves_by_rule.add(self)
             except torch.OutOfMemoryError:  # (taken by somebody else meanwhile)
                 pass
         elif halves:
-            self.halves = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+            self.halves = _device_bytes(nbytes, self.device)
         if self.halves is not None:
             _chk(L.rtams_set_halves(h, self.halves.data_ptr(), nbytes), "rtams_set_halves")
 
@@ -223,11 +245,13 @@ class Index:
         _chk(lib().rtams_drop_halves(self._h), "rtams_drop_halves")
         torch.cuda.synchronize(self.device)
         self.halves = None
+        _halves_by_rule.discard(self)
 
     def close(self):
         if getattr(self, "_h", None):
             lib().rtams_destroy(self._h)
             self._h = None
+            _halves_by_rule.discard(self)
 
     def __del__(self):
         try:

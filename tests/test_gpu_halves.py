@@ -304,6 +304,54 @@ def test_whether_an_index_keeps_halves_is_its_callers_choice(monkeypatch):
         g.close()
 
 
+# (the allocation that fails is made to: nothing here fills the device)
+def test_halves_that_nobody_asked_for_make_room_for_an_index(monkeypatch):
+    print("[case] room for an index", flush=True)
+    monkeypatch.setattr(rtams, "HALVES_LEAST", 1)
+    kw = dict(block_vecs=64, pool_blocks=500, n_resources=2, max_batch=64, max_k=10, max_nprobe=8, candidates_per_query=10_000)
+    gen = torch.Generator(DEV).manual_seed(13)
+    x = torch.randn(10_000, 32, device=DEV, generator=gen)
+    q = x[:64].contiguous()
+
+    def filled(**more):
+        g = rtams.Index(32, 64, "l2", **kw, **more)
+        g.set_centroids(x[:64].contiguous())
+        g.add(x)
+        g.set_param("scan_halves", 2)
+        g.set_param("small_requests", 0)
+        torch.cuda.synchronize()
+        return g
+
+    by_rule, asked = filled(), filled(halves=True)
+    recorded = filled()
+    od, oi = torch.empty(64, 10, device=DEV), torch.empty(64, 10, dtype=torch.int64, device=DEV)
+    recorded.search(q, 10, 8)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        recorded.search(q, 10, 8, od, oi)
+    want = by_rule.search(q, 10, 8)
+    torch.cuda.synchronize()
+    real, failed = torch.empty, []
+
+    def empty(*a, **k):
+        if k.get("dtype") is torch.uint8 and not failed:
+            failed.append(a)
+            raise torch.OutOfMemoryError("no memory left")
+        return real(*a, **k)
+
+    monkeypatch.setattr(rtams.torch, "empty", empty)
+    g = rtams.Index(32, 64, "l2", **kw, halves=False)
+    monkeypatch.setattr(rtams.torch, "empty", real)
+    assert failed and by_rule.halves_bytes == 0 and asked.halves_bytes > 0 and recorded.halves_bytes > 0 and g.halves_bytes == 0
+    same(want, by_rule.search(q, 10, 8))
+    graph.replay()
+    torch.cuda.synchronize()
+    same(want, (od, oi))
+    for ix in (by_rule, asked, recorded, g):
+        ix.close()
+
+
 def test_who_keeps_halves_and_when_they_are_taken():
     L = rtams.lib()
     kinds = {"f32": (64, {}), "16 lists": (16, {}), "15 lists": (15, {}), "f16": (64, dict(storage="f16")), "u8": (64, dict(storage="u8")), "pq": (64, dict(pq_m=8))}
